@@ -15,7 +15,7 @@
 // Storing the raw scores of every query instead (one pass) would write and re-read
 // W * Hq * len * 4 bytes: more than the second pass over K from W = 8 on at the usual shapes.
 //
-// Per tile of 32 rows the scores of all columns come from the matrix cores
+// Per tile of 64 rows the scores of all columns come from the matrix cores
 // (v_mfma_f32_16x16x32_bf16, K rows as the 16-row operand straight from global memory in
 // operand layout; the queries, 16 columns at a time, from LDS).  Column c = i * Gp + gi: query
 // i of the window, head gi of the GQA group, Gp = G rounded up to a power of two so that a lane
@@ -42,7 +42,9 @@ struct WindowParams {
     const int32_t* pred; int32_t pred_val;
 };
 
-constexpr int kWinWaves = 4, kWinRows = 32;
+constexpr int kWinWaves = 8, kWinTiles = 4, kWinRows = 16 * kWinTiles;     // rows per wavefront and step: 64
+constexpr int kWinThreads = kWinWaves * 64;
+constexpr int kWinTargetWgs = 512;     // workgroups a pass aims for: two per CU
 constexpr int kQStride = kD + 8;       // bf16 elements between columns in LDS: 272 bytes, conflict-free 16-byte reads
 
 __device__ __forceinline__ int window_workgroups(int n_rows, int nch) {
@@ -56,23 +58,35 @@ __device__ __forceinline__ int column_limit(const WindowParams& p, int col, int 
     return (i < p.W && gi < p.G && pos >= 0) ? pos : -1;
 }
 
-// The window's queries of KV head g into LDS, one column per (query, head), zero where none.
-__device__ __forceinline__ void stage_queries(const WindowParams& p, int b, int g, int n, int ncol, uint16_t* sQ) {
-    for (int x = threadIdx.x; x < ncol * 16; x += blockDim.x) {
-        const int col = x >> 4, piece = x & 15;
-        uint4 u = make_uint4(0, 0, 0, 0);
-        if (column_limit(p, col, n) >= 0) {
-            const int i = col >> p.gp_shift, gi = col & ((1 << p.gp_shift) - 1);
-            u = *reinterpret_cast<const uint4*>(p.q + (((int64_t)b * p.W + i) * p.Hq + (int64_t)g * p.G + gi) * kD + piece * 8);
-        }
-        *reinterpret_cast<uint4*>(sQ + col * kQStride + piece * 8) = u;
-    }
+// The window's queries of KV head g go to LDS, one column per (query, head), zero where none, 16 pieces of
+// 16 bytes per column.  In two parts, request and store, so that the request can go out ahead of the first rows'
+// (memory answers a wavefront in the order of its requests) and nobody waits for rows to have the queries:
+// the request holds the first kQHeld pieces of a thread (128 columns in all), a wider window's rest is
+// copied by the store.
+constexpr int kQHeld = 4;
+__device__ __forceinline__ uint4 query_piece(const WindowParams& p, int b, int g, int n, int x) {
+    const int col = x >> 4, piece = x & 15;
+    if (column_limit(p, col, n) < 0) return make_uint4(0, 0, 0, 0);
+    const int i = col >> p.gp_shift, gi = col & ((1 << p.gp_shift) - 1);
+    return *reinterpret_cast<const uint4*>(p.q + (((int64_t)b * p.W + i) * p.Hq + (int64_t)g * p.G + gi) * kD + piece * 8);
+}
+__device__ __forceinline__ void request_queries(const WindowParams& p, int b, int g, int n, uint4 (&held)[kQHeld]) {
+#pragma unroll
+    for (int u = 0; u < kQHeld; ++u) held[u] = query_piece(p, b, g, n, u * kWinThreads + threadIdx.x);
+}
+__device__ __forceinline__ void store_queries(const WindowParams& p, int b, int g, int n, int ncol, const uint4 (&held)[kQHeld],
+                                              uint16_t* sQ) {
+    auto put = [&](int x, const uint4 u) { *reinterpret_cast<uint4*>(sQ + (x >> 4) * kQStride + (x & 15) * 8) = u; };
+#pragma unroll
+    for (int u = 0; u < kQHeld; ++u)
+        if (u * kWinThreads + (int)threadIdx.x < ncol * 16) put(u * kWinThreads + threadIdx.x, held[u]);
+    for (int x = kQHeld * kWinThreads + threadIdx.x; x < ncol * 16; x += kWinThreads) put(x, query_piece(p, b, g, n, x));
 }
 
-// Rows r .. r + 31 of K in operand layout (rows past the end repeat the last row; masked later).
-__device__ __forceinline__ void load_k_tile(u32x4 (&dst)[2][4], const uint16_t* kb, int r, int n16, int n) {
+// Rows r .. r + 63 of K in operand layout (rows past the end repeat the last row; masked later).
+__device__ __forceinline__ void load_k_rows(u32x4 (&dst)[kWinTiles][4], const uint16_t* kb, int r, int n16, int n) {
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
+    for (int t = 0; t < kWinTiles; ++t) {
         const int row = min(r + t * 16 + n16, n - 1);
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk)
@@ -80,22 +94,24 @@ __device__ __forceinline__ void load_k_tile(u32x4 (&dst)[2][4], const uint16_t* 
     }
 }
 
-// Scores of one tile against the 16 columns of block cb: s[t][i] is row r + 16 t + 4 c4 + i of
-// column cb * 16 + n16, scaled, -inf beyond `limit`.
-__device__ __forceinline__ void tile_scores(const u32x4 (&k)[2][4], const uint16_t* sQ, int cb, int n16, int c4,
-                                            int r, int limit, float scale, float (&s)[2][4]) {
+// Scores of these rows against the 16 columns of block cb: s[t][i] is row r + 16 t + 4 c4 + i of
+// column cb * 16 + n16, scaled; MASKED: -inf beyond `limit`.
+template <bool MASKED>
+__device__ __forceinline__ void block_scores(const u32x4 (&k)[kWinTiles][4], const uint16_t* sQ, int cb, int n16, int c4,
+                                             int r, int limit, float scale, float (&s)[kWinTiles][4]) {
     bf16x8 qa[4];
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk)
         qa[kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(sQ + (cb * 16 + n16) * kQStride + (kk * 4 + c4) * 8));
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
+    for (int t = 0; t < kWinTiles; ++t) {
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk)
             acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, k[t][kk]), qa[kk], acc, 0, 0, 0);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) s[t][i] = (r + t * 16 + 4 * c4 + i <= limit) ? acc[i] * scale : -INFINITY;
+        for (int i = 0; i < 4; ++i)
+            s[t][i] = (!MASKED || r + t * 16 + 4 * c4 + i <= limit) ? acc[i] * scale : -INFINITY;
     }
 }
 
@@ -110,12 +126,44 @@ __device__ __forceinline__ void merge_ml(float& m, float& l, float m2, float l2)
 
 extern __shared__ __attribute__((aligned(16))) unsigned char window_lds[];
 
+// Both passes: a wavefront takes 64 rows at a time and goes through the blocks of columns with them in
+// registers, so that a block's queries are read from LDS, and its running state is updated, once per 64
+// rows; eight wavefronts share one copy of the queries, and two such workgroups per CU (four wavefronts
+// per SIMD, up to 128 columns) hide one another's chains; the rows are requested behind the queries and before
+// anything waits, so at 32768 rows of 8 KV heads all of K is in flight at once.  The causal masks are worked out only for rows
+// that some query does not see.  Bound: the vector instructions of 8 exponentials per 32 x 16 scores from about 16
+// queries on, memory below.  Measured at 32 heads over 8,
+// 32768 rows: 32 queries 41.7 + 26.7 -> 25.1 + 20.8 us (32-row tiles, 4 wavefronts per workgroup before), 1 query
+// 16.8 + 15.5 us (67 MB: 4.2 TB/s); 131072 rows, 32 queries 65.7 + 60.3 us.  The queries requested behind the rows
+// instead of before them: 27.3 + 23.9 us.
+//
 // Pass 1.  The running (max, sum) of a lane's column in every block lives in LDS (one float2 per
 // lane and block), so that the number of blocks is a run-time value and the register count does
 // not grow with the window.
-__global__ __launch_bounds__(kWinWaves * 64)
+template <bool MASKED>
+__device__ __forceinline__ void lse_rows(const WindowParams& p, const u32x4 (&k)[kWinTiles][4], const uint16_t* sQ,
+                                         float2* sRun, int r, int n, bool first) {
+    const int lane = threadIdx.x & 63, n16 = lane & 15, c4 = lane >> 4;
+#pragma unroll 1
+    for (int cb = 0; cb < p.ncb; ++cb) {
+        float s[kWinTiles][4];
+        block_scores<MASKED>(k, sQ, cb, n16, c4, r, MASKED ? column_limit(p, cb * 16 + n16, n) : 0, p.scale, s);
+        float mx = s[0][0];
+#pragma unroll
+        for (int e = 1; e < 4 * kWinTiles; ++e) mx = fmaxf(mx, s[e >> 2][e & 3]);
+        const float2 run = first ? make_float2(-INFINITY, 0.f) : sRun[cb * kWinThreads + threadIdx.x];
+        const float m_new = fmaxf(run.x, mx);
+        const float ref = m_new == -INFINITY ? 0.f : m_new;      // nothing seen yet: every term is 2^-inf = 0
+        float ps = 0.f;
+#pragma unroll
+        for (int e = 0; e < 4 * kWinTiles; ++e) ps += fast_exp2((s[e >> 2][e & 3] - ref) * kLog2e);
+        sRun[cb * kWinThreads + threadIdx.x] = make_float2(m_new, run.y * fast_exp2((run.x - ref) * kLog2e) + ps);
+    }
+}
+
+__global__ __launch_bounds__(kWinThreads, 4)
 void window_lse_kernel(const WindowParams p) {
-    constexpr int NW = kWinWaves, NT = kWinWaves * 64;
+    constexpr int NW = kWinWaves;
     const int ncb = p.ncb, ncol = ncb * 16;
     const int c = blockIdx.x, g = blockIdx.y, b = blockIdx.z;
     if (p.pred != nullptr && p.pred[b] != p.pred_val) return;
@@ -124,64 +172,41 @@ void window_lse_kernel(const WindowParams p) {
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int n16 = lane & 15, c4 = lane >> 4;
     uint16_t* sQ = reinterpret_cast<uint16_t*>(window_lds);
-    float2* sRun = reinterpret_cast<float2*>(window_lds + (size_t)ncol * kQStride * 2);   // [ncb][NT]
-    float* sM = reinterpret_cast<float*>(sRun + (size_t)ncb * NT);                        // [NW][ncol]
-    float* sL = sM + NW * ncol;
-    stage_queries(p, b, g, n, ncol, sQ);
-    for (int cb = 0; cb < ncb; ++cb) sRun[cb * NT + tid] = make_float2(-INFINITY, 0.f);
-    __syncthreads();
+    float2* sRun = reinterpret_cast<float2*>(window_lds + (size_t)ncol * kQStride * 2);   // [ncb][kWinThreads]
 
     const uint16_t* kb = p.k + (int64_t)b * p.s_b + (int64_t)g * p.s_h + c4 * 8;
-    const int step = p.nch * NW * kWinRows;
-    u32x4 kA[2][4], kB[2][4];
-    auto tile = [&](const u32x4 (&k)[2][4], int r) {
-#pragma unroll 1
-        for (int cb = 0; cb < ncb; ++cb) {
-            float s[2][4];
-            tile_scores(k, sQ, cb, n16, c4, r, column_limit(p, cb * 16 + n16, n), p.scale, s);
-            const float mx = fmaxf(fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3])),
-                                   fmaxf(fmaxf(s[1][0], s[1][1]), fmaxf(s[1][2], s[1][3])));
-            const float2 run = sRun[cb * NT + tid];
-            const float m_new = fmaxf(run.x, mx);
-            if (m_new != -INFINITY) {
-                float ps = 0.f;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) ps += fast_exp2((s[e >> 2][e & 3] - m_new) * kLog2e);
-                sRun[cb * NT + tid] = make_float2(m_new, run.y * fast_exp2((run.x - m_new) * kLog2e) + ps);
-            }
-        }
-    };
-    int r = (c * NW + w) * kWinRows;
-    if (r < n) load_k_tile(kA, kb, r, n16, n);
-    if (r + step < n) load_k_tile(kB, kb, r + step, n16, n);
-    while (r < n) {
-        tile(kA, r);
-        if (r + 2 * step < n) load_k_tile(kA, kb, r + 2 * step, n16, n);
-        r += step;
-        if (r >= n) break;
-        tile(kB, r);
-        if (r + 2 * step < n) load_k_tile(kB, kb, r + 2 * step, n16, n);
-        r += step;
+    const int step = p.nch * NW * kWinRows, r0 = (c * NW + w) * kWinRows;
+    uint4 held[kQHeld];
+    u32x4 k[kWinTiles][4];
+    request_queries(p, b, g, n, held);
+    if (r0 < n) load_k_rows(k, kb, r0, n16, n);
+    store_queries(p, b, g, n, ncol, held, sQ);
+    __syncthreads();
+    for (int r = r0; r < n; r += step) {
+        if (r != r0) load_k_rows(k, kb, r, n16, n);
+        if (r + kWinRows > n - p.W) lse_rows<true>(p, k, sQ, sRun, r, n, r == r0);
+        else                        lse_rows<false>(p, k, sQ, sRun, r, n, r == r0);
     }
-    // fold the four row groups of the wavefront, then the wavefronts
+    // fold the four row groups of the wavefront, then the wavefronts (through the LDS of the queries)
+    __syncthreads();
+    float* sM = reinterpret_cast<float*>(window_lds);                // [NW][ncol]
+    float* sL = sM + NW * ncol;
+    static_assert(2 * NW * sizeof(float) <= kQStride * sizeof(uint16_t), "the wavefronts' pairs fit where the queries were");
     for (int cb = 0; cb < ncb; ++cb) {
-        const float2 run = sRun[cb * NT + tid];
-        float m = run.x, l = run.y;
-#pragma unroll
-        for (int x = 16; x < 64; x <<= 1) {
-            const float m2 = __shfl_xor(m, x), l2 = __shfl_xor(l, x);
-            merge_ml(m, l, m2, l2);
-        }
-        if (c4 == 0) { sM[w * ncol + cb * 16 + n16] = m; sL[w * ncol + cb * 16 + n16] = l; }
+        const float2 run = r0 < n ? sRun[cb * kWinThreads + tid] : make_float2(-INFINITY, 0.f);
+        const float M = max_xor32(max_xor16(run.x));
+        const float a = run.x == -INFINITY ? 0.f : fast_exp2((run.x - M) * kLog2e);
+        const float L = sum_xor32(sum_xor16(run.y * a));
+        if (c4 == 0) { sM[w * ncol + cb * 16 + n16] = M; sL[w * ncol + cb * 16 + n16] = L; }
     }
     __syncthreads();
     const int64_t bg = (int64_t)b * p.Hkv + g;
     float* part = p.part + ((bg * p.nch + c) * ncol) * 2;
-    for (int col = tid; col < ncol; col += NT) {
-        float m = sM[col], l = sL[col];
+    for (int col = tid; col < ncol; col += kWinThreads) {
+        float M = sM[col], L = sL[col];
 #pragma unroll
-        for (int ww = 1; ww < NW; ++ww) merge_ml(m, l, sM[ww * ncol + col], sL[ww * ncol + col]);
-        *reinterpret_cast<float2*>(part + col * 2) = make_float2(m, l);
+        for (int ww = 1; ww < NW; ++ww) merge_ml(M, L, sM[ww * ncol + col], sL[ww * ncol + col]);
+        *reinterpret_cast<float2*>(part + col * 2) = make_float2(M, L);
     }
 }
 
@@ -224,7 +249,7 @@ void window_lse_merge_kernel(const WindowParams p) {
         for (int x = 0; x < 16; ++x)
             if (sM[x][n16] != -INFINITY) L += (double)fast_exp2((sM[x][n16] - M) * kLog2e) * (double)sL[x][n16];
         float hi = INFINITY, lo = 0.f;                     // a column nobody votes in: e^{s - inf} = 0
-        if (M != -INFINITY) {
+        if (M != -INFINITY && column_limit(p, col, n) >= 0) {      // (a column that does not exist was summed like the others)
             const double lse = (double)M + log(L);
             hi = (float)lse; lo = (float)(lse - (double)hi);
         }
@@ -232,11 +257,55 @@ void window_lse_merge_kernel(const WindowParams p) {
     }
 }
 
+// Sum over the lanes of a row of 16 that hold the same head (lane % gp), on the DPP operand path.
+__device__ __forceinline__ float sum_queries(float v, int gp) {
+    if (gp <= 8) v += dpp_move_f<kDppRor8>(v);
+    if (gp <= 4) v += dpp_move_f<kDppRor4>(v);
+    if (gp <= 2) v += dpp_move_f<kDppXor2>(v);
+    if (gp <= 1) v += dpp_move_f<kDppXor1>(v);
+    return v;
+}
+
 // Pass 2.
-__global__ __launch_bounds__(kWinWaves * 64)
+template <bool MASKED>
+__device__ __forceinline__ void vote_rows(const WindowParams& p, const u32x4 (&k)[kWinTiles][4], const uint16_t* sQ,
+                                          const float2* sLse, float* vrow, int r, int n) {
+    const int lane = threadIdx.x & 63, n16 = lane & 15, c4 = lane >> 4;
+    float v[kWinTiles][4];
+#pragma unroll
+    for (int e = 0; e < 4 * kWinTiles; ++e) v[e >> 2][e & 3] = 0.f;
+#pragma unroll 1
+    for (int cb = 0; cb < p.ncb; ++cb) {
+        float s[kWinTiles][4];
+        block_scores<MASKED>(k, sQ, cb, n16, c4, r, MASKED ? column_limit(p, cb * 16 + n16, n) : 0, p.scale, s);
+        const float2 lse = sLse[cb * 16 + n16];
+#pragma unroll
+        for (int e = 0; e < 4 * kWinTiles; ++e)            // s = -inf (masked) and lse = inf (no such column) give 2^-inf = 0
+            v[e >> 2][e & 3] += fast_exp2(((s[e >> 2][e & 3] - lse.x) - lse.y) * kLog2e);
+    }
+    // lanes n16, n16 + Gp, n16 + 2 Gp ... hold the same head for different queries
+    const int gp = 1 << p.gp_shift;
+#pragma unroll
+    for (int e = 0; e < 4 * kWinTiles; ++e) v[e >> 2][e & 3] = sum_queries(v[e >> 2][e & 3], gp);
+    if (n16 < p.G) {
+#pragma unroll
+        for (int t = 0; t < kWinTiles; ++t) {
+            const int first = r + t * 16 + 4 * c4;
+            if (p.v_vec && first + 4 <= n) {
+                *reinterpret_cast<float4*>(vrow + first) = make_float4(v[t][0], v[t][1], v[t][2], v[t][3]);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (first + i < n) vrow[first + i] = v[t][i];
+            }
+        }
+    }
+}
+
+__global__ __launch_bounds__(kWinThreads, 4)
 void window_vote_kernel(const WindowParams p) {
     constexpr int NW = kWinWaves;
-    const int ncb = p.ncb, NCOL = ncb * 16;
+    const int ncol = p.ncb * 16;
     const int c = blockIdx.x, g = blockIdx.y, b = blockIdx.z;
     if (p.pred != nullptr && p.pred[b] != p.pred_val) return;
     const int n = min(max(min(p.seq_lens[b], p.cap), 0), p.max_rows);
@@ -244,66 +313,31 @@ void window_vote_kernel(const WindowParams p) {
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int n16 = lane & 15, c4 = lane >> 4;
     uint16_t* sQ = reinterpret_cast<uint16_t*>(window_lds);
-    float2* sLse = reinterpret_cast<float2*>(window_lds + (size_t)NCOL * kQStride * 2);   // [NCOL]
+    float2* sLse = reinterpret_cast<float2*>(window_lds + (size_t)ncol * kQStride * 2);   // [ncol]
     const int64_t bg = (int64_t)b * p.Hkv + g;
-    stage_queries(p, b, g, n, NCOL, sQ);
-    for (int col = tid; col < NCOL; col += NW * 64) sLse[col] = *reinterpret_cast<const float2*>(p.lse + (bg * NCOL + col) * 2);
-    __syncthreads();
 
     const uint16_t* kb = p.k + (int64_t)b * p.s_b + (int64_t)g * p.s_h + c4 * 8;
-    const int step = p.nch * NW * kWinRows;
-    const int gp = 1 << p.gp_shift;
+    const int step = p.nch * NW * kWinRows, r0 = (c * NW + w) * kWinRows;
+    uint4 held[kQHeld];
+    u32x4 k[kWinTiles][4];
+    const float2* lse_of = reinterpret_cast<const float2*>(p.lse) + bg * ncol;
+    const float2 my_lse = tid < ncol ? lse_of[tid] : make_float2(0.f, 0.f);      // (at most 256 columns)
+    request_queries(p, b, g, n, held);
+    if (r0 < n) load_k_rows(k, kb, r0, n16, n);
+    store_queries(p, b, g, n, ncol, held, sQ);
+    if (tid < ncol) sLse[tid] = my_lse;
+    __syncthreads();
     float* vrow = p.votes + ((int64_t)b * p.Hq + (int64_t)g * p.G + (n16 < p.G ? n16 : 0)) * p.v_stride;
-
-    u32x4 kA[2][4], kB[2][4];
-    auto tile = [&](const u32x4 (&k)[2][4], int r) {
-        float v[2][4] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-#pragma unroll 1
-        for (int cb = 0; cb < ncb; ++cb) {
-            float s[2][4];
-            const int limit = column_limit(p, cb * 16 + n16, n);
-            tile_scores(k, sQ, cb, n16, c4, r, limit, p.scale, s);
-            const float2 lse = sLse[cb * 16 + n16];
-#pragma unroll
-            for (int e = 0; e < 8; ++e)                    // s = -inf (masked) gives 2^-inf = 0
-                v[e >> 2][e & 3] += fast_exp2(((s[e >> 2][e & 3] - lse.x) - lse.y) * kLog2e);
-        }
-        // lanes n16, n16 + Gp, n16 + 2 Gp ... hold the same head for different queries
-        for (int x = gp; x < 16; x <<= 1) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) v[e >> 2][e & 3] += __shfl_xor(v[e >> 2][e & 3], x);
-        }
-        if (n16 < p.G) {
-#pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                const int first = r + t * 16 + 4 * c4;
-                if (p.v_vec && first + 4 <= n) {
-                    *reinterpret_cast<float4*>(vrow + first) = make_float4(v[t][0], v[t][1], v[t][2], v[t][3]);
-                } else {
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        if (first + i < n) vrow[first + i] = v[t][i];
-                }
-            }
-        }
-    };
-    int r = (c * NW + w) * kWinRows;
-    if (r < n) load_k_tile(kA, kb, r, n16, n);
-    if (r + step < n) load_k_tile(kB, kb, r + step, n16, n);
-    while (r < n) {
-        tile(kA, r);
-        if (r + 2 * step < n) load_k_tile(kA, kb, r + 2 * step, n16, n);
-        r += step;
-        if (r >= n) break;
-        tile(kB, r);
-        if (r + 2 * step < n) load_k_tile(kB, kb, r + 2 * step, n16, n);
-        r += step;
+    for (int r = r0; r < n; r += step) {
+        if (r != r0) load_k_rows(k, kb, r, n16, n);
+        if (r + kWinRows > n - p.W) vote_rows<true>(p, k, sQ, sLse, vrow, r, n);
+        else                        vote_rows<false>(p, k, sQ, sLse, vrow, r, n);
     }
 }
 
 static int launch_window(const WindowParams& p, int batch, hipStream_t st) {
-    const size_t ncol = (size_t)p.ncb * 16, nt = kWinWaves * 64;
-    const size_t lds1 = ncol * kQStride * 2 + p.ncb * nt * sizeof(float2) + 2 * kWinWaves * ncol * sizeof(float);
+    const size_t ncol = (size_t)p.ncb * 16;
+    const size_t lds1 = ncol * kQStride * 2 + (size_t)p.ncb * kWinThreads * sizeof(float2);
     const size_t lds2 = ncol * kQStride * 2 + ncol * sizeof(float2);
     static size_t lds_allowed = 48 * 1024;       // grows monotonically; lds1 > lds2
     if (lds1 > lds_allowed) {
@@ -317,13 +351,22 @@ static int launch_window(const WindowParams& p, int batch, hipStream_t st) {
         lds_allowed = lds1;
     }
     dim3 grid(p.nch, p.Hkv, batch);
-    hipLaunchKernelGGL(window_lse_kernel, grid, dim3(kWinWaves * 64), lds1, st, p);
+    hipLaunchKernelGGL(window_lse_kernel, grid, dim3(kWinThreads), lds1, st, p);
     int rc = launch_status();
     if (rc != RK_OK) return rc;
     hipLaunchKernelGGL(window_lse_merge_kernel, dim3(p.ncb, p.Hkv, batch), dim3(256), 0, st, p);
     if ((rc = launch_status()) != RK_OK) return rc;
-    hipLaunchKernelGGL(window_vote_kernel, grid, dim3(kWinWaves * 64), lds2, st, p);
+    hipLaunchKernelGGL(window_vote_kernel, grid, dim3(kWinThreads), lds2, st, p);
     return launch_status();
+}
+
+// Workgroups per (sequence, KV head) of the two passes.
+static int window_split(int64_t max_rows, int64_t problems, int limit) {
+    int64_t per = kWinTargetWgs / problems;
+    const int64_t stretches = (max_rows + kWinWaves * kWinRows - 1) / (kWinWaves * kWinRows);
+    if (per > stretches) per = stretches;
+    if (per > limit) per = limit;
+    return per < 1 ? 1 : (int)per;
 }
 
 }  // namespace rk
@@ -363,7 +406,7 @@ extern "C" int rk_window_select(const rk_geom* geom, const void* q_win, int32_t 
     p.k = (const uint16_t*)full.k; p.s_b = full.stride_b; p.s_h = full.stride_h; p.cap = (int32_t)full.capacity;
     p.seq_lens = seq_lens; p.max_rows = max_len;
     p.W = window; p.G = G; p.gp_shift = gp_shift;
-    p.nch = split_workgroups(max_len, (int64_t)geom->batch * geom->n_kv_heads, ws.max_chunks);
+    p.nch = window_split(max_len, (int64_t)geom->batch * geom->n_kv_heads, ws.max_chunks);
     p.Hq = geom->n_q_heads; p.Hkv = geom->n_kv_heads;
     p.scale = geom->scale;
     p.part = ws.part_o; p.lse = ws.part_ml;
