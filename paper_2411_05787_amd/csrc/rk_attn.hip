@@ -1392,6 +1392,40 @@ __device__ __forceinline__ float weight_of(float s, float nl, float ll) {
     return fmaf(e, lo, e);
 }
 
+// The largest of the G weights of one position.  e^x is monotone, so the head with the largest exponent has
+// the largest weight and one exponential is enough, unless another head's exponent comes so close that the
+// rounding of the weights decides (`tol`: 1.5e-5, which covers the error of weight_of with exponents down to
+// -80, plus what the low parts of the lse differ by) or the weights are near the subnormal range: then
+// (about one wavefront in a thousand) all G are worked out.  The result is that of the maximum over
+// weight_of of all heads, bit for bit.  `lse`: (hi, lo) per head in LDS.  The pooling kernels were bound by these
+// instructions (32 layers of 33k rows, 32 heads: 33 million exponentials, 26 us of vector issue alone); with this and
+// the pooling in pool_tile, us per launch: 32 layers of 33k rows 65 -> 45 - 49, 4 layers of 16 ragged rows 71 -> 54, 28
+// layers of 65k rows (7 heads per group, 3 in 8 layers refreshed) 52 -> 36, one layer of 33k rows 8.6 -> 7.3, of 131k
+// rows 19.5 -> 13.5.
+template <int G>
+__device__ __forceinline__ float max_weight(const float (&s)[G], const float (*lse)[2], float tol) {
+    float best = -INFINITY, second = -INFINITY, bs = 0.f;
+    int bi = 0;
+#pragma unroll
+    for (int gi = 0; gi < G; ++gi) {
+        const float hi = s[gi] - lse[gi][0];
+        const bool up = hi > best;
+        second = __builtin_amdgcn_fmed3f(best, second, hi);
+        best = fmaxf(best, hi);
+        bs = up ? s[gi] : bs;
+        bi = up ? gi : bi;
+    }
+    float w;
+    if (__any(!(best - second > tol) || best < -80.f)) {
+        w = weight_of(s[0], -lse[0][0], lse[0][1]);
+#pragma unroll
+        for (int gi = 1; gi < G; ++gi) w = fmaxf(w, weight_of(s[gi], -lse[gi][0], lse[gi][1]));
+    } else {
+        w = weight_of(bs, -lse[bi][0], lse[bi][1]);
+    }
+    return w;
+}
+
 // Second kernel of a full step that returns the attention weights.  Every workgroup first
 // rebuilds lse of its (sequence, query head).  Workgroup x = 0 then merges the partial outputs of
 // that head; workgroups x >= 1 turn kNormTile raw scores each into
@@ -1469,9 +1503,9 @@ void finish_pool_body(const AttnParams& p, const float* __restrict__ scores, int
     const int j0 = (x - n_merge) * TILE;
     if (j0 >= len && !(j0 == 0 && n_merge == 0)) return;   // (an empty sequence still gets its lse = -inf)
 
-    __shared__ float sA[TILE + RK_MAX_POOL_W - 1];
+    __shared__ __attribute__((aligned(16))) float sA[TILE + RK_MAX_POOL_W + 1];
     __shared__ uint32_t sH[kHistBins];
-    __shared__ float sLse[G][2];
+    __shared__ __attribute__((aligned(8))) float sLse[G][2];
     constexpr int R = (TILE + RK_MAX_POOL_W - 1 + 255) / 256;
     const int span = TILE + 2 * half;
     const float* sg = scores + ((int64_t)b * p.Hq + (int64_t)g * G) * s_stride;
@@ -1540,44 +1574,40 @@ void finish_pool_body(const AttnParams& p, const float* __restrict__ scores, int
     if (j0 >= len) return;
 
     // ---- weights, max over the group ----
+    const bool only_max = agg == RK_AGG_MAX && p.weights == nullptr;
+    float tol = 1.5e-5f;
+#pragma unroll
+    for (int gi = 0; gi < G; ++gi) tol += fabsf(sLse[gi][1]);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int i = r * 256 + tid, j = j0 - half + i;
-        if (i < span) {
-            float a = -INFINITY;                     // outside [0, len): never wins a max
-            if (j >= 0 && j < len) {
-                const bool core = p.weights != nullptr && i >= half && i < half + TILE;
+        if (r * 256 >= span) break;
+        float one[G];
 #pragma unroll
-                for (int gi = 0; gi < G; ++gi) {
-                    const float wgt = weight_of(sc[gi][r], -sLse[gi][0], sLse[gi][1]);
-                    if (core) p.weights[((int64_t)b * p.Hq + (int64_t)g * G + gi) * p.w_stride + j] = wgt;
-                    a = aggregate(a, wgt, gi, agg);
-                }
-                if (agg == RK_AGG_MEAN) a = __fdiv_rn(a, (float)G);
+        for (int gi = 0; gi < G; ++gi) one[gi] = sc[gi][r];
+        const bool in = i < span && j >= 0 && j < len;
+        float a = -INFINITY;                         // outside [0, len): never wins a max
+        if (only_max) {
+            const float w = max_weight<G>(one, sLse, tol);
+            if (in) a = w;
+        } else if (in) {
+            const bool core = p.weights != nullptr && i >= half && i < half + TILE;
+#pragma unroll
+            for (int gi = 0; gi < G; ++gi) {
+                const float wgt = weight_of(one[gi], -sLse[gi][0], sLse[gi][1]);
+                if (core) p.weights[((int64_t)b * p.Hq + (int64_t)g * G + gi) * p.w_stride + j] = wgt;
+                a = aggregate(a, wgt, gi, agg);
             }
-            sA[i] = a;
+            if (agg == RK_AGG_MEAN) a = __fdiv_rn(a, (float)G);
         }
+        if (i < span) sA[i] = a;
     }
     __syncthreads();
 
     // ---- max-pool, store, histogram ----
-    float* prow = pooled + bg * pooled_stride;
-    for (int i = tid; i < TILE; i += 256) {
-        const int j = j0 + i;
-        if (j < len) {
-            float mx = sA[i];
-            for (int d = 1; d <= 2 * half; ++d) mx = fmaxf(mx, sA[i + d]);
-            mx += 0.0f;                           // -0 becomes +0: one bit pattern per value
-            prow[j] = mx;
-            atomicAdd(&sH[key_of(mx) >> kHistShift], 1u);
-        }
-    }
+    pool_tile<TILE>(sA, half, j0, len, pooled + bg * pooled_stride, sH);
     __syncthreads();
-    uint32_t* gh = hist + bg * kHistBins;
-    for (int i = tid; i < kHistBins; i += 256) {
-        const uint32_t c = sH[i];
-        if (c != 0) atomicAdd(&gh[i], c);
-    }
+    flush_histogram(sH, hist + bg * kHistBins);
 }
 
 template <int G, int TILE>
@@ -1593,7 +1623,7 @@ void finish_pool_kernel(const AttnParams p, const float* __restrict__ scores, in
 // passed by value.
 // With many layers in one launch the workgroups come in rounds and each pays its own chain of
 // round trips (statistics, lse, scores, histogram): larger tiles, fewer rounds.
-constexpr int kBatchedPoolTile = 2048;       // (the launch alone, 32 layers of 33k rows or 8 of 131k: 1024: 81, 2048: 72, 4096: 85, 8192: 103 us)
+constexpr int kBatchedPoolTile = 2048;       // (the launch alone, 32 layers of 33k rows or 8 of 131k, before max_weight and pool_tile: 1024: 81, 2048: 72, 4096: 85, 8192: 103 us)
 
 struct PoolBatch {
     const float* part_ml[kBatchLayers];

@@ -226,6 +226,57 @@ __device__ __forceinline__ float aggregate(float acc, float w, int head, int agg
     return acc;                               // RK_AGG_FIRST
 }
 
+// Max-pool of one tile and the selection's first-level histogram of the results; 256 threads.  sA[i] is the
+// group score of position j0 - half + i (-inf outside the row), 16-byte aligned; row: the row's pooled scores (16-byte
+// aligned, room for whole groups of four); sH: kHistBins counters in LDS, the top 11 bits of the score image each.
+// The usual width of 7 takes four neighbours per thread: 10 scores from LDS instead of 28, four of them common
+// to all four windows, one 16-byte store, and one atomic per stretch of neighbours in the same bin
+// instead of one per position (the window makes neighbours equal).
+template <int TILE>
+__device__ __forceinline__ void pool_tile(const float* sA, int half, int j0, int len, float* __restrict__ row, uint32_t* sH) {
+    if (half == 3) {
+        for (int i = 4 * (int)threadIdx.x; i < TILE && j0 + i < len; i += 4 * 256) {
+            const float4 x = *reinterpret_cast<const float4*>(sA + i), y = *reinterpret_cast<const float4*>(sA + i + 4);
+            const float2 z = *reinterpret_cast<const float2*>(sA + i + 8);
+            const float mid = fmaxf(fmaxf(x.w, y.x), fmaxf(y.y, y.z));
+            const float yz = fmaxf(y.w, z.x);
+            float m[4] = {fmaxf(mid, fmaxf(x.x, fmaxf(x.y, x.z))), fmaxf(mid, fmaxf(fmaxf(x.y, x.z), y.w)),
+                          fmaxf(mid, fmaxf(x.z, yz)), fmaxf(mid, fmaxf(yz, z.y))};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) m[e] += 0.0f;         // -0 becomes +0: one bit pattern per value
+            *reinterpret_cast<float4*>(row + j0 + i) = make_float4(m[0], m[1], m[2], m[3]);
+            const int n = min(len - (j0 + i), 4);
+            uint32_t bin = key_of(m[0]) >> kHistShift, count = 1;
+#pragma unroll
+            for (int e = 1; e < 4; ++e) {
+                const uint32_t next = key_of(m[e]) >> kHistShift;
+                if (e < n) {
+                    if (next != bin) { atomicAdd(&sH[bin], count); bin = next; count = 0; }
+                    ++count;
+                }
+            }
+            atomicAdd(&sH[bin], count);
+        }
+        return;
+    }
+    for (int i = threadIdx.x; i < TILE; i += 256) {
+        const int j = j0 + i;
+        if (j < len) {
+            float m = sA[i];
+            for (int d = 1; d <= 2 * half; ++d) m = fmaxf(m, sA[i + d]);
+            m += 0.0f;
+            row[j] = m;
+            atomicAdd(&sH[key_of(m) >> kHistShift], 1u);
+        }
+    }
+}
+__device__ __forceinline__ void flush_histogram(const uint32_t* sH, uint32_t* __restrict__ hist) {
+    for (int i = threadIdx.x; i < kHistBins; i += 256) {
+        const uint32_t c = sH[i];
+        if (c != 0) atomicAdd(&hist[i], c);
+    }
+}
+
 // Orders LDS traffic of the lanes of one wavefront: what was written before is visible to
 // every lane after.  Lanes of a wavefront run in lockstep, so no hardware barrier is needed,
 // only the compiler and the LDS queue have to be told.

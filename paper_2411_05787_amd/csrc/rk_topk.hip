@@ -73,39 +73,33 @@ void pool_hist_kernel(const float* __restrict__ weights, int64_t w_stride, const
     const int len = min(seq_lens[b], max_len);
     const int j0 = blockIdx.x * TILE;
     if (j0 >= len) return;
-    __shared__ float sA[TILE + RK_MAX_POOL_W - 1];
+    __shared__ __attribute__((aligned(16))) float sA[TILE + RK_MAX_POOL_W + 1];
     __shared__ uint32_t sH[kHistBins];
     const float* wg = weights + ((int64_t)b * Hq + (int64_t)g * G) * w_stride;
     const int span = TILE + 2 * half;
     for (int i = threadIdx.x; i < kHistBins; i += 256) sH[i] = 0;
-    for (int i = threadIdx.x; i < span; i += 256) {
-        const int j = j0 - half + i;
+    constexpr int R = (TILE + RK_MAX_POOL_W - 1 + 255) / 256;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        if (r * 256 >= span) break;
+        const int i = r * 256 + threadIdx.x, j = j0 - half + i;
         float a = -INFINITY;                     // outside [0, len): never wins a max
-        if (j >= 0 && j < len) {
-            for (int gi = 0; gi < G; ++gi) a = aggregate(a, wg[(int64_t)gi * w_stride + j], gi, agg);
+        if (i < span && j >= 0 && j < len) {
+            float w[RK_MAX_GROUP];               // the heads' weights, all requested together
+#pragma unroll
+            for (int gi = 0; gi < RK_MAX_GROUP; ++gi) w[gi] = gi < G ? wg[(int64_t)gi * w_stride + j] : 0.f;
+#pragma unroll
+            for (int gi = 0; gi < RK_MAX_GROUP; ++gi)
+                if (gi < G) a = aggregate(a, w[gi], gi, agg);
             if (agg == RK_AGG_MEAN) a = __fdiv_rn(a, (float)G);
         }
-        sA[i] = a;
+        if (i < span) sA[i] = a;
     }
     __syncthreads();
     const int64_t bg = (int64_t)b * Hkv + g;
-    float* out = pooled + bg * pooled_stride;
-    for (int i = threadIdx.x; i < TILE; i += 256) {
-        const int j = j0 + i;
-        if (j < len) {
-            float m = sA[i];
-            for (int d = 1; d <= 2 * half; ++d) m = fmaxf(m, sA[i + d]);
-            m += 0.0f;                           // -0 becomes +0: one bit pattern per value
-            out[j] = m;
-            atomicAdd(&sH[key_of(m) >> kHistShift], 1u);
-        }
-    }
+    pool_tile<TILE>(sA, half, j0, len, pooled + bg * pooled_stride, sH);
     __syncthreads();
-    uint32_t* gh = hist + bg * kHistBins;
-    for (int i = threadIdx.x; i < kHistBins; i += 256) {
-        const uint32_t c = sH[i];
-        if (c != 0) atomicAdd(&gh[i], c);
-    }
+    flush_histogram(sH, hist + bg * kHistBins);
 }
 
 // Inclusive prefix sum over the NT threads of the workgroup, in thread order.  `scratch` holds

@@ -65,3 +65,66 @@ def test_window_select_at_tile_edges(rk, case):
         for g in range(Hkv):
             P = oracle.pooled_group_scores(v_ref[b, g * G:(g + 1) * G, :n].astype(np.float32), 7)
             assert_idx_equivalent(idx[b, g].cpu().numpy(), i_ref[b, g], P, n, k, "%s b=%d g=%d" % (name, b, g))
+
+
+# (group, pooling width, rows): the tiles of the pooling kernels end at multiples of 512, 1024 (from 98304 rows on) and,
+# batched over layers, 2048
+POOL_EDGES = [(4, 7, 512), (4, 7, 513), (1, 7, 1021), (7, 7, 1023), (8, 7, 1030), (4, 1, 700), (5, 15, 1537), (2, 63, 515),
+              (4, 7, 2047), (4, 7, 2051), (3, 7, 3), (4, 7, 1), (4, 7, 98309)]
+
+
+@pytest.mark.parametrize("spread", ["plain", "near_ties", "far_apart"])
+@pytest.mark.parametrize("shape", POOL_EDGES, ids=["g%d_w%d_n%d" % s for s in POOL_EDGES])
+def test_group_maximum_by_one_exponential_is_exact(rk, shape, spread):
+    """The selection without returned weights (one exponential per position, of the head with the largest exponent)
+    against the same call with them (all heads' weights, their maximum): the same positions and the same scores
+    bit for bit, also batched over two layers.  near_ties: heads that are copies of one another, or differ in
+    the last bit of a few dimensions; far_apart: scores of magnitude 100 and more, weights down to subnormal and zero."""
+    G, pool_w, n = shape
+    say("one exponential", shape, spread)
+    B, Hkv, k = (1, 1, 64) if n > 50000 else (2, 2, 40)
+    Hq, cap = G * Hkv, n + 5
+    q, K, V = draw(G + n, B, Hq, 128), draw(n, B, Hkv, cap, 128), draw(n + 1, B, Hkv, cap, 128)
+    if spread == "near_ties":
+        q = q.view(B, Hkv, G, 128)
+        q[:, :, 1:] = q[:, :, :1]                        # every head of a group equal to the first ...
+        bits = q.view(torch.int16)
+        bits[:, :, G // 2:, ::40] ^= 1                   # ... or one unit in the last place away in four dimensions
+        q = q.view(B, Hq, 128)
+    elif spread == "far_apart":
+        q = (q.float() * 30).to(torch.bfloat16)
+    lens = [n] * B if B == 1 else [n, max(n - 3, 0)]
+    geom = rk.Geom(B, Hq, Hkv, 128, SCALE)
+    sl = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    q, K, V = q.cuda(), K.cuda(), V.cuda()
+    got = []
+    for want in (False, True):
+        ws = rk.Workspace(geom, cap, k)
+        out = torch.zeros(B, Hq, 128, dtype=torch.bfloat16, device="cuda")
+        idx = torch.full((B, Hkv, k), -5, dtype=torch.int32, device="cuda")
+        sel = torch.full((B, Hkv, k), -5.0, device="cuda")
+        w = torch.zeros(B, Hq, cap, device="cuda") if want else None
+        rk.rk_full_attn_select(geom, q, K, V, sl, n, out, k, pool_w, idx, weights=w, sel_scores=sel, workspace=ws)
+        got.append((idx.cpu(), sel.cpu(), out.cpu()))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    # ... and what the maximum over the returned weights selects
+    A = w.view(B, Hkv, G, cap).amax(2).cpu().numpy()
+    for b in range(B):
+        for g in range(Hkv):
+            P = oracle.pooled_group_scores(A[b, g, None, :lens[b]], pool_w)
+            order = np.lexsort((np.arange(lens[b]), -P))[:k]
+            assert (got[0][0][b, g, :len(order)].numpy() == order).all()
+            assert (got[0][1][b, g, :len(order)].numpy() == P[order].astype(np.float32)).all()
+    wss = [rk.Workspace(geom, cap, k) for _ in range(2)]
+    small = torch.zeros(2, 2, B, Hkv, k, 128, dtype=torch.bfloat16, device="cuda")
+    idx = torch.full((2, B, Hkv, k), -5, dtype=torch.int32, device="cuda")
+    tail = torch.zeros(2, B, dtype=torch.int32, device="cuda")
+    layers = (type(rk.layer_state(geom, K, V, small[0, 0], small[0, 1], idx[0], tail[0], k=k)) * 2)(
+        *[rk.layer_state(geom, K, V, small[l, 0], small[l, 1], idx[l], tail[l], k=k) for l in range(2)])
+    for l in range(2):
+        rk.rk_full_attn_deferred(geom, q, K, V, sl, n, out, workspace=wss[l])
+    import ctypes
+    rk.rk_refresh_batched(geom, layers, (ctypes.c_void_p * 2)(*[x.ptr for x in wss]), wss[0].nbytes, sl, n, k, pool_w=pool_w)
+    torch.cuda.synchronize()
+    for l in range(2):
+        assert torch.equal(idx[l].cpu(), got[0][0])
