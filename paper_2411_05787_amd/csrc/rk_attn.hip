@@ -70,6 +70,7 @@ struct AttnParams {
     const int32_t* idx; int32_t idx_stride;   // LAZY only: the selection [B, Hkv, idx_stride] whose rows are not gathered yet
     float* trig_q_ref; float* trig_sim; int32_t* trig_need; float trig_threshold;   // TRIG only: the query-similarity test
     int32_t ragged_batch;              // != 0 (= batch): workgroups are shared out by length, see ragged_share_lane
+    int32_t share_cap;                 // ... at most this many to a sequence
     int32_t slice_merge;               // TAGGED: every workgroup merges a slice of the output (all workgroups of the launch are resident together)
     int32_t slice_spin;                // ... re-reading rows still in flight at most this often before it leaves its slice to the last one
 };
@@ -91,66 +92,69 @@ __device__ __forceinline__ int active_workgroups(int n_rows, int nch) {
 // resident as a whole takes as long as its longest sequence.  Score-emitting launches over
 // 2..kRaggedMaxBatch sequences therefore share the nch * batch workgroups of a KV head out in
 // proportion to the lengths: sequence i gets a_i = 1 + its share of the other nch * batch - batch by
-// the largest-remainder rule (at least one, at most one per 128 rows and kMaxChunks; the a_i add up
+// the largest-remainder rule (at least one, at most one per 128 rows and share_cap; the a_i add up
 // to no more than there are), and workgroup z * nch + x of the grid is number (that minus the a_j before it) of
-// the sequence it falls into; those past the sum do nothing.  Every kernel of the call derives the
-// same a_i from seq_lens: exact integer arithmetic, one wavefront, lane i for sequence i.
+// the sequence it falls into; those past the sum do nothing.  Every workgroup derives the same a_i from
+// seq_lens: exact arithmetic (fp64 on whole numbers below 2^46), one wavefront, lane i for sequence i.  All of
+// the launch waits for it before its first request, so it keeps to the data-parallel operand path and scalar
+// registers (64-bit integer division and shuffles through LDS took 0.6 us longer).
+// The kernels that read the partial results do not repeat it: the first workgroup of every (sequence, KV head)
+// leaves their number in its counter line (kCountWord).  16 ragged sequences of 10k rows, us per launch: output merge
+// 7.8 -> 6.2, pooling of 4 layers 54 -> 45.
 constexpr int kRaggedMaxBatch = 64;
+constexpr int kCountWord = 4;
 __device__ __forceinline__ int clamped_len(int raw, int cap, int max_rows) { return min(max(min(raw, cap), 0), max_rows); }
+__device__ __forceinline__ double lane_of(double v, int lane) {          // (lane: the same in all lanes)
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane), __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
 
 // Lane i < batch: a_i.  Other lanes: 0.  Called by whole wavefronts.
-__device__ __forceinline__ int ragged_share_lane(const int32_t* seq_lens, int batch, int nch, int cap, int max_rows) {
+__device__ __forceinline__ int ragged_share_lane(const int32_t* seq_lens, int batch, int nch, int cap, int max_rows, int share_cap) {
     const int lane = threadIdx.x & 63;
     const int len = lane < batch ? clamped_len(seq_lens[lane], cap, max_rows) : 0;
-    long long total = len;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) total += __shfl_xor(total, d);
-    const long long spare = (long long)nch * batch - batch;
+    const double total = wave_sum((double)len);
     int a = 1;
-    if (total > 0) {
-        const long long num = spare * (long long)len;
-        const long long fl = num / total;
-        const long long rem = num - fl * total;
+    if (total > 0.0) {
+        const int spare = nch * batch - batch;                 // at most kMaxChunks * kRaggedMaxBatch
+        const double num = (double)spare * (double)len;
+        double fl = floor(num / total);
+        double rem = fma(-fl, total, num);                     // exact; the quotient may have been rounded across a whole number
+        if (rem < 0.0) { fl -= 1.0; rem += total; }
+        if (rem >= total) { fl += 1.0; rem -= total; }
         // what the floors leave over goes, one each, to the largest remainders (ties: lower sequence first)
-        long long given = fl;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) given += __shfl_xor(given, d);
-        const int left = (int)(spare - given);                 // 0 <= left < batch
+        const int left = spare - (int)wave_sum(fl);            // 0 <= left < batch
         int rank = 0;
         for (int j = 0; j < batch; ++j) {
-            const long long rj = __shfl(rem, j);
+            const double rj = lane_of(rem, j);
             rank += (rj > rem || (rj == rem && j < lane)) ? 1 : 0;
         }
         a += (int)fl + (rank < left ? 1 : 0);
     }
-    a = min(a, min(kMaxChunks, max(1, (len + kSplitWaves * kTileRows - 1) / (kSplitWaves * kTileRows))));
+    a = min(a, min(share_cap, max(1, (len + kSplitWaves * kTileRows - 1) / (kSplitWaves * kTileRows))));
     return lane < batch ? a : 0;
 }
 
-// Partial results sequence b leaves behind (what active_workgroups is to the even split).
-__device__ __forceinline__ int ragged_chunks_of(const AttnParams& p, int b) {
-    const int a = ragged_share_lane(p.seq_lens, p.ragged_batch, p.nch, p.cap2, p.max_rows2);
-    return __shfl(a, b);
+// Partial results that the launch before this one left for (sequence, KV head) number bg.
+__device__ __forceinline__ int stored_chunks(const int32_t* counters, int64_t bg) {
+    return min(max(counters[bg * kCounterStride + kCountWord], 1), kMaxChunks);
+}
+__device__ __forceinline__ void store_chunks(int32_t* counters, int64_t bg, int nchunks) {
+    counters[bg * kCounterStride + kCountWord] = nchunks;
 }
 
 // Sequence, number within it and share of the workgroup at `slot` (b < 0: none).
 struct RaggedSlot { int b, c, nchunks; };
 __device__ __forceinline__ RaggedSlot ragged_slot(const AttnParams& p, const int32_t* seq_lens, int slot) {
     const int lane = threadIdx.x & 63;
-    const int a = ragged_share_lane(seq_lens, p.ragged_batch, p.nch, p.cap2, p.max_rows2);
-    int incl = a;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int up = __shfl_up(incl, d);
-        if (lane >= d) incl += up;
-    }
+    const int a = ragged_share_lane(seq_lens, p.ragged_batch, p.nch, p.cap2, p.max_rows2, p.share_cap);
+    const int incl = (int)wave_inclusive_scan((uint32_t)a);
     const int before = incl - a;
     const unsigned long long hit = __ballot(a > 0 && before <= slot && slot < incl);
     RaggedSlot r{-1, 0, 0};
     if (hit != 0) {
         r.b = __ffsll(hit) - 1;
-        r.c = slot - __shfl(before, r.b);
-        r.nchunks = __shfl(a, r.b);
+        r.c = slot - __builtin_amdgcn_readlane(before, r.b);
+        r.nchunks = __builtin_amdgcn_readlane(a, r.b);
     }
     return r;
 }
@@ -1029,6 +1033,8 @@ void attn_split_kernel(const uint16_t* k_first, const uint16_t* v_first, int64_t
 
     // ---- merge the NW wavefronts and publish the partial result of this chunk ----
     const int64_t bg = (int64_t)b * p.Hkv + g;
+    // (here and not where the number is known: the waits for the first rows would cover the store as well)
+    if (EMIT && c == 0 && tid == 0) store_chunks(p.counters, bg, nchunks);
     // what the NW wavefronts found for dims d, d + 1 of head gi, as one: max, sum, unnormalised output
     auto combine = [&](int gi, int d, float& M, float& L, float& acc0, float& acc1) {
         M = sMw[0][gi];
@@ -1293,6 +1299,7 @@ void score_split_kernel(const AttnParams p) {
         }
         float* ml = p.part_ml + (((int64_t)b * p.Hkv + g) * kMaxChunks + c) * G * 2;
         *reinterpret_cast<float2*>(ml + tid * 2) = make_float2(M, L);
+        if (c == 0 && tid == 0) store_chunks(p.counters, (int64_t)b * p.Hkv + g, nchunks);
     }
 }
 
@@ -1439,9 +1446,9 @@ void merge_normalise_kernel(const AttnParams p, int G) {
     const int tid = threadIdx.x;
     const int g = h / G, gi = h % G;
     const int len = min(max(min(p.seq_lens[b], p.cap2), 0), p.max_rows2);
-    const int nchunks = p.ragged_batch != 0 ? ragged_chunks_of(p, b) : active_workgroups(len, p.nch);
     const int j0 = (x - 1) * kNormTile;
     if (x >= 1 && j0 >= len) return;
+    const int nchunks = stored_chunks(p.counters, (int64_t)b * p.Hkv + g);
 
     __shared__ HeadMergeLds s;
     constexpr int PER = kNormTile / 256;         // scores per thread
@@ -1488,11 +1495,13 @@ void finish_pool_body(const AttnParams& p, const float* __restrict__ scores, int
     if (p.pred != nullptr && p.pred[b] != p.pred_val) return;
     const int tid = threadIdx.x;
     const int len = min(max(min(p.seq_lens[b], p.cap2), 0), p.max_rows2);
-    const int nchunks = p.ragged_batch != 0 ? ragged_chunks_of(p, b) : active_workgroups(len, p.nch);
     const int64_t bg = (int64_t)b * p.Hkv + g;
+    const int n_merge = p.out != nullptr ? G : 0;     // no output to merge after a scores-only pass
+    const int j0 = (x - n_merge) * TILE;
+    if (x >= n_merge && j0 >= len && !(j0 == 0 && n_merge == 0)) return;   // (an empty sequence still gets its lse = -inf)
+    const int nchunks = stored_chunks(p.counters, bg);
 
     __shared__ HeadMergeLds s;
-    const int n_merge = p.out != nullptr ? G : 0;     // no output to merge after a scores-only pass
     if (x < n_merge) {
         float2 v[kOutBatch];
         head_out_request(p, G, bg, x, nchunks, v);
@@ -1500,9 +1509,6 @@ void finish_pool_body(const AttnParams& p, const float* __restrict__ scores, int
         block_head_out(p, G, b, bg, x, nchunks, s, v);
         return;
     }
-    const int j0 = (x - n_merge) * TILE;
-    if (j0 >= len && !(j0 == 0 && n_merge == 0)) return;   // (an empty sequence still gets its lse = -inf)
-
     __shared__ __attribute__((aligned(16))) float sA[TILE + RK_MAX_POOL_W + 1];
     __shared__ uint32_t sH[kHistBins];
     __shared__ __attribute__((aligned(8))) float sLse[G][2];
@@ -1626,6 +1632,7 @@ void finish_pool_kernel(const AttnParams p, const float* __restrict__ scores, in
 constexpr int kBatchedPoolTile = 2048;       // (the launch alone, 32 layers of 33k rows or 8 of 131k, before max_weight and pool_tile: 1024: 81, 2048: 72, 4096: 85, 8192: 103 us)
 
 struct PoolBatch {
+    const int32_t* counters[kBatchLayers];
     const float* part_ml[kBatchLayers];
     const float* scores[kBatchLayers];
     float* lse[kBatchLayers];
@@ -1642,6 +1649,7 @@ __global__ __launch_bounds__(256, G <= 4 ? 5 : 1)
 void pool_batched_kernel(const PoolBatch tab, const AttnParams common, int32_t batch, int64_t stride, int half, int agg) {
     const int layer = blockIdx.z / batch, b = blockIdx.z - layer * batch;
     AttnParams p = common;                   // out == NULL and weights == NULL: pooling tiles only
+    p.counters = const_cast<int32_t*>(tab.counters[layer]);
     p.part_ml = const_cast<float*>(tab.part_ml[layer]);
     p.lse = tab.lse[layer];
     p.pred = tab.pred[layer];
@@ -1797,6 +1805,7 @@ int full_attn_stage(const rk_geom* geom, const void* q, rk_kv full, const int32_
     p.counters = ws.counters; p.part_ml = ws.part_ml; p.part_o = ws.part_o; p.max_chunks = ws.max_chunks;
     p.epochs = ws.epochs; p.tag_rows = ws.tag_rows;
     p.ragged_batch = (emit && !no_v) ? ragged_batch_of(geom) : 0;
+    p.share_cap = kMaxChunks;
     if (!emit) {
         // No scores wanted.  Short rows: one launch, merged by the last workgroup inside it (at most
         // kMergeChunks partial results).  Long rows: the wider split of the score-emitting kernel
@@ -1868,7 +1877,7 @@ int full_attn_stage(const rk_geom* geom, const void* q, rk_kv full, const int32_
 }
 
 // The pooled scores and histograms of n_layers layers whose full attention ran with defer_pool,
-// each on its own workspace, with the launch shape emit_split_workgroups gives.
+// each on its own workspace.
 int pool_batched_stage(const rk_geom* geom, int n_layers, const Workspace* wss, const int32_t* seq_lens, int32_t max_len,
                        int64_t full_capacity, int pool_half, int agg, const int32_t* const* pred, int32_t pred_val,
                        hipStream_t st) {
@@ -1878,8 +1887,6 @@ int pool_batched_stage(const rk_geom* geom, int n_layers, const Workspace* wss, 
     p.seq_lens = seq_lens;
     p.max_rows2 = max_len;
     p.cap2 = (int32_t)full_capacity;
-    p.nch = emit_split_workgroups(geom, max_len);
-    p.ragged_batch = ragged_batch_of(geom);
     p.Hq = geom->n_q_heads; p.Hkv = geom->n_kv_heads;
     p.w_inter = G == 4 ? 1 : 0;              // how full_attn_stage(defer_pool) left the raw scores
     p.pred_val = pred_val;
@@ -1888,7 +1895,7 @@ int pool_batched_stage(const rk_geom* geom, int n_layers, const Workspace* wss, 
         PoolBatch tab{};
         for (int l = 0; l < n; ++l) {
             const Workspace& w = wss[l0 + l];
-            tab.part_ml[l] = w.part_ml; tab.scores[l] = w.scores; tab.lse[l] = w.lse;
+            tab.counters[l] = w.counters; tab.part_ml[l] = w.part_ml; tab.scores[l] = w.scores; tab.lse[l] = w.lse;
             tab.pooled[l] = w.pooled; tab.hist[l] = w.hist;
             tab.pred[l] = pred ? pred[l0 + l] : nullptr;
         }

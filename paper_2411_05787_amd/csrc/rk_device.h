@@ -226,6 +226,20 @@ __device__ __forceinline__ float aggregate(float acc, float w, int head, int agg
     return acc;                               // RK_AGG_FIRST
 }
 
+// Inclusive prefix sum over the 64 lanes of the wavefront.
+__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v) {
+    const int lane = threadIdx.x & 63;
+    uint32_t x = v;
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, true);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, true);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, true);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, true);
+    const uint32_t t0 = (uint32_t)__builtin_amdgcn_readlane((int)x, 15), t1 = (uint32_t)__builtin_amdgcn_readlane((int)x, 31);
+    const uint32_t t2 = (uint32_t)__builtin_amdgcn_readlane((int)x, 47);
+    const int row = lane >> 4;
+    return x + (row == 0 ? 0u : row == 1 ? t0 : row == 2 ? t0 + t1 : t0 + t1 + t2);
+}
+
 // Max-pool of one tile and the selection's first-level histogram of the results; 256 threads.  sA[i] is the
 // group score of position j0 - half + i (-inf outside the row), 16-byte aligned; row: the row's pooled scores (16-byte
 // aligned, room for whole groups of four); sH: kHistBins counters in LDS, the top 11 bits of the score image each.

@@ -197,8 +197,9 @@ static inline int topk_cand_cap(int64_t k) {
 // whole workspace once); the counters and histograms are left cleared by the kernels that use
 // them, the call numbers and tags only ever grow.  Where these regions lie depends on the
 // geometry alone, never on max_len or max_k.
-//   counters  int32 [B*Hkv][kCounterStride]  arrival tickets of the split attention kernel, one per
-//                                            128-byte line
+//   counters  int32 [B*Hkv][kCounterStride]  one 128-byte line each: arrival ticket of the split attention
+//                                            kernel (word 0), the trigger's ticket (1), slices left over
+//                                            (2, 3), number of partial results of the last full pass (4)
 //   sel_counters int32 [B*Hkv][2]            listed candidates and arrival tickets of the selection
 //   epochs    uint32 [B*Hkv]                 call number of the last merge inside a split kernel
 //   hist      uint32 [B*Hkv][kHistBins]      first-level histogram of the pooled scores

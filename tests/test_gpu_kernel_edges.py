@@ -128,3 +128,49 @@ def test_group_maximum_by_one_exponential_is_exact(rk, shape, spread):
     torch.cuda.synchronize()
     for l in range(2):
         assert torch.equal(idx[l].cpu(), got[0][0])
+
+
+# the workgroups of a launch over 2..64 sequences are shared out by length, with exact remainders
+RAGGED = [("two_far_apart", [9000, 1]), ("three_equal", [1280, 1280, 1280]), ("ties", [300, 300, 301, 0, 299, 300]),
+          ("one_long_of_64", [30000] + [1, 0, 129] * 21), ("steps_64", [128 * i for i in range(64)]), ("beyond_64", [200] * 64 + [4000]),
+          ("primes", [7919, 6007, 4999, 3001, 2003, 1009, 503, 251, 127, 61, 31])]
+
+
+@pytest.mark.parametrize("G", [1, 4, 7])
+@pytest.mark.parametrize("case", RAGGED, ids=[c[0] for c in RAGGED])
+def test_ragged_batches_cover_every_row_once(rk, case, G):
+    """Full attention over batches of very different lengths, with weights, without, and deferred, against fp64: a row
+    left out or taken twice by the shares would move lse by far more than its bound (1e-5)."""
+    name, lens = case
+    say("ragged", name, G)
+    B, Hkv, cap = len(lens), 2, max(lens) + 2
+    g = torch.Generator(device="cuda").manual_seed(B + G)
+    K = torch.randn(B, Hkv, cap, 128, generator=g, device="cuda").to(torch.bfloat16)
+    V = torch.randn(B, Hkv, cap, 128, generator=g, device="cuda").to(torch.bfloat16)
+    q = torch.randn(B, Hkv * G, 128, generator=g, device="cuda").to(torch.bfloat16)
+    geom = rk.Geom(B, Hkv * G, Hkv, 128, SCALE)
+    ws = rk.Workspace(geom, cap, 16)
+    sl = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    runs = []
+    for kind in ("weights", "plain", "deferred"):
+        out = torch.full_like(q, 7.0)
+        lse = torch.full((B, Hkv * G), 7.0, device="cuda")
+        if kind == "deferred":
+            rk.rk_full_attn_deferred(geom, q, K, V, sl, max(lens), out, lse=lse, workspace=ws)
+        else:
+            w = torch.zeros(B, Hkv * G, cap, device="cuda") if kind == "weights" else None
+            rk.rk_full_attn(geom, q, K, V, sl, max(lens), out, weights=w, lse=lse, workspace=ws)
+        runs.append((kind, out, lse))
+    torch.cuda.synchronize()
+    for b, n in enumerate(lens):
+        if n == 0:
+            for kind, out, lse in runs:
+                assert (out[b] == 0).all() and (lse[b] == -float("inf")).all(), (name, kind, b)
+            continue
+        s = SCALE * torch.matmul(q[b].double().view(Hkv, G, 128), K[b, :, :n].double().transpose(1, 2).contiguous())
+        z = torch.logsumexp(s, dim=-1)
+        ref = torch.matmul(torch.exp(s - z[..., None]), V[b, :, :n].double()).reshape(-1, 128)
+        for kind, out, lse in runs:
+            assert (lse[b].double() - z.reshape(-1)).abs().max() < 1e-5, (name, kind, b)
+            d = (out[b].double() - ref).abs()             # one bf16 step of the larger value, and 4e-6 (see helpers)
+            assert (d <= torch.maximum(out[b].double().abs(), ref.abs()) * 2.0 ** -7 + 4e-6).all(), (name, kind, b)
