@@ -99,7 +99,7 @@ __device__ __forceinline__ int active_workgroups(int n_rows, int nch) {
 // the launch waits for it before its first request, so it keeps to the data-parallel operand path and scalar
 // registers (64-bit integer division and shuffles through LDS took 0.6 us longer).
 // The kernels that read the partial results do not repeat it: the first workgroup of every (sequence, KV head)
-// leaves their number in its counter line (kCountWord).  16 ragged sequences of 10k rows, us per launch: output merge
+// of such a launch leaves their number in its counter line (kCountWord).  16 ragged sequences of 10k rows, us per launch: output merge
 // 7.8 -> 6.2, pooling of 4 layers 54 -> 45.
 constexpr int kRaggedMaxBatch = 64;
 constexpr int kCountWord = 4;
@@ -1034,7 +1034,7 @@ void attn_split_kernel(const uint16_t* k_first, const uint16_t* v_first, int64_t
     // ---- merge the NW wavefronts and publish the partial result of this chunk ----
     const int64_t bg = (int64_t)b * p.Hkv + g;
     // (here and not where the number is known: the waits for the first rows would cover the store as well)
-    if (EMIT && c == 0 && tid == 0) store_chunks(p.counters, bg, nchunks);
+    if (kCanBeRagged && p.ragged_batch != 0 && c == 0 && tid == 0) store_chunks(p.counters, bg, nchunks);
     // what the NW wavefronts found for dims d, d + 1 of head gi, as one: max, sum, unnormalised output
     auto combine = [&](int gi, int d, float& M, float& L, float& acc0, float& acc1) {
         M = sMw[0][gi];
@@ -1299,7 +1299,6 @@ void score_split_kernel(const AttnParams p) {
         }
         float* ml = p.part_ml + (((int64_t)b * p.Hkv + g) * kMaxChunks + c) * G * 2;
         *reinterpret_cast<float2*>(ml + tid * 2) = make_float2(M, L);
-        if (c == 0 && tid == 0) store_chunks(p.counters, (int64_t)b * p.Hkv + g, nchunks);
     }
 }
 
@@ -1448,7 +1447,7 @@ void merge_normalise_kernel(const AttnParams p, int G) {
     const int len = min(max(min(p.seq_lens[b], p.cap2), 0), p.max_rows2);
     const int j0 = (x - 1) * kNormTile;
     if (x >= 1 && j0 >= len) return;
-    const int nchunks = stored_chunks(p.counters, (int64_t)b * p.Hkv + g);
+    const int nchunks = p.ragged_batch != 0 ? stored_chunks(p.counters, (int64_t)b * p.Hkv + g) : active_workgroups(len, p.nch);
 
     __shared__ HeadMergeLds s;
     constexpr int PER = kNormTile / 256;         // scores per thread
@@ -1499,7 +1498,7 @@ void finish_pool_body(const AttnParams& p, const float* __restrict__ scores, int
     const int n_merge = p.out != nullptr ? G : 0;     // no output to merge after a scores-only pass
     const int j0 = (x - n_merge) * TILE;
     if (x >= n_merge && j0 >= len && !(j0 == 0 && n_merge == 0)) return;   // (an empty sequence still gets its lse = -inf)
-    const int nchunks = stored_chunks(p.counters, bg);
+    const int nchunks = p.ragged_batch != 0 ? stored_chunks(p.counters, bg) : active_workgroups(len, p.nch);
 
     __shared__ HeadMergeLds s;
     if (x < n_merge) {
@@ -1788,8 +1787,7 @@ int full_attn_stage(const rk_geom* geom, const void* q, rk_kv full, const int32_
     p.n_sel = 0;
     p.max_rows2 = max_len;
     p.cap1 = 0; p.cap2 = (int32_t)full.capacity;
-    p.nch = emit ? emit_split_workgroups(geom, max_len)
-                 : split_workgroups(max_len, (int64_t)geom->batch * geom->n_kv_heads, kMergeChunks);
+    p.nch = emit ? emit_split_workgroups(geom, max_len) : 0;       // (without scores: below)
     if (co_run) {       // more, smaller workgroups, unless that means more partial results than the finish takes cheaply
         const int wide = split_workgroups(max_len, (int64_t)geom->batch * geom->n_kv_heads, kMaxChunks, kCoRunTargetWgs);
         if (wide <= kCoRunMaxChunks) p.nch = wide;
@@ -1819,33 +1817,34 @@ int full_attn_stage(const rk_geom* geom, const void* q, rk_kv full, const int32_
             set_slice_merge(p, true, (int64_t)p.nch * problems);
             return launch_split<false, false>(p, geom->batch, G, p.nch, st);
         }
-        p.nch = wide;
         p.weights = nullptr;
         p.ragged_batch = ragged_batch_of(geom);
+        const int inside = inside_split_workgroups(geom, max_len);
+        if (inside > 0) {
+            p.nch = inside;
+            p.share_cap = kMergeChunks;
+            set_slice_merge(p, true, (int64_t)p.nch * geom->batch * geom->n_kv_heads);
+            return launch_split<true, false, true>(p, geom->batch, G, p.nch, st);
+        }
+        p.nch = wide;
         int rc = launch_split<true, false>(p, geom->batch, G, p.nch, st);
         if (rc != RK_OK) return rc;
         hipLaunchKernelGGL(merge_normalise_kernel, dim3(1, geom->n_q_heads, geom->batch), dim3(256), 0, st, p, G);
         return launch_status();
     }
-    const int nchunk_grid = p.nch;
     // Where the pooling is deferred, nothing but the output merge would follow this kernel at once: it is merged
-    // inside the kernel instead of by a launch that waits for this one (tagged partial results, merged by slices, as
-    // in the partial step; full step of 32 heads over 32768 rows: 36.8 -> 35.7 us per layer).  Groups of up to 4 heads,
-    // all workgroups of the launch resident at once, no more partial results than that merge takes.  (Where the
+    // inside the kernel instead of by a launch that waits for this one (tagged partial results, as in the partial step:
+    // by slices where all workgroups are resident at once, by the last arrival of each (sequence, KV head) beyond).  (Where the
     // finish follows at once its first workgroups merge the output beside the pooling tiles, which costs nothing;
     // merged inside, that step was 2.5 us slower.)
-    const bool merge_inside = fused && defer_pool && !no_v && !scores_only && ws.tag_rows != nullptr && G <= kSplitWaves && p.ragged_batch == 0 &&
-                              nchunk_grid <= kSliceChunks4 &&
-                              (int64_t)nchunk_grid * geom->batch * geom->n_kv_heads <= 2 * kComputeUnits;
+    const int inside = fused && defer_pool && !no_v && !scores_only ? inside_split_workgroups(geom, max_len) : 0;
+    const bool merge_inside = inside > 0;
+    if (merge_inside) { p.nch = inside; p.share_cap = kMergeChunks; }
+    const int nchunk_grid = p.nch;
     int rc;
     if (merge_inside) {
         set_slice_merge(p, true, (int64_t)nchunk_grid * geom->batch * geom->n_kv_heads);
-        switch (G) {
-            case 1: rc = launch_split_g<1, true, false, true>(p, geom->batch, nchunk_grid, st); break;
-            case 2: rc = launch_split_g<2, true, false, true>(p, geom->batch, nchunk_grid, st); break;
-            case 3: rc = launch_split_g<3, true, false, true>(p, geom->batch, nchunk_grid, st); break;
-            default: rc = launch_split_g<4, true, false, true>(p, geom->batch, nchunk_grid, st); break;
-        }
+        rc = launch_split<true, false, true>(p, geom->batch, G, nchunk_grid, st);
     } else {
         rc = no_v ? launch_score_split(p, geom->batch, G, nchunk_grid, st)
                   : launch_split<true, false>(p, geom->batch, G, nchunk_grid, st);
@@ -1877,7 +1876,7 @@ int full_attn_stage(const rk_geom* geom, const void* q, rk_kv full, const int32_
 }
 
 // The pooled scores and histograms of n_layers layers whose full attention ran with defer_pool,
-// each on its own workspace.
+// each on its own workspace, with the launch shape deferred_split_workgroups gives.
 int pool_batched_stage(const rk_geom* geom, int n_layers, const Workspace* wss, const int32_t* seq_lens, int32_t max_len,
                        int64_t full_capacity, int pool_half, int agg, const int32_t* const* pred, int32_t pred_val,
                        hipStream_t st) {
@@ -1887,6 +1886,8 @@ int pool_batched_stage(const rk_geom* geom, int n_layers, const Workspace* wss, 
     p.seq_lens = seq_lens;
     p.max_rows2 = max_len;
     p.cap2 = (int32_t)full_capacity;
+    p.nch = deferred_split_workgroups(geom, max_len);
+    p.ragged_batch = ragged_batch_of(geom);
     p.Hq = geom->n_q_heads; p.Hkv = geom->n_kv_heads;
     p.w_inter = G == 4 ? 1 : 0;              // how full_attn_stage(defer_pool) left the raw scores
     p.pred_val = pred_val;

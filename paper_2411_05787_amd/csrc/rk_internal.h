@@ -48,8 +48,10 @@ static inline int split_workgroups(int64_t max_rows, int64_t n_problems, int lim
     if (per < 1) per = 1;
     const int64_t tiles = (max_rows + 31) / 32;
     auto rounds = [&](int64_t nch) { return (tiles + 4 * nch - 1) / (4 * nch); };
-    for (int64_t nch = per; nch >= 1 && 8 * nch >= 5 * per; --nch)
-        if ((nch * n_problems) % kComputeUnits == 0 && rounds(nch) == rounds(per)) return (int)nch;
+    // (a total that is a multiple of kComputeUnits: every unit-th count)
+    const int64_t low = n_problems & -n_problems, unit = low < kComputeUnits ? kComputeUnits / low : 1;
+    for (int64_t nch = per / unit * unit; nch >= 1 && 8 * nch >= 5 * per; nch -= unit)
+        if (rounds(nch) == rounds(per)) return (int)nch;
     return (int)per;
 }
 
@@ -263,13 +265,37 @@ static inline int max_chunks_for(int64_t max_len) {
 // launch's fixed costs (start, the merge across the wavefronts, the partial results) a larger share
 // and make a ragged last round (2.67 tiles per wavefront with 768 workgroups at 32k rows) cost more;
 // long rows want more loads in flight.
-static inline int emit_split_workgroups(const rk_geom* g, int64_t max_len) {
-    const int64_t problems = (int64_t)g->batch * g->n_kv_heads;
-    const int64_t tiles = (max_len + 31) / 32 * problems;
+static inline int emit_split_target(const rk_geom* g, int64_t max_len) {
+    const int64_t tiles = (max_len + 31) / 32 * g->batch * g->n_kv_heads;
     int64_t target = (tiles / 16 + kComputeUnits / 2) / kComputeUnits * kComputeUnits;      // 16 tiles per workgroup: 4 per wavefront
     if (target < kComputeUnits) target = kComputeUnits;
     if (target > 4 * kComputeUnits) target = 4 * kComputeUnits;
-    return split_workgroups(max_len, problems, kMaxChunks, (int)target);
+    return (int)target;
+}
+static inline int emit_split_workgroups(const rk_geom* g, int64_t max_len) {
+    return split_workgroups(max_len, (int64_t)g->batch * g->n_kv_heads, kMaxChunks, emit_split_target(g, max_len));
+}
+
+// Workgroups per (sequence, KV head) of the same kernel where it merges its partial results itself (nothing but the
+// output merge would follow it): no more than there are slots for.  That form is compiled for two workgroups per CU:
+// a launch is resident as a whole (512, merged by slices) or a multiple of that (1024), never in one and a half rounds
+// (768), and groups of more than 4 heads, whose merge by the last arrival takes two heads per wavefront, stay with
+// 512.  Full step, us per layer at 768 or 1024 -> 512 workgroups: 6 ragged sequences of 10k rows, 4 KV heads of 7: 57.4 ->
+// 47.7; 2 of 24000 rows, 8 of 4: 64.7 -> 53.6; 16 ragged of 5.5k rows, 4 of 7: 89.7 -> 82.9; 16 ragged of 10k, 8 of 4,
+// stays with 1024: 186.0 against 188.4.
+// 0: compute units would be left without work (few, long rows; small batches), and the merge stays a launch of its own.
+static inline int inside_split_workgroups(const rk_geom* g, int64_t max_len) {
+    const int64_t problems = (int64_t)g->batch * g->n_kv_heads;
+    int target = emit_split_target(g, max_len);
+    if (target > 2 * kComputeUnits && (target < 4 * kComputeUnits || g->n_q_heads > 4 * g->n_kv_heads)) target = 2 * kComputeUnits;
+    const int n = split_workgroups(max_len, problems, kMergeChunks, target);
+    if ((g->batch > 1 || max_len > (int64_t)kMergeChunks * kMinChunk) && n * problems < kComputeUnits) return 0;
+    return n;
+}
+// ... and of a full step whose pooling is deferred: the pooling kernels must be told the same number.
+static inline int deferred_split_workgroups(const rk_geom* g, int64_t max_len) {
+    const int inside = inside_split_workgroups(g, max_len);
+    return inside > 0 ? inside : emit_split_workgroups(g, max_len);
 }
 
 static inline Workspace carve(const rk_geom* g, int64_t max_len, int64_t max_k, void* base) {

@@ -133,6 +133,7 @@ def test_group_maximum_by_one_exponential_is_exact(rk, shape, spread):
 # the workgroups of a launch over 2..64 sequences are shared out by length, with exact remainders
 RAGGED = [("two_far_apart", [9000, 1]), ("three_equal", [1280, 1280, 1280]), ("ties", [300, 300, 301, 0, 299, 300]),
           ("one_long_of_64", [30000] + [1, 0, 129] * 21), ("steps_64", [128 * i for i in range(64)]), ("beyond_64", [200] * 64 + [4000]),
+          ("one_short", [700]), ("one_of_8192", [8192]), ("one_of_8193", [8193]), ("four_of_9000", [9000, 8999, 8193, 9000]),
           ("primes", [7919, 6007, 4999, 3001, 2003, 1009, 503, 251, 127, 61, 31])]
 
 
