@@ -251,9 +251,8 @@ class RefreshKVModel:
         if not q.is_cuda or q.dtype != torch.bfloat16 or not q.is_contiguous() or \
                 tuple(q.shape) != (n, g.batch, g.n_q_heads, g.head_dim):
             raise ValueError("q must be a contiguous bf16 GPU tensor [n_layers, batch, n_q_heads, head_dim]")
-        base, step_bytes = q.data_ptr(), q.stride(0) * 2
-        for l in range(n):
-            self._q_ptrs[l] = base + l * step_bytes
+        base, step_bytes = q.data_ptr(), g.batch * g.n_q_heads * g.head_dim * 2
+        self._q_ptrs[:] = range(base, base + n * step_bytes, step_bytes)
         if getattr(self, "_batched_ptrs", None) is not None:
             kind = rk.rk_decode_step_batched(g, self.sched, t, self._layers, self._q_ptrs, self._out_ptrs, self.seq_lens,
                                              self.max_len, max(self.recent_bound, 1), self._batched_ptrs,
