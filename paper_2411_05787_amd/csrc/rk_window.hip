@@ -15,7 +15,7 @@
 // Storing the raw scores of every query instead (one pass) would write and re-read
 // W * Hq * len * 4 bytes: more than the second pass over K from W = 8 on at the usual shapes.
 //
-// Per tile of 64 rows the scores of all columns come from the matrix cores
+// Per tile of 16 to 64 rows the scores of all columns come from the matrix cores
 // (v_mfma_f32_16x16x32_bf16, K rows as the 16-row operand straight from global memory in
 // operand layout; the queries, 16 columns at a time, from LDS).  Column c = i * Gp + gi: query
 // i of the window, head gi of the GQA group, Gp = G rounded up to a power of two so that a lane
@@ -34,7 +34,7 @@ struct WindowParams {
     const int32_t* seq_lens; int32_t max_rows;
     int32_t W, G, gp_shift;            // Gp = 1 << gp_shift
     int32_t ncb;                       // blocks of 16 columns
-    int32_t nch, Hq, Hkv;
+    int32_t nch, wg_rows, Hq, Hkv;     // workgroups per (sequence, KV head); rows a workgroup takes per step
     float scale;
     float* part;                       // fp32 [B*Hkv][nch][ncb*16][2]  (max, sum) per workgroup and column
     float* lse;                        // fp32 [B*Hkv][ncb*16][2]       lse as hi + lo
@@ -42,13 +42,11 @@ struct WindowParams {
     const int32_t* pred; int32_t pred_val;
 };
 
-constexpr int kWinWaves = 8, kWinTiles = 4, kWinRows = 16 * kWinTiles;     // rows per wavefront and step: 64
-constexpr int kWinThreads = kWinWaves * 64;
-constexpr int kWinTargetWgs = 512;     // workgroups a pass aims for: two per CU
+constexpr int kWinTargetWgs = 512;     // workgroups of eight wavefronts a pass aims for: two per CU
 constexpr int kQStride = kD + 8;       // bf16 elements between columns in LDS: 272 bytes, conflict-free 16-byte reads
 
-__device__ __forceinline__ int window_workgroups(int n_rows, int nch) {
-    return max(1, min(nch, (n_rows + kWinWaves * kWinRows - 1) / (kWinWaves * kWinRows)));
+__device__ __forceinline__ int window_workgroups(const WindowParams& p, int n_rows) {
+    return max(1, min(p.nch, (n_rows + p.wg_rows - 1) / p.wg_rows));
 }
 
 // Last row that column `col` may see (-1: the column does not exist).
@@ -70,23 +68,26 @@ __device__ __forceinline__ uint4 query_piece(const WindowParams& p, int b, int g
     const int i = col >> p.gp_shift, gi = col & ((1 << p.gp_shift) - 1);
     return *reinterpret_cast<const uint4*>(p.q + (((int64_t)b * p.W + i) * p.Hq + (int64_t)g * p.G + gi) * kD + piece * 8);
 }
+template <int NT>
 __device__ __forceinline__ void request_queries(const WindowParams& p, int b, int g, int n, uint4 (&held)[kQHeld]) {
 #pragma unroll
-    for (int u = 0; u < kQHeld; ++u) held[u] = query_piece(p, b, g, n, u * kWinThreads + threadIdx.x);
+    for (int u = 0; u < kQHeld; ++u) held[u] = query_piece(p, b, g, n, u * NT + threadIdx.x);
 }
+template <int NT>
 __device__ __forceinline__ void store_queries(const WindowParams& p, int b, int g, int n, int ncol, const uint4 (&held)[kQHeld],
                                               uint16_t* sQ) {
     auto put = [&](int x, const uint4 u) { *reinterpret_cast<uint4*>(sQ + (x >> 4) * kQStride + (x & 15) * 8) = u; };
 #pragma unroll
     for (int u = 0; u < kQHeld; ++u)
-        if (u * kWinThreads + (int)threadIdx.x < ncol * 16) put(u * kWinThreads + threadIdx.x, held[u]);
-    for (int x = kQHeld * kWinThreads + threadIdx.x; x < ncol * 16; x += kWinThreads) put(x, query_piece(p, b, g, n, x));
+        if (u * NT + (int)threadIdx.x < ncol * 16) put(u * NT + threadIdx.x, held[u]);
+    for (int x = kQHeld * NT + threadIdx.x; x < ncol * 16; x += NT) put(x, query_piece(p, b, g, n, x));
 }
 
-// Rows r .. r + 63 of K in operand layout (rows past the end repeat the last row; masked later).
-__device__ __forceinline__ void load_k_rows(u32x4 (&dst)[kWinTiles][4], const uint16_t* kb, int r, int n16, int n) {
+// Rows r .. r + 16 T - 1 of K in operand layout (rows past the end repeat the last row; masked later).
+template <int T>
+__device__ __forceinline__ void load_k_rows(u32x4 (&dst)[T][4], const uint16_t* kb, int r, int n16, int n) {
 #pragma unroll
-    for (int t = 0; t < kWinTiles; ++t) {
+    for (int t = 0; t < T; ++t) {
         const int row = min(r + t * 16 + n16, n - 1);
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk)
@@ -96,15 +97,15 @@ __device__ __forceinline__ void load_k_rows(u32x4 (&dst)[kWinTiles][4], const ui
 
 // Scores of these rows against the 16 columns of block cb: s[t][i] is row r + 16 t + 4 c4 + i of
 // column cb * 16 + n16, scaled; MASKED: -inf beyond `limit`.
-template <bool MASKED>
-__device__ __forceinline__ void block_scores(const u32x4 (&k)[kWinTiles][4], const uint16_t* sQ, int cb, int n16, int c4,
-                                             int r, int limit, float scale, float (&s)[kWinTiles][4]) {
+template <bool MASKED, int T>
+__device__ __forceinline__ void block_scores(const u32x4 (&k)[T][4], const uint16_t* sQ, int cb, int n16, int c4,
+                                             int r, int limit, float scale, float (&s)[T][4]) {
     bf16x8 qa[4];
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk)
         qa[kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(sQ + (cb * 16 + n16) * kQStride + (kk * 4 + c4) * 8));
 #pragma unroll
-    for (int t = 0; t < kWinTiles; ++t) {
+    for (int t = 0; t < T; ++t) {
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk)
@@ -126,66 +127,80 @@ __device__ __forceinline__ void merge_ml(float& m, float& l, float m2, float l2)
 
 extern __shared__ __attribute__((aligned(16))) unsigned char window_lds[];
 
-// Both passes: a wavefront takes 64 rows at a time and goes through the blocks of columns with them in
-// registers, so that a block's queries are read from LDS, and its running state is updated, once per 64
+// Both passes: a wavefront takes 16 T rows at a time and goes through the blocks of columns with them in
+// registers, so that a block's queries are read from LDS, and its running state is updated, once per 16 T
 // rows; eight wavefronts share one copy of the queries, and two such workgroups per CU (four wavefronts
 // per SIMD, up to 128 columns) hide one another's chains; the rows are requested behind the queries and before
-// anything waits, so at 32768 rows of 8 KV heads all of K is in flight at once.  The causal masks are worked out only for rows
-// that some query does not see.  Bound: the vector instructions of 8 exponentials per 32 x 16 scores from about 16
-// queries on, memory below.  Measured at 32 heads over 8,
-// 32768 rows: 32 queries 41.7 + 26.7 -> 25.1 + 20.8 us (32-row tiles, 4 wavefronts per workgroup before), 1 query
-// 16.8 + 15.5 us (67 MB: 4.2 TB/s); 131072 rows, 32 queries 65.7 + 60.3 us.  The queries requested behind the rows
-// instead of before them: 27.3 + 23.9 us.
+// anything waits, so at 32768 rows of 8 KV heads all of K is in flight at once.  The causal masks are worked out only
+// for rows that some query does not see.  Bound: the vector instructions of 8 exponentials per 32 x 16 scores from about
+// 16 queries on, memory below.  The forms (window_form):
+//   T = 4, S = 1  rows enough to give every wavefront of the chip 64; us at 32 heads over 8, 32768 rows, 32 queries: 41.7 +
+//                 26.7 (32 rows, 4 wavefronts per workgroup, 3 per CU) -> 25.1 + 20.8; the queries requested behind the
+//                 rows instead of before them: 27.3 + 23.9
+//   T = 2, S = 2  up to 32 columns, where a step is short and bound by memory: two sets of 32 rows, each requested
+//                 again as soon as it is used, 4 wavefronts per workgroup (finer: the last round of a row is not full;
+//                 8 wavefronts and 4 sets of 16 rows were 2-3% slower at 33000 to 60000 rows)
+//   T = 1, S = 1  few rows: more, shorter wavefronts (3000 rows, 32 queries, the whole case: 45.6 with T = 4, 34.9)
 //
 // Pass 1.  The running (max, sum) of a lane's column in every block lives in LDS (one float2 per
 // lane and block), so that the number of blocks is a run-time value and the register count does
 // not grow with the window.
-template <bool MASKED>
-__device__ __forceinline__ void lse_rows(const WindowParams& p, const u32x4 (&k)[kWinTiles][4], const uint16_t* sQ,
+template <bool MASKED, int T, int NT>
+__device__ __forceinline__ void lse_rows(const WindowParams& p, const u32x4 (&k)[T][4], const uint16_t* sQ,
                                          float2* sRun, int r, int n, bool first) {
     const int lane = threadIdx.x & 63, n16 = lane & 15, c4 = lane >> 4;
 #pragma unroll 1
     for (int cb = 0; cb < p.ncb; ++cb) {
-        float s[kWinTiles][4];
-        block_scores<MASKED>(k, sQ, cb, n16, c4, r, MASKED ? column_limit(p, cb * 16 + n16, n) : 0, p.scale, s);
+        float s[T][4];
+        block_scores<MASKED, T>(k, sQ, cb, n16, c4, r, MASKED ? column_limit(p, cb * 16 + n16, n) : 0, p.scale, s);
         float mx = s[0][0];
 #pragma unroll
-        for (int e = 1; e < 4 * kWinTiles; ++e) mx = fmaxf(mx, s[e >> 2][e & 3]);
-        const float2 run = first ? make_float2(-INFINITY, 0.f) : sRun[cb * kWinThreads + threadIdx.x];
+        for (int e = 1; e < 4 * T; ++e) mx = fmaxf(mx, s[e >> 2][e & 3]);
+        const float2 run = first ? make_float2(-INFINITY, 0.f) : sRun[cb * NT + threadIdx.x];
         const float m_new = fmaxf(run.x, mx);
         const float ref = m_new == -INFINITY ? 0.f : m_new;      // nothing seen yet: every term is 2^-inf = 0
         float ps = 0.f;
 #pragma unroll
-        for (int e = 0; e < 4 * kWinTiles; ++e) ps += fast_exp2((s[e >> 2][e & 3] - ref) * kLog2e);
-        sRun[cb * kWinThreads + threadIdx.x] = make_float2(m_new, run.y * fast_exp2((run.x - ref) * kLog2e) + ps);
+        for (int e = 0; e < 4 * T; ++e) ps += fast_exp2((s[e >> 2][e & 3] - ref) * kLog2e);
+        sRun[cb * NT + threadIdx.x] = make_float2(m_new, run.y * fast_exp2((run.x - ref) * kLog2e) + ps);
     }
 }
 
-__global__ __launch_bounds__(kWinThreads, 4)
+template <int T, int S, int NW>
+__global__ __launch_bounds__(NW * 64, 4)
 void window_lse_kernel(const WindowParams p) {
-    constexpr int NW = kWinWaves;
     const int ncb = p.ncb, ncol = ncb * 16;
     const int c = blockIdx.x, g = blockIdx.y, b = blockIdx.z;
     if (p.pred != nullptr && p.pred[b] != p.pred_val) return;
     const int n = min(max(min(p.seq_lens[b], p.cap), 0), p.max_rows);
-    if (n == 0 || c >= window_workgroups(n, p.nch)) return;
+    if (n == 0 || c >= window_workgroups(p, n)) return;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int n16 = lane & 15, c4 = lane >> 4;
     uint16_t* sQ = reinterpret_cast<uint16_t*>(window_lds);
-    float2* sRun = reinterpret_cast<float2*>(window_lds + (size_t)ncol * kQStride * 2);   // [ncb][kWinThreads]
+    float2* sRun = reinterpret_cast<float2*>(window_lds + (size_t)ncol * kQStride * 2);   // [ncb][NW * 64]
 
     const uint16_t* kb = p.k + (int64_t)b * p.s_b + (int64_t)g * p.s_h + c4 * 8;
-    const int step = p.nch * NW * kWinRows, r0 = (c * NW + w) * kWinRows;
+    const int step = p.nch * NW * 16 * T, r0 = (c * NW + w) * 16 * T;
     uint4 held[kQHeld];
-    u32x4 k[kWinTiles][4];
-    request_queries(p, b, g, n, held);
-    if (r0 < n) load_k_rows(k, kb, r0, n16, n);
-    store_queries(p, b, g, n, ncol, held, sQ);
+    u32x4 k[S][T][4];
+    request_queries<NW * 64>(p, b, g, n, held);
+#pragma unroll
+    for (int x = 0; x < S; ++x)
+        if (r0 + x * step < n) load_k_rows<T>(k[x], kb, r0 + x * step, n16, n);
+    store_queries<NW * 64>(p, b, g, n, ncol, held, sQ);
     __syncthreads();
-    for (int r = r0; r < n; r += step) {
-        if (r != r0) load_k_rows(k, kb, r, n16, n);
-        if (r + kWinRows > n - p.W) lse_rows<true>(p, k, sQ, sRun, r, n, r == r0);
-        else                        lse_rows<false>(p, k, sQ, sRun, r, n, r == r0);
+    auto rows = [&](const u32x4 (&x)[T][4], int r) {
+        if (r + 16 * T > n - p.W) lse_rows<true, T, NW * 64>(p, x, sQ, sRun, r, n, r == r0);
+        else                      lse_rows<false, T, NW * 64>(p, x, sQ, sRun, r, n, r == r0);
+    };
+    for (int r = r0; r < n;) {
+#pragma unroll
+        for (int x = 0; x < S; ++x) {
+            if (r >= n) break;
+            rows(k[x], r);
+            if (r + S * step < n) load_k_rows<T>(k[x], kb, r + S * step, n16, n);
+            r += step;
+        }
     }
     // fold the four row groups of the wavefront, then the wavefronts (through the LDS of the queries)
     __syncthreads();
@@ -193,7 +208,7 @@ void window_lse_kernel(const WindowParams p) {
     float* sL = sM + NW * ncol;
     static_assert(2 * NW * sizeof(float) <= kQStride * sizeof(uint16_t), "the wavefronts' pairs fit where the queries were");
     for (int cb = 0; cb < ncb; ++cb) {
-        const float2 run = r0 < n ? sRun[cb * kWinThreads + tid] : make_float2(-INFINITY, 0.f);
+        const float2 run = r0 < n ? sRun[cb * NW * 64 + tid] : make_float2(-INFINITY, 0.f);
         const float M = max_xor32(max_xor16(run.x));
         const float a = run.x == -INFINITY ? 0.f : fast_exp2((run.x - M) * kLog2e);
         const float L = sum_xor32(sum_xor16(run.y * a));
@@ -202,7 +217,7 @@ void window_lse_kernel(const WindowParams p) {
     __syncthreads();
     const int64_t bg = (int64_t)b * p.Hkv + g;
     float* part = p.part + ((bg * p.nch + c) * ncol) * 2;
-    for (int col = tid; col < ncol; col += kWinThreads) {
+    for (int col = tid; col < ncol; col += NW * 64) {
         float M = sM[col], L = sL[col];
 #pragma unroll
         for (int ww = 1; ww < NW; ++ww) merge_ml(M, L, sM[ww * ncol + col], sL[ww * ncol + col]);
@@ -220,7 +235,7 @@ void window_lse_merge_kernel(const WindowParams p) {
     if (p.pred != nullptr && p.pred[b] != p.pred_val) return;
     const int n = min(max(min(p.seq_lens[b], p.cap), 0), p.max_rows);
     if (n == 0) return;
-    const int nchunks = window_workgroups(n, p.nch);
+    const int nchunks = window_workgroups(p, n);
     const int ncol = p.ncb * 16;
     const int n16 = threadIdx.x & 15, cl = threadIdx.x >> 4;
     const int col = cb * 16 + n16;
@@ -267,29 +282,29 @@ __device__ __forceinline__ float sum_queries(float v, int gp) {
 }
 
 // Pass 2.
-template <bool MASKED>
-__device__ __forceinline__ void vote_rows(const WindowParams& p, const u32x4 (&k)[kWinTiles][4], const uint16_t* sQ,
+template <bool MASKED, int T>
+__device__ __forceinline__ void vote_rows(const WindowParams& p, const u32x4 (&k)[T][4], const uint16_t* sQ,
                                           const float2* sLse, float* vrow, int r, int n) {
     const int lane = threadIdx.x & 63, n16 = lane & 15, c4 = lane >> 4;
-    float v[kWinTiles][4];
+    float v[T][4];
 #pragma unroll
-    for (int e = 0; e < 4 * kWinTiles; ++e) v[e >> 2][e & 3] = 0.f;
+    for (int e = 0; e < 4 * T; ++e) v[e >> 2][e & 3] = 0.f;
 #pragma unroll 1
     for (int cb = 0; cb < p.ncb; ++cb) {
-        float s[kWinTiles][4];
-        block_scores<MASKED>(k, sQ, cb, n16, c4, r, MASKED ? column_limit(p, cb * 16 + n16, n) : 0, p.scale, s);
+        float s[T][4];
+        block_scores<MASKED, T>(k, sQ, cb, n16, c4, r, MASKED ? column_limit(p, cb * 16 + n16, n) : 0, p.scale, s);
         const float2 lse = sLse[cb * 16 + n16];
 #pragma unroll
-        for (int e = 0; e < 4 * kWinTiles; ++e)            // s = -inf (masked) and lse = inf (no such column) give 2^-inf = 0
+        for (int e = 0; e < 4 * T; ++e)            // s = -inf (masked) and lse = inf (no such column) give 2^-inf = 0
             v[e >> 2][e & 3] += fast_exp2(((s[e >> 2][e & 3] - lse.x) - lse.y) * kLog2e);
     }
     // lanes n16, n16 + Gp, n16 + 2 Gp ... hold the same head for different queries
     const int gp = 1 << p.gp_shift;
 #pragma unroll
-    for (int e = 0; e < 4 * kWinTiles; ++e) v[e >> 2][e & 3] = sum_queries(v[e >> 2][e & 3], gp);
+    for (int e = 0; e < 4 * T; ++e) v[e >> 2][e & 3] = sum_queries(v[e >> 2][e & 3], gp);
     if (n16 < p.G) {
 #pragma unroll
-        for (int t = 0; t < kWinTiles; ++t) {
+        for (int t = 0; t < T; ++t) {
             const int first = r + t * 16 + 4 * c4;
             if (p.v_vec && first + 4 <= n) {
                 *reinterpret_cast<float4*>(vrow + first) = make_float4(v[t][0], v[t][1], v[t][2], v[t][3]);
@@ -302,14 +317,14 @@ __device__ __forceinline__ void vote_rows(const WindowParams& p, const u32x4 (&k
     }
 }
 
-__global__ __launch_bounds__(kWinThreads, 4)
+template <int T, int S, int NW>
+__global__ __launch_bounds__(NW * 64, 4)
 void window_vote_kernel(const WindowParams p) {
-    constexpr int NW = kWinWaves;
     const int ncol = p.ncb * 16;
     const int c = blockIdx.x, g = blockIdx.y, b = blockIdx.z;
     if (p.pred != nullptr && p.pred[b] != p.pred_val) return;
     const int n = min(max(min(p.seq_lens[b], p.cap), 0), p.max_rows);
-    if (n == 0 || c >= window_workgroups(n, p.nch)) return;
+    if (n == 0 || c >= window_workgroups(p, n)) return;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int n16 = lane & 15, c4 = lane >> 4;
     uint16_t* sQ = reinterpret_cast<uint16_t*>(window_lds);
@@ -317,33 +332,45 @@ void window_vote_kernel(const WindowParams p) {
     const int64_t bg = (int64_t)b * p.Hkv + g;
 
     const uint16_t* kb = p.k + (int64_t)b * p.s_b + (int64_t)g * p.s_h + c4 * 8;
-    const int step = p.nch * NW * kWinRows, r0 = (c * NW + w) * kWinRows;
+    const int step = p.nch * NW * 16 * T, r0 = (c * NW + w) * 16 * T;
     uint4 held[kQHeld];
-    u32x4 k[kWinTiles][4];
+    u32x4 k[S][T][4];
     const float2* lse_of = reinterpret_cast<const float2*>(p.lse) + bg * ncol;
-    const float2 my_lse = tid < ncol ? lse_of[tid] : make_float2(0.f, 0.f);      // (at most 256 columns)
-    request_queries(p, b, g, n, held);
-    if (r0 < n) load_k_rows(k, kb, r0, n16, n);
-    store_queries(p, b, g, n, ncol, held, sQ);
+    const float2 my_lse = tid < ncol ? lse_of[tid] : make_float2(0.f, 0.f);
+    static_assert(NW * 64 >= 32 * RK_MAX_GROUP, "a thread per column");
+    request_queries<NW * 64>(p, b, g, n, held);
+#pragma unroll
+    for (int x = 0; x < S; ++x)
+        if (r0 + x * step < n) load_k_rows<T>(k[x], kb, r0 + x * step, n16, n);
+    store_queries<NW * 64>(p, b, g, n, ncol, held, sQ);
     if (tid < ncol) sLse[tid] = my_lse;
     __syncthreads();
     float* vrow = p.votes + ((int64_t)b * p.Hq + (int64_t)g * p.G + (n16 < p.G ? n16 : 0)) * p.v_stride;
-    for (int r = r0; r < n; r += step) {
-        if (r != r0) load_k_rows(k, kb, r, n16, n);
-        if (r + kWinRows > n - p.W) vote_rows<true>(p, k, sQ, sLse, vrow, r, n);
-        else                        vote_rows<false>(p, k, sQ, sLse, vrow, r, n);
+    auto rows = [&](const u32x4 (&x)[T][4], int r) {
+        if (r + 16 * T > n - p.W) vote_rows<true, T>(p, x, sQ, sLse, vrow, r, n);
+        else                      vote_rows<false, T>(p, x, sQ, sLse, vrow, r, n);
+    };
+    for (int r = r0; r < n;) {
+#pragma unroll
+        for (int x = 0; x < S; ++x) {
+            if (r >= n) break;
+            rows(k[x], r);
+            if (r + S * step < n) load_k_rows<T>(k[x], kb, r + S * step, n16, n);
+            r += step;
+        }
     }
 }
 
+template <int T, int S, int NW>
 static int launch_window(const WindowParams& p, int batch, hipStream_t st) {
     const size_t ncol = (size_t)p.ncb * 16;
-    const size_t lds1 = ncol * kQStride * 2 + (size_t)p.ncb * kWinThreads * sizeof(float2);
+    const size_t lds1 = ncol * kQStride * 2 + (size_t)p.ncb * NW * 64 * sizeof(float2);
     const size_t lds2 = ncol * kQStride * 2 + ncol * sizeof(float2);
     static size_t lds_allowed = 48 * 1024;       // grows monotonically; lds1 > lds2
     if (lds1 > lds_allowed) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&window_lse_kernel),
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&window_lse_kernel<T, S, NW>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds1) != hipSuccess ||
-            hipFuncSetAttribute(reinterpret_cast<const void*>(&window_vote_kernel),
+            hipFuncSetAttribute(reinterpret_cast<const void*>(&window_vote_kernel<T, S, NW>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds1) != hipSuccess) {
             (void)hipGetLastError();
             return RK_ERR_UNSUPPORTED;
@@ -351,19 +378,19 @@ static int launch_window(const WindowParams& p, int batch, hipStream_t st) {
         lds_allowed = lds1;
     }
     dim3 grid(p.nch, p.Hkv, batch);
-    hipLaunchKernelGGL(window_lse_kernel, grid, dim3(kWinThreads), lds1, st, p);
+    hipLaunchKernelGGL((window_lse_kernel<T, S, NW>), grid, dim3(NW * 64), lds1, st, p);
     int rc = launch_status();
     if (rc != RK_OK) return rc;
     hipLaunchKernelGGL(window_lse_merge_kernel, dim3(p.ncb, p.Hkv, batch), dim3(256), 0, st, p);
     if ((rc = launch_status()) != RK_OK) return rc;
-    hipLaunchKernelGGL(window_vote_kernel, grid, dim3(kWinThreads), lds2, st, p);
+    hipLaunchKernelGGL((window_vote_kernel<T, S, NW>), grid, dim3(NW * 64), lds2, st, p);
     return launch_status();
 }
 
-// Workgroups per (sequence, KV head) of the two passes.
-static int window_split(int64_t max_rows, int64_t problems, int limit) {
+// Workgroups per (sequence, KV head) of the forms with eight wavefronts.
+static int window_split(int64_t max_rows, int64_t problems, int limit, int wg_rows) {
     int64_t per = kWinTargetWgs / problems;
-    const int64_t stretches = (max_rows + kWinWaves * kWinRows - 1) / (kWinWaves * kWinRows);
+    const int64_t stretches = (max_rows + wg_rows - 1) / wg_rows;
     if (per > stretches) per = stretches;
     if (per > limit) per = limit;
     return per < 1 ? 1 : (int)per;
@@ -406,7 +433,10 @@ extern "C" int rk_window_select(const rk_geom* geom, const void* q_win, int32_t 
     p.k = (const uint16_t*)full.k; p.s_b = full.stride_b; p.s_h = full.stride_h; p.cap = (int32_t)full.capacity;
     p.seq_lens = seq_lens; p.max_rows = max_len;
     p.W = window; p.G = G; p.gp_shift = gp_shift;
-    p.nch = window_split(max_len, (int64_t)geom->batch * geom->n_kv_heads, ws.max_chunks);
+    const int64_t problems = (int64_t)geom->batch * geom->n_kv_heads;
+    const bool few_rows = max_len * problems <= (int64_t)kWinTargetWgs * 128, narrow = ncb <= 2;
+    p.wg_rows = few_rows || narrow ? 128 : 512;
+    p.nch = narrow && !few_rows ? split_workgroups(max_len, problems, ws.max_chunks) : window_split(max_len, problems, ws.max_chunks, p.wg_rows);
     p.Hq = geom->n_q_heads; p.Hkv = geom->n_kv_heads;
     p.scale = geom->scale;
     p.part = ws.part_o; p.lse = ws.part_ml;
@@ -415,7 +445,8 @@ extern "C" int rk_window_select(const rk_geom* geom, const void* q_win, int32_t 
     p.v_vec = ((p.v_stride % 4 == 0) && aligned16(p.votes)) ? 1 : 0;
     p.pred = pred; p.pred_val = pred_val;
     p.ncb = ncb;
-    rc = launch_window(p, geom->batch, st);
+    rc = few_rows ? launch_window<1, 1, 8>(p, geom->batch, st)
+       : narrow   ? launch_window<2, 2, 4>(p, geom->batch, st) : launch_window<4, 1, 8>(p, geom->batch, st);
     if (rc != RK_OK) return rc;
     if ((rc = pool_stage(geom, p.votes, p.v_stride, seq_lens, max_len, pool_w, agg, pred, pred_val, ws, st)) != RK_OK) return rc;
     return select_stage(geom, seq_lens, max_len, k, idx, sel_scores, pred, pred_val, ws, st);
