@@ -71,6 +71,7 @@ struct AttnParams {
     float* trig_q_ref; float* trig_sim; int32_t* trig_need; float trig_threshold;   // TRIG only: the query-similarity test
     int32_t ragged_batch;              // != 0 (= batch): workgroups are shared out by length, see ragged_share_lane
     int32_t share_cap;                 // ... at most this many to a sequence
+    int32_t* n_attend;                 // APPEND only: [B], rows attended over, for the kernel that follows
     int32_t slice_merge;               // TAGGED: every workgroup merges a slice of the output (all workgroups of the launch are resident together)
     int32_t slice_spin;                // ... re-reading rows still in flight at most this often before it leaves its slice to the last one
 };
@@ -605,6 +606,11 @@ constexpr int kSliceChunks = 20, kSliceChunks4 = 64;   // the merge by slices se
 // follow (the full step under that predicate).  Where the test asks for a full step the averaged
 // query becomes the new reference; every workgroup of the sequence has read the old one by then:
 // each takes a ticket after its test, and the last one stores.
+
+// EMIT with TWO_SEG (APPEND below): the step of the H2O policy.  The first segment is the policy's cache,
+// seq_lens[b] rows of it (the rows kept so far), the second the new token's row, read where the caller has
+// it: k2 / v2 with one row per (sequence, KV head).  n_sel is the most rows the step attends over; a cache that
+// is over it already (outside the policy's contract) is cut there and the new row is left out.
 template <int G, int NW, bool EMIT, bool TWO_SEG, bool LAZY = false, bool TAGGED = !EMIT, bool TRIG = false>
 __global__ __launch_bounds__(NW * 64, (EMIT && !TAGGED) ? RK_EMIT_OCCUPANCY : 2)
 void attn_split_kernel(const uint16_t* k_first, const uint16_t* v_first, int64_t s_b_and_tail, int32_t s_h, int32_t spec_rows,
@@ -614,6 +620,8 @@ void attn_split_kernel(const uint16_t* k_first, const uint16_t* v_first, int64_t
     // (EMIT with TAGGED: the scores go out as usual, and the output is merged inside the kernel all the same; the
     // per-chunk (max, sum) pairs are still stored for the kernels that turn the scores into weights)
     static_assert(!TRIG || (TWO_SEG && !LAZY), "the trigger is tested by the partial step");
+    constexpr bool APPEND = EMIT && TWO_SEG;
+    static_assert(!APPEND || (!TAGGED && !TRIG && !LAZY), "merged by the kernel that updates the totals");
     // The leading arguments repeat what the first loads need (the cache that holds the first rows,
     // its strides, the two length arrays, the predicate, the call numbers): 16 dwords that the command processor
     // hands over in registers at wavefront launch (kernel-argument preload), so neither the first
@@ -724,7 +732,7 @@ void attn_split_kernel(const uint16_t* k_first, const uint16_t* v_first, int64_t
         uint4 qu[4] = {make_uint4(0, 0, 0, 0), make_uint4(0, 0, 0, 0), make_uint4(0, 0, 0, 0), make_uint4(0, 0, 0, 0)};
         if (spec_rows >= 0) {
             len_raw = seq_lens[b];
-            if (TWO_SEG) tail_raw = tail_start[b];
+            if (TWO_SEG && !APPEND) tail_raw = tail_start[b];
             if (TAGGED) epoch = (TRIG ? p.epochs : epochs)[(int64_t)b * n_kv + g];
             const uint16_t* qrow = p.q + ((int64_t)b * p.Hq + (int64_t)g * G + (n16 < G ? n16 : 0)) * kD;
 #pragma unroll
@@ -773,7 +781,11 @@ void attn_split_kernel(const uint16_t* k_first, const uint16_t* v_first, int64_t
     // (device-side lengths are clamped to the allocated rows: no access leaves the caches)
     const int len = min(len_raw, p.cap2);
     int n1 = 0, start2 = 0;
-    if (TWO_SEG) {
+    int slot = 0;
+    if (APPEND) {
+        slot = min(max(len_raw, 0), p.cap1 - 1);
+        n1 = min(slot, p.n_sel);
+    } else if (TWO_SEG) {
         const int t0 = min(max(tail_raw, 0), p.cap2);
         // fixed-size small cache: every row decoded since the refresh pushed out the selected row
         // with the lowest score, i.e. the last one (the small cache is in descending score order)
@@ -782,7 +794,7 @@ void attn_split_kernel(const uint16_t* k_first, const uint16_t* v_first, int64_t
         n1 = max(n1, 0);
         start2 = t0;
     }
-    const int n2 = min(max(len - start2, 0), p.max_rows2);
+    const int n2 = APPEND ? (slot < p.n_sel ? 1 : 0) : min(max(len - start2, 0), p.max_rows2);
     const int n = n1 + n2;
     int nchunks, row1 = n, c_rec = c, n_split;          // partial results in all; end of this workgroup's rows; its slot; workgroups it shares rows with
     if (tail_mode) {
@@ -1034,6 +1046,7 @@ void attn_split_kernel(const uint16_t* k_first, const uint16_t* v_first, int64_t
     // ---- merge the NW wavefronts and publish the partial result of this chunk ----
     const int64_t bg = (int64_t)b * p.Hkv + g;
     // (here and not where the number is known: the waits for the first rows would cover the store as well)
+    if (APPEND && c_rec == 0 && g == 0 && tid == 0) p.n_attend[b] = slot + 1;
     if (kCanBeRagged && p.ragged_batch != 0 && c == 0 && tid == 0) store_chunks(p.counters, bg, nchunks);
     // what the NW wavefronts found for dims d, d + 1 of head gi, as one: max, sum, unnormalised output
     auto combine = [&](int gi, int d, float& M, float& L, float& acc0, float& acc1) {
@@ -1384,52 +1397,6 @@ __device__ __forceinline__ void block_head_out(const AttnParams& p, int G, int b
         p.out[((int64_t)b * p.Hq + h) * kD + tid] = f32_to_bf16(o);
     }
     if (tid == 0) p.lse[(int64_t)b * p.Hq + h] = s.lse[0];
-}
-
-// weight = e^{s - lse} with lse = -nl + ll given as an fp32 pair.  The exponent is formed as an
-// exact fp32 pair (two-sum) minus the low part of lse, so a weight carries the error of its
-// score and of expf only (a plain fp32 subtraction alone would cost up to 5e-7 relative, which
-// is the size of the gaps that decide the selection).
-__device__ __forceinline__ float weight_of(float s, float nl, float ll) {
-    const float hi = s + nl;
-    const float bp = hi - s;
-    const float lo = (s - (hi - bp)) + (nl - bp) - ll;     // s - lse = hi + lo, |lo| << 1
-    const float e = expf(hi);
-    return fmaf(e, lo, e);
-}
-
-// The largest of the G weights of one position.  e^x is monotone, so the head with the largest exponent has
-// the largest weight and one exponential is enough, unless another head's exponent comes so close that the
-// rounding of the weights decides (`tol`: 1.5e-5, which covers the error of weight_of with exponents down to
-// -80, plus what the low parts of the lse differ by) or the weights are near the subnormal range: then
-// (about one wavefront in a thousand) all G are worked out.  The result is that of the maximum over
-// weight_of of all heads, bit for bit.  `lse`: (hi, lo) per head in LDS.  The pooling kernels were bound by these
-// instructions (32 layers of 33k rows, 32 heads: 33 million exponentials, 26 us of vector issue alone); with this and
-// the pooling in pool_tile, us per launch: 32 layers of 33k rows 65 -> 45 - 49, 4 layers of 16 ragged rows 71 -> 54, 28
-// layers of 65k rows (7 heads per group, 3 in 8 layers refreshed) 52 -> 36, one layer of 33k rows 8.6 -> 7.3, of 131k
-// rows 19.5 -> 13.5.
-template <int G>
-__device__ __forceinline__ float max_weight(const float (&s)[G], const float (*lse)[2], float tol) {
-    float best = -INFINITY, second = -INFINITY, bs = 0.f;
-    int bi = 0;
-#pragma unroll
-    for (int gi = 0; gi < G; ++gi) {
-        const float hi = s[gi] - lse[gi][0];
-        const bool up = hi > best;
-        second = __builtin_amdgcn_fmed3f(best, second, hi);
-        best = fmaxf(best, hi);
-        bs = up ? s[gi] : bs;
-        bi = up ? gi : bi;
-    }
-    float w;
-    if (__any(!(best - second > tol) || best < -80.f)) {
-        w = weight_of(s[0], -lse[0][0], lse[0][1]);
-#pragma unroll
-        for (int gi = 1; gi < G; ++gi) w = fmaxf(w, weight_of(s[gi], -lse[gi][0], lse[gi][1]));
-    } else {
-        w = weight_of(bs, -lse[bi][0], lse[bi][1]);
-    }
-    return w;
 }
 
 // Second kernel of a full step that returns the attention weights.  Every workgroup first
@@ -1873,6 +1840,37 @@ int full_attn_stage(const rk_geom* geom, const void* q, rk_kv full, const int32_
         case 8: return launch_finish_pool<8>(p, geom->batch, max_len, ws, pool_half, agg, st);
         default: return RK_ERR_UNSUPPORTED;
     }
+}
+
+// The attention of an H2O step: raw scores to ws.scores, partial results to ws.part_ml / part_o, n_attend[b] set.
+// The launch is sized like the partial step it resembles (the new row has a workgroup of its own where that pays:
+// as the 65th tile of 2049 rows it would be a round of its own); *nch and *tail say how, for the kernel that merges.
+int h2o_attn_stage(const rk_geom* geom, const void* q, const rk_h2o_state& st, const void* k_new, const void* v_new,
+                   int32_t budget, const Workspace& ws, hipStream_t stream, int32_t* nch, int32_t* tail) {
+    const int G = geom->n_q_heads / geom->n_kv_heads;
+    const int64_t problems = (int64_t)geom->batch * geom->n_kv_heads;
+    const int most = ws.max_chunks < kMergeChunks ? ws.max_chunks : kMergeChunks;
+    int own = 0;
+    int n = problems >= 16 ? batched_tagged_workgroups(budget, 1, &own, problems)
+                           : sliced_split_workgroups(budget, 1, &own, problems, most);
+    if (n > most) n = most;
+    if (n + own > most) own = 0;
+    AttnParams p{};
+    p.q = (const uint16_t*)q;
+    p.k1 = (const uint16_t*)st.cache.k; p.v1 = (const uint16_t*)st.cache.v;
+    p.s1_b = st.cache.stride_b; p.s1_h = st.cache.stride_h;
+    p.k2 = (const uint16_t*)k_new; p.v2 = (const uint16_t*)v_new;
+    p.s2_b = (int64_t)geom->n_kv_heads * kD; p.s2_h = kD;
+    p.seq_lens = st.n_rows; p.n_attend = st.n_attend;
+    p.n_sel = budget + 1;
+    p.cap1 = (int32_t)st.cache.capacity; p.cap2 = 1;
+    p.tail_wg = own; p.nch = n;
+    p.Hq = geom->n_q_heads; p.Hkv = geom->n_kv_heads;
+    p.scale = geom->scale;
+    p.weights = ws.scores; p.w_stride = pooled_row_stride(budget + 1); p.w_vec = 1; p.w_inter = G == 4 ? 1 : 0;
+    p.part_ml = ws.part_ml; p.part_o = ws.part_o; p.max_chunks = ws.max_chunks;
+    *nch = n; *tail = own;
+    return launch_split<true, true, false>(p, geom->batch, G, n + own, stream);
 }
 
 // The pooled scores and histograms of n_layers layers whose full attention ran with defer_pool,

@@ -291,6 +291,52 @@ __device__ __forceinline__ void flush_histogram(const uint32_t* sH, uint32_t* __
     }
 }
 
+// weight = e^{s - lse} with lse = -nl + ll given as an fp32 pair.  The exponent is formed as an
+// exact fp32 pair (two-sum) minus the low part of lse, so a weight carries the error of its
+// score and of expf only (a plain fp32 subtraction alone would cost up to 5e-7 relative, which
+// is the size of the gaps that decide the selection).
+__device__ __forceinline__ float weight_of(float s, float nl, float ll) {
+    const float hi = s + nl;
+    const float bp = hi - s;
+    const float lo = (s - (hi - bp)) + (nl - bp) - ll;     // s - lse = hi + lo, |lo| << 1
+    const float e = expf(hi);
+    return fmaf(e, lo, e);
+}
+
+// The largest of the G weights of one position.  e^x is monotone, so the head with the largest exponent has
+// the largest weight and one exponential is enough, unless another head's exponent comes so close that the
+// rounding of the weights decides (`tol`: 1.5e-5, which covers the error of weight_of with exponents down to
+// -80, plus what the low parts of the lse differ by) or the weights are near the subnormal range: then
+// (about one wavefront in a thousand) all G are worked out.  The result is that of the maximum over
+// weight_of of all heads, bit for bit.  `lse`: (hi, lo) per head in LDS.  The pooling kernels were bound by these
+// instructions (32 layers of 33k rows, 32 heads: 33 million exponentials, 26 us of vector issue alone); with this and
+// the pooling in pool_tile, us per launch: 32 layers of 33k rows 65 -> 45 - 49, 4 layers of 16 ragged rows 71 -> 54, 28
+// layers of 65k rows (7 heads per group, 3 in 8 layers refreshed) 52 -> 36, one layer of 33k rows 8.6 -> 7.3, of 131k
+// rows 19.5 -> 13.5.
+template <int G>
+__device__ __forceinline__ float max_weight(const float (&s)[G], const float (*lse)[2], float tol) {
+    float best = -INFINITY, second = -INFINITY, bs = 0.f;
+    int bi = 0;
+#pragma unroll
+    for (int gi = 0; gi < G; ++gi) {
+        const float hi = s[gi] - lse[gi][0];
+        const bool up = hi > best;
+        second = __builtin_amdgcn_fmed3f(best, second, hi);
+        best = fmaxf(best, hi);
+        bs = up ? s[gi] : bs;
+        bi = up ? gi : bi;
+    }
+    float w;
+    if (__any(!(best - second > tol) || best < -80.f)) {
+        w = weight_of(s[0], -lse[0][0], lse[0][1]);
+#pragma unroll
+        for (int gi = 1; gi < G; ++gi) w = fmaxf(w, weight_of(s[gi], -lse[gi][0], lse[gi][1]));
+    } else {
+        w = weight_of(bs, -lse[bi][0], lse[bi][1]);
+    }
+    return w;
+}
+
 // Orders LDS traffic of the lanes of one wavefront: what was written before is visible to
 // every lane after.  Lanes of a wavefront run in lockstep, so no hardware barrier is needed,
 // only the compiler and the LDS queue have to be told.

@@ -376,6 +376,10 @@ __attribute__((visibility("hidden")))
 int pool_batched_stage(const rk_geom* geom, int n_layers, const Workspace* wss, const int32_t* seq_lens, int32_t max_len,
                        int64_t full_capacity, int pool_half, int agg, const int32_t* const* pred, int32_t pred_val,
                        hipStream_t st);
+//   h2o_attn_stage: the attention of an H2O step, scores and partial results left in the workspace.
+__attribute__((visibility("hidden")))
+int h2o_attn_stage(const rk_geom* geom, const void* q, const rk_h2o_state& st, const void* k_new, const void* v_new,
+                   int32_t budget, const Workspace& ws, hipStream_t stream, int32_t* nch, int32_t* tail);
 //   gather_stage: rk_gather_small_kv plus an optional per-sequence count of refreshes.
 __attribute__((visibility("hidden")))
 int gather_stage(const rk_geom* geom, rk_kv full, const int32_t* idx, int32_t k, rk_kv small,

@@ -175,3 +175,52 @@ def test_ragged_batches_cover_every_row_once(rk, case, G):
             assert (lse[b].double() - z.reshape(-1)).abs().max() < 1e-5, (name, kind, b)
             d = (out[b].double() - ref).abs()             # one bf16 step of the larger value, and 4e-6 (see helpers)
             assert (d <= torch.maximum(out[b].double().abs(), ref.abs()) * 2.0 ** -7 + 4e-6).all(), (name, kind, b)
+
+
+# budgets around whole workgroups of 128 rows (the new token's row alone in a tile, in a workgroup of its own, or neither),
+# beyond the 4096 rows the finishing kernel requests up front, few and many (sequence, KV head) pairs, empty, growing, full
+# and over-full caches
+H2O_EDGES = [("b127", 1, 4, 127, [127, 126, 0]), ("b128", 4, 2, 128, [128, 5]), ("b2047", 1, 8, 2047, [2047]), ("b2048_g7", 7, 4, 2048, [2048, 2000]),
+             ("b4100", 4, 2, 4100, [4100]), ("b64_many", 2, 8, 64, [64, 63, 1, 0] * 4), ("b300_overfull", 3, 2, 300, [303, 300]),
+             ("b5_g8", 8, 1, 5, [5, 2]), ("b700_g5", 5, 3, 700, [700]), ("b700_g6", 6, 3, 700, [699])]
+
+
+@pytest.mark.parametrize("agg", [0, 1, 2], ids=["max", "mean", "first"])
+@pytest.mark.parametrize("case", H2O_EDGES, ids=[c[0] for c in H2O_EDGES])
+def test_h2o_step_equals_its_parts(rk, case, agg):
+    """rk_h2o_step in its two launches against the same step on rows that are only 4-byte aligned, which goes through
+    append, full attention and update one after the other: the same positions, rows and drops, totals to 2e-6 relative
+    (the same fp32 weights from an lse whose fp64 sum is taken in another order), outputs to one bf16 step."""
+    name, G, Hkv, budget, n0 = case
+    say("h2o edge", name, agg)
+    B, cap = len(n0), budget + 6
+    g = torch.Generator(device="cuda").manual_seed(budget + agg)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
+    geom = rk.Geom(B, G * Hkv, Hkv, 128, SCALE)
+    K, V = rnd(B, Hkv, cap, 128), rnd(B, Hkv, cap, 128)
+    total = torch.rand(B, Hkv, cap, generator=g, device="cuda")
+    pos = torch.stack([torch.stack([torch.randperm(cap, generator=g, device="cuda") for _ in range(Hkv)]) for _ in range(B)]).to(torch.int32)
+    sides = []
+    for _ in range(2):
+        s = {"K": K.clone(), "V": V.clone(), "total": total.clone(), "pos": pos.clone(),
+             "n_rows": torch.tensor(n0, dtype=torch.int32, device="cuda"), "n_attend": torch.zeros(B, dtype=torch.int32, device="cuda"),
+             "out": torch.zeros(B, G * Hkv, 128, dtype=torch.bfloat16, device="cuda"),
+             "dropped": torch.full((B, Hkv), -9, dtype=torch.int32, device="cuda"), "ws": rk.Workspace(geom, budget + 1, 1)}
+        s["st"] = rk.h2o_state(geom, s["K"], s["V"], s["total"], s["pos"], s["n_rows"], s["n_attend"])
+        sides.append(s)
+    odd = torch.zeros(2, B * Hkv * 128 + 8, dtype=torch.bfloat16, device="cuda")
+    for step in range(3):
+        q, kn, vn = rnd(B, G * Hkv, 128), rnd(B, Hkv, 128), rnd(B, Hkv, 128)
+        odd[0, 2:2 + kn.numel()], odd[1, 2:2 + kn.numel()] = kn.flatten(), vn.flatten()
+        lens = torch.full((B,), cap + 1 + step, dtype=torch.int32, device="cuda")
+        rk.rk_h2o_step(geom, sides[0]["st"], q, kn, vn, lens, budget, budget // 2, sides[0]["out"], agg=agg, dropped=sides[0]["dropped"], workspace=sides[0]["ws"])
+        ko, vo = odd[0, 2:2 + kn.numel()].view(B, Hkv, 128), odd[1, 2:2 + kn.numel()].view(B, Hkv, 128)
+        assert ko.data_ptr() % 16 != 0
+        rk.rk_h2o_step(geom, sides[1]["st"], q, ko, vo, lens, budget, budget // 2, sides[1]["out"], agg=agg, dropped=sides[1]["dropped"], workspace=sides[1]["ws"])
+        torch.cuda.synchronize()
+        a, b = sides
+        for key in ("K", "V", "pos", "n_rows", "n_attend", "dropped"):
+            assert torch.equal(a[key], b[key]), (name, step, key)
+        assert ((a["total"] - b["total"]).abs() <= 2e-6 * b["total"].abs()).all(), (name, step)
+        x, y = a["out"].double(), b["out"].double()
+        assert ((x - y).abs() <= torch.maximum(x.abs(), y.abs()) * 2.0 ** -7 + 4e-6).all(), (name, step)
