@@ -21,7 +21,8 @@
 //            (rk_partial_attn_static), where an old tag could sit where a new one is expected.
 //
 // Data path per wavefront and tile of 32 rows:
-//   K rows  -> registers in MFMA operand layout (16-byte loads, no LDS)
+//   K rows  -> registers in MFMA operand layout (16-byte loads; the partial steps straight from memory, the kernels
+//             that stream the full cache in whole rows and through LDS)
 //   S^T = K Q^T on the matrix cores: v_mfma_f32_16x16x32_bf16, M = 16 rows, N = query heads
 //             (padded to 16), contraction over head_dim in 4 steps; a lane ends up with four
 //             consecutive rows of one head
@@ -589,9 +590,6 @@ constexpr int kSliceChunks = 20, kSliceChunks4 = 64;   // the merge by slices se
 //   P operand   head n16, contraction slot e = 4*t + i  <->  row 16*t + 4*c4 + i
 //   V operand   dim 16*dt + n16, the same slots (LDS transpose read)
 //   O result    dim 16*dt + n16, heads 4*c4 + i
-#ifndef RK_EMIT_OCCUPANCY
-#define RK_EMIT_OCCUPANCY 3       // workgroups per CU the score-emitting kernel is compiled for
-#endif
 // LAZY (with TWO_SEG): the first partial step after a refresh whose gather was left out.  The rows
 // of the small-cache segment are read from the full cache through the selection (row r of the list
 // is row idx[r] of the full cache) and written to the small cache on the way, so that the step
@@ -612,7 +610,7 @@ constexpr int kSliceChunks = 20, kSliceChunks4 = 64;   // the merge by slices se
 // it: k2 / v2 with one row per (sequence, KV head).  n_sel is the most rows the step attends over; a cache that
 // is over it already (outside the policy's contract) is cut there and the new row is left out.
 template <int G, int NW, bool EMIT, bool TWO_SEG, bool LAZY = false, bool TAGGED = !EMIT, bool TRIG = false>
-__global__ __launch_bounds__(NW * 64, (EMIT && !TAGGED) ? RK_EMIT_OCCUPANCY : 2)
+__global__ __launch_bounds__(NW * 64, 2)
 void attn_split_kernel(const uint16_t* k_first, const uint16_t* v_first, int64_t s_b_and_tail, int32_t s_h, int32_t spec_rows,
                        const int32_t* seq_lens, const int32_t* tail_start, const int32_t* pred, const uint32_t* epochs,
                        const AttnParams p) {
@@ -630,6 +628,7 @@ void attn_split_kernel(const uint16_t* k_first, const uint16_t* v_first, int64_t
     // does wait for it (and for p.pred_val) before it requests anything: a switched-off sequence
     // must not cost memory traffic.
     constexpr int ROWS = kTileRows;          // rows per wavefront and tile = contraction depth of P V
+    constexpr bool KLDS = !TWO_SEG;          // K rows reach the operand layout through LDS (see load_k)
     static_assert(NW == kSplitWaves, "work split");
     constexpr int NV = ROWS / 4;             // V loads per lane and tile
     constexpr int NC = (G + 3) / 4;          // lane groups whose O accumulators hold real heads
@@ -703,12 +702,19 @@ void attn_split_kernel(const uint16_t* k_first, const uint16_t* v_first, int64_t
     if (spec) {
         const uint16_t* kspec = k_first + (int64_t)b * s_b + (int64_t)g * s_h + c4 * 8;
         const int cap_full = p.cap2;
+        if (KLDS) {
+            const uint16_t* krows = k_first + (int64_t)b * s_b + (int64_t)g * s_h + n16 * 8;
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const int64_t row = LAZY ? min(max(__shfl(sel0, t * 16 + n16), 0), cap_full - 1) : r_first + t * 16 + n16;
+            for (int jj = 0; jj < 8; ++jj)
+                kA[jj >> 2][jj & 3] = load_rows16<true>(krows + (int64_t)(r_first + jj * 4 + c4) * kD);
+        } else {
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk)
-                kA[t][kk] = load_rows16<!TWO_SEG>(kspec + row * kD + kk * 32);
+            for (int t = 0; t < 2; ++t) {
+                const int64_t row = LAZY ? min(max(__shfl(sel0, t * 16 + n16), 0), cap_full - 1) : r_first + t * 16 + n16;
+#pragma unroll
+                for (int kk = 0; kk < 4; ++kk)
+                    kA[t][kk] = load_rows16<false>(kspec + row * kD + kk * 32);
+            }
         }
         const uint16_t* vspec = v_first + (int64_t)b * s_b + (int64_t)g * s_h + n16 * 8;
 #pragma unroll
@@ -859,7 +865,21 @@ void attn_split_kernel(const uint16_t* k_first, const uint16_t* v_first, int64_t
     // (LAZY: kfull / vfull are row 0 of the full cache of this (sequence, KV head))
     const uint16_t* kfull = LAZY ? p.k2 + (int64_t)b * p.s2_b + (int64_t)g * p.s2_h : nullptr;
     const uint16_t* vfull = LAZY ? p.v2 + (int64_t)b * p.s2_b + (int64_t)g * p.s2_h : nullptr;
+    // The full cache (KLDS): whole rows, 16 lanes to one, like V, and into the operand layout through the V tile's
+    // room in LDS.  Loaded straight into that layout a row comes in four pieces of 64 bytes, which non-temporal loads
+    // pay for: a kernel that only reads 268 MB with them takes 46 us, with whole rows 40 (plain loads: 43 either way).
+    // Here: full step of 32 layers of 33k rows 1078 -> 1043 us, 4 layers of 16 ragged sequences of 10k rows 743 -> 706, one
+    // layer of 131072 rows with its selection 146.2 -> 140.8; the registers it takes want two workgroups per CU (with
+    // three it spilled and that layer took 151.9).  Plain loads of K beside non-temporal ones of V: 1139 us
+    // for the 32 layers.  A partial step, which waits for its chain of instructions and not for memory, loads
+    // into the operand layout.
     auto load_k = [&](int r) {
+        if (KLDS) {
+#pragma unroll
+            for (int jj = 0; jj < 8; ++jj)
+                kA[jj >> 2][jj & 3] = load_rows16<true>(kb2 + (int64_t)min(r + jj * 4 + c4, row1 - 1) * kD + n16 * 8);
+            return;
+        }
         const int sv = LAZY ? tile_sel(r, n1) : 0;
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
@@ -873,7 +893,7 @@ void attn_split_kernel(const uint16_t* k_first, const uint16_t* v_first, int64_t
                 rp = base + (int64_t)row * kD + c4 * 8;
             }
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk) kA[t][kk] = load_rows16<!TWO_SEG>(rp + kk * 32);
+            for (int kk = 0; kk < 4; ++kk) kA[t][kk] = load_rows16<false>(rp + kk * 32);
         }
     };
     auto load_v = [&](int r) {
@@ -906,17 +926,26 @@ void attn_split_kernel(const uint16_t* k_first, const uint16_t* v_first, int64_t
             }
         }
         // ---- S^T = K Q^T on the matrix cores: head n16, rows r + 16 t + 4 c4 + i ----
+        if (KLDS) {
+#pragma unroll
+            for (int jj = 0; jj < 8; ++jj) *reinterpret_cast<u32x4*>(&sV[w][jj * 4 + c4][n16 * 8]) = kA[jj >> 2][jj & 3];
+            if (r_next < row1) load_k(r_next);
+            wave_lds_sync();
+        }
         float s[2][4];
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
             f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk)
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kA[t][kk]), qa[kk], acc, 0, 0, 0);
+            for (int kk = 0; kk < 4; ++kk) {
+                const u32x4 rows = KLDS ? *reinterpret_cast<const u32x4*>(&sV[w][t * 16 + n16][kk * 32 + c4 * 8]) : kA[t][kk];
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, rows), qa[kk], acc, 0, 0, 0);
+            }
 #pragma unroll
             for (int i = 0; i < 4; ++i) s[t][i] = (r + t * 16 + 4 * c4 + i < row1) ? acc[i] * p.scale : -INFINITY;
         }
-        if (r_next < row1) load_k(r_next);
+        if (KLDS) wave_lds_sync();               // (the V tile is written to the same room)
+        else if (r_next < row1) load_k(r_next);
         // ---- raw scores out: four consecutive rows of one head per lane, one 16-byte store
         //      where the row of the weights tensor allows it ----
         if (EMIT && G == 4 && p.w_inter) {
@@ -1661,7 +1690,7 @@ static int launch_split_g(const AttnParams& p, int batch, int nchunk_grid, hipSt
     // 27.0 - 29.7; 8 KV heads, 1024 workgroups, which are not all resident at once, 131072..131400 rows
     // 101.3 - 105.4 / 105.5; no difference at 8192 and 16384 rows)
     const bool heads_first = EMIT && !TWO_SEG && p.ragged_batch == 0 &&
-                             (int64_t)nchunk_grid * p.Hkv * batch <= 3 * kComputeUnits;
+                             (int64_t)nchunk_grid * p.Hkv * batch <= 2 * kComputeUnits;
     dim3 grid(heads_first ? p.Hkv : nchunk_grid, heads_first ? batch : p.Hkv, heads_first ? nchunk_grid : batch);
     // four wavefronts of 32 rows per iteration; with 64-row chunks two of them only help to merge
     const int32_t spec_rows = TWO_SEG ? (p.n_sel < p.cap1 ? p.n_sel : p.cap1) : p.cap2;

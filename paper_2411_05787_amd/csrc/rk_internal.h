@@ -264,12 +264,14 @@ static inline int max_chunks_for(int64_t max_len) {
 // (384 workgroups, uneven over the CUs: 28.8 / 32.8 / 115.3.)  Few tiles per wavefront leave the
 // launch's fixed costs (start, the merge across the wavefronts, the partial results) a larger share
 // and make a ragged last round (2.67 tiles per wavefront with 768 workgroups at 32k rows) cost more;
-// long rows want more loads in flight.
+// long rows want more loads in flight.  768 workgroups are left out: the kernel is compiled for two per CU and would
+// run one and a half residency rounds (layer by layer, 768 -> 512: 2 sequences of 24000 rows 66.8 -> 63.3 us, one of 50000
+// 68.1 -> 66.3).
 static inline int emit_split_target(const rk_geom* g, int64_t max_len) {
     const int64_t tiles = (max_len + 31) / 32 * g->batch * g->n_kv_heads;
     int64_t target = (tiles / 16 + kComputeUnits / 2) / kComputeUnits * kComputeUnits;      // 16 tiles per workgroup: 4 per wavefront
     if (target < kComputeUnits) target = kComputeUnits;
-    if (target > 4 * kComputeUnits) target = 4 * kComputeUnits;
+    if (target > 2 * kComputeUnits) target = (target < 4 * kComputeUnits ? 2 : 4) * kComputeUnits;
     return (int)target;
 }
 static inline int emit_split_workgroups(const rk_geom* g, int64_t max_len) {
@@ -277,17 +279,16 @@ static inline int emit_split_workgroups(const rk_geom* g, int64_t max_len) {
 }
 
 // Workgroups per (sequence, KV head) of the same kernel where it merges its partial results itself (nothing but the
-// output merge would follow it): no more than there are slots for.  That form is compiled for two workgroups per CU:
-// a launch is resident as a whole (512, merged by slices) or a multiple of that (1024), never in one and a half rounds
-// (768), and groups of more than 4 heads, whose merge by the last arrival takes two heads per wavefront, stay with
-// 512.  Full step, us per layer at 768 or 1024 -> 512 workgroups: 6 ragged sequences of 10k rows, 4 KV heads of 7: 57.4 ->
-// 47.7; 2 of 24000 rows, 8 of 4: 64.7 -> 53.6; 16 ragged of 5.5k rows, 4 of 7: 89.7 -> 82.9; 16 ragged of 10k, 8 of 4,
-// stays with 1024: 186.0 against 188.4.
+// output merge would follow it): no more than there are slots for; groups of more than 4 heads, whose merge by the last
+// arrival takes two heads per wavefront, stay with one residency round of 512 workgroups, merged by slices.  Full
+// step, us per layer at 768 or 1024 -> 512 workgroups: 6 ragged sequences of 10k rows, 4 KV heads of 7: 57.4 -> 47.7; 2 of
+// 24000 rows, 8 of 4: 64.7 -> 53.6; 16 ragged of 5.5k rows, 4 of 7: 89.7 -> 82.9; 16 ragged of 10k, 8 of 4, stays with
+// 1024: 186.0 against 188.4.
 // 0: compute units would be left without work (few, long rows; small batches), and the merge stays a launch of its own.
 static inline int inside_split_workgroups(const rk_geom* g, int64_t max_len) {
     const int64_t problems = (int64_t)g->batch * g->n_kv_heads;
     int target = emit_split_target(g, max_len);
-    if (target > 2 * kComputeUnits && (target < 4 * kComputeUnits || g->n_q_heads > 4 * g->n_kv_heads)) target = 2 * kComputeUnits;
+    if (target > 2 * kComputeUnits && g->n_q_heads > 4 * g->n_kv_heads) target = 2 * kComputeUnits;
     const int n = split_workgroups(max_len, problems, kMergeChunks, target);
     if ((g->batch > 1 || max_len > (int64_t)kMergeChunks * kMinChunk) && n * problems < kComputeUnits) return 0;
     return n;
