@@ -1225,10 +1225,12 @@ void attn_split_kernel(const uint16_t* k_first, const uint16_t* v_first, int64_t
 // Scores-only pass over the full cache (Section 4.3, "Impact of full attention steps", the
 // "w/o full attention" setting: the attention scores over the entire cache are computed and the
 // small cache is refreshed from them, but the step's output comes from the refreshed small cache,
-// so V is never read here: half the bytes of a full step).  Same work split, K operand layout
-// and score emission as attn_split_kernel; per workgroup it leaves only the (max, sum) pair of
-// every head.  With no V registers to hold, two K tiles per wavefront are in flight.
-template <int G>
+// so V is never read here: half the bytes of a full step).  Same work split, way of the K rows
+// (whole rows, through LDS into the operand layout) and score emission as attn_split_kernel; per workgroup it
+// leaves only the (max, sum) pair of every head.  With no V registers to hold, two K tiles per wavefront
+// are in flight.  Measured against rows loaded straight into the operand layout, the whole scores-only step of
+// one layer, us: 131072 rows 119.3 -> 111.3, 4 sequences of 16384 66.8 -> 59.5, 60000 rows 66.2 -> 59.7.
+template <int G, bool STREAM>
 __global__ __launch_bounds__(256, 3)
 void score_split_kernel(const AttnParams p) {
     constexpr int NW = kSplitWaves, ROWS = kTileRows;
@@ -1238,18 +1240,15 @@ void score_split_kernel(const AttnParams p) {
     const int n16 = lane & 15, c4 = lane >> 4;
     const int r_first = (c * NW + w) * ROWS;
     const int step = p.nch * NW * ROWS;
-    const uint16_t* kb = p.k2 + (int64_t)b * p.s2_b + (int64_t)g * p.s2_h + c4 * 8;
+    const uint16_t* kb = p.k2 + (int64_t)b * p.s2_b + (int64_t)g * p.s2_h + n16 * 8;
 
     // first two tiles of this wavefront, requested before the length is known where they exist anyhow
-    u32x4 kA[2][4], kB[2][4];
+    u32x4 kA[8], kB[8];
     const bool spec_a = (c + 1) * NW * ROWS <= p.cap2;
     const bool spec_b = (int64_t)r_first + step + ROWS <= p.cap2;
-    auto load_exact = [&](u32x4 (&dst)[2][4], int r) {
+    auto load_exact = [&](u32x4 (&dst)[8], int r) {
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk)
-                dst[t][kk] = load_rows16<false>(kb + (int64_t)(r + t * 16 + n16) * kD + kk * 32);
+        for (int jj = 0; jj < 8; ++jj) dst[jj] = load_rows16<STREAM>(kb + (int64_t)(r + jj * 4 + c4) * kD);
     };
     if (spec_a) load_exact(kA, r_first);
     if (spec_b) load_exact(kB, r_first + step);
@@ -1267,24 +1266,26 @@ void score_split_kernel(const AttnParams p) {
     const int n = min(max(min(p.seq_lens[b], p.cap2), 0), p.max_rows2);
     const int nchunks = active_workgroups(n, p.nch);
     if (c >= nchunks) return;
-    auto load_clamped = [&](u32x4 (&dst)[2][4], int r) {     // rows past the end re-read the last row (masked later)
+    auto load_clamped = [&](u32x4 (&dst)[8], int r) {        // rows past the end re-read the last row (masked later)
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const int row = min(r + t * 16 + n16, n - 1);
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk)
-                dst[t][kk] = load_rows16<false>(kb + (int64_t)row * kD + kk * 32);
-        }
+        for (int jj = 0; jj < 8; ++jj) dst[jj] = load_rows16<STREAM>(kb + (int64_t)min(r + jj * 4 + c4, n - 1) * kD);
     };
+    __shared__ __attribute__((aligned(16))) uint16_t sK[NW][ROWS][kD + 8];
     float m_run = -INFINITY, l_run = 0.f;
-    auto tile = [&](const u32x4 (&k)[2][4], int r) {
+    // one tile; its registers are requested again as soon as the rows are in LDS
+    auto tile = [&](u32x4 (&k)[8], int r) {
+#pragma unroll
+        for (int jj = 0; jj < 8; ++jj) *reinterpret_cast<u32x4*>(&sK[w][jj * 4 + c4][n16 * 8]) = k[jj];
+        if (r + 2 * step < n) load_clamped(k, r + 2 * step);
+        wave_lds_sync();
         float s[2][4];
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
             f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int kk = 0; kk < 4; ++kk)
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, k[t][kk]), qa[kk], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                    __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(&sK[w][t * 16 + n16][kk * 32 + c4 * 8])), qa[kk], acc, 0, 0, 0);
 #pragma unroll
             for (int i = 0; i < 4; ++i) s[t][i] = (r + t * 16 + 4 * c4 + i < n) ? acc[i] * p.scale : -INFINITY;
         }
@@ -1311,18 +1312,17 @@ void score_split_kernel(const AttnParams p) {
         for (int e = 0; e < 8; ++e) ps += fast_exp2((s[e >> 2][e & 3] - m_new) * kLog2e);
         l_run = l_run * fast_exp2((m_run - m_new) * kLog2e) + ps;
         m_run = m_new;
+        wave_lds_sync();      // sK is rewritten by the next tile
     };
-    // tiles alternate between the two register sets; each set is re-requested right after use
+    // tiles alternate between the two register sets
     int r = r_first;
     if (r < n && !spec_a) load_clamped(kA, r);
     if (r + step < n && !spec_b) load_clamped(kB, r + step);
     while (r < n) {
         tile(kA, r);
-        if (r + 2 * step < n) load_clamped(kA, r + 2 * step);
         r += step;
         if (r >= n) break;
         tile(kB, r);
-        if (r + 2 * step < n) load_clamped(kB, r + 2 * step);
         r += step;
     }
     l_run = sum_xor32(sum_xor16(l_run));
@@ -1757,10 +1757,21 @@ static int launch_split_triggered(const AttnParams& p, int batch, int G, int nch
     }
 }
 
+// Keys of more than this many bytes are read with non-temporal loads, fewer with plain ones: the last-level cache (256 MB)
+// can hold them, and those of a few more layers, until the next step.  Measured, the whole step in us with plain /
+// non-temporal loads: 131072 rows of 8
+// KV heads (268 MB) 119 / 111, 60000 (123 MB) 66.2 / 59.7, 32768 (67 MB) 42.2 / 42.7, 5000 (10 MB) 32.1 / 32.9.
+constexpr int64_t kScoreStreamBytes = 96ll << 20;
+template <int G>
+static void launch_score_split_g(const AttnParams& p, dim3 grid, bool stream, hipStream_t st) {
+    if (stream) hipLaunchKernelGGL((score_split_kernel<G, true>), grid, dim3(256), 0, st, p);
+    else        hipLaunchKernelGGL((score_split_kernel<G, false>), grid, dim3(256), 0, st, p);
+}
 static int launch_score_split(const AttnParams& p, int batch, int G, int nchunk_grid, hipStream_t st) {
     dim3 grid(nchunk_grid, p.Hkv, batch);
+    const bool stream = (int64_t)p.max_rows2 * batch * p.Hkv * kD * 2 > kScoreStreamBytes;
     switch (G) {
-#define RK_CASE(g) case g: hipLaunchKernelGGL((score_split_kernel<g>), grid, dim3(256), 0, st, p); break;
+#define RK_CASE(g) case g: launch_score_split_g<g>(p, grid, stream, st); break;
         RK_CASE(1) RK_CASE(2) RK_CASE(3) RK_CASE(4) RK_CASE(5) RK_CASE(6) RK_CASE(7) RK_CASE(8)
 #undef RK_CASE
         default: return RK_ERR_UNSUPPORTED;
