@@ -42,6 +42,15 @@ struct GatherBatch {
     const int32_t* pred[kBatchLayers];
 };
 
+// STREAM: non-temporal loads and stores, for launches whose small caches the last-level cache could not keep until the
+// next step anyway (kStreamBytes; smaller ones are left to it: the partial steps that follow read them).
+// Bound by memory both ways.  268 MB read and 268 MB written, the full step around it: 32 layers of 2048 rows per KV head
+// 1044 -> 1030 us, 4 layers of 16 x 1024 713 -> 691 (105 us and more of it in this launch).  The per-layer kernel above is
+// slower with it (47.5 against 46.8 us per step of one layer).
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+constexpr int64_t kStreamBytes = 192ll << 20;
+
+template <bool STREAM>
 __global__ __launch_bounds__(256)
 void gather_rows_batched_kernel(const GatherBatch tab, int32_t batch, int64_t fs_b, int64_t fs_h, int64_t ss_b, int64_t ss_h,
                                 int32_t k, int32_t Hkv, int32_t full_cap, const int32_t* __restrict__ seq_lens,
@@ -59,10 +68,19 @@ void gather_rows_batched_kernel(const GatherBatch tab, int32_t batch, int64_t fs
     const int seg = (threadIdx.x & 15) * 8;
     const int64_t src = (int64_t)b * fs_b + (int64_t)g * fs_h + (int64_t)j * kD + seg;
     const int64_t dst = (int64_t)b * ss_b + (int64_t)g * ss_h + (int64_t)i * kD + seg;
-    const uint4 kr = *reinterpret_cast<const uint4*>(tab.fk[layer] + src);
-    const uint4 vr = *reinterpret_cast<const uint4*>(tab.fv[layer] + src);
-    *reinterpret_cast<uint4*>(tab.sk[layer] + dst) = kr;
-    *reinterpret_cast<uint4*>(tab.sv[layer] + dst) = vr;
+    const u32x4* ks = reinterpret_cast<const u32x4*>(tab.fk[layer] + src);
+    const u32x4* vs = reinterpret_cast<const u32x4*>(tab.fv[layer] + src);
+    u32x4* kd = reinterpret_cast<u32x4*>(tab.sk[layer] + dst);
+    u32x4* vd = reinterpret_cast<u32x4*>(tab.sv[layer] + dst);
+    if (STREAM) {
+        const u32x4 kr = __builtin_nontemporal_load(ks), vr = __builtin_nontemporal_load(vs);
+        __builtin_nontemporal_store(kr, kd);
+        __builtin_nontemporal_store(vr, vd);
+    } else {
+        const u32x4 kr = *ks, vr = *vs;
+        *kd = kr;
+        *vd = vr;
+    }
 }
 
 }  // namespace rk
@@ -93,7 +111,9 @@ int gather_batched_stage(const rk_geom* geom, int n_layers, const rk_kv* full, c
             tab.pred[l] = pred ? pred[l0 + l] : nullptr;
         }
         dim3 grid((k + kGatherRows - 1) / kGatherRows, geom->n_kv_heads, n * geom->batch);
-        hipLaunchKernelGGL(gather_rows_batched_kernel, grid, dim3(256), 0, st, tab, (int32_t)geom->batch,
+        const bool stream = (int64_t)n * geom->batch * geom->n_kv_heads * k * (2 * kD * 2) > kStreamBytes;
+        auto kernel = stream ? gather_rows_batched_kernel<true> : gather_rows_batched_kernel<false>;
+        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, tab, (int32_t)geom->batch,
                            full[0].stride_b, full[0].stride_h, small[0].stride_b, small[0].stride_h,
                            k, geom->n_kv_heads, (int32_t)full[0].capacity, seq_lens, pred_val);
         const int rc = launch_status();

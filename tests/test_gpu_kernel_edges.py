@@ -224,3 +224,30 @@ def test_h2o_step_equals_its_parts(rk, case, agg):
         assert ((a["total"] - b["total"]).abs() <= 2e-6 * b["total"].abs()).all(), (name, step)
         x, y = a["out"].double(), b["out"].double()
         assert ((x - y).abs() <= torch.maximum(x.abs(), y.abs()) * 2.0 ** -7 + 4e-6).all(), (name, step)
+
+
+@pytest.mark.parametrize("B", [24, 25], ids=["up_to_192MB", "beyond_192MB"])
+def test_batched_gather_of_large_small_caches(rk, B):
+    """The batched gather on both sides of the size from which it stores past the caches: bit copies of the selected
+    rows, slots without a row left alone."""
+    say("large batched gather", B)
+    import ctypes
+    Hkv, k, n = 8, 2048, 2060
+    g = torch.Generator(device="cuda").manual_seed(B)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda", dtype=torch.bfloat16)
+    K, V, q = rnd(B, Hkv, n, 128), rnd(B, Hkv, n, 128), rnd(B, Hkv, 128)
+    lens = torch.full((B,), n, dtype=torch.int32, device="cuda")
+    lens[1] = k - 7                                      # fewer rows than slots
+    geom = rk.Geom(B, Hkv, Hkv, 128, SCALE)
+    ws = rk.Workspace(geom, n, k)
+    sK, sV = torch.full((B, Hkv, k, 128), 3.0, dtype=torch.bfloat16, device="cuda"), torch.full((B, Hkv, k, 128), 5.0, dtype=torch.bfloat16, device="cuda")
+    idx, tail = torch.zeros(B, Hkv, k, dtype=torch.int32, device="cuda"), torch.zeros(B, dtype=torch.int32, device="cuda")
+    state = rk.layer_state(geom, K, V, sK, sV, idx, tail, k=k)
+    rk.rk_full_attn_deferred(geom, q, K, V, lens, n, torch.empty_like(q), workspace=ws)
+    rk.rk_refresh_batched(geom, (type(state) * 1)(state), (ctypes.c_void_p * 1)(ws.ptr), ws.nbytes, lens, n, k, pool_w=7)
+    torch.cuda.synchronize()
+    at = idx.long().clamp(min=0)[..., None].expand(-1, -1, -1, 128)
+    there = (idx >= 0)[..., None]
+    assert int((idx < 0).sum()) == 7 * Hkv and torch.equal(tail, lens)
+    assert torch.equal(sK, torch.where(there, torch.gather(K, 2, at), torch.full_like(sK, 3.0)))
+    assert torch.equal(sV, torch.where(there, torch.gather(V, 2, at), torch.full_like(sV, 5.0)))
