@@ -1225,8 +1225,9 @@ void attn_split_kernel(const uint16_t* k_first, const uint16_t* v_first, int64_t
 // Scores-only pass over the full cache (Section 4.3, "Impact of full attention steps", the
 // "w/o full attention" setting: the attention scores over the entire cache are computed and the
 // small cache is refreshed from them, but the step's output comes from the refreshed small cache,
-// so V is never read here: half the bytes of a full step).  Same work split, way of the K rows
-// (whole rows, through LDS into the operand layout) and score emission as attn_split_kernel; per workgroup it
+// so V is never read here: half the bytes of a full step).  Same work split and score
+// emission as attn_split_kernel, and for many keys (STREAM) the same way of the K rows, whole rows through LDS
+// into the operand layout; fewer, read with plain loads, come straight in it; per workgroup it
 // leaves only the (max, sum) pair of every head.  With no V registers to hold, two K tiles per wavefront
 // are in flight.  Measured against rows loaded straight into the operand layout, the whole scores-only step of
 // one layer, us: 131072 rows 119.3 -> 111.3, 4 sequences of 16384 66.8 -> 59.5, 60000 rows 66.2 -> 59.7.
@@ -1240,7 +1241,11 @@ void score_split_kernel(const AttnParams p) {
     const int n16 = lane & 15, c4 = lane >> 4;
     const int r_first = (c * NW + w) * ROWS;
     const int step = p.nch * NW * ROWS;
-    const uint16_t* kb = p.k2 + (int64_t)b * p.s2_b + (int64_t)g * p.s2_h + n16 * 8;
+    const uint16_t* kb = p.k2 + (int64_t)b * p.s2_b + (int64_t)g * p.s2_h + (STREAM ? n16 : c4) * 8;
+
+    // load jj of a tile: row jj * 4 + c4 whole, or 64 bytes of row n16 of a half tile
+    auto row_of = [&](int jj) { return STREAM ? jj * 4 + c4 : (jj >> 2) * 16 + n16; };
+    auto part_of = [](int jj) { return STREAM ? 0 : (jj & 3) * 32; };
 
     // first two tiles of this wavefront, requested before the length is known where they exist anyhow
     u32x4 kA[8], kB[8];
@@ -1248,7 +1253,7 @@ void score_split_kernel(const AttnParams p) {
     const bool spec_b = (int64_t)r_first + step + ROWS <= p.cap2;
     auto load_exact = [&](u32x4 (&dst)[8], int r) {
 #pragma unroll
-        for (int jj = 0; jj < 8; ++jj) dst[jj] = load_rows16<STREAM>(kb + (int64_t)(r + jj * 4 + c4) * kD);
+        for (int jj = 0; jj < 8; ++jj) dst[jj] = load_rows16<STREAM>(kb + (int64_t)(r + row_of(jj)) * kD + part_of(jj));
     };
     if (spec_a) load_exact(kA, r_first);
     if (spec_b) load_exact(kB, r_first + step);
@@ -1268,24 +1273,28 @@ void score_split_kernel(const AttnParams p) {
     if (c >= nchunks) return;
     auto load_clamped = [&](u32x4 (&dst)[8], int r) {        // rows past the end re-read the last row (masked later)
 #pragma unroll
-        for (int jj = 0; jj < 8; ++jj) dst[jj] = load_rows16<STREAM>(kb + (int64_t)min(r + jj * 4 + c4, n - 1) * kD);
+        for (int jj = 0; jj < 8; ++jj) dst[jj] = load_rows16<STREAM>(kb + (int64_t)min(r + row_of(jj), n - 1) * kD + part_of(jj));
     };
-    __shared__ __attribute__((aligned(16))) uint16_t sK[NW][ROWS][kD + 8];
+    __shared__ __attribute__((aligned(16))) uint16_t sK[STREAM ? NW : 1][STREAM ? ROWS : 1][kD + 8];
     float m_run = -INFINITY, l_run = 0.f;
-    // one tile; its registers are requested again as soon as the rows are in LDS
+    // one tile; its registers are requested again as soon as the rows are in LDS, or used
     auto tile = [&](u32x4 (&k)[8], int r) {
+        if constexpr (STREAM) {
 #pragma unroll
-        for (int jj = 0; jj < 8; ++jj) *reinterpret_cast<u32x4*>(&sK[w][jj * 4 + c4][n16 * 8]) = k[jj];
-        if (r + 2 * step < n) load_clamped(k, r + 2 * step);
-        wave_lds_sync();
+            for (int jj = 0; jj < 8; ++jj) *reinterpret_cast<u32x4*>(&sK[w][jj * 4 + c4][n16 * 8]) = k[jj];
+            if (r + 2 * step < n) load_clamped(k, r + 2 * step);
+            wave_lds_sync();
+        }
         float s[2][4];
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
             f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk)
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                    __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(&sK[w][t * 16 + n16][kk * 32 + c4 * 8])), qa[kk], acc, 0, 0, 0);
+            for (int kk = 0; kk < 4; ++kk) {
+                u32x4 rows = k[t * 4 + kk];
+                if constexpr (STREAM) rows = *reinterpret_cast<const u32x4*>(&sK[w][t * 16 + n16][kk * 32 + c4 * 8]);
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, rows), qa[kk], acc, 0, 0, 0);
+            }
 #pragma unroll
             for (int i = 0; i < 4; ++i) s[t][i] = (r + t * 16 + 4 * c4 + i < n) ? acc[i] * p.scale : -INFINITY;
         }
@@ -1312,7 +1321,8 @@ void score_split_kernel(const AttnParams p) {
         for (int e = 0; e < 8; ++e) ps += fast_exp2((s[e >> 2][e & 3] - m_new) * kLog2e);
         l_run = l_run * fast_exp2((m_run - m_new) * kLog2e) + ps;
         m_run = m_new;
-        wave_lds_sync();      // sK is rewritten by the next tile
+        if constexpr (STREAM) wave_lds_sync();      // sK is rewritten by the next tile
+        else if (r + 2 * step < n) load_clamped(k, r + 2 * step);
     };
     // tiles alternate between the two register sets
     int r = r_first;
@@ -1760,7 +1770,7 @@ static int launch_split_triggered(const AttnParams& p, int batch, int G, int nch
 // Keys of more than this many bytes are read with non-temporal loads, fewer with plain ones: the last-level cache (256 MB)
 // can hold them, and those of a few more layers, until the next step.  Measured, the whole step in us with plain /
 // non-temporal loads: 131072 rows of 8
-// KV heads (268 MB) 119 / 111, 60000 (123 MB) 66.2 / 59.7, 32768 (67 MB) 42.2 / 42.7, 5000 (10 MB) 32.1 / 32.9.
+// KV heads (268 MB) 119 / 111, 60000 (123 MB) 66.2 / 59.7, 32768 (67 MB) 41.6 / 42.7, 5000 (10 MB) 31.5 / 32.9.
 constexpr int64_t kScoreStreamBytes = 96ll << 20;
 template <int G>
 static void launch_score_split_g(const AttnParams& p, dim3 grid, bool stream, hipStream_t st) {
