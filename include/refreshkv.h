@@ -409,10 +409,12 @@ typedef struct rk_h2o_state {
     int32_t* pos;          /* int32 [batch, n_kv_heads, cache.capacity]: token position per slot */
     int32_t* n_rows;       /* int32 [batch]: tokens kept (the same for every head)              */
     int32_t* n_attend;     /* int32 [batch]: rows the current step attends over (written by
-                              rk_h2o_append, read by the attention and by rk_h2o_update)        */
+                              rk_h2o_append or by the attention of rk_h2o_step, read by the
+                              launches after it)                                                */
 } rk_h2o_state;
 
-/* The three parts of a step; rk_h2o_step enqueues all of them.
+/* The three parts of a step; rk_h2o_step does the work of all of them in two launches, with the
+ * same results.
  *   rk_h2o_append  rows k_new, v_new (bf16 [batch, n_kv_heads, 128]) go to slot n_rows[b] with
  *                  total 0 and position seq_lens[b] - 1 (seq_lens: tokens so far, the new one
  *                  included); n_attend[b] = n_rows[b] + 1.

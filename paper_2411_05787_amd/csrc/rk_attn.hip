@@ -103,17 +103,17 @@ __device__ __forceinline__ int active_workgroups(int n_rows, int nch) {
 // The kernels that read the partial results do not repeat it: the first workgroup of every (sequence, KV head)
 // of such a launch leaves their number in its counter line (kCountWord).  16 ragged sequences of 10k rows, us per launch: output merge
 // 7.8 -> 6.2, pooling of 4 layers 54 -> 45.
-constexpr int kRaggedMaxBatch = 64;
-constexpr int kCountWord = 4;
 __device__ __forceinline__ int clamped_len(int raw, int cap, int max_rows) { return min(max(min(raw, cap), 0), max_rows); }
 __device__ __forceinline__ double lane_of(double v, int lane) {          // (lane: the same in all lanes)
     return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane), __builtin_amdgcn_readlane(__double2loint(v), lane));
 }
 
-// Lane i < batch: a_i.  Other lanes: 0.  Called by whole wavefronts.
-__device__ __forceinline__ int ragged_share_lane(const int32_t* seq_lens, int batch, int nch, int cap, int max_rows, int share_cap) {
-    const int lane = threadIdx.x & 63;
-    const int len = lane < batch ? clamped_len(seq_lens[lane], cap, max_rows) : 0;
+// Lane i < batch: a_i.  Other lanes: 0.  Called by whole wavefronts.  APPEND: the rows kept so far and one more.
+template <bool APPEND>
+__device__ __forceinline__ int ragged_share_lane(const AttnParams& p, const int32_t* seq_lens) {
+    const int lane = threadIdx.x & 63, batch = p.ragged_batch, nch = p.nch, share_cap = p.share_cap;
+    const int raw = lane < batch ? seq_lens[lane] : 0;
+    const int len = lane >= batch ? 0 : APPEND ? min(min(max(raw, 0), p.cap1 - 1) + 1, p.n_sel) : clamped_len(raw, p.cap2, p.max_rows2);
     const double total = wave_sum((double)len);
     int a = 1;
     if (total > 0.0) {
@@ -136,19 +136,11 @@ __device__ __forceinline__ int ragged_share_lane(const int32_t* seq_lens, int ba
     return lane < batch ? a : 0;
 }
 
-// Partial results that the launch before this one left for (sequence, KV head) number bg.
-__device__ __forceinline__ int stored_chunks(const int32_t* counters, int64_t bg) {
-    return min(max(counters[bg * kCounterStride + kCountWord], 1), kMaxChunks);
-}
-__device__ __forceinline__ void store_chunks(int32_t* counters, int64_t bg, int nchunks) {
-    counters[bg * kCounterStride + kCountWord] = nchunks;
-}
-
 // Sequence, number within it and share of the workgroup at `slot` (b < 0: none).
 struct RaggedSlot { int b, c, nchunks; };
+template <bool APPEND>
 __device__ __forceinline__ RaggedSlot ragged_slot(const AttnParams& p, const int32_t* seq_lens, int slot) {
-    const int lane = threadIdx.x & 63;
-    const int a = ragged_share_lane(seq_lens, p.ragged_batch, p.nch, p.cap2, p.max_rows2, p.share_cap);
+    const int a = ragged_share_lane<APPEND>(p, seq_lens);
     const int incl = (int)wave_inclusive_scan((uint32_t)a);
     const int before = incl - a;
     const unsigned long long hit = __ballot(a > 0 && before <= slot && slot < incl);
@@ -160,8 +152,6 @@ __device__ __forceinline__ RaggedSlot ragged_slot(const AttnParams& p, const int
     }
     return r;
 }
-
-static inline int ragged_batch_of(const rk_geom* g) { return (g->batch > 1 && g->batch <= kRaggedMaxBatch) ? g->batch : 0; }
 
 __device__ __forceinline__ void coherent_store2(float* p, float a, float b) {
     const uint64_t v = (uint64_t)__float_as_uint(a) | ((uint64_t)__float_as_uint(b) << 32);
@@ -650,9 +640,9 @@ void attn_split_kernel(const uint16_t* k_first, const uint16_t* v_first, int64_t
     const int n_kv = heads_first ? gridDim.x : gridDim.y;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int n16 = lane & 15, c4 = lane >> 4;
-    constexpr bool kCanBeRagged = EMIT && !TWO_SEG;
+    constexpr bool kCanBeRagged = EMIT;
     if (kCanBeRagged && p.ragged_batch != 0) {           // which sequence this workgroup works for: by length
-        const RaggedSlot rs = ragged_slot(p, seq_lens, (int)(blockIdx.z * p.nch + blockIdx.x));
+        const RaggedSlot rs = ragged_slot<APPEND>(p, seq_lens, (int)(blockIdx.z * p.nch + blockIdx.x));
         if (rs.b < 0) return;
         b = __builtin_amdgcn_readfirstlane(rs.b);
         c = __builtin_amdgcn_readfirstlane(rs.c);
@@ -1792,7 +1782,7 @@ static int launch_score_split(const AttnParams& p, int batch, int G, int nchunk_
 int full_attn_stage(const rk_geom* geom, const void* q, rk_kv full, const int32_t* seq_lens, int32_t max_len,
                     void* out, float* weights, int64_t w_stride, float* lse, const int32_t* pred, int32_t pred_val,
                     const Workspace& ws, hipStream_t st, bool scores_only, int pool_half, bool no_v, int agg,
-                    bool co_run, bool defer_pool) {
+                    bool co_run, bool defer_pool, int nch) {
     const int G = geom->n_q_heads / geom->n_kv_heads;
     const bool fused = pool_half >= 0;
     const bool emit = weights != nullptr || fused;
@@ -1804,7 +1794,7 @@ int full_attn_stage(const rk_geom* geom, const void* q, rk_kv full, const int32_
     p.n_sel = 0;
     p.max_rows2 = max_len;
     p.cap1 = 0; p.cap2 = (int32_t)full.capacity;
-    p.nch = emit ? emit_split_workgroups(geom, max_len) : 0;       // (without scores: below)
+    p.nch = nch > 0 ? nch : emit ? emit_split_workgroups(geom, max_len) : 0;       // (without scores: below)
     if (co_run) {       // more, smaller workgroups, unless that means more partial results than the finish takes cheaply
         const int wide = split_workgroups(max_len, (int64_t)geom->batch * geom->n_kv_heads, kMaxChunks, kCoRunTargetWgs);
         if (wide <= kCoRunMaxChunks) p.nch = wide;
@@ -1893,18 +1883,11 @@ int full_attn_stage(const rk_geom* geom, const void* q, rk_kv full, const int32_
 }
 
 // The attention of an H2O step: raw scores to ws.scores, partial results to ws.part_ml / part_o, n_attend[b] set.
-// The launch is sized like the partial step it resembles (the new row has a workgroup of its own where that pays:
-// as the 65th tile of 2049 rows it would be a round of its own); *nch and *tail say how, for the kernel that merges.
+// Rows are shared out as full_attn_stage does it for a cache of the rows kept so far and the new one: the same
+// partial results, bit for bit.
 int h2o_attn_stage(const rk_geom* geom, const void* q, const rk_h2o_state& st, const void* k_new, const void* v_new,
-                   int32_t budget, const Workspace& ws, hipStream_t stream, int32_t* nch, int32_t* tail) {
+                   int32_t budget, const Workspace& ws, hipStream_t stream) {
     const int G = geom->n_q_heads / geom->n_kv_heads;
-    const int64_t problems = (int64_t)geom->batch * geom->n_kv_heads;
-    const int most = ws.max_chunks < kMergeChunks ? ws.max_chunks : kMergeChunks;
-    int own = 0;
-    int n = problems >= 16 ? batched_tagged_workgroups(budget, 1, &own, problems)
-                           : sliced_split_workgroups(budget, 1, &own, problems, most);
-    if (n > most) n = most;
-    if (n + own > most) own = 0;
     AttnParams p{};
     p.q = (const uint16_t*)q;
     p.k1 = (const uint16_t*)st.cache.k; p.v1 = (const uint16_t*)st.cache.v;
@@ -1914,13 +1897,13 @@ int h2o_attn_stage(const rk_geom* geom, const void* q, const rk_h2o_state& st, c
     p.seq_lens = st.n_rows; p.n_attend = st.n_attend;
     p.n_sel = budget + 1;
     p.cap1 = (int32_t)st.cache.capacity; p.cap2 = 1;
-    p.tail_wg = own; p.nch = n;
+    p.nch = h2o_split_workgroups(geom, budget + 1);
+    p.ragged_batch = ragged_batch_of(geom); p.share_cap = kMaxChunks; p.counters = ws.counters;
     p.Hq = geom->n_q_heads; p.Hkv = geom->n_kv_heads;
     p.scale = geom->scale;
     p.weights = ws.scores; p.w_stride = pooled_row_stride(budget + 1); p.w_vec = 1; p.w_inter = G == 4 ? 1 : 0;
     p.part_ml = ws.part_ml; p.part_o = ws.part_o; p.max_chunks = ws.max_chunks;
-    *nch = n; *tail = own;
-    return launch_split<true, true, false>(p, geom->batch, G, n + own, stream);
+    return launch_split<true, true, false>(p, geom->batch, G, p.nch, stream);
 }
 
 // The pooled scores and histograms of n_layers layers whose full attention ran with defer_pool,

@@ -226,6 +226,14 @@ __device__ __forceinline__ float aggregate(float acc, float w, int head, int agg
     return acc;                               // RK_AGG_FIRST
 }
 
+// Partial results that the launch before this one left for (sequence, KV head) number bg of a ragged batch.
+__device__ __forceinline__ int stored_chunks(const int32_t* counters, int64_t bg) {
+    return min(max(counters[bg * kCounterStride + kCountWord], 1), kMaxChunks);
+}
+__device__ __forceinline__ void store_chunks(int32_t* counters, int64_t bg, int nchunks) {
+    counters[bg * kCounterStride + kCountWord] = nchunks;
+}
+
 // Inclusive prefix sum over the 64 lanes of the wavefront.
 __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v) {
     const int lane = threadIdx.x & 63;

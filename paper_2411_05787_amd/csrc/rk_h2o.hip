@@ -8,7 +8,8 @@
 // care): the newest token, always in the last slot, moves into the slot of the dropped one, so the
 // cache stays dense without shifting rows.  rk_h2o_step takes two launches: the attention reads the new row from
 // the caller's tensors, and the kernel that follows merges the output, updates the totals and stores the row.
-// The parts as calls of their own (and new rows that are not 16-byte aligned) go append, rk_full_attn's kernels, update.
+// The parts as calls of their own (and new rows that are not 16-byte aligned) go append, rk_full_attn's kernels, update;
+// rows are shared out and partial results summed in the same order either way, so the results have the same bits.
 #include "rk_internal.h"
 #include "rk_device.h"
 
@@ -107,12 +108,13 @@ void h2o_update_kernel(rk_h2o_state st, const float* __restrict__ weights, int64
 // A chain of dependent steps on one CU: what it costs is round trips and barriers, so everything it reads is
 // requested before the first wait and the output merge runs between the requests and the weights.
 // Measured, 32 heads over 8, 2048 rows, us per launch: 4 sequences: append 2.9 + attention 12.6 + merge and weights 5.9 +
-// update 8.0 -> attention (the new row read where the caller has it) 10.3 + this 7.2; one sequence 5.8 + 7.5.
+// update 8.0 -> attention (the new row read where the caller has it) 8.8 + this 7.0; one sequence 5.7 + 7.0.  (A workgroup
+// of its own for the new row, and the small cache in wavefronts of one tile: 10.3, and other bits than the parts.)
 constexpr int kH2oHeld = 4;                        // rows per thread requested up front: 4096 in all
 template <int G>
 __global__ __launch_bounds__(kH2oThreads)
 void h2o_finish_kernel(rk_h2o_state st, const float* __restrict__ scores, int64_t s_stride, const float* __restrict__ part_ml,
-                       const float* __restrict__ part_o, int32_t max_chunks, int32_t nch, int32_t tail, int32_t max_rows,
+                       const float* __restrict__ part_o, int32_t max_chunks, int32_t nch, const int32_t* __restrict__ counters, int32_t max_rows,
                        const uint16_t* __restrict__ k_new, const uint16_t* __restrict__ v_new, const int32_t* __restrict__ seq_lens,
                        int32_t Hkv, int32_t budget, int32_t recent, int32_t agg, uint16_t* __restrict__ out,
                        int32_t* __restrict__ dropped, int64_t meta_stride) {
@@ -120,30 +122,31 @@ void h2o_finish_kernel(rk_h2o_state st, const float* __restrict__ scores, int64_
     const int cap = (int)st.cache.capacity;
     const int attend = min(max(st.n_attend[b], 1), cap), slot = attend - 1;      // the new token's slot
     const int n = min(attend, max_rows);
-    const int n1 = min(slot, max_rows);                                          // rows that were in the cache
     const int64_t bg = (int64_t)b * Hkv + g;
     float* total = st.total + bg * meta_stride;
     int32_t* pos = st.pos + bg * meta_stride;
     const float* sg = scores + bg * G * s_stride;
-    constexpr int kStretch = 128;                                                // rows a workgroup of the attention takes per round
-    auto active = [&](int rows) { return max(1, min(nch, (rows + kStretch - 1) / kStretch)); };
-    const bool has_new = n > n1;
-    const int nchunks = tail ? ((n1 > 0 || !has_new) ? active(n1) : 0) + (has_new ? 1 : 0) : active(n);
+    // (counters: a ragged batch, whose shares the attention left there; NULL: all sequences share rows out alike)
+    const int nchunks = counters != nullptr ? stored_chunks(counters, bg) : max(1, min(nch, (n + kMinChunk - 1) / kMinChunk));
 
     __shared__ uint64_t red[kH2oThreads / 64];
     __shared__ int sVictim;
     __shared__ __attribute__((aligned(8))) float sLse[G][2];
-    __shared__ float sW[G][kMergeChunks + 1];
+    __shared__ float sW[G][kMaxChunks];
     __shared__ float sInv[G];
-    constexpr int kPairs = G * kD / 2, kSets = kH2oThreads / kPairs;             // threads of a set: two dims of a head each
-    static_assert(kSets >= 1 && kSets <= 16, "sets of partial results");
-    __shared__ __attribute__((aligned(8))) float2 sAcc[kSets][kPairs];
+    // four sums over every fourth partial result each, as in the merge of rk_full_attn, so that the output has its bits
+    constexpr int kPairs = G * kD / 2, kSums = 4;                                // threads of a set: two dims of a head each
+    constexpr int kSets = kSums * kPairs <= kH2oThreads ? kSums : kSums / 2;     // sets of threads, kSums / kSets sums each
+    static_assert(kSets * kPairs <= kH2oThreads, "sets of partial results");
+    __shared__ __attribute__((aligned(8))) float2 sAcc[kSums][kPairs];
 
     // ---- requests: the chunk statistics, the first scores, totals and positions, the first partial outputs ----
-    float m[2] = {-INFINITY, -INFINITY}, l[2] = {0.f, 0.f};
+    constexpr int kStat = kMaxChunks / 64;
+    float m[kStat], l[kStat];
     if (w < G) {
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
+        for (int u = 0; u < kStat; ++u) {
+            m[u] = -INFINITY; l[u] = 0.f;
             const int c = lane + 64 * u;
             if (c < nchunks) {
                 const float2 t2 = *reinterpret_cast<const float2*>(part_ml + ((bg * kMaxChunks + c) * G + w) * 2);
@@ -176,7 +179,7 @@ void h2o_finish_kernel(rk_h2o_state st, const float* __restrict__ scores, int64_
     auto request_out = [&](int c0) {
 #pragma unroll
         for (int u = 0; u < kOut; ++u)
-            o[u] = *reinterpret_cast<const float2*>(po + (int64_t)min(c0 + u * kSets, nchunks - 1) * G * kD);
+            o[u] = *reinterpret_cast<const float2*>(po + (int64_t)min(c0 + u * kSums, nchunks - 1) * G * kD);
     };
     if (set < kSets) request_out(set);
     // the new row, two dims per lane: wavefront 14 its key, wavefront 15 its value
@@ -185,15 +188,18 @@ void h2o_finish_kernel(rk_h2o_state st, const float* __restrict__ scores, int64_
 
     // ---- lse of the heads, fp64, one wavefront each ----
     if (w < G) {
-        const float M = wave_max(fmaxf(m[0], m[1]));
+        float M = m[0];
+#pragma unroll
+        for (int u = 1; u < kStat; ++u) M = fmaxf(M, m[u]);
+        M = wave_max(M);
         double L = 0.0;
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
+        for (int u = 0; u < kStat; ++u) {
+            if (64 * u >= nchunks) break;
             const float wgt = m[u] == -INFINITY ? 0.f : fast_exp2((m[u] - M) * kLog2e);
             if (lane + 64 * u < nchunks) sW[w][lane + 64 * u] = wgt;
-            L += (double)wgt * (double)l[u];
+            L += wave_sum((double)wgt * (double)l[u]);
         }
-        L = wave_sum(L);
         if (lane == 0) {
             float hi = -INFINITY, lo = 0.f;
             if (L > 0.0) {
@@ -208,20 +214,23 @@ void h2o_finish_kernel(rk_h2o_state st, const float* __restrict__ scores, int64_
     if (tid == 0) sVictim = -1;
     __syncthreads();
 
-    // ---- output: every set of threads adds up every kSets-th partial result ----
+    // ---- output: sum x takes the partial results x, x + 4, x + 8 ... ----
     if (set < kSets) {
-        float2 acc = make_float2(0.f, 0.f);
-        for (int c0 = set; c0 < nchunks; c0 += kOut * kSets) {
-            if (c0 != set) request_out(c0);
 #pragma unroll
-            for (int u = 0; u < kOut; ++u) {
-                const int c = c0 + u * kSets;
-                const float wc = c < nchunks ? sW[gi_out][c] : 0.f;
-                acc.x = fmaf(wc, o[u].x, acc.x);
-                acc.y = fmaf(wc, o[u].y, acc.y);
+        for (int x = set; x < kSums; x += kSets) {
+            float2 acc = make_float2(0.f, 0.f);
+            for (int c0 = x; c0 < nchunks; c0 += kOut * kSums) {
+                if (c0 != set) request_out(c0);
+#pragma unroll
+                for (int u = 0; u < kOut; ++u) {
+                    const int c = c0 + u * kSums;
+                    const float wc = c < nchunks ? sW[gi_out][c] : 0.f;
+                    acc.x = fmaf(wc, o[u].x, acc.x);
+                    acc.y = fmaf(wc, o[u].y, acc.y);
+                }
             }
+            sAcc[x][e2] = acc;
         }
-        sAcc[set][e2] = acc;
     }
 
     // ---- totals, and the lowest of the old ones ----
@@ -263,7 +272,7 @@ void h2o_finish_kernel(rk_h2o_state st, const float* __restrict__ scores, int64_
     if (tid < kPairs) {
         float2 acc = sAcc[0][tid];
 #pragma unroll
-        for (int x = 1; x < kSets; ++x) { acc.x += sAcc[x][tid].x; acc.y += sAcc[x][tid].y; }
+        for (int x = 1; x < kSums; ++x) { acc.x += sAcc[x][tid].x; acc.y += sAcc[x][tid].y; }
         const float L = sInv[2 * tid / kD];
         const float ox = L > 0.f ? acc.x / L : 0.f, oy = L > 0.f ? acc.y / L : 0.f;
         const uint32_t pair = (uint32_t)f32_to_bf16(ox) | ((uint32_t)f32_to_bf16(oy) << 16);
@@ -358,19 +367,20 @@ extern "C" int rk_h2o_step(const rk_geom* geom, rk_h2o_state state, const void* 
     Workspace ws;
     if ((rc = check_workspace(geom, max_rows, 0, workspace, workspace_bytes, &ws)) != RK_OK) return rc;
     hipStream_t s = (hipStream_t)stream;
+    const int nch = h2o_split_workgroups(geom, max_rows);
     if (!aligned16(k_new) || !aligned16(v_new)) {      // the attention reads the new row where it is, in 16-byte loads
         if ((rc = append_stage(geom, state, k_new, v_new, seq_lens, s)) != RK_OK) return rc;
         const int64_t w_stride = pooled_row_stride(max_rows);
         rc = full_attn_stage(geom, q, state.cache, state.n_attend, max_rows, out, ws.scores, w_stride, nullptr,
-                             nullptr, 0, ws, s, false, -1, false, RK_AGG_MAX);
+                             nullptr, 0, ws, s, false, -1, false, RK_AGG_MAX, false, false, nch);
         if (rc != RK_OK) return rc;
         return update_stage(geom, state, ws.scores, w_stride, max_rows, budget, recent, agg, dropped, s);
     }
-    int32_t nch = 0, tail = 0;
-    if ((rc = h2o_attn_stage(geom, q, state, k_new, v_new, budget, ws, s, &nch, &tail)) != RK_OK) return rc;
+    if ((rc = h2o_attn_stage(geom, q, state, k_new, v_new, budget, ws, s)) != RK_OK) return rc;
+    const int32_t* counters = ragged_batch_of(geom) != 0 ? ws.counters : nullptr;
     switch (geom->n_q_heads / geom->n_kv_heads) {
 #define RK_CASE(g) case g: hipLaunchKernelGGL((h2o_finish_kernel<g>), dim3(geom->n_kv_heads, geom->batch), dim3(kH2oThreads), 0, s, state, \
-                       ws.scores, pooled_row_stride(max_rows), ws.part_ml, ws.part_o, ws.max_chunks, nch, tail, max_rows, \
+                       ws.scores, pooled_row_stride(max_rows), ws.part_ml, ws.part_o, ws.max_chunks, nch, counters, max_rows, \
                        (const uint16_t*)k_new, (const uint16_t*)v_new, seq_lens, geom->n_kv_heads, budget, recent, agg, \
                        (uint16_t*)out, dropped, state.cache.capacity); break;
         RK_CASE(1) RK_CASE(2) RK_CASE(3) RK_CASE(4) RK_CASE(5) RK_CASE(6) RK_CASE(7) RK_CASE(8)

@@ -214,6 +214,9 @@ static inline int topk_cand_cap(int64_t k) {
 //   scores    fp32  [B*Hq][max_len up to a multiple of 4]    raw scores between the two kernels of
 //                                                            rk_full_attn_select
 constexpr int kCounterStride = 32;       // int32 between two arrival counters: one 128-byte line each
+constexpr int kCountWord = 4;
+constexpr int kRaggedMaxBatch = 64;      // most sequences whose workgroups are shared out by length
+static inline int ragged_batch_of(const rk_geom* g) { return (g->batch > 1 && g->batch <= kRaggedMaxBatch) ? g->batch : 0; }
 constexpr int kTagDataRows = 43;          // a head's 128 output dims as rows of three (the last one holds two) ...
 constexpr int kTagRowsPerHead = kTagDataRows + 1;   // ... plus the row with the chunk's log-sum-exp (see merge_tagged_heads)
 constexpr int kTagSlots = kMergeChunks + 1;   // tagged partial results per (sequence, KV head): the chunks + the tail's own
@@ -276,6 +279,16 @@ static inline int emit_split_target(const rk_geom* g, int64_t max_len) {
 }
 static inline int emit_split_workgroups(const rk_geom* g, int64_t max_len) {
     return split_workgroups(max_len, (int64_t)g->batch * g->n_kv_heads, kMaxChunks, emit_split_target(g, max_len));
+}
+
+// The attention of an H2O step over budget + 1 rows: the same aim, 768 workgroups among the choices (that kernel is
+// resident three times per CU).
+static inline int h2o_split_workgroups(const rk_geom* g, int64_t max_rows) {
+    const int64_t problems = (int64_t)g->batch * g->n_kv_heads;
+    int64_t target = ((max_rows + 31) / 32 * problems / 16 + kComputeUnits / 2) / kComputeUnits * kComputeUnits;
+    if (target < kComputeUnits) target = kComputeUnits;
+    if (target > 4 * kComputeUnits) target = 4 * kComputeUnits;
+    return split_workgroups(max_rows, problems, kMaxChunks, (int)target);
 }
 
 // Workgroups per (sequence, KV head) of the same kernel where it merges its partial results itself (nothing but the
@@ -366,13 +379,14 @@ static inline int launch_status() {
 //     shaped for running beside another stream's kernels (see split_workgroups).  defer_pool (with
 //     pool_half >= 0 and out != NULL): only the output is finished; the raw scores and the chunk
 //     statistics stay in the workspace for pool_batched_stage, which does for several layers at
-//     once what the finishing kernel's pooling tiles do for one.
+//     once what the finishing kernel's pooling tiles do for one.  nch: workgroups per (sequence, KV head), where the
+//     caller's own rule decides (with weights; 0: this stage's).
 //   select_stage: top-K over the pooled scores and histogram that are in the workspace.
 __attribute__((visibility("hidden")))
 int full_attn_stage(const rk_geom* geom, const void* q, rk_kv full, const int32_t* seq_lens, int32_t max_len,
                     void* out, float* weights, int64_t w_stride, float* lse, const int32_t* pred, int32_t pred_val,
                     const Workspace& ws, hipStream_t st, bool scores_only, int pool_half, bool no_v, int agg,
-                    bool co_run = false, bool defer_pool = false);
+                    bool co_run = false, bool defer_pool = false, int nch = 0);
 __attribute__((visibility("hidden")))
 int pool_batched_stage(const rk_geom* geom, int n_layers, const Workspace* wss, const int32_t* seq_lens, int32_t max_len,
                        int64_t full_capacity, int pool_half, int agg, const int32_t* const* pred, int32_t pred_val,
@@ -380,7 +394,7 @@ int pool_batched_stage(const rk_geom* geom, int n_layers, const Workspace* wss, 
 //   h2o_attn_stage: the attention of an H2O step, scores and partial results left in the workspace.
 __attribute__((visibility("hidden")))
 int h2o_attn_stage(const rk_geom* geom, const void* q, const rk_h2o_state& st, const void* k_new, const void* v_new,
-                   int32_t budget, const Workspace& ws, hipStream_t stream, int32_t* nch, int32_t* tail);
+                   int32_t budget, const Workspace& ws, hipStream_t stream);
 //   gather_stage: rk_gather_small_kv plus an optional per-sequence count of refreshes.
 __attribute__((visibility("hidden")))
 int gather_stage(const rk_geom* geom, rk_kv full, const int32_t* idx, int32_t k, rk_kv small,

@@ -226,6 +226,54 @@ def test_h2o_step_equals_its_parts(rk, case, agg):
         assert ((x - y).abs() <= torch.maximum(x.abs(), y.abs()) * 2.0 ** -7 + 4e-6).all(), (name, step)
 
 
+# every sum of the merge of its own (up to 4 heads) and two to a thread (beyond), few and more than 64 partial results, shares by
+# length, evenly over more sequences than are shared out, the new row alone in a tile and in the middle of one
+H2O_BITS = [("batch4", 4, 8, 2048, [2048] * 4), ("ragged", 4, 8, 2048, [2048, 700, 1, 1999]), ("one", 4, 8, 2048, [2048]), ("g1_one_head_71_parts", 1, 1, 9000, [9000]),
+            ("g5_ragged", 5, 2, 1500, [1500, 31, 640]), ("g7_130_parts", 7, 1, 16700, [16700]), ("g8", 8, 2, 700, [700, 699]), ("g2_70_sequences", 2, 2, 130, [130, 64] * 35),
+            ("g3_overfull", 3, 2, 300, [303, 300]), ("g6", 6, 1, 31, [31])]
+
+
+@pytest.mark.parametrize("aligned", [True, False])
+@pytest.mark.parametrize("case", H2O_BITS, ids=[c[0] for c in H2O_BITS])
+def test_h2o_step_has_the_bits_of_append_attention_update(rk, case, aligned):
+    """rk_h2o_step against rk_h2o_append, rk_full_attn with its weights and rk_h2o_update called one after the other, over
+    three steps: the same bits everywhere, output and totals among them."""
+    name, G, Hkv, budget, n0 = case
+    say("h2o bits", name, aligned)
+    B, cap = len(n0), budget + 6
+    g = torch.Generator(device="cuda").manual_seed(budget + G)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
+    geom = rk.Geom(B, G * Hkv, Hkv, 128, SCALE)
+    K, V = rnd(B, Hkv, cap, 128), rnd(B, Hkv, cap, 128)
+    total = torch.rand(B, Hkv, cap, generator=g, device="cuda")
+    pos = torch.randperm(cap, generator=g, device="cuda").to(torch.int32).expand(B, Hkv, cap).contiguous()
+    sides = []
+    for _ in range(2):
+        s = {"K": K.clone(), "V": V.clone(), "total": total.clone(), "pos": pos.clone(),
+             "n_rows": torch.tensor(n0, dtype=torch.int32, device="cuda"), "n_attend": torch.zeros(B, dtype=torch.int32, device="cuda"),
+             "out": torch.zeros(B, G * Hkv, 128, dtype=torch.bfloat16, device="cuda"),
+             "dropped": torch.full((B, Hkv), -9, dtype=torch.int32, device="cuda"), "ws": rk.Workspace(geom, budget + 1, 1)}
+        s["st"] = rk.h2o_state(geom, s["K"], s["V"], s["total"], s["pos"], s["n_rows"], s["n_attend"])
+        sides.append(s)
+    a, b = sides
+    weights = torch.zeros(B, G * Hkv, budget + 1, device="cuda")
+    room = torch.zeros(2, B * Hkv * 128 + 8, dtype=torch.bfloat16, device="cuda")
+    for step in range(3):
+        q, new = rnd(B, G * Hkv, 128), rnd(2, B, Hkv, 128)
+        at = 0 if aligned else 2
+        room[:, at:at + new[0].numel()] = new.view(2, -1)
+        kn, vn = (room[i, at:at + new[0].numel()].view(B, Hkv, 128) for i in range(2))
+        assert (kn.data_ptr() % 16 == 0 and vn.data_ptr() % 16 == 0) == aligned
+        lens = torch.full((B,), cap + 1 + step, dtype=torch.int32, device="cuda")
+        rk.rk_h2o_step(geom, a["st"], q, kn, vn, lens, budget, budget // 2, a["out"], dropped=a["dropped"], workspace=a["ws"])
+        rk.rk_h2o_append(geom, b["st"], kn, vn, lens, budget)
+        rk.rk_full_attn(geom, q, b["K"], b["V"], b["n_attend"], budget + 1, b["out"], weights=weights, workspace=b["ws"])
+        rk.rk_h2o_update(geom, b["st"], weights, budget, budget // 2, dropped=b["dropped"])
+        torch.cuda.synchronize()
+        for key in ("K", "V", "pos", "n_rows", "n_attend", "dropped", "total", "out"):
+            assert torch.equal(a[key], b[key]), (name, step, key)
+
+
 @pytest.mark.parametrize("B", [24, 25], ids=["up_to_192MB", "beyond_192MB"])
 def test_batched_gather_of_large_small_caches(rk, B):
     """The batched gather on both sides of the size from which it stores past the caches: bit copies of the selected
