@@ -314,6 +314,11 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
 // max and sum across lanes, and w_u reaches the other lanes as a scalar operand (v_readlane), which
 // leaves three multiply-adds per chunk and lane.  Chunks are summed in order: the result does not
 // depend on which workgroup merges or when.
+// EXACT (full passes whose output merge would otherwise be a launch of its own): the rows hold the unnormalised sums
+// sum_j e^{s_j - m} v_j and the last row { m, l, 0, tag }.  A lambda rounded to fp32 costs a weight |lambda| * 2^-24 (6e-5
+// at 1000), which that launch does not lose; so the sum of the weights is taken in fp64 from the pairs, the quotient
+// is one division, and all is summed in the order of block_head_lse and block_head_out, four sums over every fourth
+// chunk: the same bits.  (At most kMergeChunks = 64 chunks: one per lane.)
 constexpr int kTagSpinLimit = 1 << 16;            // re-reads of rows still in flight before giving up (NaN output)
 constexpr int kAgentScopeAux = 16;                // cache-policy operand of buffer loads and stores: sc1
 
@@ -324,6 +329,21 @@ __device__ __forceinline__ void store_tagged_row(uint32_t* rows, int n_rows, int
     const u32x4 v = {__float_as_uint(x0), __float_as_uint(x1), __float_as_uint(x2), tag};
     __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, row * 16, 0, kAgentScopeAux);
 }
+
+// EXACT: the weights e^{m_c - max} of a head, lane c's in lane c (0 beyond nchunks), from the rows { m, l } of all chunks,
+// and what the output is divided by.
+struct ExactWeights { float wgt, L, lse; };
+__device__ __forceinline__ ExactWeights exact_weights(const u32x4 ml, int lane, int nchunks) {
+    const float m = lane < nchunks ? __uint_as_float(ml.x) : -INFINITY, l = lane < nchunks ? __uint_as_float(ml.y) : 0.f;
+    const float M = wave_max(m);
+    ExactWeights e;
+    e.wgt = m == -INFINITY ? 0.f : fast_exp2((m - M) * kLog2e);
+    const double L64 = wave_sum((double)e.wgt * (double)l);
+    e.L = (float)L64;
+    e.lse = L64 > 0.0 ? M + __logf(e.L) : -INFINITY;
+    return e;
+}
+__device__ __forceinline__ float exact_quotient(float sum, float L) { return L > 0.f ? sum / L : 0.f; }
 
 // Merge of the heads gi0, gi0 + 4, ... (NH of them; those >= G are skipped) of one (sequence, KV
 // head) by one whole wavefront.  TB partial results per round trip: the loads of all NH heads are
@@ -405,6 +425,95 @@ __device__ __forceinline__ void merge_tagged_heads(const AttnParams& p, int b, i
     }
 }
 
+// Three output elements of data row r of a head (two of the last row), and its lse; NaN where rows never arrived.
+template <int G>
+__device__ __forceinline__ void store_merged(const AttnParams& p, int b, int g, int gi, int r, bool has_row, bool has_lse,
+                                             float o0, float o1, float o2, float lse, bool good) {
+    const float nan = __uint_as_float(0x7fc00000u);
+    const uint32_t p01 = good ? pack_bf16(o0, o1) : pack_bf16(nan, nan);
+    const uint32_t p2 = good ? pack_bf16(o2, 0.f) : pack_bf16(nan, 0.f);
+    const int64_t bh = (int64_t)b * p.Hq + g * G + gi;
+    uint16_t* o = p.out + bh * kD + 3 * r;
+    if (has_row) {
+        o[0] = (uint16_t)p01; o[1] = (uint16_t)(p01 >> 16);
+        if (r < kTagDataRows - 1) o[2] = (uint16_t)p2;
+    }
+    if (has_lse) p.lse[bh] = good ? lse : nan;
+}
+
+// EXACT: the weights of all chunks first, then the rows.
+template <int G, int NH, int TB>
+__device__ __forceinline__ void merge_exact_heads(const AttnParams& p, int b, int g, int gi0, int nchunks_any_lane, uint32_t tag) {
+    constexpr int ROWS = G * kTagRowsPerHead;
+    static_assert(TB % 4 == 0, "chunk c belongs to sum c % 4");
+    const int nchunks = __builtin_amdgcn_readfirstlane(nchunks_any_lane);
+    const int lane = threadIdx.x & 63;
+    const int64_t bg = (int64_t)b * p.Hkv + g;
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        p.tag_rows + bg * kTagSlots * ROWS * 4, 0, kTagSlots * ROWS * 16, 0x00020000);
+    const int r = min(lane, kTagDataRows - 1);
+    auto head_off = [&](int i) { return min(gi0 + i * kSplitWaves, G - 1) * kTagRowsPerHead; };
+    u32x4 ml[NH];
+    bool ok = false, good = true;
+    for (int tries = 0; !__all(ok) && tries < kTagSpinLimit; ++tries) {
+        if (tries > 0) __builtin_amdgcn_s_sleep(2);
+        ok = true;
+#pragma unroll
+        for (int i = 0; i < NH; ++i) {
+            ml[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (min(lane, nchunks - 1) * ROWS + head_off(i) + kTagDataRows) * 16, 0, kAgentScopeAux);
+            ok = ok && ml[i].w == tag;
+        }
+    }
+    good = __all(ok);
+    ExactWeights e[NH];
+    float acc[NH][4][3];
+#pragma unroll
+    for (int i = 0; i < NH; ++i) {
+        e[i] = exact_weights(ml[i], lane, nchunks);
+#pragma unroll
+        for (int x = 0; x < 4; ++x) { acc[i][x][0] = 0.f; acc[i][x][1] = 0.f; acc[i][x][2] = 0.f; }
+    }
+#pragma unroll 1
+    for (int c0 = 0; c0 < nchunks; c0 += TB) {                   // one round trip up to TB partial results
+        u32x4 v[NH][TB];
+        ok = false;
+        for (int tries = 0; !__all(ok) && tries < kTagSpinLimit; ++tries) {      // again only for rows that were still in flight
+            if (tries > 0) __builtin_amdgcn_s_sleep(2);
+#pragma unroll
+            for (int i = 0; i < NH; ++i)
+#pragma unroll
+                for (int u = 0; u < TB; ++u)
+                    v[i][u] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (min(c0 + u, nchunks - 1) * ROWS + head_off(i) + r) * 16, 0, kAgentScopeAux);
+            ok = true;
+#pragma unroll
+            for (int i = 0; i < NH; ++i)
+#pragma unroll
+                for (int u = 0; u < TB; ++u) ok = ok && v[i][u].w == tag;
+        }
+        good = good && __all(ok);
+#pragma unroll
+        for (int i = 0; i < NH; ++i)
+#pragma unroll
+            for (int u = 0; u < TB; ++u) {
+                const float wl = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(e[i].wgt), min(c0 + u, 63)));
+                const float wu = c0 + u < nchunks ? wl : 0.f;
+                acc[i][u & 3][0] = fmaf(wu, __uint_as_float(v[i][u].x), acc[i][u & 3][0]);
+                acc[i][u & 3][1] = fmaf(wu, __uint_as_float(v[i][u].y), acc[i][u & 3][1]);
+                acc[i][u & 3][2] = fmaf(wu, __uint_as_float(v[i][u].z), acc[i][u & 3][2]);
+            }
+    }
+#pragma unroll
+    for (int i = 0; i < NH; ++i) {
+        const int gi = gi0 + i * kSplitWaves;
+        if (gi < G) {
+            float o[3];
+#pragma unroll
+            for (int d = 0; d < 3; ++d) o[d] = exact_quotient(acc[i][0][d] + acc[i][1][d] + acc[i][2][d] + acc[i][3][d], e[i].L);
+            store_merged<G>(p, b, g, gi, r, lane < kTagDataRows, lane == 0, o[0], o[1], o[2], e[i].lse, good);
+        }
+    }
+}
+
 // ---- merge by slices ----
 // The same merge, shared out: workgroup c of the nchunks of a (sequence, KV head) merges a slice of its output,
 // some consecutive data rows of one head (one per lane), reading them from every partial result.  One wavefront
@@ -430,7 +539,7 @@ __device__ __forceinline__ TagSlice tag_slice_of(int c, int nchunks) {
 
 // TB: partial results read (at least nchunks).  Rows still in flight are re-read at most `spin` times; if
 // some are still missing then, the output is left alone and the result is false (final: NaN is written instead).
-template <int G, int TB>
+template <int G, int TB, bool EXACT>
 __device__ __forceinline__ bool merge_tagged_slice(const AttnParams& p, int b, int g, const __amdgpu_buffer_rsrc_t rsrc, const TagSlice sl,
                                                    int nchunks, uint32_t tag, int spin, bool final) {
     constexpr int STRIDE = G * kTagRowsPerHead * 16;               // bytes of a partial result
@@ -447,7 +556,7 @@ __device__ __forceinline__ bool merge_tagged_slice(const AttnParams& p, int b, i
     while (!__all(ok) && tries++ < spin) {
         if (tries > 1) __builtin_amdgcn_s_sleep(2);
         lt = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lam_off, 0, kAgentScopeAux);
-        l0 = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lam0_off, 0, kAgentScopeAux);
+        l0 = EXACT ? lt : __builtin_amdgcn_raw_buffer_load_b128(rsrc, lam0_off, 0, kAgentScopeAux);
 #pragma unroll
         for (int u = 0; u < TB; ++u)
             v[u] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, row_off, min(u * STRIDE, last), kAgentScopeAux);
@@ -458,6 +567,22 @@ __device__ __forceinline__ bool merge_tagged_slice(const AttnParams& p, int b, i
     }
     const bool good = __all(ok);
     if (!good && !final) return false;
+    if constexpr (EXACT) {
+        const ExactWeights e = exact_weights(lt, lane, nchunks);
+        float acc[4][3] = {};
+#pragma unroll
+        for (int u = 0; u < TB; ++u) {
+            const float wu = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(e.wgt), u));
+            acc[u & 3][0] = fmaf(wu, __uint_as_float(v[u].x), acc[u & 3][0]);
+            acc[u & 3][1] = fmaf(wu, __uint_as_float(v[u].y), acc[u & 3][1]);
+            acc[u & 3][2] = fmaf(wu, __uint_as_float(v[u].z), acc[u & 3][2]);
+        }
+        float o[3];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) o[d] = exact_quotient(acc[0][d] + acc[1][d] + acc[2][d] + acc[3][d], e.L);
+        store_merged<G>(p, b, g, sl.gi, r, lane < sl.n_rows, sl.r0 == 0 && lane == 0, o[0], o[1], o[2], e.lse, good);
+        return true;
+    }
     const float lam = lane < nchunks ? __uint_as_float(lt.x) : -INFINITY;
     // reference: the first chunk's lambda, unless some chunk lies so far from it that a weight could overflow
     // or all could vanish (then the largest, by a reduction)
@@ -494,7 +619,7 @@ __device__ __forceinline__ bool merge_tagged_slice(const AttnParams& p, int b, i
 // sums are added across the lanes, (q0 + q1) + (q2 + q3).  A lane's chunks are a quarter of the loads, checks and
 // multiply-adds of the loop above; the weight of a chunk comes from the lane that holds it (ds_bpermute).
 // Slots past the last chunk re-read the last chunk's row, with weight 0 (their weight lanes hold none).
-template <int G, int TBP>
+template <int G, int TBP, bool EXACT>
 __device__ __forceinline__ bool merge_tagged_slice4(const AttnParams& p, int b, int g, const __amdgpu_buffer_rsrc_t rsrc, const TagSlice sl,
                                                     int nchunks, uint32_t tag, int spin, bool final) {
     constexpr int STRIDE = G * kTagRowsPerHead * 16;               // bytes of a partial result
@@ -506,7 +631,8 @@ __device__ __forceinline__ bool merge_tagged_slice4(const AttnParams& p, int b, 
     const int lam_off = min(lane, nchunks - 1) * STRIDE + (sl.gi * kTagRowsPerHead + kTagDataRows) * 16;   // lane u: chunk u's lambda row
     const int lam0_off = (sl.gi * kTagRowsPerHead + kTagDataRows) * 16;                            // the first chunk's, for every lane
     const int first = q * per;                                     // this lane's first chunk
-    const int base_v = row_off + first * STRIDE;
+    const int base_v = row_off + (EXACT ? q : first) * STRIDE;     // (EXACT: sum q takes the chunks q, q + 4, q + 8 ...)
+    constexpr int NEXT = EXACT ? 4 * STRIDE : STRIDE;
     const int limit_v = row_off + (nchunks - 1) * STRIDE;
     u32x4 v[TBP], lt, l0;
     bool ok = false;
@@ -514,10 +640,10 @@ __device__ __forceinline__ bool merge_tagged_slice4(const AttnParams& p, int b, 
     while (!__all(ok) && tries++ < spin) {
         if (tries > 1) __builtin_amdgcn_s_sleep(2);
         lt = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lam_off, 0, kAgentScopeAux);
-        l0 = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lam0_off, 0, kAgentScopeAux);
+        l0 = EXACT ? lt : __builtin_amdgcn_raw_buffer_load_b128(rsrc, lam0_off, 0, kAgentScopeAux);
 #pragma unroll
         for (int u = 0; u < TBP; ++u)
-            v[u] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, min(base_v + u * STRIDE, limit_v), 0, kAgentScopeAux);
+            v[u] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, min(base_v + u * NEXT, limit_v), 0, kAgentScopeAux);
         uint32_t bad = (lt.w ^ tag) | (l0.w ^ tag);
 #pragma unroll
         for (int u = 0; u < TBP; ++u) bad |= v[u].w ^ tag;
@@ -525,6 +651,27 @@ __device__ __forceinline__ bool merge_tagged_slice4(const AttnParams& p, int b, 
     }
     const bool good = __all(ok);
     if (!good && !final) return false;
+    if constexpr (EXACT) {
+        const ExactWeights e = exact_weights(lt, lane, nchunks);
+        float acc[3] = {0.f, 0.f, 0.f};
+        static_assert(4 * TBP <= 64, "the weight of chunk q + 4 u is in a lane");
+#pragma unroll
+        for (int u = 0; u < TBP; ++u) {
+            const float wu = __int_as_float(__builtin_amdgcn_ds_bpermute((q + 4 * u) * 4, __float_as_int(e.wgt)));      // 0 beyond nchunks
+            acc[0] = fmaf(wu, __uint_as_float(v[u].x), acc[0]);
+            acc[1] = fmaf(wu, __uint_as_float(v[u].y), acc[1]);
+            acc[2] = fmaf(wu, __uint_as_float(v[u].z), acc[2]);
+        }
+        float o[3];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {                              // ((sum 0 + sum 1) + sum 2) + sum 3, in the lanes of the first quarter
+            const LanePair x = rows_xor16(__float_as_int(acc[d]));
+            const LanePair even = halves_xor32(x.a), odd = halves_xor32(x.b);
+            o[d] = exact_quotient(__int_as_float(even.a) + __int_as_float(odd.a) + __int_as_float(even.b) + __int_as_float(odd.b), e.L);
+        }
+        store_merged<G>(p, b, g, sl.gi, r, lane < sl.n_rows, sl.r0 == 0 && lane == 0, o[0], o[1], o[2], e.lse, good);
+        return true;
+    }
     const float lam = lane < nchunks ? __uint_as_float(lt.x) : -INFINITY;
     float ref = __uint_as_float(l0.x);
     const bool near = lane >= nchunks || lam == -INFINITY || fabsf(lam - ref) < 20.f;
@@ -559,16 +706,16 @@ __device__ __forceinline__ bool merge_tagged_slice4(const AttnParams& p, int b, 
 }
 // (17 partial results at the shape that matters most: 16 workgroups for 2048 selected rows and one for the
 // rows decoded since; otherwise up to 20)
-template <int G>
+template <int G, bool EXACT>
 __device__ __forceinline__ bool merge_tagged_slice_n(const AttnParams& p, int b, int g, const __amdgpu_buffer_rsrc_t rsrc, const TagSlice sl,
                                                      int nchunks, uint32_t tag, int spin, bool final) {
     if (sl.n_rows <= 16 && nchunks > 4) {
-        if (nchunks <= 20) return merge_tagged_slice4<G, 5>(p, b, g, rsrc, sl, nchunks, tag, spin, final);
-        if (nchunks <= 36) return merge_tagged_slice4<G, 9>(p, b, g, rsrc, sl, nchunks, tag, spin, final);
-        return merge_tagged_slice4<G, 16>(p, b, g, rsrc, sl, nchunks, tag, spin, final);
+        if (nchunks <= 20) return merge_tagged_slice4<G, 5, EXACT>(p, b, g, rsrc, sl, nchunks, tag, spin, final);
+        if (nchunks <= 36) return merge_tagged_slice4<G, 9, EXACT>(p, b, g, rsrc, sl, nchunks, tag, spin, final);
+        return merge_tagged_slice4<G, 16, EXACT>(p, b, g, rsrc, sl, nchunks, tag, spin, final);
     }
-    if (nchunks <= 17) return merge_tagged_slice<G, 17>(p, b, g, rsrc, sl, nchunks, tag, spin, final);
-    return merge_tagged_slice<G, 20>(p, b, g, rsrc, sl, nchunks, tag, spin, final);
+    if (nchunks <= 17) return merge_tagged_slice<G, 17, EXACT>(p, b, g, rsrc, sl, nchunks, tag, spin, final);
+    return merge_tagged_slice<G, 20, EXACT>(p, b, g, rsrc, sl, nchunks, tag, spin, final);
 }
 constexpr int kSliceChunks = 20, kSliceChunks4 = 64;   // the merge by slices serves up to this many partial results (slices of up to 16 rows: the latter)
 
@@ -599,7 +746,7 @@ constexpr int kSliceChunks = 20, kSliceChunks4 = 64;   // the merge by slices se
 // seq_lens[b] rows of it (the rows kept so far), the second the new token's row, read where the caller has
 // it: k2 / v2 with one row per (sequence, KV head).  n_sel is the most rows the step attends over; a cache that
 // is over it already (outside the policy's contract) is cut there and the new row is left out.
-template <int G, int NW, bool EMIT, bool TWO_SEG, bool LAZY = false, bool TAGGED = !EMIT, bool TRIG = false>
+template <int G, int NW, bool EMIT, bool TWO_SEG, bool LAZY = false, bool TAGGED = !EMIT, bool TRIG = false, bool EXACT = false>
 __global__ __launch_bounds__(NW * 64, 2)
 void attn_split_kernel(const uint16_t* k_first, const uint16_t* v_first, int64_t s_b_and_tail, int32_t s_h, int32_t spec_rows,
                        const int32_t* seq_lens, const int32_t* tail_start, const int32_t* pred, const uint32_t* epochs,
@@ -609,6 +756,7 @@ void attn_split_kernel(const uint16_t* k_first, const uint16_t* v_first, int64_t
     // per-chunk (max, sum) pairs are still stored for the kernels that turn the scores into weights)
     static_assert(!TRIG || (TWO_SEG && !LAZY), "the trigger is tested by the partial step");
     constexpr bool APPEND = EMIT && TWO_SEG;
+    static_assert(!EXACT || (EMIT && TAGGED), "the exact merge belongs to the full passes that merge inside");
     static_assert(!APPEND || (!TAGGED && !TRIG && !LAZY), "merged by the kernel that updates the totals");
     // The leading arguments repeat what the first loads need (the cache that holds the first rows,
     // its strides, the two length arrays, the predicate, the call numbers): 16 dwords that the command processor
@@ -1107,14 +1255,14 @@ void attn_split_kernel(const uint16_t* k_first, const uint16_t* v_first, int64_t
                     a2 = fmaf(sc, sO[ww][gi][min(d + 2, kD - 1)], a2);
                     L = fmaf(sc, sLw[ww][gi], L);
                 }
-                const float inv = L > 0.f ? __builtin_amdgcn_rcpf(L) : 0.f;
-                const float lam = L > 0.f ? M + __logf(L) : -INFINITY;
+                const float inv = EXACT ? 1.f : L > 0.f ? __builtin_amdgcn_rcpf(L) : 0.f;
+                const float lam = EXACT ? M : L > 0.f ? M + __logf(L) : -INFINITY;
                 if (EMIT && lane == 0)
                     *reinterpret_cast<float2*>(p.part_ml + ((bg * kMaxChunks + c_rec) * G + gi) * 2) = make_float2(M, L);
                 const bool lam_row = lane == kTagDataRows;
                 if (lane <= kTagDataRows)
                     store_tagged_row(trows, G * kTagRowsPerHead, gi * kTagRowsPerHead + lane, lam_row ? lam : a0 * inv,
-                                     lam_row ? 0.f : a1 * inv, (lam_row || d + 2 >= kD) ? 0.f : a2 * inv, tag);
+                                     lam_row ? (EXACT ? L : 0.f) : a1 * inv, (lam_row || d + 2 >= kD) ? 0.f : a2 * inv, tag);
             }
         }
         int32_t* counter = p.counters + bg * kCounterStride;
@@ -1147,7 +1295,7 @@ void attn_split_kernel(const uint16_t* k_first, const uint16_t* v_first, int64_t
         }
         if (slices && w == NW - 1) {
             const TagSlice sl = my_slice;
-            if (sl.n_rows > 0 && !merge_tagged_slice_n<G>(p, b, g, tag_rsrc, sl, nchunks, tag, p.slice_spin, false)) {
+            if (sl.n_rows > 0 && !merge_tagged_slice_n<G, EXACT>(p, b, g, tag_rsrc, sl, nchunks, tag, p.slice_spin, false)) {
                 const unsigned long long bit = 1ull << c_rec;
                 uint32_t seen = 0;
                 if (lane == 0) {
@@ -1157,7 +1305,7 @@ void attn_split_kernel(const uint16_t* k_first, const uint16_t* v_first, int64_t
                 }
                 seen = __builtin_amdgcn_readfirstlane(seen);
                 if (seen == tag) {
-                    merge_tagged_slice_n<G>(p, b, g, tag_rsrc, sl, nchunks, tag, kTagSpinLimit, true);
+                    merge_tagged_slice_n<G, EXACT>(p, b, g, tag_rsrc, sl, nchunks, tag, kTagSpinLimit, true);
                     if (lane == 0) __hip_atomic_fetch_and(pend, ~bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
             }
@@ -1166,7 +1314,8 @@ void attn_split_kernel(const uint16_t* k_first, const uint16_t* v_first, int64_t
         if (sTicket != nchunks - 1) return;
         if (!slices) {
             // last arrival: every wavefront merges its heads
-            merge_tagged_heads<G, UPW, (UPW == 1 ? 20 : 17)>(p, b, g, w, nchunks, tag);
+            if constexpr (EXACT) merge_exact_heads<G, UPW, (UPW == 1 ? 20 : 16)>(p, b, g, w, nchunks, tag);
+            else                 merge_tagged_heads<G, UPW, (UPW == 1 ? 20 : 17)>(p, b, g, w, nchunks, tag);
             if (tid == 0) {
                 __hip_atomic_store(&p.epochs[bg], tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);       // next call
@@ -1181,7 +1330,7 @@ void attn_split_kernel(const uint16_t* k_first, const uint16_t* v_first, int64_t
             sl.gi = __builtin_amdgcn_readfirstlane(sl.gi); sl.r0 = __builtin_amdgcn_readfirstlane(sl.r0);
             sl.n_rows = __builtin_amdgcn_readfirstlane(sl.n_rows);
             if ((k & (NW - 1)) == w && cb < nchunks && sl.n_rows > 0)
-                merge_tagged_slice_n<G>(p, b, g, tag_rsrc, sl, nchunks, tag, kTagSpinLimit, true);
+                merge_tagged_slice_n<G, EXACT>(p, b, g, tag_rsrc, sl, nchunks, tag, kTagSpinLimit, true);
         }
         return;
     }
@@ -1683,7 +1832,7 @@ static void set_slice_merge(AttnParams& p, bool tagged, int64_t workgroups) {
     p.slice_spin = g_slice_spin.load(std::memory_order_relaxed);
 }
 
-template <int G, bool EMIT, bool TWO_SEG, bool TAGGED, bool TRIG = false>
+template <int G, bool EMIT, bool TWO_SEG, bool TAGGED, bool TRIG = false, bool EXACT = false>
 static int launch_split_g(const AttnParams& p, int batch, int nchunk_grid, hipStream_t st) {
     // (measured on the kernel alone, us per launch, chunk as grid x / KV head as grid x: 8 KV heads, 512
     // workgroups, 32768..33000 rows 25.8 - 29.2 / 25.2 - 26.0; 4 KV heads, 65536..65800 rows 27.0 - 32.7 /
@@ -1696,7 +1845,7 @@ static int launch_split_g(const AttnParams& p, int batch, int nchunk_grid, hipSt
     const int32_t spec_rows = TWO_SEG ? (p.n_sel < p.cap1 ? p.n_sel : p.cap1) : p.cap2;
     const int64_t tail_c = (TWO_SEG && p.tail_wg) ? p.nch : heads_first ? kHeadsFirst : kNoTailWg;
     // (TRIG: the pointers the test needs first travel in the preloaded slots of the predicate and the call numbers)
-    hipLaunchKernelGGL((attn_split_kernel<G, 4, EMIT, TWO_SEG, false, TAGGED, TRIG>), grid, dim3(256), 0, st,
+    hipLaunchKernelGGL((attn_split_kernel<G, 4, EMIT, TWO_SEG, false, TAGGED, TRIG, EXACT>), grid, dim3(256), 0, st,
                        TWO_SEG ? p.k1 : p.k2, TWO_SEG ? p.v1 : p.v2, (TWO_SEG ? p.s1_b : p.s2_b) | (tail_c << 56),
                        (int32_t)(TWO_SEG ? p.s1_h : p.s2_h), spec_rows, p.seq_lens, p.tail_start,
                        TRIG ? reinterpret_cast<const int32_t*>(p.q) : p.pred,
@@ -1737,6 +1886,20 @@ static int launch_split(const AttnParams& p, int batch, int G, int nchunk_grid, 
         case 6: return launch_split_g<6, EMIT, TWO_SEG, TAGGED>(p, batch, nchunk_grid, st);
         case 7: return launch_split_g<7, EMIT, TWO_SEG, TAGGED>(p, batch, nchunk_grid, st);
         case 8: return launch_split_g<8, EMIT, TWO_SEG, TAGGED>(p, batch, nchunk_grid, st);
+        default: return RK_ERR_UNSUPPORTED;
+    }
+}
+
+// The full pass that merges its output inside (exact: see merge_exact_heads; always for groups of more than 4 heads).
+static int launch_split_inside(const AttnParams& p, int batch, int G, int nchunk_grid, bool exact, hipStream_t st) {
+    switch (G) {
+#define RK_CASE(g) case g: return exact ? launch_split_g<g, true, false, true, false, true>(p, batch, nchunk_grid, st) \
+                                        : launch_split_g<g, true, false, true, false, false>(p, batch, nchunk_grid, st);
+        RK_CASE(1) RK_CASE(2) RK_CASE(3) RK_CASE(4)
+#undef RK_CASE
+#define RK_CASE(g) case g: return launch_split_g<g, true, false, true, false, true>(p, batch, nchunk_grid, st);
+        RK_CASE(5) RK_CASE(6) RK_CASE(7) RK_CASE(8)
+#undef RK_CASE
         default: return RK_ERR_UNSUPPORTED;
     }
 }
@@ -1831,7 +1994,7 @@ int full_attn_stage(const rk_geom* geom, const void* q, rk_kv full, const int32_
             p.nch = inside;
             p.share_cap = kMergeChunks;
             set_slice_merge(p, true, (int64_t)p.nch * geom->batch * geom->n_kv_heads);
-            return launch_split<true, false, true>(p, geom->batch, G, p.nch, st);
+            return launch_split_inside(p, geom->batch, G, p.nch, true, st);
         }
         p.nch = wide;
         int rc = launch_split<true, false>(p, geom->batch, G, p.nch, st);
@@ -1851,7 +2014,7 @@ int full_attn_stage(const rk_geom* geom, const void* q, rk_kv full, const int32_
     int rc;
     if (merge_inside) {
         set_slice_merge(p, true, (int64_t)nchunk_grid * geom->batch * geom->n_kv_heads);
-        rc = launch_split<true, false, true>(p, geom->batch, G, nchunk_grid, st);
+        rc = launch_split_inside(p, geom->batch, G, nchunk_grid, !merges_in_fp32(geom, max_len), st);
     } else {
         rc = no_v ? launch_score_split(p, geom->batch, G, nchunk_grid, st)
                   : launch_split<true, false>(p, geom->batch, G, nchunk_grid, st);

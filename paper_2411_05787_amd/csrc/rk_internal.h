@@ -218,7 +218,7 @@ constexpr int kCountWord = 4;
 constexpr int kRaggedMaxBatch = 64;      // most sequences whose workgroups are shared out by length
 static inline int ragged_batch_of(const rk_geom* g) { return (g->batch > 1 && g->batch <= kRaggedMaxBatch) ? g->batch : 0; }
 constexpr int kTagDataRows = 43;          // a head's 128 output dims as rows of three (the last one holds two) ...
-constexpr int kTagRowsPerHead = kTagDataRows + 1;   // ... plus the row with the chunk's log-sum-exp (see merge_tagged_heads)
+constexpr int kTagRowsPerHead = kTagDataRows + 1;   // ... plus the row with the chunk's log-sum-exp or (max, sum) (see merge_tagged_heads)
 constexpr int kTagSlots = kMergeChunks + 1;   // tagged partial results per (sequence, KV head): the chunks + the tail's own
 struct Workspace {
     int32_t* counters;
@@ -306,6 +306,16 @@ static inline int inside_split_workgroups(const rk_geom* g, int64_t max_len) {
     if ((g->batch > 1 || max_len > (int64_t)kMergeChunks * kMinChunk) && n * problems < kComputeUnits) return 0;
     return n;
 }
+// Deferred full steps whose merge inside weighs the partial results by their fp32 log-sum-exps, as a partial step does
+// (|lse| * 2^-24 to a weight), instead of exactly as the merge launch (see merge_tagged_heads): groups of up to 4 heads,
+// rows shared out alike, one residency round at 4 tiles per wavefront.  The exact form takes 0.6 us longer in that one
+// launch (32 layers of 33k rows 1028 -> 1046 us per step).
+static inline bool merges_in_fp32(const rk_geom* g, int64_t max_len) {
+    const int64_t tiles = (max_len + 31) / 32 * g->batch * g->n_kv_heads;
+    return g->n_q_heads <= 4 * g->n_kv_heads && ragged_batch_of(g) == 0 && tiles < 40 * kComputeUnits &&
+           inside_split_workgroups(g, max_len) == emit_split_workgroups(g, max_len);
+}
+
 // ... and of a full step whose pooling is deferred: the pooling kernels must be told the same number.
 static inline int deferred_split_workgroups(const rk_geom* g, int64_t max_len) {
     const int inside = inside_split_workgroups(g, max_len);

@@ -177,6 +177,64 @@ def test_ragged_batches_cover_every_row_once(rk, case, G):
             assert (d <= torch.maximum(out[b].double().abs(), ref.abs()) * 2.0 ** -7 + 4e-6).all(), (name, kind, b)
 
 
+@pytest.mark.parametrize("G", [1, 4, 5, 7, 8])
+@pytest.mark.parametrize("case", [("slices_64", 4, [8192]), ("slices_64_long", 4, [33000]), ("longer", 4, [90000]), ("ragged", 4, [5000, 9000, 4097, 8192]),
+                                  ("last_arrival", 4, [16500] * 10), ("slices_21", 8, [9000] * 3)],
+                         ids=lambda c: c[0])
+def test_output_merged_inside_is_normalised_in_fp64(rk, case, G):
+    """Full passes that merge their partial results in the streaming kernel, at scores around 4096: a log-sum-exp of that
+    size rounded to fp32 moves the weight of a whole partial result by up to 2.4e-4, an output of rows that cancel by
+    about 2e-5.  The scores are exact here (whole multiples of 2^-6 below 2^13), so the bound is what is left: 2^-17 of
+    P's two bf16 parts and 3e-7 of an exponential, on 4097 and more weights that add up to 1 and meet at random signs (below 1e-6), twice.
+    The bits are those of the pass that returns its weights, whose merge is a launch of its own.  (8 heads: 21 partial
+    results have no merge by slices, the last arrival takes them in two rounds.)"""
+    name, Hkv, lens = case
+    say("inside merge", name, G)
+    B, cap = len(lens), max(lens)
+    in_fp32 = B == 1 and G <= 4 and cap < 80000             # deferred: one residency round, merged like a partial step
+    g = torch.Generator(device="cuda").manual_seed(B + 10 * G)
+    q = torch.zeros(B, Hkv * G, 128, device="cuda")
+    q[..., 0], q[..., 1] = 64.0, 1.0
+    K = torch.zeros(B, Hkv, cap, 128, device="cuda")
+    K[..., 0], K[..., 1] = 64.0, torch.randint(-128, 129, (B, Hkv, cap), generator=g, device="cuda") / 64.0
+    sign = 1.0 - 2.0 * (torch.arange(cap, device="cuda") // 128 % 2)
+    V = sign[:, None].expand(B, Hkv, cap, 128).contiguous()
+    for b, n in enumerate(lens):                            # the last rows bring the output to nearly nothing
+        w = torch.softmax(K[b, :, :n, 1].double(), dim=-1)
+        for r in range(max(n - 4, 0), n):
+            V[b, :, r] = 0
+            V[b, :, r] = (-torch.matmul(w[:, None], V[b, :, :n].double())[:, 0] / w[:, r, None]).to(torch.bfloat16).float()
+    q, K, V = q.to(torch.bfloat16), K.to(torch.bfloat16), V.to(torch.bfloat16)
+    geom = rk.Geom(B, Hkv * G, Hkv, 128, 1.0)
+    ws = rk.Workspace(geom, cap, 16)
+    sl = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    outs = []
+    for kind in ("deferred", "plain", "weights"):
+        out, lse = torch.full_like(q, 7.0), torch.full((B, Hkv * G), 7.0, device="cuda")
+        if kind == "deferred":
+            rk.rk_full_attn_deferred(geom, q, K, V, sl, cap, out, lse=lse, workspace=ws)
+        else:
+            w = torch.zeros(B, Hkv * G, cap, device="cuda") if kind == "weights" else None
+            rk.rk_full_attn(geom, q, K, V, sl, cap, out, weights=w, lse=lse, workspace=ws)
+        outs.append((kind, out, lse))
+    torch.cuda.synchronize()
+    for b, n in enumerate(lens):
+        s = 4096.0 + K[b, :, :n, 1].double()
+        z = torch.logsumexp(s, dim=-1)
+        ref = torch.matmul(torch.exp(s - z[:, None])[:, None], V[b, :, :n].double())              # [Hkv, 1, 128]
+        for kind, out, lse in outs:
+            if kind == "plain" and not (B == 1 and cap > 8192):
+                continue                                    # few rows to a pair: the merge of the partial steps
+            if kind == "deferred" and in_fp32:
+                continue
+            assert (out[b].double().view(Hkv, G, 128) - ref).abs().max() < 2e-6, (name, kind, b)
+            assert (lse[b].double().view(Hkv, G) - z[:, None]).abs().max() <= 4.9e-4, (name, kind, b)      # fp32 at 4096: 2^-11
+    if B == 1 and cap > 8192 and cap < 80000:
+        assert torch.equal(outs[1][1], outs[2][1]), name
+    if not in_fp32 and name != "longer" and (name != "last_arrival" or G <= 4):      # (the others are split otherwise)
+        assert torch.equal(outs[0][1], outs[2][1]), name
+
+
 # budgets around whole workgroups of 128 rows (the new token's row alone in a tile, in a workgroup of its own, or neither),
 # beyond the 4096 rows the finishing kernel requests up front, few and many (sequence, KV head) pairs, empty, growing, full
 # and over-full caches
