@@ -22,6 +22,7 @@
 // keeps the same head in every block of 16 columns and the sum over the window is a per-lane
 // sum over blocks plus log2(16 / Gp) cross-lane steps.
 #include "rk_internal.h"
+#include <type_traits>
 #include "rk_device.h"
 
 namespace rk {
@@ -289,15 +290,21 @@ __device__ __forceinline__ void vote_rows(const WindowParams& p, const u32x4 (&k
     float v[T][4];
 #pragma unroll
     for (int e = 0; e < 4 * T; ++e) v[e >> 2][e & 3] = 0.f;
-#pragma unroll 1
-    for (int cb = 0; cb < p.ncb; ++cb) {
+    auto block = [&](auto masked, int cb) {
+        constexpr bool kMasked = decltype(masked)::value;
         float s[T][4];
-        block_scores<MASKED, T>(k, sQ, cb, n16, c4, r, MASKED ? column_limit(p, cb * 16 + n16, n) : 0, p.scale, s);
+        block_scores<kMasked, T>(k, sQ, cb, n16, c4, r, kMasked ? column_limit(p, cb * 16 + n16, n) : 0, p.scale, s);
         const float2 lse = sLse[cb * 16 + n16];
 #pragma unroll
         for (int e = 0; e < 4 * T; ++e)            // s = -inf (masked) and lse = inf (no such column) give 2^-inf = 0
             v[e >> 2][e & 3] += fast_exp2(((s[e >> 2][e & 3] - lse.x) - lse.y) * kLog2e);
-    }
+    };
+    // A last block that the queries do not fill has columns which are added to real ones below; their zero queries' scores
+    // are NaN where a key is infinite, so that block is masked also where every query sees every row.
+    const int full = MASKED ? p.ncb : (p.W << p.gp_shift) >> 4;
+#pragma unroll 1
+    for (int cb = 0; cb < full; ++cb) block(std::integral_constant<bool, MASKED>{}, cb);
+    if (!MASKED && full < p.ncb) block(std::true_type{}, full);
     // lanes n16, n16 + Gp, n16 + 2 Gp ... hold the same head for different queries
     const int gp = 1 << p.gp_shift;
 #pragma unroll

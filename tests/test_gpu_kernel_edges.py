@@ -67,6 +67,33 @@ def test_window_select_at_tile_edges(rk, case):
             assert_idx_equivalent(idx[b, g].cpu().numpy(), i_ref[b, g], P, n, k, "%s b=%d g=%d" % (name, b, g))
 
 
+@pytest.mark.parametrize("shape", [(4, 1, 2, 700), (1, 3, 2, 700), (4, 5, 8, 9000), (4, 13, 8, 9000), (2, 1, 8, 33000), (3, 7, 8, 33000)],
+                         ids=lambda s: "g%d_w%d_h%d_n%d" % s)
+def test_window_select_with_infinite_keys(rk, shape):
+    """A key with an infinite component and minus infinity as every query's score gets no vote, as one does whose scores are
+    finite and hopeless: the same votes, bit for bit, and the same selection (a window that does not fill its last block of
+    16 columns; few rows, few columns, and 64 rows per wavefront)."""
+    G, W, Hkv, n = shape
+    say("window with infinite keys", shape)
+    k, Hq = 64, G * Hkv
+    q, K = draw(n + W, 1, W, Hq, 128), draw(n + G, 1, Hkv, n, 128)
+    q[..., 5] = -1.0
+    rows = torch.tensor([0, 17, n // 2, n - W - 130])
+    geom = rk.Geom(1, Hq, Hkv, 128, SCALE)
+    got = []
+    for hopeless in (1e30, float("inf")):
+        K[:, :, rows, 5] = hopeless
+        ws = rk.Workspace(geom, n, k)
+        votes = torch.zeros(1, Hq, n, device="cuda")
+        idx = torch.full((1, Hkv, k), -5, dtype=torch.int32, device="cuda")
+        rk.rk_window_select(geom, q.cuda(), K.cuda(), torch.tensor([n], dtype=torch.int32, device="cuda"), n, k, 1, idx,
+                            votes=votes, workspace=ws)
+        torch.cuda.synchronize()
+        got.append((votes.cpu(), idx.cpu()))
+    assert (got[1][0][:, :, rows] == 0).all()
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
 # (group, pooling width, rows): the tiles of the pooling kernels end at multiples of 512, 1024 (from 98304 rows on) and,
 # batched over layers, 2048
 POOL_EDGES = [(4, 7, 512), (4, 7, 513), (1, 7, 1021), (7, 7, 1023), (8, 7, 1030), (4, 1, 700), (5, 15, 1537), (2, 63, 515),
