@@ -311,9 +311,9 @@ static inline int inside_split_workgroups(const rk_geom* g, int64_t max_len) {
 // rows shared out alike, one residency round at 4 tiles per wavefront.  The exact form takes 0.6 us longer in that one
 // launch (32 layers of 33k rows 1028 -> 1046 us per step).
 static inline bool merges_in_fp32(const rk_geom* g, int64_t max_len) {
-    const int64_t tiles = (max_len + 31) / 32 * g->batch * g->n_kv_heads;
-    return g->n_q_heads <= 4 * g->n_kv_heads && ragged_batch_of(g) == 0 && tiles < 40 * kComputeUnits &&
-           inside_split_workgroups(g, max_len) == emit_split_workgroups(g, max_len);
+    const int64_t problems = (int64_t)g->batch * g->n_kv_heads, n = inside_split_workgroups(g, max_len);
+    return g->n_q_heads <= 4 * g->n_kv_heads && ragged_batch_of(g) == 0 && (max_len + 31) / 32 * problems < 40 * kComputeUnits &&
+           n * problems <= 2 * kComputeUnits && n == emit_split_workgroups(g, max_len);
 }
 
 // ... and of a full step whose pooling is deferred: the pooling kernels must be told the same number.

@@ -40,6 +40,12 @@ int main() {
         rk_geom g{b, hkv * 4, hkv, 128, 1.0f};
         printf("emit %ld %d %d %d\n", l, b, hkv, emit_split_workgroups(&g, l));
     }
+    for (long l : {1L, 500L, 2000L, 6000L, 8000L, 8192L, 8193L, 16384L, 20000L, 33008L, 65536L, 100000L, 131072L, 1000000L}) for (int b : {1, 2, 3, 5, 6, 9, 16, 64, 65})
+        for (int hkv : {1, 2, 3, 4, 5, 6, 7, 8}) for (int G : {1, 4, 7}) {
+            rk_geom g{b, hkv * G, hkv, 128, 1.0f};
+            printf("inside %ld %d %d %d %d %d %d %d\n", l, b, hkv, G, inside_split_workgroups(&g, l), emit_split_workgroups(&g, l),
+                   deferred_split_workgroups(&g, l), (int)merges_in_fp32(&g, l));
+        }
     return 0;
 }
 """
@@ -138,3 +144,22 @@ def test_sliced_split_bounds_and_measured_choices(table):
     assert got[(8192, 10, 4)] == (64, 0)
     assert got[(16384, 10, 8)] == (64, 0)         # two tiles per wavefront either way
     assert got[(3072, 10, 8)] == (24, 1)
+
+
+@pytest.fixture(scope="module")
+def inside(table):
+    got = {tuple(map(int, v[:4])): tuple(map(int, v[4:])) for kind, *v in table if kind == "inside"}
+    assert len(got) == 14 * 9 * 8 * 3
+    return got
+
+
+def test_inside_split_bounds(inside):
+    """Full passes merged inside the kernel: within the slots of the merge and the stretches of 128 rows; the pooling
+    kernels of a deferred step are told the number that was launched."""
+    for (rows, b, hkv, G), (n, emit, deferred, fp32) in inside.items():
+        assert 0 <= n <= 64 and n <= max((rows + 127) // 128, 1)
+        assert deferred == (n if n > 0 else emit) and deferred >= 1
+        if fp32:
+            assert n == emit and G <= 4 and (b == 1 or b > 64) and n * b * hkv <= 512
+        if G > 4:
+            assert n <= 1 or n * b * hkv <= 512
