@@ -297,13 +297,15 @@ static inline int h2o_split_workgroups(const rk_geom* g, int64_t max_rows) {
 // step, us per layer at 768 or 1024 -> 512 workgroups: 6 ragged sequences of 10k rows, 4 KV heads of 7: 57.4 -> 47.7; 2 of
 // 24000 rows, 8 of 4: 64.7 -> 53.6; 16 ragged of 5.5k rows, 4 of 7: 89.7 -> 82.9; 16 ragged of 10k, 8 of 4, stays with
 // 1024: 186.0 against 188.4.
-// 0: compute units would be left without work (few, long rows; small batches), and the merge stays a launch of its own.
+// 0: compute units would be left without work (few pairs with long rows, small batches), and the merge stays a launch of
+// its own.  (That the pairs do not divide 256 is no reason: one sequence of 5 KV heads, 16384 rows, 255 workgroups 13.2 us,
+// with the merge launch 15.5; 3 sequences of 8 KV heads, 8000 rows, 240 workgroups 22.4 against 25.4.)
 static inline int inside_split_workgroups(const rk_geom* g, int64_t max_len) {
     const int64_t problems = (int64_t)g->batch * g->n_kv_heads;
     int target = emit_split_target(g, max_len);
     if (target > 2 * kComputeUnits && g->n_q_heads > 4 * g->n_kv_heads) target = 2 * kComputeUnits;
     const int n = split_workgroups(max_len, problems, kMergeChunks, target);
-    if ((g->batch > 1 || max_len > (int64_t)kMergeChunks * kMinChunk) && n * problems < kComputeUnits) return 0;
+    if ((g->batch > 1 || max_len > (int64_t)kMergeChunks * kMinChunk) && (n + 1) * problems <= kComputeUnits) return 0;
     return n;
 }
 // Deferred full steps whose merge inside weighs the partial results by their fp32 log-sum-exps, as a partial step does

@@ -163,3 +163,12 @@ def test_inside_split_bounds(inside):
             assert n == emit and G <= 4 and (b == 1 or b > 64) and n * b * hkv <= 512
         if G > 4:
             assert n <= 1 or n * b * hkv <= 512
+
+
+def test_inside_split_is_not_given_up_for_a_remainder(inside):
+    """A number of (sequence, KV head) pairs that does not divide 256 leaves a few workgroups fewer whichever launch merges."""
+    for key, n in {(16384, 1, 5, 4): 51, (20000, 1, 6, 4): 42, (6000, 6, 4, 4): 10, (8000, 3, 8, 1): 10}.items():
+        assert inside[key][0] == n == inside[key][1], key
+    for (rows, b, hkv, G), (n, emit, _, _) in inside.items():
+        if n == 0 and hkv > 1:
+            assert min(emit, 64) * b * hkv < 256 and (min(emit, 64) + 1) * b * hkv <= 256, (rows, b, hkv, G)
