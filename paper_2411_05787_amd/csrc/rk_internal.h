@@ -300,11 +300,22 @@ static inline int h2o_split_workgroups(const rk_geom* g, int64_t max_rows) {
 // 0: compute units would be left without work (few pairs with long rows, small batches), and the merge stays a launch of
 // its own.  (That the pairs do not divide 256 is no reason: one sequence of 5 KV heads, 16384 rows, 255 workgroups 13.2 us,
 // with the merge launch 15.5; 3 sequences of 8 KV heads, 8000 rows, 240 workgroups 22.4 against 25.4.)
+// Where the 64 slots bind, a total between 256 and 512 would leave some CUs a workgroup more than others, and one beyond 512
+// start a second residency round that is merged by the last arrival: 256 or 512 then, as near as the pairs come (us per
+// deferred step with the merge launch, with 64 partial results to a pair, as here: 3 sequences of 131072 rows, 4 KV heads of 4,
+// 768 -> 504 workgroups: 162.4, 166.9, 147.2; 3 KV heads, 576 -> 504: 123.5, 126.6, 112.2; 2 sequences of 65536 rows, 8 KV
+// heads, 1024 -> 512: 108.3, 109.1, 103.3; one sequence, 5 KV heads, 320 -> 255: 69.9, 71.6, 62.2; 7 KV heads, 448 ->
+// 252: 93.7, 90.8, 86.3).
 static inline int inside_split_workgroups(const rk_geom* g, int64_t max_len) {
     const int64_t problems = (int64_t)g->batch * g->n_kv_heads;
     int target = emit_split_target(g, max_len);
     if (target > 2 * kComputeUnits && g->n_q_heads > 4 * g->n_kv_heads) target = 2 * kComputeUnits;
-    const int n = split_workgroups(max_len, problems, kMergeChunks, target);
+    int n = split_workgroups(max_len, problems, kMergeChunks, target);
+    if (n == kMergeChunks) {
+        const int64_t total = n * problems, round = 2 * kComputeUnits;
+        if (total > round) n = (int)(round / problems);
+        else if (total > kComputeUnits && total < round) n = (int)(kComputeUnits / problems);
+    }
     if ((g->batch > 1 || max_len > (int64_t)kMergeChunks * kMinChunk) && (n + 1) * problems <= kComputeUnits) return 0;
     return n;
 }

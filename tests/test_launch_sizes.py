@@ -172,3 +172,16 @@ def test_inside_split_is_not_given_up_for_a_remainder(inside):
     for (rows, b, hkv, G), (n, emit, _, _) in inside.items():
         if n == 0 and hkv > 1:
             assert min(emit, 64) * b * hkv < 256 and (min(emit, 64) + 1) * b * hkv <= 256, (rows, b, hkv, G)
+
+
+def test_inside_split_leaves_no_part_of_a_round(inside):
+    """Where the slots of the merge bind, the total is as near below a multiple of the 256 compute units as the pairs allow."""
+    for key, n in {(131072, 3, 4, 4): 42, (131072, 3, 3, 4): 56, (131072, 1, 5, 4): 51, (131072, 1, 7, 4): 36, (131072, 1, 6, 7): 42,
+                   (131072, 1, 4, 7): 64, (131072, 1, 8, 4): 64, (65536, 2, 8, 4): 32, (131072, 16, 1, 4): 32}.items():
+        assert inside[key][0] == n, key
+    for (rows, b, hkv, G), (n, emit, _, _) in inside.items():
+        total = n * b * hkv
+        if total > 256 and n == 64:
+            assert total == 512, (rows, b, hkv, G)
+        if 0 < n < 64 and n < emit and G <= 4 and rows > 8192:       # trimmed: one workgroup more per pair would be the remainder
+            assert total <= 512 and (total + b * hkv > 512 or 256 - b * hkv < total <= 256), (rows, b, hkv, G)
