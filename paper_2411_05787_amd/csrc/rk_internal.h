@@ -306,8 +306,14 @@ static inline int h2o_split_workgroups(const rk_geom* g, int64_t max_rows) {
 // 768 -> 504 workgroups: 162.4, 166.9, 147.2; 3 KV heads, 576 -> 504: 123.5, 126.6, 112.2; 2 sequences of 65536 rows, 8 KV
 // heads, 1024 -> 512: 108.3, 109.1, 103.3; one sequence, 5 KV heads, 320 -> 255: 69.9, 71.6, 62.2; 7 KV heads, 448 ->
 // 252: 93.7, 90.8, 86.3).
+// A ragged batch with one or two KV heads: one sequence much longer than the others would have to make do with 64 or 128
+// workgroups in all, while the launch it replaces gives it 256 of the CUs (us per deferred step with the merge launch before
+// these forms, merged inside, with it now: one of 131072 rows and 3 of 64, one KV head: 24.2, 29.0, 21.7; and 15 of 64, two KV
+// heads: 36.7, 37.9, 32.6; sequences alike, 16 of 65536, one KV head: 111.5, 105.4, 102.7; three KV heads, 131072 and 15 of
+// 64, stay inside: 53.9, 44.2, 47.6).
 static inline int inside_split_workgroups(const rk_geom* g, int64_t max_len) {
     const int64_t problems = (int64_t)g->batch * g->n_kv_heads;
+    if (ragged_batch_of(g) != 0 && max_len > (int64_t)kMergeChunks * kMinChunk && kMergeChunks * g->n_kv_heads <= kComputeUnits / 2) return 0;
     int target = emit_split_target(g, max_len);
     if (target > 2 * kComputeUnits && g->n_q_heads > 4 * g->n_kv_heads) target = 2 * kComputeUnits;
     int n = split_workgroups(max_len, problems, kMergeChunks, target);

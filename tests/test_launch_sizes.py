@@ -170,14 +170,14 @@ def test_inside_split_is_not_given_up_for_a_remainder(inside):
     for key, n in {(16384, 1, 5, 4): 51, (20000, 1, 6, 4): 42, (6000, 6, 4, 4): 10, (8000, 3, 8, 1): 10}.items():
         assert inside[key][0] == n == inside[key][1], key
     for (rows, b, hkv, G), (n, emit, _, _) in inside.items():
-        if n == 0 and hkv > 1:
+        if n == 0 and (hkv > 2 or b == 1 or b > 64 or rows <= 8192):
             assert min(emit, 64) * b * hkv < 256 and (min(emit, 64) + 1) * b * hkv <= 256, (rows, b, hkv, G)
 
 
 def test_inside_split_leaves_no_part_of_a_round(inside):
     """Where the slots of the merge bind, the total is as near below a multiple of the 256 compute units as the pairs allow."""
     for key, n in {(131072, 3, 4, 4): 42, (131072, 3, 3, 4): 56, (131072, 1, 5, 4): 51, (131072, 1, 7, 4): 36, (131072, 1, 6, 7): 42,
-                   (131072, 1, 4, 7): 64, (131072, 1, 8, 4): 64, (65536, 2, 8, 4): 32, (131072, 16, 1, 4): 32}.items():
+                   (131072, 1, 4, 7): 64, (131072, 1, 8, 4): 64, (65536, 2, 8, 4): 32, (131072, 65, 1, 4): 15}.items():
         assert inside[key][0] == n, key
     for (rows, b, hkv, G), (n, emit, _, _) in inside.items():
         total = n * b * hkv
@@ -185,3 +185,13 @@ def test_inside_split_leaves_no_part_of_a_round(inside):
             assert total == 512, (rows, b, hkv, G)
         if 0 < n < 64 and n < emit and G <= 4 and rows > 8192:       # trimmed: one workgroup more per pair would be the remainder
             assert total <= 512 and (total + b * hkv > 512 or 256 - b * hkv < total <= 256), (rows, b, hkv, G)
+
+
+def test_one_long_sequence_of_a_ragged_batch_can_fill_the_chip(inside):
+    """With one or two KV heads the 64 slots of the merge inside would hold a long sequence to 64 or 128 workgroups: the
+    launch with up to 256 partial results to a sequence and KV head, and the merge launch, instead."""
+    for (rows, b, hkv, G), (n, emit, deferred, _) in inside.items():
+        if 1 < b <= 64 and hkv <= 2 and rows > 8192:
+            assert n == 0 and deferred == emit, (rows, b, hkv, G)
+        if 1 < b <= 64 and hkv > 2 and rows * b >= 65536:
+            assert n > 0, (rows, b, hkv, G)
