@@ -196,10 +196,8 @@ int rk_full_attn_select(const rk_geom* geom, const void* q, rk_kv full,
  *                       scores and their histogram, which stay in `workspace`;
  *   rk_select_pooled    the top-K from what rk_full_attn_pool left in the SAME workspace, with the
  *                       same seq_lens, max_len, predicate and geometry.
- * beside_other_work != 0: the attention kernel is launched in more, smaller workgroups (two
- * residency waves): 5-10% slower when it has the GPU to itself, but kernels of another stream (the
- * selections and gathers of earlier layers) can start while it runs; 0: the launch shape of
- * rk_full_attn_select.
+ * beside_other_work is a hint that kernels of another stream (the selections and gathers of earlier
+ * layers) run beside this one.  The launch shape of rk_full_attn_select serves both.
  * Between the two calls no other call may use that workspace (two workspaces used in turn let the
  * next layer's rk_full_attn_pool start before this layer's rk_select_pooled has run).  The pair
  * leaves the workspace as clean as rk_full_attn_select does. */

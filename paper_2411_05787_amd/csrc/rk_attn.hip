@@ -1945,7 +1945,7 @@ static int launch_score_split(const AttnParams& p, int batch, int G, int nchunk_
 int full_attn_stage(const rk_geom* geom, const void* q, rk_kv full, const int32_t* seq_lens, int32_t max_len,
                     void* out, float* weights, int64_t w_stride, float* lse, const int32_t* pred, int32_t pred_val,
                     const Workspace& ws, hipStream_t st, bool scores_only, int pool_half, bool no_v, int agg,
-                    bool co_run, bool defer_pool, int nch) {
+                    bool defer_pool, int nch) {
     const int G = geom->n_q_heads / geom->n_kv_heads;
     const bool fused = pool_half >= 0;
     const bool emit = weights != nullptr || fused;
@@ -1958,10 +1958,6 @@ int full_attn_stage(const rk_geom* geom, const void* q, rk_kv full, const int32_
     p.max_rows2 = max_len;
     p.cap1 = 0; p.cap2 = (int32_t)full.capacity;
     p.nch = nch > 0 ? nch : emit ? emit_split_workgroups(geom, max_len) : 0;       // (without scores: below)
-    if (co_run) {       // more, smaller workgroups, unless that means more partial results than the finish takes cheaply
-        const int wide = split_workgroups(max_len, (int64_t)geom->batch * geom->n_kv_heads, kMaxChunks, kCoRunTargetWgs);
-        if (wide <= kCoRunMaxChunks) p.nch = wide;
-    }
     p.Hq = geom->n_q_heads; p.Hkv = geom->n_kv_heads;
     p.scale = geom->scale;
     p.out = (uint16_t*)out;

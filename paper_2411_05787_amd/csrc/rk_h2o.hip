@@ -372,7 +372,7 @@ extern "C" int rk_h2o_step(const rk_geom* geom, rk_h2o_state state, const void* 
         if ((rc = append_stage(geom, state, k_new, v_new, seq_lens, s)) != RK_OK) return rc;
         const int64_t w_stride = pooled_row_stride(max_rows);
         rc = full_attn_stage(geom, q, state.cache, state.n_attend, max_rows, out, ws.scores, w_stride, nullptr,
-                             nullptr, 0, ws, s, false, -1, false, RK_AGG_MAX, false, false, nch);
+                             nullptr, 0, ws, s, false, -1, false, RK_AGG_MAX, false, nch);
         if (rc != RK_OK) return rc;
         return update_stage(geom, state, ws.scores, w_stride, max_rows, budget, recent, agg, dropped, s);
     }

@@ -14,31 +14,22 @@ constexpr int kMinChunk = 128;           // rows one workgroup takes per round: 
 constexpr int kMaxChunks = 256;          // most partial results one (sequence, KV head) produces
 constexpr int kMergeChunks = 64;         // ... when the split kernel itself merges them
 #ifndef RK_TARGET_WGS
-#define RK_TARGET_WGS 768                // workgroups a split launch aims for (3 per CU, all resident)
+#define RK_TARGET_WGS 768                // workgroups a split launch aims for where its caller says nothing else
 #endif
 
 // Workgroups per (sequence, KV head) of a split attention launch whose partial results a second
-// kernel merges.  Upper bound: as many as give the launch RK_TARGET_WGS workgroups in all (such a
-// launch is resident as a whole from the start), never more than `limit` (the most partial
-// results the merge takes), never more than there are stretches of kMinChunk rows.
+// kernel merges.  Upper bound: as many as give the launch `target` workgroups in all, never more than
+// `limit` (the most partial results the merge takes), never more than there are stretches of kMinChunk rows.
 // Below that bound, a count that gives every CU the same number of workgroups is preferred
 // (total a multiple of the 256 CUs) as long as no wavefront gets more tiles for it.  Measured on
-// the score-emitting kernel alone, 8 KV heads, total workgroups -> us per launch:
+// the score-emitting kernel alone, compiled for three workgroups per CU then (K straight into the operand layout), 8 KV
+// heads, total workgroups -> us per launch:
 //   24576 rows: 512 -> 20.5, 768 -> 21.5, 1024 -> 22.4;   560..720 -> 22.5..25.9
 //   32768 rows: 512 -> 27.1, 768 -> 27.5, 1024 -> 26.6;   560..720 -> 28.9..31.6
 //   65536 rows: 512 -> 51.5, 768 -> 52.5, 1024 -> 49.7;   560..720 -> 54.5..60.1
 // and the same picture with 4 KV heads and with a batch of 4: an even spread is worth 10-20%,
-// which of the even spreads is worth 3-5% and depends on the length; 3 per CU (one residency
-// wave) is never more than 5% from the best.
-// `target` above RK_TARGET_WGS (rk_full_attn_pool: 4 per CU): the launch then runs in two
-// residency waves, which costs it 5% when it has the chip to itself (26.7 -> 29.7 us at 32k rows)
-// but lets the kernels of a second stream, which do not fit beside three of these workgroups on a
-// CU, start while it runs: full step of 32 layers with the refresh on a second stream 46.7 -> 45.3 us
-// per layer.
+// which of the even spreads is worth 3-5% and depends on the length (emit_split_target decides there).
 constexpr int kComputeUnits = 256;
-constexpr int kCoRunTargetWgs = 1024;
-constexpr int kCoRunMaxChunks = 128;     // with 4 KV heads 1024 workgroups are 256 partial results per head: the finish
-                                         // then costs more than the co-running gains (46.2 -> 51.5 us per layer)
 static inline int split_workgroups(int64_t max_rows, int64_t n_problems, int limit, int target = RK_TARGET_WGS) {
     if (n_problems < 1) n_problems = 1;
     int64_t per = target / n_problems;
@@ -404,8 +395,7 @@ static inline int launch_status() {
 //   full_attn_stage: the split kernel, then either the merge inside it (no weights), the merge +
 //     normalise kernel (weights in place), or, with pool_half >= 0, the fused finish that also
 //     leaves the pooled group scores and their histogram in the workspace.  no_v: the split kernel
-//     is the scores-only one (K rows only; out must be NULL, pool_half >= 0).  co_run: the launch is
-//     shaped for running beside another stream's kernels (see split_workgroups).  defer_pool (with
+//     is the scores-only one (K rows only; out must be NULL, pool_half >= 0).  defer_pool (with
 //     pool_half >= 0 and out != NULL): only the output is finished; the raw scores and the chunk
 //     statistics stay in the workspace for pool_batched_stage, which does for several layers at
 //     once what the finishing kernel's pooling tiles do for one.  nch: workgroups per (sequence, KV head), where the
@@ -415,7 +405,7 @@ __attribute__((visibility("hidden")))
 int full_attn_stage(const rk_geom* geom, const void* q, rk_kv full, const int32_t* seq_lens, int32_t max_len,
                     void* out, float* weights, int64_t w_stride, float* lse, const int32_t* pred, int32_t pred_val,
                     const Workspace& ws, hipStream_t st, bool scores_only, int pool_half, bool no_v, int agg,
-                    bool co_run = false, bool defer_pool = false, int nch = 0);
+                    bool defer_pool = false, int nch = 0);
 __attribute__((visibility("hidden")))
 int pool_batched_stage(const rk_geom* geom, int n_layers, const Workspace* wss, const int32_t* seq_lens, int32_t max_len,
                        int64_t full_capacity, int pool_half, int agg, const int32_t* const* pred, int32_t pred_val,

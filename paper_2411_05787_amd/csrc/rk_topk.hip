@@ -892,7 +892,7 @@ extern "C" int rk_score_select(const rk_geom* geom, const void* q, rk_kv full,
 extern "C" int rk_full_attn_pool(const rk_geom* geom, const void* q, rk_kv full,
                                  const int32_t* seq_lens, int32_t max_len,
                                  void* out, float* weights, int64_t w_stride, float* lse,
-                                 int32_t pool_w, int32_t agg, int32_t beside_other_work,
+                                 int32_t pool_w, int32_t agg, int32_t /*beside_other_work*/,
                                  const int32_t* pred, int32_t pred_val,
                                  void* workspace, size_t workspace_bytes, void* stream) {
     int rc = check_geom(geom);
@@ -905,7 +905,7 @@ extern "C" int rk_full_attn_pool(const rk_geom* geom, const void* q, rk_kv full,
     Workspace ws;
     if ((rc = check_workspace(geom, max_len, 0, workspace, workspace_bytes, &ws)) != RK_OK) return rc;
     return full_attn_stage(geom, q, full, seq_lens, max_len, out, weights, w_stride, lse, pred, pred_val, ws,
-                           (hipStream_t)stream, false, (pool_w - 1) / 2, false, agg, beside_other_work != 0);
+                           (hipStream_t)stream, false, (pool_w - 1) / 2, false, agg);
 }
 
 extern "C" int rk_full_attn_deferred(const rk_geom* geom, const void* q, rk_kv full,
@@ -920,7 +920,7 @@ extern "C" int rk_full_attn_deferred(const rk_geom* geom, const void* q, rk_kv f
     Workspace ws;
     if ((rc = check_workspace(geom, max_len, 0, workspace, workspace_bytes, &ws)) != RK_OK) return rc;
     return full_attn_stage(geom, q, full, seq_lens, max_len, out, nullptr, 0, lse, pred, pred_val, ws,
-                           (hipStream_t)stream, false, 0, false, RK_AGG_MAX, false, true);
+                           (hipStream_t)stream, false, 0, false, RK_AGG_MAX, true);
 }
 
 extern "C" int rk_select_pooled(const rk_geom* geom, const int32_t* seq_lens, int32_t max_len, int32_t k,
