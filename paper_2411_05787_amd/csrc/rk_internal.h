@@ -332,6 +332,22 @@ static inline int deferred_split_workgroups(const rk_geom* g, int64_t max_len) {
     return inside > 0 ? inside : emit_split_workgroups(g, max_len);
 }
 
+// Form and split of the two passes of rk_window_select over K (see rk_window.hip): 16 T rows per wavefront and step,
+// wg_rows per workgroup and step, nch workgroups per (sequence, KV head), at most `limit`.
+constexpr int kWinTargetWgs = 512;     // workgroups of eight wavefronts a pass aims for: two per CU
+struct WindowForm { int T, wg_rows, nch; };
+static inline WindowForm window_form(int64_t max_rows, int64_t problems, int column_blocks, int limit) {
+    WindowForm f{4, 512, 1};
+    if (max_rows * problems <= (int64_t)kWinTargetWgs * 128) f = {1, 128, 1};
+    else if (column_blocks <= 2) return {2, 128, split_workgroups(max_rows, problems, limit)};
+    int64_t per = kWinTargetWgs / problems;
+    const int64_t stretches = (max_rows + f.wg_rows - 1) / f.wg_rows;
+    if (per > stretches) per = stretches;
+    if (per > limit) per = limit;
+    f.nch = per < 1 ? 1 : (int)per;
+    return f;
+}
+
 static inline Workspace carve(const rk_geom* g, int64_t max_len, int64_t max_k, void* base) {
     Workspace w;
     const size_t problems = (size_t)g->batch * g->n_kv_heads;

@@ -43,7 +43,6 @@ struct WindowParams {
     const int32_t* pred; int32_t pred_val;
 };
 
-constexpr int kWinTargetWgs = 512;     // workgroups of eight wavefronts a pass aims for: two per CU
 constexpr int kQStride = kD + 8;       // bf16 elements between columns in LDS: 272 bytes, conflict-free 16-byte reads
 
 __device__ __forceinline__ int window_workgroups(const WindowParams& p, int n_rows) {
@@ -394,15 +393,6 @@ static int launch_window(const WindowParams& p, int batch, hipStream_t st) {
     return launch_status();
 }
 
-// Workgroups per (sequence, KV head) of the forms with eight wavefronts.
-static int window_split(int64_t max_rows, int64_t problems, int limit, int wg_rows) {
-    int64_t per = kWinTargetWgs / problems;
-    const int64_t stretches = (max_rows + wg_rows - 1) / wg_rows;
-    if (per > stretches) per = stretches;
-    if (per > limit) per = limit;
-    return per < 1 ? 1 : (int)per;
-}
-
 }  // namespace rk
 
 using namespace rk;
@@ -440,10 +430,8 @@ extern "C" int rk_window_select(const rk_geom* geom, const void* q_win, int32_t 
     p.k = (const uint16_t*)full.k; p.s_b = full.stride_b; p.s_h = full.stride_h; p.cap = (int32_t)full.capacity;
     p.seq_lens = seq_lens; p.max_rows = max_len;
     p.W = window; p.G = G; p.gp_shift = gp_shift;
-    const int64_t problems = (int64_t)geom->batch * geom->n_kv_heads;
-    const bool few_rows = max_len * problems <= (int64_t)kWinTargetWgs * 128, narrow = ncb <= 2;
-    p.wg_rows = few_rows || narrow ? 128 : 512;
-    p.nch = narrow && !few_rows ? split_workgroups(max_len, problems, ws.max_chunks) : window_split(max_len, problems, ws.max_chunks, p.wg_rows);
+    const WindowForm form = window_form(max_len, (int64_t)geom->batch * geom->n_kv_heads, ncb, ws.max_chunks);
+    p.wg_rows = form.wg_rows; p.nch = form.nch;
     p.Hq = geom->n_q_heads; p.Hkv = geom->n_kv_heads;
     p.scale = geom->scale;
     p.part = ws.part_o; p.lse = ws.part_ml;
@@ -452,8 +440,8 @@ extern "C" int rk_window_select(const rk_geom* geom, const void* q_win, int32_t 
     p.v_vec = ((p.v_stride % 4 == 0) && aligned16(p.votes)) ? 1 : 0;
     p.pred = pred; p.pred_val = pred_val;
     p.ncb = ncb;
-    rc = few_rows ? launch_window<1, 1, 8>(p, geom->batch, st)
-       : narrow   ? launch_window<2, 2, 4>(p, geom->batch, st) : launch_window<4, 1, 8>(p, geom->batch, st);
+    rc = form.T == 1 ? launch_window<1, 1, 8>(p, geom->batch, st)
+       : form.T == 2 ? launch_window<2, 2, 4>(p, geom->batch, st) : launch_window<4, 1, 8>(p, geom->batch, st);
     if (rc != RK_OK) return rc;
     if ((rc = pool_stage(geom, p.votes, p.v_stride, seq_lens, max_len, pool_w, agg, pred, pred_val, ws, st)) != RK_OK) return rc;
     return select_stage(geom, seq_lens, max_len, k, idx, sel_scores, pred, pred_val, ws, st);

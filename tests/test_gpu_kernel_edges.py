@@ -30,10 +30,16 @@ def draw(seed, *shape):
     return torch.randn(*shape, generator=torch.Generator().manual_seed(seed)).to(torch.bfloat16)
 
 
-# 64 rows per wavefront, 512 per workgroup and round; 128 pairs leave a pair 4 workgroups (2048 rows per
-# round), 520 pairs one; 16 blocks of columns, and a negative scale
+# Up to 65536 rows over all pairs 16 rows per wavefront, 128 per workgroup; beyond, two sets of 32 rows and 128 per workgroup
+# for up to 32 columns ("narrow", 520 and 260 pairs: one and two workgroups to a pair), 64 rows and 512 per workgroup for
+# more ("wide" and the last but one: one workgroup to a pair, and four).  Lengths around whole tiles and steps, in either of the
+# two sets, and, less the window, around the first row that not every query sees; groups with columns that do not exist (3, 5
+# and 7 heads), blocks of columns that the queries do not fill, 16 blocks, and a negative scale.
 WINDOW_EDGES = [("rows_63_64_65", 3, 8, 2, [63, 64, 65], 5, SCALE), ("rows_511_512_513", 3, 4, 4, [511, 512, 513], 32, SCALE),
-                ("rows_575_576_577_w1", 3, 8, 1, [575, 576, 577], 1, SCALE), ("three_rounds", 65, 8, 8, [1100, 1025] + [40] * 63, 3, SCALE),
+                ("rows_575_576_577_w1", 3, 8, 1, [575, 576, 577], 1, SCALE), ("narrow_1100r", 65, 8, 8, [1100, 1025] + [40] * 63, 3, SCALE),
+                ("narrow_g3_sets", 65, 12, 4, [130, 300, 1090] + [40] * 62, 3, SCALE),
+                ("wide_g3_w12", 65, 12, 4, [1036, 1035, 1037] + [40] * 62, 12, SCALE), ("wide_g7_w5", 65, 28, 4, [1023, 1024, 1025] + [40] * 62, 5, SCALE),
+                ("wide_g5_w9", 65, 20, 4, [511, 512, 513] + [65] * 62, 9, SCALE),
                 ("g8_w32_two_rounds", 128, 8, 1, [2100, 2049] + [33] * 126, 32, SCALE), ("negative_scale", 1, 8, 2, [700], 9, -SCALE)]
 
 
@@ -204,9 +210,9 @@ def test_ragged_batches_cover_every_row_once(rk, case, G):
             assert (d <= torch.maximum(out[b].double().abs(), ref.abs()) * 2.0 ** -7 + 4e-6).all(), (name, kind, b)
 
 
-@pytest.mark.parametrize("G", [1, 4, 5, 7, 8])
+@pytest.mark.parametrize("G", [1, 4, 5, 6, 7, 8])
 @pytest.mark.parametrize("case", [("slices_64", 4, [8192]), ("slices_64_long", 4, [33000]), ("longer", 4, [90000]), ("ragged", 4, [5000, 9000, 4097, 8192]),
-                                  ("last_arrival", 4, [16500] * 10), ("slices_21", 8, [9000] * 3)],
+                                  ("last_arrival", 4, [16500] * 10), ("slices_21", 8, [9000] * 3), ("one_long", 4, [30000] + [4100] * 7)],
                          ids=lambda c: c[0])
 def test_output_merged_inside_is_normalised_in_fp64(rk, case, G):
     """Full passes that merge their partial results in the streaming kernel, at scores around 4096: a log-sum-exp of that
@@ -258,7 +264,7 @@ def test_output_merged_inside_is_normalised_in_fp64(rk, case, G):
             assert (lse[b].double().view(Hkv, G) - z[:, None]).abs().max() <= 4.9e-4, (name, kind, b)      # fp32 at 4096: 2^-11
     if B == 1 and cap > 8192 and cap < 80000:
         assert torch.equal(outs[1][1], outs[2][1]), name
-    if not in_fp32 and name != "longer" and (name != "last_arrival" or G <= 4):      # (the others are split otherwise)
+    if not in_fp32 and name not in ("longer", "one_long") and (name != "last_arrival" or G <= 4):      # (the others are split otherwise)
         assert torch.equal(outs[0][1], outs[2][1]), name
 
 

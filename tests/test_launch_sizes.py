@@ -46,6 +46,16 @@ int main() {
             printf("inside %ld %d %d %d %d %d %d %d\n", l, b, hkv, G, inside_split_workgroups(&g, l), emit_split_workgroups(&g, l),
                    deferred_split_workgroups(&g, l), (int)merges_in_fp32(&g, l));
         }
+    for (long l : {1L, 63L, 512L, 513L, 1100L, 2100L, 32768L, 40000L, 131072L}) for (long p : {1L, 4L, 8L, 128L, 260L, 520L, 4096L})
+        for (int blocks : {1, 2, 3, 8, 16}) {
+            const int limit = max_chunks_for(l);
+            const WindowForm f = window_form(l, p, blocks, limit);
+            printf("window %ld %ld %d %d %d %d %d\n", l, p, blocks, limit, f.T, f.wg_rows, f.nch);
+        }
+    for (long l : {2L, 31L, 128L, 129L, 2049L, 4101L, 8193L, 16701L, 32769L}) for (int b : {1, 4, 16, 70}) for (int hkv : {1, 4, 8}) {
+        rk_geom g{b, hkv * 4, hkv, 128, 1.0f};
+        printf("h2o %ld %d %d %d %d %d\n", l, b, hkv, h2o_split_workgroups(&g, l), emit_split_workgroups(&g, l), max_chunks_for(l));
+    }
     return 0;
 }
 """
@@ -195,3 +205,34 @@ def test_one_long_sequence_of_a_ragged_batch_can_fill_the_chip(inside):
             assert n == 0 and deferred == emit, (rows, b, hkv, G)
         if 1 < b <= 64 and hkv > 2 and rows * b >= 65536:
             assert n > 0, (rows, b, hkv, G)
+
+
+def test_window_form_bounds_and_measured_choices(table):
+    got = {}
+    for kind, *v in table:
+        if kind != "window":
+            continue
+        rows, pairs, blocks, limit, T, wg_rows, nch = map(int, v)
+        got[(rows, pairs, blocks)] = (T, nch)
+        assert 1 <= nch <= limit and nch <= max((rows + wg_rows - 1) // wg_rows, 1)
+        assert (T, wg_rows) in ((1, 128), (2, 128), (4, 512))
+        if T != 2:
+            assert nch == 1 or nch * pairs <= 512
+    assert got[(32768, 8, 8)] == (4, 64)          # 32 queries of 4 heads: every wavefront of the chip 64 rows
+    assert got[(32768, 8, 1)][0] == 2             # one query
+    assert got[(2100, 8, 8)][0] == 1 and got[(40000, 1, 8)][0] == 1
+    assert got[(1100, 260, 3)] == (4, 1) and got[(1100, 260, 2)] == (2, 2) and got[(513, 128, 16)] == (4, 2)
+
+
+def test_h2o_split_bounds(table):
+    seen = 0
+    for kind, *v in table:
+        if kind != "h2o":
+            continue
+        rows, b, hkv, n, emit, slots = map(int, v)
+        assert 1 <= n <= slots                    # partial results the workspace of budget + 1 rows has room for
+        tiles = (rows + 31) // 32 * b * hkv
+        if not 10240 <= tiles < 14336:            # 768 workgroups are a choice here only
+            assert n == emit, (rows, b, hkv)
+        seen += 1
+    assert seen == 9 * 4 * 3
