@@ -145,9 +145,10 @@ int rk_full_attn(const rk_geom* geom, const void* q, rk_kv full,
  * turns the scores into weights; Section 2.2 "Decoding with full cache", Appendix A.1).
  * Exposed so that a benchmark can time the HBM-bound kernel alone, launch after launch.
  * scores: fp32 [batch, n_q_heads, s_stride], s_stride >= max_len; or NULL: the raw scores stay in the
- * workspace, arranged as the full steps of rk_full_attn_select, rk_full_attn_pool and
- * rk_full_attn_deferred keep them (for groups of 4 query heads: the 4 scores of a position side by
- * side), i.e. the launch is exactly the first kernel of those steps. */
+ * workspace, arranged as the full steps keep them (for groups of 4 query heads: the 4 scores of a
+ * position side by side), i.e. the launch is the first kernel of rk_full_attn_select and
+ * rk_full_attn_pool.  (rk_full_attn_deferred streams the same rows in a kernel that merges the
+ * output as well, in its own number of workgroups.) */
 int rk_full_attn_scores(const rk_geom* geom, const void* q, rk_kv full,
                         const int32_t* seq_lens, int32_t max_len,
                         float* scores, int64_t s_stride,
@@ -514,8 +515,9 @@ int rk_decode_step_overlapped(const rk_geom* geom, const rk_schedule* sched, int
 /* Full attention of a full step whose pooling is left for rk_refresh_batched (Section 2.2,
  * "Decoding with full cache"): `out` (and lse, if given) as rk_full_attn; the raw scores of the
  * step and the statistics that normalise them stay in `workspace`, which must not be used for
- * anything else until rk_refresh_batched has run with pool_w != 0.  Launches the same kernels as
- * the first half of rk_full_attn_pool, less the pooling tiles of its finishing kernel. */
+ * anything else until rk_refresh_batched has run with pool_w != 0.  One launch that streams the
+ * cache, emits the scores and merges the output; small batches, and batches with one or two KV heads
+ * and long rows, take a second one for the merge. */
 int rk_full_attn_deferred(const rk_geom* geom, const void* q, rk_kv full,
                           const int32_t* seq_lens, int32_t max_len, void* out, float* lse,
                           const int32_t* pred, int32_t pred_val,

@@ -282,8 +282,8 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));      // 16 bytes
 // far more than the caches hold has passed through (the full cache): a non-temporal load, which
 // leaves the L2 and the last-level cache to the data that does come back (the small caches, read
 // at every partial step).  Measured: the kernel that streams K and V of the full cache runs 4%
-// faster with it; the partial step 3% slower and the K-only passes 3-5% slower, so only the
-// former uses it.
+// faster with it, the scores-only pass too where its keys outgrow the last-level cache (kScoreStreamBytes; below
+// it is 3-5% slower); the partial step is 3% slower.
 template <bool STREAM>
 __device__ __forceinline__ u32x4 load_rows16(const uint16_t* p) {
     if (STREAM) return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
@@ -2145,8 +2145,8 @@ extern "C" int rk_full_attn_scores(const rk_geom* geom, const void* q, rk_kv ful
     if (rc != RK_OK) return rc;
     Workspace ws;
     if ((rc = check_workspace(geom, max_len, 0, workspace, workspace_bytes, &ws)) != RK_OK) return rc;
-    // scores == NULL: the kernel exactly as a full step of rk_full_attn_select / rk_full_attn_deferred
-    // launches it, the raw scores going to the workspace in the library's own arrangement
+    // scores == NULL: the kernel exactly as a full step of rk_full_attn_select / rk_full_attn_pool launches it,
+    // the raw scores going to the workspace in the library's own arrangement
     return full_attn_stage(geom, q, full, seq_lens, max_len, nullptr, scores, s_stride, nullptr, pred, pred_val,
                            ws, (hipStream_t)stream, true, scores ? -1 : 0, false, RK_AGG_MAX);
 }

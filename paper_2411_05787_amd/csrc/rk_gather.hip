@@ -42,11 +42,13 @@ struct GatherBatch {
     const int32_t* pred[kBatchLayers];
 };
 
-// STREAM: non-temporal loads and stores, for launches whose small caches the last-level cache could not keep until the
-// next step anyway (kStreamBytes; smaller ones are left to it: the partial steps that follow read them).
-// Bound by memory both ways.  268 MB read and 268 MB written, the full step around it: 32 layers of 2048 rows per KV head
-// 1044 -> 1030 us, 4 layers of 16 x 1024 713 -> 691 (105 us and more of it in this launch).  The per-layer kernel above is
-// slower with it (47.5 against 46.8 us per step of one layer).
+// STREAM: non-temporal loads and stores, for launches that fill most of the last-level cache (256 MB) with small caches or
+// outgrow it (kStreamBytes).  Bound by memory both ways.  The first partial step after it then reads from memory what plain
+// stores leave in that cache, so both steps count: full step alone, full step and the partial step after it, us, plain ->
+// non-temporal: 32 layers of 33k rows, 256 MB of small caches: 1070 -> 1044, 1279 -> 1273; 219 MB: 1265 -> 1257 with
+// the partial step; 200 MB: 1048 -> 1022, 1252 -> 1252; 144 MB: 1234 -> 1239 with it; 4 layers of 16 sequences, 256 MB: 669 ->
+// 656, 750 -> 740; 200 MB: 714 -> 707 with it.  The per-layer kernel above is slower with it (47.5 against 46.8 us
+// per step of one layer).
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 constexpr int64_t kStreamBytes = 192ll << 20;
 

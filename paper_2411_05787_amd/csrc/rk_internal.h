@@ -258,9 +258,11 @@ static inline int max_chunks_for(int64_t max_len) {
 // (384 workgroups, uneven over the CUs: 28.8 / 32.8 / 115.3.)  Few tiles per wavefront leave the
 // launch's fixed costs (start, the merge across the wavefronts, the partial results) a larger share
 // and make a ragged last round (2.67 tiles per wavefront with 768 workgroups at 32k rows) cost more;
-// long rows want more loads in flight.  768 workgroups are left out: the kernel is compiled for two per CU and would
-// run one and a half residency rounds (layer by layer, 768 -> 512: 2 sequences of 24000 rows 66.8 -> 63.3 us, one of 50000
-// 68.1 -> 66.3).
+// long rows want more loads in flight.  768 workgroups are left out: for groups of 4 heads (170 registers) the kernel is resident
+// twice per CU, and they would be one and a half rounds (one layer with its selection, 768 -> 512: 2 sequences of 24000
+// rows 58.7 -> 55.6 us, one of 50000 60.9 -> 56.7).  For the other groups (168 registers, three per CU) they would be
+// one round, and it makes no difference (one sequence, 768 / 512: 50000 rows of 8 KV heads, groups of 1, 2 and 8: 53.2 / 53.0,
+// 54.9 / 54.1, 63.0 / 63.0; 100000 rows of 4 KV heads, groups of 7: 62.3 / 62.3).
 static inline int emit_split_target(const rk_geom* g, int64_t max_len) {
     const int64_t tiles = (max_len + 31) / 32 * g->batch * g->n_kv_heads;
     int64_t target = (tiles / 16 + kComputeUnits / 2) / kComputeUnits * kComputeUnits;      // 16 tiles per workgroup: 4 per wavefront

@@ -116,13 +116,13 @@ def pmc(workload, layers, fetch_csv, write_csv, copy_bytes):
            "  rocprofv3 --pmc WRITE_SIZE -d gpurun_out/pmc_write_%s -o w --output-format csv -- %s" % (workload, base), "",
            "calibration: rk::calibration_copy_kernel copies %d bytes (reads them once, writes them once)." % copy_bytes,
            "  FETCH_SIZE reads %.1f KiB for it -> scale %.4f;  WRITE_SIZE reads %.1f KiB -> scale %.4f" % (cf, fs, cw, wsc), "",
-           "%-60s %6s %14s %14s %12s %12s" % ("kernel (median over its dispatches)", "n", "FETCH_SIZE KiB", "WRITE_SIZE KiB", "read MB", "written MB")]
+           "%-68s %6s %14s %14s %12s %12s" % ("kernel (median over its dispatches)", "n", "FETCH_SIZE KiB", "WRITE_SIZE KiB", "read MB", "written MB")]
     js = {"workload": workload, "layers": int(layers), "commit": commit_id(), "fetch_scale": fs, "write_scale": wsc, "copy_bytes": copy_bytes}
     for k in f:
         if "rk::" not in k:
             continue
         a, b = st.median(f[k]), st.median(w.get(k, [0.0]))
-        out.append("%-60s %6d %14.1f %14.1f %12.2f %12.2f" % (k[-60:], len(f[k]), a, b, a * 1024 * fs / 1e6, b * 1024 * wsc / 1e6))
+        out.append("%-68s %6d %14.1f %14.1f %12.2f %12.2f" % (k[-68:], len(f[k]), a, b, a * 1024 * fs / 1e6, b * 1024 * wsc / 1e6))
         if re.search(FULL_KERNEL, k):
             js["attn_split"] = {"kernel": k, "fetch_kib": a, "write_kib": b}
         if re.search(PARTIAL_KERNEL, k) and len(f[k]) > js.get("partial_attn", {}).get("dispatches", 0):
