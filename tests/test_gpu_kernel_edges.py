@@ -268,6 +268,42 @@ def test_output_merged_inside_is_normalised_in_fp64(rk, case, G):
         assert torch.equal(outs[0][1], outs[2][1]), name
 
 
+@pytest.mark.parametrize("case", [(7, 4, [33000]), (4, 8, [9000, 8000, 8999]), (2, 4, [2000] * 16), (4, 4, [33000]), (8, 8, [9000] * 3), (3, 4, [700] * 30)],
+                         ids=lambda c: "g%d_%d_pairs_n%d" % (c[0], c[1] * len(c[2]), c[2][0]))
+def test_full_passes_hand_over_slices_to_the_last_workgroup(rk, case):
+    """Full passes merged by slices with the bound on re-reads of rows in flight at 0 (every workgroup leaves its slice to
+    the one that publishes last), 1, 2 and its default: the same bits, out and lse, call after call on one workspace."""
+    G, Hkv, lens = case
+    say("hand-over", case)
+    B, cap = len(lens), max(lens)
+    g = torch.Generator(device="cuda").manual_seed(G + cap)
+    K, V = (torch.randn(B, Hkv, cap, 128, generator=g, device="cuda").to(torch.bfloat16) for _ in range(2))
+    q = torch.randn(B, Hkv * G, 128, generator=g, device="cuda").to(torch.bfloat16)
+    geom = rk.Geom(B, Hkv * G, Hkv, 128, SCALE)
+    ws = rk.Workspace(geom, cap, 16)
+    sl = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    got = {"deferred": [], "plain": []}
+    try:
+        for spin in (256, 0, 1, 2, 0, 256):
+            rk.rk_debug_set_slice_spin(spin)
+            for kind, runs in got.items():
+                out, lse = torch.full_like(q, 7.0), torch.full((B, Hkv * G), 7.0, device="cuda")
+                (rk.rk_full_attn_deferred if kind == "deferred" else rk.rk_full_attn)(geom, q, K, V, sl, cap, out, lse=lse, workspace=ws)
+                torch.cuda.synchronize()
+                runs.append((out.clone(), lse.clone()))
+    finally:
+        rk.rk_debug_set_slice_spin(256)
+    for kind, runs in got.items():
+        for out, lse in runs[1:]:
+            assert torch.equal(out, runs[0][0]) and torch.equal(lse, runs[0][1]), kind
+    for b, n in enumerate(lens[:3]):
+        s = SCALE * torch.matmul(q[b].double().view(Hkv, G, 128), K[b, :, :n].double().transpose(1, 2).contiguous())
+        ref = torch.matmul(torch.softmax(s, dim=-1), V[b, :, :n].double()).reshape(-1, 128)
+        for kind, runs in got.items():
+            d = (runs[0][0][b].double() - ref).abs()                   # one bf16 step of the larger value, and 4e-6 (see helpers)
+            assert (d <= torch.maximum(runs[0][0][b].double().abs(), ref.abs()) * 2.0 ** -7 + 4e-6).all(), (kind, b)
+
+
 # budgets around whole workgroups of 128 rows (the new token's row alone in a tile, in a workgroup of its own, or neither),
 # beyond the 4096 rows the finishing kernel requests up front, few and many (sequence, KV head) pairs, empty, growing, full
 # and over-full caches
