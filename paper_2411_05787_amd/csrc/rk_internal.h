@@ -336,18 +336,28 @@ static inline int deferred_split_workgroups(const rk_geom* g, int64_t max_len) {
 
 // Form and split of the two passes of rk_window_select over K (see rk_window.hip): 16 T rows per wavefront and step,
 // wg_rows per workgroup and step, nch workgroups per (sequence, KV head), at most `limit`.
+// T = 4 takes 512 rows per workgroup and round and gains from every block of columns it holds the rows for, but a last round
+// with little in it costs as much as a full one; T = 2, 128 rows at a time, does not care.  Up to 2 blocks T = 2, from 9 on T
+// = 4; between, T = 4 where the rows fill 17/20 of its rounds (of the chip's up to 4 blocks: there fewer, longer workgroups gain
+// nothing either).  Whole call, us, 32 heads over 8, both passes with 32 rows and masks everywhere / T = 4 / T = 2: 16 queries (4
+// blocks): 24000 rows 57.3 / 55.7 / 52.3, 36000 70.2 / 77.9 / 65.4, 64000 95.3 / 87.4 / 90.1, 66000 96.4 / 98.5 / 91.5; 24 queries (6):
+// 16000 53.3 / 47.0 / 49.2, 36000 76.1 / 80.6 / 68.7, 80000 117.9 / 111.4 / 108.5; 32 queries (8): 32768 89.3 / 67.5 / 71.7, 36000
+// 90.6 / 85.8 / 74.5, 57000 127.6 / 101.2 / 103.2, 100000 168.1 / 144.7 / 137.2; 28 heads over 4, 8 queries (4): 76000 72.3 / 80.1 / 68.1;
+// 64 over 8, 20 queries (10): 36000 105.1 / 103.6 / 91.9, 58000 137.7 / 112.4 / 119.6, 32 queries (16): 36000 166.9 / 131.8 / 145.4.
 constexpr int kWinTargetWgs = 512;     // workgroups of eight wavefronts a pass aims for: two per CU
 struct WindowForm { int T, wg_rows, nch; };
 static inline WindowForm window_form(int64_t max_rows, int64_t problems, int column_blocks, int limit) {
-    WindowForm f{4, 512, 1};
-    if (max_rows * problems <= (int64_t)kWinTargetWgs * 128) f = {1, 128, 1};
-    else if (column_blocks <= 2) return {2, 128, split_workgroups(max_rows, problems, limit)};
+    const bool few = max_rows * problems <= (int64_t)kWinTargetWgs * 128;
+    WindowForm f = few ? WindowForm{1, 128, 1} : WindowForm{4, 512, 1};
     int64_t per = kWinTargetWgs / problems;
+    if (per < 1) per = 1;
     const int64_t stretches = (max_rows + f.wg_rows - 1) / f.wg_rows;
-    if (per > stretches) per = stretches;
-    if (per > limit) per = limit;
-    f.nch = per < 1 ? 1 : (int)per;
-    return f;
+    f.nch = (int)(per < stretches ? per : stretches);
+    if (f.nch > limit) f.nch = limit;
+    if (few || column_blocks > 8) return f;
+    const int64_t round = (column_blocks <= 4 ? per : f.nch) * f.wg_rows, rounds = (max_rows + round - 1) / round;
+    if (column_blocks > 2 && 20 * max_rows >= 17 * rounds * round) return f;
+    return {2, 128, split_workgroups(max_rows, problems, limit)};
 }
 
 static inline Workspace carve(const rk_geom* g, int64_t max_len, int64_t max_k, void* base) {

@@ -137,8 +137,8 @@ extern __shared__ __attribute__((aligned(16))) unsigned char window_lds[];
 //   T = 4, S = 1  rows enough to give every wavefront of the chip 64; us at 32 heads over 8, 32768 rows, 32 queries, with K
 //                 in the last-level cache: 41.7 + 26.7 (32 rows, 4 wavefronts per workgroup, 3 per CU) -> 25.1 + 20.8 (K from
 //                 memory: 28.3 + 26.6); the queries requested behind the rows instead of before them: 27.3 + 23.9
-//   T = 2, S = 2  up to 32 columns, where a step is short and bound by memory: two sets of 32 rows, each requested
-//                 again as soon as it is used, 4 wavefronts per workgroup (finer: the last round of a row is not full;
+//   T = 2, S = 2  up to 32 columns, where a step is short and bound by memory, and up to 128 where the rows would leave the
+//                 last round of T = 4 half empty: two sets of 32 rows, each requested again as soon as it is used, 4 wavefronts per workgroup (finer: the last round of a row is not full;
 //                 8 wavefronts and 4 sets of 16 rows were 2-3% slower at 33000 to 60000 rows); 0-4% over the form with
 //                 masks everywhere, most for K in the last-level cache
 //   T = 1, S = 1  few rows: more, shorter wavefronts (3000 rows, 32 queries, the whole case: 45.6 with T = 4, 34.9)

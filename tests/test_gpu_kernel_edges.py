@@ -31,15 +31,17 @@ def draw(seed, *shape):
 
 
 # Up to 65536 rows over all pairs 16 rows per wavefront, 128 per workgroup; beyond, two sets of 32 rows and 128 per workgroup
-# for up to 32 columns ("narrow", 520 and 260 pairs: one and two workgroups to a pair), 64 rows and 512 per workgroup for
-# more ("wide" and the last but one: one workgroup to a pair, and four).  Lengths around whole tiles and steps, in either of the
+# for up to 32 columns ("narrow", 520 and 260 pairs: one and two workgroups to a pair) and where rounds of 512 rows per
+# workgroup would be left half empty ("half_empty"), 64 rows and 512 per workgroup for the rest ("wide" and the last but one: one
+# workgroup to a pair, and four).  Lengths around whole tiles and steps, in either of the
 # two sets, and, less the window, around the first row that not every query sees; groups with columns that do not exist (3, 5
 # and 7 heads), blocks of columns that the queries do not fill, 16 blocks, and a negative scale.
 WINDOW_EDGES = [("rows_63_64_65", 3, 8, 2, [63, 64, 65], 5, SCALE), ("rows_511_512_513", 3, 4, 4, [511, 512, 513], 32, SCALE),
                 ("rows_575_576_577_w1", 3, 8, 1, [575, 576, 577], 1, SCALE), ("narrow_1100r", 65, 8, 8, [1100, 1025] + [40] * 63, 3, SCALE),
                 ("narrow_g3_sets", 65, 12, 4, [130, 300, 1090] + [40] * 62, 3, SCALE),
-                ("wide_g3_w12", 65, 12, 4, [1036, 1035, 1037] + [40] * 62, 12, SCALE), ("wide_g7_w5", 65, 28, 4, [1023, 1024, 1025] + [40] * 62, 5, SCALE),
-                ("wide_g5_w9", 65, 20, 4, [511, 512, 513] + [65] * 62, 9, SCALE),
+                ("wide_g3_w12", 65, 12, 4, [1036, 1035, 1400] + [40] * 62, 12, SCALE), ("wide_g7_w5", 65, 28, 4, [1025, 1024, 1400] + [40] * 62, 5, SCALE),
+                ("wide_g5_w9", 65, 20, 4, [513, 512, 1000] + [65] * 62, 9, SCALE), ("half_empty_g7", 65, 28, 4, [1025, 1055, 1093] + [40] * 62, 5, SCALE),
+                ("half_empty_g5", 65, 20, 4, [511, 600, 512] + [65] * 62, 14, SCALE),
                 ("g8_w32_two_rounds", 128, 8, 1, [2100, 2049] + [33] * 126, 32, SCALE), ("negative_scale", 1, 8, 2, [700], 9, -SCALE)]
 
 
@@ -73,7 +75,7 @@ def test_window_select_at_tile_edges(rk, case):
             assert_idx_equivalent(idx[b, g].cpu().numpy(), i_ref[b, g], P, n, k, "%s b=%d g=%d" % (name, b, g))
 
 
-@pytest.mark.parametrize("shape", [(4, 1, 2, 700), (1, 3, 2, 700), (4, 5, 8, 9000), (4, 13, 8, 9000), (2, 1, 8, 33000), (3, 7, 8, 33000)],
+@pytest.mark.parametrize("shape", [(4, 1, 2, 700), (1, 3, 2, 700), (4, 5, 8, 9000), (4, 13, 8, 9000), (4, 13, 8, 32000), (2, 1, 8, 33000), (3, 7, 8, 33000)],
                          ids=lambda s: "g%d_w%d_h%d_n%d" % s)
 def test_window_select_with_infinite_keys(rk, shape):
     """A key with an infinite component and minus infinity as every query's score gets no vote, as one does whose scores are

@@ -46,7 +46,7 @@ int main() {
             printf("inside %ld %d %d %d %d %d %d %d\n", l, b, hkv, G, inside_split_workgroups(&g, l), emit_split_workgroups(&g, l),
                    deferred_split_workgroups(&g, l), (int)merges_in_fp32(&g, l));
         }
-    for (long l : {1L, 63L, 512L, 513L, 1100L, 2100L, 32768L, 40000L, 131072L}) for (long p : {1L, 4L, 8L, 128L, 260L, 520L, 4096L})
+    for (long l : {1L, 63L, 512L, 513L, 1100L, 1400L, 2100L, 16000L, 32768L, 36000L, 40000L, 64000L, 76000L, 131072L}) for (long p : {1L, 4L, 8L, 128L, 260L, 520L, 4096L})
         for (int blocks : {1, 2, 3, 8, 16}) {
             const int limit = max_chunks_for(l);
             const WindowForm f = window_form(l, p, blocks, limit);
@@ -221,7 +221,12 @@ def test_window_form_bounds_and_measured_choices(table):
     assert got[(32768, 8, 8)] == (4, 64)          # 32 queries of 4 heads: every wavefront of the chip 64 rows
     assert got[(32768, 8, 1)][0] == 2             # one query
     assert got[(2100, 8, 8)][0] == 1 and got[(40000, 1, 8)][0] == 1
-    assert got[(1100, 260, 3)] == (4, 1) and got[(1100, 260, 2)] == (2, 2) and got[(513, 128, 16)] == (4, 2)
+    assert got[(1100, 260, 2)] == (2, 2) and got[(513, 128, 16)] == (4, 2)
+    # a last round of T = 4 with little in it (with 4 KV heads it takes 65536 rows to a round, with 8 32768)
+    assert got[(1400, 260, 3)] == (4, 1) and got[(1100, 260, 3)][0] == 2
+    assert got[(36000, 8, 3)][0] == 2 and got[(36000, 8, 8)][0] == 2 and got[(36000, 8, 16)][0] == 4
+    assert got[(76000, 4, 3)][0] == 2 and got[(64000, 8, 3)][0] == 4 and got[(64000, 8, 8)][0] == 4
+    assert got[(16000, 8, 3)][0] == 2 and got[(16000, 8, 8)][0] == 4          # half a round: fewer workgroups, none of them idle
 
 
 def test_h2o_split_bounds(table):
