@@ -1738,8 +1738,11 @@ void finish_pool_body(const AttnParams& p, const float* __restrict__ scores, int
         const bool in = i < span && j >= 0 && j < len;
         float a = -INFINITY;                         // outside [0, len): never wins a max
         if (only_max) {
-            const float w = max_weight<G>(one, sLse, tol);
-            if (in) a = w;
+            // (a tile of the batched launch may lie mostly beyond the end of a short row)
+            if (G <= 2 ? in : TILE <= kPoolTileLong || __any(in)) {
+                const float w = max_weight<G>(one, sLse, tol);
+                if (in) a = w;
+            }
         } else if (in) {
             const bool core = p.weights != nullptr && i >= half && i < half + TILE;
 #pragma unroll

@@ -323,6 +323,13 @@ __device__ __forceinline__ float weight_of(float s, float nl, float ll) {
 // rows 19.5 -> 13.5.
 template <int G>
 __device__ __forceinline__ float max_weight(const float (&s)[G], const float (*lse)[2], float tol) {
+    // (one or two heads: the choice between them and the branch cost more than the second exponential; two test steps of 3
+    // layers of 2667 rows, 8 KV heads of 2: 112.1 us with them, 111.1 without)
+    if constexpr (G <= 2) {
+        float w = weight_of(s[0], -lse[0][0], lse[0][1]);
+        if constexpr (G == 2) w = fmaxf(w, weight_of(s[1], -lse[1][0], lse[1][1]));
+        return w;
+    }
     float best = -INFINITY, second = -INFINITY, bs = 0.f;
     int bi = 0;
 #pragma unroll
