@@ -37,45 +37,12 @@
 // The rows of a wavefront's next tile are requested as soon as the registers of the current tile
 // are consumed (K after S^T, V after the copy to LDS), so loads are in flight during the rest of
 // the tile's work.
-#include "rk_internal.h"
-#include "rk_device.h"
+#include "rk_attn_common.h"
 
 #include <atomic>
 #include <mutex>
 
 namespace rk {
-
-struct AttnParams {
-    const uint16_t* q;                 // bf16 [B, Hq, 128]
-    const uint16_t* k1; const uint16_t* v1; int64_t s1_b, s1_h;   // small cache (TWO_SEG only)
-    const uint16_t* k2; const uint16_t* v2; int64_t s2_b, s2_h;   // full cache
-    const int32_t* tail_start;         // TWO_SEG only
-    const int32_t* seq_lens;
-    int32_t n_sel;                     // rows taken from the small cache (TWO_SEG only)
-    int32_t evict;                     // ... less one per row decoded since the refresh (fixed-size small cache)
-    int32_t tail_wg;                   // TWO_SEG: the rows of the full cache have a workgroup of their own (grid x = nch + 1)
-    int32_t max_rows2;                 // host bound on the rows taken from the full cache
-    int32_t cap1, cap2;                // rows allocated in the small / full cache
-    int32_t nch;                       // workgroups per (sequence, KV head): the launch's grid x
-    int32_t Hq, Hkv;
-    float scale;
-    uint16_t* out;                     // bf16 [B, Hq, 128]
-    float* weights; int64_t w_stride;  // raw scores go here first (EMIT only)
-    int32_t w_vec;                     // rows of `weights` start 16-byte aligned: vector stores allowed
-    int32_t w_inter;                   // groups of 4 heads, scores kept in the workspace: the 4 heads of a position side by side
-                                       // (score of head gi at position j of group (b, g): weights[(b*Hq + g*4) * w_stride + 4*j + gi])
-    float* lse;                        // fp32 [B, Hq], never NULL here
-    const int32_t* pred; int32_t pred_val;
-    int32_t* counters; float* part_ml; float* part_o; int32_t max_chunks;
-    uint32_t* epochs; uint32_t* tag_rows;     // TAGGED only: call number per (sequence, KV head), tagged partial results
-    const int32_t* idx; int32_t idx_stride;   // LAZY only: the selection [B, Hkv, idx_stride] whose rows are not gathered yet
-    float* trig_q_ref; float* trig_sim; int32_t* trig_need; float trig_threshold;   // TRIG only: the query-similarity test
-    int32_t ragged_batch;              // != 0 (= batch): workgroups are shared out by length, see ragged_share_lane
-    int32_t share_cap;                 // ... at most this many to a sequence
-    int32_t* n_attend;                 // APPEND only: [B], rows attended over, for the kernel that follows
-    int32_t slice_merge;               // TAGGED: every workgroup merges a slice of the output (all workgroups of the launch are resident together)
-    int32_t slice_spin;                // ... re-reading rows still in flight at most this often before it leaves its slice to the last one
-};
 
 // Work split of the split kernels.  The rows of a (sequence, KV head) are cut into tiles of 32;
 // tile t belongs to wavefront t % 4 of workgroup (t / 4) % nch, so workgroup c starts at row
@@ -83,9 +50,6 @@ struct AttnParams {
 // same number of tiles, give or take one, whatever the length, and at any moment the launch
 // streams one contiguous stretch of the cache.  Workgroups whose first row is past the end do
 // nothing; the others each leave one partial result (the merge takes any subsets of the rows).
-constexpr int kSplitWaves = 4, kTileRows = 32;
-constexpr int kNoTailWg = 0xff;                   // top byte of the kernel argument s_b_and_tail: no workgroup for the tail rows
-constexpr int kHeadsFirst = 0xfe;                 // ... (launches over the full cache only) grid x = KV head, y = sequence, z = chunk
 __device__ __forceinline__ int active_workgroups(int n_rows, int nch) {
     return max(1, min(nch, (n_rows + kSplitWaves * kTileRows - 1) / (kSplitWaves * kTileRows)));
 }
@@ -162,8 +126,6 @@ __device__ __forceinline__ uint64_t coherent_load2(const float* p) {
 }
 __device__ __forceinline__ float lo_f(uint64_t v) { return __uint_as_float((uint32_t)v); }
 __device__ __forceinline__ float hi_f(uint64_t v) { return __uint_as_float((uint32_t)(v >> 32)); }
-// All global stores this thread issued so far are acknowledged once this returns.
-__device__ __forceinline__ void wait_stores_acknowledged() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // Merge of the partial results of one (sequence, KV head); run by one whole workgroup.
 //   M = max_c m_c;  L = sum_c e^{m_c - M} l_c;  out = sum_c e^{m_c - M} o_c / L;  lse = M + ln L
@@ -272,32 +234,6 @@ __device__ void merge_partials(const AttnParams& p, int b, int g, int nchunks, f
     }
 }
 
-// ds_read_b64_tr_b16: every 16 lanes hand in 16 addresses of 4 consecutive bf16 (a 16 x 4
-// matrix M, row = lane) and lane i gets back M[i/4 + 4e][i%4] for e = 0..3.
-typedef short v4s __attribute__((ext_vector_type(4)));
-typedef short v8s __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));      // 16 bytes in four registers
-// 16-byte load of cache rows.  STREAM: the rows are read once per step and not again before
-// far more than the caches hold has passed through (the full cache): a non-temporal load, which
-// leaves the L2 and the last-level cache to the data that does come back (the small caches, read
-// at every partial step).  Measured: the kernel that streams K and V of the full cache runs 4%
-// faster with it, the scores-only pass too where its keys outgrow the last-level cache (kScoreStreamBytes; below
-// it is 3-5% slower); the partial step is 3% slower.
-template <bool STREAM>
-__device__ __forceinline__ u32x4 load_rows16(const uint16_t* p) {
-    if (STREAM) return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
-    return *reinterpret_cast<const u32x4*>(p);
-}
-__device__ __forceinline__ v4s lds_read_tr16(const uint16_t* ptr) {
-    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)ptr);
-}
-// Two fp32 -> packed bf16 pair, round to nearest even (v_cvt_pk_bf16_f32).
-__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
-    typedef float f32x2 __attribute__((ext_vector_type(2)));
-    const f32x2 v = {a, b};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
-}
 
 // ---- tagged partial results ----
 // The partial result of workgroup c of a (sequence, KV head) is G * 44 rows of 16 bytes.  For each
@@ -319,8 +255,6 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
 // at 1000), which that launch does not lose; so the sum of the weights is taken in fp64 from the pairs, the quotient
 // is one division, and all is summed in the order of block_head_lse and block_head_out, four sums over every fourth
 // chunk: the same bits.  (At most kMergeChunks = 64 chunks: one per lane.)
-constexpr int kTagSpinLimit = 1 << 16;            // re-reads of rows still in flight before giving up (NaN output)
-constexpr int kAgentScopeAux = 16;                // cache-policy operand of buffer loads and stores: sc1
 
 // (`rows`: the partial result of one workgroup, the same for all lanes; `row`: this lane's row of it)
 __device__ __forceinline__ void store_tagged_row(uint32_t* rows, int n_rows, int row, float x0, float x1, float x2,
@@ -356,7 +290,7 @@ __device__ __forceinline__ void merge_tagged_heads(const AttnParams& p, int b, i
     const int lane = threadIdx.x & 63;
     const int64_t bg = (int64_t)b * p.Hkv + g;
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
-        p.tag_rows + bg * kTagSlots * ROWS * 4, 0, kTagSlots * ROWS * 16, 0x00020000);
+        p.tag_rows + bg * kTagRegionRows * G * 4, 0, kTagRegionRows * G * 16, 0x00020000);
     const int r = min(lane, kTagDataRows - 1);
     float num[NH][3], den[NH], Lam[NH];
     bool good = true;
@@ -450,7 +384,7 @@ __device__ __forceinline__ void merge_exact_heads(const AttnParams& p, int b, in
     const int lane = threadIdx.x & 63;
     const int64_t bg = (int64_t)b * p.Hkv + g;
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
-        p.tag_rows + bg * kTagSlots * ROWS * 4, 0, kTagSlots * ROWS * 16, 0x00020000);
+        p.tag_rows + bg * kTagRegionRows * G * 4, 0, kTagRegionRows * G * 16, 0x00020000);
     const int r = min(lane, kTagDataRows - 1);
     auto head_off = [&](int i) { return min(gi0 + i * kSplitWaves, G - 1) * kTagRowsPerHead; };
     u32x4 ml[NH];
@@ -980,8 +914,8 @@ void attn_split_kernel(const uint16_t* k_first, const uint16_t* v_first, int64_t
         my_slice.gi = __builtin_amdgcn_readfirstlane(my_slice.gi);
         my_slice.r0 = __builtin_amdgcn_readfirstlane(my_slice.r0);
         my_slice.n_rows = __builtin_amdgcn_readfirstlane(my_slice.n_rows);
-        tag_rsrc = __builtin_amdgcn_make_buffer_rsrc(p.tag_rows + ((int64_t)b * p.Hkv + g) * kTagSlots * (G * kTagRowsPerHead) * 4, 0,
-                                                     kTagSlots * G * kTagRowsPerHead * 16, 0x00020000);
+        tag_rsrc = __builtin_amdgcn_make_buffer_rsrc(p.tag_rows + ((int64_t)b * p.Hkv + g) * kTagRegionRows * G * 4, 0,
+                                                     kTagRegionRows * G * 16, 0x00020000);
     }
 
     __shared__ __attribute__((aligned(16))) uint16_t sV[NW][ROWS][VS];
@@ -1235,7 +1169,7 @@ void attn_split_kernel(const uint16_t* k_first, const uint16_t* v_first, int64_t
         // Wavefront w publishes the rows of heads w, w + NW: lane r < 43 dims 3r .. 3r + 2, lane 43 the
         // head's log-sum-exp.  The ticket is taken once every wavefront has ISSUED its rows; nothing
         // waits for their acknowledgement (hence a bare barrier: __syncthreads would wait for the stores).
-        uint32_t* trows = p.tag_rows + (bg * kTagSlots + c_rec) * (G * kTagRowsPerHead * 4);
+        uint32_t* trows = p.tag_rows + bg * kTagRegionRows * G * 4 + c_rec * (G * kTagRowsPerHead * 4);
         const uint32_t tag = epoch + 1u != 0u ? epoch + 1u : 1u;           // this call's number: never 0
 #pragma unroll
         for (int i = 0; i < UPW; ++i) {
@@ -2196,6 +2130,17 @@ static int launch_partial(const rk_geom* geom, const void* q, rk_kv small, int32
     p.pred = pred; p.pred_val = pred_val;
     p.counters = ws.counters; p.part_ml = ws.part_ml; p.part_o = ws.part_o; p.max_chunks = ws.max_chunks;
     p.epochs = ws.epochs; p.tag_rows = ws.tag_rows;
+    // one tile per workgroup where all of them are resident at once
+    const TileForm tile = partial_tile_form(n_sel, max_recent, (int64_t)geom->batch * geom->n_kv_heads, G);
+    if (tile.waves != 0 && ws.tag_rows != nullptr && lazy_idx == nullptr) {
+        if (trig != nullptr) {
+            if (pred != nullptr) return RK_ERR_INVALID_ARG;
+            p.trig_q_ref = trig->q_ref; p.trig_sim = trig->sim; p.trig_need = trig->need_full; p.trig_threshold = trig->threshold;
+        }
+        p.nch = tile.nch; p.tail_wg = tile.tail;
+        set_slice_merge(p, true, 0);
+        return launch_partial_tile(p, geom->batch, G, tile.waves, trig != nullptr, (hipStream_t)stream);
+    }
     // Which hand-over.  Tagged partial results merged by slices (every workgroup its share, see the kernel) wherever
     // that merge applies: a launch whose workgroups are all resident at once, with no more partial results per
     // (sequence, KV head) than it has a form for.  Otherwise: rows enough for 32 workgroups per pair of a launch over

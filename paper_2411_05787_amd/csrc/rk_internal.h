@@ -164,6 +164,35 @@ static inline int sliced_split_workgroups(int64_t rows, int64_t tail_rows, int* 
     return (int)n;
 }
 
+constexpr int kTagDataRows = 43;          // a head's 128 output dims as rows of three (the last one holds two) ...
+constexpr int kTagRowsPerHead = kTagDataRows + 1;   // ... plus the row with the chunk's log-sum-exp or (max, sum) (see merge_tagged_heads)
+constexpr int kTagSlots = kMergeChunks + 1;   // tagged partial results per (sequence, KV head): the chunks + the tail's own
+constexpr int kTagRegionRows = kTagSlots * (kD / 2);   // rows per head of a pair's region: 64 to a partial result (rk_attn_common.h), or 44 of the form above
+
+// The partial step in one tile per workgroup (rk_partial.hip): 4 or 8 wavefronts of 16 rows, nch workgroups per (sequence,
+// KV head) for the `rows` of the small cache and `tail` for at most tail_rows rows of the full one; waves = 0: not used.  Its
+// workgroups wait for one another, so all have to be resident at once: by registers and LDS that is three workgroups of 8 wavefronts per
+// compute unit for groups of up to 4 heads, two beyond, and twice that of 4.  4 wavefronts while that is one workgroup per unit and the
+// tails: more of them share the request and the merge; 8 beyond, with half the partial results to write and read.
+// Many partial results to a pair and more than two workgroups per unit (33 MB of rows) are better off in longer stretches
+// (attn_split_kernel).  us per launch, attn_split_kernel / 4 / 8 wavefronts, 32 heads over 8 unless noted: 256 rows 6.9 / 4.9 / 5.5,
+// 1024: 6.7 / 4.8 / 5.9, 2048: 6.5 / 5.6 / 6.0, 4096: 8.4 / 8.3 / 7.9, 6000: 10.0 / - / 9.3, 8192: 11.2 / - / 11.9; 28 over 4, 2048:
+// 7.4 / 5.1 / 5.9, 4096: 7.4 / 6.0 / 6.3, 8192: 9.9 / - / 8.5; 2 sequences of 2048: 8.7 / 7.9 / 7.9, of 4096: 11.2 / - / 11.4; 4 of 1024:
+// 9.3 / 7.8 / 8.2, of 2048: 12.3 / 16.8 / 11.1, of 2048 and 28 over 4: 10.1 / 9.3 / 8.8; 8 of 1024: 12.1 / 13.8 / 11.1; 16 of 512:
+// 12.2 / 14.1 / 10.8, of 1024: 17.7 / 22.9 / 19.0.
+struct TileForm { int waves, nch, tail; };
+static inline TileForm partial_tile_form(int64_t rows, int64_t tail_rows, int64_t problems, int G) {
+    for (int waves = 4; waves <= 8; waves += 4) {
+        const int wg = 16 * waves;
+        const int64_t nch = (rows + wg - 1) / wg, tail = (tail_rows + wg - 1) / wg, total = (nch + tail) * problems;
+        if (nch > kMergeChunks || nch + tail > kTagSlots) continue;
+        if (waves == 4 ? nch * problems <= kComputeUnits && total <= 2 * kComputeUnits
+                       : total <= 2 * kComputeUnits || (G <= 4 && total <= 3 * kComputeUnits && nch <= 20))
+            return {waves, (int)nch, (int)tail};
+    }
+    return {0, 0, 0};
+}
+
 static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 constexpr int kBatchLayers = 32;         // layers one batched launch (rk_refresh_batched) takes; more go in several launches
@@ -196,8 +225,8 @@ static inline int topk_cand_cap(int64_t k) {
 //   sel_counters int32 [B*Hkv][2]            listed candidates and arrival tickets of the selection
 //   epochs    uint32 [B*Hkv]                 call number of the last merge inside a split kernel
 //   hist      uint32 [B*Hkv][kHistBins]      first-level histogram of the pooled scores
-//   tag_rows  16 B  [B*Hkv][kTagSlots][G*44]  tagged partial results of the kernels that merge
-//                                            inside the launch (see merge_tagged in rk_attn.hip)
+//   tag_rows  16 B  [B*Hkv][kTagSlots][G*64]  tagged partial results of the kernels that merge
+//                                            inside the launch (see rk_attn_common.h, and merge_tagged_heads in rk_attn.hip)
 //   lse       fp32  [B*Hq]                   log-sum-exp when the caller does not ask for it
 //   part_ml   fp32  [B*Hkv][kMaxChunks][G][2] running max and sum of every partial result
 //   part_o    fp32  [B*Hkv][nch][G][128]     unnormalised partial outputs
@@ -208,9 +237,6 @@ constexpr int kCounterStride = 32;       // int32 between two arrival counters: 
 constexpr int kCountWord = 4;
 constexpr int kRaggedMaxBatch = 64;      // most sequences whose workgroups are shared out by length
 static inline int ragged_batch_of(const rk_geom* g) { return (g->batch > 1 && g->batch <= kRaggedMaxBatch) ? g->batch : 0; }
-constexpr int kTagDataRows = 43;          // a head's 128 output dims as rows of three (the last one holds two) ...
-constexpr int kTagRowsPerHead = kTagDataRows + 1;   // ... plus the row with the chunk's log-sum-exp or (max, sum) (see merge_tagged_heads)
-constexpr int kTagSlots = kMergeChunks + 1;   // tagged partial results per (sequence, KV head): the chunks + the tail's own
 struct Workspace {
     int32_t* counters;
     int32_t* sel_counters;
@@ -238,7 +264,7 @@ static inline size_t zero_kept_bytes(const rk_geom* g) {
     const size_t G = (size_t)(g->n_q_heads / g->n_kv_heads);
     size_t off = problems * ((size_t)kCounterStride + 2 + 1 + (size_t)kHistBins) * sizeof(int32_t);
     off = (off + 255) / 256 * 256;
-    return off + problems * kTagSlots * G * kTagRowsPerHead * 16;
+    return off + problems * kTagRegionRows * G * 16;
 }
 
 static inline int max_chunks_for(int64_t max_len) {
@@ -372,7 +398,7 @@ static inline Workspace carve(const rk_geom* g, int64_t max_len, int64_t max_k, 
     w.epochs = (uint32_t*)(p + off);  off += problems * sizeof(uint32_t);
     w.hist = (uint32_t*)(p + off);    off += problems * kHistBins * sizeof(uint32_t);
     off = align_up(off, 256);
-    w.tag_rows = (uint32_t*)(p + off); off += problems * kTagSlots * G * kTagRowsPerHead * 16;
+    w.tag_rows = (uint32_t*)(p + off); off += problems * kTagRegionRows * G * 16;
     w.lse = (float*)(p + off);        off += align_up((size_t)g->batch * g->n_q_heads * sizeof(float), 256);
     w.part_ml = (float*)(p + off);    off += align_up(problems * kMaxChunks * G * 2 * sizeof(float), 256);
     w.part_o = (float*)(p + off);     off += align_up(problems * w.max_chunks * G * kD * sizeof(float), 256);

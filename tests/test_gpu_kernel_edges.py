@@ -428,3 +428,63 @@ def test_batched_gather_of_large_small_caches(rk, B):
     assert int((idx < 0).sum()) == 7 * Hkv and torch.equal(tail, lens)
     assert torch.equal(sK, torch.where(there, torch.gather(K, 2, at), torch.full_like(sK, 3.0)))
     assert torch.equal(sV, torch.where(there, torch.gather(V, 2, at), torch.full_like(sV, 5.0)))
+
+
+# One tile per workgroup: 64 rows (16 per wavefront) up to 256 workgroups, 128 rows beyond, in up to 65 partial results (merged in
+# units of 16, 8 and 4 rows, by up to 20, 40 and more of them), a workgroup or more for the rows decoded since the refresh; and
+# attn_split_kernel where that ends.  Per sequence: (tail_start, rows since).
+TILE_EDGES = [("k1", 4, 8, 1, 4, 0, [(900, 3)]), ("k16_17_g1", 1, 3, 17, 4, 0, [(900, 4), (16, 1)]), ("k63_g8", 8, 2, 63, 70, 0, [(900, 65), (900, 64), (62, 0)]),
+              ("k64_g5", 5, 2, 64, 8, 0, [(64, 8), (63, 7), (0, 2), (0, 0)]), ("k65_evict", 4, 4, 65, 40, 1, [(900, 40), (900, 1), (900, 0)]),
+              ("k256_evicts_all", 2, 2, 256, 300, 1, [(900, 300), (900, 256), (900, 129)]), ("none_selected", 4, 2, 0, 200, 0, [(900, 200), (500, 0), (0, 129)]),
+              ("k1280_20_chunks", 3, 2, 1280, 5, 0, [(1279, 5), (2000, 0)]), ("k2560_g7", 7, 2, 2560, 5, 0, [(2560, 5)]), ("k2561_u4", 4, 4, 2561, 1, 0, [(3000, 1)]),
+              ("k4096_65_chunks_g7", 7, 4, 4096, 64, 0, [(4096, 64)]), ("k4096_8w", 4, 8, 4096, 5, 0, [(4096, 5)]), ("k4100_8w_g6", 6, 8, 4100, 128, 0, [(4100, 128)]),
+              ("k8192_65_chunks_8w_g8", 8, 4, 8192, 100, 0, [(8192, 100)]), ("k8192_split", 4, 8, 8192, 5, 0, [(8192, 5)]),
+              ("batch", 4, 8, 700, 9, 0, [(700 + 37 * b, b) for b in range(9)]), ("batch_3_per_cu", 4, 8, 512, 9, 0, [(600, 9 - b % 4) for b in range(16)])]
+
+
+@pytest.mark.parametrize("case", TILE_EDGES, ids=[c[0] for c in TILE_EDGES])
+def test_partial_step_at_tile_edges(rk, case):
+    """Against fp64, one bf16 step of the larger value and 4e-6 (see helpers); the bits do not depend on who merges (bound on the
+    re-reads of rows in flight at 0, 1, default), nor does NaN past the rows of a sequence; strided caches, out 2-byte aligned."""
+    name, G, Hkv, k, max_recent, evict, seqs = case
+    say("tile edge", name)
+    B, cap = len(seqs), max(t + r for t, r in seqs) + 2
+    g = torch.Generator(device="cuda").manual_seed(k + G)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
+    K, V = rnd(B, Hkv, cap, 128), rnd(B, Hkv, cap, 128)
+    sK, sV = rnd(B, Hkv, max(k, 1) + 3, 128), rnd(B, Hkv, max(k, 1) + 3, 128)
+    q = rnd(B, Hkv * G, 128)
+    rows, nan = [], float("nan")
+    for b, (t0, r) in enumerate(seqs):
+        n1 = min(max(k - (r if evict else 0), 0), t0)
+        rows.append((n1, t0, t0 + r))
+        sK[b, :, n1:], sV[b, :, n1:] = nan, nan
+        K[b, :, :t0], V[b, :, :t0], K[b, :, t0 + r:], V[b, :, t0 + r:] = nan, nan, nan, nan
+    geom = rk.Geom(B, Hkv * G, Hkv, 128, SCALE)
+    ws = rk.Workspace(geom, cap, max(k, 16))
+    i32 = lambda x: torch.tensor(x, dtype=torch.int32, device="cuda")
+    tail, lens = i32([t for t, _ in seqs]), i32([t + r for t, r in seqs])
+    outs = []
+    try:
+        for spin in (256, 0, 1, 256):
+            rk.rk_debug_set_slice_spin(spin)
+            buf = torch.full((B * Hkv * G * 128 + 1,), 7.0, dtype=torch.bfloat16, device="cuda")
+            out = buf[1:].view(B, Hkv * G, 128)
+            fn = rk.rk_partial_attn_fixed if evict else rk.rk_partial_attn
+            fn(geom, q, sK, sV, k, K, V, tail, lens, max_recent, out, workspace=ws)
+            torch.cuda.synchronize()
+            outs.append(out.clone())
+    finally:
+        rk.rk_debug_set_slice_spin(256)
+    for o in outs[1:]:
+        assert torch.equal(o, outs[0])
+    for b, (n1, t0, n) in enumerate(rows):
+        if n1 + n - t0 == 0:
+            assert (outs[0][b] == 0).all()
+            continue
+        Kb = torch.cat([sK[b, :, :n1], K[b, :, t0:n]], dim=1).double()
+        Vb = torch.cat([sV[b, :, :n1], V[b, :, t0:n]], dim=1).double()
+        s = SCALE * torch.matmul(q[b].double().view(Hkv, G, 128), Kb.transpose(1, 2).contiguous())
+        ref = torch.matmul(torch.softmax(s, dim=-1), Vb).reshape(-1, 128)
+        d = (outs[0][b].double() - ref).abs()
+        assert (d <= torch.maximum(outs[0][b].double().abs(), ref.abs()) * 2.0 ** -7 + 4e-6).all(), (b, float(d.max()))

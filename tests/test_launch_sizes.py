@@ -35,6 +35,12 @@ int main() {
             const int n = sliced_split_workgroups(r, tail, &own, p, 64);
             printf("sliced %ld %d %ld %d %d\n", r, tail, p, n, own);
         }
+    for (long r : {0L, 1L, 64L, 65L, 256L, 700L, 1024L, 2048L, 4096L, 6000L, 8192L, 8193L, 100000L}) for (long p : {1L, 4L, 8L, 12L, 32L, 64L, 128L, 512L, 4096L})
+        for (int tail : {0, 1, 64, 65, 128, 500, 100000}) for (int G : {1, 4, 5, 8}) {
+            if (r + tail == 0) continue;
+            const TileForm f = partial_tile_form(r, tail, p, G);
+            printf("tile %ld %ld %d %d %d %d %d\n", r, p, tail, G, f.waves, f.nch, f.tail);
+        }
     const long lens[] = {1, 2000, 32768, 33008, 65536, 131072, 1000000};
     for (long l : lens) for (int b : {1, 2, 16}) for (int hkv : {1, 4, 8}) {
         rk_geom g{b, hkv * 4, hkv, 128, 1.0f};
@@ -154,6 +160,25 @@ def test_sliced_split_bounds_and_measured_choices(table):
     assert got[(8192, 10, 4)] == (64, 0)
     assert got[(16384, 10, 8)] == (64, 0)         # two tiles per wavefront either way
     assert got[(3072, 10, 8)] == (24, 1)
+
+
+def test_partial_tile_form_bounds_and_measured_choices(table):
+    """Every row has a wavefront's 16-row slot, the partial results have slots, and the launch is resident as a whole."""
+    got = {}
+    for kind, *v in table:
+        if kind != "tile":
+            continue
+        rows, pairs, tail, G, waves, nch, ntail = map(int, v)
+        got[(rows, pairs, tail, G)] = (waves, nch, ntail)
+        assert waves in (0, 4, 8)
+        if waves:
+            assert nch * 16 * waves >= rows and ntail * 16 * waves >= tail and nch <= 64 and 1 <= nch + ntail <= 65
+            assert (nch + ntail) * pairs <= (512 if waves == 4 or G > 4 else 768)
+    assert got[(2048, 8, 1, 4)] == (4, 32, 1) and got[(256, 8, 1, 4)] == (4, 4, 1) and got[(4096, 4, 1, 8)] == (4, 64, 1)
+    assert got[(4096, 8, 1, 4)] == (8, 32, 1) and got[(8192, 4, 1, 8)] == (8, 64, 1)
+    assert got[(8192, 8, 1, 4)][0] == 0 and got[(1024, 128, 1, 4)][0] == 0            # 33 MB and more in many partial results
+    assert got[(2048, 32, 1, 4)] == (8, 16, 1) and got[(1024, 64, 1, 4)] == (8, 8, 1) and got[(1024, 64, 1, 5)][0] == 0
+    assert got[(0, 8, 500, 4)] == (4, 0, 8) and got[(2048, 8, 100000, 4)][0] == 0
 
 
 @pytest.fixture(scope="module")
