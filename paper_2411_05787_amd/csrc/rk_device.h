@@ -234,18 +234,20 @@ __device__ __forceinline__ void store_chunks(int32_t* counters, int64_t bg, int 
     counters[bg * kCounterStride + kCountWord] = nchunks;
 }
 
-// Inclusive prefix sum over the 64 lanes of the wavefront.
-__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v) {
-    const int lane = threadIdx.x & 63;
+// Inclusive prefix sum over every row of 16 lanes, and over the 64 lanes of the wavefront (a lane without a source adds 0).
+__device__ __forceinline__ uint32_t row_inclusive_scan(uint32_t v) {
     uint32_t x = v;
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, true);
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, true);
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, true);
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, true);
-    const uint32_t t0 = (uint32_t)__builtin_amdgcn_readlane((int)x, 15), t1 = (uint32_t)__builtin_amdgcn_readlane((int)x, 31);
-    const uint32_t t2 = (uint32_t)__builtin_amdgcn_readlane((int)x, 47);
-    const int row = lane >> 4;
-    return x + (row == 0 ? 0u : row == 1 ? t0 : row == 2 ? t0 + t1 : t0 + t1 + t2);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, true);     // row_shr:1
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, true);     // row_shr:2
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, true);     // row_shr:4
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, true);     // row_shr:8
+    return x;
+}
+__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v) {
+    uint32_t x = row_inclusive_scan(v);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false);    // row_bcast:15 into rows 1 and 3
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false);    // row_bcast:31 into rows 2 and 3
+    return x;
 }
 
 // Max-pool of one tile and the selection's first-level histogram of the results; 256 threads.  sA[i] is the
@@ -360,5 +362,9 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
+
+// LDS traffic of this thread is done, and every wavefront of the workgroup got here: unlike __syncthreads() this does
+// not wait for loads from memory that are still in flight.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 }  // namespace rk

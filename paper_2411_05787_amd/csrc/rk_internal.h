@@ -214,6 +214,19 @@ static inline int topk_cand_cap(int64_t k) {
     return (int)c;
 }
 
+// Workgroups that share one row of the selection (a power of two; select_part, rk_topk.hip), for `rows` (sequence, KV head) pairs
+// in the launch: 8, as long as all are resident at once (one per compute unit).  us per call of rk_topk_select (pooling included)
+// with 1 / 2 / 4 / 8 / 16: 8 rows of 32768, K = 2048: 16.1 / 15.1 / 14.8 / 14.9 / 15.6; of 131072, K = 8192: 35.9 / 25.8 / 24.1 / 23.3 /
+// 23.3; of 2048, K = 256: 12.5 / 10.9 / 10.8 / 11.0 / 11.6; 4 rows of 65536, K = 4096: 22.2 / 18.9 / 18.1 / 17.5 / 17.4; 32 rows of
+// 65536, K = 8192: 33.4 / 28.0 / 26.6 / 25.8 / 36.7; 64 rows of 8192: 14.7 / 14.3 / 14.0 / 20.3; 128 rows of 16384: 22.2 / 21.9 / 29.9.
+// (What this replaced, every row's candidates listed by a workgroup per 4096 positions and ranked by the last to arrive, one
+// workgroup alone up to 8192: 16.0, 28.9, 13.4, 17.8, 42.0, 15.3, 32.9.)
+static inline int select_parts(int64_t max_len, int64_t rows) {
+    int64_t parts = 8;
+    while (parts > 1 && parts * rows > kComputeUnits) parts /= 2;
+    return (int)parts;
+}
+
 // Device workspace, carved in this order (every region 256-byte aligned).  The regions up to and
 // including tag_rows must be zero when a workspace is first used (rk_workspace_init clears the
 // whole workspace once); the counters and histograms are left cleared by the kernels that use
@@ -222,7 +235,7 @@ static inline int topk_cand_cap(int64_t k) {
 //   counters  int32 [B*Hkv][kCounterStride]  one 128-byte line each: arrival ticket of the split attention
 //                                            kernel (word 0), the trigger's ticket (1), slices left over
 //                                            (2, 3), number of partial results of the last full pass (4)
-//   sel_counters int32 [B*Hkv][2]            listed candidates and arrival tickets of the selection
+//   sel_counters int32 [B*Hkv][2]            arrival tickets of the selection (word 0)
 //   epochs    uint32 [B*Hkv]                 call number of the last merge inside a split kernel
 //   hist      uint32 [B*Hkv][kHistBins]      first-level histogram of the pooled scores
 //   tag_rows  16 B  [B*Hkv][kTagSlots][G*64]  tagged partial results of the kernels that merge
@@ -248,8 +261,6 @@ struct Workspace {
     float* part_o;
     float* pooled;
     float* scores;
-    uint64_t* cand_list;  // [B*Hkv][cand_cap] candidates (score image, ~position) of the spread-out selection;
-                          // last, because its size depends on k
     int cand_cap;         // candidate slots the selection sorts in LDS
     int max_chunks;       // nch above
     size_t total;
@@ -405,7 +416,6 @@ static inline Workspace carve(const rk_geom* g, int64_t max_len, int64_t max_k, 
     w.pooled = (float*)(p + off);     off += align_up(problems * (size_t)pooled_row_stride(max_len > 0 ? max_len : 1) * sizeof(float), 256);
     w.scores = (float*)(p + off);     off += align_up((size_t)g->batch * g->n_q_heads * (size_t)pooled_row_stride(max_len > 0 ? max_len : 1) * sizeof(float), 256);
     w.cand_cap = topk_cand_cap(max_k > 0 ? max_k : 1);
-    w.cand_list = (uint64_t*)(p + off); off += align_up(problems * (size_t)w.cand_cap * sizeof(uint64_t), 256);
     w.total = off;
     return w;
 }

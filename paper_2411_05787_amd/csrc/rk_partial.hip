@@ -18,10 +18,6 @@
 
 namespace rk {
 
-// LDS traffic of this thread is done, and every wavefront of the workgroup got here: unlike __syncthreads() this does
-// not wait for loads from memory that are still in flight.
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 // What the kernel needs beyond its preloaded arguments, in the order in which it needs it.
 struct TileParams {
     float scale2;                             // scale * log2 e: scores, maxima and lambda are kept in units of ln 2

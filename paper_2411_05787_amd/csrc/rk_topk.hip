@@ -11,11 +11,9 @@
 //   the K-th largest score; every position in that bin or a higher one is a candidate (the K
 //   winners plus the rest of one bin).  What is listed and ranked are runs of candidates: up to
 //   four neighbours with the same pooled score (the pooling window makes neighbours equal, so runs
-//   are several times fewer than positions).  The runs are packed into a dense list: for rows up
-//   to 8192 positions by the one workgroup of the (sequence, KV head), in LDS; for longer rows by
-//   one workgroup per 4096 positions (per 32768 in a launch over many long rows), into the
-//   workspace (one atomic add per workgroup reserves the space), and the workgroup that arrives
-//   last goes on alone.  It takes the list into registers and bucket-sorts it back into LDS on the
+//   are several times fewer than positions).  Up to 8 workgroups share a row, by rank (select_part):
+//   each lists and ranks the runs of its own stretch of scores.  Up to 256 runs are compared each with
+//   each; more, or those of a whole row, are taken into registers and bucket-sorted back into LDS on the
 //   64-bit item (P image, position, length): 2048 buckets from the lowest candidate image up to
 //   the bin of the 64-th largest score (of equal width, or laid out from the histogram), one more
 //   bucket for everything above (fewer than 64 positions); a scan turns bucket counts into
@@ -23,7 +21,7 @@
 //   above plus those of the larger runs in its own bucket (a few compares).  Positions that rank
 //   below K' are written out directly: idx comes out in rank order.  The kernel also clears the
 //   histogram for the next call.
-// Dense or degenerate score distributions take further exact steps in kernel 2 (one workgroup):
+// Dense or degenerate score distributions take further exact steps in kernel 2 (select_row, one workgroup):
 // more runs than fit in LDS -> bin b1 is cut once more by the next 11 image bits (one more pass
 // over P) and only its upper part stays a candidate; a bucket with more than 1024 runs -> the list
 // is bitonic-sorted instead of ranked; still too many candidates (e.g. all scores equal) -> a last
@@ -35,17 +33,18 @@
 namespace rk {
 
 constexpr int kSelThreads = 1024;
-constexpr int kSelTile = 4 * kSelThreads;                // positions per workgroup when the selection is spread out
-constexpr int kSelSingle = 2 * kSelTile;                 // rows up to this length are left to one workgroup
-constexpr int kSelHeld = 8 * kSelTile;                   // positions a workgroup keeps in registers (NV vectors per thread)
-constexpr int kBatchSingleFrom = 64;                     // ... and so are all rows of a batched launch with this many rows
+constexpr int kSelHeld = 8;                              // vectors of four positions of a row in a thread's registers at a time
 constexpr int kBuckets = 2048;                           // regular buckets, plus one for all above
 constexpr int kBucketLimit = 1024;                       // larger buckets: sort instead of ranking
 constexpr int kAdaptiveFrom = 8192;                      // candidates from which buckets follow the histogram
 constexpr int kTopLoose = 64;                            // scores above the bucketed range: fewer than this
+constexpr int kPairs = 256;                               // a part's runs up to here are compared each with each
+static_assert(kMaxCandidates / 2 * 4 <= 0xFFFF, "buckets of a part count positions in 16 bits");
+constexpr int kNonFinite = 1;                            // thread whose two bins of the histogram start at infinity
 constexpr int kListTry = 4;                              // runs are listed for up to this many times cand_cap positions
 static_assert(kHistBins == 1 << 11, "first-level histogram is 11 bits wide");
 static_assert(kHistBins == 2 * kSelThreads, "the selection scans the histogram two bins per thread");
+static_assert(((uint32_t)(2 * (kSelThreads - 1 - kNonFinite)) << kHistShift) == 0xFF800000u, "image of infinity");
 
 // What is ranked is a run: up to kRunMax positions next to each other with the same pooled score
 // (the pooling window makes the scores of up to pool_w neighbours equal, so there are several
@@ -106,31 +105,15 @@ void pool_hist_kernel(const float* __restrict__ weights, int64_t w_stride, const
 // NT / 64 words.  Returns the inclusive sum; *total gets the workgroup sum.
 template <int NT>
 __device__ __forceinline__ uint32_t block_inclusive_scan(uint32_t v, uint32_t* scratch, uint32_t* total) {
-    constexpr int NWV = NT / 64;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    // inside the wavefront: a scan of every row of 16 lanes on the DPP path (a lane whose source
-    // would lie outside its row adds 0), then the totals of the rows before, through scalar registers
-    uint32_t x = v;
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, true);     // row_shr:1
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, true);     // row_shr:2
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, true);     // row_shr:4
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, true);     // row_shr:8
-    {
-        const uint32_t t0 = (uint32_t)__builtin_amdgcn_readlane((int)x, 15), t1 = (uint32_t)__builtin_amdgcn_readlane((int)x, 31);
-        const uint32_t t2 = (uint32_t)__builtin_amdgcn_readlane((int)x, 47);
-        const int row = lane >> 4;
-        x += row == 0 ? 0u : row == 1 ? t0 : row == 2 ? t0 + t1 : t0 + t1 + t2;
-    }
-    __syncthreads();                              // scratch may still be read from a previous scan
+    static_assert(NT / 64 == 16, "a row of lanes adds up the wavefronts");
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t x = wave_inclusive_scan(v);
+    lds_barrier();                                // scratch may still be read from a previous scan (loads from memory stay in flight)
     if (lane == 63) scratch[w] = x;
-    __syncthreads();
-    uint32_t base = 0, tot = 0;
-#pragma unroll
-    for (int i = 0; i < NWV; ++i) {
-        const uint32_t s = scratch[i];
-        if (i < w) base += s;
-        tot += s;
-    }
+    lds_barrier();
+    const uint32_t s = row_inclusive_scan(scratch[lane & 15]);
+    const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)s, 15);
+    const uint32_t base = w != 0 ? (uint32_t)__builtin_amdgcn_readlane((int)s, w - 1) : 0u;
     *total = tot;
     return x + base;
 }
@@ -241,85 +224,195 @@ __device__ void bitonic_sort_desc(uint64_t* sKeys, int npad) {
     __syncthreads();
 }
 
-// Grid (tiles, KV heads, sequences).  With one tile the workgroup does everything.  With more,
-// every workgroup derives the thresholds from the histogram, packs the runs of candidates among
-// its own tile_vecs * kSelTile positions into a list in the workspace (one atomic add per
-// workgroup reserves the space), and the workgroup that arrives last (ticket, as in the attention
-// kernels) takes the list into registers and ranks it: the pass over all positions, which is what
-// a single workgroup spends most of its time on, is spread over the chip.
-// The selection of one (sequence b, KV head blockIdx.y), by the workgroups blockIdx.x = 0 .. gridDim.x - 1.
-template <bool ADAPT>                    // ADAPT: compiled with the histogram-driven bucket layout (large K only)
-__device__ __forceinline__
-void select_body(const float* __restrict__ pooled, int64_t pooled_stride, const int32_t* seq_lens,
-                 int32_t max_len, int32_t k, uint32_t* __restrict__ hist, int32_t cand_cap,
-                 int32_t* __restrict__ idx, float* __restrict__ sel_scores,
-                 const int32_t* pred, int32_t pred_val,
-                 int32_t* __restrict__ sel_counters, uint64_t* __restrict__ cand_list, const int b,
-                 const int tile_vecs) {
-    const int tile = blockIdx.x, g = blockIdx.y, Hkv = gridDim.y;
-    const bool multi = gridDim.x > 1;
-    if (pred != nullptr && pred[b] != pred_val) return;
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    uint64_t* sKeys = reinterpret_cast<uint64_t*>(smem);                   // [cand_cap]
-    uint32_t* sHist = reinterpret_cast<uint32_t*>(sKeys + cand_cap);       // [2 * (kBuckets + 1)]: bucket
-                                                                           // arrays, or the radix histogram
-    uint32_t* sScan = sHist + 2 * (kBuckets + 1);                          // [16]
-    uint32_t* sOut = sScan + kSelThreads / 64;                             // [4]
-    uint32_t* sCount = sOut + 4;                                           // [1]
-    uint16_t* sTab = reinterpret_cast<uint16_t*>(sCount + 1);              // [kHistBins] buckets of each first-level bin
-                                                                           // (allocated only if cand_cap > kAdaptiveFrom)
+// One (sequence, KV head)'s row, and the workgroup's LDS.
+struct SelectRow {
+    const float* P;                         // pooled scores, 16-byte aligned
+    uint32_t* gh;                           // their first-level histogram
+    int n, k, kprime;                       // positions, ranks asked for, ranks that exist
+    int room;                               // vectors of four positions that rows have room for
+    int cand_cap;
+    int32_t* idx; float* sel_scores;        // [k]; sel_scores may be NULL
 
-    const int tid = threadIdx.x;
-    const int n = min(seq_lens[b], max_len);
-    const int kprime = min(k, max(n, 0));
-    const int64_t bg = (int64_t)b * Hkv + g;
-    const int64_t ob = bg * k;
-    if (kprime <= 0) {                      // nothing was histogrammed for an empty sequence
-        if (tile == 0)
-            for (int i = tid; i < k; i += kSelThreads) { idx[ob + i] = -1; if (sel_scores) sel_scores[ob + i] = 0.f; }
-        return;
+    // Vector v of the row as it lies in memory: a buffer, so that nothing branches around a load; behind `room` zeros.
+    __device__ __forceinline__ float4 raw4(int v) const {
+        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(P), 0, room * 16, 0x00020000);
+        return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(r, v * 16, 0, 0));
     }
-    const float* P = pooled + bg * pooled_stride;
-    uint32_t* gh = hist + bg * kHistBins;
-
-    // The first 32 scores of every thread (the whole row up to 32768 positions) are requested now,
-    // 16-byte loads all in flight together with the histogram's, and stay in registers.
-    constexpr int NV = kSelHeld / kSelTile;
-    const float4* P4 = reinterpret_cast<const float4*>(P);
-    const int nvec = (n + 3) >> 2;
-    // positions at and beyond n read as -1: below every candidate threshold (scores are >= 0)
-    auto load4 = [&](int v) -> float4 {
-        float4 x = (v < nvec) ? P4[v] : make_float4(-1.f, -1.f, -1.f, -1.f);
-        if (4 * v + 3 >= n && v < nvec) {             // the row's last, partial vector
-            if (4 * v + 1 >= n) x.y = -1.f;
-            if (4 * v + 2 >= n) x.z = -1.f;
-            x.w = -1.f;
-        }
+    // ... with positions at and beyond n as -1: below every candidate threshold (scores are >= 0).
+    __device__ __forceinline__ float4 load4(int v) const {
+        float4 x = raw4(v);
+        x.x = 4 * v < n ? x.x : -1.f; x.y = 4 * v + 1 < n ? x.y : -1.f;
+        x.z = 4 * v + 2 < n ? x.z : -1.f; x.w = 4 * v + 3 < n ? x.w : -1.f;
         return x;
-    };
-    float4 held[NV];
-    if (!multi) {
-#pragma unroll
-        for (int u = 0; u < NV; ++u) held[u] = load4(u * kSelThreads + tid);
-    } else {
-        // this workgroup's tile_vecs * kSelTile positions (tile_vecs is 1 or NV)
-        held[0] = load4(tile * tile_vecs * kSelThreads + tid);
-        if (tile_vecs > 1) {
-#pragma unroll
-            for (int u = 1; u < NV; ++u) held[u] = load4((tile * tile_vecs + u) * kSelThreads + tid);
+    }
+    // The positions of a run whose first one has rank r, as far as they rank below K'.
+    __device__ __forceinline__ void write_run(uint64_t item, uint32_t r) const {
+        const int j = item_pos(item);
+        const uint32_t len = min(item_len(item), (uint32_t)kprime - min(r, (uint32_t)kprime));
+        for (uint32_t i = 0; i < len; ++i) {
+            idx[r + i] = j + (int)i;
+            if (sel_scores) sel_scores[r + i] = value_of((uint32_t)(item >> 32));
         }
     }
+    __device__ __forceinline__ void fill_rest() const {     // ranks that no position has
+        for (int i = kprime + (int)threadIdx.x; i < k; i += kSelThreads) {
+            idx[i] = -1;
+            if (sel_scores) sel_scores[i] = 0.f;
+        }
+    }
+};
+struct SelectLds {
+    uint64_t* keys;                         // [cand_cap]
+    uint32_t* hist;                         // [2 * (kBuckets + 1)]: bucket arrays, or the radix histogram
+    uint32_t* scan;                         // [kSelThreads / 64]
+    uint32_t* out;                          // [4]
+    uint32_t* count;                        // [1]
+    uint32_t* part;                         // [8]
+    uint16_t* tab;                          // [kHistBins] buckets of each first-level bin (allocated only if cand_cap > kAdaptiveFrom)
 
-    // From the histogram, in one scan from the top bin down (thread 0 owns the top two bins):
-    // the bin b1 that holds the K'-th largest score (with the count above it), and the bin that
-    // holds the kTopLoose-th largest, which bounds the bucketed range from above so that the one
-    // bucket for "everything above" stays small (its items are ranked by a loop over the bucket).
-    if (tid == 0) *sCount = 0;
-    for (int i = tid; i < kBuckets + 1; i += kSelThreads) sHist[i] = 0;     // bucket sizes of the fast path
-    uint32_t h0, h1;                         // this thread's two bins of the first-level histogram
+    __device__ __forceinline__ SelectLds(unsigned char* smem, int cand_cap) {
+        keys = reinterpret_cast<uint64_t*>(smem);
+        hist = reinterpret_cast<uint32_t*>(keys + cand_cap);
+        scan = hist + 2 * (kBuckets + 1);
+        out = scan + kSelThreads / 64;
+        count = out + 4;
+        part = count + 1;
+        tab = reinterpret_cast<uint16_t*>(part + 8);
+    }
+};
+
+// Ranks the n_items runs in the list (keys) by buckets and writes them out, the first position after `base` others; hist is cleared.
+// False: some bucket holds too many; the list is as it was.
+// The list is taken into registers, up to kItems items per thread, so that the same LDS array can receive them again
+// sorted by bucket.  A bucket is counted twice in one word, runs << 16 | positions (neither field overflows:
+// at most cand_cap runs and 65535 positions in all).
+template <class Bucket>
+__device__ __forceinline__ bool rank_by_buckets(const SelectRow& row, const SelectLds& lds, uint32_t n_items, uint32_t base, Bucket&& bucket_of) {
+    const int tid = threadIdx.x;
+    uint64_t* const sKeys = lds.keys;
+    uint32_t *const sHist = lds.hist, *const sScan = lds.scan;
+    uint32_t* sCnt = sHist;                         // [kBuckets + 1] bucket sizes, then fill marks (in runs)
+    uint32_t* sStart = sHist + kBuckets + 1;        // [kBuckets + 1] bucket offsets: runs << 16 | positions
+    static_assert(kMaxCandidates < (1 << 16), "runs and positions of a bucket are counted in 16 bits each");
+    constexpr int kItems = kMaxCandidates / kSelThreads;
+    uint64_t it[kItems];
+#pragma unroll
+    for (int u = 0; u < kItems; ++u) {
+        const int e = u * kSelThreads + tid;
+        it[u] = (e < (int)n_items) ? sKeys[e] : 0ull;
+    }
+    const int n_mine = ((int)n_items - tid + kSelThreads - 1) / kSelThreads;   // items of this thread
+    __syncthreads();                                // the list is in registers: sKeys is free
+#pragma unroll
+    for (int u = 0; u < kItems; ++u)
+        if (u < n_mine) atomicAdd(&sCnt[bucket_of((uint32_t)(it[u] >> 32))], 0x10000u | item_len(it[u]));
+    __syncthreads();
+    // offsets from the top bucket down: thread 0 owns the two highest regular buckets
+    const int rt = kSelThreads - 1 - tid;
+    const uint32_t c0 = sCnt[2 * rt], c1 = sCnt[2 * rt + 1], cov = sCnt[kBuckets];
+    const bool big = (c0 >> 16) > (uint32_t)kBucketLimit || (c1 >> 16) > (uint32_t)kBucketLimit ||
+                     (cov >> 16) > (uint32_t)kBucketLimit;
+    uint32_t total;
+    const uint32_t incl = block_inclusive_scan<kSelThreads>(c0 + c1, sScan, &total);
+    const uint32_t above2 = incl - (c0 + c1) + cov;
+    if (!__syncthreads_or(big ? 1 : 0)) {
+        sStart[2 * rt + 1] = above2;      sCnt[2 * rt + 1] = above2 >> 16;
+        sStart[2 * rt] = above2 + c1;     sCnt[2 * rt] = (above2 + c1) >> 16;
+        if (tid == 0) { sStart[kBuckets] = 0; sCnt[kBuckets] = 0; }
+        __syncthreads();
+        // every item into its bucket (order inside a bucket is arbitrary)
+#pragma unroll
+        for (int u = 0; u < kItems; ++u)
+            if (u < n_mine) sKeys[atomicAdd(&sCnt[bucket_of((uint32_t)(it[u] >> 32))], 1u)] = it[u];
+        __syncthreads();
+        // rank of a run's first position = positions in the buckets above + positions of the
+        // larger runs in its own bucket; ranks below K' are the answer
+        for (int e = tid; e < (int)n_items; e += kSelThreads) {
+            const uint64_t item = sKeys[e];
+            const uint32_t bk = bucket_of((uint32_t)(item >> 32));
+            const uint32_t st = sStart[bk], lo = st >> 16, hi = sCnt[bk];
+            uint32_t r = base + (st & 0xFFFFu);
+            // four reads in flight; a read past the bucket's end takes the item itself, which counts nothing
+            for (uint32_t x = lo; x < hi; x += 4) {
+                uint64_t o[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) o[i] = sKeys[x + i < hi ? x + i : (uint32_t)e];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) r += (o[i] > item) ? item_len(o[i]) : 0u;
+            }
+            row.write_run(item, r);
+        }
+        return true;
+    }
+    // a huge bucket (many equal or nearly equal scores): put the list back and sort it instead
+#pragma unroll
+    for (int u = 0; u < kItems; ++u)
+        if (u < n_mine) sKeys[u * kSelThreads + tid] = it[u];
+    __syncthreads();
+    return false;
+}
+
+// Sorts the list's nvalid runs and writes them out, the first position after `base` others.
+__device__ __forceinline__ void rank_by_sorting(const SelectRow& row, const SelectLds& lds, int nvalid, uint32_t base) {
+    const int tid = threadIdx.x;
+    uint64_t* const sKeys = lds.keys;
+    uint32_t* const sScan = lds.scan;
+    int npad = 1;
+    while (npad < nvalid) npad <<= 1;
+    for (int i = nvalid + tid; i < npad; i += kSelThreads) sKeys[i] = 0;   // sorts behind every real item
+    __syncthreads();
+    bitonic_sort_desc(sKeys, npad);
+    // sKeys[0 .. nvalid) in order: a run's rank is the number of positions in the runs before it.
+    // Every thread takes a stretch of the list: the lengths of the stretches before it, then its own.
     {
-        const int rt = kSelThreads - 1 - tid;
-        h0 = gh[2 * rt]; h1 = gh[2 * rt + 1];
+        const int per = (nvalid + kSelThreads - 1) / kSelThreads;
+        const int e0 = min(tid * per, nvalid), e1 = min(e0 + per, nvalid);
+        uint32_t mine = 0, total;
+        for (int e = e0; e < e1; ++e) mine += item_len(sKeys[e]);
+        uint32_t r = block_inclusive_scan<kSelThreads>(mine, sScan, &total) - mine + base;
+        for (int e = e0; e < e1; ++e) {
+            const uint64_t item = sKeys[e];
+            row.write_run(item, r);
+            r += item_len(item);
+        }
+    }
+}
+
+// Part number `part` of the selection of one row.
+//
+// One workgroup alone spends its time on the phases of the ranking (a barrier and some dozen instructions per item and phase, 16
+// wavefronts on one CU), so they are shared out by rank: every workgroup reads the whole row and its histogram, cuts the range of
+// the candidates' scores into stretches of about the same count (bins of the histogram, cut linearly inside), and lists
+// and ranks the runs of its own stretch.  Where its ranks start follows from the histogram and the scores it counts between its
+// stretch and the next bin.  Nothing is handed over: the workgroups meet only in the ticket whose last drawer clears the
+// histogram, and does the row alone should a stretch not have fitted some workgroup's list (many equal scores).
+// True: this workgroup is that one.
+// What bounds it is latency: us after the first workgroup's first instruction, 8 rows of 32768 positions, K = 2048, medians:
+// lengths 0.7, histogram and stretch 2.6, row looked through 3.8, runs listed 5.5, ranked 6.7, written 7.1 (the launch 9 - 10
+// against 10.6 before); of 131072, K = 8192, 32 parts: 0.8, 2.7, 6.6, 10.5 (512 KB through one CU), 11.9, 12.4.
+__device__ __forceinline__ bool select_part(const SelectRow& row, const SelectLds& lds, int32_t* __restrict__ ticket, const int part, const int lg_parts) {
+    const int tid = threadIdx.x, n = row.n, kprime = row.kprime, nvec = (n + 3) >> 2, cand_cap = row.cand_cap;
+    uint64_t* const sKeys = lds.keys;
+    uint32_t *const sHist = lds.hist, *const sScan = lds.scan, *const sOut = lds.out, *const sCount = lds.count, *const sPart = lds.part;
+    const int list_cap = cand_cap / 2;      // runs a part lists; the other half of the room is the queue's
+    uint32_t* const sQueue = reinterpret_cast<uint32_t*>(sKeys + list_cap);                // [cand_cap]
+    uint32_t* const gh = row.gh;
+    // This thread's two bins of the first-level histogram are requested first, the row's scores (whatever its length: rows have room
+    // for max_len) behind them: the bins are counted while the scores are on their way.
+    const int rt = kSelThreads - 1 - tid;
+    const uint2 h01 = *reinterpret_cast<const uint2*>(gh + 2 * rt);
+    constexpr int NV = kSelHeld;
+    float4 held[NV];
+#pragma unroll
+    for (int u = 0; u < NV; ++u) held[u] = row.raw4(u * kSelThreads + tid);
+
+    // The stretch is [B(part + 1), B(part)): B(i) leaves i / parts of the K' ranks above it, the last one all candidates.  sPart: this
+    // part's B(i), the end of B(i)'s bin, the positions above that bin; B(i + 1); positions with an infinite score or NaN; vectors
+    // queued; positions between the stretch and the end of the bin; positions in the stretch.  sOut: as in select_row.
+    if (tid == 0) { *sCount = 0; sPart[5] = 0; sPart[6] = 0; sPart[7] = 0; }
+    for (int i = tid; i < kBuckets + 1; i += kSelThreads) sHist[i] = 0;
+    const uint32_t h0 = h01.x, h1 = h01.y;
+    {
         uint32_t total;
         const uint32_t incl = block_inclusive_scan<kSelThreads>(h0 + h1, sScan, &total);   // entries in bins >= 2 rt
         const uint32_t abv = incl - (h0 + h1);
@@ -331,7 +424,217 @@ void select_body(const float* __restrict__ pooled, int64_t pooled_stride, const 
             sOut[2] = upper ? h1 : h0;
         }
         if (abv < kk2 && kk2 <= incl) sOut[3] = (uint32_t)(2 * rt + (abv + h1 >= kk2 ? 1 : 0));
-        if (!multi) { gh[2 * rt] = 0; gh[2 * rt + 1] = 0; }     // cleared for the next call
+        {                                       // (stretches in bits of scores >= 0)
+            if (tid == kNonFinite) sPart[4] = incl;
+            const uint32_t t0 = (kk1 * (uint32_t)part) >> lg_parts, t1 = (kk1 * (uint32_t)(part + 1)) >> lg_parts;
+            const uint32_t spare = part + 1 == 1 << lg_parts ? (kk1 * 3u >> 3) + 16u : 0u;        // the last part: that many ranks more
+            auto bound = [&](uint32_t t, uint32_t spare, uint32_t& at, uint32_t& end, uint32_t& a) {
+                const bool upper = abv + h1 >= t;
+                const uint32_t h = upper ? h1 : h0, width = 1u << kHistShift;
+                a = upper ? abv : abv + h1;
+                end = ((uint32_t)(2 * rt + (upper ? 1 : 0) + 1) << kHistShift) - 0x80000000u;
+                at = end - min((uint32_t)((float)(t + spare - a) * ((float)width / (float)h)), width);
+                if (t - a == h) { at = end = end - width; a = t; }       // the whole bin: nothing to count
+            };
+            uint32_t at, end, a;
+            if (t0 == 0) {                  // (the top, or fewer ranks than parts)
+                if (tid == 0) { sPart[0] = sPart[1] = 0x80000000u; sPart[2] = 0; }
+            } else if (abv < t0 && t0 <= incl) {
+                bound(t0, 0u, at, end, a);
+                sPart[0] = at; sPart[1] = end; sPart[2] = a;
+            }
+            if (t1 == 0) {
+                if (tid == 0) sPart[3] = 0x80000000u;
+            } else if (abv < t1 && t1 <= incl) {
+                bound(t1, spare, at, end, a);
+                sPart[3] = at;
+            }
+        }
+        lds_barrier();
+    }
+    // the lowest and highest candidates' bits (scores as whole numbers; a row whose threshold lies among negative scores, or
+    // with infinities or NaN, is the last workgroup's alone)
+    const uint32_t b1 = sOut[0], key_top = (sOut[3] + 1u) << kHistShift;
+    // The K'-th score lies anywhere in its bin, and that bin may hold many times the ranks that are left: the last part starts
+    // with an estimate of its lower end and takes the rest of the bin only if too few positions turn up.  (131072 positions with half of
+    // the keys near 64 centroids, K = 8192: 4136 runs in the last part without it, 350 in the others; a step of one layer 105.8 ->
+    // 101.3 us.  The second look at the row costs 4 - 8 us: with 3/16 of the ranks to spare instead of 3/8 that step takes 110, a window
+    // of 32 queries over 32768 positions 70.9 instead of 67.7.)
+    const uint32_t hi = sPart[0], end = sPart[1], floor = part + 1 < (1 << lg_parts) ? sPart[3] : (b1 << kHistShift) - 0x80000000u;
+    uint32_t lo = max(sPart[3], floor), top = hi, top_end = end;       // the stretch so far, and what is looked for in this pass over the row
+    bool bad = b1 < (uint32_t)kHistBins / 2 || sPart[4] != 0;
+    while (!bad && lo < top) {
+        // Bits of scores as whole numbers, from the stretch's lowest.  A vector of four positions with none in the stretch or
+        // between it and the end of its bin is passed over after one comparison of the least; the numbers of the others are
+        // queued, so that what is left to do with them takes every lane.
+        const uint32_t stretch = top - lo, upto = top_end - lo, more = upto - stretch;
+        for (int v0 = 0; v0 < nvec; v0 += NV * kSelThreads) {
+            float4 next[NV];
+#pragma unroll
+            for (int u = 0; u < NV; ++u) next[u] = row.raw4(v0 + (NV + u) * kSelThreads + tid);
+            uint64_t hit[NV];
+            int found = 0;
+            const int left = nvec - v0 - tid;           // (what lies behind the row is whatever the workspace holds)
+#pragma unroll
+            for (int u = 0; u < NV; ++u) {
+                const uint32_t ra = __float_as_uint(held[u].x) - lo, rb = __float_as_uint(held[u].y) - lo;
+                const uint32_t rc = __float_as_uint(held[u].z) - lo, rd = __float_as_uint(held[u].w) - lo;
+                hit[u] = __ballot(min(min(ra, rb), min(rc, rd)) < upto && u * kSelThreads < left);
+                found += __popcll(hit[u]);
+            }
+            if (found != 0) {
+                int at = 0;
+                if ((tid & 63) == 0) at = (int)atomicAdd(&sPart[5], (uint32_t)found);
+                at = __builtin_amdgcn_readfirstlane(at);
+#pragma unroll
+                for (int u = 0; u < NV; ++u) {
+                    const int q = at + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(hit[u] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hit[u], 0u));
+                    if ((hit[u] >> (tid & 63) & 1) != 0 && q < cand_cap) sQueue[q] = (uint32_t)(v0 + u * kSelThreads + tid);
+                    at += __popcll(hit[u]);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < NV; ++u) held[u] = next[u];
+        }
+        lds_barrier();
+        const int queued = min((int)sPart[5], cand_cap);
+        uint32_t higher = 0, inside = 0;
+        for (int e0 = 0; e0 < queued; e0 += kSelThreads) {
+            const int e = e0 + tid;
+            if (e - (tid & 63) >= queued) break;        // (whole wavefronts)
+            uint32_t a = 0xBF800000u, b = a, c = a, d = a;
+            int j = 0;
+            if (e < queued) {
+                const int v = (int)sQueue[e];
+                const float4 x = row.raw4(v);
+                j = v << 2;
+                const int in = n - j;                   // positions of the vector inside the row
+                a = __float_as_uint(x.x);
+                b = in > 1 ? __float_as_uint(x.y) : b; c = in > 2 ? __float_as_uint(x.z) : c; d = in > 3 ? __float_as_uint(x.w) : d;
+            }
+            const uint32_t ra = a - lo, rb = b - lo, rc = c - lo, rd = d - lo;
+            higher += (ra - stretch < more ? 1u : 0u) + (rb - stretch < more ? 1u : 0u) + (rc - stretch < more ? 1u : 0u) +
+                      (rd - stretch < more ? 1u : 0u);
+            inside += (ra < stretch ? 1u : 0u) + (rb < stretch ? 1u : 0u) + (rc < stretch ? 1u : 0u) + (rd < stretch ? 1u : 0u);
+            // the runs (up to four neighbours with the same score) among them
+            const bool fa = ra < stretch, fb = rb < stretch && b != a, fc = rc < stretch && c != b, fd = rd < stretch && d != c;
+            const uint32_t runs = (fa ? 1u : 0u) + (fb ? 1u : 0u) + (fc ? 1u : 0u) + (fd ? 1u : 0u);
+            const uint32_t incl = wave_inclusive_scan(runs);
+            uint32_t at = 0;
+            if ((tid & 63) == 63) at = atomicAdd(sCount, incl);
+            uint32_t pos = (uint32_t)__builtin_amdgcn_readlane((int)at, 63) + incl - runs;
+            auto put = [&](uint32_t bits, int first, int len) {
+                if (pos < (uint32_t)list_cap) sKeys[pos] = item_of(bits | 0x80000000u, first, len);      // runs beyond the end are only counted
+                ++pos;
+            };
+            const int ed = d == c ? 1 : 0, ec = c == b ? 1 + ed : 0, eb = b == a ? 1 + ec : 0;
+            if (fa) put(a, j, 1 + eb);
+            if (fb) put(b, j + 1, 1 + ec);
+            if (fc) put(c, j + 2, 1 + ed);
+            if (fd) put(d, j + 3, 1);
+        }
+        if (top_end != top) {
+            higher = wave_inclusive_scan(higher);
+            if ((tid & 63) == 63 && higher != 0) atomicAdd(&sPart[6], higher);
+        }
+        if (lo == floor) break;
+        inside = wave_inclusive_scan(inside);
+        if ((tid & 63) == 63 && inside != 0) atomicAdd(&sPart[7], inside);
+        lds_barrier();
+        if (sPart[2] + sPart[6] + sPart[7] >= (uint32_t)kprime) break;
+        if (sPart[5] > (uint32_t)cand_cap) break;       // (the queue was too short: what was counted is not all)
+        top = top_end = lo;
+        lo = floor;
+        lds_barrier();
+        if (tid == 0) sPart[5] = 0;
+        lds_barrier();
+#pragma unroll
+        for (int u = 0; u < NV; ++u) held[u] = row.raw4(u * kSelThreads + tid);
+    }
+    lds_barrier();
+    const uint32_t n_items = *sCount, base = sPart[2] + sPart[6];
+    bad = bad || sPart[5] > (uint32_t)cand_cap || n_items > (uint32_t)list_cap;
+    uint32_t seen = 0;                      // (every thread has read the histogram; the answer is waited for behind the ranking)
+    if (tid == 0) seen = (uint32_t)__hip_atomic_fetch_add(ticket, bad ? 0x10001 : 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!bad && n_items != 0) {
+        if (n_items <= (uint32_t)kPairs) {
+            // few runs: every one against every other, a wavefront for 64 of them and a share of the others
+            const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lg = n_items > 64 ? n_items > 128 ? 2 : 1 : 0;
+            const int shares = kSelThreads / 64 >> lg, share = w >> lg, e = (w & ((1 << lg) - 1)) * 64 + (tid & 63);
+            {
+                const uint64_t item = e < (int)n_items ? sKeys[e] : ~0ull;
+                uint32_t r = 0;
+#pragma unroll 4
+                for (int x = share; x < (int)n_items; x += shares) {
+                    const uint64_t o = sKeys[x];
+                    r += o > item ? item_len(o) : 0u;
+                }
+                if (r != 0) atomicAdd(&sHist[e], r);
+            }
+            lds_barrier();                  // (leaves the ticket on its way)
+            if (tid < (int)n_items) row.write_run(sKeys[tid], base + sHist[tid]);
+        } else {
+            // equal widths; the first part's thin top in one bucket (see select_row)
+            const uint32_t from = lo + 0x80000000u, to = part == 0 && key_top > from ? key_top : hi + 0x80000000u;
+            const uint32_t width = to - 1u - from;
+            const int shift = width >= (uint32_t)kBuckets ? 32 - 11 - __builtin_clz(width) : 0;
+            if (!rank_by_buckets(row, lds, n_items, base, [&](uint32_t key) { return min((key - from) >> shift, (uint32_t)kBuckets); }))
+                rank_by_sorting(row, lds, (int)n_items, base);
+        }
+    }
+    if (part == 0) row.fill_rest();
+    if (tid == 0) sOut[0] = seen + (bad ? 0x10000u : 0u);
+    __syncthreads();
+    const uint32_t drawn = sOut[0];
+    if ((drawn & 0xFFFFu) != (1u << lg_parts) - 1u) return false;
+    // last to arrive: the workspace is left clean
+    if (tid == 0) __hip_atomic_store(ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (drawn >= 0x10000u) {                // (the ranks that others have written come out the same)
+        __syncthreads();
+        return true;
+    }
+    gh[2 * tid] = 0; gh[2 * tid + 1] = 0;
+    return false;
+}
+
+// The whole selection of one row by one workgroup.
+template <bool ADAPT>                    // ADAPT: compiled with the histogram-driven bucket layout (large K only)
+__device__ __forceinline__ void select_row(const SelectRow& row, const SelectLds& lds) {
+    const int tid = threadIdx.x, n = row.n, kprime = row.kprime, nvec = (n + 3) >> 2, cand_cap = row.cand_cap;
+    uint64_t* const sKeys = lds.keys;
+    uint32_t *const sHist = lds.hist, *const sScan = lds.scan, *const sOut = lds.out, *const sCount = lds.count;
+    uint16_t* const sTab = lds.tab;
+    const float* const P = row.P;
+    uint32_t* const gh = row.gh;
+    // The first 32 scores of every thread (the whole row up to 32768 positions) are requested now, behind this thread's two bins of
+    // the histogram, 16-byte loads all in flight together, and stay in registers.
+    const int rt = kSelThreads - 1 - tid;
+    const uint2 h01 = *reinterpret_cast<const uint2*>(gh + 2 * rt);
+    constexpr int NV = kSelHeld;
+    float4 held[NV];
+#pragma unroll
+    for (int u = 0; u < NV; ++u) held[u] = row.load4(u * kSelThreads + tid);
+
+    // From the histogram, in one scan from the top bin down (thread 0 owns the top two bins):
+    // the bin b1 that holds the K'-th largest score (with the count above it), and the bin that
+    // holds the kTopLoose-th largest, which bounds the bucketed range from above so that the one
+    // bucket for "everything above" stays small (its items are ranked by a loop over the bucket).
+    if (tid == 0) *sCount = 0;
+    for (int i = tid; i < kBuckets + 1; i += kSelThreads) sHist[i] = 0;     // bucket sizes of the fast path
+    const uint32_t h0 = h01.x, h1 = h01.y;
+    {
+        uint32_t total;
+        const uint32_t incl = block_inclusive_scan<kSelThreads>(h0 + h1, sScan, &total);   // entries in bins >= 2 rt
+        const uint32_t abv = incl - (h0 + h1);
+        const uint32_t kk1 = (uint32_t)kprime, kk2 = min((uint32_t)kprime, (uint32_t)kTopLoose);
+        if (abv < kk1 && kk1 <= incl) {
+            const bool upper = abv + h1 >= kk1;
+            sOut[0] = (uint32_t)(2 * rt + (upper ? 1 : 0));
+            sOut[1] = upper ? abv : abv + h1;
+            sOut[2] = upper ? h1 : h0;
+        }
+        if (abv < kk2 && kk2 <= incl) sOut[3] = (uint32_t)(2 * rt + (abv + h1 >= kk2 ? 1 : 0));
+        gh[2 * rt] = 0; gh[2 * rt + 1] = 0;                     // cleared for the next call
         __syncthreads();
     }
     const uint32_t b1 = sOut[0];
@@ -343,8 +646,7 @@ void select_body(const float* __restrict__ pooled, int64_t pooled_stride, const 
     // The list holds runs, so it may have room where the positions are too many: up to
     // kListTry * cand_cap positions the runs are listed anyway, counted as they are, and the list
     // is used if they fit.  (Bucket offsets below are counted in 16 bits: 65535 positions at most.)
-    const bool try_list = count_ge <= (uint32_t)min(kListTry * cand_cap, 0xFFFF);    // the same in every workgroup of (b, g)
-    bool listed = false;                    // the runs of all candidates are in the workspace
+    const bool try_list = count_ge <= (uint32_t)min(kListTry * cand_cap, 0xFFFF);
 
     // The runs of candidates inside one vector of four scores (positions j .. j + 3; a candidate is
     // a score >= thr; scores are >= +0 and -0 never occurs, so equal scores have equal bits and the
@@ -368,57 +670,6 @@ void select_body(const float* __restrict__ pooled, int64_t pooled_stride, const 
     static_assert(kRunMax == 4, "runs are found inside one float4");
 
     uint32_t n_items = 0;                   // runs in the list
-    if (multi) {
-        int32_t* n_listed = sel_counters + bg * 2;
-        int32_t* arrived = n_listed + 1;
-        uint64_t* list = cand_list + bg * cand_cap;
-        if (try_list) {
-            const float t1 = value_of(key_thr);
-            uint32_t c = count_runs(held[0], t1);
-            if (tile_vecs > 1) {
-#pragma unroll
-                for (int u = 1; u < NV; ++u) c += count_runs(held[u], t1);
-            }
-            uint32_t total;
-            const uint32_t incl = block_inclusive_scan<kSelThreads>(c, sScan, &total);
-            if (tid == 0 && total != 0)
-                *sCount = (uint32_t)__hip_atomic_fetch_add(n_listed, (int32_t)total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __syncthreads();
-            uint32_t pos = *sCount + incl - c;
-            auto put = [&](uint32_t key, int j, int len) {
-                if (pos < (uint32_t)cand_cap)                      // runs beyond the list's end are only counted
-                    __hip_atomic_store(&list[pos], item_of(key, j, len), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                ++pos;
-            };
-            visit_runs(held[0], (tile * tile_vecs * kSelThreads + tid) << 2, t1, put);
-            if (tile_vecs > 1) {
-#pragma unroll
-                for (int u = 1; u < NV; ++u) visit_runs(held[u], ((tile * tile_vecs + u) * kSelThreads + tid) << 2, t1, put);
-            }
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // the list entries are acknowledged
-        }
-        __syncthreads();                                           // ... and every thread has read the histogram
-        if (tid == 0) sOut[1] = (uint32_t)__hip_atomic_fetch_add(arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __syncthreads();
-        if (sOut[1] != gridDim.x - 1) return;
-        // last to arrive: everything of this (b, g) is in (a workgroup has the answer of its
-        // reservation before it writes its entries, hence before its ticket: the count is final);
-        // leave the workspace clean, then rank
-        if (tid == 0) {
-            sOut[2] = (uint32_t)__hip_atomic_load(n_listed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(n_listed, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(arrived, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            *sCount = 0;
-        }
-        { const int rt = kSelThreads - 1 - tid; gh[2 * rt] = 0; gh[2 * rt + 1] = 0; }
-        __syncthreads();
-        n_items = sOut[2];
-        listed = try_list && n_items <= (uint32_t)cand_cap;
-        if (!listed) {                                             // too many candidates: go on alone, from the scores
-#pragma unroll
-            for (int u = 0; u < NV; ++u) held[u] = load4(u * kSelThreads + tid);
-        }
-    }
     float thr = value_of(key_thr);                       // lowest candidate score (scores are >= 0)
     // The runs of candidates among NV vectors per thread (vector u of the thread is number
     // v0 + u * kSelThreads + tid of the row) go to the end of the list in sKeys: every wavefront
@@ -448,12 +699,12 @@ void select_body(const float* __restrict__ pooled, int64_t pooled_stride, const 
     auto list_row = [&]() -> uint32_t {
         if (!held_is_row_start) {
 #pragma unroll
-            for (int u = 0; u < NV; ++u) held[u] = load4(u * kSelThreads + tid);
+            for (int u = 0; u < NV; ++u) held[u] = row.load4(u * kSelThreads + tid);
         }
         list_candidates(held, 0);
         for (int v0 = NV * kSelThreads; v0 < nvec; v0 += kSelThreads * NV) {
 #pragma unroll
-            for (int u = 0; u < NV; ++u) held[u] = load4(v0 + u * kSelThreads + tid);
+            for (int u = 0; u < NV; ++u) held[u] = row.load4(v0 + u * kSelThreads + tid);
             list_candidates(held, v0);
             held_is_row_start = false;
         }
@@ -463,17 +714,16 @@ void select_body(const float* __restrict__ pooled, int64_t pooled_stride, const 
         if (tid == 0) *sCount = 0;
         return runs;
     };
-    // Candidates are the positions whose image is >= key_thr.  Normally that is "bin b1 or above",
-    // taken from the workspace (listed) or from the row; if their runs are too many for LDS, bin
-    // b1 is cut once more by the next 11 image bits.
+    // Candidates are the positions whose image is >= key_thr.  Normally that is "bin b1 or above"; if their runs are too many for
+    // LDS, bin b1 is cut once more by the next 11 image bits.
     uint32_t prefix = key_thr, mask = 0x7FFu << kHistShift, kk = (uint32_t)kprime - above;   // radix-select state
     bool refined = false;
     bool in_lds = false;                    // the runs of all candidates are in sKeys
-    if (!listed && try_list && !multi) {    // (spread out and not listed: the runs were counted and do not fit)
+    if (try_list) {
         n_items = list_row();
         in_lds = n_items <= (uint32_t)cand_cap;
     }
-    if (!listed && !in_lds) {               // (more than cand_cap positions: fewer would have been listed)
+    if (!in_lds) {                          // (more than cand_cap positions: fewer would have been listed)
         radix_pass<11>(P, n, prefix, mask, 10, kk, sHist, sScan, sOut);
         const uint32_t b2 = sOut[0];
         count_ge = above + sOut[1] + sHist[b2];
@@ -509,32 +759,13 @@ void select_body(const float* __restrict__ pooled, int64_t pooled_stride, const 
         }
         return min((key - key_thr) >> bucket_shift, (uint32_t)kBuckets);
     };
-    // The positions of a run whose first one has rank r, as far as they rank below K'.
-    auto write_run = [&](uint64_t item, uint32_t r) {
-        const int j = item_pos(item);
-        const uint32_t len = min(item_len(item), (uint32_t)kprime - min(r, (uint32_t)kprime));
-        for (uint32_t i = 0; i < len; ++i) {
-            idx[ob + r + i] = j + (int)i;
-            if (sel_scores) sel_scores[ob + r + i] = value_of((uint32_t)(item >> 32));
-        }
-    };
     int nvalid;                             // entries of sKeys that are real (sorting paths)
-    if (listed || in_lds) {
-        // ---- candidates = every position whose image is >= key_thr, count_ge of them ----
-        // Their runs are in a dense list (in the workspace, put there by all the workgroups of the
-        // row, or in LDS); everything from here on runs on the list: up to kItems items per thread,
-        // taken into registers so that the same LDS array can receive them again sorted by bucket.
-        // A bucket is counted twice in one word, runs << 16 | positions (neither field overflows:
-        // at most cand_cap runs and 65535 positions in all).
-        uint32_t* sCnt = sHist;                         // [kBuckets + 1] bucket sizes, then fill marks (in runs)
-        uint32_t* sStart = sHist + kBuckets + 1;        // [kBuckets + 1] bucket offsets: runs << 16 | positions
-        static_assert(kMaxCandidates < (1 << 16), "runs and positions of a bucket are counted in 16 bits each");
+    if (in_lds) {
+        // ---- candidates = every position whose image is >= key_thr, count_ge of them; their runs are in LDS ----
         if (refined) {                                  // the radix pass used the array: clear it again
-            for (int i = tid; i < kBuckets + 1; i += kSelThreads) sCnt[i] = 0;
+            for (int i = tid; i < kBuckets + 1; i += kSelThreads) sHist[i] = 0;
         }
-        uint32_t total;
         if (ADAPT && !refined && count_ge > (uint32_t)kAdaptiveFrom) {
-            const int rt = kSelThreads - 1 - tid;
             const uint32_t top = (key_top - 1u) >> kHistShift;
             const float per_item = 1400.f / (float)count_ge;              // aims at ~1500 buckets in all
             auto log2_buckets = [&](uint32_t h, uint32_t bin) -> int {    // -1: no bucket
@@ -544,6 +775,7 @@ void select_body(const float* __restrict__ pooled, int64_t pooled_stride, const 
             };
             const int e0 = log2_buckets(h0, 2 * rt), e1 = log2_buckets(h1, 2 * rt + 1);
             const uint32_t nb0 = e0 < 0 ? 0u : 1u << e0, nb1 = e1 < 0 ? 0u : 1u << e1;
+            uint32_t total;
             const uint32_t incl = block_inclusive_scan<kSelThreads>(nb0 + nb1, sScan, &total);   // buckets of bins >= 2 rt
             adaptive = total != 0 && total <= (uint32_t)kBuckets;
             if (adaptive) {
@@ -553,72 +785,10 @@ void select_body(const float* __restrict__ pooled, int64_t pooled_stride, const 
             }
             __syncthreads();
         }
-        constexpr int kItems = kMaxCandidates / kSelThreads;
-        uint64_t it[kItems];
-        if (listed) {                                   // the dense list is in the workspace already
-            const uint64_t* list = cand_list + bg * cand_cap;
-#pragma unroll
-            for (int u = 0; u < kItems; ++u) {
-                const int e = u * kSelThreads + tid;
-                it[u] = (e < (int)n_items) ? __hip_atomic_load(&list[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
-            }
-        } else {
-#pragma unroll
-            for (int u = 0; u < kItems; ++u) {
-                const int e = u * kSelThreads + tid;
-                it[u] = (e < (int)n_items) ? sKeys[e] : 0ull;
-            }
-        }
-        const int n_mine = ((int)n_items - tid + kSelThreads - 1) / kSelThreads;   // items of this thread
-        __syncthreads();                                // the list is in registers: sKeys is free
-#pragma unroll
-        for (int u = 0; u < kItems; ++u)
-            if (u < n_mine) atomicAdd(&sCnt[bucket_of((uint32_t)(it[u] >> 32))], 0x10000u | item_len(it[u]));
-        __syncthreads();
-        // offsets from the top bucket down: thread 0 owns the two highest regular buckets
-        const int rt = kSelThreads - 1 - tid;
-        const uint32_t c0 = sCnt[2 * rt], c1 = sCnt[2 * rt + 1], cov = sCnt[kBuckets];
-        const bool big = (c0 >> 16) > (uint32_t)kBucketLimit || (c1 >> 16) > (uint32_t)kBucketLimit ||
-                         (cov >> 16) > (uint32_t)kBucketLimit;
-        const uint32_t incl = block_inclusive_scan<kSelThreads>(c0 + c1, sScan, &total);
-        const uint32_t above2 = incl - (c0 + c1) + cov;
-        if (!__syncthreads_or(big ? 1 : 0)) {
-            sStart[2 * rt + 1] = above2;      sCnt[2 * rt + 1] = above2 >> 16;
-            sStart[2 * rt] = above2 + c1;     sCnt[2 * rt] = (above2 + c1) >> 16;
-            if (tid == 0) { sStart[kBuckets] = 0; sCnt[kBuckets] = 0; }
-            __syncthreads();
-            // every item into its bucket (order inside a bucket is arbitrary)
-#pragma unroll
-            for (int u = 0; u < kItems; ++u)
-                if (u < n_mine) sKeys[atomicAdd(&sCnt[bucket_of((uint32_t)(it[u] >> 32))], 1u)] = it[u];
-            __syncthreads();
-            // rank of a run's first position = positions in the buckets above + positions of the
-            // larger runs in its own bucket; ranks below K' are the answer
-            for (int e = tid; e < (int)n_items; e += kSelThreads) {
-                const uint64_t item = sKeys[e];
-                const uint32_t bk = bucket_of((uint32_t)(item >> 32));
-                const uint32_t st = sStart[bk], lo = st >> 16, hi = sCnt[bk];
-                uint32_t r = st & 0xFFFFu;
-                // four reads in flight; a read past the bucket's end takes the item itself, which counts nothing
-                for (uint32_t x = lo; x < hi; x += 4) {
-                    uint64_t o[4];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) o[i] = sKeys[x + i < hi ? x + i : (uint32_t)e];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) r += (o[i] > item) ? item_len(o[i]) : 0u;
-                }
-                write_run(item, r);
-            }
-            for (int i = kprime + tid; i < k; i += kSelThreads) {
-                idx[ob + i] = -1;
-                if (sel_scores) sel_scores[ob + i] = 0.f;
-            }
+        if (rank_by_buckets(row, lds, n_items, 0u, bucket_of)) {
+            row.fill_rest();
             return;
         }
-        // a huge bucket (many equal or nearly equal scores): put the list back and sort it instead
-#pragma unroll
-        for (int u = 0; u < kItems; ++u)
-            if (u < n_mine) sKeys[u * kSelThreads + tid] = it[u];
         nvalid = (int)n_items;
     } else {
         // ---- slow path: exact K-th largest image T by radix select over P ----
@@ -648,40 +818,43 @@ void select_body(const float* __restrict__ pooled, int64_t pooled_stride, const 
         }
         nvalid = kprime;                                // runs of one position each
     }
-    int npad = 1;
-    while (npad < nvalid) npad <<= 1;
-    for (int i = nvalid + tid; i < npad; i += kSelThreads) sKeys[i] = 0;   // sorts behind every real item
-    __syncthreads();
-    bitonic_sort_desc(sKeys, npad);
-    // sKeys[0 .. nvalid) in order: a run's rank is the number of positions in the runs before it.
-    // Every thread takes a stretch of the list: the lengths of the stretches before it, then its own.
-    {
-        const int per = (nvalid + kSelThreads - 1) / kSelThreads;
-        const int e0 = min(tid * per, nvalid), e1 = min(e0 + per, nvalid);
-        uint32_t mine = 0, total;
-        for (int e = e0; e < e1; ++e) mine += item_len(sKeys[e]);
-        uint32_t r = block_inclusive_scan<kSelThreads>(mine, sScan, &total) - mine;
-        for (int e = e0; e < e1; ++e) {
-            const uint64_t item = sKeys[e];
-            write_run(item, r);
-            r += item_len(item);
-        }
-    }
-    for (int i = kprime + tid; i < k; i += kSelThreads) {
-        idx[ob + i] = -1;
-        if (sel_scores) sel_scores[ob + i] = 0.f;
-    }
+    rank_by_sorting(row, lds, nvalid, 0u);
+    row.fill_rest();
 }
 
+template <bool ADAPT>
+__device__ __forceinline__
+void select_body(const float* __restrict__ pooled, int64_t pooled_stride, const int32_t* seq_lens,
+                 int32_t max_len, int32_t k, uint32_t* __restrict__ hist, int32_t cand_cap,
+                 int32_t* __restrict__ idx, float* __restrict__ sel_scores,
+                 const int32_t* pred, int32_t pred_val,
+                 int32_t* __restrict__ sel_counters, const int b, const int g, const int Hkv,
+                 const int part, const int lg_parts) {
+    if (pred != nullptr && pred[b] != pred_val) return;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const SelectLds lds(smem, cand_cap);
+    const int64_t bg = (int64_t)b * Hkv + g;
+    const int n = min(seq_lens[b], max_len);
+    const SelectRow row{pooled + bg * pooled_stride, hist + bg * kHistBins, n, k, min(k, max(n, 0)), (max_len + 3) >> 2, cand_cap, idx + bg * k,
+                        sel_scores ? sel_scores + bg * k : nullptr};
+    if (row.kprime <= 0) {                  // nothing was histogrammed for an empty sequence
+        if (part == 0) row.fill_rest();
+        return;
+    }
+    if (lg_parts > 0 && !select_part(row, lds, sel_counters + bg * 2, part, lg_parts)) return;
+    select_row<ADAPT>(row, lds);
+}
+
+// Grid (KV heads, parts, sequences): consecutive workgroups go to the 8 XCDs in turn, so with 8 KV heads (or 4, or 16) the parts of
+// a row share an L2.
 template <bool ADAPT>
 __global__ __launch_bounds__(kSelThreads)
 void select_kernel(const float* __restrict__ pooled, int64_t pooled_stride, const int32_t* seq_lens,
                    int32_t max_len, int32_t k, uint32_t* __restrict__ hist, int32_t cand_cap,
                    int32_t* __restrict__ idx, float* __restrict__ sel_scores,
-                   const int32_t* pred, int32_t pred_val,
-                   int32_t* __restrict__ sel_counters, uint64_t* __restrict__ cand_list) {
+                   const int32_t* pred, int32_t pred_val, int32_t* __restrict__ sel_counters) {
     select_body<ADAPT>(pooled, pooled_stride, seq_lens, max_len, k, hist, cand_cap, idx, sel_scores, pred, pred_val,
-                       sel_counters, cand_list, (int)blockIdx.z, 1);
+                       sel_counters, (int)blockIdx.z, (int)blockIdx.x, (int)gridDim.x, (int)blockIdx.y, 31 - __builtin_clz(gridDim.y));
 }
 
 // The selections of several layers in one launch: grid z = layer * batch + sequence; what differs
@@ -691,17 +864,17 @@ struct SelectBatch {
     uint32_t* hist[kBatchLayers];
     int32_t* idx[kBatchLayers];
     int32_t* sel_counters[kBatchLayers];
-    uint64_t* cand_list[kBatchLayers];
     const int32_t* pred[kBatchLayers];       // NULL: every sequence of the layer
 };
 
 template <bool ADAPT>
 __global__ __launch_bounds__(kSelThreads)
 void select_batched_kernel(const SelectBatch tab, int32_t batch, int64_t pooled_stride, const int32_t* seq_lens,
-                           int32_t max_len, int32_t k, int32_t cand_cap, int32_t pred_val, int32_t tile_vecs) {
+                           int32_t max_len, int32_t k, int32_t cand_cap, int32_t pred_val) {
     const int layer = blockIdx.z / batch, b = blockIdx.z - layer * batch;
     select_body<ADAPT>(tab.pooled[layer], pooled_stride, seq_lens, max_len, k, tab.hist[layer], cand_cap, tab.idx[layer],
-                       nullptr, tab.pred[layer], pred_val, tab.sel_counters[layer], tab.cand_list[layer], b, tile_vecs);
+                       nullptr, tab.pred[layer], pred_val, tab.sel_counters[layer], b, (int)blockIdx.x, (int)gridDim.x,
+                       (int)blockIdx.y, 31 - __builtin_clz(gridDim.y));
 }
 
 }  // namespace rk
@@ -740,7 +913,7 @@ static int launch_select(const rk_geom* geom, const int32_t* seq_lens, int32_t m
     // the sort kernel may need more than the default dynamic LDS; the per-bin bucket table is part
     // of it only where there can be kAdaptiveFrom candidates
     const size_t lds = (size_t)ws.cand_cap * sizeof(uint64_t) +
-                       (2 * (kBuckets + 1) + kSelThreads / 64 + 4 + 1) * sizeof(uint32_t) +
+                       (2 * (kBuckets + 1) + kSelThreads / 64 + 4 + 1 + 8) * sizeof(uint32_t) +
                        (ADAPT ? kHistBins * sizeof(uint16_t) : 0);
     static size_t lds_allowed = 48 * 1024;       // grows monotonically (one per instantiation)
     if (lds > lds_allowed) {
@@ -751,11 +924,9 @@ static int launch_select(const rk_geom* geom, const int32_t* seq_lens, int32_t m
         }
         lds_allowed = lds;
     }
-    // short rows: one workgroup per (sequence, KV head) does it all; longer ones: one per kSelTile positions
-    const int tiles = max_len > kSelSingle ? (max_len + kSelTile - 1) / kSelTile : 1;
-    dim3 sgrid(tiles, geom->n_kv_heads, geom->batch);
+    dim3 sgrid(geom->n_kv_heads, select_parts(max_len, (int64_t)geom->batch * geom->n_kv_heads), geom->batch);
     hipLaunchKernelGGL((select_kernel<ADAPT>), sgrid, dim3(kSelThreads), lds, st, ws.pooled, pooled_row_stride(max_len), seq_lens,
-                       max_len, k, ws.hist, ws.cand_cap, idx, sel_scores, pred, pred_val, ws.sel_counters, ws.cand_list);
+                       max_len, k, ws.hist, ws.cand_cap, idx, sel_scores, pred, pred_val, ws.sel_counters);
     return launch_status();
 }
 
@@ -765,7 +936,7 @@ static int launch_select_batched(const rk_geom* geom, int n_layers, const Worksp
                                  int32_t pred_val, hipStream_t st) {
     const int cand_cap = wss[0].cand_cap;
     const size_t lds = (size_t)cand_cap * sizeof(uint64_t) +
-                       (2 * (kBuckets + 1) + kSelThreads / 64 + 4 + 1) * sizeof(uint32_t) +
+                       (2 * (kBuckets + 1) + kSelThreads / 64 + 4 + 1 + 8) * sizeof(uint32_t) +
                        (ADAPT ? kHistBins * sizeof(uint16_t) : 0);
     static size_t lds_allowed = 48 * 1024;
     if (lds > lds_allowed) {
@@ -776,27 +947,20 @@ static int launch_select_batched(const rk_geom* geom, int n_layers, const Worksp
         }
         lds_allowed = lds;
     }
-    // Spreading a row over workgroups shortens one selection, but with many selections in one launch
-    // the chip is full anyway and the hand-over between a row's workgroups only costs: measured at
-    // 32k..128k rows, one workgroup per row wins from about 64 rows on (256 rows of 32k: 29 against 116 us).
-    // Rows too long for one workgroup's registers (kSelHeld positions) are the exception: there a
-    // workgroup per kSelHeld positions lists from registers what a single one would read in rounds.
     const int problems = (n_layers < kBatchLayers ? n_layers : kBatchLayers) * geom->batch * geom->n_kv_heads;
-    int tiles = 1, tile_vecs = 1;
-    if (max_len > kSelSingle && problems < kBatchSingleFrom) tiles = (max_len + kSelTile - 1) / kSelTile;
-    else if (max_len >= 2 * kSelHeld) { tile_vecs = kSelHeld / kSelTile; tiles = (max_len + kSelHeld - 1) / kSelHeld; }
+    const int parts = select_parts(max_len, problems);
     for (int l0 = 0; l0 < n_layers; l0 += kBatchLayers) {
         const int n = n_layers - l0 < kBatchLayers ? n_layers - l0 : kBatchLayers;
         SelectBatch tab{};
         for (int l = 0; l < n; ++l) {
             const Workspace& w = wss[l0 + l];
             tab.pooled[l] = w.pooled; tab.hist[l] = w.hist; tab.idx[l] = idx[l0 + l];
-            tab.sel_counters[l] = w.sel_counters; tab.cand_list[l] = w.cand_list;
+            tab.sel_counters[l] = w.sel_counters;
             tab.pred[l] = pred ? pred[l0 + l] : nullptr;
         }
-        dim3 grid(tiles, geom->n_kv_heads, n * geom->batch);
+        dim3 grid(geom->n_kv_heads, parts, n * geom->batch);
         hipLaunchKernelGGL((select_batched_kernel<ADAPT>), grid, dim3(kSelThreads), lds, st, tab, (int32_t)geom->batch,
-                           pooled_row_stride(max_len), seq_lens, max_len, k, (int32_t)cand_cap, pred_val, (int32_t)tile_vecs);
+                           pooled_row_stride(max_len), seq_lens, max_len, k, (int32_t)cand_cap, pred_val);
         const int rc = launch_status();
         if (rc != RK_OK) return rc;
     }

@@ -488,3 +488,57 @@ def test_partial_step_at_tile_edges(rk, case):
         ref = torch.matmul(torch.softmax(s, dim=-1), Vb).reshape(-1, 128)
         d = (outs[0][b].double() - ref).abs()
         assert (d <= torch.maximum(outs[0][b].double().abs(), ref.abs()) * 2.0 ** -7 + 4e-6).all(), (b, float(d.max()))
+
+
+def _select_scores(name, rows, n, g):
+    w = torch.exp(torch.randn(*rows, n, generator=g) * 1.2 - 10)
+    if name == "levels":                   # few values: stretches do not fit, the row is one workgroup's
+        w = torch.round(w * 2.0 ** 17) * 2.0 ** -17
+    elif name == "equal":
+        w = torch.full_like(w, 0.25)
+    elif name == "mostly_zero":
+        w = torch.where(torch.rand(*rows, n, generator=g) < 0.01, w, torch.zeros_like(w))
+    elif name == "one_bin":                # all scores in one bin of the histogram
+        w = 1.0 + 0.1 * torch.rand(*rows, n, generator=g)
+    elif name == "infinite":
+        w[..., 5], w[..., n // 2] = float("inf"), float("inf")
+    return w
+
+
+# (scores, B, Hkv, n, k, pool): 8 / 4 / 2 / 1 workgroups per row, fewer ranks than workgroups, fewer positions than ranks, vectors of
+# four and rounds of 32768 positions that end in the row, more than 256 runs in a stretch
+SELECT_EDGES = [("normal", 1, 1, 1, 1, 1), ("normal", 1, 2, 9, 3, 7), ("normal", 1, 3, 31, 100, 7), ("normal", 1, 8, 1027, 9, 1), ("normal", 2, 16, 4099, 300, 7),
+                ("normal", 5, 8, 5001, 700, 3), ("normal", 16, 8, 3001, 257, 7), ("normal", 33, 8, 1025, 64, 7), ("normal", 1, 8, 32771, 2048, 7),
+                ("normal", 1, 4, 65537, 8192, 1), ("normal", 1, 2, 98305, 16384, 7), ("levels", 1, 8, 20001, 3000, 1), ("levels", 3, 8, 20001, 900, 7),
+                ("equal", 1, 8, 5003, 500, 7), ("equal", 1, 4, 40001, 12000, 1), ("mostly_zero", 1, 8, 30001, 2000, 1), ("one_bin", 1, 8, 30001, 2000, 1),
+                ("one_bin", 2, 8, 9001, 1000, 7), ("infinite", 1, 8, 9001, 300, 7)]
+
+
+@pytest.mark.parametrize("case", SELECT_EDGES, ids=["%s_%dx%d_%d_k%d_w%d" % c for c in SELECT_EDGES])
+def test_selection_shared_out_by_rank(rk, case):
+    """Positions and scores exactly those of a stable sort, three calls in a row (the workspace is left clean), with rows shorter
+    than the longest whose workspace holds NaN behind them."""
+    name, B, Hkv, n, k, pool_w = case
+    say("selection by rank", *case)
+    g = torch.Generator().manual_seed(n + k)
+    w = _select_scores(name, (B, Hkv), n, g)
+    lens = [n if b == 0 else max(1, n - 7 * b) for b in range(B)]
+    geom = rk.Geom(B, Hkv, Hkv, 128, SCALE)
+    ws = rk.Workspace(geom, n, k)
+    idx = torch.empty(B, Hkv, k, dtype=torch.int32, device="cuda")
+    sel = torch.empty(B, Hkv, k, device="cuda")
+    wd, ld = w.cuda(), torch.tensor(lens, dtype=torch.int32, device="cuda")
+    full = torch.full((B,), n, dtype=torch.int32, device="cuda")
+    if B > 1:
+        rk.rk_topk_select(geom, torch.full_like(wd, float("nan")), full, n, k, pool_w, idx, workspace=ws)
+    for _ in range(3):
+        idx.fill_(-7)
+        rk.rk_topk_select(geom, wd, ld, n, k, pool_w, idx, sel_scores=sel, workspace=ws)
+        torch.cuda.synchronize()
+        for b, m in enumerate(lens):
+            P = torch.nn.functional.max_pool1d(w[b, :, :m], pool_w, stride=1, padding=pool_w // 2)
+            v, i = torch.sort(P, dim=-1, descending=True, stable=True)
+            kk = min(k, m)
+            assert torch.equal(idx[b, :, :kk].cpu().long(), i[:, :kk]), (name, b)
+            assert torch.equal(sel[b, :, :kk].cpu(), v[:, :kk]), (name, b)
+            assert (idx[b, :, kk:] == -1).all() and (sel[b, :, kk:] == 0).all()

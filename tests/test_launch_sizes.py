@@ -41,6 +41,7 @@ int main() {
             const TileForm f = partial_tile_form(r, tail, p, G);
             printf("tile %ld %ld %d %d %d %d %d\n", r, p, tail, G, f.waves, f.nch, f.tail);
         }
+    for (long p : {1L, 4L, 8L, 12L, 32L, 33L, 64L, 65L, 128L, 129L, 256L, 257L, 100000L}) printf("parts %ld %d\n", p, select_parts(32768, p));
     const long lens[] = {1, 2000, 32768, 33008, 65536, 131072, 1000000};
     for (long l : lens) for (int b : {1, 2, 16}) for (int hkv : {1, 4, 8}) {
         rk_geom g{b, hkv * 4, hkv, 128, 1.0f};
@@ -179,6 +180,12 @@ def test_partial_tile_form_bounds_and_measured_choices(table):
     assert got[(8192, 8, 1, 4)][0] == 0 and got[(1024, 128, 1, 4)][0] == 0            # 33 MB and more in many partial results
     assert got[(2048, 32, 1, 4)] == (8, 16, 1) and got[(1024, 64, 1, 4)] == (8, 8, 1) and got[(1024, 64, 1, 5)][0] == 0
     assert got[(0, 8, 500, 4)] == (4, 0, 8) and got[(2048, 8, 100000, 4)][0] == 0
+
+
+def test_selection_parts_are_resident_at_once(table):
+    got = {int(v[0]): int(v[1]) for kind, *v in table if kind == "parts"}
+    for rows, parts in got.items():
+        assert parts in (1, 2, 4, 8) and (parts == 1 or rows * parts <= 256) and (parts == 8 or rows * parts > 128), (rows, parts)
 
 
 @pytest.fixture(scope="module")
