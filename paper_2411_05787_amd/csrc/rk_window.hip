@@ -7,8 +7,8 @@
 // then the selection of rk_topk_select runs on the votes.
 //
 // Only K is read, twice:
-//   pass 1  window_lse_kernel     log-sum-exp of every (query, head) column, split over
-//                                 workgroups like the decode kernels; window_lse_merge_kernel
+//   pass 1  window_lse_kernel     maximum and sum of every (query, head) column, split over
+//                                 workgroups like the decode kernels; pass 2, or window_lse_merge_kernel,
 //                                 folds the partial (max, sum) pairs
 //   pass 2  window_vote_kernel    the same stream again: normalised scores, summed over the
 //                                 window's queries on the lanes, stored once per (head, row)
@@ -36,9 +36,9 @@ struct WindowParams {
     int32_t W, G, gp_shift;            // Gp = 1 << gp_shift
     int32_t ncb;                       // blocks of 16 columns
     int32_t nch, wg_rows, Hq, Hkv;     // workgroups per (sequence, KV head); rows a workgroup takes per step
-    float scale;
+    float scale2;                      // scale x log2 e: scores, maxima and exponents are to base 2
     float* part;                       // fp32 [B*Hkv][nch][ncb*16][2]  (max, sum) per workgroup and column
-    float* lse;                        // fp32 [B*Hkv][ncb*16][2]       lse as hi + lo
+    float* lse;                        // fp32 [B*Hkv][ncb*16][2]       maximum and 1 / sum of every column (0, 0: nobody votes in it)
     float* votes; int64_t v_stride; int32_t v_vec;
     const int32_t* pred; int32_t pred_val;
 };
@@ -96,10 +96,10 @@ __device__ __forceinline__ void load_k_rows(u32x4 (&dst)[T][4], const uint16_t* 
 }
 
 // Scores of these rows against the 16 columns of block cb: s[t][i] is row r + 16 t + 4 c4 + i of
-// column cb * 16 + n16, scaled; MASKED: -inf beyond `limit`.
-template <bool MASKED, int T>
+// column cb * 16 + n16, as `scaled` makes it of the product; MASKED: -inf beyond `limit`.
+template <bool MASKED, int T, class Scaled>
 __device__ __forceinline__ void block_scores(const u32x4 (&k)[T][4], const uint16_t* sQ, int cb, int n16, int c4,
-                                             int r, int limit, float scale, float (&s)[T][4]) {
+                                             int r, int limit, float (&s)[T][4], Scaled&& scaled) {
     bf16x8 qa[4];
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk)
@@ -112,15 +112,15 @@ __device__ __forceinline__ void block_scores(const u32x4 (&k)[T][4], const uint1
             acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, k[t][kk]), qa[kk], acc, 0, 0, 0);
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-            s[t][i] = (!MASKED || r + t * 16 + 4 * c4 + i <= limit) ? acc[i] * scale : -INFINITY;
+            s[t][i] = (!MASKED || r + t * 16 + 4 * c4 + i <= limit) ? scaled(acc[i]) : -INFINITY;
     }
 }
 
 // (m, l) <- (m, l) merged with (m2, l2): running max and sum of exponentials relative to it.
 __device__ __forceinline__ void merge_ml(float& m, float& l, float m2, float l2) {
     const float M = fmaxf(m, m2);
-    const float a = (m == -INFINITY) ? 0.f : fast_exp2((m - M) * kLog2e);
-    const float c = (m2 == -INFINITY) ? 0.f : fast_exp2((m2 - M) * kLog2e);
+    const float a = (m == -INFINITY) ? 0.f : fast_exp2(m - M);
+    const float c = (m2 == -INFINITY) ? 0.f : fast_exp2(m2 - M);
     l = l * a + l2 * c;
     m = M;
 }
@@ -153,7 +153,8 @@ __device__ __forceinline__ void lse_rows(const WindowParams& p, const u32x4 (&k)
 #pragma unroll 1
     for (int cb = 0; cb < p.ncb; ++cb) {
         float s[T][4];
-        block_scores<MASKED, T>(k, sQ, cb, n16, c4, r, MASKED ? column_limit(p, cb * 16 + n16, n) : 0, p.scale, s);
+        block_scores<MASKED, T>(k, sQ, cb, n16, c4, r, MASKED ? column_limit(p, cb * 16 + n16, n) : 0, s,
+                                [&](float x) { return x * p.scale2; });
         float mx = s[0][0];
 #pragma unroll
         for (int e = 1; e < 4 * T; ++e) mx = fmaxf(mx, s[e >> 2][e & 3]);
@@ -162,8 +163,8 @@ __device__ __forceinline__ void lse_rows(const WindowParams& p, const u32x4 (&k)
         const float ref = m_new == -INFINITY ? 0.f : m_new;      // nothing seen yet: every term is 2^-inf = 0
         float ps = 0.f;
 #pragma unroll
-        for (int e = 0; e < 4 * T; ++e) ps += fast_exp2((s[e >> 2][e & 3] - ref) * kLog2e);
-        sRun[cb * NT + threadIdx.x] = make_float2(m_new, run.y * fast_exp2((run.x - ref) * kLog2e) + ps);
+        for (int e = 0; e < 4 * T; ++e) ps += fast_exp2(s[e >> 2][e & 3] - ref);
+        sRun[cb * NT + threadIdx.x] = make_float2(m_new, run.y * fast_exp2(run.x - ref) + ps);
     }
 }
 
@@ -211,7 +212,7 @@ void window_lse_kernel(const WindowParams p) {
     for (int cb = 0; cb < ncb; ++cb) {
         const float2 run = r0 < n ? sRun[cb * NW * 64 + tid] : make_float2(-INFINITY, 0.f);
         const float M = max_xor32(max_xor16(run.x));
-        const float a = run.x == -INFINITY ? 0.f : fast_exp2((run.x - M) * kLog2e);
+        const float a = run.x == -INFINITY ? 0.f : fast_exp2(run.x - M);
         const float L = sum_xor32(sum_xor16(run.y * a));
         if (c4 == 0) { sM[w * ncol + cb * 16 + n16] = M; sL[w * ncol + cb * 16 + n16] = L; }
     }
@@ -226,10 +227,18 @@ void window_lse_kernel(const WindowParams p) {
     }
 }
 
-// lse of every column from the per-workgroup pairs: one workgroup per (block of 16 columns,
+// What a column's scores are normalised with: vote = 2^(s - maximum) / sum.  With lse = maximum + ln sum as two floats and
+// e^(s - lse) an exponent took two subtractions and two products instead of one multiply-add, and twice the error against 64
+// bits (32768 rows, 32 queries: 1.7e-7 -> 8.0e-8).  Whole call, us: 32768 rows, 32 queries 61.2 -> 60.2, 28 heads over 4, 30000 rows
+// 73.1 -> 70.7, 64 over 8, 20000 rows 87.5 -> 84.6, 8 sequences of 2000 rows 48.1 -> 46.5.
+__device__ __forceinline__ float2 column_norm(const WindowParams& p, int col, int n, float M, double L) {
+    // (a column that does not exist was summed like the others; one without a finite score has no sum)
+    return (M != -INFINITY && column_limit(p, col, n) >= 0) ? make_float2(M, (float)(1.0 / L)) : make_float2(0.f, 0.f);
+}
+
+// Maximum and 1 / sum of every column from the per-workgroup pairs: one workgroup per (block of 16 columns,
 // sequence, KV head); thread (n16, cl) folds the pairs of column n16 from workgroups cl, cl + 16,
-// ...; thread (n16, 0) folds the 16 results.  Stored as hi + lo (two floats) so that scores
-// normalised with it keep full fp32 precision.
+// ...; thread (n16, 0) folds the 16 results, the sum in fp64.
 __global__ __launch_bounds__(256)
 void window_lse_merge_kernel(const WindowParams p) {
     const int cb = blockIdx.x, g = blockIdx.y, b = blockIdx.z;
@@ -263,13 +272,8 @@ void window_lse_merge_kernel(const WindowParams p) {
         double L = 0.0;
 #pragma unroll
         for (int x = 0; x < 16; ++x)
-            if (sM[x][n16] != -INFINITY) L += (double)fast_exp2((sM[x][n16] - M) * kLog2e) * (double)sL[x][n16];
-        float hi = INFINITY, lo = 0.f;                     // a column nobody votes in: e^{s - inf} = 0
-        if (M != -INFINITY && column_limit(p, col, n) >= 0) {      // (a column that does not exist was summed like the others)
-            const double lse = (double)M + log(L);
-            hi = (float)lse; lo = (float)(lse - (double)hi);
-        }
-        *reinterpret_cast<float2*>(p.lse + (bg * ncol + col) * 2) = make_float2(hi, lo);
+            if (sM[x][n16] != -INFINITY) L += (double)fast_exp2(sM[x][n16] - M) * (double)sL[x][n16];
+        *reinterpret_cast<float2*>(p.lse + (bg * ncol + col) * 2) = column_norm(p, col, n, M, L);
     }
 }
 
@@ -293,11 +297,12 @@ __device__ __forceinline__ void vote_rows(const WindowParams& p, const u32x4 (&k
     auto block = [&](auto masked, int cb) {
         constexpr bool kMasked = decltype(masked)::value;
         float s[T][4];
-        block_scores<kMasked, T>(k, sQ, cb, n16, c4, r, kMasked ? column_limit(p, cb * 16 + n16, n) : 0, p.scale, s);
-        const float2 lse = sLse[cb * 16 + n16];
+        const float2 norm = sLse[cb * 16 + n16];
+        block_scores<kMasked, T>(k, sQ, cb, n16, c4, r, kMasked ? column_limit(p, cb * 16 + n16, n) : 0, s,
+                                 [&](float x) { return fmaf(x, p.scale2, -norm.x); });
 #pragma unroll
-        for (int e = 0; e < 4 * T; ++e)            // s = -inf (masked) and lse = inf (no such column) give 2^-inf = 0
-            v[e >> 2][e & 3] += fast_exp2(((s[e >> 2][e & 3] - lse.x) - lse.y) * kLog2e);
+        for (int e = 0; e < 4 * T; ++e)            // (masked: 2^-inf = 0; no such column: times 0)
+            v[e >> 2][e & 3] = fmaf(fast_exp2(s[e >> 2][e & 3]), norm.y, v[e >> 2][e & 3]);
     };
     // A last block that the queries do not fill has columns which are added to real ones below; their zero queries' scores
     // are NaN where a key is infinite, so that block is masked also where every query sees every row.
@@ -324,7 +329,12 @@ __device__ __forceinline__ void vote_rows(const WindowParams& p, const u32x4 (&k
     }
 }
 
-template <int T, int S, int NW>
+// FOLD: the (max, sum) pairs of pass 1 are folded here, up to kFoldHeld per thread, while the rows are on their way; where there
+// are more (or the columns are no power of two) by window_lse_merge_kernel, a launch of 4.6 us between the passes.  Whole
+// call with that launch / folded here, us, 32 heads over 8: 1100 rows, 32 queries 28.6 / 26.8; 3000 rows 33.2 / 31.2; 8 sequences of
+// 2000 rows 46.5 / 44.7; 32768 rows, 8 queries 49.8 / 48.6, 32 queries 60.2 / 59.5 (every workgroup reads 64 KB of pairs there).
+constexpr int kFoldHeld = 16;
+template <int T, int S, int NW, bool FOLD>
 __global__ __launch_bounds__(NW * 64, 4)
 void window_vote_kernel(const WindowParams p) {
     const int ncol = p.ncb * 16;
@@ -343,15 +353,49 @@ void window_vote_kernel(const WindowParams p) {
     uint4 held[kQHeld];
     u32x4 k[S][T][4];
     const float2* lse_of = reinterpret_cast<const float2*>(p.lse) + bg * ncol;
-    const float2 my_lse = tid < ncol ? lse_of[tid] : make_float2(0.f, 0.f);
+    const float2 my_lse = !FOLD && tid < ncol ? lse_of[tid] : make_float2(0.f, 0.f);
     static_assert(NW * 64 >= 32 * RK_MAX_GROUP, "a thread per column");
     request_queries<NW * 64>(p, b, g, n, held);
+    // column tid mod ncol (ncol is a power of two where FOLD is used), every groups-th workgroup's pair from tid / ncol on
+    const int fold_col = tid & (ncol - 1), fold_lg = 31 - __builtin_clz(ncol), groups = NW * 64 >> fold_lg, fold_g = tid >> fold_lg;
+    const int nchunks = window_workgroups(p, n);
+    float2 pairs[kFoldHeld];
+    if constexpr (FOLD) {
+        const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(p.part + bg * p.nch * ncol * 2, 0, nchunks * ncol * 8, 0x00020000);
+#pragma unroll
+        for (int u = 0; u < kFoldHeld; ++u)       // (behind the last workgroup's: zeros, a sum of nothing)
+            pairs[u] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rp, ((fold_g + u * groups) * ncol + fold_col) * 8, 0, 0));
+    }
 #pragma unroll
     for (int x = 0; x < S; ++x)
         if (r0 + x * step < n) load_k_rows<T>(k[x], kb, r0 + x * step, n16, n);
     store_queries<NW * 64>(p, b, g, n, ncol, held, sQ);
-    if (tid < ncol) sLse[tid] = my_lse;
-    __syncthreads();
+    if constexpr (FOLD) {
+        float2* sMl = sLse + ncol;                // [NW * 64]
+        double* sSum = reinterpret_cast<double*>(sMl);
+        float M = -INFINITY;
+#pragma unroll
+        for (int u = 0; u < kFoldHeld; ++u) M = fmaxf(M, pairs[u].y != 0.f ? pairs[u].x : -INFINITY);
+        double L = 0.0;
+#pragma unroll
+        for (int u = 0; u < kFoldHeld; ++u)
+            if (pairs[u].y != 0.f && pairs[u].x != -INFINITY) L += (double)fast_exp2(pairs[u].x - M) * (double)pairs[u].y;
+        float* sM = reinterpret_cast<float*>(sSum + NW * 64);
+        sSum[tid] = L; sM[tid] = M;
+        lds_barrier();
+        if (tid < ncol) {
+            float all = -INFINITY;
+            for (int x = 0; x < groups; ++x) all = fmaxf(all, sM[x * ncol + tid]);
+            double sum = 0.0;
+            for (int x = 0; x < groups; ++x)
+                if (sM[x * ncol + tid] != -INFINITY) sum += (double)fast_exp2(sM[x * ncol + tid] - all) * sSum[x * ncol + tid];
+            sLse[tid] = column_norm(p, tid, n, all, sum);
+        }
+        lds_barrier();
+    } else {
+        if (tid < ncol) sLse[tid] = my_lse;
+        __syncthreads();
+    }
     float* vrow = p.votes + ((int64_t)b * p.Hq + (int64_t)g * p.G + (n16 < p.G ? n16 : 0)) * p.v_stride;
     auto rows = [&](const u32x4 (&x)[T][4], int r) {
         if (r + 16 * T > n - p.W) vote_rows<true, T>(p, x, sQ, sLse, vrow, r, n);
@@ -372,25 +416,33 @@ template <int T, int S, int NW>
 static int launch_window(const WindowParams& p, int batch, hipStream_t st) {
     const size_t ncol = (size_t)p.ncb * 16;
     const size_t lds1 = ncol * kQStride * 2 + (size_t)p.ncb * NW * 64 * sizeof(float2);
-    const size_t lds2 = ncol * kQStride * 2 + ncol * sizeof(float2);
-    static size_t lds_allowed = 48 * 1024;       // grows monotonically; lds1 > lds2
-    if (lds1 > lds_allowed) {
+    const bool fold = (ncol & (ncol - 1)) == 0 && ncol <= (size_t)NW * 64 && (size_t)p.nch * ncol <= (size_t)kFoldHeld * NW * 64;
+    const size_t lds2 = ncol * kQStride * 2 + ncol * sizeof(float2) + (fold ? NW * 64 * (sizeof(double) + sizeof(float)) : 0);
+    const size_t lds = lds1 > lds2 ? lds1 : lds2;
+    static size_t lds_allowed = 48 * 1024;       // grows monotonically
+    if (lds > lds_allowed) {
         if (hipFuncSetAttribute(reinterpret_cast<const void*>(&window_lse_kernel<T, S, NW>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds1) != hipSuccess ||
-            hipFuncSetAttribute(reinterpret_cast<const void*>(&window_vote_kernel<T, S, NW>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds1) != hipSuccess) {
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
+            hipFuncSetAttribute(reinterpret_cast<const void*>(&window_vote_kernel<T, S, NW, true>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
+            hipFuncSetAttribute(reinterpret_cast<const void*>(&window_vote_kernel<T, S, NW, false>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
             (void)hipGetLastError();
             return RK_ERR_UNSUPPORTED;
         }
-        lds_allowed = lds1;
+        lds_allowed = lds;
     }
     dim3 grid(p.nch, p.Hkv, batch);
     hipLaunchKernelGGL((window_lse_kernel<T, S, NW>), grid, dim3(NW * 64), lds1, st, p);
     int rc = launch_status();
     if (rc != RK_OK) return rc;
+    if (fold) {
+        hipLaunchKernelGGL((window_vote_kernel<T, S, NW, true>), grid, dim3(NW * 64), lds2, st, p);
+        return launch_status();
+    }
     hipLaunchKernelGGL(window_lse_merge_kernel, dim3(p.ncb, p.Hkv, batch), dim3(256), 0, st, p);
     if ((rc = launch_status()) != RK_OK) return rc;
-    hipLaunchKernelGGL((window_vote_kernel<T, S, NW>), grid, dim3(NW * 64), lds2, st, p);
+    hipLaunchKernelGGL((window_vote_kernel<T, S, NW, false>), grid, dim3(NW * 64), lds2, st, p);
     return launch_status();
 }
 
@@ -434,7 +486,7 @@ extern "C" int rk_window_select(const rk_geom* geom, const void* q_win, int32_t 
     const WindowForm form = window_form(max_len, (int64_t)geom->batch * geom->n_kv_heads, ncb, ws.max_chunks);
     p.wg_rows = form.wg_rows; p.nch = form.nch;
     p.Hq = geom->n_q_heads; p.Hkv = geom->n_kv_heads;
-    p.scale = geom->scale;
+    p.scale2 = (float)((double)geom->scale * 1.4426950408889634);
     p.part = ws.part_o; p.lse = ws.part_ml;
     if (votes) { p.votes = votes; p.v_stride = v_stride; }
     else       { p.votes = ws.scores; p.v_stride = pooled_row_stride(max_len); }

@@ -75,6 +75,17 @@ def test_window_select_at_tile_edges(rk, case):
             assert_idx_equivalent(idx[b, g].cpu().numpy(), i_ref[b, g], P, n, k, "%s b=%d g=%d" % (name, b, g))
 
 
+# The (max, sum) pairs of pass 1 folded in pass 2 (16 per thread: one workgroup's, 64 workgroups' of 128 columns, 256 workgroups'
+# of 16) and by the launch between the passes (65 workgroups, 80 columns).
+WINDOW_FOLDS = [("one_row", 1, 8, 2, [1], 3, SCALE), ("128_columns_64_wgs", 1, 4, 1, [8192], 32, SCALE), ("128_columns_65_wgs", 1, 4, 1, [8193], 32, SCALE),
+                ("16_columns", 2, 4, 1, [32768, 129], 4, SCALE), ("80_columns", 2, 8, 2, [3000, 60], 20, SCALE)]
+
+
+@pytest.mark.parametrize("case", WINDOW_FOLDS, ids=[c[0] for c in WINDOW_FOLDS])
+def test_window_select_folds_pass_1(rk, case):
+    test_window_select_at_tile_edges(rk, case)
+
+
 @pytest.mark.parametrize("shape", [(4, 1, 2, 700), (1, 3, 2, 700), (4, 5, 8, 9000), (4, 13, 8, 9000), (4, 13, 8, 32000), (2, 1, 8, 33000), (3, 7, 8, 33000)],
                          ids=lambda s: "g%d_w%d_h%d_n%d" % s)
 def test_window_select_with_infinite_keys(rk, shape):
