@@ -443,11 +443,7 @@ def run_workload(args, workload, light):
     partial_bytes = 2 * Hkv * D * 2 * (sel_rows + recent_rows)
     partial_us = graph_us(partial_call, reps=8)
     p_traffic, p_source = profile_traffic(w.name, "partial_attn")
-    # which hand-over the library picks for this shape: tagged partial results (merged by slices) for launches over few
-    # (sequence, KV head) pairs and for groups of up to 4 heads; ticketed for larger groups in launches over many pairs
-    pairs = B * Hkv
-    tagged = pairs <= 16 or w.group <= 4
-    roofline_partial = {"bound": "hbm", "kernel": "rk::attn_split_kernel<%d, 4, false, true, false, %s, false, false> (rk_partial_attn)" % (w.group, "true" if tagged else "false"),
+    roofline_partial = {"bound": "hbm", "kernel": "rk::partial_tile_kernel<%d, *, false>, or rk::attn_split_kernel<%d, 4, false, true, ...> over longer or more small caches (rk_partial_attn)" % (w.group, w.group),
                         "achieved": round(partial_bytes / (partial_us * 1e-6) / 1e9, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                         "frac": round(partial_bytes / (partial_us * 1e-6) / 1e9 / HBM_PEAK_GBPS, 4),
                         "traffic": p_traffic, "traffic_source": p_source, "avg_launch_us": round(partial_us, 2),
