@@ -227,6 +227,25 @@ static inline int select_parts(int64_t max_len, int64_t rows) {
     return (int)parts;
 }
 
+// ---- stretches of scores that the parts of a row's selection take (select_part, rk_topk.hip) ----
+// Scores >= 0 as whole numbers (their bits), the first-level histogram's bins of 2^kHistShift of them.  The stretch of part i
+// is [B(i + 1), B(i)): B leaves t = i / parts of the K' ranks above it, as the histogram has it and, inside the bin that holds rank t,
+// as if its scores were spread evenly: `at`; `end` is where that bin ends and `above` the positions beyond.
+struct StretchBound { uint32_t at, end, above; };
+// `bin` (of images; scores >= 0 start at bin 1024) holds rank t: `above` positions in higher bins, `h` in this one, above < t <= above + h.
+__host__ __device__ static inline StretchBound stretch_bound(uint32_t t, uint32_t spare, uint32_t bin, uint32_t above, uint32_t h) {
+    const uint32_t width = 1u << kHistShift, end = ((bin + 1u) << kHistShift) - 0x80000000u;
+    if (t - above == h) return {end - width, end - width, t};      // the whole bin: nothing to count
+    const float down = (float)(t + spare - above) * ((float)width / (float)h);
+    return {end - (down < (float)width ? (uint32_t)down : width), end, above};
+}
+// The lower end that a part starts with.  The last part's is an estimate, `floor` (the K'-th score's bin) what it may have to go down to;
+// in a bin of tens of millions of positions that estimate can fall on the part's own upper end `top`, and an empty
+// stretch would be taken for one without candidates: all of the bin then.
+__host__ __device__ static inline uint32_t stretch_low(uint32_t estimate, uint32_t floor, uint32_t top) {
+    return estimate <= floor || estimate >= top ? floor : estimate;
+}
+
 // Device workspace, carved in this order (every region 256-byte aligned).  The regions up to and
 // including tag_rows must be zero when a workspace is first used (rk_workspace_init clears the
 // whole workspace once); the counters and histograms are left cleared by the kernels that use

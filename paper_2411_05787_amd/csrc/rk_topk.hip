@@ -428,26 +428,20 @@ __device__ __forceinline__ bool select_part(const SelectRow& row, const SelectLd
             if (tid == kNonFinite) sPart[4] = incl;
             const uint32_t t0 = (kk1 * (uint32_t)part) >> lg_parts, t1 = (kk1 * (uint32_t)(part + 1)) >> lg_parts;
             const uint32_t spare = part + 1 == 1 << lg_parts ? (kk1 * 3u >> 3) + 16u : 0u;        // the last part: that many ranks more
-            auto bound = [&](uint32_t t, uint32_t spare, uint32_t& at, uint32_t& end, uint32_t& a) {
+            auto bound = [&](uint32_t t, uint32_t spare) {
                 const bool upper = abv + h1 >= t;
-                const uint32_t h = upper ? h1 : h0, width = 1u << kHistShift;
-                a = upper ? abv : abv + h1;
-                end = ((uint32_t)(2 * rt + (upper ? 1 : 0) + 1) << kHistShift) - 0x80000000u;
-                at = end - min((uint32_t)((float)(t + spare - a) * ((float)width / (float)h)), width);
-                if (t - a == h) { at = end = end - width; a = t; }       // the whole bin: nothing to count
+                return stretch_bound(t, spare, (uint32_t)(2 * rt + (upper ? 1 : 0)), upper ? abv : abv + h1, upper ? h1 : h0);
             };
-            uint32_t at, end, a;
             if (t0 == 0) {                  // (the top, or fewer ranks than parts)
                 if (tid == 0) { sPart[0] = sPart[1] = 0x80000000u; sPart[2] = 0; }
             } else if (abv < t0 && t0 <= incl) {
-                bound(t0, 0u, at, end, a);
-                sPart[0] = at; sPart[1] = end; sPart[2] = a;
+                const StretchBound b = bound(t0, 0u);
+                sPart[0] = b.at; sPart[1] = b.end; sPart[2] = b.above;
             }
             if (t1 == 0) {
                 if (tid == 0) sPart[3] = 0x80000000u;
             } else if (abv < t1 && t1 <= incl) {
-                bound(t1, spare, at, end, a);
-                sPart[3] = at;
+                sPart[3] = bound(t1, spare).at;
             }
         }
         lds_barrier();
@@ -461,7 +455,7 @@ __device__ __forceinline__ bool select_part(const SelectRow& row, const SelectLd
     // 101.3 us.  The second look at the row costs 4 - 8 us: with 3/16 of the ranks to spare instead of 3/8 that step takes 110, a window
     // of 32 queries over 32768 positions 70.9 instead of 67.7.)
     const uint32_t hi = sPart[0], end = sPart[1], floor = part + 1 < (1 << lg_parts) ? sPart[3] : (b1 << kHistShift) - 0x80000000u;
-    uint32_t lo = max(sPart[3], floor), top = hi, top_end = end;       // the stretch so far, and what is looked for in this pass over the row
+    uint32_t lo = stretch_low(sPart[3], floor, hi), top = hi, top_end = end;       // the stretch so far, and what is looked for in this pass over the row
     bool bad = b1 < (uint32_t)kHistBins / 2 || sPart[4] != 0;
     while (!bad && lo < top) {
         // Bits of scores as whole numbers, from the stretch's lowest.  A vector of four positions with none in the stretch or

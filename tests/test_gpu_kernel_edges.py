@@ -553,3 +553,25 @@ def test_selection_shared_out_by_rank(rk, case):
             assert torch.equal(idx[b, :, :kk].cpu().long(), i[:, :kk]), (name, b)
             assert torch.equal(sel[b, :, :kk].cpu(), v[:, :kk]), (name, b)
             assert (idx[b, :, kk:] == -1).all() and (sel[b, :, kk:] == 0).all()
+
+
+@pytest.mark.parametrize("n,k", [(60_000_001, 5), (100_000_000, 50)], ids=["60m_k5", "100m_k50"])
+def test_selection_of_few_among_tens_of_millions_in_one_bin(rk, n, k):
+    """So many positions in the bin of the K-th score that the last part's estimate leaves it no stretch: every rank is written."""
+    say("selection, few ranks of one huge bin", n, k)
+    w = torch.ones(1, 1, n, device="cuda")
+    g = torch.Generator(device="cuda").manual_seed(k)
+    at = torch.randperm(n, generator=g, device="cuda")[:k - 2]
+    w[0, 0, at] = 1.0 + torch.arange(1, k - 1, device="cuda") * 2.0 ** -10       # ... and two ranks among the equal ones
+    geom = rk.Geom(1, 1, 1, 128, SCALE)
+    ws = rk.Workspace(geom, n, k)
+    lens = torch.tensor([n], dtype=torch.int32, device="cuda")
+    idx = torch.full((1, 1, k), -7, dtype=torch.int32, device="cuda")
+    sel = torch.full((1, 1, k), -7.0, device="cuda")
+    for _ in range(2):
+        rk.rk_topk_select(geom, w, lens, n, k, 1, idx, sel_scores=sel, workspace=ws)
+    torch.cuda.synchronize()
+    taken = set(at.tolist())
+    rest = [j for j in range(k + 2) if j not in taken][:2]
+    assert idx[0, 0].tolist() == at.flip(0).tolist() + rest
+    assert torch.equal(sel[0, 0], w[0, 0, idx[0, 0].long()])

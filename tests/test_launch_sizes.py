@@ -42,6 +42,29 @@ int main() {
             printf("tile %ld %ld %d %d %d %d %d\n", r, p, tail, G, f.waves, f.nch, f.tail);
         }
     for (long p : {1L, 4L, 8L, 12L, 32L, 33L, 64L, 65L, 128L, 129L, 256L, 257L, 100000L}) printf("parts %ld %d\n", p, select_parts(32768, p));
+    // the parts of a row whose K' ranks end in a bin of h positions, `above` of the ranks in higher bins: stretches from the top
+    // down to where the last part starts, or may have to go down to
+    for (long h : {1L, 2L, 3L, 7L, 8L, 100L, 5000L, 100000L, 1L << 21, 20000000L, 40000000L, 60000000L, 100000000L, 1L << 28}) for (int lg : {1, 2, 3}) {
+        long open = 0, order = 0, empty = 0;
+        for (uint32_t above : {0u, 1u, 13u, 4096u}) for (uint32_t k = above + 1; k <= above + h && k <= 16384; k += k < above + 300 ? 1 : 97) {
+            const uint32_t bin = 1500, floor = (bin << kHistShift) - 0x80000000u;
+            uint32_t upper = floor + (1u << kHistShift);          // where the bins above end
+            for (int part = 0; part < 1 << lg; ++part) {
+                const uint32_t t0 = (k * (uint32_t)part) >> lg, t1 = (k * (uint32_t)(part + 1)) >> lg;
+                const bool last = part + 1 == 1 << lg;
+                const uint32_t top = t0 > above ? stretch_bound(t0, 0, bin, above, (uint32_t)h).at : upper;
+                order += top != upper;                            // the stretch above ended there
+                if (t1 <= above) continue;
+                const uint32_t at = stretch_bound(t1, last ? (k * 3u >> 3) + 16u : 0u, bin, above, (uint32_t)h).at;
+                order += at > top || at < floor;
+                const uint32_t low = stretch_low(at, last ? floor : at, top);
+                open += last && low >= top && low != floor;       // ranks between the stretch and the floor that nobody takes
+                empty += last && at >= top && at > floor;
+                upper = at;
+            }
+        }
+        printf("stretch %ld %d %ld %ld %ld\n", h, lg, open, order, empty);
+    }
     const long lens[] = {1, 2000, 32768, 33008, 65536, 131072, 1000000};
     for (long l : lens) for (int b : {1, 2, 16}) for (int hkv : {1, 4, 8}) {
         rk_geom g{b, hkv * 4, hkv, 128, 1.0f};
@@ -186,6 +209,16 @@ def test_selection_parts_are_resident_at_once(table):
     got = {int(v[0]): int(v[1]) for kind, *v in table if kind == "parts"}
     for rows, parts in got.items():
         assert parts in (1, 2, 4, 8) and (parts == 1 or rows * parts <= 256) and (parts == 8 or rows * parts > 128), (rows, parts)
+
+
+def test_selection_stretches_leave_no_rank_out(table):
+    """Every part's stretch ends where the next one's starts, and the last part looks at its bin down to the floor wherever its
+    estimate leaves it nothing (bins of tens of millions of positions, few ranks): no rank stays unwritten."""
+    seen = {(int(v[0]), int(v[1])): tuple(map(int, v[2:])) for kind, *v in table if kind == "stretch"}
+    assert len(seen) == 42
+    for key, (unwritten, order, empty) in seen.items():
+        assert unwritten == 0 and order == 0, key
+    assert seen[(1 << 28, 3)][2] > 100 and seen[(40000000, 3)][2] > 0 and seen[(20000000, 3)][2] == 0      # the case does come up
 
 
 @pytest.fixture(scope="module")
