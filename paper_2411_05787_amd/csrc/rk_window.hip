@@ -22,6 +22,8 @@
 // keeps the same head in every block of 16 columns and the sum over the window is a per-lane
 // sum over blocks plus log2(16 / Gp) cross-lane steps.
 #include "rk_internal.h"
+#include <cfloat>
+#include <cmath>
 #include <type_traits>
 #include "rk_device.h"
 
@@ -36,7 +38,8 @@ struct WindowParams {
     int32_t W, G, gp_shift;            // Gp = 1 << gp_shift
     int32_t ncb;                       // blocks of 16 columns
     int32_t nch, wg_rows, Hq, Hkv;     // workgroups per (sequence, KV head); rows a workgroup takes per step
-    float scale2;                      // scale x log2 e: scores, maxima and exponents are to base 2
+    float scale2;                      // |scale| x log2 e, not 0: scores, maxima and exponents are to base 2
+    uint32_t q_sign;                   // 0x80008000 where the scale is negative: the queries take its sign
     float* part;                       // fp32 [B*Hkv][nch][ncb*16][2]  (max, sum) per workgroup and column
     float* lse;                        // fp32 [B*Hkv][ncb*16][2]       maximum and 1 / sum of every column (0, 0: nobody votes in it)
     float* votes; int64_t v_stride; int32_t v_vec;
@@ -76,7 +79,9 @@ __device__ __forceinline__ void request_queries(const WindowParams& p, int b, in
 template <int NT>
 __device__ __forceinline__ void store_queries(const WindowParams& p, int b, int g, int n, int ncol, const uint4 (&held)[kQHeld],
                                               uint16_t* sQ) {
-    auto put = [&](int x, const uint4 u) { *reinterpret_cast<uint4*>(sQ + (x >> 4) * kQStride + (x & 15) * 8) = u; };
+    auto put = [&](int x, const uint4 u) {
+        *reinterpret_cast<uint4*>(sQ + (x >> 4) * kQStride + (x & 15) * 8) = make_uint4(u.x ^ p.q_sign, u.y ^ p.q_sign, u.z ^ p.q_sign, u.w ^ p.q_sign);
+    };
 #pragma unroll
     for (int u = 0; u < kQHeld; ++u)
         if (u * NT + (int)threadIdx.x < ncol * 16) put(u * NT + threadIdx.x, held[u]);
@@ -95,11 +100,13 @@ __device__ __forceinline__ void load_k_rows(u32x4 (&dst)[T][4], const uint16_t* 
     }
 }
 
-// Scores of these rows against the 16 columns of block cb: s[t][i] is row r + 16 t + 4 c4 + i of
-// column cb * 16 + n16, as `scaled` makes it of the product; MASKED: -inf beyond `limit`.
-template <bool MASKED, int T, class Scaled>
-__device__ __forceinline__ void block_scores(const u32x4 (&k)[T][4], const uint16_t* sQ, int cb, int n16, int c4,
-                                             int r, int limit, float (&s)[T][4], Scaled&& scaled) {
+// Products of these rows with the 16 columns of block cb: x[t][i] is row r + 16 t + 4 c4 + i of
+// column cb * 16 + n16; MASKED: -inf beyond `limit`.  Scores are scale2 times that, and both passes take them
+// relative to a maximum M in one rounding, 2^fma(x, scale2, -M): were they rounded before the subtraction in one of the passes and not in the
+// other, a column's votes would carry the rounding of its largest score (1.4e-5 at scores of 400).
+template <bool MASKED, int T>
+__device__ __forceinline__ void block_products(const u32x4 (&k)[T][4], const uint16_t* sQ, int cb, int n16, int c4,
+                                               int r, int limit, float (&x)[T][4]) {
     bf16x8 qa[4];
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk)
@@ -112,7 +119,7 @@ __device__ __forceinline__ void block_scores(const u32x4 (&k)[T][4], const uint1
             acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, k[t][kk]), qa[kk], acc, 0, 0, 0);
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-            s[t][i] = (!MASKED || r + t * 16 + 4 * c4 + i <= limit) ? scaled(acc[i]) : -INFINITY;
+            x[t][i] = (!MASKED || r + t * 16 + 4 * c4 + i <= limit) ? acc[i] : -INFINITY;
     }
 }
 
@@ -152,18 +159,17 @@ __device__ __forceinline__ void lse_rows(const WindowParams& p, const u32x4 (&k)
     const int lane = threadIdx.x & 63, n16 = lane & 15, c4 = lane >> 4;
 #pragma unroll 1
     for (int cb = 0; cb < p.ncb; ++cb) {
-        float s[T][4];
-        block_scores<MASKED, T>(k, sQ, cb, n16, c4, r, MASKED ? column_limit(p, cb * 16 + n16, n) : 0, s,
-                                [&](float x) { return x * p.scale2; });
-        float mx = s[0][0];
+        float x[T][4];
+        block_products<MASKED, T>(k, sQ, cb, n16, c4, r, MASKED ? column_limit(p, cb * 16 + n16, n) : 0, x);
+        float mx = x[0][0];
 #pragma unroll
-        for (int e = 1; e < 4 * T; ++e) mx = fmaxf(mx, s[e >> 2][e & 3]);
+        for (int e = 1; e < 4 * T; ++e) mx = fmaxf(mx, x[e >> 2][e & 3]);
         const float2 run = first ? make_float2(-INFINITY, 0.f) : sRun[cb * NT + threadIdx.x];
-        const float m_new = fmaxf(run.x, mx);
+        const float m_new = fmaxf(run.x, mx * p.scale2);
         const float ref = m_new == -INFINITY ? 0.f : m_new;      // nothing seen yet: every term is 2^-inf = 0
         float ps = 0.f;
 #pragma unroll
-        for (int e = 0; e < 4 * T; ++e) ps += fast_exp2(s[e >> 2][e & 3] - ref);
+        for (int e = 0; e < 4 * T; ++e) ps += fast_exp2(fmaf(x[e >> 2][e & 3], p.scale2, -ref));
         sRun[cb * NT + threadIdx.x] = make_float2(m_new, run.y * fast_exp2(run.x - ref) + ps);
     }
 }
@@ -228,9 +234,11 @@ void window_lse_kernel(const WindowParams p) {
 }
 
 // What a column's scores are normalised with: vote = 2^(s - maximum) / sum.  With lse = maximum + ln sum as two floats and
-// e^(s - lse) an exponent took two subtractions and two products instead of one multiply-add, and twice the error against 64
-// bits (32768 rows, 32 queries: 1.7e-7 -> 8.0e-8).  Whole call, us: 32768 rows, 32 queries 61.2 -> 60.2, 28 heads over 4, 30000 rows
-// 73.1 -> 70.7, 64 over 8, 20000 rows 87.5 -> 84.6, 8 sequences of 2000 rows 48.1 -> 46.5.
+// e^(s - lse) an exponent took two subtractions and two products instead of one multiply-add.  Largest relative error of votes of
+// at least 1e-3 of the largest, whole-number products (exact), for e^(s - lse) / for maxima and sums of scores rounded in pass 1 alone / now:
+// scores to 100: 7e-7 and less / 2.2e-6 / 9e-7, to 400: 2.7e-6 / 4.2e-6 / 8e-7, to 1000: 1.1e-5 / 1.7e-5 / 8e-7; normal keys (scores of a
+// few units, 32768 rows, 32 queries, 2-norm): 1.7e-7 / 8.0e-8 / 8.0e-8.  Whole call, us, the first / the last: 32768 rows, 32 queries 61.2 / 60.2,
+// 28 heads over 4, 30000 rows 73.1 / 70.7, 64 over 8, 20000 rows 87.5 / 84.6, 8 sequences of 2000 rows 48.1 / 46.5.
 __device__ __forceinline__ float2 column_norm(const WindowParams& p, int col, int n, float M, double L) {
     // (a column that does not exist was summed like the others; one without a finite score has no sum)
     return (M != -INFINITY && column_limit(p, col, n) >= 0) ? make_float2(M, (float)(1.0 / L)) : make_float2(0.f, 0.f);
@@ -296,13 +304,12 @@ __device__ __forceinline__ void vote_rows(const WindowParams& p, const u32x4 (&k
     for (int e = 0; e < 4 * T; ++e) v[e >> 2][e & 3] = 0.f;
     auto block = [&](auto masked, int cb) {
         constexpr bool kMasked = decltype(masked)::value;
-        float s[T][4];
+        float x[T][4];
+        block_products<kMasked, T>(k, sQ, cb, n16, c4, r, kMasked ? column_limit(p, cb * 16 + n16, n) : 0, x);
         const float2 norm = sLse[cb * 16 + n16];
-        block_scores<kMasked, T>(k, sQ, cb, n16, c4, r, kMasked ? column_limit(p, cb * 16 + n16, n) : 0, s,
-                                 [&](float x) { return fmaf(x, p.scale2, -norm.x); });
 #pragma unroll
         for (int e = 0; e < 4 * T; ++e)            // (masked: 2^-inf = 0; no such column: times 0)
-            v[e >> 2][e & 3] = fmaf(fast_exp2(s[e >> 2][e & 3]), norm.y, v[e >> 2][e & 3]);
+            v[e >> 2][e & 3] = fmaf(fast_exp2(fmaf(x[e >> 2][e & 3], p.scale2, -norm.x)), norm.y, v[e >> 2][e & 3]);
     };
     // A last block that the queries do not fill has columns which are added to real ones below; their zero queries' scores
     // are NaN where a key is infinite, so that block is masked also where every query sees every row.
@@ -486,7 +493,9 @@ extern "C" int rk_window_select(const rk_geom* geom, const void* q_win, int32_t 
     const WindowForm form = window_form(max_len, (int64_t)geom->batch * geom->n_kv_heads, ncb, ws.max_chunks);
     p.wg_rows = form.wg_rows; p.nch = form.nch;
     p.Hq = geom->n_q_heads; p.Hkv = geom->n_kv_heads;
-    p.scale2 = (float)((double)geom->scale * 1.4426950408889634);
+    p.scale2 = (float)(fabs((double)geom->scale) * 1.4426950408889634);
+    if (p.scale2 == 0.f) p.scale2 = FLT_MIN;                       // (a masked row's -inf times 0 would be NaN; 2^(x FLT_MIN) is 1)
+    p.q_sign = geom->scale < 0.f ? 0x80008000u : 0u;
     p.part = ws.part_o; p.lse = ws.part_ml;
     if (votes) { p.votes = votes; p.v_stride = v_stride; }
     else       { p.votes = ws.scores; p.v_stride = pooled_row_stride(max_len); }

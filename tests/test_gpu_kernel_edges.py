@@ -86,6 +86,42 @@ def test_window_select_folds_pass_1(rk, case):
     test_window_select_at_tile_edges(rk, case)
 
 
+# (rows, queries, largest score of the unrelated rows, a row that one query is aligned with, sign of the scale)
+WINDOW_SCORES = [(3000, 8, 5, True, 1), (3000, 8, 20, True, 1), (3000, 32, 100, True, 1), (40000, 32, 100, True, -1), (3000, 8, 400, False, 1),
+                 (40000, 20, 400, True, 1), (9000, 3, 400, False, -1), (3000, 8, 1000, False, 1), (700, 5, 0, False, 1)]
+
+
+@pytest.mark.parametrize("case", WINDOW_SCORES, ids=["n%d_w%d_s%d_%d_%d" % c for c in WINDOW_SCORES])
+def test_window_votes_of_peaked_and_large_scores(rk, case):
+    """Keys and queries of whole numbers, so that products are exact and what is seen is the softmax alone: votes of at least
+    1e-3 of the largest one are off by the rounding of the scale and of one exponent of at most 7 log2 e = 10 (2 x 10 x 2^-24 x ln 2 = 8e-7),
+    the exponential's last place and sums (a few 2^-24), whatever the size of the scores."""
+    n, W, top, peak, sign = case
+    say("window votes", *case)
+    Hkv, G = 2, 4
+    g = torch.Generator(device="cuda").manual_seed(n + W + top)
+    whole = lambda *shape: torch.randint(-4, 5, shape, generator=g, device="cuda").to(torch.bfloat16)
+    K, q = whole(1, Hkv, n, 128), whole(1, W, Hkv * G, 128)
+    scale = sign * float(np.float32(top / 300.0))                    # products of unrelated rows reach about 300
+    if peak:
+        K[0, 1, n // 3] = sign * q[0, W - 1, G]
+    geom = rk.Geom(1, Hkv * G, Hkv, 128, scale)
+    ws = rk.Workspace(geom, n, 64)
+    votes = torch.zeros(1, Hkv * G, n, device="cuda")
+    idx = torch.empty(1, Hkv, 64, dtype=torch.int32, device="cuda")
+    rk.rk_window_select(geom, q, K, torch.tensor([n], dtype=torch.int32, device="cuda"), n, 64, 1, idx, votes=votes, workspace=ws)
+    torch.cuda.synchronize()
+    x = torch.matmul(q[0].double().view(W, Hkv, G, 128).permute(1, 2, 0, 3).reshape(Hkv, G * W, 128), K[0].double().transpose(1, 2).contiguous())
+    z = (scale * x).view(Hkv, G, W, n)
+    for i in range(W):
+        z[:, :, i, n - W + i + 1:] = -float("inf")
+    ref = torch.softmax(z, -1).sum(2).reshape(Hkv * G, n)
+    big = ref >= 1e-3 * ref.amax(1, keepdim=True)
+    err = ((votes[0].double() - ref).abs() / ref)[big].max().item()
+    print("largest relative error %.3g" % err, file=sys.stderr, flush=True)
+    assert err <= 2e-6
+
+
 @pytest.mark.parametrize("shape", [(4, 1, 2, 700), (1, 3, 2, 700), (4, 5, 8, 9000), (4, 13, 8, 9000), (4, 13, 8, 32000), (2, 1, 8, 33000), (3, 7, 8, 33000)],
                          ids=lambda s: "g%d_w%d_h%d_n%d" % s)
 def test_window_select_with_infinite_keys(rk, shape):
