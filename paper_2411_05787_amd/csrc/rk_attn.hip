@@ -2139,7 +2139,7 @@ static int launch_partial(const rk_geom* geom, const void* q, rk_kv small, int32
         }
         p.nch = tile.nch; p.tail_wg = tile.tail;
         set_slice_merge(p, true, 0);
-        return launch_partial_tile(p, geom->batch, G, tile.waves, trig != nullptr, (hipStream_t)stream);
+        return launch_partial_tile(p, geom->batch, G, tile, trig != nullptr, (hipStream_t)stream);
     }
     // Which hand-over.  Tagged partial results merged by slices (every workgroup its share, see the kernel) wherever
     // that merge applies: a launch whose workgroups are all resident at once, with no more partial results per

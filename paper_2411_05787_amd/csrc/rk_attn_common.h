@@ -40,7 +40,7 @@ struct AttnParams {
 
 // The partial step in one tile per workgroup (rk_partial.hip): `waves` wavefronts of 16 rows.
 __attribute__((visibility("hidden")))
-int launch_partial_tile(const AttnParams& p, int batch, int G, int waves, bool trig, hipStream_t st);
+int launch_partial_tile(const AttnParams& p, int batch, int G, const TileForm& form, bool trig, hipStream_t st);
 
 constexpr int kSplitWaves = 4, kTileRows = 32;
 constexpr int kNoTailWg = 0xff;                   // top byte of the kernel argument s_b_and_tail: no workgroup for the tail rows
@@ -88,23 +88,30 @@ constexpr int kAgentScopeAux = 16;                // cache-policy operand of buf
 // own, keeps its tags in the same word of rows on the same 16-byte grid of the same region: neither can take a row of
 // the other for one of this call's.)
 //
+// EXACT: a lambda of fp32 puts ln 2 ulp(lambda) / 2 into a weight (2e-5 at scores of 400, 1.7e-4 at 4096).  Launches whose
+// shapes took (max, sum) pairs before this form did keep them: the rows hold the sums 2^{s - m} v as they are, { x, x, m, tag }, and one more row
+// per head, behind all partial results (head by head: a merge reads neighbours), holds { l, -, m, tag }; w_c = 2^{m_c - max m}, out = sum_c w_c x_c / sum_c w_c l_c.
+//
 // The merge is cut into units of U consecutive rows of a head, a wavefront each, 64 / U lanes to a row: lane U q + i
 // sums the chunks q, q + 64/U, q + 2 * 64/U, ... (at most TB) of row i, and the sums are added across the lanes in a fixed
 // order.  Which workgroup merges a unit does not change a bit of it.
 constexpr int kPairRows = kD / 2;                 // rows of a head
 // log2 U for a number of partial results: about five rows for a lane to read, at most 64 units (a bit each).
 template <int G> __device__ __forceinline__ int pair_unit_shift(int nchunks) { return nchunks <= 20 ? 4 : (nchunks <= 40 || G > 4) ? 3 : 2; }
-// What a lane reads of a unit: the first partial result's number, the row, and the two's place in the region.
-template <int G> struct PairLane {
+// What a lane reads of a unit: the first partial result's number, the row, and the two's place in the region.  EXACT: and the row of l of
+// one partial result (a unit lies within a head), the lane's number, so that the sum of the weights is one of all lanes.
+template <int G, bool EXACT> struct PairLane {
     static constexpr int STRIDE = G * kPairRows * 16;              // bytes of a partial result
-    int q, row, first, last;
+    int q, row, first, last, sum = 0;
     __device__ __forceinline__ PairLane(int unit, int shift, int nchunks) {
         const int lane = threadIdx.x & 63;
         q = lane >> shift;
         row = (unit << shift) + (lane & ((1 << shift) - 1));       // of all the group's rows
         first = q * STRIDE + row * 16;
         last = (nchunks - 1) * STRIDE + row * 16;
+        if (EXACT) sum = sum_row(row / kPairRows, min(lane, nchunks - 1));
     }
+    static __device__ __forceinline__ int sum_row(int head, int c) { return kTileExactChunks * STRIDE + (head * kTileExactChunks + c) * 16; }
 };
 
 // Max and sum over the lanes i, i + U, i + 2U ... of the wavefront.
@@ -112,32 +119,38 @@ template <int U>
 __device__ __forceinline__ float lanes_max(float v) {
     if (U <= 8) v = fmaxf(v, dpp_move_f<kDppRor8>(v));
     if (U <= 4) v = fmaxf(v, dpp_move_f<kDppRor4>(v));
+    if (U <= 2) v = fmaxf(v, dpp_move_f<kDppXor2>(v));
+    if (U <= 1) v = fmaxf(v, dpp_move_f<kDppXor1>(v));
     return max_xor32(max_xor16(v));
 }
 template <int U>
 __device__ __forceinline__ float lanes_sum(float v) {
     if (U <= 8) v += dpp_move_f<kDppRor8>(v);
     if (U <= 4) v += dpp_move_f<kDppRor4>(v);
+    if (U <= 2) v += dpp_move_f<kDppXor2>(v);
+    if (U <= 1) v += dpp_move_f<kDppXor1>(v);
     return sum_xor32(sum_xor16(v));
 }
 
 // One unit.  Rows still in flight are re-read at most `spin` times; if some are still missing then, the output is left
 // alone and the result is false (final: NaN is written instead).  `out`: the group's first head.
-template <int G, int U, int TB>
-__device__ __forceinline__ bool merge_pair_unit(uint16_t* out, const __amdgpu_buffer_rsrc_t rsrc, const PairLane<G> at, int nchunks,
+template <int G, bool EXACT, int U, int TB>
+__device__ __forceinline__ bool merge_pair_unit(uint16_t* out, const __amdgpu_buffer_rsrc_t rsrc, const PairLane<G, EXACT> at, int nchunks,
                                                 uint32_t tag, int spin, bool final) {
     constexpr int LPR = 64 / U;
-    u32x4 v[TB];
+    u32x4 v[TB], l;
     bool ok = false;
     int tries = 0;
     while (!__all(ok) && tries++ < spin) {
         if (tries > 1) __builtin_amdgcn_s_sleep(2);
 #pragma unroll
         for (int u = 0; u < TB; ++u)
-            v[u] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, min(at.first + u * LPR * PairLane<G>::STRIDE, at.last), 0, kAgentScopeAux);
+            v[u] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, min(at.first + u * LPR * PairLane<G, EXACT>::STRIDE, at.last), 0, kAgentScopeAux);
+        if constexpr (EXACT) l = __builtin_amdgcn_raw_buffer_load_b128(rsrc, at.sum, 0, kAgentScopeAux);
         uint32_t bad = 0;
 #pragma unroll
         for (int u = 0; u < TB; ++u) bad |= v[u].w ^ tag;
+        if constexpr (EXACT) bad |= l.w ^ tag;
         ok = bad == 0u;
     }
     const bool good = __all(ok);
@@ -148,16 +161,19 @@ __device__ __forceinline__ bool merge_pair_unit(uint16_t* out, const __amdgpu_bu
         lam[u] = at.q + u * LPR < nchunks ? __uint_as_float(v[u].z) : -INFINITY;
         ref = fmaxf(ref, lam[u]);
     }
-    ref = lanes_max<U>(ref);
+    const int lane = threadIdx.x & 63;
+    if constexpr (EXACT) ref = fmaxf(ref, lane < nchunks ? __uint_as_float(l.z) : -INFINITY);
+    ref = lanes_max<EXACT ? 1 : U>(ref);
     float a0 = 0.f, a1 = 0.f, den = 0.f;
 #pragma unroll
     for (int u = 0; u < TB; ++u) {
         const float wu = fast_exp2(lam[u] - ref);                  // 0 beyond nchunks and for empty chunks
         a0 = fmaf(wu, __uint_as_float(v[u].x), a0);
         a1 = fmaf(wu, __uint_as_float(v[u].y), a1);
-        den += wu;
+        if constexpr (!EXACT) den += wu;
     }
-    a0 = lanes_sum<U>(a0); a1 = lanes_sum<U>(a1); den = lanes_sum<U>(den);
+    if constexpr (EXACT) den = lane < nchunks ? fast_exp2(__uint_as_float(l.z) - ref) * __uint_as_float(l.x) : 0.f;
+    a0 = lanes_sum<U>(a0); a1 = lanes_sum<U>(a1); den = lanes_sum<EXACT ? 1 : U>(den);
     const float inv = den > 0.f ? __builtin_amdgcn_rcpf(den) : 0.f;
     const float nan = __uint_as_float(0x7fc00000u);
     const uint32_t pair = good ? pack_bf16(a0 * inv, a1 * inv) : pack_bf16(nan, nan);
@@ -167,14 +183,14 @@ __device__ __forceinline__ bool merge_pair_unit(uint16_t* out, const __amdgpu_bu
     }
     return true;
 }
-template <int G>
-__device__ __forceinline__ bool merge_pairs(uint16_t* out, const __amdgpu_buffer_rsrc_t rsrc, const PairLane<G> at, int nchunks,
+template <int G, bool EXACT>
+__device__ __forceinline__ bool merge_pairs(uint16_t* out, const __amdgpu_buffer_rsrc_t rsrc, const PairLane<G, EXACT> at, int nchunks,
                                             uint32_t tag, int spin, bool final) {
-    if (nchunks <= 8) return merge_pair_unit<G, 16, 2>(out, rsrc, at, nchunks, tag, spin, final);
-    if (nchunks <= 20) return merge_pair_unit<G, 16, 5>(out, rsrc, at, nchunks, tag, spin, final);
-    if (nchunks <= 40) return merge_pair_unit<G, 8, 5>(out, rsrc, at, nchunks, tag, spin, final);
-    if constexpr (G <= 4) return merge_pair_unit<G, 4, 5>(out, rsrc, at, nchunks, tag, spin, final);
-    else                  return merge_pair_unit<G, 8, 9>(out, rsrc, at, nchunks, tag, spin, final);
+    if (nchunks <= 8) return merge_pair_unit<G, EXACT, 16, 2>(out, rsrc, at, nchunks, tag, spin, final);
+    if (nchunks <= 20) return merge_pair_unit<G, EXACT, 16, 5>(out, rsrc, at, nchunks, tag, spin, final);
+    if (nchunks <= 40) return merge_pair_unit<G, EXACT, 8, 5>(out, rsrc, at, nchunks, tag, spin, final);
+    if constexpr (G <= 4) return merge_pair_unit<G, EXACT, 4, 5>(out, rsrc, at, nchunks, tag, spin, final);
+    else                  return merge_pair_unit<G, EXACT, 8, 9>(out, rsrc, at, nchunks, tag, spin, final);
 }
 
 }  // namespace rk

@@ -180,17 +180,24 @@ constexpr int kTagRegionRows = kTagSlots * (kD / 2);   // rows per head of a pai
 // 7.4 / 5.1 / 5.9, 4096: 7.4 / 6.0 / 6.3, 8192: 9.9 / - / 8.5; 2 sequences of 2048: 8.7 / 7.9 / 7.9, of 4096: 11.2 / - / 11.4; 4 of 1024:
 // 9.3 / 7.8 / 8.2, of 2048: 12.3 / 16.8 / 11.1, of 2048 and 28 over 4: 10.1 / 9.3 / 8.8; 8 of 1024: 12.1 / 13.8 / 11.1; 16 of 512:
 // 12.2 / 14.1 / 10.8, of 1024: 17.7 / 22.9 / 19.0.
-struct TileForm { int waves, nch, tail; };
+struct TileForm { int waves, nch, tail; bool exact; };
+// exact: partial results weighed by (max, sum) pairs (rk_attn_common.h): groups beyond 4 over more than 16 pairs, which have no tagged form in
+// attn_split_kernel and kept such pairs before they came here; a lane of a wavefront each, and the region has room for 65 rows of each.  us per launch, attn_split_kernel with
+// pairs / this kernel with a lambda / with pairs: 28 heads over 4, 6 sequences of K = 512: 8.5 / 5.2 / 5.4, of 2048: 11.2 / 7.7 / 7.7, 8 of 512:
+// 8.5 / 5.8 / 5.9, 16 of 256: 8.6 / 6.2 / 6.4, 64 heads over 8, 8 sequences of 256: 8.3 / 6.3 / 6.5.
+constexpr int kTileExactChunks = 64;
+static_assert(kTileExactChunks * (kD / 2 + 1) <= kTagRegionRows, "a pair's region holds them");
 static inline TileForm partial_tile_form(int64_t rows, int64_t tail_rows, int64_t problems, int G) {
+    const bool exact = G > 4 && problems > 16;
     for (int waves = 4; waves <= 8; waves += 4) {
         const int wg = 16 * waves;
         const int64_t nch = (rows + wg - 1) / wg, tail = (tail_rows + wg - 1) / wg, total = (nch + tail) * problems;
-        if (nch > kMergeChunks || nch + tail > kTagSlots) continue;
+        if (nch > kMergeChunks || nch + tail > (exact ? kTileExactChunks : kTagSlots)) continue;
         if (waves == 4 ? nch * problems <= kComputeUnits && total <= 2 * kComputeUnits
                        : total <= 2 * kComputeUnits || (G <= 4 && total <= 3 * kComputeUnits && nch <= 20))
-            return {waves, (int)nch, (int)tail};
+            return {waves, (int)nch, (int)tail, exact};
     }
-    return {0, 0, 0};
+    return {0, 0, 0, false};
 }
 
 static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }

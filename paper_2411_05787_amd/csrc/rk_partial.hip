@@ -32,7 +32,7 @@ static_assert(kMergeChunks * 128 < (1 << kSpecBits), "rows of the small cache");
 
 // Attention over the small cache and the rows decoded since the refresh, where no workgroup has more rows than it holds
 // at once: 16 per wavefront.
-template <int G, int NW, bool TRIG>
+template <int G, int NW, bool TRIG, bool EXACT>
 __global__ __launch_bounds__((NW + TRIG) * 64, 4)
 void partial_tile_kernel(const uint16_t* k1, const uint16_t* v1, int64_t s_b_and_tail, int32_t s_h, uint32_t rows_heads,
                          const int32_t* seq_lens, const int32_t* tail_start, const uint16_t* q, const TileParams p) {
@@ -159,7 +159,7 @@ void partial_tile_kernel(const uint16_t* k1, const uint16_t* v1, int64_t s_b_and
     const uint32_t tag = max(epoch + 1u, 1u);                          // this call's number: never 0
     // this wavefront's first unit of the merge, worked out while the rows are on their way
     const int shift = pair_unit_shift<G>(nchunks), units = (kPairRows * G) >> shift, unit0 = c_rec + (NW - 1 - w) * nchunks;
-    PairLane<G> at0(unit0, shift, nchunks);
+    PairLane<G, EXACT> at0(unit0, shift, nchunks);
     asm volatile("" : "+v"(at0.q), "+v"(at0.row), "+v"(at0.first), "+v"(at0.last) : "s"(tag));
 
     // ---- S^T = K Q^T: head n16, rows 4 c4 + i of the wavefront's 16 ----
@@ -226,18 +226,25 @@ void partial_tile_kernel(const uint16_t* k1, const uint16_t* v1, int64_t s_b_and
             o[t][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vb, p_lo, o[t][1], 0, 0, 0);
         }
     }
-    float inv = L > 0.f ? __builtin_amdgcn_rcpf(L) : 0.f, lam = L > 0.f ? M + __builtin_amdgcn_logf(L) : -INFINITY;
-    asm volatile("" : "+v"(inv), "+v"(lam));  // (beside the matrix instructions)
+    float inv = 1.f, lam = M;                 // EXACT: the sums as they are, weighed by their maximum (-inf: no rows)
+    if constexpr (!EXACT) {
+        inv = L > 0.f ? __builtin_amdgcn_rcpf(L) : 0.f; lam = L > 0.f ? M + __builtin_amdgcn_logf(L) : -INFINITY;
+        asm volatile("" : "+v"(inv), "+v"(lam));  // (beside the matrix instructions)
+    }
     // ---- publish ----
     if (n16 < G) {
 #pragma unroll
         for (int t = 0; t < DT; ++t) {
-            const f32x4 x = (o[t][0] + o[t][1]) * inv;
-            const int off = ((c_rec * G + n16) * kPairRows + (w * DT + t) * 8 + 2 * c4) * 16;
+            const f32x4 x = EXACT ? o[t][0] + o[t][1] : (o[t][0] + o[t][1]) * inv;
+            const int off = c_rec * PairLane<G, EXACT>::STRIDE + (n16 * kPairRows + (w * DT + t) * 8 + 2 * c4) * 16;
             const u32x4 r0 = {__float_as_uint(x[0]), __float_as_uint(x[1]), __float_as_uint(lam), tag};
             const u32x4 r1 = {__float_as_uint(x[2]), __float_as_uint(x[3]), __float_as_uint(lam), tag};
             __builtin_amdgcn_raw_buffer_store_b128(r0, rsrc, off, 0, kAgentScopeAux);
             __builtin_amdgcn_raw_buffer_store_b128(r1, rsrc, off + 16, 0, kAgentScopeAux);
+        }
+        if (EXACT && w == 0 && c4 == 0) {
+            const u32x4 r = {__float_as_uint(L), 0u, __float_as_uint(lam), tag};
+            __builtin_amdgcn_raw_buffer_store_b128(r, rsrc, PairLane<G, EXACT>::sum_row(n16, c_rec), 0, kAgentScopeAux);
         }
     }
     // ---- merge (see attn_split_kernel: the same protocol, a bit per unit) ----
@@ -258,8 +265,8 @@ void partial_tile_kernel(const uint16_t* k1, const uint16_t* v1, int64_t s_b_and
         if (lane == 0) sTicket = ticket;
     }
     for (int unit = unit0; unit < units; unit += NW * nchunks) {
-        if (unit != unit0) at0 = PairLane<G>(unit, shift, nchunks);
-        if (merge_pairs<G>(out, rsrc, at0, nchunks, tag, spin, false)) continue;
+        if (unit != unit0) at0 = PairLane<G, EXACT>(unit, shift, nchunks);
+        if (merge_pairs<G, EXACT>(out, rsrc, at0, nchunks, tag, spin, false)) continue;
         const unsigned long long bit = 1ull << unit;
         uint32_t seen = 0;
         if (lane == 0) {
@@ -269,7 +276,7 @@ void partial_tile_kernel(const uint16_t* k1, const uint16_t* v1, int64_t s_b_and
         }
         seen = __builtin_amdgcn_readfirstlane(seen);
         if (seen == tag) {
-            merge_pairs<G>(out, rsrc, at0, nchunks, tag, kTagSpinLimit, true);
+            merge_pairs<G, EXACT>(out, rsrc, at0, nchunks, tag, kTagSpinLimit, true);
             if (lane == 0) __hip_atomic_fetch_and(pend, ~bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
@@ -279,11 +286,11 @@ void partial_tile_kernel(const uint16_t* k1, const uint16_t* v1, int64_t s_b_and
     for (int k = 0; left != 0; ++k) {
         const int unit = __builtin_ctzll(left);
         left &= left - 1;
-        if ((k & (NW - 1)) == w && unit < units) merge_pairs<G>(out, rsrc, PairLane<G>(unit, shift, nchunks), nchunks, tag, kTagSpinLimit, true);
+        if ((k & (NW - 1)) == w && unit < units) merge_pairs<G, EXACT>(out, rsrc, PairLane<G, EXACT>(unit, shift, nchunks), nchunks, tag, kTagSpinLimit, true);
     }
 }
 
-template <int G, int NW>
+template <int G, int NW, bool EXACT>
 static int launch_g(const AttnParams& p, int batch, bool trig, hipStream_t st) {
     TileParams t{(float)((double)p.scale * 1.4426950408889634), p.n_sel, p.evict, p.max_rows2, p.cap1, p.cap2, p.slice_spin, p.pred_val,
                  p.epochs, p.out, p.counters, p.tag_rows, p.k2, p.v2, p.s2_b, p.s2_h,
@@ -292,15 +299,22 @@ static int launch_g(const AttnParams& p, int batch, bool trig, hipStream_t st) {
     const uint32_t spec_rows = (uint32_t)(p.n_sel < p.cap1 ? p.n_sel : p.cap1);
     const uint32_t rows_heads = spec_rows | (p.pred != nullptr ? kPredBit : 0) | ((uint32_t)p.Hkv << 16);
     const int64_t s_b_and_tail = p.s1_b | ((int64_t)p.nch << 56);
-    auto kernel = trig ? partial_tile_kernel<G, NW, true> : partial_tile_kernel<G, NW, false>;
+    auto kernel = trig ? partial_tile_kernel<G, NW, true, EXACT> : partial_tile_kernel<G, NW, false, EXACT>;
     hipLaunchKernelGGL(kernel, grid, dim3((NW + (trig ? 1 : 0)) * 64), 0, st, p.k1, p.v1, s_b_and_tail, (int32_t)p.s1_h, rows_heads,
                        p.seq_lens, p.tail_start, p.q, t);
     return launch_status();
 }
 
-int launch_partial_tile(const AttnParams& p, int batch, int G, int waves, bool trig, hipStream_t st) {
+template <int G>
+static int launch_form(const AttnParams& p, int batch, const TileForm& form, bool trig, hipStream_t st) {
+    if constexpr (G > 4)
+        if (form.exact) return form.waves == 4 ? launch_g<G, 4, true>(p, batch, trig, st) : launch_g<G, 8, true>(p, batch, trig, st);
+    return form.waves == 4 ? launch_g<G, 4, false>(p, batch, trig, st) : launch_g<G, 8, false>(p, batch, trig, st);
+}
+
+int launch_partial_tile(const AttnParams& p, int batch, int G, const TileForm& form, bool trig, hipStream_t st) {
     switch (G) {
-#define RK_CASE(g) case g: return waves == 4 ? launch_g<g, 4>(p, batch, trig, st) : launch_g<g, 8>(p, batch, trig, st);
+#define RK_CASE(g) case g: return launch_form<g>(p, batch, form, trig, st);
         RK_CASE(1) RK_CASE(2) RK_CASE(3) RK_CASE(4) RK_CASE(5) RK_CASE(6) RK_CASE(7) RK_CASE(8)
 #undef RK_CASE
         default: return RK_ERR_UNSUPPORTED;

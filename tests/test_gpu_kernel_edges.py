@@ -486,7 +486,10 @@ TILE_EDGES = [("k1", 4, 8, 1, 4, 0, [(900, 3)]), ("k16_17_g1", 1, 3, 17, 4, 0, [
               ("k1280_20_chunks", 3, 2, 1280, 5, 0, [(1279, 5), (2000, 0)]), ("k2560_g7", 7, 2, 2560, 5, 0, [(2560, 5)]), ("k2561_u4", 4, 4, 2561, 1, 0, [(3000, 1)]),
               ("k4096_65_chunks_g7", 7, 4, 4096, 64, 0, [(4096, 64)]), ("k4096_8w", 4, 8, 4096, 5, 0, [(4096, 5)]), ("k4100_8w_g6", 6, 8, 4100, 128, 0, [(4100, 128)]),
               ("k8192_65_chunks_8w_g8", 8, 4, 8192, 100, 0, [(8192, 100)]), ("k8192_split", 4, 8, 8192, 5, 0, [(8192, 5)]),
-              ("batch", 4, 8, 700, 9, 0, [(700 + 37 * b, b) for b in range(9)]), ("batch_3_per_cu", 4, 8, 512, 9, 0, [(600, 9 - b % 4) for b in range(16)])]
+              ("batch", 4, 8, 700, 9, 0, [(700 + 37 * b, b) for b in range(9)]), ("batch_3_per_cu", 4, 8, 512, 9, 0, [(600, 9 - b % 4) for b in range(16)]),
+              # groups beyond 4 over more than 16 pairs: partial results with maximum and sum apart
+              ("exact_g7", 7, 4, 300, 9, 0, [(700 + 37 * b, b) for b in range(6)]), ("exact_g8_8w", 8, 8, 500, 9, 0, [(505, 9 - b) for b in range(7)]),
+              ("exact_g5_23_chunks", 5, 1, 2800, 5, 1, [(2790 + b, 5) for b in range(17)]), ("exact_g6_empty", 6, 9, 70, 70, 0, [(0, 0), (0, 70), (200, 0)])]
 
 
 @pytest.mark.parametrize("case", TILE_EDGES, ids=[c[0] for c in TILE_EDGES])
@@ -535,6 +538,34 @@ def test_partial_step_at_tile_edges(rk, case):
         ref = torch.matmul(torch.softmax(s, dim=-1), Vb).reshape(-1, 128)
         d = (outs[0][b].double() - ref).abs()
         assert (d <= torch.maximum(outs[0][b].double().abs(), ref.abs()) * 2.0 ** -7 + 4e-6).all(), (b, float(d.max()))
+
+
+# (heads per group, KV heads, sequences, rows of a workgroup)
+TILE_WEIGHTS = [(7, 4, 6, 64), (8, 8, 4, 64), (5, 4, 16, 128), (6, 8, 9, 128)]
+
+
+@pytest.mark.parametrize("shape", TILE_WEIGHTS, ids=["g%d_%dx%d_%d" % c for c in TILE_WEIGHTS])
+def test_partial_step_weighs_its_workgroups_exactly(rk, shape):
+    """Groups beyond 4 over more than 16 pairs: three workgroups whose sums are 1, 3/4 and 1/4 of a workgroup's rows with the same score
+    of several hundred, values +1, -1 and -1.  The output is exactly 0; weights that went through a rounded log-sum-exp leave about
+    1e-5 (scores of 400) and more."""
+    G, Hkv, B, wg = shape
+    say("tile weights", *shape)
+    k = 3 * wg
+    q = torch.ones(B, Hkv * G, 128, dtype=torch.bfloat16, device="cuda") * (1 + torch.arange(Hkv * G, device="cuda") / 16).to(torch.bfloat16)[:, None]
+    sK = torch.zeros(B, Hkv, k, 128, dtype=torch.bfloat16, device="cuda")
+    sV = torch.full_like(sK, 5.0)                             # rows of score 0 weigh e^-400: nothing
+    for rows, value in ((slice(0, wg), 1.0), (slice(wg, wg + 3 * wg // 4), -1.0), (slice(2 * wg, 2 * wg + wg // 4), -1.0)):
+        sK[:, :, rows], sV[:, :, rows] = 35.0 + torch.arange(Hkv, device="cuda")[:, None, None] / 4, value
+    K = torch.full((B, Hkv, k + 4, 128), float("nan"), dtype=torch.bfloat16, device="cuda")
+    geom = rk.Geom(B, Hkv * G, Hkv, 128, SCALE)
+    ws = rk.Workspace(geom, k + 4, k)
+    lens = torch.full((B,), k, dtype=torch.int32, device="cuda")
+    out = torch.full((B, Hkv * G, 128), 7.0, dtype=torch.bfloat16, device="cuda")
+    rk.rk_partial_attn(geom, q, sK, sV, k, K, K, lens, lens, 4, out, workspace=ws)
+    torch.cuda.synchronize()
+    say("largest output %.3g" % out.float().abs().max().item())
+    assert (out == 0).all()
 
 
 def _select_scores(name, rows, n, g):
