@@ -2131,7 +2131,7 @@ static int launch_partial(const rk_geom* geom, const void* q, rk_kv small, int32
     p.counters = ws.counters; p.part_ml = ws.part_ml; p.part_o = ws.part_o; p.max_chunks = ws.max_chunks;
     p.epochs = ws.epochs; p.tag_rows = ws.tag_rows;
     // one tile per workgroup where all of them are resident at once
-    const TileForm tile = partial_tile_form(n_sel, max_recent, (int64_t)geom->batch * geom->n_kv_heads, G);
+    const TileForm tile = partial_tile_form(n_sel, max_recent, (int64_t)geom->batch * geom->n_kv_heads, G, trig != nullptr);
     if (tile.waves != 0 && ws.tag_rows != nullptr && lazy_idx == nullptr) {
         if (trig != nullptr) {
             if (pred != nullptr) return RK_ERR_INVALID_ARG;

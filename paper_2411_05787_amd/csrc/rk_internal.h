@@ -172,7 +172,10 @@ constexpr int kTagRegionRows = kTagSlots * (kD / 2);   // rows per head of a pai
 // The partial step in one tile per workgroup (rk_partial.hip): 4 or 8 wavefronts of 16 rows, nch workgroups per (sequence,
 // KV head) for the `rows` of the small cache and `tail` for at most tail_rows rows of the full one; waves = 0: not used.  Its
 // workgroups wait for one another, so all have to be resident at once: by registers and LDS that is three workgroups of 8 wavefronts per
-// compute unit for groups of up to 4 heads, two beyond, and twice that of 4.  4 wavefronts while that is one workgroup per unit and the
+// compute unit for groups of up to 4 heads, two beyond, and twice that of 4.  With the trigger (one wavefront more, 7 registers) it is
+// two workgroups of 8 + 1 for groups of up to 4 heads and one beyond (beyond that, us per launch, attn_split_kernel / this one: 4 sequences of
+// K = 2048, 32 heads over 8: 11.2 / 14.6, 16 of 512: 11.4 / 14.5, K = 4096, 64 over 8: 9.6 / 14.1, 8 of 1024, 28 over 4: 10.2 / 12.7).  4
+// wavefronts while that is one workgroup per unit and the
 // tails: more of them share the request and the merge; 8 beyond, with half the partial results to write and read.
 // Many partial results to a pair and more than two workgroups per unit (33 MB of rows) are better off in longer stretches
 // (attn_split_kernel).  us per launch, attn_split_kernel / 4 / 8 wavefronts, 32 heads over 8 unless noted: 256 rows 6.9 / 4.9 / 5.5,
@@ -187,11 +190,12 @@ struct TileForm { int waves, nch, tail; bool exact; };
 // 8.5 / 5.8 / 5.9, 16 of 256: 8.6 / 6.2 / 6.4, 64 heads over 8, 8 sequences of 256: 8.3 / 6.3 / 6.5.
 constexpr int kTileExactChunks = 64;
 static_assert(kTileExactChunks * (kD / 2 + 1) <= kTagRegionRows, "a pair's region holds them");
-static inline TileForm partial_tile_form(int64_t rows, int64_t tail_rows, int64_t problems, int G) {
+static inline TileForm partial_tile_form(int64_t rows, int64_t tail_rows, int64_t problems, int G, bool trig) {
     const bool exact = G > 4 && problems > 16;
     for (int waves = 4; waves <= 8; waves += 4) {
         const int wg = 16 * waves;
         const int64_t nch = (rows + wg - 1) / wg, tail = (tail_rows + wg - 1) / wg, total = (nch + tail) * problems;
+        if (trig && waves == 8 && total > (G > 4 ? 1 : 2) * kComputeUnits) continue;
         if (nch > kMergeChunks || nch + tail > (exact ? kTileExactChunks : kTagSlots)) continue;
         if (waves == 4 ? nch * problems <= kComputeUnits && total <= 2 * kComputeUnits
                        : total <= 2 * kComputeUnits || (G <= 4 && total <= 3 * kComputeUnits && nch <= 20))

@@ -568,6 +568,64 @@ def test_partial_step_weighs_its_workgroups_exactly(rk, shape):
     assert (out == 0).all()
 
 
+# The triggered step in each of its kernels: one tile per workgroup of 4 and 8 wavefronts, with a log-sum-exp and with (max, sum) pairs,
+# and, where nine wavefronts to a workgroup would not all be resident, attn_split_kernel in its tagged and its ticketed form
+# (test_launch_sizes asserts which takes which).  (heads per group, KV heads, sequences, K, bound on the rows since, fixed size)
+TRIGGERED = {"tile_4w": (4, 8, 1, 2048, 5, False), "tile_4w_g8": (8, 4, 3, 700, 16, True), "tile_8w": (4, 8, 4, 1024, 9, True), "tile_8w_g7": (7, 4, 4, 1100, 5, False),
+             "tile_8w_exact_g8": (8, 8, 4, 700, 9, False), "split_tagged_long": (4, 8, 1, 8192, 5, False), "split_tagged_batch": (4, 8, 4, 2048, 5, True),
+             "split_tagged_g8": (8, 8, 1, 4096, 5, False), "split_ticketed_g7": (7, 4, 8, 1024, 5, True)}
+
+
+@pytest.mark.parametrize("name", list(TRIGGERED))
+def test_triggered_step_in_each_form(rk, name):
+    """Outputs of the sequences that do not fire against fp64 (one bf16 step of the larger value and 4e-6), the others' untouched; sim, decision
+    and reference as rk_query_sim has them; the same bits whoever merges and however often it is called."""
+    G, Hkv, B, k, recent, fixed = TRIGGERED[name]
+    say("triggered", name)
+    Hq, cap = G * Hkv, k + 40
+    g = torch.Generator(device="cuda").manual_seed(k + G + B)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
+    K, V, sK, sV, q = rnd(B, Hkv, cap, 128), rnd(B, Hkv, cap, 128), rnd(B, Hkv, k, 128), rnd(B, Hkv, k, 128), rnd(B, Hq, 128)
+    ref = q.float().mean(1) * 2
+    ref[1::2] = torch.randn(ref[1::2].shape, generator=g, device="cuda")
+    since = [min(recent, 5 - b % 4) for b in range(B)]
+    lens = torch.tensor([cap - 2 - b for b in range(B)], dtype=torch.int32, device="cuda")
+    tail = lens - torch.tensor(since, dtype=torch.int32, device="cuda")
+    geom = rk.Geom(B, Hq, Hkv, 128, SCALE)
+    ws = rk.Workspace(geom, cap, k)
+    i32 = lambda: torch.full((B,), -1, dtype=torch.int32, device="cuda")
+    ref_a, sim_a, need_a = ref.clone(), torch.zeros(B, device="cuda"), i32()
+    rk.rk_query_sim(geom, q, ref_a, 0.5, False, sim_a, need_a)
+    torch.cuda.synchronize()
+    fired = need_a.bool().tolist()
+    assert fired == [b % 2 == 1 for b in range(B)]
+    outs = []
+    try:
+        for spin in (256, 0, 1, 256):
+            rk.rk_debug_set_slice_spin(spin)
+            out = torch.full((B, Hq, 128), 7.0, dtype=torch.bfloat16, device="cuda")
+            ref_b, sim_b, need_b = ref.clone(), torch.zeros(B, device="cuda"), i32()
+            rk.rk_partial_attn_triggered(geom, q, sK, sV, k, K, V, tail, lens, recent, out, ref_b, 0.5, sim_b, need_b, fixed_size=fixed, workspace=ws)
+            torch.cuda.synchronize()
+            assert torch.equal(sim_b, sim_a) and torch.equal(need_b, need_a) and torch.equal(ref_b, ref_a)
+            outs.append(out)
+    finally:
+        rk.rk_debug_set_slice_spin(256)
+    for o in outs[1:]:
+        assert torch.equal(o, outs[0])
+    for b in range(B):
+        if fired[b]:
+            assert (outs[0][b] == 7.0).all()
+            continue
+        n1, n, t0 = k - (since[b] if fixed else 0), int(lens[b]), int(tail[b])
+        Kb = torch.cat([sK[b, :, :n1], K[b, :, t0:n]], dim=1).double()
+        Vb = torch.cat([sV[b, :, :n1], V[b, :, t0:n]], dim=1).double()
+        x = SCALE * torch.matmul(q[b].double().view(Hkv, G, 128), Kb.transpose(1, 2).contiguous())
+        want = torch.matmul(torch.softmax(x, dim=-1), Vb).reshape(-1, 128)
+        d = (outs[0][b].double() - want).abs()
+        assert (d <= torch.maximum(outs[0][b].double().abs(), want.abs()) * 2.0 ** -7 + 4e-6).all(), (b, float(d.max()))
+
+
 def _select_scores(name, rows, n, g):
     w = torch.exp(torch.randn(*rows, n, generator=g) * 1.2 - 10)
     if name == "levels":                   # few values: stretches do not fit, the row is one workgroup's

@@ -630,7 +630,7 @@ def test_query_sim_matches_oracle(rk):
         assert np.abs(q_ref.cpu().numpy() - r_ref).max() < 1e-6
 
 
-@pytest.mark.parametrize("heads", [(32, 8), (28, 4)], ids=["g4_tagged", "g7_ticketed"])
+@pytest.mark.parametrize("heads", [(32, 8), (28, 4)], ids=["g4_tile_8w", "g7_tile_4w"])
 @pytest.mark.parametrize("fixed_size", [False, True], ids=["growing", "fixed_size"])
 def test_partial_attn_triggered_equals_test_then_step(rk, heads, fixed_size):
     """rk_partial_attn_triggered against rk_query_sim followed by the partial step under its predicate

@@ -38,8 +38,10 @@ int main() {
     for (long r : {0L, 1L, 64L, 65L, 256L, 700L, 1024L, 2048L, 4096L, 6000L, 8192L, 8193L, 100000L}) for (long p : {1L, 4L, 8L, 12L, 32L, 64L, 128L, 512L, 4096L})
         for (int tail : {0, 1, 64, 65, 128, 500, 100000}) for (int G : {1, 4, 5, 8}) {
             if (r + tail == 0) continue;
-            const TileForm f = partial_tile_form(r, tail, p, G);
-            printf("tile %ld %ld %d %d %d %d %d\n", r, p, tail, G, f.waves, f.nch, f.tail);
+            for (int trig = 0; trig < 2; ++trig) {
+                const TileForm f = partial_tile_form(r, tail, p, G, trig != 0);
+                printf("tile %ld %ld %d %d %d %d %d %d %d\n", r, p, tail, G, trig, f.waves, f.nch, f.tail, (int)f.exact);
+            }
         }
     for (long p : {1L, 4L, 8L, 12L, 32L, 33L, 64L, 65L, 128L, 129L, 256L, 257L, 100000L}) printf("parts %ld %d\n", p, select_parts(32768, p));
     // the parts of a row whose K' ranks end in a bin of h positions, `above` of the ranks in higher bins: stretches from the top
@@ -188,20 +190,25 @@ def test_sliced_split_bounds_and_measured_choices(table):
 
 def test_partial_tile_form_bounds_and_measured_choices(table):
     """Every row has a wavefront's 16-row slot, the partial results have slots, and the launch is resident as a whole."""
-    got = {}
+    got, triggered = {}, {}
     for kind, *v in table:
         if kind != "tile":
             continue
-        rows, pairs, tail, G, waves, nch, ntail = map(int, v)
-        got[(rows, pairs, tail, G)] = (waves, nch, ntail)
+        rows, pairs, tail, G, trig, waves, nch, ntail, exact = map(int, v)
+        (triggered if trig else got)[(rows, pairs, tail, G)] = (waves, nch, ntail)
         assert waves in (0, 4, 8)
         if waves:
-            assert nch * 16 * waves >= rows and ntail * 16 * waves >= tail and nch <= 64 and 1 <= nch + ntail <= 65
-            assert (nch + ntail) * pairs <= (512 if waves == 4 or G > 4 else 768)
+            assert nch * 16 * waves >= rows and ntail * 16 * waves >= tail and nch <= 64 and 1 <= nch + ntail <= (64 if exact else 65)
+            assert (nch + ntail) * pairs <= (512 if waves == 4 else (256 if G > 4 else 512) if trig else 512 if G > 4 else 768)
+            assert exact == (G > 4 and pairs > 16)
     assert got[(2048, 8, 1, 4)] == (4, 32, 1) and got[(256, 8, 1, 4)] == (4, 4, 1) and got[(4096, 4, 1, 8)] == (4, 64, 1)
     assert got[(4096, 8, 1, 4)] == (8, 32, 1) and got[(8192, 4, 1, 8)] == (8, 64, 1)
     assert got[(8192, 8, 1, 4)][0] == 0 and got[(1024, 128, 1, 4)][0] == 0            # 33 MB and more in many partial results
     assert got[(2048, 32, 1, 4)] == (8, 16, 1) and got[(1024, 64, 1, 4)] == (8, 8, 1) and got[(1024, 64, 1, 5)][0] == 0
+    # the forms that the triggered cases of test_gpu_kernel_edges.py mean to reach
+    assert triggered[(2048, 8, 1, 4)] == (4, 32, 1) and triggered[(700, 12, 1, 8)] == (4, 11, 1) and triggered[(700, 32, 1, 8)] == (8, 6, 1)
+    assert triggered[(1024, 32, 1, 4)] == (8, 8, 1) and triggered[(2048, 32, 1, 4)][0] == 0 and triggered[(8192, 8, 1, 4)][0] == 0
+    assert triggered[(1024, 32, 1, 8)][0] == 0 and triggered[(4096, 8, 1, 8)][0] == 0
     assert got[(0, 8, 500, 4)] == (4, 0, 8) and got[(2048, 8, 100000, 4)][0] == 0
 
 
