@@ -102,7 +102,7 @@ template <int G> __device__ __forceinline__ int pair_unit_shift(int nchunks) { r
 // one partial result (a unit lies within a head), the lane's number, so that the sum of the weights is one of all lanes.
 template <int G, bool EXACT> struct PairLane {
     static constexpr int STRIDE = G * kPairRows * 16;              // bytes of a partial result
-    int q, row, first, last, sum = 0;
+    int q, row, first, last, sum;
     __device__ __forceinline__ PairLane(int unit, int shift, int nchunks) {
         const int lane = threadIdx.x & 63;
         q = lane >> shift;

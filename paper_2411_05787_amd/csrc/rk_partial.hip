@@ -161,6 +161,7 @@ void partial_tile_kernel(const uint16_t* k1, const uint16_t* v1, int64_t s_b_and
     const int shift = pair_unit_shift<G>(nchunks), units = (kPairRows * G) >> shift, unit0 = c_rec + (NW - 1 - w) * nchunks;
     PairLane<G, EXACT> at0(unit0, shift, nchunks);
     asm volatile("" : "+v"(at0.q), "+v"(at0.row), "+v"(at0.first), "+v"(at0.last) : "s"(tag));
+    if constexpr (EXACT) asm volatile("" : "+v"(at0.sum));
 
     // ---- S^T = K Q^T: head n16, rows 4 c4 + i of the wavefront's 16 ----
     float s[4];
@@ -236,7 +237,7 @@ void partial_tile_kernel(const uint16_t* k1, const uint16_t* v1, int64_t s_b_and
 #pragma unroll
         for (int t = 0; t < DT; ++t) {
             const f32x4 x = EXACT ? o[t][0] + o[t][1] : (o[t][0] + o[t][1]) * inv;
-            const int off = c_rec * PairLane<G, EXACT>::STRIDE + (n16 * kPairRows + (w * DT + t) * 8 + 2 * c4) * 16;
+            const int off = ((c_rec * G + n16) * kPairRows + (w * DT + t) * 8 + 2 * c4) * 16;
             const u32x4 r0 = {__float_as_uint(x[0]), __float_as_uint(x[1]), __float_as_uint(lam), tag};
             const u32x4 r1 = {__float_as_uint(x[2]), __float_as_uint(x[3]), __float_as_uint(lam), tag};
             __builtin_amdgcn_raw_buffer_store_b128(r0, rsrc, off, 0, kAgentScopeAux);
