@@ -188,6 +188,10 @@ struct TileForm { int waves, nch, tail; bool exact; };
 // attn_split_kernel and kept such pairs before they came here; a lane of a wavefront each, and the region has room for 65 rows of each.  us per launch, attn_split_kernel with
 // pairs / this kernel with a lambda / with pairs: 28 heads over 4, 6 sequences of K = 512: 8.5 / 5.2 / 5.4, of 2048: 11.2 / 7.7 / 7.7, 8 of 512:
 // 8.5 / 5.8 / 5.9, 16 of 256: 8.6 / 6.2 / 6.4, 64 heads over 8, 8 sequences of 256: 8.3 / 6.3 / 6.5.
+// The merge is 4 G units, whatever the number of results: with two of them (or three of 8 wavefronts) a wavefront has several in a row, and
+// groups of 8, and any over many pairs, are better off with all rows in one or two workgroups of attn_split_kernel (64 heads over 8, K = 64, 3 / 16 / 32
+// sequences: 7.0 / 7.2 / 7.3 against 7.4 / 8.2 / 9.4, K = 192, 16: 7.5 against 8.4; 48 over 8, K = 64, 16 / 32: 7.4 / 7.5 against 7.3 / 8.3; 40 over
+// 8, K = 96, 32: 7.75 against 8.1; 28 over 4, K = 64, 16: 7.4 against 7.0).
 constexpr int kTileExactChunks = 64;
 static_assert(kTileExactChunks * (kD / 2 + 1) <= kTagRegionRows, "a pair's region holds them");
 static inline TileForm partial_tile_form(int64_t rows, int64_t tail_rows, int64_t problems, int G, bool trig) {
@@ -195,6 +199,7 @@ static inline TileForm partial_tile_form(int64_t rows, int64_t tail_rows, int64_
     for (int waves = 4; waves <= 8; waves += 4) {
         const int wg = 16 * waves;
         const int64_t nch = (rows + wg - 1) / wg, tail = (tail_rows + wg - 1) / wg, total = (nch + tail) * problems;
+        if (exact && nch + tail <= (waves == 4 ? 2 : 3) && (G == 8 || problems >= (G > 5 ? 128 : 192))) continue;
         if (trig && waves == 8 && total > (G > 4 ? 1 : 2) * kComputeUnits) continue;
         if (nch > kMergeChunks || nch + tail > (exact ? kTileExactChunks : kTagSlots)) continue;
         if (waves == 4 ? nch * problems <= kComputeUnits && total <= 2 * kComputeUnits

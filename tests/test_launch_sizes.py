@@ -200,7 +200,7 @@ def test_partial_tile_form_bounds_and_measured_choices(table):
         if waves:
             assert nch * 16 * waves >= rows and ntail * 16 * waves >= tail and nch <= 64 and 1 <= nch + ntail <= (64 if exact else 65)
             assert (nch + ntail) * pairs <= (512 if waves == 4 else (256 if G > 4 else 512) if trig else 512 if G > 4 else 768)
-            assert exact == (G > 4 and pairs > 16)
+            assert exact == (G > 4 and pairs > 16) and not (exact and G == 8 and nch + ntail <= (2 if waves == 4 else 3))
     assert got[(2048, 8, 1, 4)] == (4, 32, 1) and got[(256, 8, 1, 4)] == (4, 4, 1) and got[(4096, 4, 1, 8)] == (4, 64, 1)
     assert got[(4096, 8, 1, 4)] == (8, 32, 1) and got[(8192, 4, 1, 8)] == (8, 64, 1)
     assert got[(8192, 8, 1, 4)][0] == 0 and got[(1024, 128, 1, 4)][0] == 0            # 33 MB and more in many partial results
