@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <stddef.h>
+#include <math.h>
 
 #include "../../include/refreshkv.h"
 
@@ -248,13 +249,33 @@ static inline int select_parts(int64_t max_len, int64_t rows) {
 // is [B(i + 1), B(i)): B leaves t = i / parts of the K' ranks above it, as the histogram has it and, inside the bin that holds rank t,
 // as if its scores were spread evenly: `at`; `end` is where that bin ends and `above` the positions beyond.
 struct StretchBound { uint32_t at, end, above; };
-// `bin` (of images; scores >= 0 start at bin 1024) holds rank t: `above` positions in higher bins, `h` in this one, above < t <= above + h.
-__host__ __device__ static inline StretchBound stretch_bound(uint32_t t, uint32_t spare, uint32_t bin, uint32_t above, uint32_t h) {
-    const uint32_t width = 1u << kHistShift, end = ((bin + 1u) << kHistShift) - 0x80000000u;
+// The bin [end - width, end) holds rank t: `above` positions in higher bins, `h` in this one, above < t <= above + h.
+// `ratio`: how many times as dense its lower end is as its upper one.
+__host__ __device__ static inline StretchBound stretch_bound(uint32_t t, uint32_t spare, uint32_t end, uint32_t width, uint32_t above, uint32_t h, float ratio) {
     if (t - above == h) return {end - width, end - width, t};      // the whole bin: nothing to count
-    const float down = (float)(t + spare - above) * ((float)width / (float)h);
+    // (one thread's work while the others wait: reciprocals as they come)
+#ifdef __HIP_DEVICE_COMPILE__
+    float part = (float)(t + spare - above) * __builtin_amdgcn_rcpf((float)h);
+    if (ratio > 1.f) part = __builtin_amdgcn_logf(1.f + part * (ratio - 1.f)) * __builtin_amdgcn_rcpf(__builtin_amdgcn_logf(ratio));
+#else
+    float part = (float)(t + spare - above) / (float)h;
+    if (ratio > 1.f) part = log2f(1.f + part * (ratio - 1.f)) / log2f(ratio);
+#endif
+    const float down = part * (float)width;
     return {end - (down < (float)width ? (uint32_t)down : width), end, above};
 }
+// ... of a bin of the first-level histogram, from the bin above, `up` positions: four bins of equal width to an octave, twice that in the next.
+__host__ __device__ static inline float density_ratio(uint32_t bin, uint32_t h, uint32_t up) {
+    const float d = (bin & 3u) == 3u ? 0.5f * (float)up : (float)up;
+#ifdef __HIP_DEVICE_COMPILE__
+    const float r = (float)h * __builtin_amdgcn_rcpf(d);
+#else
+    const float r = (float)h / d;
+#endif
+    return up == 0 || !(r > 1.25f) ? 1.f : r < 16.f ? r : 16.f;
+}
+// Ranks by which the last part's estimate goes beyond K'.
+__host__ __device__ static inline uint32_t last_spare(uint32_t kprime) { return (kprime * 3u >> 3) + 16u; }
 // The lower end that a part starts with.  The last part's is an estimate, `floor` (the K'-th score's bin) what it may have to go down to;
 // in a bin of tens of millions of positions that estimate can fall on the part's own upper end `top`, and an empty
 // stretch would be taken for one without candidates: all of the bin then.

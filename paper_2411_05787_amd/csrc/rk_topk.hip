@@ -41,6 +41,8 @@ constexpr int kTopLoose = 64;                            // scores above the buc
 constexpr int kPairs = 256;                               // a part's runs up to here are compared each with each
 static_assert(kMaxCandidates / 2 * 4 <= 0xFFFF, "buckets of a part count positions in 16 bits");
 constexpr int kNonFinite = 1;                            // thread whose two bins of the histogram start at infinity
+constexpr int kFineFrom = 2;                             // a bin of more than this many times K' positions is looked at more closely
+constexpr int kPartWords = 8;                            // what a part knows of its stretch
 constexpr int kListTry = 4;                              // runs are listed for up to this many times cand_cap positions
 static_assert(kHistBins == 1 << 11, "first-level histogram is 11 bits wide");
 static_assert(kHistBins == 2 * kSelThreads, "the selection scans the histogram two bins per thread");
@@ -233,6 +235,7 @@ struct SelectRow {
     int cand_cap;
     int32_t* idx; float* sel_scores;        // [k]; sel_scores may be NULL
 
+    __device__ __forceinline__ uint32_t list_limit() const { return (uint32_t)min(kListTry * cand_cap, 0xFFFF); }
     // Vector v of the row as it lies in memory: a buffer, so that nothing branches around a load; behind `room` zeros.
     __device__ __forceinline__ float4 raw4(int v) const {
         const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(P), 0, room * 16, 0x00020000);
@@ -267,7 +270,7 @@ struct SelectLds {
     uint32_t* scan;                         // [kSelThreads / 64]
     uint32_t* out;                          // [4]
     uint32_t* count;                        // [1]
-    uint32_t* part;                         // [8]
+    uint32_t* part;                         // [kPartWords]
     uint16_t* tab;                          // [kHistBins] buckets of each first-level bin (allocated only if cand_cap > kAdaptiveFrom)
 
     __device__ __forceinline__ SelectLds(unsigned char* smem, int cand_cap) {
@@ -277,7 +280,7 @@ struct SelectLds {
         out = scan + kSelThreads / 64;
         count = out + 4;
         part = count + 1;
-        tab = reinterpret_cast<uint16_t*>(part + 8);
+        tab = reinterpret_cast<uint16_t*>(part + kPartWords);
     }
 };
 
@@ -385,12 +388,15 @@ __device__ __forceinline__ void rank_by_sorting(const SelectRow& row, const Sele
 // the candidates' scores into stretches of about the same count (bins of the histogram, cut linearly inside), and lists
 // and ranks the runs of its own stretch.  Where its ranks start follows from the histogram and the scores it counts between its
 // stretch and the next bin.  Nothing is handed over: the workgroups meet only in the ticket whose last drawer clears the
-// histogram, and does the row alone should a stretch not have fitted some workgroup's list (many equal scores).
-// True: this workgroup is that one.
+// histogram, and does the row alone should a stretch not have fitted some workgroup's list (many equal scores).  Where the
+// histogram says it (K-th score zero or negative, infinities), the first part does the row, and does not wait for the others.
+// What is left to do for this workgroup:
+enum SelectLeft { kRowDone, kRowAnew, kRowKnown };       // nothing; the row; the row, with what the histogram says in place (it is cleared by another)
 // What bounds it is latency: us after the first workgroup's first instruction, 8 rows of 32768 positions, K = 2048, medians:
 // lengths 0.7, histogram and stretch 2.6, row looked through 3.8, runs listed 5.5, ranked 6.7, written 7.1 (the launch 9 - 10
 // against 10.6 before); of 131072, K = 8192, 32 parts: 0.8, 2.7, 6.6, 10.5 (512 KB through one CU), 11.9, 12.4.
-__device__ __forceinline__ bool select_part(const SelectRow& row, const SelectLds& lds, int32_t* __restrict__ ticket, const int part, const int lg_parts) {
+__device__ __forceinline__ SelectLeft select_part(const SelectRow& row, const SelectLds& lds, int32_t* __restrict__ ticket, const int part, const int lg_parts,
+                                                  uint2& h01) {
     const int tid = threadIdx.x, n = row.n, kprime = row.kprime, nvec = (n + 3) >> 2, cand_cap = row.cand_cap;
     uint64_t* const sKeys = lds.keys;
     uint32_t *const sHist = lds.hist, *const sScan = lds.scan, *const sOut = lds.out, *const sCount = lds.count, *const sPart = lds.part;
@@ -400,7 +406,7 @@ __device__ __forceinline__ bool select_part(const SelectRow& row, const SelectLd
     // This thread's two bins of the first-level histogram are requested first, the row's scores (whatever its length: rows have room
     // for max_len) behind them: the bins are counted while the scores are on their way.
     const int rt = kSelThreads - 1 - tid;
-    const uint2 h01 = *reinterpret_cast<const uint2*>(gh + 2 * rt);
+    h01 = *reinterpret_cast<const uint2*>(gh + 2 * rt);
     constexpr int NV = kSelHeld;
     float4 held[NV];
 #pragma unroll
@@ -412,6 +418,7 @@ __device__ __forceinline__ bool select_part(const SelectRow& row, const SelectLd
     if (tid == 0) { *sCount = 0; sPart[5] = 0; sPart[6] = 0; sPart[7] = 0; }
     for (int i = tid; i < kBuckets + 1; i += kSelThreads) sHist[i] = 0;
     const uint32_t h0 = h01.x, h1 = h01.y;
+    const uint32_t t0 = ((uint32_t)kprime * (uint32_t)part) >> lg_parts, t1 = ((uint32_t)kprime * (uint32_t)(part + 1)) >> lg_parts;
     {
         uint32_t total;
         const uint32_t incl = block_inclusive_scan<kSelThreads>(h0 + h1, sScan, &total);   // entries in bins >= 2 rt
@@ -426,11 +433,14 @@ __device__ __forceinline__ bool select_part(const SelectRow& row, const SelectLd
         if (abv < kk2 && kk2 <= incl) sOut[3] = (uint32_t)(2 * rt + (abv + h1 >= kk2 ? 1 : 0));
         {                                       // (stretches in bits of scores >= 0)
             if (tid == kNonFinite) sPart[4] = incl;
-            const uint32_t t0 = (kk1 * (uint32_t)part) >> lg_parts, t1 = (kk1 * (uint32_t)(part + 1)) >> lg_parts;
-            const uint32_t spare = part + 1 == 1 << lg_parts ? (kk1 * 3u >> 3) + 16u : 0u;        // the last part: that many ranks more
+            const uint32_t spare = part + 1 == 1 << lg_parts ? last_spare(kk1) : 0u;
+            // (the bin above thread 64 i's upper one is another wavefront's: no ratio there)
+            const uint32_t h2 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)h0, 0x138, 0xF, 0xF, true);      // wave_shr:1
             auto bound = [&](uint32_t t, uint32_t spare) {
                 const bool upper = abv + h1 >= t;
-                return stretch_bound(t, spare, (uint32_t)(2 * rt + (upper ? 1 : 0)), upper ? abv : abv + h1, upper ? h1 : h0);
+                const uint32_t bin = (uint32_t)(2 * rt + (upper ? 1 : 0)), h = upper ? h1 : h0;
+                return stretch_bound(t, spare, ((bin + 1u) << kHistShift) - 0x80000000u, 1u << kHistShift, upper ? abv : abv + h1, h,
+                                     density_ratio(bin, h, upper ? h2 : h1));
             };
             if (t0 == 0) {                  // (the top, or fewer ranks than parts)
                 if (tid == 0) { sPart[0] = sPart[1] = 0x80000000u; sPart[2] = 0; }
@@ -446,18 +456,79 @@ __device__ __forceinline__ bool select_part(const SelectRow& row, const SelectLd
         }
         lds_barrier();
     }
-    // the lowest and highest candidates' bits (scores as whole numbers; a row whose threshold lies among negative scores, or
-    // with infinities or NaN, is the last workgroup's alone)
-    const uint32_t b1 = sOut[0], key_top = (sOut[3] + 1u) << kHistShift;
+    // the lowest and highest candidates' bits (scores as whole numbers)
+    if (sOut[0] <= (uint32_t)kHistBins / 2 || sPart[4] != 0) {      // the same in every part
+        lds_barrier();
+        if (tid == 0) sPart[4] = (uint32_t)__hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        if (sPart[4] == (1u << lg_parts) - 1u) {         // everybody has read the histogram
+            if (tid == 0) __hip_atomic_store(ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            gh[2 * tid] = 0; gh[2 * tid + 1] = 0;
+        }
+        return part == 0 ? kRowKnown : kRowDone;
+    }
+    const uint32_t b1 = sOut[0], above1 = sOut[1], in1 = sOut[2], key_top = (sOut[3] + 1u) << kHistShift;
     // The K'-th score lies anywhere in its bin, and that bin may hold many times the ranks that are left: the last part starts
     // with an estimate of its lower end and takes the rest of the bin only if too few positions turn up.  (131072 positions with half of
     // the keys near 64 centroids, K = 8192: 4136 runs in the last part without it, 350 in the others; a step of one layer 105.8 ->
     // 101.3 us.  The second look at the row costs 4 - 8 us: with 3/16 of the ranks to spare instead of 3/8 that step takes 110, a window
     // of 32 queries over 32768 positions 70.9 instead of 67.7.)
-    const uint32_t hi = sPart[0], end = sPart[1], floor = part + 1 < (1 << lg_parts) ? sPart[3] : (b1 << kHistShift) - 0x80000000u;
-    uint32_t lo = stretch_low(sPart[3], floor, hi), top = hi, top_end = end;       // the stretch so far, and what is looked for in this pass over the row
-    bool bad = b1 < (uint32_t)kHistBins / 2 || sPart[4] != 0;
-    while (!bad && lo < top) {
+    const bool last = part + 1 == 1 << lg_parts;
+    bool hopeless = false;
+    uint32_t hi = sPart[0], end = sPart[1], above_end = sPart[2], estimate = sPart[3], floor = last ? (b1 << kHistShift) - 0x80000000u : estimate;
+    if (in1 > (uint32_t)(kprime * kFineFrom) && t1 > above1) {
+        // The K'-th score's bin (no other can) holds many times the ranks there are, which says little about where in it they lie:
+        // one look at the row counts its scores by the next 11 bits.  Scores that differ little, us per call: one workgroup or spread-out listing
+        // / parts without this look, bins taken as even / now: e^(0.05 N(0, 1)), pooled by 7, 8 rows of 32768, K = 2048: 26.8 / 32.3 / 17.8, 4 of
+        // 131072, K = 8192: 59.5 / 81.8 / 33.8, 8 of 2000, K = 125: 13.3 / 20.2 / 14.0; e^(0.25 N(0, 1)), where the densities of the bins do: 16.1 /
+        // 18.7 / 15.2, 28.0 / 36.1 / 24.4.  (Equal scores throughout: 8 of 2000 29.3 / 31.8 / 34.5, of 32768 100 / 101 / 104.)
+        constexpr int kSub = kHistShift - 11;
+        const uint32_t from = (b1 << kHistShift) - 0x80000000u;
+        for (int v0 = 0; v0 < nvec; v0 += NV * kSelThreads) {
+            float4 next[NV];
+#pragma unroll
+            for (int u = 0; u < NV; ++u) next[u] = row.raw4(v0 + (NV + u) * kSelThreads + tid);
+#pragma unroll
+            for (int u = 0; u < NV; ++u) {
+                if (v0 + u * kSelThreads >= nvec) break;
+                const int in = n - ((v0 + u * kSelThreads + tid) << 2);         // positions of the vector inside the row
+                const uint32_t none = 0xBF800000u;
+                const uint32_t a = in > 0 ? __float_as_uint(held[u].x) : none, b = in > 1 ? __float_as_uint(held[u].y) : none;
+                const uint32_t c = in > 2 ? __float_as_uint(held[u].z) : none, d = in > 3 ? __float_as_uint(held[u].w) : none;
+                const int ed = d == c ? 1 : 0, ec = c == b ? 1 + ed : 0, eb = b == a ? 1 + ec : 0;
+                auto count = [&](uint32_t bits, int len) {
+                    if (bits - from < 1u << kHistShift) atomicAdd(&sHist[(bits - from) >> kSub], (uint32_t)len);
+                };
+                count(a, 1 + eb);
+                if (b != a) count(b, 1 + ec);
+                if (c != b) count(c, 1 + ed);
+                if (d != c) count(d, 1);
+            }
+#pragma unroll
+            for (int u = 0; u < NV; ++u) held[u] = next[u];
+        }
+        // (so many in a 2^-13th of an octave are equal scores: some part's list would not do)
+        auto closer = [&](uint32_t t, uint32_t spare) {
+            find_bin_from_top<kSelThreads, 1 << 11>(sHist, t - above1, sScan, sOut);
+            const uint32_t sub = sOut[0], over = sOut[1], h = sHist[sub];
+            hopeless = hopeless || h > (uint32_t)cand_cap;
+            return stretch_bound(t, spare, from + ((sub + 1u) << kSub), 1u << kSub, above1 + over, h, 1.f);
+        };
+        lds_barrier();
+        if (t0 > above1) {
+            const StretchBound b = closer(t0, 0u);
+            hi = b.at; end = b.end; above_end = b.above;
+        }
+        const StretchBound b = closer(t1, last ? last_spare((uint32_t)kprime) : 0u);
+        estimate = b.at;
+        floor = last ? b.end - (b.above == t1 ? 0u : 1u << kSub) : estimate;       // (above all ranks: the whole of its bin)
+        lds_barrier();
+        for (int i = tid; i < kBuckets + 1; i += kSelThreads) sHist[i] = 0;
+#pragma unroll
+        for (int u = 0; u < NV; ++u) held[u] = row.raw4(u * kSelThreads + tid);
+    }
+    uint32_t lo = stretch_low(estimate, floor, hi), top = hi, top_end = end;       // the stretch so far, and what is looked for in this pass over the row
+    while (lo < top && !hopeless) {
         // Bits of scores as whole numbers, from the stretch's lowest.  A vector of four positions with none in the stretch or
         // between it and the end of its bin is passed over after one comparison of the least; the numbers of the others are
         // queued, so that what is left to do with them takes every lane.
@@ -535,7 +606,7 @@ __device__ __forceinline__ bool select_part(const SelectRow& row, const SelectLd
         inside = wave_inclusive_scan(inside);
         if ((tid & 63) == 63 && inside != 0) atomicAdd(&sPart[7], inside);
         lds_barrier();
-        if (sPart[2] + sPart[6] + sPart[7] >= (uint32_t)kprime) break;
+        if (above_end + sPart[6] + sPart[7] >= (uint32_t)kprime) break;
         if (sPart[5] > (uint32_t)cand_cap) break;       // (the queue was too short: what was counted is not all)
         top = top_end = lo;
         lo = floor;
@@ -546,8 +617,8 @@ __device__ __forceinline__ bool select_part(const SelectRow& row, const SelectLd
         for (int u = 0; u < NV; ++u) held[u] = row.raw4(u * kSelThreads + tid);
     }
     lds_barrier();
-    const uint32_t n_items = *sCount, base = sPart[2] + sPart[6];
-    bad = bad || sPart[5] > (uint32_t)cand_cap || n_items > (uint32_t)list_cap;
+    const uint32_t n_items = *sCount, base = above_end + sPart[6];
+    const bool bad = hopeless || sPart[5] > (uint32_t)cand_cap || n_items > (uint32_t)list_cap;
     uint32_t seen = 0;                      // (every thread has read the histogram; the answer is waited for behind the ranking)
     if (tid == 0) seen = (uint32_t)__hip_atomic_fetch_add(ticket, bad ? 0x10001 : 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (!bad && n_items != 0) {
@@ -580,20 +651,20 @@ __device__ __forceinline__ bool select_part(const SelectRow& row, const SelectLd
     if (tid == 0) sOut[0] = seen + (bad ? 0x10000u : 0u);
     __syncthreads();
     const uint32_t drawn = sOut[0];
-    if ((drawn & 0xFFFFu) != (1u << lg_parts) - 1u) return false;
+    if ((drawn & 0xFFFFu) != (1u << lg_parts) - 1u) return kRowDone;
     // last to arrive: the workspace is left clean
     if (tid == 0) __hip_atomic_store(ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (drawn >= 0x10000u) {                // (the ranks that others have written come out the same)
         __syncthreads();
-        return true;
+        return kRowAnew;
     }
     gh[2 * tid] = 0; gh[2 * tid + 1] = 0;
-    return false;
+    return kRowDone;
 }
 
-// The whole selection of one row by one workgroup.
+// The whole selection of one row by one workgroup.  known: h01 and lds.out are what the histogram says of it, and LDS is as below after the scan.
 template <bool ADAPT>                    // ADAPT: compiled with the histogram-driven bucket layout (large K only)
-__device__ __forceinline__ void select_row(const SelectRow& row, const SelectLds& lds) {
+__device__ __forceinline__ void select_row(const SelectRow& row, const SelectLds& lds, uint2 h01, const bool known) {
     const int tid = threadIdx.x, n = row.n, kprime = row.kprime, nvec = (n + 3) >> 2, cand_cap = row.cand_cap;
     uint64_t* const sKeys = lds.keys;
     uint32_t *const sHist = lds.hist, *const sScan = lds.scan, *const sOut = lds.out, *const sCount = lds.count;
@@ -603,7 +674,7 @@ __device__ __forceinline__ void select_row(const SelectRow& row, const SelectLds
     // The first 32 scores of every thread (the whole row up to 32768 positions) are requested now, behind this thread's two bins of
     // the histogram, 16-byte loads all in flight together, and stay in registers.
     const int rt = kSelThreads - 1 - tid;
-    const uint2 h01 = *reinterpret_cast<const uint2*>(gh + 2 * rt);
+    if (!known) h01 = *reinterpret_cast<const uint2*>(gh + 2 * rt);
     constexpr int NV = kSelHeld;
     float4 held[NV];
 #pragma unroll
@@ -613,10 +684,10 @@ __device__ __forceinline__ void select_row(const SelectRow& row, const SelectLds
     // the bin b1 that holds the K'-th largest score (with the count above it), and the bin that
     // holds the kTopLoose-th largest, which bounds the bucketed range from above so that the one
     // bucket for "everything above" stays small (its items are ranked by a loop over the bucket).
-    if (tid == 0) *sCount = 0;
-    for (int i = tid; i < kBuckets + 1; i += kSelThreads) sHist[i] = 0;     // bucket sizes of the fast path
     const uint32_t h0 = h01.x, h1 = h01.y;
-    {
+    if (!known) {
+        if (tid == 0) *sCount = 0;
+        for (int i = tid; i < kBuckets + 1; i += kSelThreads) sHist[i] = 0;     // bucket sizes of the fast path
         uint32_t total;
         const uint32_t incl = block_inclusive_scan<kSelThreads>(h0 + h1, sScan, &total);   // entries in bins >= 2 rt
         const uint32_t abv = incl - (h0 + h1);
@@ -640,7 +711,7 @@ __device__ __forceinline__ void select_row(const SelectRow& row, const SelectLds
     // The list holds runs, so it may have room where the positions are too many: up to
     // kListTry * cand_cap positions the runs are listed anyway, counted as they are, and the list
     // is used if they fit.  (Bucket offsets below are counted in 16 bits: 65535 positions at most.)
-    const bool try_list = count_ge <= (uint32_t)min(kListTry * cand_cap, 0xFFFF);
+    const bool try_list = count_ge <= row.list_limit();
 
     // The runs of candidates inside one vector of four scores (positions j .. j + 3; a candidate is
     // a score >= thr; scores are >= +0 and -0 never occurs, so equal scores have equal bits and the
@@ -835,8 +906,9 @@ void select_body(const float* __restrict__ pooled, int64_t pooled_stride, const 
         if (part == 0) row.fill_rest();
         return;
     }
-    if (lg_parts > 0 && !select_part(row, lds, sel_counters + bg * 2, part, lg_parts)) return;
-    select_row<ADAPT>(row, lds);
+    uint2 h01 = make_uint2(0, 0);
+    const SelectLeft left = lg_parts > 0 ? select_part(row, lds, sel_counters + bg * 2, part, lg_parts, h01) : kRowAnew;
+    if (left != kRowDone) select_row<ADAPT>(row, lds, h01, left == kRowKnown);
 }
 
 // Grid (KV heads, parts, sequences): consecutive workgroups go to the 8 XCDs in turn, so with 8 KV heads (or 4, or 16) the parts of
@@ -907,7 +979,7 @@ static int launch_select(const rk_geom* geom, const int32_t* seq_lens, int32_t m
     // the sort kernel may need more than the default dynamic LDS; the per-bin bucket table is part
     // of it only where there can be kAdaptiveFrom candidates
     const size_t lds = (size_t)ws.cand_cap * sizeof(uint64_t) +
-                       (2 * (kBuckets + 1) + kSelThreads / 64 + 4 + 1 + 8) * sizeof(uint32_t) +
+                       (2 * (kBuckets + 1) + kSelThreads / 64 + 4 + 1 + kPartWords) * sizeof(uint32_t) +
                        (ADAPT ? kHistBins * sizeof(uint16_t) : 0);
     static size_t lds_allowed = 48 * 1024;       // grows monotonically (one per instantiation)
     if (lds > lds_allowed) {
@@ -930,7 +1002,7 @@ static int launch_select_batched(const rk_geom* geom, int n_layers, const Worksp
                                  int32_t pred_val, hipStream_t st) {
     const int cand_cap = wss[0].cand_cap;
     const size_t lds = (size_t)cand_cap * sizeof(uint64_t) +
-                       (2 * (kBuckets + 1) + kSelThreads / 64 + 4 + 1 + 8) * sizeof(uint32_t) +
+                       (2 * (kBuckets + 1) + kSelThreads / 64 + 4 + 1 + kPartWords) * sizeof(uint32_t) +
                        (ADAPT ? kHistBins * sizeof(uint16_t) : 0);
     static size_t lds_allowed = 48 * 1024;
     if (lds > lds_allowed) {

@@ -636,18 +636,26 @@ def _select_scores(name, rows, n, g):
         w = torch.where(torch.rand(*rows, n, generator=g) < 0.01, w, torch.zeros_like(w))
     elif name == "one_bin":                # all scores in one bin of the histogram
         w = 1.0 + 0.1 * torch.rand(*rows, n, generator=g)
+    elif name == "narrow":                 # a few bins with many times K positions each
+        w = torch.exp(torch.randn(*rows, n, generator=g) * 0.05 - 10)
+    elif name == "narrow2":
+        w = torch.exp(torch.randn(*rows, n, generator=g) * 0.25 - 10)
+    elif name == "steps":                  # ... in which scores come in clusters
+        w = (1.0 + 0.25 * torch.rand(*rows, n, generator=g).mul(5).floor() / 5) * (1 + 2.0 ** -16 * torch.rand(*rows, n, generator=g))
     elif name == "infinite":
         w[..., 5], w[..., n // 2] = float("inf"), float("inf")
     return w
 
 
-# (scores, B, Hkv, n, k, pool): 8 / 4 / 2 / 1 workgroups per row, fewer ranks than workgroups, fewer positions than ranks, vectors of
+# Bins with more than twice K positions, which a part looks into ("narrow", "one_bin", "steps"), (scores, B, Hkv, n, k, pool): 8 / 4 / 2 / 1 workgroups per row, fewer ranks than workgroups, fewer positions than ranks, vectors of
 # four and rounds of 32768 positions that end in the row, more than 256 runs in a stretch
 SELECT_EDGES = [("normal", 1, 1, 1, 1, 1), ("normal", 1, 2, 9, 3, 7), ("normal", 1, 3, 31, 100, 7), ("normal", 1, 8, 1027, 9, 1), ("normal", 2, 16, 4099, 300, 7),
                 ("normal", 5, 8, 5001, 700, 3), ("normal", 16, 8, 3001, 257, 7), ("normal", 33, 8, 1025, 64, 7), ("normal", 1, 8, 32771, 2048, 7),
                 ("normal", 1, 4, 65537, 8192, 1), ("normal", 1, 2, 98305, 16384, 7), ("levels", 1, 8, 20001, 3000, 1), ("levels", 3, 8, 20001, 900, 7),
                 ("equal", 1, 8, 5003, 500, 7), ("equal", 1, 4, 40001, 12000, 1), ("mostly_zero", 1, 8, 30001, 2000, 1), ("one_bin", 1, 8, 30001, 2000, 1),
-                ("one_bin", 2, 8, 9001, 1000, 7), ("infinite", 1, 8, 9001, 300, 7)]
+                ("one_bin", 2, 8, 9001, 1000, 7), ("infinite", 1, 8, 9001, 300, 7), ("narrow", 1, 8, 2001, 125, 1), ("narrow", 1, 8, 33001, 1500, 7), ("narrow", 1, 1, 70003, 9, 1),
+                ("narrow2", 1, 4, 131073, 8192, 7), ("narrow2", 3, 16, 9001, 500, 1), ("narrow2", 20, 8, 5001, 64, 7), ("steps", 1, 8, 20001, 1000, 1),
+                ("steps", 1, 4, 40001, 4001, 1), ("steps", 2, 16, 5003, 100, 7)]
 
 
 @pytest.mark.parametrize("case", SELECT_EDGES, ids=["%s_%dx%d_%d_k%d_w%d" % c for c in SELECT_EDGES])

@@ -48,16 +48,16 @@ int main() {
     // down to where the last part starts, or may have to go down to
     for (long h : {1L, 2L, 3L, 7L, 8L, 100L, 5000L, 100000L, 1L << 21, 20000000L, 40000000L, 60000000L, 100000000L, 1L << 28}) for (int lg : {1, 2, 3}) {
         long open = 0, order = 0, empty = 0;
-        for (uint32_t above : {0u, 1u, 13u, 4096u}) for (uint32_t k = above + 1; k <= above + h && k <= 16384; k += k < above + 300 ? 1 : 97) {
-            const uint32_t bin = 1500, floor = (bin << kHistShift) - 0x80000000u;
-            uint32_t upper = floor + (1u << kHistShift);          // where the bins above end
+        for (float ratio : {1.f, 2.f, 16.f}) for (uint32_t above : {0u, 1u, 13u, 4096u}) for (uint32_t k = above + 1; k <= above + h && k <= 16384; k += k < above + 300 ? 1 : 97) {
+            const uint32_t width = 1u << kHistShift, floor = (1500u << kHistShift) - 0x80000000u;
+            uint32_t upper = floor + width;                       // where the bins above end
             for (int part = 0; part < 1 << lg; ++part) {
                 const uint32_t t0 = (k * (uint32_t)part) >> lg, t1 = (k * (uint32_t)(part + 1)) >> lg;
                 const bool last = part + 1 == 1 << lg;
-                const uint32_t top = t0 > above ? stretch_bound(t0, 0, bin, above, (uint32_t)h).at : upper;
+                const uint32_t top = t0 > above ? stretch_bound(t0, 0, floor + width, width, above, (uint32_t)h, ratio).at : upper;
                 order += top != upper;                            // the stretch above ended there
                 if (t1 <= above) continue;
-                const uint32_t at = stretch_bound(t1, last ? (k * 3u >> 3) + 16u : 0u, bin, above, (uint32_t)h).at;
+                const uint32_t at = stretch_bound(t1, last ? last_spare(k) : 0u, floor + width, width, above, (uint32_t)h, ratio).at;
                 order += at > top || at < floor;
                 const uint32_t low = stretch_low(at, last ? floor : at, top);
                 open += last && low >= top && low != floor;       // ranks between the stretch and the floor that nobody takes
