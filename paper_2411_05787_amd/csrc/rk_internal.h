@@ -238,7 +238,7 @@ static inline int topk_cand_cap(int64_t k) {
 // 65536, K = 8192: 33.4 / 28.0 / 26.6 / 25.8 / 36.7; 64 rows of 8192: 14.7 / 14.3 / 14.0 / 20.3; 128 rows of 16384: 22.2 / 21.9 / 29.9.
 // (What this replaced, every row's candidates listed by a workgroup per 4096 positions and ranked by the last to arrive, one
 // workgroup alone up to 8192: 16.0, 28.9, 13.4, 17.8, 42.0, 15.3, 32.9.)
-static inline int select_parts(int64_t max_len, int64_t rows) {
+static inline int select_parts(int64_t rows) {
     int64_t parts = 8;
     while (parts > 1 && parts * rows > kComputeUnits) parts /= 2;
     return (int)parts;
@@ -247,7 +247,9 @@ static inline int select_parts(int64_t max_len, int64_t rows) {
 // ---- stretches of scores that the parts of a row's selection take (select_part, rk_topk.hip) ----
 // Scores >= 0 as whole numbers (their bits), the first-level histogram's bins of 2^kHistShift of them.  The stretch of part i
 // is [B(i + 1), B(i)): B leaves t = i / parts of the K' ranks above it, as the histogram has it and, inside the bin that holds rank t,
-// as if its scores were spread evenly: `at`; `end` is where that bin ends and `above` the positions beyond.
+// as if its scores thinned out upwards at the rate at which they do from there to the bin above: `at`; `end` is where that bin ends and
+// `above` the positions beyond.  Parts that share a bound work it out from the same numbers; ranks are counted, so that a bound
+// that is off costs time and no more.
 struct StretchBound { uint32_t at, end, above; };
 // The bin [end - width, end) holds rank t: `above` positions in higher bins, `h` in this one, above < t <= above + h.
 // `ratio`: how many times as dense its lower end is as its upper one.
@@ -283,6 +285,18 @@ __host__ __device__ static inline uint32_t stretch_low(uint32_t estimate, uint32
     return estimate <= floor || estimate >= top ? floor : estimate;
 }
 
+// A few long rows are listed by a workgroup per 4096 positions and ranked by the last to arrive instead (select_listed_kernel): parts all read the whole
+// row, which takes a CU 40 us per million positions and leaves the chip idle; ranking K positions in one workgroup costs more than
+// in eight.  `rows`: (sequence, KV head) pairs in the launch.  us per call of rk_topk_select, parts / listed: one row of 98304, K = 512: 16.5 /
+// 14.5, of 1048576: 67 / 33, of 4194304: 236 / 106; 4 rows of 131072, K = 4096: 20.9 / 18.8, of 1048576: 84 / 72; K = 8192: one row of 131072:
+// 21.3 / 21.1, of 262144: 29.4 / 23.8, 4 of 131072: 23.1 / 24.3, of 262144: 33.5 / 31.5; K = 16384: one row of 196608: 30 / 34, of 393216: 41 / 34;
+// 6 rows of 196608, K = 2048: 0.92 of the parts' time, K = 8192: 1.05; 8 rows: 1.0 to 1.45.
+constexpr int kListRows = 6;
+constexpr int64_t kListFrom = 98304;
+static inline bool select_listed(int64_t max_len, int64_t k, int64_t rows) {
+    return rows <= (k <= 4096 ? kListRows : 4) && max_len >= kListFrom && max_len >= 20 * k;
+}
+
 // Device workspace, carved in this order (every region 256-byte aligned).  The regions up to and
 // including tag_rows must be zero when a workspace is first used (rk_workspace_init clears the
 // whole workspace once); the counters and histograms are left cleared by the kernels that use
@@ -291,7 +305,8 @@ __host__ __device__ static inline uint32_t stretch_low(uint32_t estimate, uint32
 //   counters  int32 [B*Hkv][kCounterStride]  one 128-byte line each: arrival ticket of the split attention
 //                                            kernel (word 0), the trigger's ticket (1), slices left over
 //                                            (2, 3), number of partial results of the last full pass (4)
-//   sel_counters int32 [B*Hkv][2]            arrival tickets of the selection (word 0)
+//   sel_counters int32 [B*Hkv][2]            arrival tickets of the selection (word 0); of its listing form the
+//                                            runs listed (0) and the tickets (1)
 //   epochs    uint32 [B*Hkv]                 call number of the last merge inside a split kernel
 //   hist      uint32 [B*Hkv][kHistBins]      first-level histogram of the pooled scores
 //   tag_rows  16 B  [B*Hkv][kTagSlots][G*64]  tagged partial results of the kernels that merge
@@ -302,6 +317,7 @@ __host__ __device__ static inline uint32_t stretch_low(uint32_t estimate, uint32
 //   pooled    fp32  [B*Hkv][max_len up to a multiple of 4]   group-max, pooled scores of the selection
 //   scores    fp32  [B*Hq][max_len up to a multiple of 4]    raw scores between the two kernels of
 //                                                            rk_full_attn_select
+//   cand_list uint64 [B*Hkv][cand_cap]       (few long rows only) runs of candidates of the selection's listing form
 constexpr int kCounterStride = 32;       // int32 between two arrival counters: one 128-byte line each
 constexpr int kCountWord = 4;
 constexpr int kRaggedMaxBatch = 64;      // most sequences whose workgroups are shared out by length
@@ -317,6 +333,7 @@ struct Workspace {
     float* part_o;
     float* pooled;
     float* scores;
+    uint64_t* cand_list;  // NULL: more rows, or shorter ones, than the listing form takes
     int cand_cap;         // candidate slots the selection sorts in LDS
     int max_chunks;       // nch above
     size_t total;
@@ -472,6 +489,10 @@ static inline Workspace carve(const rk_geom* g, int64_t max_len, int64_t max_k, 
     w.pooled = (float*)(p + off);     off += align_up(problems * (size_t)pooled_row_stride(max_len > 0 ? max_len : 1) * sizeof(float), 256);
     w.scores = (float*)(p + off);     off += align_up((size_t)g->batch * g->n_q_heads * (size_t)pooled_row_stride(max_len > 0 ? max_len : 1) * sizeof(float), 256);
     w.cand_cap = topk_cand_cap(max_k > 0 ? max_k : 1);
+    w.cand_list = nullptr;
+    if (problems <= (size_t)kListRows && max_len >= kListFrom) {
+        w.cand_list = (uint64_t*)(p + off); off += align_up(problems * (size_t)w.cand_cap * sizeof(uint64_t), 256);
+    }
     w.total = off;
     return w;
 }

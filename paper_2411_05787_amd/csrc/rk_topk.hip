@@ -662,9 +662,56 @@ __device__ __forceinline__ SelectLeft select_part(const SelectRow& row, const Se
     return kRowDone;
 }
 
+// From the histogram, in one scan from the top bin down (thread 0 owns the top two bins):
+// the bin b1 that holds the K'-th largest score (with the count above it), and the bin that
+// holds the kTopLoose-th largest, which bounds the bucketed range from above so that the one
+// bucket for "everything above" stays small (its items are ranked by a loop over the bucket).
+__device__ __forceinline__ void scan_histogram(const SelectRow& row, const SelectLds& lds, uint2 h01) {
+    const int tid = threadIdx.x, rt = kSelThreads - 1 - tid;
+    const uint32_t h0 = h01.x, h1 = h01.y;
+    if (tid == 0) *lds.count = 0;
+    for (int i = tid; i < kBuckets + 1; i += kSelThreads) lds.hist[i] = 0;     // bucket sizes of the fast path
+    uint32_t total;
+    const uint32_t incl = block_inclusive_scan<kSelThreads>(h0 + h1, lds.scan, &total);   // entries in bins >= 2 rt
+    const uint32_t abv = incl - (h0 + h1);
+    const uint32_t kk1 = (uint32_t)row.kprime, kk2 = min((uint32_t)row.kprime, (uint32_t)kTopLoose);
+    if (abv < kk1 && kk1 <= incl) {
+        const bool upper = abv + h1 >= kk1;
+        lds.out[0] = (uint32_t)(2 * rt + (upper ? 1 : 0));
+        lds.out[1] = upper ? abv : abv + h1;
+        lds.out[2] = upper ? h1 : h0;
+    }
+    if (abv < kk2 && kk2 <= incl) lds.out[3] = (uint32_t)(2 * rt + (abv + h1 >= kk2 ? 1 : 0));
+}
+
+// The runs of candidates inside one vector of four scores (positions j .. j + 3; a candidate is
+// a score >= thr; scores are >= +0 and -0 never occurs, so equal scores have equal bits and the
+// order-preserving image is the bit pattern with the top bit set): count_runs() counts them,
+// visit_runs() calls visit(image, first position, length) for each, in position order.
+__device__ __forceinline__ uint32_t count_runs(const float4 x, float thr) {
+    const uint32_t a = __float_as_uint(x.x), b = __float_as_uint(x.y), c = __float_as_uint(x.z), d = __float_as_uint(x.w);
+    return (x.x >= thr ? 1u : 0u) + (x.y >= thr && b != a ? 1u : 0u) + (x.z >= thr && c != b ? 1u : 0u) +
+           (x.w >= thr && d != c ? 1u : 0u);
+}
+template <class Visit>
+__device__ __forceinline__ void visit_runs(const float4 x, int j, float thr, Visit&& visit) {
+    const uint32_t a = __float_as_uint(x.x), b = __float_as_uint(x.y), c = __float_as_uint(x.z), d = __float_as_uint(x.w);
+    const int ed = d == c ? 1 : 0;                       // positions after j + 2 with its score
+    const int ec = c == b ? 1 + ed : 0;                  // ... after j + 1
+    const int eb = b == a ? 1 + ec : 0;                  // ... after j
+    if (x.x >= thr) visit(a | 0x80000000u, j, 1 + eb);
+    if (x.y >= thr && b != a) visit(b | 0x80000000u, j + 1, 1 + ec);
+    if (x.z >= thr && c != b) visit(c | 0x80000000u, j + 2, 1 + ed);
+    if (x.w >= thr && d != c) visit(d | 0x80000000u, j + 3, 1);
+}
+static_assert(kRunMax == 4, "runs are found inside one float4");
+
+// The runs of a row's candidates that lds.keys holds already, or:
+constexpr int kNotListed = -1, kTooManyRuns = -2;
+
 // The whole selection of one row by one workgroup.  known: h01 and lds.out are what the histogram says of it, and LDS is as below after the scan.
 template <bool ADAPT>                    // ADAPT: compiled with the histogram-driven bucket layout (large K only)
-__device__ __forceinline__ void select_row(const SelectRow& row, const SelectLds& lds, uint2 h01, const bool known) {
+__device__ __forceinline__ void select_row(const SelectRow& row, const SelectLds& lds, uint2 h01, const bool known, const int listed) {
     const int tid = threadIdx.x, n = row.n, kprime = row.kprime, nvec = (n + 3) >> 2, cand_cap = row.cand_cap;
     uint64_t* const sKeys = lds.keys;
     uint32_t *const sHist = lds.hist, *const sScan = lds.scan, *const sOut = lds.out, *const sCount = lds.count;
@@ -677,28 +724,14 @@ __device__ __forceinline__ void select_row(const SelectRow& row, const SelectLds
     if (!known) h01 = *reinterpret_cast<const uint2*>(gh + 2 * rt);
     constexpr int NV = kSelHeld;
     float4 held[NV];
+    if (listed < 0) {
 #pragma unroll
-    for (int u = 0; u < NV; ++u) held[u] = row.load4(u * kSelThreads + tid);
+        for (int u = 0; u < NV; ++u) held[u] = row.load4(u * kSelThreads + tid);
+    }
 
-    // From the histogram, in one scan from the top bin down (thread 0 owns the top two bins):
-    // the bin b1 that holds the K'-th largest score (with the count above it), and the bin that
-    // holds the kTopLoose-th largest, which bounds the bucketed range from above so that the one
-    // bucket for "everything above" stays small (its items are ranked by a loop over the bucket).
     const uint32_t h0 = h01.x, h1 = h01.y;
     if (!known) {
-        if (tid == 0) *sCount = 0;
-        for (int i = tid; i < kBuckets + 1; i += kSelThreads) sHist[i] = 0;     // bucket sizes of the fast path
-        uint32_t total;
-        const uint32_t incl = block_inclusive_scan<kSelThreads>(h0 + h1, sScan, &total);   // entries in bins >= 2 rt
-        const uint32_t abv = incl - (h0 + h1);
-        const uint32_t kk1 = (uint32_t)kprime, kk2 = min((uint32_t)kprime, (uint32_t)kTopLoose);
-        if (abv < kk1 && kk1 <= incl) {
-            const bool upper = abv + h1 >= kk1;
-            sOut[0] = (uint32_t)(2 * rt + (upper ? 1 : 0));
-            sOut[1] = upper ? abv : abv + h1;
-            sOut[2] = upper ? h1 : h0;
-        }
-        if (abv < kk2 && kk2 <= incl) sOut[3] = (uint32_t)(2 * rt + (abv + h1 >= kk2 ? 1 : 0));
+        scan_histogram(row, lds, h01);
         gh[2 * rt] = 0; gh[2 * rt + 1] = 0;                     // cleared for the next call
         __syncthreads();
     }
@@ -712,27 +745,6 @@ __device__ __forceinline__ void select_row(const SelectRow& row, const SelectLds
     // kListTry * cand_cap positions the runs are listed anyway, counted as they are, and the list
     // is used if they fit.  (Bucket offsets below are counted in 16 bits: 65535 positions at most.)
     const bool try_list = count_ge <= row.list_limit();
-
-    // The runs of candidates inside one vector of four scores (positions j .. j + 3; a candidate is
-    // a score >= thr; scores are >= +0 and -0 never occurs, so equal scores have equal bits and the
-    // order-preserving image is the bit pattern with the top bit set): count_runs() counts them,
-    // visit_runs() calls visit(image, first position, length) for each, in position order.
-    auto count_runs = [](const float4 x, float thr) -> uint32_t {
-        const uint32_t a = __float_as_uint(x.x), b = __float_as_uint(x.y), c = __float_as_uint(x.z), d = __float_as_uint(x.w);
-        return (x.x >= thr ? 1u : 0u) + (x.y >= thr && b != a ? 1u : 0u) + (x.z >= thr && c != b ? 1u : 0u) +
-               (x.w >= thr && d != c ? 1u : 0u);
-    };
-    auto visit_runs = [](const float4 x, int j, float thr, auto&& visit) {
-        const uint32_t a = __float_as_uint(x.x), b = __float_as_uint(x.y), c = __float_as_uint(x.z), d = __float_as_uint(x.w);
-        const int ed = d == c ? 1 : 0;                       // positions after j + 2 with its score
-        const int ec = c == b ? 1 + ed : 0;                  // ... after j + 1
-        const int eb = b == a ? 1 + ec : 0;                  // ... after j
-        if (x.x >= thr) visit(a | 0x80000000u, j, 1 + eb);
-        if (x.y >= thr && b != a) visit(b | 0x80000000u, j + 1, 1 + ec);
-        if (x.z >= thr && c != b) visit(c | 0x80000000u, j + 2, 1 + ed);
-        if (x.w >= thr && d != c) visit(d | 0x80000000u, j + 3, 1);
-    };
-    static_assert(kRunMax == 4, "runs are found inside one float4");
 
     uint32_t n_items = 0;                   // runs in the list
     float thr = value_of(key_thr);                       // lowest candidate score (scores are >= 0)
@@ -784,7 +796,10 @@ __device__ __forceinline__ void select_row(const SelectRow& row, const SelectLds
     uint32_t prefix = key_thr, mask = 0x7FFu << kHistShift, kk = (uint32_t)kprime - above;   // radix-select state
     bool refined = false;
     bool in_lds = false;                    // the runs of all candidates are in sKeys
-    if (try_list) {
+    if (listed >= 0) {
+        n_items = (uint32_t)listed;
+        in_lds = true;
+    } else if (try_list && listed != kTooManyRuns) {
         n_items = list_row();
         in_lds = n_items <= (uint32_t)cand_cap;
     }
@@ -908,7 +923,87 @@ void select_body(const float* __restrict__ pooled, int64_t pooled_stride, const 
     }
     uint2 h01 = make_uint2(0, 0);
     const SelectLeft left = lg_parts > 0 ? select_part(row, lds, sel_counters + bg * 2, part, lg_parts, h01) : kRowAnew;
-    if (left != kRowDone) select_row<ADAPT>(row, lds, h01, left == kRowKnown);
+    if (left != kRowDone) select_row<ADAPT>(row, lds, h01, left == kRowKnown, kNotListed);
+}
+
+// A row among a few long ones (select_listed): this workgroup's 4096 positions; the last to arrive ranks.
+template <bool ADAPT>
+__device__ __forceinline__
+void select_listed_body(const float* __restrict__ pooled, int64_t pooled_stride, const int32_t* seq_lens,
+                        int32_t max_len, int32_t k, uint32_t* __restrict__ hist, int32_t cand_cap,
+                        int32_t* __restrict__ idx, float* __restrict__ sel_scores,
+                        const int32_t* pred, int32_t pred_val,
+                        int32_t* __restrict__ sel_counters, uint64_t* __restrict__ cand_list, const int b, const int g, const int Hkv) {
+    if (pred != nullptr && pred[b] != pred_val) return;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const SelectLds lds(smem, cand_cap);
+    const int tid = threadIdx.x, tile = blockIdx.x;
+    const int64_t bg = (int64_t)b * Hkv + g;
+    const int n = min(seq_lens[b], max_len);
+    const SelectRow row{pooled + bg * pooled_stride, hist + bg * kHistBins, n, k, min(k, max(n, 0)), (max_len + 3) >> 2, cand_cap, idx + bg * k,
+                        sel_scores ? sel_scores + bg * k : nullptr};
+    if (row.kprime <= 0) {                  // nothing was histogrammed for an empty sequence
+        if (tile == 0) row.fill_rest();
+        return;
+    }
+    uint32_t* const gh = row.gh;
+    const int rt = kSelThreads - 1 - tid;
+    const uint2 h01 = *reinterpret_cast<const uint2*>(gh + 2 * rt);
+    const float4 x = row.load4(tile * kSelThreads + tid);
+    scan_histogram(row, lds, h01);
+    __syncthreads();
+    int32_t* n_listed = sel_counters + bg * 2;
+    int32_t* arrived = n_listed + 1;
+    uint64_t* list = cand_list + bg * cand_cap;
+    const bool try_list = lds.out[1] + lds.out[2] <= row.list_limit();         // the same in every workgroup of the row
+    if (try_list) {
+        const float thr = value_of(lds.out[0] << kHistShift);
+        const uint32_t c = count_runs(x, thr);
+        uint32_t total;
+        const uint32_t incl = block_inclusive_scan<kSelThreads>(c, lds.scan, &total);
+        if (tid == 0 && total != 0)
+            *lds.count = (uint32_t)__hip_atomic_fetch_add(n_listed, (int32_t)total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        uint32_t pos = *lds.count + incl - c;
+        visit_runs(x, (tile * kSelThreads + tid) << 2, thr, [&](uint32_t key, int j, int len) {
+            if (pos < (uint32_t)cand_cap)                      // runs beyond the list's end are only counted
+                __hip_atomic_store(&list[pos], item_of(key, j, len), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            ++pos;
+        });
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // the list entries are acknowledged
+    }
+    __syncthreads();                                           // ... and every thread has read the histogram
+    if (tid == 0) lds.part[0] = (uint32_t)__hip_atomic_fetch_add(arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (lds.part[0] != gridDim.x - 1) return;
+    // last to arrive: everything of this row is in (a workgroup has the answer of its reservation before it writes its
+    // entries, hence before its ticket: the count is final); leave the workspace clean, then rank
+    if (tid == 0) {
+        lds.part[1] = (uint32_t)__hip_atomic_load(n_listed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(n_listed, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(arrived, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        *lds.count = 0;
+    }
+    gh[2 * rt] = 0; gh[2 * rt + 1] = 0;
+    __syncthreads();
+    const uint32_t runs = lds.part[1];
+    const bool fits = try_list && runs <= (uint32_t)cand_cap;
+    if (fits) {
+        for (uint32_t e = tid; e < runs; e += kSelThreads) lds.keys[e] = __hip_atomic_load(&list[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+    }
+    select_row<ADAPT>(row, lds, h01, true, fits ? (int)runs : try_list ? kTooManyRuns : kNotListed);
+}
+
+// Grid (workgroups of a row, KV heads, sequences).
+template <bool ADAPT>
+__global__ __launch_bounds__(kSelThreads)
+void select_listed_kernel(const float* __restrict__ pooled, int64_t pooled_stride, const int32_t* seq_lens,
+                          int32_t max_len, int32_t k, uint32_t* __restrict__ hist, int32_t cand_cap,
+                          int32_t* __restrict__ idx, float* __restrict__ sel_scores,
+                          const int32_t* pred, int32_t pred_val, int32_t* __restrict__ sel_counters, uint64_t* __restrict__ cand_list) {
+    select_listed_body<ADAPT>(pooled, pooled_stride, seq_lens, max_len, k, hist, cand_cap, idx, sel_scores, pred, pred_val,
+                              sel_counters, cand_list, (int)blockIdx.z, (int)blockIdx.y, (int)gridDim.y);
 }
 
 // Grid (KV heads, parts, sequences): consecutive workgroups go to the 8 XCDs in turn, so with 8 KV heads (or 4, or 16) the parts of
@@ -981,16 +1076,27 @@ static int launch_select(const rk_geom* geom, const int32_t* seq_lens, int32_t m
     const size_t lds = (size_t)ws.cand_cap * sizeof(uint64_t) +
                        (2 * (kBuckets + 1) + kSelThreads / 64 + 4 + 1 + kPartWords) * sizeof(uint32_t) +
                        (ADAPT ? kHistBins * sizeof(uint16_t) : 0);
+    const int64_t rows = (int64_t)geom->batch * geom->n_kv_heads;
+    const bool listed = ws.cand_list != nullptr && select_listed(max_len, k, rows);
     static size_t lds_allowed = 48 * 1024;       // grows monotonically (one per instantiation)
     if (lds > lds_allowed) {
         if (hipFuncSetAttribute(reinterpret_cast<const void*>(&select_kernel<ADAPT>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
+            hipFuncSetAttribute(reinterpret_cast<const void*>(&select_listed_kernel<ADAPT>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
             (void)hipGetLastError();
             return RK_ERR_UNSUPPORTED;
         }
         lds_allowed = lds;
     }
-    dim3 sgrid(geom->n_kv_heads, select_parts(max_len, (int64_t)geom->batch * geom->n_kv_heads), geom->batch);
+    if (listed) {
+        constexpr int kTile = 4 * kSelThreads;
+        dim3 lgrid((max_len + kTile - 1) / kTile, geom->n_kv_heads, geom->batch);
+        hipLaunchKernelGGL((select_listed_kernel<ADAPT>), lgrid, dim3(kSelThreads), lds, st, ws.pooled, pooled_row_stride(max_len), seq_lens,
+                           max_len, k, ws.hist, ws.cand_cap, idx, sel_scores, pred, pred_val, ws.sel_counters, ws.cand_list);
+        return launch_status();
+    }
+    dim3 sgrid(geom->n_kv_heads, select_parts(rows), geom->batch);
     hipLaunchKernelGGL((select_kernel<ADAPT>), sgrid, dim3(kSelThreads), lds, st, ws.pooled, pooled_row_stride(max_len), seq_lens,
                        max_len, k, ws.hist, ws.cand_cap, idx, sel_scores, pred, pred_val, ws.sel_counters);
     return launch_status();
@@ -1014,7 +1120,7 @@ static int launch_select_batched(const rk_geom* geom, int n_layers, const Worksp
         lds_allowed = lds;
     }
     const int problems = (n_layers < kBatchLayers ? n_layers : kBatchLayers) * geom->batch * geom->n_kv_heads;
-    const int parts = select_parts(max_len, problems);
+    const int parts = select_parts(problems);
     for (int l0 = 0; l0 < n_layers; l0 += kBatchLayers) {
         const int n = n_layers - l0 < kBatchLayers ? n_layers - l0 : kBatchLayers;
         SelectBatch tab{};
@@ -1039,6 +1145,8 @@ int select_batched_stage(const rk_geom* geom, int n_layers, const Workspace* wss
     if ((int64_t)kBatchLayers * geom->batch > 65535) return RK_ERR_UNSUPPORTED;      // grid z
     for (int l = 1; l < n_layers; ++l)
         if (wss[l].cand_cap != wss[0].cand_cap) return RK_ERR_INVALID_ARG;
+    if (n_layers == 1)
+        return select_stage(geom, seq_lens, max_len, k, idx[0], nullptr, pred ? pred[0] : nullptr, pred_val, wss[0], st);
     if (wss[0].cand_cap > kAdaptiveFrom) return launch_select_batched<true>(geom, n_layers, wss, idx, seq_lens, max_len, k, pred, pred_val, st);
     return launch_select_batched<false>(geom, n_layers, wss, idx, seq_lens, max_len, k, pred, pred_val, st);
 }

@@ -43,7 +43,13 @@ int main() {
                 printf("tile %ld %ld %d %d %d %d %d %d %d\n", r, p, tail, G, trig, f.waves, f.nch, f.tail, (int)f.exact);
             }
         }
-    for (long p : {1L, 4L, 8L, 12L, 32L, 33L, 64L, 65L, 128L, 129L, 256L, 257L, 100000L}) printf("parts %ld %d\n", p, select_parts(32768, p));
+    for (long p : {1L, 4L, 8L, 12L, 32L, 33L, 64L, 65L, 128L, 129L, 256L, 257L, 100000L}) printf("parts %ld %d\n", p, select_parts(p));
+    for (long l : {1000L, 98303L, 98304L, 131072L, 163840L, 327679L, 327680L, 1000000L}) for (long k : {1L, 4096L, 4097L, 8192L, 16384L}) for (int b : {1, 2}) for (int hkv : {1, 2, 3, 4, 7}) {
+        rk_geom g{b, hkv, hkv, 128, 1.0f};
+        const Workspace w = carve(&g, l, k, nullptr), shorter = carve(&g, l - 1, k, nullptr), fewer = carve(&g, l, k - 1, nullptr);
+        printf("listed %ld %ld %d %d %d %d\n", l, k, b * hkv, (int)select_listed(l, k, b * hkv), (int)(w.cand_list != nullptr),
+               (int)(shorter.total <= w.total && fewer.total <= w.total));
+    }
     // the parts of a row whose K' ranks end in a bin of h positions, `above` of the ranks in higher bins: stretches from the top
     // down to where the last part starts, or may have to go down to
     for (long h : {1L, 2L, 3L, 7L, 8L, 100L, 5000L, 100000L, 1L << 21, 20000000L, 40000000L, 60000000L, 100000000L, 1L << 28}) for (int lg : {1, 2, 3}) {
@@ -216,6 +222,16 @@ def test_selection_parts_are_resident_at_once(table):
     got = {int(v[0]): int(v[1]) for kind, *v in table if kind == "parts"}
     for rows, parts in got.items():
         assert parts in (1, 2, 4, 8) and (parts == 1 or rows * parts <= 256) and (parts == 8 or rows * parts > 128), (rows, parts)
+
+
+def test_few_long_rows_are_listed(table):
+    """... where that was measured to be faster; wherever it is, the workspace has room for the list, and what is sized for
+    longer rows or more ranks serves shorter ones and fewer."""
+    got = {tuple(map(int, v[:3])): tuple(map(int, v[3:])) for kind, *v in table if kind == "listed"}
+    assert len(got) == 8 * 5 * 8
+    for (n, k, rows), (listed, room, grows) in got.items():
+        assert grows and (room or not listed) and (not room or rows <= 6), (n, k, rows)
+        assert listed == (rows <= (6 if k <= 4096 else 4) and n >= 98304 and n >= 20 * k), (n, k, rows)
 
 
 def test_selection_stretches_leave_no_rank_out(table):
