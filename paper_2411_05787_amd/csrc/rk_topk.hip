@@ -41,7 +41,7 @@ constexpr int kTopLoose = 64;                            // scores above the buc
 constexpr int kPairs = 256;                               // a part's runs up to here are compared each with each
 static_assert(kMaxCandidates / 2 * 4 <= 0xFFFF, "buckets of a part count positions in 16 bits");
 constexpr int kNonFinite = 1;                            // thread whose two bins of the histogram start at infinity
-constexpr int kFineFrom = 2;                             // a bin of more than this many times K' positions is looked at more closely
+constexpr int kFineFrom = 4;                             // a bin of more than this many times K' positions is looked at more closely
 constexpr int kPartWords = 8;                            // what a part knows of its stretch
 constexpr int kListTry = 4;                              // runs are listed for up to this many times cand_cap positions
 static_assert(kHistBins == 1 << 11, "first-level histogram is 11 bits wide");
@@ -478,10 +478,11 @@ __device__ __forceinline__ SelectLeft select_part(const SelectRow& row, const Se
     uint32_t hi = sPart[0], end = sPart[1], above_end = sPart[2], estimate = sPart[3], floor = last ? (b1 << kHistShift) - 0x80000000u : estimate;
     if (in1 > (uint32_t)(kprime * kFineFrom) && t1 > above1) {
         // The K'-th score's bin (no other can) holds many times the ranks there are, which says little about where in it they lie:
-        // one look at the row counts its scores by the next 11 bits.  Scores that differ little, us per call: one workgroup or spread-out listing
-        // / parts without this look, bins taken as even / now: e^(0.05 N(0, 1)), pooled by 7, 8 rows of 32768, K = 2048: 26.8 / 32.3 / 17.8, 4 of
-        // 131072, K = 8192: 59.5 / 81.8 / 33.8, 8 of 2000, K = 125: 13.3 / 20.2 / 14.0; e^(0.25 N(0, 1)), where the densities of the bins do: 16.1 /
-        // 18.7 / 15.2, 28.0 / 36.1 / 24.4.  (Equal scores throughout: 8 of 2000 29.3 / 31.8 / 34.5, of 32768 100 / 101 / 104.)
+        // one look at the row counts its scores by the next 11 bits (a dozen LDS atomics per thread and 32768 positions at the least:
+        // from twice K positions on instead of four times it cost votes of 20 queries over 131072 rows 11 us of 109).  Scores that differ
+        // little, 8 rows, us per call: one workgroup or spread-out listing / parts without this look, bins taken as even / now: e^(0.05 N(0, 1)),
+        // 8000 positions, K = 500: 22.3 / 28.3 / 14.7, 131072, K = 8192: 83 / 115 / 36; e^(0.25 N(0, 1)), pooled by 7, where the densities of the
+        // bins do: 14.0 / 16.7 / 12.0 and 33.0 / 37.1 / 25.2.  (Equal scores throughout, 8 rows of 2000: 29.3 / 31.8 / 34.5, of 32768 100 / 101 / 104.)
         constexpr int kSub = kHistShift - 11;
         const uint32_t from = (b1 << kHistShift) - 0x80000000u;
         for (int v0 = 0; v0 < nvec; v0 += NV * kSelThreads) {

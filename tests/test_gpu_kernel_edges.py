@@ -647,7 +647,7 @@ def _select_scores(name, rows, n, g):
     return w
 
 
-# Bins with more than twice K positions, which a part looks into ("narrow", "one_bin", "steps"), (scores, B, Hkv, n, k, pool): 8 / 4 / 2 / 1 workgroups per row, fewer ranks than workgroups, fewer positions than ranks, vectors of
+# Bins with more than four times K positions, which a part looks into ("narrow", "one_bin", "steps"), (scores, B, Hkv, n, k, pool): 8 / 4 / 2 / 1 workgroups per row, fewer ranks than workgroups, fewer positions than ranks, vectors of
 # four and rounds of 32768 positions that end in the row, more than 256 runs in a stretch
 SELECT_EDGES = [("normal", 1, 1, 1, 1, 1), ("normal", 1, 2, 9, 3, 7), ("normal", 1, 3, 31, 100, 7), ("normal", 1, 8, 1027, 9, 1), ("normal", 2, 16, 4099, 300, 7),
                 ("normal", 5, 8, 5001, 700, 3), ("normal", 16, 8, 3001, 257, 7), ("normal", 33, 8, 1025, 64, 7), ("normal", 1, 8, 32771, 2048, 7),
