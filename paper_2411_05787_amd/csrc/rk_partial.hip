@@ -13,7 +13,9 @@
 // us per launch, one sequence, 32 heads over 8: K = 256: 6.9 -> 4.9, 1024: 6.7 -> 4.8, 2048: 6.5 -> 5.6, 4096: 8.4 -> 7.9; 28 over 4, K
 // = 4096: 7.4 -> 6.0 (more at partial_tile_form).  At K = 2048 in cycles after a wavefront's first instruction: first rows
 // there 3700, S^T 3800, maximum known 4000, P and V in LDS 4800, O 5300, published 5800, merged 9500 (the slowest workgroups
-// start 0.3 us after the first); the launch to launch time is 1.2 us more than the slowest of it.
+// start 0.3 us after the first); the launch to launch time is 1.2 us more than the slowest of it.  The latency is paid for in traffic: 64 rows
+// of 16 bytes per head and partial result instead of 44, and twice the partial results (K = 2048: 12.0 MB per launch against 9.8
+// with attn_split_kernel, 8.4 needed), which is one reason why more than two workgroups per unit are better off there.
 #include "rk_attn_common.h"
 
 namespace rk {

@@ -12,7 +12,8 @@
 //   winners plus the rest of one bin).  What is listed and ranked are runs of candidates: up to
 //   four neighbours with the same pooled score (the pooling window makes neighbours equal, so runs
 //   are several times fewer than positions).  Up to 8 workgroups share a row, by rank (select_part):
-//   each lists and ranks the runs of its own stretch of scores.  Up to 256 runs are compared each with
+//   each lists and ranks the runs of its own stretch of scores.  A few long rows are listed by a workgroup per 4096 positions
+//   and ranked by the last to arrive (select_listed_kernel).  Up to 256 runs are compared each with
 //   each; more, or those of a whole row, are taken into registers and bucket-sorted back into LDS on the
 //   64-bit item (P image, position, length): 2048 buckets from the lowest candidate image up to
 //   the bin of the 64-th largest score (of equal width, or laid out from the histogram), one more

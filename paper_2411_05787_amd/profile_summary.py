@@ -23,14 +23,14 @@ import sys
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
-# attn_split_kernel<G, NW, EMIT, TWO_SEG, LAZY, TAGGED, TRIG, EXACT>: the first kernel of a full step, and the partial step without the trigger inside (or partial_tile_kernel<G, NW, TRIG>)
+# attn_split_kernel<G, NW, EMIT, TWO_SEG, LAZY, TAGGED, TRIG, EXACT>: the first kernel of a full step, and the partial step without the trigger inside (or partial_tile_kernel<G, NW, TRIG, EXACT>)
 FULL_KERNEL = r"attn_split_kernel<\d+, 4, true, false, false, false, false, false>"
-PARTIAL_KERNEL = r"partial_tile_kernel<\d+, \d+, false>|attn_split_kernel<\d+, 4, false, true, false, (true|false), false, false>"
+PARTIAL_KERNEL = r"partial_tile_kernel<\d+, \d+, false, (true|false)>|attn_split_kernel<\d+, 4, false, true, false, (true|false), false, false>"
 LEGEND = [
     ("attn_split_kernel<G, 4, true, false, false, false, false, false>", "streams C_f once and emits raw scores: first kernel of rk_full_attn (weights returned) and rk_full_attn_select; rk_full_attn_scores launches it alone (the roofline measurement)"),
     ("attn_split_kernel<G, 4, true, false, false, true, false, *>", "the same with the output merged inside (tagged partial results, by slices or by the last workgroup): the one kernel of rk_full_attn_deferred and of rk_full_attn without weights over long rows; last parameter true: with the sums and the order of the merge launch"),
     ("attn_split_kernel<G, 4, true, true, false, false, false, false>", "rk_h2o_step: the policy's cache and the new token's row as two segments, scores emitted"),
-    ("partial_tile_kernel<G, NW, TRIG>", "rk_partial_attn in one tile per workgroup; TRIG true: rk_partial_attn_triggered"),
+    ("partial_tile_kernel<G, NW, TRIG, EXACT>", "rk_partial_attn in one tile per workgroup; TRIG true: rk_partial_attn_triggered; EXACT true: partial results weighed by (max, sum) pairs (groups of more than 4 heads over more than 16 pairs)"),
     ("attn_split_kernel<G, 4, false, true, false, true, false, false>", "rk_partial_attn over longer or more small caches: one launch, tagged partial results, merged by slices (every workgroup its share) or by the last workgroup"),
     ("attn_split_kernel<G, 4, false, true, false, false, false, false>", "rk_partial_attn, groups of more than 4 heads in launches over many (sequence, KV head) pairs, and rk_partial_attn_static: one launch, ticketed merge"),
     ("attn_split_kernel<G, 4, false, true, false, *, true, false>", "rk_partial_attn_triggered: the partial step of a trigger test step, with the query-similarity test inside"),
@@ -38,7 +38,7 @@ LEGEND = [
     ("merge_normalise_kernel", "output merge of rk_full_attn / rk_full_attn_deferred (+ weights in place for rk_full_attn)"),
     ("finish_pool_kernel<G, TILE>", "second kernel of rk_full_attn_select: merge, weights, group max, max-pool, histogram"),
     ("pool_batched_kernel<G>", "pooling tiles of the finishing kernel for all layers in one launch (rk_refresh_batched)"),
-    ("select_kernel / select_batched_kernel", "top-K: per call / for all layers in one launch"),
+    ("select_kernel / select_listed_kernel / select_batched_kernel", "top-K: per call / per call over a few long rows / for all layers in one launch"),
     ("gather_rows_kernel / gather_rows_batched_kernel", "rk_gather_small_kv: per call / for all layers in one launch"),
     ("pool_hist_kernel", "first kernel of rk_topk_select"),
     ("query_sim_kernel", "rk_query_sim"),
