@@ -13,7 +13,7 @@
 //   four neighbours with the same pooled score (the pooling window makes neighbours equal, so runs
 //   are several times fewer than positions).  Up to 8 workgroups share a row, by rank (select_part):
 //   each lists and ranks the runs of its own stretch of scores.  A few long rows are listed by a workgroup per 4096 positions
-//   and ranked by the last to arrive (select_listed_kernel).  Up to 256 runs are compared each with
+//   and ranked by the last to arrive (select_listed_kernel, select_listed_batched_kernel).  Up to 256 runs are compared each with
 //   each; more, or those of a whole row, are taken into registers and bucket-sorted back into LDS on the
 //   64-bit item (P image, position, length): 2048 buckets from the lowest candidate image up to
 //   the bin of the 64-th largest score (of equal width, or laid out from the histogram), one more
@@ -44,6 +44,7 @@ static_assert(kMaxCandidates / 2 * 4 <= 0xFFFF, "buckets of a part count positio
 constexpr int kNonFinite = 1;                            // thread whose two bins of the histogram start at infinity
 constexpr int kFineFrom = 4;                             // a bin of more than this many times K' positions is looked at more closely
 constexpr int kPartWords = 8;                            // what a part knows of its stretch
+constexpr int kListTile = 4 * kSelThreads;               // positions that a workgroup of select_listed_kernel lists
 constexpr int kListTry = 4;                              // runs are listed for up to this many times cand_cap positions
 static_assert(kHistBins == 1 << 11, "first-level histogram is 11 bits wide");
 static_assert(kHistBins == 2 * kSelThreads, "the selection scans the histogram two bins per thread");
@@ -1040,6 +1041,22 @@ void select_batched_kernel(const SelectBatch tab, int32_t batch, int64_t pooled_
                        (int)blockIdx.y, 31 - __builtin_clz(gridDim.y));
 }
 
+// ... of a few long rows in all layers together: grid (workgroups of a row, KV heads, layer * batch + sequence).
+struct ListBatch {
+    SelectBatch rows;
+    uint64_t* cand_list[kListRows];
+};
+
+template <bool ADAPT>
+__global__ __launch_bounds__(kSelThreads)
+void select_listed_batched_kernel(const ListBatch tab, int32_t batch, int64_t pooled_stride, const int32_t* seq_lens,
+                                  int32_t max_len, int32_t k, int32_t cand_cap, int32_t pred_val) {
+    const int layer = blockIdx.z / batch, b = blockIdx.z - layer * batch;
+    select_listed_body<ADAPT>(tab.rows.pooled[layer], pooled_stride, seq_lens, max_len, k, tab.rows.hist[layer], cand_cap, tab.rows.idx[layer],
+                              nullptr, tab.rows.pred[layer], pred_val, tab.rows.sel_counters[layer], tab.cand_list[layer], b,
+                              (int)blockIdx.y, (int)gridDim.y);
+}
+
 }  // namespace rk
 
 using namespace rk;
@@ -1092,8 +1109,7 @@ static int launch_select(const rk_geom* geom, const int32_t* seq_lens, int32_t m
         lds_allowed = lds;
     }
     if (listed) {
-        constexpr int kTile = 4 * kSelThreads;
-        dim3 lgrid((max_len + kTile - 1) / kTile, geom->n_kv_heads, geom->batch);
+        dim3 lgrid((max_len + kListTile - 1) / kListTile, geom->n_kv_heads, geom->batch);
         hipLaunchKernelGGL((select_listed_kernel<ADAPT>), lgrid, dim3(kSelThreads), lds, st, ws.pooled, pooled_row_stride(max_len), seq_lens,
                            max_len, k, ws.hist, ws.cand_cap, idx, sel_scores, pred, pred_val, ws.sel_counters, ws.cand_list);
         return launch_status();
@@ -1115,13 +1131,16 @@ static int launch_select_batched(const rk_geom* geom, int n_layers, const Worksp
     static size_t lds_allowed = 48 * 1024;
     if (lds > lds_allowed) {
         if (hipFuncSetAttribute(reinterpret_cast<const void*>(&select_batched_kernel<ADAPT>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
+            hipFuncSetAttribute(reinterpret_cast<const void*>(&select_listed_batched_kernel<ADAPT>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
             (void)hipGetLastError();
             return RK_ERR_UNSUPPORTED;
         }
         lds_allowed = lds;
     }
-    const int problems = (n_layers < kBatchLayers ? n_layers : kBatchLayers) * geom->batch * geom->n_kv_heads;
+    const int64_t problems = (int64_t)(n_layers < kBatchLayers ? n_layers : kBatchLayers) * geom->batch * geom->n_kv_heads;
+    const bool listed = wss[0].cand_list != nullptr && select_listed(max_len, k, problems);      // (no more than kListRows layers then)
     const int parts = select_parts(problems);
     for (int l0 = 0; l0 < n_layers; l0 += kBatchLayers) {
         const int n = n_layers - l0 < kBatchLayers ? n_layers - l0 : kBatchLayers;
@@ -1131,6 +1150,14 @@ static int launch_select_batched(const rk_geom* geom, int n_layers, const Worksp
             tab.pooled[l] = w.pooled; tab.hist[l] = w.hist; tab.idx[l] = idx[l0 + l];
             tab.sel_counters[l] = w.sel_counters;
             tab.pred[l] = pred ? pred[l0 + l] : nullptr;
+        }
+        if (listed) {
+            ListBatch list{tab, {}};
+            for (int l = 0; l < n; ++l) list.cand_list[l] = wss[l].cand_list;
+            dim3 lgrid((max_len + kListTile - 1) / kListTile, geom->n_kv_heads, n * geom->batch);
+            hipLaunchKernelGGL((select_listed_batched_kernel<ADAPT>), lgrid, dim3(kSelThreads), lds, st, list, (int32_t)geom->batch,
+                               pooled_row_stride(max_len), seq_lens, max_len, k, (int32_t)cand_cap, pred_val);
+            return launch_status();
         }
         dim3 grid(geom->n_kv_heads, parts, n * geom->batch);
         hipLaunchKernelGGL((select_batched_kernel<ADAPT>), grid, dim3(kSelThreads), lds, st, tab, (int32_t)geom->batch,
@@ -1147,8 +1174,6 @@ int select_batched_stage(const rk_geom* geom, int n_layers, const Workspace* wss
     if ((int64_t)kBatchLayers * geom->batch > 65535) return RK_ERR_UNSUPPORTED;      // grid z
     for (int l = 1; l < n_layers; ++l)
         if (wss[l].cand_cap != wss[0].cand_cap) return RK_ERR_INVALID_ARG;
-    if (n_layers == 1)
-        return select_stage(geom, seq_lens, max_len, k, idx[0], nullptr, pred ? pred[0] : nullptr, pred_val, wss[0], st);
     if (wss[0].cand_cap > kAdaptiveFrom) return launch_select_batched<true>(geom, n_layers, wss, idx, seq_lens, max_len, k, pred, pred_val, st);
     return launch_select_batched<false>(geom, n_layers, wss, idx, seq_lens, max_len, k, pred, pred_val, st);
 }

@@ -38,7 +38,8 @@ LEGEND = [
     ("merge_normalise_kernel", "output merge of rk_full_attn / rk_full_attn_deferred (+ weights in place for rk_full_attn)"),
     ("finish_pool_kernel<G, TILE>", "second kernel of rk_full_attn_select: merge, weights, group max, max-pool, histogram"),
     ("pool_batched_kernel<G>", "pooling tiles of the finishing kernel for all layers in one launch (rk_refresh_batched)"),
-    ("select_kernel / select_listed_kernel / select_batched_kernel", "top-K: per call / per call over a few long rows / for all layers in one launch"),
+    ("select_kernel / select_batched_kernel", "top-K: per call / for all layers in one launch"),
+    ("select_listed_kernel / select_listed_batched_kernel", "the same over a few long rows"),
     ("gather_rows_kernel / gather_rows_batched_kernel", "rk_gather_small_kv: per call / for all layers in one launch"),
     ("pool_hist_kernel", "first kernel of rk_topk_select"),
     ("query_sim_kernel", "rk_query_sim"),

@@ -692,6 +692,50 @@ def test_selection_shared_out_by_rank(rk, case):
             assert (idx[b, :, kk:] == -1).all() and (sel[b, :, kk:] == 0).all()
 
 
+# (layers, B, Hkv, n, k, lengths, which (layer, sequence) refresh)
+LISTED_BATCHES = [(2, 1, 3, 98304, 1000, [98304], None), (3, 2, 1, 98309, 300, [98309, 50], [[1, 1], [0, 1], [1, 0]]), (2, 1, 2, 163841, 8192, [163841], None),
+                  (1, 1, 6, 98305, 4096, [98304], None)]
+
+
+@pytest.mark.parametrize("case", LISTED_BATCHES, ids=["l%d_%dx%d_%d_k%d" % c[:5] for c in LISTED_BATCHES])
+def test_batched_selection_of_few_long_rows(rk, case):
+    """rk_refresh_batched where the rows of all layers are few and long: the positions that rk_full_attn_select takes layer by layer
+    and that a stable sort of its weights gives; others untouched; three calls on the same workspaces."""
+    import ctypes
+    L, B, Hkv, n, k, lens, on = case
+    say("few long rows, batched", *case[:5])
+    g = torch.Generator(device="cuda").manual_seed(n + k)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda", dtype=torch.bfloat16)
+    K, V, q = rnd(L, B, Hkv, n, 128), rnd(L, B, Hkv, n, 128), rnd(L, B, Hkv * 2, 128)
+    geom = rk.Geom(B, Hkv * 2, Hkv, 128, SCALE)
+    sl = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    need = torch.tensor(on or [[1] * B] * L, dtype=torch.int32, device="cuda")
+    wss = [rk.Workspace(geom, n, k) for _ in range(L)]
+    sK, sV = torch.zeros(L, B, Hkv, k, 128, dtype=torch.bfloat16, device="cuda"), torch.zeros(L, B, Hkv, k, 128, dtype=torch.bfloat16, device="cuda")
+    idx, tail = torch.full((L, B, Hkv, k), -5, dtype=torch.int32, device="cuda"), torch.zeros(L, B, dtype=torch.int32, device="cuda")
+    states = [rk.layer_state(geom, K[l], V[l], sK[l], sV[l], idx[l], tail[l], need_full=need[l], k=k) for l in range(L)]
+    out, one = torch.empty_like(q[0]), torch.full((B, Hkv, k), -5, dtype=torch.int32, device="cuda")
+    w = torch.zeros(B, Hkv * 2, (n + 3) // 4 * 4, device="cuda")
+    for _ in range(3):
+        idx.fill_(-5)
+        for l in range(L):
+            rk.rk_full_attn_deferred(geom, q[l], K[l], V[l], sl, n, out, pred=need[l], pred_val=1, workspace=wss[l])
+        rk.rk_refresh_batched(geom, (type(states[0]) * L)(*states), (ctypes.c_void_p * L)(*[x.ptr for x in wss]), wss[0].nbytes, sl, n, k, pool_w=7,
+                              by_need_full=True)
+        torch.cuda.synchronize()
+        for l in range(L):
+            rk.rk_full_attn_select(geom, q[l], K[l], V[l], sl, n, out, k, 7, one, weights=w, workspace=rk.Workspace(geom, n, k))
+            for b in range(B):
+                if need[l, b].item() == 0:
+                    assert (idx[l, b] == -5).all() and (sK[l, b] == 0).all()
+                    continue
+                assert torch.equal(idx[l, b], one[b]), (l, b)
+                kk = min(k, lens[b])
+                P = torch.nn.functional.max_pool1d(w[b, :, :lens[b]].view(Hkv, 2, -1).amax(1)[None], 7, stride=1, padding=3)[0]
+                assert torch.equal(idx[l, b, :, :kk].long(), torch.sort(P, dim=-1, descending=True, stable=True)[1][:, :kk]), (l, b)
+                assert (idx[l, b, :, kk:] == -1).all()
+
+
 @pytest.mark.parametrize("n,k", [(60_000_001, 5), (100_000_000, 50)], ids=["60m_k5", "100m_k50"])
 def test_selection_of_few_among_tens_of_millions_in_one_bin(rk, n, k):
     """So many positions in the bin of the K-th score that the last part's estimate leaves it no stretch: every rank is written."""
