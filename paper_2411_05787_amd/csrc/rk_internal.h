@@ -255,13 +255,13 @@ struct StretchBound { uint32_t at, end, above; };
 // `ratio`: how many times as dense its lower end is as its upper one.
 __host__ __device__ static inline StretchBound stretch_bound(uint32_t t, uint32_t spare, uint32_t end, uint32_t width, uint32_t above, uint32_t h, float ratio) {
     if (t - above == h) return {end - width, end - width, t};      // the whole bin: nothing to count
-    // (one thread's work while the others wait: reciprocals as they come)
+    // (one thread's work while the others wait: reciprocals as they come; the multiply-add by name, so that every copy of this rounds alike)
 #ifdef __HIP_DEVICE_COMPILE__
     float part = (float)(t + spare - above) * __builtin_amdgcn_rcpf((float)h);
-    if (ratio > 1.f) part = __builtin_amdgcn_logf(1.f + part * (ratio - 1.f)) * __builtin_amdgcn_rcpf(__builtin_amdgcn_logf(ratio));
+    if (ratio > 1.f) part = __builtin_amdgcn_logf(fmaf(part, ratio - 1.f, 1.f)) * __builtin_amdgcn_rcpf(__builtin_amdgcn_logf(ratio));
 #else
     float part = (float)(t + spare - above) / (float)h;
-    if (ratio > 1.f) part = log2f(1.f + part * (ratio - 1.f)) / log2f(ratio);
+    if (ratio > 1.f) part = log2f(fmaf(part, ratio - 1.f, 1.f)) / log2f(ratio);
 #endif
     const float down = part * (float)width;
     return {end - (down < (float)width ? (uint32_t)down : width), end, above};
