@@ -287,15 +287,17 @@ __host__ __device__ static inline uint32_t stretch_low(uint32_t estimate, uint32
 
 // A few long rows are listed by a workgroup per 4096 positions and ranked by the last to arrive instead (select_listed_kernel): parts all read the whole
 // row, which takes a CU 40 us per million positions and leaves the chip idle; ranking K positions in one workgroup costs more than
-// in eight.  `rows`: (sequence, KV head) pairs in the launch, of all layers where it takes several.  us per call of rk_topk_select, parts / listed: one row of 98304, K = 512: 16.5 /
-// 14.5, of 1048576: 67 / 33, of 4194304: 236 / 106; 4 rows of 131072, K = 4096: 20.9 / 18.8, of 1048576: 84 / 72; K = 8192: one row of 131072:
-// 21.3 / 21.1, of 262144: 29.4 / 23.8, 4 of 131072: 23.1 / 24.3, of 262144: 33.5 / 31.5; K = 16384: one row of 196608: 30 / 34, of 393216: 41 / 34;
-// 6 rows of 196608, K = 2048: 0.92 of the parts' time, K = 8192: 1.05; 8 rows: 1.0 to 1.45.  A full step with the batched refresh, K = 1024, 2 layers of
-// one KV head, 131072 rows: 69.8 / 65.5, 524288: 155.6 / 139.4, 3 layers of 2, 131072: 122.1 / 118.2; 12 and 16 rows, 131072 to 1048576: 0.96 to 1.01 of listing with parts.
+// in eight.  `rows`: (sequence, KV head) pairs in the launch, of all layers where it takes several.  us per call of rk_topk_select, parts / listed, log-normal
+// scores: one row of 65537, K = 2730: 18.9 / 16.0, of 131073, K = 2048: 21.5 / 16.4, of 1048576, K = 512: 67 / 33, of 4194304: 236 / 106; 4 rows of
+// 65537, K = 4096: 20.4 / 19.1, of 1048576: 84 / 72; 6 of 98305, K = 1536: 21.1 / 18.8; one row of 36001, K = 562: 1.0 of the parts' time; K an eighth of the row: 1.0 to 1.2, a
+// twelfth 1.0 to 1.1; 4 rows of 131073, K = 8192: 1.06; 8 rows: 1.0 to 1.45.  Scores in tight clusters, no pooling (crowded buckets to rank): 1.1 to 1.4.
+// A full step with the batched refresh, K = 1024, 2 layers of one KV head, 131072 rows: 69.8 / 65.5, 524288: 155.6 / 139.4, 3 layers of 2, 131072:
+// 122.1 / 118.2; 12 and 16 rows, 131072 to 1048576: 0.96 to 1.01 of listing with parts.
 constexpr int kListRows = 6;
-constexpr int64_t kListFrom = 98304;
+constexpr int64_t kListFrom = 49152;
 static inline bool select_listed(int64_t max_len, int64_t k, int64_t rows) {
-    return rows <= (k <= 4096 ? kListRows : 4) && max_len >= kListFrom && max_len >= 20 * k;
+    const bool few = k <= 4096 || (rows <= 3 && k <= 12288);
+    return rows <= (k <= 4096 ? kListRows : 4) && max_len >= kListFrom && max_len >= (few ? 16 : 20) * k;
 }
 
 // Device workspace, carved in this order (every region 256-byte aligned).  The regions up to and

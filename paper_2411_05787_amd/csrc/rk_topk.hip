@@ -45,6 +45,9 @@ constexpr int kNonFinite = 1;                            // thread whose two bin
 constexpr int kFineFrom = 4;                             // a bin of more than this many times K' positions is looked at more closely
 constexpr int kPartWords = 8;                            // what a part knows of its stretch
 constexpr int kListTile = 4 * kSelThreads;               // positions that a workgroup of select_listed_kernel lists
+// Of more candidates than positions fit, more runs than this, or than a 32nd of the row, rank faster in parts (one row of 65537, K = 4096, 6231 runs: 25.3 us, in parts 19.7;
+// the longer the row, the more it costs the parts to read: of 262145, K = 10922, 0.9 of the parts' time).
+constexpr int kListRuns = 4096;
 constexpr int kListTry = 4;                              // runs are listed for up to this many times cand_cap positions
 static_assert(kHistBins == 1 << 11, "first-level histogram is 11 bits wide");
 static_assert(kHistBins == 2 * kSelThreads, "the selection scans the histogram two bins per thread");
@@ -394,11 +397,27 @@ __device__ __forceinline__ void rank_by_sorting(const SelectRow& row, const Sele
 // histogram says it (K-th score zero or negative, infinities), the first part does the row, and does not wait for the others.
 // What is left to do for this workgroup:
 enum SelectLeft { kRowDone, kRowAnew, kRowKnown };       // nothing; the row; the row, with what the histogram says in place (it is cleared by another)
+// The ticket: parts that have drawn, those of them that the row does not fit (four bits each), workgroups without a part (select_listed_body).
+constexpr uint32_t kDrawn = 1, kDrawnBad = 0x10, kDrawnIdle = 0x100;
+__device__ __forceinline__ uint32_t draw_ticket(int32_t* ticket, uint32_t what) {
+    return (uint32_t)__hip_atomic_fetch_add(ticket, (int32_t)what, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// All threads of a workgroup, with what has been drawn, its own included: the last one leaves the workspace clean, or has the row to do.
+__device__ __forceinline__ SelectLeft after_drawing(const SelectRow& row, int32_t* ticket, uint32_t drawn, int lg_parts, int idle) {
+    if ((drawn & ~(kDrawnIdle - kDrawnBad)) != (1u << lg_parts) + (uint32_t)idle * kDrawnIdle) return kRowDone;
+    if (threadIdx.x == 0) __hip_atomic_store(ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if ((drawn & (kDrawnIdle - kDrawnBad)) != 0) {           // (the ranks that others have written come out the same)
+        __syncthreads();
+        return kRowAnew;
+    }
+    row.gh[2 * threadIdx.x] = 0; row.gh[2 * threadIdx.x + 1] = 0;
+    return kRowDone;
+}
 // What bounds it is latency: us after the first workgroup's first instruction, 8 rows of 32768 positions, K = 2048, medians:
 // lengths 0.7, histogram and stretch 2.6, row looked through 3.8, runs listed 5.5, ranked 6.7, written 7.1 (the launch 9 - 10
 // against 10.6 before); of 131072, K = 8192, 32 parts: 0.8, 2.7, 6.6, 10.5 (512 KB through one CU), 11.9, 12.4.
 __device__ __forceinline__ SelectLeft select_part(const SelectRow& row, const SelectLds& lds, int32_t* __restrict__ ticket, const int part, const int lg_parts,
-                                                  uint2& h01) {
+                                                  const int idle, uint2& h01) {
     const int tid = threadIdx.x, n = row.n, kprime = row.kprime, nvec = (n + 3) >> 2, cand_cap = row.cand_cap;
     uint64_t* const sKeys = lds.keys;
     uint32_t *const sHist = lds.hist, *const sScan = lds.scan, *const sOut = lds.out, *const sCount = lds.count, *const sPart = lds.part;
@@ -461,12 +480,9 @@ __device__ __forceinline__ SelectLeft select_part(const SelectRow& row, const Se
     // the lowest and highest candidates' bits (scores as whole numbers)
     if (sOut[0] <= (uint32_t)kHistBins / 2 || sPart[4] != 0) {      // the same in every part
         lds_barrier();
-        if (tid == 0) sPart[4] = (uint32_t)__hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (tid == 0) sPart[4] = draw_ticket(ticket, kDrawn) + kDrawn;
         __syncthreads();
-        if (sPart[4] == (1u << lg_parts) - 1u) {         // everybody has read the histogram
-            if (tid == 0) __hip_atomic_store(ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            gh[2 * tid] = 0; gh[2 * tid + 1] = 0;
-        }
+        after_drawing(row, ticket, sPart[4], lg_parts, idle);        // (nobody's row is bad here)
         return part == 0 ? kRowKnown : kRowDone;
     }
     const uint32_t b1 = sOut[0], above1 = sOut[1], in1 = sOut[2], key_top = (sOut[3] + 1u) << kHistShift;
@@ -622,8 +638,9 @@ __device__ __forceinline__ SelectLeft select_part(const SelectRow& row, const Se
     lds_barrier();
     const uint32_t n_items = *sCount, base = above_end + sPart[6];
     const bool bad = hopeless || sPart[5] > (uint32_t)cand_cap || n_items > (uint32_t)list_cap;
+    const uint32_t mine = bad ? kDrawn + kDrawnBad : kDrawn;
     uint32_t seen = 0;                      // (every thread has read the histogram; the answer is waited for behind the ranking)
-    if (tid == 0) seen = (uint32_t)__hip_atomic_fetch_add(ticket, bad ? 0x10001 : 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid == 0) seen = draw_ticket(ticket, mine);
     if (!bad && n_items != 0) {
         if (n_items <= (uint32_t)kPairs) {
             // few runs: every one against every other, a wavefront for 64 of them and a share of the others
@@ -651,18 +668,9 @@ __device__ __forceinline__ SelectLeft select_part(const SelectRow& row, const Se
         }
     }
     if (part == 0) row.fill_rest();
-    if (tid == 0) sOut[0] = seen + (bad ? 0x10000u : 0u);
+    if (tid == 0) sOut[0] = seen + mine;
     __syncthreads();
-    const uint32_t drawn = sOut[0];
-    if ((drawn & 0xFFFFu) != (1u << lg_parts) - 1u) return kRowDone;
-    // last to arrive: the workspace is left clean
-    if (tid == 0) __hip_atomic_store(ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (drawn >= 0x10000u) {                // (the ranks that others have written come out the same)
-        __syncthreads();
-        return kRowAnew;
-    }
-    gh[2 * tid] = 0; gh[2 * tid + 1] = 0;
-    return kRowDone;
+    return after_drawing(row, ticket, sOut[0], lg_parts, idle);
 }
 
 // From the histogram, in one scan from the top bin down (thread 0 owns the top two bins):
@@ -709,8 +717,7 @@ __device__ __forceinline__ void visit_runs(const float4 x, int j, float thr, Vis
 }
 static_assert(kRunMax == 4, "runs are found inside one float4");
 
-// The runs of a row's candidates that lds.keys holds already, or:
-constexpr int kNotListed = -1, kTooManyRuns = -2;
+constexpr int kNotListed = -1;              // instead of the number of a row's candidate runs that lds.keys holds already
 
 // The whole selection of one row by one workgroup.  known: h01 and lds.out are what the histogram says of it, and LDS is as below after the scan.
 template <bool ADAPT>                    // ADAPT: compiled with the histogram-driven bucket layout (large K only)
@@ -802,7 +809,7 @@ __device__ __forceinline__ void select_row(const SelectRow& row, const SelectLds
     if (listed >= 0) {
         n_items = (uint32_t)listed;
         in_lds = true;
-    } else if (try_list && listed != kTooManyRuns) {
+    } else if (try_list) {
         n_items = list_row();
         in_lds = n_items <= (uint32_t)cand_cap;
     }
@@ -925,11 +932,13 @@ void select_body(const float* __restrict__ pooled, int64_t pooled_stride, const 
         return;
     }
     uint2 h01 = make_uint2(0, 0);
-    const SelectLeft left = lg_parts > 0 ? select_part(row, lds, sel_counters + bg * 2, part, lg_parts, h01) : kRowAnew;
+    const SelectLeft left = lg_parts > 0 ? select_part(row, lds, sel_counters + bg * 2, part, lg_parts, 0, h01) : kRowAnew;
     if (left != kRowDone) select_row<ADAPT>(row, lds, h01, left == kRowKnown, kNotListed);
 }
 
-// A row among a few long ones (select_listed): this workgroup's 4096 positions; the last to arrive ranks.
+// A row among a few long ones (select_listed): this workgroup's 4096 positions; the last to arrive ranks.  Where the candidates hardly
+// fit one list (scores that crowd in the K-th one's bin), the first workgroups take the row by parts instead: the last to
+// arrive would have to look through all of it by itself, several times (4 rows of 262145, K = 10922, scores in clusters: 2.5 times the parts' time).
 template <bool ADAPT>
 __device__ __forceinline__
 void select_listed_body(const float* __restrict__ pooled, int64_t pooled_stride, const int32_t* seq_lens,
@@ -949,18 +958,39 @@ void select_listed_body(const float* __restrict__ pooled, int64_t pooled_stride,
         if (tile == 0) row.fill_rest();
         return;
     }
-    uint32_t* const gh = row.gh;
     const int rt = kSelThreads - 1 - tid;
-    const uint2 h01 = *reinterpret_cast<const uint2*>(gh + 2 * rt);
-    const float4 x = row.load4(tile * kSelThreads + tid);
+    uint2 h01 = *reinterpret_cast<const uint2*>(row.gh + 2 * rt);
+    const float4 x = row.load4(tile * kSelThreads + tid), sample = row.load4(tid);
     scan_histogram(row, lds, h01);
     __syncthreads();
-    int32_t* n_listed = sel_counters + bg * 2;
-    int32_t* arrived = n_listed + 1;
-    uint64_t* list = cand_list + bg * cand_cap;
-    const bool try_list = lds.out[1] + lds.out[2] <= row.list_limit();         // the same in every workgroup of the row
-    if (try_list) {
-        const float thr = value_of(lds.out[0] << kHistShift);
+    const float thr = value_of(lds.out[0] << kHistShift);
+    const uint32_t candidates = lds.out[1] + lds.out[2];
+    bool list_it = candidates <= (uint32_t)cand_cap;           // (all of this the same in every workgroup of the row)
+    if (!list_it && candidates <= row.list_limit()) {          // their runs, going by the row's first positions
+        const uint32_t some = (sample.x >= thr ? 1u : 0u) + (sample.y >= thr ? 1u : 0u) + (sample.z >= thr ? 1u : 0u) + (sample.w >= thr ? 1u : 0u);
+        uint32_t total;
+        (void)block_inclusive_scan<kSelThreads>(count_runs(sample, thr) << 16 | some, lds.scan, &total);
+        list_it = total != 0 && candidates * (total >> 16) <= (total & 0xFFFFu) * (uint32_t)min(cand_cap - cand_cap / 8, max(kListRuns, n >> 5));
+    }
+    SelectLeft left = kRowKnown;
+    int runs = kNotListed;
+    if (!list_it || lds.out[0] < (uint32_t)kHistBins / 2) {
+        constexpr int kLgParts = 3, kParts = 1 << kLgParts;
+        static_assert((kListFrom + kListTile - 1) / kListTile >= kParts && kListRows * kParts <= kComputeUnits, "a listed row has workgroups for its parts");
+        const int idle = (int)gridDim.x - kParts;
+        int32_t* ticket = sel_counters + bg * 2;
+        if (tile < kParts) {
+            left = select_part(row, lds, ticket, tile, kLgParts, idle, h01);
+        } else {
+            if (tid == 0) lds.part[0] = draw_ticket(ticket, kDrawnIdle) + kDrawnIdle;
+            __syncthreads();
+            left = after_drawing(row, ticket, lds.part[0], kLgParts, idle);
+        }
+        if (left == kRowDone) return;
+    } else {
+        int32_t* n_listed = sel_counters + bg * 2;
+        int32_t* arrived = n_listed + 1;
+        uint64_t* list = cand_list + bg * cand_cap;
         const uint32_t c = count_runs(x, thr);
         uint32_t total;
         const uint32_t incl = block_inclusive_scan<kSelThreads>(c, lds.scan, &total);
@@ -974,28 +1004,25 @@ void select_listed_body(const float* __restrict__ pooled, int64_t pooled_stride,
             ++pos;
         });
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // the list entries are acknowledged
-    }
-    __syncthreads();                                           // ... and every thread has read the histogram
-    if (tid == 0) lds.part[0] = (uint32_t)__hip_atomic_fetch_add(arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __syncthreads();
-    if (lds.part[0] != gridDim.x - 1) return;
-    // last to arrive: everything of this row is in (a workgroup has the answer of its reservation before it writes its
-    // entries, hence before its ticket: the count is final); leave the workspace clean, then rank
-    if (tid == 0) {
-        lds.part[1] = (uint32_t)__hip_atomic_load(n_listed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(n_listed, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(arrived, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        *lds.count = 0;
-    }
-    gh[2 * rt] = 0; gh[2 * rt + 1] = 0;
-    __syncthreads();
-    const uint32_t runs = lds.part[1];
-    const bool fits = try_list && runs <= (uint32_t)cand_cap;
-    if (fits) {
-        for (uint32_t e = tid; e < runs; e += kSelThreads) lds.keys[e] = __hip_atomic_load(&list[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();                                       // ... and every thread has read the histogram
+        if (tid == 0) lds.part[0] = (uint32_t)__hip_atomic_fetch_add(arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        if (lds.part[0] != gridDim.x - 1) return;
+        // last to arrive: everything of this row is in (a workgroup has the answer of its reservation before it writes its
+        // entries, hence before its ticket: the count is final); leave the workspace clean, then rank
+        if (tid == 0) {
+            lds.part[1] = (uint32_t)__hip_atomic_load(n_listed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(n_listed, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(arrived, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            *lds.count = 0;
+        }
+        row.gh[2 * rt] = 0; row.gh[2 * rt + 1] = 0;
+        __syncthreads();
+        if (lds.part[1] <= (uint32_t)cand_cap) runs = (int)lds.part[1];
+        for (int e = tid; e < runs; e += kSelThreads) lds.keys[e] = __hip_atomic_load(&list[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
     }
-    select_row<ADAPT>(row, lds, h01, true, fits ? (int)runs : try_list ? kTooManyRuns : kNotListed);
+    select_row<ADAPT>(row, lds, h01, left == kRowKnown, runs);
 }
 
 // Grid (workgroups of a row, KV heads, sequences).

@@ -647,8 +647,9 @@ def _select_scores(name, rows, n, g):
     return w
 
 
-# Bins with more than four times K positions, which a part looks into ("narrow", "one_bin", "steps"), (scores, B, Hkv, n, k, pool): 8 / 4 / 2 / 1 workgroups per row, fewer ranks than workgroups, fewer positions than ranks, vectors of
-# four and rounds of 32768 positions that end in the row, more than 256 runs in a stretch
+# (scores, B, Hkv, n, k, pool): 8 / 4 / 2 / 1 workgroups per row, fewer ranks than workgroups, fewer positions than ranks, vectors of
+# four and rounds of 32768 positions that end in the row, more than 256 runs in a stretch; bins with more than four times K positions,
+# which a part looks into ("narrow", "one_bin", "steps")
 SELECT_EDGES = [("normal", 1, 1, 1, 1, 1), ("normal", 1, 2, 9, 3, 7), ("normal", 1, 3, 31, 100, 7), ("normal", 1, 8, 1027, 9, 1), ("normal", 2, 16, 4099, 300, 7),
                 ("normal", 5, 8, 5001, 700, 3), ("normal", 16, 8, 3001, 257, 7), ("normal", 33, 8, 1025, 64, 7), ("normal", 1, 8, 32771, 2048, 7),
                 ("normal", 1, 4, 65537, 8192, 1), ("normal", 1, 2, 98305, 16384, 7), ("levels", 1, 8, 20001, 3000, 1), ("levels", 3, 8, 20001, 900, 7),
@@ -659,7 +660,11 @@ SELECT_EDGES = [("normal", 1, 1, 1, 1, 1), ("normal", 1, 2, 9, 3, 7), ("normal",
                 # a few long rows: listed by a workgroup per 4096 positions, ranked by the last to arrive
                 ("normal", 1, 1, 98304, 3, 1), ("normal", 3, 2, 98309, 4096, 7), ("normal", 1, 4, 163841, 8192, 1), ("normal", 1, 1, 327683, 16384, 7),
                 ("levels", 2, 2, 98305, 2000, 1), ("equal", 1, 1, 98306, 500, 7), ("narrow", 1, 6, 100003, 1500, 7), ("mostly_zero", 2, 1, 98307, 2000, 1),
-                ("infinite", 1, 3, 98305, 300, 7)]
+                ("infinite", 1, 3, 98305, 300, 7), ("normal", 1, 1, 49152, 3072, 7), ("normal", 4, 1, 49157, 1000, 1), ("infinite", 2, 1, 49153, 1500, 1),
+                # ... shared out by rank after all, all of them or some (candidates that do not fit, not even as runs; thousands of runs), by one workgroup
+                ("narrow", 1, 2, 49153, 3000, 1), ("narrow", 2, 3, 65537, 4096, 7), ("narrow2", 1, 4, 65539, 4096, 7), ("narrow2", 1, 1, 196611, 12288, 7),
+                ("one_bin", 1, 1, 50001, 2000, 1), ("steps", 1, 3, 70001, 1100, 1), ("levels", 1, 2, 262147, 10000, 1), ("equal", 3, 1, 49155, 3000, 1),
+                ("mostly_zero", 1, 5, 50003, 1000, 1)]
 
 
 @pytest.mark.parametrize("case", SELECT_EDGES, ids=["%s_%dx%d_%d_k%d_w%d" % c for c in SELECT_EDGES])
