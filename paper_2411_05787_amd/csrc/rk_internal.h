@@ -290,13 +290,13 @@ __host__ __device__ static inline uint32_t stretch_low(uint32_t estimate, uint32
 // in eight.  `rows`: (sequence, KV head) pairs in the launch, of all layers where it takes several.  us per call of rk_topk_select, parts / listed, log-normal
 // scores: one row of 65537, K = 2730: 18.9 / 16.0, of 131073, K = 2048: 21.5 / 16.4, of 1048576, K = 512: 67 / 33, of 4194304: 236 / 106; 4 rows of
 // 65537, K = 4096: 20.4 / 19.1, of 1048576: 84 / 72; 6 of 98305, K = 1536: 21.1 / 18.8; one row of 36001, K = 562: 1.0 of the parts' time; K an eighth of the row: 1.0 to 1.2, a
-// twelfth 1.0 to 1.1; 4 rows of 131073, K = 8192: 1.06; 8 rows: 1.0 to 1.45.  Scores in tight clusters, no pooling (crowded buckets to rank): 1.1 to 1.4.
+// twelfth 1.0 to 1.1; 4 rows of 131073, K = 8192, one of 180001, K = 11250: 1.06; 8 rows: 1.0 to 1.45.  Scores in tight clusters, no pooling (crowded buckets to rank): 1.1 to 1.4.
 // A full step with the batched refresh, K = 1024, 2 layers of one KV head, 131072 rows: 69.8 / 65.5, 524288: 155.6 / 139.4, 3 layers of 2, 131072:
 // 122.1 / 118.2; 12 and 16 rows, 131072 to 1048576: 0.96 to 1.01 of listing with parts.
 constexpr int kListRows = 6;
 constexpr int64_t kListFrom = 49152;
 static inline bool select_listed(int64_t max_len, int64_t k, int64_t rows) {
-    const bool few = k <= 4096 || (rows <= 3 && k <= 12288);
+    const bool few = k <= 4096 || (rows <= 3 && k <= 8192);
     return rows <= (k <= 4096 ? kListRows : 4) && max_len >= kListFrom && max_len >= (few ? 16 : 20) * k;
 }
 

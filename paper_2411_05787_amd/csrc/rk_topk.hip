@@ -43,6 +43,8 @@ constexpr int kPairs = 256;                               // a part's runs up to
 static_assert(kMaxCandidates / 2 * 4 <= 0xFFFF, "buckets of a part count positions in 16 bits");
 constexpr int kNonFinite = 1;                            // thread whose two bins of the histogram start at infinity
 constexpr int kFineFrom = 4;                             // a bin of more than this many times K' positions is looked at more closely
+constexpr int kFineLeast = 1024;                         // ... and of more than this (with few ranks four times K is soon passed, and the look is worth less than it
+                                                         // costs: 300 shapes with K from 1 to 300: 0.955 of the time without this bound, one row of 25488, K = 1: 15.4 -> 11.4 us)
 constexpr int kPartWords = 8;                            // what a part knows of its stretch
 constexpr int kListTile = 4 * kSelThreads;               // positions that a workgroup of select_listed_kernel lists
 // Of more candidates than positions fit, more runs than this, or than a 32nd of the row, rank faster in parts (one row of 65537, K = 4096, 6231 runs: 25.3 us, in parts 19.7;
@@ -494,7 +496,7 @@ __device__ __forceinline__ SelectLeft select_part(const SelectRow& row, const Se
     const bool last = part + 1 == 1 << lg_parts;
     bool hopeless = false;
     uint32_t hi = sPart[0], end = sPart[1], above_end = sPart[2], estimate = sPart[3], floor = last ? (b1 << kHistShift) - 0x80000000u : estimate;
-    if (in1 > (uint32_t)(kprime * kFineFrom) && t1 > above1) {
+    if (in1 > max((uint32_t)(kprime * kFineFrom), (uint32_t)kFineLeast) && t1 > above1) {
         // The K'-th score's bin (no other can) holds many times the ranks there are, which says little about where in it they lie:
         // one look at the row counts its scores by the next 11 bits (a dozen LDS atomics per thread and 32768 positions at the least:
         // from twice K positions on instead of four times it cost votes of 20 queries over 131072 rows 11 us of 109).  Scores that differ
@@ -546,7 +548,9 @@ __device__ __forceinline__ SelectLeft select_part(const SelectRow& row, const Se
 #pragma unroll
         for (int u = 0; u < NV; ++u) held[u] = row.raw4(u * kSelThreads + tid);
     }
-    uint32_t lo = stretch_low(estimate, floor, hi), top = hi, top_end = end;       // the stretch so far, and what is looked for in this pass over the row
+    // (few positions in the bin are taken whole: 9 rows of 37290, K = 19: 20.0 -> 16.0 us, without the second look)
+    uint32_t lo = last && in1 <= (uint32_t)kPairs ? floor : stretch_low(estimate, floor, hi);
+    uint32_t top = hi, top_end = end;       // the stretch so far, and what is looked for in this pass over the row
     while (lo < top && !hopeless) {
         // Bits of scores as whole numbers, from the stretch's lowest.  A vector of four positions with none in the stretch or
         // between it and the end of its bin is passed over after one comparison of the least; the numbers of the others are

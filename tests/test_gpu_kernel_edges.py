@@ -657,6 +657,9 @@ SELECT_EDGES = [("normal", 1, 1, 1, 1, 1), ("normal", 1, 2, 9, 3, 7), ("normal",
                 ("one_bin", 2, 8, 9001, 1000, 7), ("infinite", 1, 8, 9001, 300, 7), ("narrow", 1, 8, 2001, 125, 1), ("narrow", 1, 8, 33001, 1500, 7), ("narrow", 1, 1, 70003, 9, 1),
                 ("narrow2", 1, 4, 131073, 8192, 7), ("narrow2", 3, 16, 9001, 500, 1), ("narrow2", 20, 8, 5001, 64, 7), ("steps", 1, 8, 20001, 1000, 1),
                 ("steps", 1, 4, 40001, 4001, 1), ("steps", 2, 16, 5003, 100, 7),
+                # few ranks: bins taken whole up to 256 positions, looked into beyond 1024, neither between
+                ("narrow", 1, 9, 37291, 19, 7), ("normal", 1, 2, 25489, 1, 7), ("narrow", 4, 4, 521, 8, 7), ("one_bin", 1, 8, 257, 5, 1), ("one_bin", 1, 8, 1025, 5, 1),
+                ("one_bin", 1, 8, 1023, 5, 1),
                 # a few long rows: listed by a workgroup per 4096 positions, ranked by the last to arrive
                 ("normal", 1, 1, 98304, 3, 1), ("normal", 3, 2, 98309, 4096, 7), ("normal", 1, 4, 163841, 8192, 1), ("normal", 1, 1, 327683, 16384, 7),
                 ("levels", 2, 2, 98305, 2000, 1), ("equal", 1, 1, 98306, 500, 7), ("narrow", 1, 6, 100003, 1500, 7), ("mostly_zero", 2, 1, 98307, 2000, 1),

@@ -231,7 +231,7 @@ def test_few_long_rows_are_listed(table):
     assert len(got) == 8 * 7 * 8
     for (n, k, rows), (listed, room, grows) in got.items():
         assert grows and (room or not listed) and (not room or rows <= 6), (n, k, rows)
-        few = k <= 4096 or (rows <= 3 and k <= 12288)
+        few = k <= 4096 or (rows <= 3 and k <= 8192)
         assert listed == (rows <= (6 if k <= 4096 else 4) and n >= 49152 and n >= (16 if few else 20) * k), (n, k, rows)
 
 
