@@ -37,7 +37,7 @@
 // The rows of a wavefront's next tile are requested as soon as the registers of the current tile
 // are consumed (K after S^T, V after the copy to LDS), so loads are in flight during the rest of
 // the tile's work.
-#include "rk_attn_common.h"
+#include "rk_tile.h"
 
 #include <atomic>
 #include <mutex>
@@ -680,11 +680,13 @@ constexpr int kSliceChunks = 20, kSliceChunks4 = 64;   // the merge by slices se
 // seq_lens[b] rows of it (the rows kept so far), the second the new token's row, read where the caller has
 // it: k2 / v2 with one row per (sequence, KV head).  n_sel is the most rows the step attends over; a cache that
 // is over it already (outside the policy's contract) is cut there and the new row is left out.
-template <int G, int NW, bool EMIT, bool TWO_SEG, bool LAZY = false, bool TAGGED = !EMIT, bool TRIG = false, bool EXACT = false>
-__global__ __launch_bounds__(NW * 64, 2)
-void attn_split_kernel(const uint16_t* k_first, const uint16_t* v_first, int64_t s_b_and_tail, int32_t s_h, int32_t spec_rows,
-                       const int32_t* seq_lens, const int32_t* tail_start, const int32_t* pred, const uint32_t* epochs,
-                       const AttnParams p) {
+// One workgroup's part of it: workgroup c of KV head g of sequence b (heads_first: see attn_split_kernel).  tail_c: the grid x of the
+// workgroup that takes the rows of the full cache on its own (kNoTailWg: none; see tail_mode below).
+template <int G, int NW, bool EMIT, bool TWO_SEG, bool LAZY, bool TAGGED, bool TRIG, bool EXACT>
+__device__ __forceinline__
+void split_pass(const uint16_t* k_first, const uint16_t* v_first, int64_t s_b, int tail_c, int32_t s_h, int32_t spec_rows,
+                const int32_t* seq_lens, const int32_t* tail_start, const int32_t* pred, const uint32_t* epochs,
+                const AttnParams& p, int c, int g, int b, int n_kv) {
     static_assert(!LAZY || (TWO_SEG && !EMIT), "the lazy gather belongs to the partial step");
     // (EMIT with TAGGED: the scores go out as usual, and the output is merged inside the kernel all the same; the
     // per-chunk (max, sum) pairs are still stored for the kernels that turn the scores into weights)
@@ -692,13 +694,6 @@ void attn_split_kernel(const uint16_t* k_first, const uint16_t* v_first, int64_t
     constexpr bool APPEND = EMIT && TWO_SEG;
     static_assert(!EXACT || (EMIT && TAGGED), "the exact merge belongs to the full passes that merge inside");
     static_assert(!APPEND || (!TAGGED && !TRIG && !LAZY), "merged by the kernel that updates the totals");
-    // The leading arguments repeat what the first loads need (the cache that holds the first rows,
-    // its strides, the two length arrays, the predicate, the call numbers): 16 dwords that the command processor
-    // hands over in registers at wavefront launch (kernel-argument preload), so neither the first
-    // K/V request nor the read of the lengths waits for a read of the argument block.  Everything
-    // else comes from `p` as before (tail_start is NULL unless TWO_SEG).  A launch with a predicate
-    // does wait for it (and for p.pred_val) before it requests anything: a switched-off sequence
-    // must not cost memory traffic.
     constexpr int ROWS = kTileRows;          // rows per wavefront and tile = contraction depth of P V
     constexpr bool KLDS = !TWO_SEG;          // K rows reach the operand layout through LDS (see load_k)
     static_assert(NW == kSplitWaves, "work split");
@@ -707,19 +702,7 @@ void attn_split_kernel(const uint16_t* k_first, const uint16_t* v_first, int64_t
     constexpr int NT = NW * 64;
     constexpr int VS = kD + 8;               // LDS row stride of the V tile (272 bytes: rows spread over banks)
 
-    // The sequence stride also carries, in its top byte, the grid x of the workgroup that takes the
-    // rows of the full cache on its own (kNoTailWg: none; see tail_mode below): like everything the
-    // first loads need, it is there when the wavefront starts.
-    const int64_t s_b = s_b_and_tail & ((1ll << 56) - 1);
-    const int tail_c = (int)(s_b_and_tail >> 56) & 0xff;
-    // kHeadsFirst in the same byte (launches of the full-cache kernel over one sequence or an evenly split
-    // batch): the KV head is grid x and the chunk grid z.  Workgroups are handed out in the grid's linear
-    // order, x fastest, and go to the 8 XCDs in turn: with the heads as x every XCD streams the same
-    // KV heads from start to end instead of every eighth chunk of all heads.
-    const bool heads_first = !TWO_SEG && tail_c == kHeadsFirst;
-    int c = heads_first ? blockIdx.z : blockIdx.x, b = heads_first ? blockIdx.y : blockIdx.z, nch_b = p.nch;
-    const int g = heads_first ? blockIdx.x : blockIdx.y;
-    const int n_kv = heads_first ? gridDim.x : gridDim.y;
+    int nch_b = p.nch;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int n16 = lane & 15, c4 = lane >> 4;
     constexpr bool kCanBeRagged = EMIT;
@@ -1293,6 +1276,53 @@ void attn_split_kernel(const uint16_t* k_first, const uint16_t* v_first, int64_t
     if (sTicket != nchunks - 1) return;
     merge_partials<G, NW>(p, b, g, nchunks, &sO[0][0][0], &sO[0][0][0] + kMergeChunks * G, sMf, sLf);
     if (tid == 0) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // next call
+}
+
+template <int G, int NW, bool EMIT, bool TWO_SEG, bool LAZY = false, bool TAGGED = !EMIT, bool TRIG = false, bool EXACT = false>
+__global__ __launch_bounds__(NW * 64, 2)
+void attn_split_kernel(const uint16_t* k_first, const uint16_t* v_first, int64_t s_b_and_tail, int32_t s_h, int32_t spec_rows,
+                       const int32_t* seq_lens, const int32_t* tail_start, const int32_t* pred, const uint32_t* epochs,
+                       const AttnParams p) {
+    // The leading arguments repeat what the first loads need (the cache that holds the first rows,
+    // its strides, the two length arrays, the predicate, the call numbers): 16 dwords that the command processor
+    // hands over in registers at wavefront launch (kernel-argument preload), so neither the first
+    // K/V request nor the read of the lengths waits for a read of the argument block.  Everything
+    // else comes from `p` as before (tail_start is NULL unless TWO_SEG).  A launch with a predicate
+    // does wait for it (and for p.pred_val) before it requests anything: a switched-off sequence
+    // must not cost memory traffic.
+    // The sequence stride also carries, in its top byte, the grid x of the workgroup that takes the
+    // rows of the full cache on its own (kNoTailWg: none; see tail_mode below): like everything the
+    // first loads need, it is there when the wavefront starts.
+    const int64_t s_b = s_b_and_tail & ((1ll << 56) - 1);
+    const int tail_c = (int)(s_b_and_tail >> 56) & 0xff;
+    // kHeadsFirst in the same byte (launches of the full-cache kernel over one sequence or an evenly split
+    // batch): the KV head is grid x and the chunk grid z.  Workgroups are handed out in the grid's linear
+    // order, x fastest, and go to the 8 XCDs in turn: with the heads as x every XCD streams the same
+    // KV heads from start to end instead of every eighth chunk of all heads.
+    const bool heads_first = !TWO_SEG && tail_c == kHeadsFirst;
+    const int c = heads_first ? blockIdx.z : blockIdx.x, b = heads_first ? blockIdx.y : blockIdx.z;
+    const int g = heads_first ? blockIdx.x : blockIdx.y;
+    const int n_kv = heads_first ? gridDim.x : gridDim.y;
+    split_pass<G, NW, EMIT, TWO_SEG, LAZY, TAGGED, TRIG, EXACT>(k_first, v_first, s_b, tail_c, s_h, spec_rows, seq_lens, tail_start, pred, epochs,
+                                                                p, c, g, b, n_kv);
+}
+
+// Both branches of a step on which the trigger is tested, over one sequence (Section 2.2, "Deciding when to decode with full cache").
+// The partial step goes as far as its maxima before the decision is looked at (partial_tile); where the sequence needs a full step, the
+// same workgroup then is its part of the full pass.  As two launches, the branch that was not taken still cost one: 4.7 us for a full
+// pass that leaves at its predicate, 6.9 for a partial step that gives up after the test.  Two test
+// steps of 28 layers at 65536 rows, 28 heads over 4, 21 of the 56 full: 1226 -> 1059 us (figures per layer at test_step_form).
+// The test is a wavefront's work beside its rows: the wavefronts of a workgroup go to the four SIMDs in the same order every time, so that
+// two workgroups of five would need four wavefronts' registers on one of them, and this kernel's are good for two.
+template <int G, bool EXACT>
+__global__ __launch_bounds__(kSplitWaves * 64, 2)
+void test_step_kernel(const uint16_t* k1, const uint16_t* v1, int64_t s_b_and_tail, int32_t s_h, uint32_t rows_heads,
+                      const int32_t* seq_lens, const int32_t* tail_start, const uint16_t* q, const TileParams t, const AttnParams p) {
+    const int g = blockIdx.x, c = blockIdx.y;      // (heads first: see attn_split_kernel)
+    if (!partial_tile<G, kSplitWaves, kTestInside, false>(k1, v1, s_b_and_tail, s_h, rows_heads, seq_lens, tail_start, q, t, c, g, 0)) return;
+    if (c >= p.nch) return;
+    split_pass<G, kSplitWaves, true, false, false, true, false, EXACT>(p.k2, p.v2, 0, kHeadsFirst, (int32_t)p.s2_h, p.cap2, seq_lens, nullptr, nullptr,
+                                                                       p.epochs, p, c, g, 0, (int)gridDim.x);
 }
 
 // Scores-only pass over the full cache (Section 4.3, "Impact of full attention steps", the
@@ -1879,13 +1909,11 @@ static int launch_score_split(const AttnParams& p, int batch, int G, int nchunk_
     return launch_status();
 }
 
-int full_attn_stage(const rk_geom* geom, const void* q, rk_kv full, const int32_t* seq_lens, int32_t max_len,
-                    void* out, float* weights, int64_t w_stride, float* lse, const int32_t* pred, int32_t pred_val,
-                    const Workspace& ws, hipStream_t st, bool scores_only, int pool_half, bool no_v, int agg,
-                    bool defer_pool, int nch) {
+// Parameters of a pass over the full cache; emit: with scores, fused: which stay in the workspace.
+static AttnParams full_params(const rk_geom* geom, const void* q, rk_kv full, const int32_t* seq_lens, int32_t max_len, void* out,
+                              float* weights, int64_t w_stride, float* lse, const int32_t* pred, int32_t pred_val, const Workspace& ws,
+                              bool emit, bool fused, bool no_v, int nch) {
     const int G = geom->n_q_heads / geom->n_kv_heads;
-    const bool fused = pool_half >= 0;
-    const bool emit = weights != nullptr || fused;
     AttnParams p{};
     p.q = (const uint16_t*)q;
     p.k2 = (const uint16_t*)full.k; p.v2 = (const uint16_t*)full.v;
@@ -1907,6 +1935,17 @@ int full_attn_stage(const rk_geom* geom, const void* q, rk_kv full, const int32_
     p.epochs = ws.epochs; p.tag_rows = ws.tag_rows;
     p.ragged_batch = (emit && !no_v) ? ragged_batch_of(geom) : 0;
     p.share_cap = kMaxChunks;
+    return p;
+}
+
+int full_attn_stage(const rk_geom* geom, const void* q, rk_kv full, const int32_t* seq_lens, int32_t max_len,
+                    void* out, float* weights, int64_t w_stride, float* lse, const int32_t* pred, int32_t pred_val,
+                    const Workspace& ws, hipStream_t st, bool scores_only, int pool_half, bool no_v, int agg,
+                    bool defer_pool, int nch) {
+    const int G = geom->n_q_heads / geom->n_kv_heads;
+    const bool fused = pool_half >= 0;
+    const bool emit = weights != nullptr || fused;
+    AttnParams p = full_params(geom, q, full, seq_lens, max_len, out, weights, w_stride, lse, pred, pred_val, ws, emit, fused, no_v, nch);
     if (!emit) {
         // No scores wanted.  Short rows: one launch, merged by the last workgroup inside it (at most
         // kMergeChunks partial results).  Long rows: the wider split of the score-emitting kernel
@@ -2104,13 +2143,9 @@ static int check_partial_args(const rk_geom* geom, const void* q, rk_kv small, i
 // The query-similarity test a partial step carries out itself (rk_partial_attn_triggered).
 struct Trigger { float* q_ref; float threshold; float* sim; int32_t* need_full; };
 
-// Launch of the partial step; `ws` needs counters, lse, part_ml, part_o and max_chunks only.
-static int launch_partial(const rk_geom* geom, const void* q, rk_kv small, int32_t n_sel, bool evict,
-                          rk_kv full, const int32_t* tail_start, const int32_t* seq_lens,
-                          int32_t max_recent, void* out, const int32_t* pred, int32_t pred_val,
-                          const Workspace& ws, void* stream, const int32_t* lazy_idx = nullptr,
-                          const Trigger* trig = nullptr) {
-    const int G = geom->n_q_heads / geom->n_kv_heads;
+static AttnParams partial_params(const rk_geom* geom, const void* q, rk_kv small, int32_t n_sel, bool evict, rk_kv full,
+                                 const int32_t* tail_start, const int32_t* seq_lens, int32_t max_recent, void* out,
+                                 const int32_t* pred, int32_t pred_val, const Workspace& ws, const Trigger* trig) {
     AttnParams p{};
     p.q = (const uint16_t*)q;
     p.k1 = (const uint16_t*)small.k; p.v1 = (const uint16_t*)small.v;
@@ -2130,13 +2165,22 @@ static int launch_partial(const rk_geom* geom, const void* q, rk_kv small, int32
     p.pred = pred; p.pred_val = pred_val;
     p.counters = ws.counters; p.part_ml = ws.part_ml; p.part_o = ws.part_o; p.max_chunks = ws.max_chunks;
     p.epochs = ws.epochs; p.tag_rows = ws.tag_rows;
+    if (trig != nullptr) { p.trig_q_ref = trig->q_ref; p.trig_sim = trig->sim; p.trig_need = trig->need_full; p.trig_threshold = trig->threshold; }
+    return p;
+}
+
+// Launch of the partial step; `ws` needs counters, lse, part_ml, part_o and max_chunks only.
+static int launch_partial(const rk_geom* geom, const void* q, rk_kv small, int32_t n_sel, bool evict,
+                          rk_kv full, const int32_t* tail_start, const int32_t* seq_lens,
+                          int32_t max_recent, void* out, const int32_t* pred, int32_t pred_val,
+                          const Workspace& ws, void* stream, const int32_t* lazy_idx = nullptr,
+                          const Trigger* trig = nullptr) {
+    const int G = geom->n_q_heads / geom->n_kv_heads;
+    if (trig != nullptr && (ws.tag_rows == nullptr || pred != nullptr)) return RK_ERR_INVALID_ARG;
+    AttnParams p = partial_params(geom, q, small, n_sel, evict, full, tail_start, seq_lens, max_recent, out, pred, pred_val, ws, trig);
     // one tile per workgroup where all of them are resident at once
     const TileForm tile = partial_tile_form(n_sel, max_recent, (int64_t)geom->batch * geom->n_kv_heads, G, trig != nullptr);
     if (tile.waves != 0 && ws.tag_rows != nullptr && lazy_idx == nullptr) {
-        if (trig != nullptr) {
-            if (pred != nullptr) return RK_ERR_INVALID_ARG;
-            p.trig_q_ref = trig->q_ref; p.trig_sim = trig->sim; p.trig_need = trig->need_full; p.trig_threshold = trig->threshold;
-        }
         p.nch = tile.nch; p.tail_wg = tile.tail;
         set_slice_merge(p, true, 0);
         return launch_partial_tile(p, geom->batch, G, tile, trig != nullptr, (hipStream_t)stream);
@@ -2181,23 +2225,13 @@ static int launch_partial(const rk_geom* geom, const void* q, rk_kv small, int32
         return launch_lazy(p, geom->batch, G, (hipStream_t)stream);
     }
     const int nchunk_grid = p.nch + p.tail_wg;
-    if (trig != nullptr) {
-        if (ws.tag_rows == nullptr || pred != nullptr) return RK_ERR_INVALID_ARG;
-        p.trig_q_ref = trig->q_ref; p.trig_sim = trig->sim; p.trig_need = trig->need_full; p.trig_threshold = trig->threshold;
-        return launch_split_triggered(p, geom->batch, G, nchunk_grid, tagged, (hipStream_t)stream);
-    }
+    if (trig != nullptr) return launch_split_triggered(p, geom->batch, G, nchunk_grid, tagged, (hipStream_t)stream);
     if (!tagged) return launch_split<false, true, false>(p, geom->batch, G, nchunk_grid, (hipStream_t)stream);
     return launch_split<false, true>(p, geom->batch, G, nchunk_grid, (hipStream_t)stream);
 }
 
-static int partial_attn_impl(const rk_geom* geom, const void* q, rk_kv small, int32_t n_sel, bool evict,
-                             rk_kv full, const int32_t* tail_start, const int32_t* seq_lens,
-                             int32_t max_recent, void* out,
-                             const int32_t* pred, int32_t pred_val,
-                             void* workspace, size_t workspace_bytes, void* stream, const int32_t* lazy_idx = nullptr,
-                             const Trigger* trig = nullptr) {
-    int rc = check_partial_args(geom, q, small, n_sel, full, tail_start, seq_lens, max_recent, out);
-    if (rc != RK_OK) return rc;
+// The workspace of a partial step.
+static int check_partial_workspace(const rk_geom* geom, void* workspace, size_t workspace_bytes, Workspace* out) {
     // What the step uses of the workspace lies at offsets that follow from the geometry alone; only the
     // partial outputs of the ticketed form grow with the launch (one slot per workgroup of a (sequence,
     // KV head), at most kMergeChunks): a bound on the rows decoded since the refresh that keeps growing
@@ -2210,6 +2244,20 @@ static int partial_attn_impl(const rk_geom* geom, const void* q, rk_kv small, in
     if (workspace_bytes < before + slot) return RK_ERR_WORKSPACE;
     const size_t slots = (workspace_bytes - before) / slot;
     ws.max_chunks = slots < (size_t)kMergeChunks ? (int)slots : kMergeChunks;     // the launch takes no more workgroups than this
+    *out = ws;
+    return RK_OK;
+}
+
+static int partial_attn_impl(const rk_geom* geom, const void* q, rk_kv small, int32_t n_sel, bool evict,
+                             rk_kv full, const int32_t* tail_start, const int32_t* seq_lens,
+                             int32_t max_recent, void* out,
+                             const int32_t* pred, int32_t pred_val,
+                             void* workspace, size_t workspace_bytes, void* stream, const int32_t* lazy_idx = nullptr,
+                             const Trigger* trig = nullptr) {
+    int rc = check_partial_args(geom, q, small, n_sel, full, tail_start, seq_lens, max_recent, out);
+    if (rc != RK_OK) return rc;
+    Workspace ws;
+    if ((rc = check_partial_workspace(geom, workspace, workspace_bytes, &ws)) != RK_OK) return rc;
     return launch_partial(geom, q, small, n_sel, evict, full, tail_start, seq_lens, max_recent, out, pred, pred_val,
                           ws, stream, lazy_idx, trig);
 }
@@ -2257,6 +2305,58 @@ extern "C" int rk_partial_attn_triggered(const rk_geom* geom, const void* q, rk_
     return partial_attn_impl(geom, q, small, n_sel, fixed_size != 0, full, tail_start, seq_lens, max_recent, out,
                              nullptr, 0, workspace, workspace_bytes, stream, nullptr, &trig);
 }
+
+// ---- a layer's step on which the trigger is tested, both branches ----
+namespace rk {
+template <int G, bool EXACT>
+static int launch_test_step(const AttnParams& part, const AttnParams& full, hipStream_t st) {
+    const TileArgs a = tile_args(part);
+    const int wgs = part.nch + part.tail_wg > full.nch ? part.nch + part.tail_wg : full.nch;
+    hipLaunchKernelGGL((test_step_kernel<G, EXACT>), dim3(part.Hkv, wgs), dim3(kSplitWaves * 64), 0, st, part.k1, part.v1, a.s_b_and_tail,
+                       (int32_t)part.s1_h, a.rows_heads, part.seq_lens, part.tail_start, part.q, a.t, full);
+    return launch_status();
+}
+template <int G>
+static int launch_test_step_g(const AttnParams& part, const AttnParams& full, bool exact, hipStream_t st) {
+    if constexpr (G <= 4)
+        if (!exact) return launch_test_step<G, false>(part, full, st);
+    return launch_test_step<G, true>(part, full, st);
+}
+
+int test_step_stage(const rk_geom* geom, const void* q, const rk_layer_state& L, const rk_schedule* sched, const int32_t* seq_lens, int32_t max_len,
+                    int32_t max_recent, void* out, void* workspace, size_t workspace_bytes, hipStream_t st) {
+    const TileForm tile = test_step_form(geom, sched->k, max_recent, max_len);
+    if (tile.waves == 0) {
+        const int rc = rk_partial_attn_triggered(geom, q, L.small, sched->k, sched->fixed_size, L.full, L.tail_start, seq_lens, max_recent, out,
+                                                 L.q_ref, sched->threshold, L.sim, L.need_full, workspace, workspace_bytes, st);
+        if (rc != RK_OK) return rc;
+        return rk_full_attn_deferred(geom, q, L.full, seq_lens, max_len, out, nullptr, L.need_full, 1, workspace, workspace_bytes, st);
+    }
+    if (!L.q_ref || !L.sim || !L.need_full || !aligned16(L.q_ref)) return RK_ERR_INVALID_ARG;
+    int rc = check_partial_args(geom, q, L.small, sched->k, L.full, L.tail_start, seq_lens, max_recent, out);
+    if (rc == RK_OK) rc = check_full_args(geom, q, L.full, seq_lens, max_len, out, true, nullptr, 0);
+    if (rc != RK_OK) return rc;
+    Workspace part_ws, ws;
+    if ((rc = check_partial_workspace(geom, workspace, workspace_bytes, &part_ws)) != RK_OK) return rc;
+    if ((rc = check_workspace(geom, max_len, 0, workspace, workspace_bytes, &ws)) != RK_OK) return rc;
+    const Trigger trig{L.q_ref, sched->threshold, L.sim, L.need_full};
+    AttnParams part = partial_params(geom, q, L.small, sched->k, sched->fixed_size != 0, L.full, L.tail_start, seq_lens, max_recent, out, nullptr, 0,
+                                     part_ws, &trig);
+    part.nch = tile.nch; part.tail_wg = tile.tail;
+    set_slice_merge(part, true, 0);
+    AttnParams full = full_params(geom, q, L.full, seq_lens, max_len, out, nullptr, 0, nullptr, nullptr, 0, ws, true, true, false, 0);
+    full.nch = inside_split_workgroups(geom, max_len);
+    full.share_cap = kMergeChunks;
+    set_slice_merge(full, true, 0);
+    const bool exact = !merges_in_fp32(geom, max_len);
+    switch (geom->n_q_heads / geom->n_kv_heads) {
+#define RK_CASE(g) case g: return launch_test_step_g<g>(part, full, exact, st);
+        RK_CASE(1) RK_CASE(2) RK_CASE(3) RK_CASE(4) RK_CASE(5) RK_CASE(6) RK_CASE(7) RK_CASE(8)
+#undef RK_CASE
+        default: return RK_ERR_UNSUPPORTED;
+    }
+}
+}  // namespace rk
 
 // ---- rk_partial_attn_static: the partial step for callers that cannot allocate ----
 // The scratch memory of the step (arrival counters, per-workgroup statistics and partial outputs)

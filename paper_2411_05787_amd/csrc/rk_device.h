@@ -185,7 +185,7 @@ __device__ __forceinline__ float similarity_finish(const uint16_t* q, int b, int
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
         mean[j] = sum_xor32(sum_xor16(acc[j])) / (float)Hq;
-        dot += mean[j] * ref[j]; n1 += mean[j] * mean[j]; n2 += ref[j] * ref[j];
+        dot = fmaf(mean[j], ref[j], dot); n1 = fmaf(mean[j], mean[j], n1); n2 = fmaf(ref[j], ref[j], n2);      // (by name: every kernel rounds alike)
     }
     // (the lanes of a row of 16 add in different orders: lane 0 speaks for all)
     dot = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(row16_sum(dot))));

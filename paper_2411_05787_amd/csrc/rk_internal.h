@@ -447,6 +447,20 @@ static inline int deferred_split_workgroups(const rk_geom* g, int64_t max_len) {
     return inside > 0 ? inside : emit_split_workgroups(g, max_len);
 }
 
+// A trigger's test step in one launch (test_step_kernel): over one sequence, where its partial step has the form of 4 wavefronts and its full
+// pass merges inside, and all workgroups of either are resident at once (two per compute unit).  With several sequences a workgroup of
+// one would have to wait for the decisions of the others.  us per layer of a test step (its share of the batched refresh included), two launches / one,
+// none full and all full: 65536 rows, K = 4096, 28 heads over 4: 9.9 / 7.6 and 42.9 / 38.8; 32768, 2048, 32 over 8: 9.7 / 7.2, 40.9 / 39.8; 8192, 700,
+// 32 over 8: 8.1 / 6.2, 18.8 / 17.1; 3000, 256, 28 over 4: 8.2 / 6.2, 14.2 / 12.1; 16384, 1000, 16 over 4: 7.9 / 5.8, 18.5 / 17.1.
+static inline TileForm test_step_form(const rk_geom* g, int64_t n_sel, int64_t max_recent, int64_t max_len) {
+    if (g->batch != 1) return {0, 0, 0, false};
+    const TileForm f = partial_tile_form(n_sel, max_recent, g->n_kv_heads, g->n_q_heads / g->n_kv_heads, true);
+    const int inside = inside_split_workgroups(g, max_len);
+    const int64_t most = f.nch + f.tail > inside ? f.nch + f.tail : inside;
+    if (f.waves != 4 || f.exact || inside == 0 || most * g->n_kv_heads > 2 * kComputeUnits) return {0, 0, 0, false};
+    return f;
+}
+
 // Form and split of the two passes of rk_window_select over K (see rk_window.hip): 16 T rows per wavefront and step,
 // wg_rows per workgroup and step, nch workgroups per (sequence, KV head), at most `limit`.
 // T = 4 takes 512 rows per workgroup and round and gains from every block of columns it holds the rows for, but a last round
@@ -554,6 +568,11 @@ __attribute__((visibility("hidden")))
 int pool_batched_stage(const rk_geom* geom, int n_layers, const Workspace* wss, const int32_t* seq_lens, int32_t max_len,
                        int64_t full_capacity, int pool_half, int agg, const int32_t* const* pred, int32_t pred_val,
                        hipStream_t st);
+//   test_step_stage: a layer's step on which the trigger is tested: rk_partial_attn_triggered, then rk_full_attn_deferred under the
+//     decision, in one launch where that has a form.
+__attribute__((visibility("hidden")))
+int test_step_stage(const rk_geom* geom, const void* q, const rk_layer_state& layer, const rk_schedule* sched, const int32_t* seq_lens, int32_t max_len,
+                    int32_t max_recent, void* out, void* workspace, size_t workspace_bytes, hipStream_t st);
 //   h2o_attn_stage: the attention of an H2O step, scores and partial results left in the workspace.
 __attribute__((visibility("hidden")))
 int h2o_attn_stage(const rk_geom* geom, const void* q, const rk_h2o_state& st, const void* k_new, const void* v_new,

@@ -16,295 +16,24 @@
 // start 0.3 us after the first); the launch to launch time is 1.2 us more than the slowest of it.  The latency is paid for in traffic: 64 rows
 // of 16 bytes per head and partial result instead of 44, and twice the partial results (K = 2048: 12.0 MB per launch against 9.8
 // with attn_split_kernel, 8.4 needed), which is one reason why more than two workgroups per unit are better off there.
-#include "rk_attn_common.h"
+#include "rk_tile.h"
 
 namespace rk {
 
-// What the kernel needs beyond its preloaded arguments, in the order in which it needs it.
-struct TileParams {
-    float scale2;                             // scale * log2 e: scores, maxima and lambda are kept in units of ln 2
-    int32_t n_sel, evict, max_rows2, cap1, cap2, slice_spin, pred_val;
-    uint32_t* epochs; uint16_t* out; int32_t* counters; uint32_t* tag_rows;
-    const uint16_t* k2; const uint16_t* v2; int64_t s2_b, s2_h;
-    const int32_t* pred; float* trig_q_ref; float* trig_sim; int32_t* trig_need; float trig_threshold;
-};
-// Preloaded argument `rows_heads`: rows of the small cache that exist whatever the lengths say | a predicate is given | KV heads << 16.
-constexpr int kSpecBits = 15, kPredBit = 1 << kSpecBits;
-static_assert(kMergeChunks * 128 < (1 << kSpecBits), "rows of the small cache");
-
-// Attention over the small cache and the rows decoded since the refresh, where no workgroup has more rows than it holds
-// at once: 16 per wavefront.
 template <int G, int NW, bool TRIG, bool EXACT>
 __global__ __launch_bounds__((NW + TRIG) * 64, 4)
 void partial_tile_kernel(const uint16_t* k1, const uint16_t* v1, int64_t s_b_and_tail, int32_t s_h, uint32_t rows_heads,
                          const int32_t* seq_lens, const int32_t* tail_start, const uint16_t* q, const TileParams p) {
-    constexpr int WG = 16 * NW;               // rows of a workgroup
-    constexpr int DT = 8 / NW, KS = NW / 2;   // P V: tiles of 16 dims of a wavefront, steps of 32 rows
-    constexpr int VS = kD + 8;                // LDS row stride of the V tile (272 bytes: rows spread over banks)
-    const int64_t s_b = s_b_and_tail & ((1ll << 56) - 1);
-    const int first_tail = (int)(s_b_and_tail >> 56) & 0xff;      // workgroups from here on have rows of the full cache, those before of the small one
-    const int spec_rows = rows_heads & ((1 << kSpecBits) - 1), n_kv = rows_heads >> 16;
-    const int c = blockIdx.x, g = blockIdx.y, b = blockIdx.z;
-    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int n16 = lane & 15, c4 = lane >> 4;
-    const int64_t bg = (int64_t)b * n_kv + g;
-    if (!TRIG && (rows_heads & kPredBit) != 0 && p.pred[b] != p.pred_val) return;
-    // ---- the scalars of the whole kernel are requested here, in one round trip (left to itself the compiler reads them
-    //      where they are used, a round trip each), and waited for behind the requests for the first rows ----
-    const int len_raw = seq_lens[b], tail_raw = tail_start[b];
-    const float scale2 = p.scale2;
-    const int spin = p.slice_spin, n_sel = p.n_sel, evict = p.evict, max_rows2 = p.max_rows2, cap1 = p.cap1,
-              cap2 = p.cap2;
-    uint16_t* const out_all = p.out;
-    int32_t* const counters = p.counters;
-    uint32_t* const tag_rows = p.tag_rows;
-    uint32_t* const epochs = p.epochs;
-    const uint16_t* const k2 = p.k2;
-    const uint16_t* const v2 = p.v2;
-    const int64_t s2_b = p.s2_b, s2_h = p.s2_h;
-    __builtin_amdgcn_sched_barrier(0);
-    // ---- K rows, queries and V rows of a workgroup of the small cache, requested before any length is known: the rows of a
-    //      cache are a buffer, whose rows past the end read as zero ----
-    u32x4 kA[4], vA[4], qa[4];
-    k1 += (uint64_t)s_b * (uint32_t)b + (uint64_t)(uint32_t)s_h * (uint32_t)g;
-    v1 += (uint64_t)s_b * (uint32_t)b + (uint64_t)(uint32_t)s_h * (uint32_t)g;
-    const int k_lane = n16 * (kD * 2) + c4 * 16, v_lane = c4 * (kD * 2) + n16 * 16;      // bytes, from the wavefront's first row
-    auto request_k = [&](const uint16_t* k, int rows, int row) {
-        const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(k), 0, rows * (kD * 2), 0x00020000);
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) kA[kk] = __builtin_amdgcn_raw_buffer_load_b128(rk, row * (kD * 2) + k_lane + kk * 64, 0, 0);
-    };
-    auto request_v = [&](const uint16_t* v, int rows, int row) {
-        const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(v), 0, rows * (kD * 2), 0x00020000);
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj) vA[jj] = __builtin_amdgcn_raw_buffer_load_b128(rv, row * (kD * 2) + v_lane + jj * 4 * (kD * 2), 0, 0);
-    };
-    int r_first = c * WG + w * 16;
-    const int early = c < first_tail ? spec_rows : 0;
-    request_k(k1, early, r_first);
-    {                                         // (heads beyond the group read as zero)
-        const __amdgpu_buffer_rsrc_t rq = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(q) + bg * G * kD, 0, G * kD * 2, 0x00020000);
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) qa[kk] = __builtin_amdgcn_raw_buffer_load_b128(rq, k_lane + kk * 64, 0, 0);
-    }
-    request_v(v1, early, r_first);
-    asm volatile("" :: "s"(scale2), "s"(spin), "s"(out_all), "s"(counters), "s"(tag_rows), "s"(epochs),
-                 "s"(k2), "s"(v2), "s"(s2_b), "s"(s2_h), "s"(p.pred_val));
-    const uint32_t epoch = *(const __attribute__((address_space(4))) uint32_t*)(epochs + bg);      // (the kernel's own store comes after: a scalar load)
-    __builtin_amdgcn_sched_barrier(0);
-
-    __shared__ __attribute__((aligned(16))) uint16_t sV[WG][VS];
-    __shared__ __attribute__((aligned(16))) uint2 sP[2][KS][64][2];      // hi and lo, step, lane, half of the step
-    __shared__ __attribute__((aligned(16))) float sM[16][NW], sL[16][NW];
-    __shared__ int sTicket, sNeed;
-    __shared__ unsigned long long sPend;
-
-    // TRIG: a wavefront of its own works the test out beside the others, which learn the decision with the maxima.  Where the
-    // sequence needs a full step every workgroup has read the old reference by the time it takes its ticket (the second
-    // word of the sequence's first counter line: zero between launches); the last one stores the new one.
-    if constexpr (TRIG) {
-        if (w == NW) {
-            SimLoads ld;
-            float qbar[8];
-            similarity_request(q, p.trig_q_ref, b, n_kv * G, ld);
-            const float s = similarity_finish(q, b, n_kv * G, ld, qbar);
-            const bool need = !(s > p.trig_threshold);
-            if (lane == 0) {
-                sNeed = need ? 1 : 0;
-                if (c == 0 && g == 0) { p.trig_sim[b] = s; p.trig_need[b] = need ? 1 : 0; }
-            }
-            lds_barrier();
-            if (!need) return;
-            int last = 0;
-            if (lane == 0) {
-                int32_t* ticket = counters + (int64_t)b * n_kv * kCounterStride + 1;
-                const int seen = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                last = seen == (int)(gridDim.x * gridDim.y) - 1 ? 1 : 0;
-                if (last) __hip_atomic_store(ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-            last = __builtin_amdgcn_readfirstlane(last);
-            if (last && lane < 16) {
-                float4* rp = reinterpret_cast<float4*>(p.trig_q_ref + (int64_t)b * kD + lane * 8);
-                rp[0] = make_float4(qbar[0], qbar[1], qbar[2], qbar[3]);
-                rp[1] = make_float4(qbar[4], qbar[5], qbar[6], qbar[7]);
-            }
-            return;
-        }
-    }
-
-    // ---- the row list of this (sequence, KV head) (lengths clamped to the allocated rows: no access leaves the caches) ----
-    const int len = min(len_raw, cap2), t0 = min(max(tail_raw, 0), cap2), recent = max(len - t0, 0);
-    // fixed-size small cache: every row decoded since the refresh pushed out the selected row with the lowest score (the last)
-    int keep = max(n_sel - (evict != 0 ? recent : 0), 0);
-    keep = min(keep, cap1);
-    asm("" : "+s"(keep));                     // (scalar minima, one after the other)
-    const int n1 = min(keep, t0), n2 = min(recent, max_rows2);
-    // partial results in all (an empty sequence leaves one of no rows), this workgroup's place among them, the end of its rows
-    const int n_main = first_tail != 0 ? max((int)((uint32_t)(n1 + WG - 1) / WG), n2 == 0 ? 1 : 0) : 0;
-    const int n_tail = max((int)((uint32_t)(n2 + WG - 1) / WG), first_tail != 0 ? 0 : 1);
-    const int nchunks = n_main + n_tail;
-    const bool tail = c >= first_tail;
-    const int c_rec = tail ? c - first_tail + n_main : c, row1 = tail ? n1 + n2 : n1;
-    if (c_rec >= (tail ? nchunks : n_main)) {
-        if constexpr (TRIG) lds_barrier();      // (the wavefront with the test waits for everybody)
-        return;
-    }
-    if (tail) {
-        // row r of the list lives at row t0 + r - n1 of the full cache
-        r_first += n1 - first_tail * WG;
-        const uint64_t at = (uint64_t)s2_b * (uint32_t)b + (uint64_t)s2_h * (uint32_t)g + (uint64_t)(uint32_t)t0 * kD;
-        request_k(k2 + at, n2, r_first - n1);
-        request_v(v2 + at, n2, r_first - n1);
-    }
-    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(tag_rows + bg * kTagRegionRows * G * 4, 0,
-                                                                          kTagRegionRows * G * 16, 0x00020000);
-    const uint32_t tag = max(epoch + 1u, 1u);                          // this call's number: never 0
-    // this wavefront's first unit of the merge, worked out while the rows are on their way
-    const int shift = pair_unit_shift<G>(nchunks), units = (kPairRows * G) >> shift, unit0 = c_rec + (NW - 1 - w) * nchunks;
-    PairLane<G, EXACT> at0(unit0, shift, nchunks);
-    asm volatile("" : "+v"(at0.q), "+v"(at0.row), "+v"(at0.first), "+v"(at0.last) : "s"(tag));
-    if constexpr (EXACT) asm volatile("" : "+v"(at0.sum));
-
-    // ---- S^T = K Q^T: head n16, rows 4 c4 + i of the wavefront's 16 ----
-    float s[4];
-    const bool whole = r_first + 16 <= row1;
-    {
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk)
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kA[kk]), __builtin_bit_cast(bf16x8, qa[kk]), acc, 0, 0, 0);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) s[i] = acc[i] * scale2;
-        if (!whole) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) s[i] = r_first + 4 * c4 + i < row1 ? s[i] : -INFINITY;
-        }
-    }
-    const float mx = max_xor32(max_xor16(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]))));
-    if (c4 == 0) sM[n16][w] = mx;
-    lds_barrier();
-    if constexpr (TRIG) {
-        if (sNeed != 0) return;
-    }
-    // ---- P against the workgroup's maximum, as two bf16 operands hi + lo (to about 2^-17) ----
-    float M = sM[n16][0];
-#pragma unroll
-    for (int ww = 1; ww < NW; ++ww) M = fmaxf(M, sM[n16][ww]);
-    const float ref = M == -INFINITY ? 0.f : M;
-    float pr[4], ps = 0.f;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) { pr[i] = fast_exp2(s[i] - ref); ps += pr[i]; }
-    const uint2 hi = make_uint2(pack_bf16(pr[0], pr[1]), pack_bf16(pr[2], pr[3]));
-    const uint2 lo = make_uint2(pack_bf16(pr[0] - bf16_lo(hi.x), pr[1] - bf16_hi(hi.x)),
-                                pack_bf16(pr[2] - bf16_lo(hi.y), pr[3] - bf16_hi(hi.y)));
-    sP[0][w >> 1][lane][w & 1] = hi;
-    sP[1][w >> 1][lane][w & 1] = lo;
-    ps = sum_xor32(sum_xor16(ps));
-    if (c4 == 0) sL[n16][w] = ps;
-    if (!whole) {       // V rows past the end hold whatever the cache holds there, maybe NaN: P is 0 for them, but 0 * NaN is NaN
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj)
-            if (r_first + jj * 4 + c4 >= row1) vA[jj] = u32x4{0u, 0u, 0u, 0u};
-    }
-#pragma unroll
-    for (int jj = 0; jj < 4; ++jj) *reinterpret_cast<u32x4*>(&sV[w * 16 + jj * 4 + c4][n16 * 8]) = vA[jj];
-    lds_barrier();
-    // ---- O^T = V^T P^T of all the workgroup's rows: this wavefront's dims, head n16, four consecutive dims per lane ----
-    float L = sL[n16][0];
-#pragma unroll
-    for (int ww = 1; ww < NW; ++ww) L += sL[n16][ww];
-    f32x4 o[DT][2];
-#pragma unroll
-    for (int t = 0; t < DT; ++t) { o[t][0] = f32x4{0.f, 0.f, 0.f, 0.f}; o[t][1] = f32x4{0.f, 0.f, 0.f, 0.f}; }
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-        const bf16x8 p_hi = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(&sP[0][ks][lane][0]));
-        const bf16x8 p_lo = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(&sP[1][ks][lane][0]));
-#pragma unroll
-        for (int t = 0; t < DT; ++t) {
-            const uint16_t* vsrc = &sV[32 * ks + 4 * c4 + (n16 >> 2)][(w * DT + t) * 16 + 4 * (n16 & 3)];
-            const v4s v0 = lds_read_tr16(vsrc), v1 = lds_read_tr16(vsrc + 16 * VS);
-            const bf16x8 vb = __builtin_bit_cast(bf16x8, __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
-            o[t][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vb, p_hi, o[t][0], 0, 0, 0);
-            o[t][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vb, p_lo, o[t][1], 0, 0, 0);
-        }
-    }
-    float inv = 1.f, lam = M;                 // EXACT: the sums as they are, weighed by their maximum (-inf: no rows)
-    if constexpr (!EXACT) {
-        inv = L > 0.f ? __builtin_amdgcn_rcpf(L) : 0.f; lam = L > 0.f ? M + __builtin_amdgcn_logf(L) : -INFINITY;
-        asm volatile("" : "+v"(inv), "+v"(lam));  // (beside the matrix instructions)
-    }
-    // ---- publish ----
-    if (n16 < G) {
-#pragma unroll
-        for (int t = 0; t < DT; ++t) {
-            const f32x4 x = EXACT ? o[t][0] + o[t][1] : (o[t][0] + o[t][1]) * inv;
-            const int off = ((c_rec * G + n16) * kPairRows + (w * DT + t) * 8 + 2 * c4) * 16;
-            const u32x4 r0 = {__float_as_uint(x[0]), __float_as_uint(x[1]), __float_as_uint(lam), tag};
-            const u32x4 r1 = {__float_as_uint(x[2]), __float_as_uint(x[3]), __float_as_uint(lam), tag};
-            __builtin_amdgcn_raw_buffer_store_b128(r0, rsrc, off, 0, kAgentScopeAux);
-            __builtin_amdgcn_raw_buffer_store_b128(r1, rsrc, off + 16, 0, kAgentScopeAux);
-        }
-        if (EXACT && w == 0 && c4 == 0) {
-            const u32x4 r = {__float_as_uint(L), 0u, __float_as_uint(lam), tag};
-            __builtin_amdgcn_raw_buffer_store_b128(r, rsrc, PairLane<G, EXACT>::sum_row(n16, c_rec), 0, kAgentScopeAux);
-        }
-    }
-    // ---- merge (see attn_split_kernel: the same protocol, a bit per unit) ----
-    int32_t* counter = counters + bg * kCounterStride;
-    unsigned long long* pend = reinterpret_cast<unsigned long long*>(counter + 2);
-    uint16_t* out = out_all + bg * G * kD;
-    asm volatile("s_barrier" ::: "memory");                                // every wavefront has issued its rows
-    if (w == 0) {
-        int ticket = 0;
-        if (lane == 0) ticket = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        ticket = __builtin_amdgcn_readfirstlane(ticket);
-        if (ticket == nchunks - 1 && lane == 0) {
-            __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);           // next call
-            __hip_atomic_store(&epochs[bg], tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            wait_stores_acknowledged();                                                           // the call number is out before the bits are collected
-            sPend = __hip_atomic_exchange(pend, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        if (lane == 0) sTicket = ticket;
-    }
-    for (int unit = unit0; unit < units; unit += NW * nchunks) {
-        if (unit != unit0) at0 = PairLane<G, EXACT>(unit, shift, nchunks);
-        if (merge_pairs<G, EXACT>(out, rsrc, at0, nchunks, tag, spin, false)) continue;
-        const unsigned long long bit = 1ull << unit;
-        uint32_t seen = 0;
-        if (lane == 0) {
-            const unsigned long long before = __hip_atomic_fetch_or(pend, bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            asm volatile("s_waitcnt vmcnt(0)" :: "v"(before) : "memory");       // the bit is set before the call number is read
-            seen = __hip_atomic_load(&epochs[bg], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        seen = __builtin_amdgcn_readfirstlane(seen);
-        if (seen == tag) {
-            merge_pairs<G, EXACT>(out, rsrc, at0, nchunks, tag, kTagSpinLimit, true);
-            if (lane == 0) __hip_atomic_fetch_and(pend, ~bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-    }
-    __syncthreads();
-    if (sTicket != nchunks - 1) return;
-    unsigned long long left = sPend;
-    for (int k = 0; left != 0; ++k) {
-        const int unit = __builtin_ctzll(left);
-        left &= left - 1;
-        if ((k & (NW - 1)) == w && unit < units) merge_pairs<G, EXACT>(out, rsrc, PairLane<G, EXACT>(unit, shift, nchunks), nchunks, tag, kTagSpinLimit, true);
-    }
+    partial_tile<G, NW, TRIG ? kTestBeside : kNoTest, EXACT>(k1, v1, s_b_and_tail, s_h, rows_heads, seq_lens, tail_start, q, p, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
 template <int G, int NW, bool EXACT>
 static int launch_g(const AttnParams& p, int batch, bool trig, hipStream_t st) {
-    TileParams t{(float)((double)p.scale * 1.4426950408889634), p.n_sel, p.evict, p.max_rows2, p.cap1, p.cap2, p.slice_spin, p.pred_val,
-                 p.epochs, p.out, p.counters, p.tag_rows, p.k2, p.v2, p.s2_b, p.s2_h,
-                 p.pred, p.trig_q_ref, p.trig_sim, p.trig_need, p.trig_threshold};
+    const TileArgs a = tile_args(p);
     dim3 grid(p.nch + p.tail_wg, p.Hkv, batch);
-    const uint32_t spec_rows = (uint32_t)(p.n_sel < p.cap1 ? p.n_sel : p.cap1);
-    const uint32_t rows_heads = spec_rows | (p.pred != nullptr ? kPredBit : 0) | ((uint32_t)p.Hkv << 16);
-    const int64_t s_b_and_tail = p.s1_b | ((int64_t)p.nch << 56);
     auto kernel = trig ? partial_tile_kernel<G, NW, true, EXACT> : partial_tile_kernel<G, NW, false, EXACT>;
-    hipLaunchKernelGGL(kernel, grid, dim3((NW + (trig ? 1 : 0)) * 64), 0, st, p.k1, p.v1, s_b_and_tail, (int32_t)p.s1_h, rows_heads,
-                       p.seq_lens, p.tail_start, p.q, t);
+    hipLaunchKernelGGL(kernel, grid, dim3((NW + (trig ? 1 : 0)) * 64), 0, st, p.k1, p.v1, a.s_b_and_tail, (int32_t)p.s1_h, a.rows_heads,
+                       p.seq_lens, p.tail_start, p.q, a.t);
     return launch_status();
 }
 

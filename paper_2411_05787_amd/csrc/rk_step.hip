@@ -210,17 +210,16 @@ extern "C" int rk_decode_step_batched(const rk_geom* geom, const rk_schedule* sc
     const int recent = max_recent > 0 ? max_recent : 1;
     for (int l = 0; l < n_layers; ++l) {
         const rk_layer_state& L = layers[l];
-        if (both) {       // the test rides on the partial step; the full step follows under the predicate it leaves
-            rc = rk_partial_attn_triggered(geom, q[l], L.small, sched->k, sched->fixed_size, L.full, L.tail_start,
-                                           seq_lens, recent, out[l], L.q_ref, sched->threshold, L.sim, L.need_full,
-                                           workspaces[l], workspace_bytes, stream);
+        if (both) {       // the test rides on the partial step; the full step follows where it asks for one
+            rc = rk::test_step_stage(geom, q[l], L, sched, seq_lens, max_len, recent, out[l], workspaces[l], workspace_bytes, (hipStream_t)stream);
             if (rc != RK_OK) return rc;
-        } else if (sched->dynamic) {      // the trigger's reference follows every full step
+            continue;
+        }
+        if (sched->dynamic) {             // the trigger's reference follows every full step
             rc = rk_query_sim(geom, q[l], L.q_ref, sched->threshold, 1, L.sim, L.need_full, stream);
             if (rc != RK_OK) return rc;
         }
-        rc = rk_full_attn_deferred(geom, q[l], L.full, seq_lens, max_len, out[l], nullptr,
-                                   both ? L.need_full : nullptr, 1, workspaces[l], workspace_bytes, stream);
+        rc = rk_full_attn_deferred(geom, q[l], L.full, seq_lens, max_len, out[l], nullptr, nullptr, 0, workspaces[l], workspace_bytes, stream);
         if (rc != RK_OK) return rc;
     }
     rc = rk_refresh_batched(geom, n_layers, layers, workspaces, workspace_bytes, seq_lens, max_len, sched->k,

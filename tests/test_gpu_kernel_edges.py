@@ -626,6 +626,60 @@ def test_triggered_step_in_each_form(rk, name):
         assert (d <= torch.maximum(outs[0][b].double().abs(), want.abs()) * 2.0 ** -7 + 4e-6).all(), (b, float(d.max()))
 
 
+# Test steps in one launch (both branches; test_launch_sizes asserts which take it).  (heads per group, KV heads, rows, K, rows since, fixed
+# size).  Full passes of 512 and of 256 workgroups, few partial results, rows fewer than K, more workgroups for the partial step than for the full pass.
+TEST_STEPS = [(4, 8, 33000, 2048, 5, False), (4, 8, 45001, 2048, 5, True), (7, 4, 66000, 4096, 3, False), (7, 4, 9001, 700, 60, True),
+              (8, 4, 2049, 128, 1, False), (1, 8, 3000, 256, 7, True), (2, 8, 700, 64, 16, False), (3, 4, 130, 64, 2, False),
+              (5, 8, 4000, 500, 9, False), (6, 3, 1000, 1000, 4, False), (4, 4, 50, 64, 3, False), (7, 8, 8192, 2047, 130, False)]
+
+
+@pytest.mark.parametrize("case", TEST_STEPS, ids=["g%d_%dx%d_k%d_r%d" % c[:5] for c in TEST_STEPS])
+def test_test_step_in_one_launch(rk, case):
+    """The bits of the partial step with its test and then the full pass under the decision, as calls of their own: layers that
+    fire and layers that do not, whoever merges, call after call."""
+    G, Hkv, n, k, recent, fixed = case
+    say("test step", case)
+    layers, Hq, cap = 3, G * Hkv, n + 8
+    g = torch.Generator(device="cuda").manual_seed(n + k)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    kv = [(rnd(1, Hkv, cap, 128).to(torch.bfloat16), rnd(1, Hkv, cap, 128).to(torch.bfloat16)) for _ in range(layers)]
+    geom = rk.Geom(1, Hq, Hkv, 128, SCALE)
+    q0 = rnd(layers, 1, Hq, 128).to(torch.bfloat16)
+    models = []
+    for _ in range(2):
+        lens = torch.tensor([n - recent], dtype=torch.int32, device="cuda")
+        m = rk.RefreshKVModel(geom, kv, lens, n - recent, k, 4, dynamic=True, threshold=0.9, evict_lowest=fixed)
+        m.batched_refresh()
+        m.step(0, q0)
+        lens += recent
+        for _ in range(recent):
+            m.advance()
+        models.append(m)
+    one, two = models
+    try:
+        for t, spin, fires in ((4, 256, [0, 1, 0]), (8, 0, [1, 0, 1]), (12, 1, [0, 0, 0]), (16, 2, [1, 1, 1]), (20, 256, [0, 1, 1])):
+            rk.rk_debug_set_slice_spin(spin)
+            q = torch.stack([rnd(1, Hq, 128).to(torch.bfloat16) if f else
+                             (m_ref[None, None] + 0.01 * rnd(1, Hq, 128)).to(torch.bfloat16) for f, m_ref in zip(fires, one.q_ref[:, 0])])
+            for m in models:
+                m.out.fill_(7.0)
+            assert one.step(t, q) == "both"
+            for l in range(layers):
+                K, V = kv[l]
+                rk.rk_partial_attn_triggered(geom, q[l], two.small_K[l], two.small_V[l], k, K, V, two.tail_start[l], two.seq_lens, max(recent, 1),
+                                             two.out[l], two.q_ref[l], 0.9, two.sim[l], two.need_full[l], fixed_size=fixed, workspace=two._wss[l])
+                rk.rk_full_attn_deferred(geom, q[l], K, V, two.seq_lens, n, two.out[l], pred=two.need_full[l], pred_val=1, workspace=two._wss[l])
+            rk.rk_refresh_batched(geom, two._layers, two._batched_ptrs, two._batched_bytes, two.seq_lens, n, k, pool_w=7, by_need_full=True)
+            torch.cuda.synchronize()
+            assert one.need_full[:, 0].tolist() == fires
+            for name in ("need_full", "sim", "q_ref", "tail_start", "n_full"):
+                assert torch.equal(getattr(one, name), getattr(two, name)), name
+            assert torch.equal(one.idx, two.idx) and torch.equal(one.small_K, two.small_K) and torch.equal(one.small_V, two.small_V)
+            assert torch.equal(one.out, two.out)
+    finally:
+        rk.rk_debug_set_slice_spin(256)
+
+
 def _select_scores(name, rows, n, g):
     w = torch.exp(torch.randn(*rows, n, generator=g) * 1.2 - 10)
     if name == "levels":                   # few values: stretches do not fit, the row is one workgroup's

@@ -84,6 +84,12 @@ int main() {
             printf("inside %ld %d %d %d %d %d %d %d\n", l, b, hkv, G, inside_split_workgroups(&g, l), emit_split_workgroups(&g, l),
                    deferred_split_workgroups(&g, l), (int)merges_in_fp32(&g, l));
         }
+    for (long l : {1L, 50L, 700L, 3000L, 8192L, 33000L, 66000L, 131072L}) for (long k : {64L, 700L, 2048L, 4096L, 8192L}) for (int recent : {1, 64, 65, 500}) for (int b : {1, 2})
+        for (int hkv : {1, 3, 4, 8, 16, 32}) for (int G : {1, 4, 7, 8}) {
+            rk_geom g{b, hkv * G, hkv, 128, 1.0f};
+            const TileForm f = test_step_form(&g, k, recent, l);
+            printf("test_step %ld %ld %d %d %d %d %d %d %d %d\n", l, k, recent, b, hkv, G, f.waves, f.nch, f.tail, inside_split_workgroups(&g, l));
+        }
     for (long l : {1L, 63L, 512L, 513L, 1100L, 1400L, 2100L, 16000L, 32768L, 36000L, 40000L, 64000L, 76000L, 131072L}) for (long p : {1L, 4L, 8L, 128L, 260L, 520L, 4096L})
         for (int blocks : {1, 2, 3, 8, 16}) {
             const int limit = max_chunks_for(l);
@@ -167,6 +173,22 @@ def test_headline_shapes(table):
     assert emit[(131072, 1, 8)] * 8 == 1024             # cfg5
     for (length, b, hkv), n in emit.items():
         assert 1 <= n <= 1024 and n <= max((length + 127) // 128, 1)
+
+
+def test_test_step_in_one_launch_is_resident_as_a_whole(table):
+    """Both branches in one launch: one sequence, and the workgroups of either branch are all resident at once."""
+    got = {}
+    for kind, *v in table:
+        if kind != "test_step":
+            continue
+        n, k, recent, batch, hkv, G, waves, nch, tail, inside = map(int, v)
+        got[(n, k, recent, batch, hkv, G)] = waves
+        if waves:
+            assert waves == 4 and batch == 1 and inside >= 1
+            assert max(nch + tail, inside) * hkv <= 512 and nch * 64 >= k and tail * 64 >= recent and nch + tail <= 65
+    assert got[(66000, 4096, 1, 1, 4, 7)] == 4 and got[(33000, 2048, 64, 1, 8, 4)] == 4
+    assert got[(66000, 4096, 65, 1, 4, 7)] == 0          # a 66th partial result
+    assert got[(33000, 8192, 1, 1, 8, 4)] == 0 and got[(33000, 2048, 1, 2, 8, 4)] == 0
 
 
 def test_sliced_split_bounds_and_measured_choices(table):
