@@ -332,6 +332,15 @@ int rk_partial_attn_lazy(const rk_geom* geom, const void* q, rk_kv small, const 
                          const int32_t* pred, int32_t pred_val,
                          void* workspace, size_t workspace_bytes, void* stream);
 
+/* What a refresh from the scores alone ends with (Section 4.3, "w/o full attention"): rk_gather_small_kv of the selection
+ * idx (int32 [batch, n_kv_heads, k]; tail_start <- seq_lens, both required), then rk_partial_attn over the k rows and nothing else (no row
+ * has been decoded since).  One launch where the rows fit the chip at once, with the rows written to `small` on the way to
+ * the output; two otherwise.  Arguments and errors as of those two calls. */
+int rk_gather_attn(const rk_geom* geom, const void* q, rk_kv full, const int32_t* idx, int32_t k, rk_kv small,
+                   const int32_t* seq_lens, int32_t* tail_start, void* out,
+                   const int32_t* pred, int32_t pred_val,
+                   void* workspace, size_t workspace_bytes, void* stream);
+
 /* Query-similarity trigger.
  *   qbar[b,:] = mean over the query heads of q[b,h,:]                        (fp32)
  *   sim[b]    = <qbar, q_ref[b]> / (max(|qbar|, 1e-8) * max(|q_ref[b]|, 1e-8))

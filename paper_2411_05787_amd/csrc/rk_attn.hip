@@ -2183,7 +2183,7 @@ static int launch_partial(const rk_geom* geom, const void* q, rk_kv small, int32
     if (tile.waves != 0 && ws.tag_rows != nullptr && lazy_idx == nullptr) {
         p.nch = tile.nch; p.tail_wg = tile.tail;
         set_slice_merge(p, true, 0);
-        return launch_partial_tile(p, geom->batch, G, tile, trig != nullptr, (hipStream_t)stream);
+        return launch_partial_tile(p, geom->batch, G, tile, trig != nullptr, nullptr, (hipStream_t)stream);
     }
     // Which hand-over.  Tagged partial results merged by slices (every workgroup its share, see the kernel) wherever
     // that merge applies: a launch whose workgroups are all resident at once, with no more partial results per
@@ -2304,6 +2304,38 @@ extern "C" int rk_partial_attn_triggered(const rk_geom* geom, const void* q, rk_
     const Trigger trig{q_ref, threshold, sim, need_full};
     return partial_attn_impl(geom, q, small, n_sel, fixed_size != 0, full, tail_start, seq_lens, max_recent, out,
                              nullptr, 0, workspace, workspace_bytes, stream, nullptr, &trig);
+}
+
+// ---- the gather and the partial step after it ----
+namespace rk {
+int gather_attn_stage(const rk_geom* geom, const void* q, rk_kv full, const int32_t* idx, int32_t k, rk_kv small, const int32_t* seq_lens,
+                      int32_t* tail_start, int32_t* n_refresh, void* out, const int32_t* pred, int32_t pred_val, void* workspace,
+                      size_t workspace_bytes, hipStream_t st) {
+    int rc = check_partial_args(geom, q, small, k, full, tail_start, seq_lens, 1, out);
+    if (rc != RK_OK) return rc;
+    if (!idx || k <= 0 || small.capacity < k) return RK_ERR_INVALID_ARG;
+    Workspace ws;
+    if ((rc = check_partial_workspace(geom, workspace, workspace_bytes, &ws)) != RK_OK) return rc;
+    const int G = geom->n_q_heads / geom->n_kv_heads;
+    const TileForm tile = partial_tile_form(k, 0, (int64_t)geom->batch * geom->n_kv_heads, G, false);
+    if (tile.waves == 0) {       // two launches
+        rc = gather_stage(geom, full, idx, k, small, seq_lens, tail_start, n_refresh, pred, pred_val, st);
+        if (rc != RK_OK) return rc;
+        return launch_partial(geom, q, small, k, false, full, tail_start, seq_lens, 1, out, pred, pred_val, ws, st);
+    }
+    AttnParams p = partial_params(geom, q, small, k, false, full, tail_start, seq_lens, 0, out, pred, pred_val, ws, nullptr);
+    p.mark_tail = tail_start; p.mark_count = n_refresh;
+    p.nch = tile.nch; p.tail_wg = 0;
+    set_slice_merge(p, true, 0);
+    return launch_partial_tile(p, geom->batch, G, tile, false, idx, st);
+}
+}  // namespace rk
+
+extern "C" int rk_gather_attn(const rk_geom* geom, const void* q, rk_kv full, const int32_t* idx, int32_t k, rk_kv small,
+                              const int32_t* seq_lens, int32_t* tail_start, void* out, const int32_t* pred, int32_t pred_val,
+                              void* workspace, size_t workspace_bytes, void* stream) {
+    return gather_attn_stage(geom, q, full, idx, k, small, seq_lens, tail_start, nullptr, out, pred, pred_val, workspace, workspace_bytes,
+                             (hipStream_t)stream);
 }
 
 // ---- a layer's step on which the trigger is tested, both branches ----

@@ -31,6 +31,7 @@ struct AttnParams {
     uint32_t* epochs; uint32_t* tag_rows;     // TAGGED only: call number per (sequence, KV head), tagged partial results
     const int32_t* idx; int32_t idx_stride;   // LAZY only: the selection [B, Hkv, idx_stride] whose rows are not gathered yet
     float* trig_q_ref; float* trig_sim; int32_t* trig_need; float trig_threshold;   // TRIG only: the query-similarity test
+    int32_t* mark_tail; int32_t* mark_count;  // the gather inside the step only: tail_start <- seq_lens, refreshes counted (may be NULL)
     int32_t ragged_batch;              // != 0 (= batch): workgroups are shared out by length, see ragged_share_lane
     int32_t share_cap;                 // ... at most this many to a sequence
     int32_t* n_attend;                 // APPEND only: [B], rows attended over, for the kernel that follows
@@ -39,8 +40,9 @@ struct AttnParams {
 };
 
 // The partial step in one tile per workgroup (rk_partial.hip): `waves` wavefronts of 16 rows.
+// idx given: the gather inside the step.
 __attribute__((visibility("hidden")))
-int launch_partial_tile(const AttnParams& p, int batch, int G, const TileForm& form, bool trig, hipStream_t st);
+int launch_partial_tile(const AttnParams& p, int batch, int G, const TileForm& form, bool trig, const int32_t* idx, hipStream_t st);
 
 constexpr int kSplitWaves = 4, kTileRows = 32;
 constexpr int kNoTailWg = 0xff;                   // top byte of the kernel argument s_b_and_tail: no workgroup for the tail rows

@@ -568,6 +568,11 @@ __attribute__((visibility("hidden")))
 int pool_batched_stage(const rk_geom* geom, int n_layers, const Workspace* wss, const int32_t* seq_lens, int32_t max_len,
                        int64_t full_capacity, int pool_half, int agg, const int32_t* const* pred, int32_t pred_val,
                        hipStream_t st);
+//   gather_attn_stage: rk_gather_attn plus an optional per-sequence count of refreshes.
+__attribute__((visibility("hidden")))
+int gather_attn_stage(const rk_geom* geom, const void* q, rk_kv full, const int32_t* idx, int32_t k, rk_kv small, const int32_t* seq_lens,
+                      int32_t* tail_start, int32_t* n_refresh, void* out, const int32_t* pred, int32_t pred_val, void* workspace,
+                      size_t workspace_bytes, hipStream_t st);
 //   test_step_stage: a layer's step on which the trigger is tested: rk_partial_attn_triggered, then rk_full_attn_deferred under the
 //     decision, in one launch where that has a form.
 __attribute__((visibility("hidden")))

@@ -27,10 +27,26 @@ void partial_tile_kernel(const uint16_t* k1, const uint16_t* v1, int64_t s_b_and
     partial_tile<G, NW, TRIG ? kTestBeside : kNoTest, EXACT>(k1, v1, s_b_and_tail, s_h, rows_heads, seq_lens, tail_start, q, p, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
+// The step right after a selection, with the gather in it: bound by memory, every row read and written once, where a gather writes what a second
+// launch then reads.  Whole rows of K through LDS: K = 8192, 32 heads over 8: 18.0 us with K loaded straight into the operand layout, 17.0.  us,
+// gather + step / this one, 32 heads over 8 unless noted: K = 256: 7.9 / 5.9, 2048: 10.5 / 7.0, 4096: 14.9 / 9.8, 6000: 17.9 / 13.4, 8192:
+// 24.1 / 17.0; 28 over 4, 4096: 11.1 / 7.4; 4 sequences of 1024: 14.9 / 9.7, of 2048: 24.2 / 16.0; 64 over 8, 4 of 700: 13.0 / 8.5.
 template <int G, int NW, bool EXACT>
-static int launch_g(const AttnParams& p, int batch, bool trig, hipStream_t st) {
+__global__ __launch_bounds__(NW * 64, 4)
+void gather_tile_kernel(uint16_t* k1, uint16_t* v1, int64_t s_b_and_tail, int32_t s_h, uint32_t rows_heads,
+                        const int32_t* seq_lens, const int32_t* idx, const uint16_t* q, const TileParams p) {
+    partial_tile<G, NW, kNoTest, EXACT, true>(k1, v1, s_b_and_tail, s_h, rows_heads, seq_lens, idx, q, p, blockIdx.x, blockIdx.y, blockIdx.z);
+}
+
+template <int G, int NW, bool EXACT>
+static int launch_g(const AttnParams& p, int batch, bool trig, const int32_t* idx, hipStream_t st) {
     const TileArgs a = tile_args(p);
     dim3 grid(p.nch + p.tail_wg, p.Hkv, batch);
+    if (idx != nullptr) {
+        hipLaunchKernelGGL((gather_tile_kernel<G, NW, EXACT>), grid, dim3(NW * 64), 0, st, const_cast<uint16_t*>(p.k1), const_cast<uint16_t*>(p.v1),
+                           a.s_b_and_tail, (int32_t)p.s1_h, a.rows_heads, p.seq_lens, idx, p.q, a.t);
+        return launch_status();
+    }
     auto kernel = trig ? partial_tile_kernel<G, NW, true, EXACT> : partial_tile_kernel<G, NW, false, EXACT>;
     hipLaunchKernelGGL(kernel, grid, dim3((NW + (trig ? 1 : 0)) * 64), 0, st, p.k1, p.v1, a.s_b_and_tail, (int32_t)p.s1_h, a.rows_heads,
                        p.seq_lens, p.tail_start, p.q, a.t);
@@ -38,15 +54,15 @@ static int launch_g(const AttnParams& p, int batch, bool trig, hipStream_t st) {
 }
 
 template <int G>
-static int launch_form(const AttnParams& p, int batch, const TileForm& form, bool trig, hipStream_t st) {
+static int launch_form(const AttnParams& p, int batch, const TileForm& form, bool trig, const int32_t* idx, hipStream_t st) {
     if constexpr (G > 4)
-        if (form.exact) return form.waves == 4 ? launch_g<G, 4, true>(p, batch, trig, st) : launch_g<G, 8, true>(p, batch, trig, st);
-    return form.waves == 4 ? launch_g<G, 4, false>(p, batch, trig, st) : launch_g<G, 8, false>(p, batch, trig, st);
+        if (form.exact) return form.waves == 4 ? launch_g<G, 4, true>(p, batch, trig, idx, st) : launch_g<G, 8, true>(p, batch, trig, idx, st);
+    return form.waves == 4 ? launch_g<G, 4, false>(p, batch, trig, idx, st) : launch_g<G, 8, false>(p, batch, trig, idx, st);
 }
 
-int launch_partial_tile(const AttnParams& p, int batch, int G, const TileForm& form, bool trig, hipStream_t st) {
+int launch_partial_tile(const AttnParams& p, int batch, int G, const TileForm& form, bool trig, const int32_t* idx, hipStream_t st) {
     switch (G) {
-#define RK_CASE(g) case g: return launch_form<g>(p, batch, form, trig, st);
+#define RK_CASE(g) case g: return launch_form<g>(p, batch, form, trig, idx, st);
         RK_CASE(1) RK_CASE(2) RK_CASE(3) RK_CASE(4) RK_CASE(5) RK_CASE(6) RK_CASE(7) RK_CASE(8)
 #undef RK_CASE
         default: return RK_ERR_UNSUPPORTED;

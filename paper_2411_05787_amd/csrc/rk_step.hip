@@ -44,12 +44,11 @@ extern "C" int rk_decode_step(const rk_geom* geom, const rk_schedule* sched, int
                                     sched->pool_w, RK_AGG_MAX, L.idx, nullptr, pred, 1, workspace, workspace_bytes,
                                     stream);
         if (r != RK_OK) return r;
-        r = gather_stage(geom, L.full, L.idx, sched->k, L.small, seq_lens, L.tail_start, L.n_full, pred, 1,
-                         (hipStream_t)stream);
-        if (r != RK_OK || !sched->scores_only) return r;
         // scores-only refresh: the output comes from the rebuilt small cache (nothing decoded since)
-        return rk_partial_attn(geom, q[l], L.small, sched->k, L.full, L.tail_start, seq_lens, 1, out[l], pred, 1,
-                               workspace, workspace_bytes, stream);
+        if (sched->scores_only)
+            return gather_attn_stage(geom, q[l], L.full, L.idx, sched->k, L.small, seq_lens, L.tail_start, L.n_full, out[l], pred, 1,
+                                     workspace, workspace_bytes, (hipStream_t)stream);
+        return gather_stage(geom, L.full, L.idx, sched->k, L.small, seq_lens, L.tail_start, L.n_full, pred, 1, (hipStream_t)stream);
     };
 
     for (int l = 0; l < n_layers; ++l) {

@@ -13,6 +13,7 @@ struct TileParams {
     uint32_t* epochs; uint16_t* out; int32_t* counters; uint32_t* tag_rows;
     const uint16_t* k2; const uint16_t* v2; int64_t s2_b, s2_h;
     const int32_t* pred; float* trig_q_ref; float* trig_sim; int32_t* trig_need; float trig_threshold;
+    int32_t* mark_tail; int32_t* mark_count;  // GATHER: tail_start, refreshes counted (may be NULL)
 };
 // Preloaded argument `rows_heads`: rows of the small cache that exist whatever the lengths say | a predicate is given | KV heads << 16.
 constexpr int kSpecBits = 15, kPredBit = 1 << kSpecBits;
@@ -21,8 +22,11 @@ static_assert(kMergeChunks * 128 < (1 << kSpecBits), "rows of the small cache");
 // Attention over the small cache and the rows decoded since the refresh, where no workgroup has more rows than it holds
 // at once: 16 per wavefront.  Workgroup c of KV head g of sequence b.  With the trigger's test: true in the wavefronts with rows if the
 // sequence needs a full step, and nothing has been published then.
+// GATHER: the step right after a selection, with the gather in it.  The rows of the small cache come from the full one (k2 / v2) through the
+// selection, which takes tail_start's place among the arguments, and are written to the small cache (k1 / v1) on the way, those beyond the
+// sequence's end too; a row whose entry is no position of the full cache is the small cache's own.  No rows since.
 enum TestBy { kNoTest, kTestBeside, kTestInside };      // the test is the work of a wavefront more, or of the first one with rows
-template <int G, int NW, TestBy TEST, bool EXACT>
+template <int G, int NW, TestBy TEST, bool EXACT, bool GATHER = false>
 __device__ __forceinline__
 bool partial_tile(const uint16_t* k1, const uint16_t* v1, int64_t s_b_and_tail, int32_t s_h, uint32_t rows_heads,
                   const int32_t* seq_lens, const int32_t* tail_start, const uint16_t* q, const TileParams& p, int c, int g, int b) {
@@ -39,7 +43,8 @@ bool partial_tile(const uint16_t* k1, const uint16_t* v1, int64_t s_b_and_tail, 
     if (!TRIG && (rows_heads & kPredBit) != 0 && p.pred[b] != p.pred_val) return false;
     // ---- the scalars of the whole kernel are requested here, in one round trip (left to itself the compiler reads them
     //      where they are used, a round trip each), and waited for behind the requests for the first rows ----
-    const int len_raw = seq_lens[b], tail_raw = tail_start[b];
+    static_assert(!GATHER || !TRIG, "no test right after a selection");
+    const int len_raw = seq_lens[b], tail_raw = GATHER ? len_raw : tail_start[b];
     const float scale2 = p.scale2;
     const int spin = p.slice_spin, n_sel = p.n_sel, evict = p.evict, max_rows2 = p.max_rows2, cap1 = p.cap1,
               cap2 = p.cap2;
@@ -72,17 +77,50 @@ bool partial_tile(const uint16_t* k1, const uint16_t* v1, int64_t s_b_and_tail, 
     };
     int r_first = c * WG + w * 16;
     const int early = c < first_tail ? spec_rows : 0;
-    request_k(k1, early, r_first);
+    // GATHER: where the rows of this lane are: row n16 of the wavefront's 16 for K, rows 4 jj + c4 for V
+    int from_k = -1, from_v[4] = {-1, -1, -1, -1};
+    if constexpr (GATHER) {
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(tail_start) + bg * spec_rows, 0, spec_rows * 4, 0x00020000);
+        from_k = (int)__builtin_amdgcn_raw_buffer_load_b32(rs, (r_first + n16) * 4, 0, 0);
+    } else {
+        request_k(k1, early, r_first);
+    }
     {                                         // (heads beyond the group read as zero)
         const __amdgpu_buffer_rsrc_t rq = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(q) + bg * G * kD, 0, G * kD * 2, 0x00020000);
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) qa[kk] = __builtin_amdgcn_raw_buffer_load_b128(rq, k_lane + kk * 64, 0, 0);
     }
-    request_v(v1, early, r_first);
+    if constexpr (!GATHER) request_v(v1, early, r_first);
     asm volatile("" :: "s"(scale2), "s"(spin), "s"(out_all), "s"(counters), "s"(tag_rows), "s"(epochs),
                  "s"(k2), "s"(v2), "s"(s2_b), "s"(s2_h), "s"(p.pred_val));
     const uint32_t epoch = *(const __attribute__((address_space(4))) uint32_t*)(epochs + bg);      // (the kernel's own store comes after: a scalar load)
     __builtin_amdgcn_sched_barrier(0);
+    if constexpr (GATHER) {
+        from_k = r_first + n16 < spec_rows && (uint32_t)from_k < (uint32_t)cap2 ? from_k : -1;
+        const uint64_t at = (uint64_t)s2_b * (uint32_t)b + (uint64_t)s2_h * (uint32_t)g;
+        auto row_at = [&](const uint16_t* full, const uint16_t* small, int from, int r) {
+            return from >= 0 ? full + at + (int64_t)from * kD : small + (int64_t)min(r, spec_rows - 1) * kD;
+        };
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) {
+            from_v[jj] = __shfl(from_k, jj * 4 + c4);
+            kA[jj] = *reinterpret_cast<const u32x4*>(row_at(k2, k1, from_v[jj], r_first + jj * 4 + c4) + n16 * 8);
+        }
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) vA[jj] = *reinterpret_cast<const u32x4*>(row_at(v2, v1, from_v[jj], r_first + jj * 4 + c4) + n16 * 8);
+        if (c == 0 && g == 0 && tid == 0) {
+            if (p.mark_tail != nullptr) p.mark_tail[b] = len_raw;
+            if (p.mark_count != nullptr) p.mark_count[b] += 1;      // (one writer per sequence and launch)
+        }
+    }
+    auto write_rows = [&](const uint16_t* small, const u32x4 (&rows)[4]) {
+        if constexpr (GATHER) {
+            uint16_t* to = const_cast<uint16_t*>(small) + (int64_t)(r_first + c4) * kD + n16 * 8;
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj)
+                if (from_v[jj] >= 0) *reinterpret_cast<u32x4*>(to + jj * 4 * kD) = rows[jj];
+        }
+    };
 
     __shared__ __attribute__((aligned(16))) uint16_t sV[WG][VS];
     __shared__ __attribute__((aligned(16))) uint2 sP[2][KS][64][2];      // hi and lo, step, lane, half of the step
@@ -155,6 +193,8 @@ bool partial_tile(const uint16_t* k1, const uint16_t* v1, int64_t s_b_and_tail, 
             lds_barrier();
             return needs_full();
         }
+        write_rows(k1, kA);
+        write_rows(v1, vA);
         return false;
     }
     if (tail) {
@@ -173,6 +213,15 @@ bool partial_tile(const uint16_t* k1, const uint16_t* v1, int64_t s_b_and_tail, 
     asm volatile("" : "+v"(at0.q), "+v"(at0.row), "+v"(at0.first), "+v"(at0.last) : "s"(tag));
     if constexpr (EXACT) asm volatile("" : "+v"(at0.sum));
 
+    if constexpr (GATHER) {                   // whole rows of K, into the operand layout by way of the V tile's room
+        write_rows(k1, kA);
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) *reinterpret_cast<u32x4*>(&sV[w * 16 + jj * 4 + c4][n16 * 8]) = kA[jj];
+        wave_lds_sync();
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) kA[kk] = *reinterpret_cast<const u32x4*>(&sV[w * 16 + n16][kk * 32 + c4 * 8]);
+        wave_lds_sync();
+    }
     // ---- S^T = K Q^T: head n16, rows 4 c4 + i of the wavefront's 16 ----
     float s[4];
     const bool whole = r_first + 16 <= row1;
@@ -209,6 +258,7 @@ bool partial_tile(const uint16_t* k1, const uint16_t* v1, int64_t s_b_and_tail, 
     sP[1][w >> 1][lane][w & 1] = lo;
     ps = sum_xor32(sum_xor16(ps));
     if (c4 == 0) sL[n16][w] = ps;
+    write_rows(v1, vA);
     if (!whole) {       // V rows past the end hold whatever the cache holds there, maybe NaN: P is 0 for them, but 0 * NaN is NaN
 #pragma unroll
         for (int jj = 0; jj < 4; ++jj)
@@ -308,7 +358,7 @@ static inline TileArgs tile_args(const AttnParams& p) {
     const uint32_t spec_rows = (uint32_t)(p.n_sel < p.cap1 ? p.n_sel : p.cap1);
     return {{(float)((double)p.scale * 1.4426950408889634), p.n_sel, p.evict, p.max_rows2, p.cap1, p.cap2, p.slice_spin, p.pred_val,
              p.epochs, p.out, p.counters, p.tag_rows, p.k2, p.v2, p.s2_b, p.s2_h,
-             p.pred, p.trig_q_ref, p.trig_sim, p.trig_need, p.trig_threshold},
+             p.pred, p.trig_q_ref, p.trig_sim, p.trig_need, p.trig_threshold, p.mark_tail, p.mark_count},
             spec_rows | (p.pred != nullptr ? kPredBit : 0) | ((uint32_t)p.Hkv << 16), p.s1_b | ((int64_t)p.nch << 56)};
 }
 

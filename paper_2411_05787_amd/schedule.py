@@ -94,12 +94,13 @@ class RefreshKVLayer:
             rk.rk_full_attn_select(g, q, self.K, self.V, self.seq_lens, self.max_len, out, self.k_small, self.pool_w,
                                    self.idx, weights=self.weights, pred=pred, pred_val=1, workspace=self.ws,
                                    stream=stream)
+        if self.scores_only_refresh:      # the K selected rows and nothing else: nothing has been decoded since
+            rk.rk_gather_attn(g, q, self.K, self.V, self.idx, self.k_small, self.small_K, self.small_V, self.seq_lens,
+                              self.tail_start, out, pred=pred, pred_val=1, workspace=self.ws, stream=stream)
+            return
         rk.rk_gather_small_kv(g, self.K, self.V, self.idx, self.k_small, self.small_K, self.small_V,
                               seq_lens=self.seq_lens, tail_start=self.tail_start,
                               pred=pred, pred_val=1, stream=stream)
-        if self.scores_only_refresh:      # tail_start == seq_lens now: the K selected rows and nothing else
-            rk.rk_partial_attn(g, q, self.small_K, self.small_V, self.k_small, self.K, self.V, self.tail_start,
-                               self.seq_lens, 1, out, pred=pred, pred_val=1, workspace=self.ws, stream=stream)
 
     def prefill_init(self, q_win: torch.Tensor, stream=None) -> None:
         """Start the small cache right after the prefill (Section 2.2, "Prefilling stage"): q_win

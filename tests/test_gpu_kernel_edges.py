@@ -680,6 +680,57 @@ def test_test_step_in_one_launch(rk, case):
         rk.rk_debug_set_slice_spin(256)
 
 
+# (heads per group, KV heads, sequences, rows, K): tiles of 4 and 8 wavefronts, their last one partly filled, pairs and log-sum-exps as weights, more
+# ranks than rows, and more rows than are resident at once (two launches).
+GATHER_ATTN = [(4, 8, 1, 9000, 8192), (4, 8, 1, 3000, 2048), (4, 8, 1, 3000, 65), (7, 4, 1, 5000, 4097), (1, 8, 1, 500, 1), (3, 3, 2, 700, 127), (8, 4, 1, 90, 200),
+               (4, 8, 4, 2100, 1025), (7, 4, 6, 1300, 512), (5, 8, 3, 1000, 300), (2, 8, 5, 3000, 2500), (6, 8, 16, 700, 350)]
+
+
+@pytest.mark.parametrize("case", GATHER_ATTN, ids=["g%d_%dx%d_n%d_k%d" % (c[0], c[2], c[1], c[3], c[4]) for c in GATHER_ATTN])
+def test_gather_inside_the_step(rk, case):
+    """Small caches and tail_start bit for bit as the gather leaves them, rows without an entry untouched; outputs against fp64 (one bf16 step
+    of the larger value and 4e-6); a sequence that the predicate leaves out stays as it is."""
+    G, Hkv, B, n, k = case
+    say("gather inside", case)
+    Hq, cap = G * Hkv, n + 6
+    g = torch.Generator(device="cuda").manual_seed(n + k)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
+    K, V, q = rnd(B, Hkv, cap, 128), rnd(B, Hkv, cap, 128), rnd(B, Hq, 128)
+    lens = torch.tensor([n - 37 * (b % 2) for b in range(B)], dtype=torch.int32, device="cuda")
+    idx = torch.full((B, Hkv, k), -1, dtype=torch.int32, device="cuda")
+    for b in range(B):
+        m = min(k, int(lens[b]))
+        idx[b, :, :m] = torch.stack([torch.randperm(int(lens[b]), generator=g, device="cuda")[:m] for _ in range(Hkv)]).to(torch.int32)
+    geom = rk.Geom(B, Hq, Hkv, 128, SCALE)
+    ws = rk.Workspace(geom, cap, k)
+    pred = torch.tensor([0 if b == 1 else 1 for b in range(B)], dtype=torch.int32, device="cuda")
+    for use_pred, spin in ((False, 256), (True, 0), (True, 256)):
+        p = pred if use_pred else None
+        rk.rk_debug_set_slice_spin(spin)
+        try:
+            state = [[torch.full((B, Hkv, k, 128), 3.0, dtype=torch.bfloat16, device="cuda") for _ in range(2)] +
+                     [torch.full((B,), 5, dtype=torch.int32, device="cuda")] for _ in range(2)]
+            rk.rk_gather_small_kv(geom, K, V, idx, k, state[0][0], state[0][1], seq_lens=lens, tail_start=state[0][2], pred=p, pred_val=1)
+            out = torch.full((B, Hq, 128), 7.0, dtype=torch.bfloat16, device="cuda")
+            rk.rk_gather_attn(geom, q, K, V, idx, k, state[1][0], state[1][1], lens, state[1][2], out, pred=p, pred_val=1, workspace=ws)
+            torch.cuda.synchronize()
+        finally:
+            rk.rk_debug_set_slice_spin(256)
+        for a, b in zip(*state):
+            assert torch.equal(a, b)
+        for b in range(B):
+            if use_pred and b == 1:
+                assert (out[b] == 7.0).all()
+                continue
+            m = min(k, int(lens[b]))
+            at = idx[b, :, :m].long()[:, :, None].expand(-1, -1, 128)
+            Kb, Vb = torch.gather(K[b], 1, at).double(), torch.gather(V[b], 1, at).double()
+            x = SCALE * torch.matmul(q[b].double().view(Hkv, G, 128), Kb.transpose(1, 2).contiguous())
+            want = torch.matmul(torch.softmax(x, dim=-1), Vb).reshape(-1, 128)
+            d = (out[b].double() - want).abs()
+            assert (d <= torch.maximum(out[b].double().abs(), want.abs()) * 2.0 ** -7 + 4e-6).all(), (b, float(d.max()))
+
+
 def _select_scores(name, rows, n, g):
     w = torch.exp(torch.randn(*rows, n, generator=g) * 1.2 - 10)
     if name == "levels":                   # few values: stretches do not fit, the row is one workgroup's
