@@ -311,7 +311,7 @@ static inline bool select_listed(int64_t max_len, int64_t k, int64_t rows) {
 //   sel_counters int32 [B*Hkv][2]            arrival tickets of the selection (word 0); of its listing form the
 //                                            runs listed (0) and the tickets (1)
 //   epochs    uint32 [B*Hkv]                 call number of the last merge inside a split kernel
-//   hist      uint32 [B*Hkv][kHistBins]      first-level histogram of the pooled scores
+//   hist      uint32 [B*Hkv][kHistBins]      first-level histogram of the pooled scores (added to two bins at a time)
 //   tag_rows  16 B  [B*Hkv][kTagSlots][G*64]  tagged partial results of the kernels that merge
 //                                            inside the launch (see rk_attn_common.h, and merge_tagged_heads in rk_attn.hip)
 //   lse       fp32  [B*Hq]                   log-sum-exp when the caller does not ask for it
@@ -349,8 +349,8 @@ static inline int64_t pooled_row_stride(int64_t max_len) { return (max_len + 3) 
 static inline size_t zero_kept_bytes(const rk_geom* g) {
     const size_t problems = (size_t)g->batch * g->n_kv_heads;
     const size_t G = (size_t)(g->n_q_heads / g->n_kv_heads);
-    size_t off = problems * ((size_t)kCounterStride + 2 + 1 + (size_t)kHistBins) * sizeof(int32_t);
-    off = (off + 255) / 256 * 256;
+    size_t off = align_up(problems * ((size_t)kCounterStride + 2 + 1) * sizeof(int32_t), 256);
+    off += problems * kHistBins * sizeof(int32_t);
     return off + problems * kTagRegionRows * G * 16;
 }
 
@@ -497,8 +497,8 @@ static inline Workspace carve(const rk_geom* g, int64_t max_len, int64_t max_k, 
     w.counters = (int32_t*)(p + off); off += problems * kCounterStride * sizeof(int32_t);
     w.sel_counters = (int32_t*)(p + off); off += 2 * problems * sizeof(int32_t);
     w.epochs = (uint32_t*)(p + off);  off += problems * sizeof(uint32_t);
-    w.hist = (uint32_t*)(p + off);    off += problems * kHistBins * sizeof(uint32_t);
     off = align_up(off, 256);
+    w.hist = (uint32_t*)(p + off);    off += problems * kHistBins * sizeof(uint32_t);
     w.tag_rows = (uint32_t*)(p + off); off += problems * kTagRegionRows * G * 16;
     w.lse = (float*)(p + off);        off += align_up((size_t)g->batch * g->n_q_heads * sizeof(float), 256);
     w.part_ml = (float*)(p + off);    off += align_up(problems * kMaxChunks * G * 2 * sizeof(float), 256);

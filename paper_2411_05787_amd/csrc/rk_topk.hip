@@ -78,27 +78,38 @@ void pool_hist_kernel(const float* __restrict__ weights, int64_t w_stride, const
                       const int32_t* pred, int32_t pred_val) {
     const int g = blockIdx.y, b = blockIdx.z;
     if (pred != nullptr && pred[b] != pred_val) return;
-    const int len = min(seq_lens[b], max_len);
     const int j0 = blockIdx.x * TILE;
-    if (j0 >= len) return;
     __shared__ __attribute__((aligned(16))) float sA[TILE + RK_MAX_POOL_W + 1];
-    __shared__ uint32_t sH[kHistBins];
+    __shared__ __attribute__((aligned(8))) uint32_t sH[kHistBins];
     const float* wg = weights + ((int64_t)b * Hq + (int64_t)g * G) * w_stride;
     const int span = TILE + 2 * half;
-    for (int i = threadIdx.x; i < kHistBins; i += 256) sH[i] = 0;
     constexpr int R = (TILE + RK_MAX_POOL_W - 1 + 255) / 256;
+    // the heads' weights, all requested together; one sequence: before its length is known (rows have room for max_len)
+    float w[R][RK_MAX_GROUP];
+    auto request = [&](int end) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int i = r * 256 + threadIdx.x, j = j0 - half + i;
+            const bool in = i < span && j >= 0 && j < end;
+#pragma unroll
+            for (int gi = 0; gi < RK_MAX_GROUP; ++gi) w[r][gi] = in && gi < G ? wg[(int64_t)gi * w_stride + j] : 0.f;
+        }
+    };
+    const bool early = gridDim.z == 1;
+    if (early) request(max_len);
+    const int len = min(seq_lens[b], max_len);
+    if (j0 >= len) return;
+    if (!early) request(len);
+    for (int i = threadIdx.x; i < kHistBins; i += 256) sH[i] = 0;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         if (r * 256 >= span) break;
         const int i = r * 256 + threadIdx.x, j = j0 - half + i;
         float a = -INFINITY;                     // outside [0, len): never wins a max
         if (i < span && j >= 0 && j < len) {
-            float w[RK_MAX_GROUP];               // the heads' weights, all requested together
-#pragma unroll
-            for (int gi = 0; gi < RK_MAX_GROUP; ++gi) w[gi] = gi < G ? wg[(int64_t)gi * w_stride + j] : 0.f;
 #pragma unroll
             for (int gi = 0; gi < RK_MAX_GROUP; ++gi)
-                if (gi < G) a = aggregate(a, w[gi], gi, agg);
+                if (gi < G) a = aggregate(a, w[r][gi], gi, agg);
             if (agg == RK_AGG_MEAN) a = __fdiv_rn(a, (float)G);
         }
         if (i < span) sA[i] = a;
