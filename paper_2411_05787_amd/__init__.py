@@ -1,6 +1,6 @@
 """RefreshKV decode-attention hot path for AMD MI355X (gfx950).
 
-A thin ctypes binding over ``librefreshkv.so`` (hand-written HIP; C ABI declared in
+A thin binding (ctypes; C++ for the shortest calls) over ``librefreshkv.so`` (hand-written HIP; C ABI declared in
 ``include/refreshkv.h``).  Every function here only marshals arguments: all arithmetic runs
 in the HIP kernels.  PyTorch tensors are used as device memory and for the current stream.
 

@@ -1,4 +1,4 @@
-"""Builds librefreshkv.so (hand-written HIP for gfx950) in-tree with hipcc."""
+"""Builds librefreshkv.so (hand-written HIP for gfx950, hipcc) and _rkbind.so (argument marshalling, g++) in-tree."""
 from __future__ import annotations
 
 import os
@@ -9,6 +9,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "librefreshkv.so")
+BIND = os.path.join(HERE, "_rkbind.so")               # argument marshalling of the short calls (csrc/rk_bind.cpp), linked against LIB
 SOURCES = ["rk_api.hip", "rk_attn.hip", "rk_partial.hip", "rk_topk.hip", "rk_gather.hip", "rk_query_sim.hip", "rk_step.hip",
            "rk_window.hip", "rk_h2o.hip"]
 # Packed fp32 VALU forms are switched off for every device compilation of this library.
@@ -26,6 +27,20 @@ def hipcc() -> str:
     raise RuntimeError("hipcc not found: the HIP library cannot be built")
 
 
+def bind_commands(obj: str) -> tuple:
+    """Compilation and link of BIND: host code only; what it needs of torch is loaded before it."""
+    import sysconfig
+    import torch
+    root, cxx = os.path.dirname(torch.__file__), shutil.which("g++") or "g++"
+    compile_ = [cxx, "-O2", "-std=c++17", "-fPIC", "-fvisibility=hidden", "-w",
+                "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+                "-I", os.path.join(root, "include"), "-I", os.path.join(root, "include", "torch", "csrc", "api", "include"),
+                "-I", sysconfig.get_paths()["include"], "-c", os.path.join(CSRC, "rk_bind.cpp"), "-o", obj]
+    link = [cxx, "-shared", obj, LIB, "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-Wl,--as-needed",
+            "-Wl,-rpath,$ORIGIN", "-o", BIND]
+    return compile_, link
+
+
 def build(verbose: bool = False, jobs: int = 6) -> str:
     """Compile every source for gfx950 and link the shared library; returns its path."""
     cc = hipcc()
@@ -33,6 +48,9 @@ def build(verbose: bool = False, jobs: int = 6) -> str:
     os.makedirs(objdir, exist_ok=True)
     procs = []
     objs = []
+    bind_obj = os.path.join(objdir, "rk_bind.o")
+    bind_compile, bind_link = bind_commands(bind_obj)
+    procs.append(("rk_bind.cpp", bind_compile, subprocess.Popen(bind_compile, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     for src in SOURCES:
         obj = os.path.join(objdir, src.replace(".hip", ".o"))
         objs.append(obj)
@@ -44,13 +62,16 @@ def build(verbose: bool = False, jobs: int = 6) -> str:
         out, _ = pr.communicate()
         lines = [ln for ln in out.splitlines() if "packed-fp32-ops" not in ln]
         if pr.returncode != 0:
-            raise RuntimeError("hipcc failed on %s:\n%s\n%s" % (src, " ".join(cmd), "\n".join(lines)))
+            raise RuntimeError("compilation failed on %s:\n%s\n%s" % (src, " ".join(cmd), "\n".join(lines)))
         if verbose and lines:
             print("\n".join(lines))
-    cmd = [cc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB]
+    cmd = [cc, "--offload-arch=gfx950", "-shared", "-fPIC", "-Wl,-soname,librefreshkv.so", *objs, "-o", LIB]
     r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stdout)
+    r = subprocess.run(bind_link, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("link of rk_bind.cpp failed:\n" + r.stdout)
     return LIB
 
 

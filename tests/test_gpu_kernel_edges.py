@@ -731,6 +731,66 @@ def test_gather_inside_the_step(rk, case):
             assert (d <= torch.maximum(out[b].double().abs(), want.abs()) * 2.0 ** -7 + 4e-6).all(), (b, float(d.max()))
 
 
+@pytest.mark.parametrize("form", ["plain", "strided", "subclass", "numpy_int", "stream", "wrong_shape", "wrong_type", "not_contiguous", "short_cache"])
+def test_calls_marshalled_in_cpp_take_what_python_takes(rk, form, monkeypatch):
+    """The same results, or the same exception, whether the arguments go through the C++ checks or through those of binding.py alone."""
+    B, G, Hkv, n, k = 2, 4, 3, 300, 64
+    g = torch.Generator(device="cuda").manual_seed(5)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
+    geom = rk.Geom(B, G * Hkv, Hkv, 128, SCALE)
+    K, V, q = rnd(B, Hkv, n, 128), rnd(B, Hkv, n, 128), rnd(B, G * Hkv, 128)
+    new = rnd(2, B, Hkv, 128)
+    idx = torch.stack([torch.randperm(n - 9, generator=g, device="cuda")[:k] for _ in range(B * Hkv)]).view(B, Hkv, k).to(torch.int32)
+    n_sel, stream = k, None
+    if form == "strided":
+        K, V = rnd(B, Hkv + 2, n + 5, 128)[:, 1:-1, :n], rnd(B, Hkv + 2, n + 5, 128)[:, 1:-1, :n]
+    elif form == "subclass":
+        q = torch.nn.Parameter(q, requires_grad=False)
+    elif form == "numpy_int":
+        n_sel = np.int64(k)
+    elif form == "stream":
+        stream = torch.cuda.current_stream()
+    elif form == "wrong_shape":
+        q = q[:, :-1].contiguous()
+    elif form == "wrong_type":
+        q = q.float()
+    elif form == "not_contiguous":
+        q = rnd(B, 128, G * Hkv).transpose(1, 2)
+    elif form == "short_cache":
+        n_sel = k + 1
+
+    def run():
+        ws = rk.Workspace(geom, n, k)
+        lens, tail = torch.tensor([n, n - 7], dtype=torch.int32, device="cuda"), torch.tensor([n - 9, n - 9], dtype=torch.int32, device="cuda")
+        sK, sV = torch.zeros(2, B, Hkv, k, 128, dtype=torch.bfloat16, device="cuda")
+        total, pos = torch.ones(B, Hkv, n, device="cuda"), torch.arange(n, dtype=torch.int32, device="cuda").expand(B, Hkv, n).contiguous()
+        cache = [t.clone().contiguous() for t in (K, V)]
+        n_rows, n_attend = torch.full((B,), n - 1, dtype=torch.int32, device="cuda"), torch.zeros(B, dtype=torch.int32, device="cuda")
+        state = rk.h2o_state(geom, *cache, total, pos, n_rows, n_attend)
+        outs = [torch.zeros(B, G * Hkv, 128, dtype=torch.bfloat16, device="cuda") for _ in range(4)]
+        res = []
+        for call in (lambda: rk.rk_gather_small_kv(geom, K, V, idx, n_sel, sK, sV, seq_lens=lens, tail_start=tail.clone(), stream=stream),
+                     lambda: rk.rk_partial_attn(geom, q, sK, sV, n_sel, K, V, tail, lens, 16, outs[0], workspace=ws, stream=stream),
+                     lambda: rk.rk_partial_attn_fixed(geom, q, sK, sV, n_sel, K, V, tail, lens, 16, outs[1], workspace=ws, stream=stream),
+                     lambda: rk.rk_full_attn(geom, q, K, V, lens, n, outs[2], workspace=ws, stream=stream),
+                     lambda: rk.rk_h2o_step(geom, state, q, new[0], new[1], lens, n - 1, n // 2, outs[3], workspace=ws, stream=stream)):
+            try:
+                call()
+                res.append(None)
+            except ValueError as e:
+                res.append(str(e))
+        torch.cuda.synchronize()
+        return res, [sK, sV, *outs, total, pos, *cache, n_rows]
+
+    by_cpp = run()
+    monkeypatch.setattr(rk.binding, "_native", type("none", (), {name: staticmethod(lambda *a: None) for name in dir(rk.binding._native)}))
+    by_python = run()
+    assert by_cpp[0] == by_python[0], (by_cpp[0], by_python[0])
+    assert any(by_cpp[0]) == (form in ("wrong_shape", "wrong_type", "not_contiguous", "short_cache"))
+    for a, b in zip(by_cpp[1], by_python[1]):
+        assert torch.equal(a, b)
+
+
 def _select_scores(name, rows, n, g):
     w = torch.exp(torch.randn(*rows, n, generator=g) * 1.2 - 10)
     if name == "levels":                   # few values: stretches do not fit, the row is one workgroup's
