@@ -2201,9 +2201,11 @@ static int launch_partial(const rk_geom* geom, const void* q, rk_kv small, int32
     if (trig != nullptr && (ws.tag_rows == nullptr || pred != nullptr)) return RK_ERR_INVALID_ARG;
     AttnParams p = partial_params(geom, q, small, n_sel, evict, full, tail_start, seq_lens, max_recent, out, pred, pred_val, ws, trig);
     // one tile per workgroup where all of them are resident at once
-    const TileForm tile = partial_tile_form(n_sel, max_recent, (int64_t)geom->batch * geom->n_kv_heads, G, trig != nullptr);
+    TileForm tile = trig == nullptr ? two_tile_form(n_sel, max_recent, (int64_t)geom->batch * geom->n_kv_heads, G, evict) : TileForm{};
+    if (tile.waves == 0) tile = partial_tile_form(n_sel, max_recent, (int64_t)geom->batch * geom->n_kv_heads, G, trig != nullptr);
     if (tile.waves != 0 && ws.tag_rows != nullptr && lazy_idx == nullptr) {
         p.nch = tile.nch; p.tail_wg = tile.tail;
+        p.tail_inside = tile.tiles == 2 && tile.tail == 0 ? 1 : 0;
         set_slice_merge(p, true, 0);
         return launch_partial_tile(p, geom->batch, G, tile, trig != nullptr, nullptr, (hipStream_t)stream);
     }

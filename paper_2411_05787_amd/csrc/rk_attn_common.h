@@ -31,6 +31,7 @@ struct AttnParams {
     uint32_t* epochs; uint32_t* tag_rows;     // TAGGED only: call number per (sequence, KV head), tagged partial results
     const int32_t* idx; int32_t idx_stride;   // LAZY only: the selection [B, Hkv, idx_stride] whose rows are not gathered yet
     float* trig_q_ref; float* trig_sim; int32_t* trig_need; float trig_threshold;   // TRIG only: the query-similarity test
+    int32_t tail_inside;               // two_tile_form only: the rows since follow the small cache's in its workgroups
     int32_t* mark_tail; int32_t* mark_count;  // the gather inside the step only: tail_start <- seq_lens, refreshes counted (may be NULL)
     int32_t ragged_batch;              // != 0 (= batch): workgroups are shared out by length, see ragged_share_lane
     int32_t share_cap;                 // ... at most this many to a sequence

@@ -184,7 +184,7 @@ constexpr int kTagRegionRows = kTagSlots * (kD / 2);   // rows per head of a pai
 // 7.4 / 5.1 / 5.9, 4096: 7.4 / 6.0 / 6.3, 8192: 9.9 / - / 8.5; 2 sequences of 2048: 8.7 / 7.9 / 7.9, of 4096: 11.2 / - / 11.4; 4 of 1024:
 // 9.3 / 7.8 / 8.2, of 2048: 12.3 / 16.8 / 11.1, of 2048 and 28 over 4: 10.1 / 9.3 / 8.8; 8 of 1024: 12.1 / 13.8 / 11.1; 16 of 512:
 // 12.2 / 14.1 / 10.8, of 1024: 17.7 / 22.9 / 19.0.
-struct TileForm { int waves, nch, tail; bool exact; };
+struct TileForm { int waves, nch, tail; bool exact; int tiles; };
 // exact: partial results weighed by (max, sum) pairs (rk_attn_common.h): groups beyond 4 over more than 16 pairs, which have no tagged form in
 // attn_split_kernel and kept such pairs before they came here; a lane of a wavefront each, and the region has room for 65 rows of each.  us per launch, attn_split_kernel with
 // pairs / this kernel with a lambda / with pairs: 28 heads over 4, 6 sequences of K = 512: 8.5 / 5.2 / 5.4, of 2048: 11.2 / 7.7 / 7.7, 8 of 512:
@@ -205,9 +205,36 @@ static inline TileForm partial_tile_form(int64_t rows, int64_t tail_rows, int64_
         if (nch > kMergeChunks || nch + tail > (exact ? kTileExactChunks : kTagSlots)) continue;
         if (waves == 4 ? nch * problems <= kComputeUnits && total <= 2 * kComputeUnits
                        : total <= 2 * kComputeUnits || (G <= 4 && total <= 3 * kComputeUnits && nch <= 20))
-            return {waves, (int)nch, (int)tail, exact};
+            return {waves, (int)nch, (int)tail, exact, 1};
     }
-    return {0, 0, 0, false};
+    return {0, 0, 0, false, 0};
+}
+
+// ... with two tiles of 16 rows to each of 8 wavefronts, 256 rows to a workgroup, two workgroups per compute unit: half the partial results to write and
+// read, for a longer chain ahead of them.  The rows since have workgroups of their own, or, where those would be the only ones beyond one
+// per unit, the slots that the small cache's rows leave (0.5 - 0.9 us, as they are requested late, against 3 for a second workgroup on some
+// of the units).  `fixed`: every row since takes the place of a selected one.
+// One workgroup per unit: instead of more than 512 of 128 rows (that are not resident, or three to a unit), or of more than 256 where
+// their results are many.  Two: where they come close to filling the units; between, some units have twice the others' work.  us per
+// launch, before (attn_split_kernel or one tile) / this, 32 heads over 8: 5120 rows 8.4 / 8.1, 6000: 9.0 / 8.3, 8150: 10.9 / 10.1, 8192 with a
+// fixed size: 12.2 / 10.4; 2 sequences of 4000: 11.0 / 10.0, of 8000 (512): 15.9 / 15.5; 4 of 2000: 11.9 / 9.9, of 3500 (448): 15.6 / 14.7; 8 of
+// 1000: 11.8 / 10.1, of 1700 (448): 16.1 / 14.7; 16 of 1000 (512): 17.0 / 16.4; 28 over 4: 9000: 10.3 / 8.4, 16000: 12.1 / 9.8, 4 of 4000: 12.6 / 9.9, 8 of
+// 1500: 9.7 / 9.2, of 2000: 12.4 / 10.1, 16 of 1000: 12.5 / 10.2; 64 over 8: 5000: 9.5 / 8.5, 4 of 2000: 12.0 / 10.1.  Left as they are, 32 over 8: 3000 rows
+// 6.7 / 8.5, 2 of 3000 (one tile: 384): 8.6 / 9.2, 8 of 1250 (320): 12.2 / 13.4, 6 of 1500 (288): 11.7 / 13.4, 8192 with rows since (264): 11.5 / 12.4.
+static inline TileForm two_tile_form(int64_t rows, int64_t tail_rows, int64_t problems, int G, bool fixed) {
+    const TileForm none{0, 0, 0, false, 0};
+    const bool exact = G > 4 && problems > 16;
+    const int64_t all = fixed ? (rows > tail_rows ? rows : tail_rows) : rows + tail_rows;
+    const int64_t nch = (rows + 255) / 256, ones = (rows + 127) / 128, one_total = (ones + (tail_rows + 127) / 128) * problems;
+    int64_t tail = (tail_rows + 255) / 256;
+    if (nch == 0 || tail == 0) return none;
+    if ((nch + tail) * problems > kComputeUnits && all <= nch * 256) tail = 0;
+    const int64_t total = (nch + tail) * problems;
+    if (nch > kMergeChunks || nch + tail > (exact ? kTileExactChunks : kTagSlots) || total > 2 * kComputeUnits) return none;
+    if (exact && nch + tail <= 3 && (G == 8 || problems >= (G > 5 ? 128 : 192))) return none;      // (see partial_tile_form)
+    const bool better = total <= kComputeUnits ? one_total > 2 * kComputeUnits || (one_total > kComputeUnits && ones >= (G > 4 ? 12 : 40))
+                                               : one_total > 2 * kComputeUnits && 8 * total >= 7 * 2 * kComputeUnits;
+    return better ? TileForm{8, (int)nch, (int)tail, exact, 2} : none;
 }
 
 static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -453,11 +480,11 @@ static inline int deferred_split_workgroups(const rk_geom* g, int64_t max_len) {
 // none full and all full: 65536 rows, K = 4096, 28 heads over 4: 9.9 / 7.6 and 42.9 / 38.8; 32768, 2048, 32 over 8: 9.7 / 7.2, 40.9 / 39.8; 8192, 700,
 // 32 over 8: 8.1 / 6.2, 18.8 / 17.1; 3000, 256, 28 over 4: 8.2 / 6.2, 14.2 / 12.1; 16384, 1000, 16 over 4: 7.9 / 5.8, 18.5 / 17.1.
 static inline TileForm test_step_form(const rk_geom* g, int64_t n_sel, int64_t max_recent, int64_t max_len) {
-    if (g->batch != 1) return {0, 0, 0, false};
+    if (g->batch != 1) return {0, 0, 0, false, 0};
     const TileForm f = partial_tile_form(n_sel, max_recent, g->n_kv_heads, g->n_q_heads / g->n_kv_heads, true);
     const int inside = inside_split_workgroups(g, max_len);
     const int64_t most = f.nch + f.tail > inside ? f.nch + f.tail : inside;
-    if (f.waves != 4 || f.exact || inside == 0 || most * g->n_kv_heads > 2 * kComputeUnits) return {0, 0, 0, false};
+    if (f.waves != 4 || f.exact || inside == 0 || most * g->n_kv_heads > 2 * kComputeUnits) return {0, 0, 0, false, 0};
     return f;
 }
 

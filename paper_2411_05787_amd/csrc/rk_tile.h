@@ -12,12 +12,16 @@ struct TileParams {
     int32_t n_sel, evict, max_rows2, cap1, cap2, slice_spin, pred_val;
     uint32_t* epochs; uint16_t* out; int32_t* counters; uint32_t* tag_rows;
     const uint16_t* k2; const uint16_t* v2; int64_t s2_b, s2_h;
-    const int32_t* pred; float* trig_q_ref; float* trig_sim; int32_t* trig_need; float trig_threshold;
-    int32_t* mark_tail; int32_t* mark_count;  // GATHER: tail_start, refreshes counted (may be NULL)
+    const int32_t* pred; float* trig_q_ref;
+    union { float* trig_sim; int32_t* mark_count; };      // GATHER: refreshes counted (may be NULL), tail_start (three lines of 64 bytes of arguments, not four)
+    union { int32_t* trig_need; int32_t* mark_tail; };
+    float trig_threshold;
 };
 // Preloaded argument `rows_heads`: rows of the small cache that exist whatever the lengths say | a predicate is given | KV heads << 16.
 constexpr int kSpecBits = 15, kPredBit = 1 << kSpecBits;
-static_assert(kMergeChunks * 128 < (1 << kSpecBits), "rows of the small cache");
+constexpr int kTailInside = 0x80;             // in the top byte of `s_b_and_tail`, beside the first workgroup with rows of the full cache
+static_assert(kMergeChunks < kTailInside, "workgroups of the small cache");
+static_assert(kMergeChunks * 256 < (1 << kSpecBits), "rows of the small cache");
 
 // Attention over the small cache and the rows decoded since the refresh, where no workgroup has more rows than it holds
 // at once: 16 per wavefront.  Workgroup c of KV head g of sequence b.  With the trigger's test: true in the wavefronts with rows if the
@@ -26,16 +30,22 @@ static_assert(kMergeChunks * 128 < (1 << kSpecBits), "rows of the small cache");
 // selection, which takes tail_start's place among the arguments, and are written to the small cache (k1 / v1) on the way, those beyond the
 // sequence's end too; a row whose entry is no position of the full cache is the small cache's own.  No rows since.
 enum TestBy { kNoTest, kTestBeside, kTestInside };      // the test is the work of a wavefront more, or of the first one with rows
-template <int G, int NW, TestBy TEST, bool EXACT, bool GATHER = false>
+// R: tiles of 16 rows to a wavefront, all requested at once.  Two: where the launch has no workgroups for the rows since, they
+// follow those of the small cache in the slots that are left (kTailInside); the host knows that they fit.
+template <int G, int NW, TestBy TEST, bool EXACT, bool GATHER = false, int R = 1>
 __device__ __forceinline__
 bool partial_tile(const uint16_t* k1, const uint16_t* v1, int64_t s_b_and_tail, int32_t s_h, uint32_t rows_heads,
                   const int32_t* seq_lens, const int32_t* tail_start, const uint16_t* q, const TileParams& p, int c, int g, int b) {
     constexpr bool TRIG = TEST != kNoTest;
-    constexpr int WG = 16 * NW;               // rows of a workgroup
-    constexpr int DT = 8 / NW, KS = NW / 2;   // P V: tiles of 16 dims of a wavefront, steps of 32 rows
+    constexpr int WG = 16 * NW * R;           // rows of a workgroup
+    constexpr int DT = 8 / NW, KS = NW * R / 2;   // P V: tiles of 16 dims of a wavefront, steps of 32 rows
+    static_assert(R == 1 || (!GATHER && !TRIG), "not built");
+    // P's lanes in LDS: those beyond the group hold nothing that is used, so where there is much of it they read the others'
+    constexpr int GP = R == 1 ? 16 : G <= 4 ? 4 : 8;
     constexpr int VS = kD + 8;                // LDS row stride of the V tile (272 bytes: rows spread over banks)
     const int64_t s_b = s_b_and_tail & ((1ll << 56) - 1);
-    const int first_tail = (int)(s_b_and_tail >> 56) & 0xff;      // workgroups from here on have rows of the full cache, those before of the small one
+    const int first_tail = (int)(s_b_and_tail >> 56) & (R > 1 ? kTailInside - 1 : 0xff);      // workgroups from here on have rows of the full cache, those before of the small one
+    const bool inside = R > 1 && (s_b_and_tail >> 56 & kTailInside) != 0;
     const int spec_rows = rows_heads & ((1 << kSpecBits) - 1), n_kv = rows_heads >> 16;
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n16 = lane & 15, c4 = lane >> 4;
@@ -61,22 +71,27 @@ bool partial_tile(const uint16_t* k1, const uint16_t* v1, int64_t s_b_and_tail, 
         if (w == 0) similarity_request(q, p.trig_q_ref, b, n_kv * G, ld);
     // ---- K rows, queries and V rows of a workgroup of the small cache, requested before any length is known: the rows of a
     //      cache are a buffer, whose rows past the end read as zero ----
-    u32x4 kA[4], vA[4], qa[4];
+    u32x4 kA[R][4], vA[R][4], qa[4];
     k1 += (uint64_t)s_b * (uint32_t)b + (uint64_t)(uint32_t)s_h * (uint32_t)g;
     v1 += (uint64_t)s_b * (uint32_t)b + (uint64_t)(uint32_t)s_h * (uint32_t)g;
     const int k_lane = n16 * (kD * 2) + c4 * 16, v_lane = c4 * (kD * 2) + n16 * 16;      // bytes, from the wavefront's first row
     auto request_k = [&](const uint16_t* k, int rows, int row) {
         const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(k), 0, rows * (kD * 2), 0x00020000);
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) kA[kk] = __builtin_amdgcn_raw_buffer_load_b128(rk, row * (kD * 2) + k_lane + kk * 64, 0, 0);
+        for (int x = 0; x < 4 * R; ++x)
+            kA[x >> 2][x & 3] = __builtin_amdgcn_raw_buffer_load_b128(rk, (row + (x >> 2) * 16) * (kD * 2) + k_lane + (x & 3) * 64, 0, 0);
     };
     auto request_v = [&](const uint16_t* v, int rows, int row) {
         const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(v), 0, rows * (kD * 2), 0x00020000);
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj) vA[jj] = __builtin_amdgcn_raw_buffer_load_b128(rv, row * (kD * 2) + v_lane + jj * 4 * (kD * 2), 0, 0);
+        for (int x = 0; x < 4 * R; ++x)
+            vA[x >> 2][x & 3] = __builtin_amdgcn_raw_buffer_load_b128(rv, row * (kD * 2) + v_lane + x * 4 * (kD * 2), 0, 0);
     };
-    int r_first = c * WG + w * 16;
-    const int early = c < first_tail ? spec_rows : 0;
+    int r_first = c * WG + w * 16 * R;
+    // (inside: the last workgroup, which has the most of the rows since, requests nothing yet: it waits for the lengths and requests every row from
+    // where it is; requested once more, those rows would come behind everybody's)
+    const bool waits = inside && c + 1 == first_tail;
+    const int early = c < first_tail && !waits ? spec_rows : 0;
     // GATHER: where the rows of this lane are: row n16 of the wavefront's 16 for K, rows 4 jj + c4 for V
     int from_k = -1, from_v[4] = {-1, -1, -1, -1};
     if constexpr (GATHER) {
@@ -104,10 +119,10 @@ bool partial_tile(const uint16_t* k1, const uint16_t* v1, int64_t s_b_and_tail, 
 #pragma unroll
         for (int jj = 0; jj < 4; ++jj) {
             from_v[jj] = __shfl(from_k, jj * 4 + c4);
-            kA[jj] = *reinterpret_cast<const u32x4*>(row_at(k2, k1, from_v[jj], r_first + jj * 4 + c4) + n16 * 8);
+            kA[0][jj] = *reinterpret_cast<const u32x4*>(row_at(k2, k1, from_v[jj], r_first + jj * 4 + c4) + n16 * 8);
         }
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj) vA[jj] = *reinterpret_cast<const u32x4*>(row_at(v2, v1, from_v[jj], r_first + jj * 4 + c4) + n16 * 8);
+        for (int jj = 0; jj < 4; ++jj) vA[0][jj] = *reinterpret_cast<const u32x4*>(row_at(v2, v1, from_v[jj], r_first + jj * 4 + c4) + n16 * 8);
         if (c == 0 && g == 0 && tid == 0) {
             if (p.mark_tail != nullptr) p.mark_tail[b] = len_raw;
             if (p.mark_count != nullptr) p.mark_count[b] += 1;      // (one writer per sequence and launch)
@@ -123,7 +138,7 @@ bool partial_tile(const uint16_t* k1, const uint16_t* v1, int64_t s_b_and_tail, 
     };
 
     __shared__ __attribute__((aligned(16))) uint16_t sV[WG][VS];
-    __shared__ __attribute__((aligned(16))) uint2 sP[2][KS][64][2];      // hi and lo, step, lane, half of the step
+    __shared__ __attribute__((aligned(16))) uint2 sP[2][KS][4 * GP][2];  // hi and lo, step, lane, half of the step
     __shared__ __attribute__((aligned(16))) float sM[16][NW], sL[16][NW];
     __shared__ int sTicket, sNeed;
     __shared__ unsigned long long sPend;
@@ -183,18 +198,19 @@ bool partial_tile(const uint16_t* k1, const uint16_t* v1, int64_t s_b_and_tail, 
     asm("" : "+s"(keep));                     // (scalar minima, one after the other)
     const int n1 = min(keep, t0), n2 = min(recent, max_rows2);
     // partial results in all (an empty sequence leaves one of no rows), this workgroup's place among them, the end of its rows
-    const int n_main = first_tail != 0 ? max((int)((uint32_t)(n1 + WG - 1) / WG), n2 == 0 ? 1 : 0) : 0;
-    const int n_tail = max((int)((uint32_t)(n2 + WG - 1) / WG), first_tail != 0 ? 0 : 1);
+    const int n_in = inside ? n2 : 0;         // rows since in the slots behind the small cache's
+    const int n_main = inside ? max((int)((uint32_t)(n1 + n2 + WG - 1) / WG), 1) : first_tail != 0 ? max((int)((uint32_t)(n1 + WG - 1) / WG), n2 == 0 ? 1 : 0) : 0;
+    const int n_tail = inside ? 0 : max((int)((uint32_t)(n2 + WG - 1) / WG), first_tail != 0 ? 0 : 1);
     const int nchunks = n_main + n_tail;
     const bool tail = c >= first_tail;
-    const int c_rec = tail ? c - first_tail + n_main : c, row1 = tail ? n1 + n2 : n1;
+    const int c_rec = tail ? c - first_tail + n_main : c, row1 = tail ? n1 + n2 : n1 + n_in;
     if (c_rec >= (tail ? nchunks : n_main)) {
         if constexpr (TRIG) {                   // (the wavefront with the test waits for everybody)
             lds_barrier();
             return needs_full();
         }
-        write_rows(k1, kA);
-        write_rows(v1, vA);
+        write_rows(k1, kA[0]);
+        write_rows(v1, vA[0]);
         return false;
     }
     if (tail) {
@@ -203,6 +219,22 @@ bool partial_tile(const uint16_t* k1, const uint16_t* v1, int64_t s_b_and_tail, 
         const uint64_t at = (uint64_t)s2_b * (uint32_t)b + (uint64_t)s2_h * (uint32_t)g + (uint64_t)(uint32_t)t0 * kD;
         request_k(k2 + at, n2, r_first - n1);
         request_v(v2 + at, n2, r_first - n1);
+    }
+    if constexpr (R > 1) {
+        if (waits || (inside && n2 > 0 && r_first < row1 && r_first + 16 * R > n1)) {      // (the same for the whole wavefront)
+            // row r of the list: the small cache's, or row t0 + r - n1 of the full one; past the list's end its last row again (masked)
+            const uint64_t at = (uint64_t)s2_b * (uint32_t)b + (uint64_t)s2_h * (uint32_t)g;
+            auto row_at = [&](const uint16_t* small, const uint16_t* full, int r) {
+                r = max(min(r, row1 - 1), 0);
+                return r < n1 || row1 == 0 ? small + (int64_t)r * kD : full + at + (int64_t)(t0 + r - n1) * kD;
+            };
+#pragma unroll
+            for (int x = 0; x < 4 * R; ++x)
+                kA[x >> 2][x & 3] = *reinterpret_cast<const u32x4*>(row_at(k1, k2, r_first + (x >> 2) * 16 + n16) + c4 * 8 + (x & 3) * 32);
+#pragma unroll
+            for (int x = 0; x < 4 * R; ++x)
+                vA[x >> 2][x & 3] = *reinterpret_cast<const u32x4*>(row_at(v1, v2, r_first + x * 4 + c4) + n16 * 8);
+        }
     }
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(tag_rows + bg * kTagRegionRows * G * 4, 0,
                                                                           kTagRegionRows * G * 16, 0x00020000);
@@ -214,30 +246,34 @@ bool partial_tile(const uint16_t* k1, const uint16_t* v1, int64_t s_b_and_tail, 
     if constexpr (EXACT) asm volatile("" : "+v"(at0.sum));
 
     if constexpr (GATHER) {                   // whole rows of K, into the operand layout by way of the V tile's room
-        write_rows(k1, kA);
+        write_rows(k1, kA[0]);
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj) *reinterpret_cast<u32x4*>(&sV[w * 16 + jj * 4 + c4][n16 * 8]) = kA[jj];
+        for (int jj = 0; jj < 4; ++jj) *reinterpret_cast<u32x4*>(&sV[w * 16 + jj * 4 + c4][n16 * 8]) = kA[0][jj];
         wave_lds_sync();
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) kA[kk] = *reinterpret_cast<const u32x4*>(&sV[w * 16 + n16][kk * 32 + c4 * 8]);
+        for (int kk = 0; kk < 4; ++kk) kA[0][kk] = *reinterpret_cast<const u32x4*>(&sV[w * 16 + n16][kk * 32 + c4 * 8]);
         wave_lds_sync();
     }
-    // ---- S^T = K Q^T: head n16, rows 4 c4 + i of the wavefront's 16 ----
-    float s[4];
-    const bool whole = r_first + 16 <= row1;
-    {
+    // ---- S^T = K Q^T: head n16, rows 4 c4 + i of each of the wavefront's tiles ----
+    float s[R][4];
+    const bool whole = r_first + 16 * R <= row1;
+#pragma unroll
+    for (int x = 0; x < R; ++x) {
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk)
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kA[kk]), __builtin_bit_cast(bf16x8, qa[kk]), acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kA[x][kk]), __builtin_bit_cast(bf16x8, qa[kk]), acc, 0, 0, 0);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) s[i] = acc[i] * scale2;
+        for (int i = 0; i < 4; ++i) s[x][i] = acc[i] * scale2;
         if (!whole) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) s[i] = r_first + 4 * c4 + i < row1 ? s[i] : -INFINITY;
+            for (int i = 0; i < 4; ++i) s[x][i] = r_first + x * 16 + 4 * c4 + i < row1 ? s[x][i] : -INFINITY;
         }
     }
-    const float mx = max_xor32(max_xor16(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]))));
+    float mx = fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3]));
+#pragma unroll
+    for (int x = 1; x < R; ++x) mx = fmaxf(mx, fmaxf(fmaxf(s[x][0], s[x][1]), fmaxf(s[x][2], s[x][3])));
+    mx = max_xor32(max_xor16(mx));
     if (c4 == 0) sM[n16][w] = mx;
     lds_barrier();
     if constexpr (TRIG) {
@@ -248,24 +284,33 @@ bool partial_tile(const uint16_t* k1, const uint16_t* v1, int64_t s_b_and_tail, 
 #pragma unroll
     for (int ww = 1; ww < NW; ++ww) M = fmaxf(M, sM[n16][ww]);
     const float ref = M == -INFINITY ? 0.f : M;
-    float pr[4], ps = 0.f;
+    const int p_lane = GP == 16 ? lane : c4 * GP + (n16 & (GP - 1));
+    float ps = 0.f;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) { pr[i] = fast_exp2(s[i] - ref); ps += pr[i]; }
-    const uint2 hi = make_uint2(pack_bf16(pr[0], pr[1]), pack_bf16(pr[2], pr[3]));
-    const uint2 lo = make_uint2(pack_bf16(pr[0] - bf16_lo(hi.x), pr[1] - bf16_hi(hi.x)),
-                                pack_bf16(pr[2] - bf16_lo(hi.y), pr[3] - bf16_hi(hi.y)));
-    sP[0][w >> 1][lane][w & 1] = hi;
-    sP[1][w >> 1][lane][w & 1] = lo;
+    for (int x = 0; x < R; ++x) {
+        float pr[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) { pr[i] = fast_exp2(s[x][i] - ref); ps += pr[i]; }
+        const uint2 hi = make_uint2(pack_bf16(pr[0], pr[1]), pack_bf16(pr[2], pr[3]));
+        const uint2 lo = make_uint2(pack_bf16(pr[0] - bf16_lo(hi.x), pr[1] - bf16_hi(hi.x)),
+                                    pack_bf16(pr[2] - bf16_lo(hi.y), pr[3] - bf16_hi(hi.y)));
+        const int at = w * R + x;
+        if (GP == 16 || n16 < GP) {
+            sP[0][at >> 1][p_lane][at & 1] = hi;
+            sP[1][at >> 1][p_lane][at & 1] = lo;
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);        // (P is on its way before the sums are worked out)
     ps = sum_xor32(sum_xor16(ps));
     if (c4 == 0) sL[n16][w] = ps;
-    write_rows(v1, vA);
+    write_rows(v1, vA[0]);
     if (!whole) {       // V rows past the end hold whatever the cache holds there, maybe NaN: P is 0 for them, but 0 * NaN is NaN
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj)
-            if (r_first + jj * 4 + c4 >= row1) vA[jj] = u32x4{0u, 0u, 0u, 0u};
+        for (int x = 0; x < 4 * R; ++x)
+            if (r_first + x * 4 + c4 >= row1) vA[x >> 2][x & 3] = u32x4{0u, 0u, 0u, 0u};
     }
 #pragma unroll
-    for (int jj = 0; jj < 4; ++jj) *reinterpret_cast<u32x4*>(&sV[w * 16 + jj * 4 + c4][n16 * 8]) = vA[jj];
+    for (int x = 0; x < 4 * R; ++x) *reinterpret_cast<u32x4*>(&sV[w * 16 * R + x * 4 + c4][n16 * 8]) = vA[x >> 2][x & 3];
     lds_barrier();
     // ---- O^T = V^T P^T of all the workgroup's rows: this wavefront's dims, head n16, four consecutive dims per lane ----
     float L = sL[n16][0];
@@ -276,8 +321,8 @@ bool partial_tile(const uint16_t* k1, const uint16_t* v1, int64_t s_b_and_tail, 
     for (int t = 0; t < DT; ++t) { o[t][0] = f32x4{0.f, 0.f, 0.f, 0.f}; o[t][1] = f32x4{0.f, 0.f, 0.f, 0.f}; }
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-        const bf16x8 p_hi = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(&sP[0][ks][lane][0]));
-        const bf16x8 p_lo = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(&sP[1][ks][lane][0]));
+        const bf16x8 p_hi = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(&sP[0][ks][p_lane][0]));
+        const bf16x8 p_lo = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(&sP[1][ks][p_lane][0]));
 #pragma unroll
         for (int t = 0; t < DT; ++t) {
             const uint16_t* vsrc = &sV[32 * ks + 4 * c4 + (n16 >> 2)][(w * DT + t) * 16 + 4 * (n16 & 3)];
@@ -356,10 +401,12 @@ bool partial_tile(const uint16_t* k1, const uint16_t* v1, int64_t s_b_and_tail, 
 struct TileArgs { TileParams t; uint32_t rows_heads; int64_t s_b_and_tail; };
 static inline TileArgs tile_args(const AttnParams& p) {
     const uint32_t spec_rows = (uint32_t)(p.n_sel < p.cap1 ? p.n_sel : p.cap1);
-    return {{(float)((double)p.scale * 1.4426950408889634), p.n_sel, p.evict, p.max_rows2, p.cap1, p.cap2, p.slice_spin, p.pred_val,
+    TileArgs a{{(float)((double)p.scale * 1.4426950408889634), p.n_sel, p.evict, p.max_rows2, p.cap1, p.cap2, p.slice_spin, p.pred_val,
              p.epochs, p.out, p.counters, p.tag_rows, p.k2, p.v2, p.s2_b, p.s2_h,
-             p.pred, p.trig_q_ref, p.trig_sim, p.trig_need, p.trig_threshold, p.mark_tail, p.mark_count},
-            spec_rows | (p.pred != nullptr ? kPredBit : 0) | ((uint32_t)p.Hkv << 16), p.s1_b | ((int64_t)p.nch << 56)};
+             p.pred, p.trig_q_ref, {p.trig_sim}, {p.trig_need}, p.trig_threshold},
+            spec_rows | (p.pred != nullptr ? kPredBit : 0) | ((uint32_t)p.Hkv << 16), p.s1_b | (int64_t)((uint64_t)(p.nch | (p.tail_inside ? kTailInside : 0)) << 56)};
+    if (p.mark_tail != nullptr) { a.t.mark_tail = p.mark_tail; a.t.mark_count = p.mark_count; }
+    return a;
 }
 
 }  // namespace rk

@@ -43,6 +43,11 @@ int main() {
                 printf("tile %ld %ld %d %d %d %d %d %d %d\n", r, p, tail, G, trig, f.waves, f.nch, f.tail, (int)f.exact);
             }
         }
+    for (long r : {0L, 1L, 256L, 500L, 1000L, 1700L, 2000L, 2048L, 3000L, 4000L, 6000L, 8150L, 8181L, 8192L, 9000L, 16000L, 16384L, 20000L}) for (long p : {1L, 4L, 8L, 16L, 32L, 64L, 128L, 512L})
+        for (int tail : {0, 1, 11, 256, 257, 9000}) for (int G : {1, 4, 5, 8}) for (int fixed : {0, 1}) {
+            const TileForm f = two_tile_form(r, tail, p, G, fixed != 0);
+            printf("two %ld %ld %d %d %d %d %d %d %d %d\n", r, p, tail, G, fixed, f.waves, f.nch, f.tail, (int)f.exact, f.tiles);
+        }
     for (long p : {1L, 4L, 8L, 12L, 32L, 33L, 64L, 65L, 128L, 129L, 256L, 257L, 100000L}) printf("parts %ld %d\n", p, select_parts(p));
     for (long l : {1000L, 49151L, 49152L, 65536L, 131072L, 163840L, 196608L, 1000000L}) for (long k : {1L, 3072L, 3073L, 4097L, 8192L, 12288L, 16384L}) for (int b : {1, 2}) for (int hkv : {1, 2, 3, 4, 7}) {
         rk_geom g{b, hkv, hkv, 128, 1.0f};
@@ -238,6 +243,24 @@ def test_partial_tile_form_bounds_and_measured_choices(table):
     assert triggered[(1024, 32, 1, 4)] == (8, 8, 1) and triggered[(2048, 32, 1, 4)][0] == 0 and triggered[(8192, 8, 1, 4)][0] == 0
     assert triggered[(1024, 32, 1, 8)][0] == 0 and triggered[(4096, 8, 1, 8)][0] == 0
     assert got[(0, 8, 500, 4)] == (4, 0, 8) and got[(2048, 8, 100000, 4)][0] == 0
+
+
+def test_two_tile_form_bounds_and_measured_choices(table):
+    """Every row has a slot (those since behind the small cache's where they have no workgroup), the partial results have theirs, the launch is
+    resident as a whole."""
+    got = {}
+    for kind, *v in table:
+        if kind != "two":
+            continue
+        rows, pairs, tail, G, fixed, waves, nch, ntail, exact, tiles = map(int, v)
+        got[(rows, pairs, tail, G, fixed)] = (nch, ntail)
+        if waves:
+            assert (waves, tiles) == (8, 2) and exact == (G > 4 and pairs > 16)
+            assert nch * 256 >= rows and 1 <= nch <= 64 and nch + ntail <= (64 if exact else 65) and (nch + ntail) * pairs <= 512
+            assert ntail * 256 >= tail or (ntail == 0 and nch * 256 >= (max(rows, tail) if fixed else rows + tail))
+    assert got[(8192, 8, 11, 4, 1)] == (32, 0) and got[(8192, 8, 11, 4, 0)] == (0, 0)
+    assert got[(8150, 8, 11, 4, 0)] == (32, 0) and got[(6000, 8, 11, 4, 0)] == (24, 1)
+    assert got[(2000, 32, 11, 4, 0)] == (8, 0) and got[(1000, 128, 11, 4, 0)] == (4, 0) and got[(3000, 8, 11, 4, 0)] == (0, 0)
 
 
 def test_selection_parts_are_resident_at_once(table):
