@@ -682,7 +682,7 @@ constexpr int kSliceChunks = 20, kSliceChunks4 = 64;   // the merge by slices se
 // is over it already (outside the policy's contract) is cut there and the new row is left out.
 // One workgroup's part of it: workgroup c of KV head g of sequence b (heads_first: see attn_split_kernel).  tail_c: the grid x of the
 // workgroup that takes the rows of the full cache on its own (kNoTailWg: none; see tail_mode below).
-template <int G, int NW, bool EMIT, bool TWO_SEG, bool LAZY, bool TAGGED, bool TRIG, bool EXACT>
+template <int G, int NW, bool EMIT, bool TWO_SEG, bool LAZY, bool TAGGED, bool TRIG, bool EXACT, int ROOM = 0>
 __device__ __forceinline__
 void split_pass(const uint16_t* k_first, const uint16_t* v_first, int64_t s_b, int tail_c, int32_t s_h, int32_t spec_rows,
                 const int32_t* seq_lens, const int32_t* tail_start, const int32_t* pred, const uint32_t* epochs,
@@ -901,7 +901,12 @@ void split_pass(const uint16_t* k_first, const uint16_t* v_first, int64_t s_b, i
                                                      kTagRegionRows * G * 16, 0x00020000);
     }
 
-    __shared__ __attribute__((aligned(16))) uint16_t sV[NW][ROWS][VS];
+    __shared__ __attribute__((aligned(16))) uint16_t own[ROOM ? 1 : NW][ROOM ? 1 : ROWS][VS];
+    uint16_t (*sV)[ROWS][VS] = reinterpret_cast<uint16_t (*)[ROWS][VS]>(own);
+    if constexpr (ROOM != 0) {
+        static_assert(ROOM >= (int)(NW * ROWS * VS * sizeof(uint16_t)), "room");
+        sV = reinterpret_cast<uint16_t (*)[ROWS][VS]>(lds_room<ROOM>());
+    }
     __shared__ __attribute__((aligned(16))) float sAlpha[NW][16];
     __shared__ __attribute__((aligned(16))) float sMw[NW][16];
     __shared__ __attribute__((aligned(16))) float sLw[NW][16];
@@ -1314,15 +1319,19 @@ void attn_split_kernel(const uint16_t* k_first, const uint16_t* v_first, int64_t
 // steps of 28 layers at 65536 rows, 28 heads over 4, 21 of the 56 full: 1226 -> 1059 us (figures per layer at test_step_form).
 // The test is a wavefront's work beside its rows: the wavefronts of a workgroup go to the four SIMDs in the same order every time, so that
 // two workgroups of five would need four wavefronts' registers on one of them, and this kernel's are good for two.
-template <int G, bool EXACT>
+// R: tiles of 16 rows of the partial step to a wavefront (test_step_form).
+template <int G, bool EXACT, int R>
 __global__ __launch_bounds__(kSplitWaves * 64, 2)
 void test_step_kernel(const uint16_t* k1, const uint16_t* v1, int64_t s_b_and_tail, int32_t s_h, uint32_t rows_heads,
                       const int32_t* seq_lens, const int32_t* tail_start, const uint16_t* q, const TileParams t, const AttnParams p) {
+    // V tiles of either branch in one place where they would not fit twice per compute unit otherwise (with R = 1 sharing them made two test
+    // steps of 28 layers 2 % slower: 1057 -> 1079 us)
+    constexpr int ROOM = R == 2 ? kSplitWaves * kTileRows * (kD + 8) * 2 : 0;
     const int g = blockIdx.x, c = blockIdx.y;      // (heads first: see attn_split_kernel)
-    if (!partial_tile<G, kSplitWaves, kTestInside, false>(k1, v1, s_b_and_tail, s_h, rows_heads, seq_lens, tail_start, q, t, c, g, 0)) return;
+    if (!partial_tile<G, kSplitWaves, kTestInside, false, false, R, ROOM>(k1, v1, s_b_and_tail, s_h, rows_heads, seq_lens, tail_start, q, t, c, g, 0)) return;
     if (c >= p.nch) return;
-    split_pass<G, kSplitWaves, true, false, false, true, false, EXACT>(p.k2, p.v2, 0, kHeadsFirst, (int32_t)p.s2_h, p.cap2, seq_lens, nullptr, nullptr,
-                                                                       p.epochs, p, c, g, 0, (int)gridDim.x);
+    split_pass<G, kSplitWaves, true, false, false, true, false, EXACT, ROOM>(p.k2, p.v2, 0, kHeadsFirst, (int32_t)p.s2_h, p.cap2, seq_lens, nullptr, nullptr,
+                                                                             p.epochs, p, c, g, 0, (int)gridDim.x);
 }
 
 // Scores-only pass over the full cache (Section 4.3, "Impact of full attention steps", the
@@ -2365,18 +2374,19 @@ extern "C" int rk_gather_attn(const rk_geom* geom, const void* q, rk_kv full, co
 // ---- a layer's step on which the trigger is tested, both branches ----
 namespace rk {
 template <int G, bool EXACT>
-static int launch_test_step(const AttnParams& part, const AttnParams& full, hipStream_t st) {
+static int launch_test_step(const AttnParams& part, const AttnParams& full, int tiles, hipStream_t st) {
     const TileArgs a = tile_args(part);
     const int wgs = part.nch + part.tail_wg > full.nch ? part.nch + part.tail_wg : full.nch;
-    hipLaunchKernelGGL((test_step_kernel<G, EXACT>), dim3(part.Hkv, wgs), dim3(kSplitWaves * 64), 0, st, part.k1, part.v1, a.s_b_and_tail,
+    auto kernel = tiles == 2 ? test_step_kernel<G, EXACT, 2> : test_step_kernel<G, EXACT, 1>;
+    hipLaunchKernelGGL(kernel, dim3(part.Hkv, wgs), dim3(kSplitWaves * 64), 0, st, part.k1, part.v1, a.s_b_and_tail,
                        (int32_t)part.s1_h, a.rows_heads, part.seq_lens, part.tail_start, part.q, a.t, full);
     return launch_status();
 }
 template <int G>
-static int launch_test_step_g(const AttnParams& part, const AttnParams& full, bool exact, hipStream_t st) {
+static int launch_test_step_g(const AttnParams& part, const AttnParams& full, bool exact, int tiles, hipStream_t st) {
     if constexpr (G <= 4)
-        if (!exact) return launch_test_step<G, false>(part, full, st);
-    return launch_test_step<G, true>(part, full, st);
+        if (!exact) return launch_test_step<G, false>(part, full, tiles, st);
+    return launch_test_step<G, true>(part, full, tiles, st);
 }
 
 int test_step_stage(const rk_geom* geom, const void* q, const rk_layer_state& L, const rk_schedule* sched, const int32_t* seq_lens, int32_t max_len,
@@ -2406,7 +2416,7 @@ int test_step_stage(const rk_geom* geom, const void* q, const rk_layer_state& L,
     set_slice_merge(full, true, 0);
     const bool exact = !merges_in_fp32(geom, max_len);
     switch (geom->n_q_heads / geom->n_kv_heads) {
-#define RK_CASE(g) case g: return launch_test_step_g<g>(part, full, exact, st);
+#define RK_CASE(g) case g: return launch_test_step_g<g>(part, full, exact, tile.tiles, st);
         RK_CASE(1) RK_CASE(2) RK_CASE(3) RK_CASE(4) RK_CASE(5) RK_CASE(6) RK_CASE(7) RK_CASE(8)
 #undef RK_CASE
         default: return RK_ERR_UNSUPPORTED;

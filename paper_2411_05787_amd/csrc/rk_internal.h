@@ -474,18 +474,23 @@ static inline int deferred_split_workgroups(const rk_geom* g, int64_t max_len) {
     return inside > 0 ? inside : emit_split_workgroups(g, max_len);
 }
 
-// A trigger's test step in one launch (test_step_kernel): over one sequence, where its partial step has the form of 4 wavefronts and its full
-// pass merges inside, and all workgroups of either are resident at once (two per compute unit).  With several sequences a workgroup of
-// one would have to wait for the decisions of the others.  us per layer of a test step (its share of the batched refresh included), two launches / one,
-// none full and all full: 65536 rows, K = 4096, 28 heads over 4: 9.9 / 7.6 and 42.9 / 38.8; 32768, 2048, 32 over 8: 9.7 / 7.2, 40.9 / 39.8; 8192, 700,
-// 32 over 8: 8.1 / 6.2, 18.8 / 17.1; 3000, 256, 28 over 4: 8.2 / 6.2, 14.2 / 12.1; 16384, 1000, 16 over 4: 7.9 / 5.8, 18.5 / 17.1.
+// A trigger's test step in one launch (test_step_kernel): over one sequence, where its full pass merges inside and its partial step fits 4 wavefronts to
+// a workgroup, of 16 rows each or of two tiles of 16, and all workgroups of either are resident at once (two per compute unit).  With several
+// sequences a workgroup of one would have to wait for the decisions of the others.  us per layer of a test step (its share of the batched refresh included), two
+// launches / one, none full and all full: 65536 rows, K = 4096, 28 heads over 4: 9.9 / 7.6 and 42.9 / 38.8; 32768, 2048, 32 over 8: 9.7 / 7.2, 40.9 / 39.8;
+// 8192, 700, 32 over 8: 8.1 / 6.2, 18.8 / 17.1; 3000, 256, 28 over 4: 8.2 / 6.2, 14.2 / 12.1; 16384, 1000, 16 over 4: 7.9 / 5.8, 18.5 / 17.1; in two tiles (and
+// where the bound on the rows since, which the trigger's schedule lets grow, leaves no slot for a 66th result), 32 over 8: 40000, 3000: 10.4 / 8.9, 47.2 / 46.0;
+// 60000, 4096: 12.9 / 10.1, 65.9 / 65.1; 65536, 7000: 14.9 / 13.2, 78.7 / 73.6; 64 over 8, 40000, 3500: 12.0 / 10.9, 54.4 / 53.7.
 static inline TileForm test_step_form(const rk_geom* g, int64_t n_sel, int64_t max_recent, int64_t max_len) {
     if (g->batch != 1) return {0, 0, 0, false, 0};
-    const TileForm f = partial_tile_form(n_sel, max_recent, g->n_kv_heads, g->n_q_heads / g->n_kv_heads, true);
-    const int inside = inside_split_workgroups(g, max_len);
-    const int64_t most = f.nch + f.tail > inside ? f.nch + f.tail : inside;
-    if (f.waves != 4 || f.exact || inside == 0 || most * g->n_kv_heads > 2 * kComputeUnits) return {0, 0, 0, false, 0};
-    return f;
+    const int64_t inside = inside_split_workgroups(g, max_len);
+    if (inside == 0 || inside * g->n_kv_heads > 2 * kComputeUnits || (g->n_kv_heads > 16 && g->n_q_heads > 4 * g->n_kv_heads)) return {0, 0, 0, false, 0};
+    for (int tiles = 1; tiles <= 2; ++tiles) {             // 64 or 128 rows to a workgroup
+        const int64_t wg = 64 * tiles, nch = (n_sel + wg - 1) / wg, tail = (max_recent + wg - 1) / wg;
+        if (nch <= kMergeChunks && nch + tail <= kTagSlots && (nch + tail) * g->n_kv_heads <= 2 * kComputeUnits &&
+            (tiles == 2 || nch * g->n_kv_heads <= kComputeUnits)) return {4, (int)nch, (int)tail, false, tiles};
+    }
+    return {0, 0, 0, false, 0};
 }
 
 // Form and split of the two passes of rk_window_select over K (see rk_window.hip): 16 T rows per wavefront and step,

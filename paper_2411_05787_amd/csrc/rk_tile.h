@@ -23,6 +23,12 @@ constexpr int kTailInside = 0x80;             // in the top byte of `s_b_and_tai
 static_assert(kMergeChunks < kTailInside, "workgroups of the small cache");
 static_assert(kMergeChunks * 256 < (1 << kSpecBits), "rows of the small cache");
 
+// LDS that the parts of a kernel use one after the other (ROOM bytes; 0: a part has its own).
+template <int BYTES> __device__ __forceinline__ unsigned char* lds_room() {
+    __shared__ __attribute__((aligned(16))) unsigned char room[BYTES];
+    return room;
+}
+
 // Attention over the small cache and the rows decoded since the refresh, where no workgroup has more rows than it holds
 // at once: 16 per wavefront.  Workgroup c of KV head g of sequence b.  With the trigger's test: true in the wavefronts with rows if the
 // sequence needs a full step, and nothing has been published then.
@@ -32,14 +38,14 @@ static_assert(kMergeChunks * 256 < (1 << kSpecBits), "rows of the small cache");
 enum TestBy { kNoTest, kTestBeside, kTestInside };      // the test is the work of a wavefront more, or of the first one with rows
 // R: tiles of 16 rows to a wavefront, all requested at once.  Two: where the launch has no workgroups for the rows since, they
 // follow those of the small cache in the slots that are left (kTailInside); the host knows that they fit.
-template <int G, int NW, TestBy TEST, bool EXACT, bool GATHER = false, int R = 1>
+template <int G, int NW, TestBy TEST, bool EXACT, bool GATHER = false, int R = 1, int ROOM = 0>
 __device__ __forceinline__
 bool partial_tile(const uint16_t* k1, const uint16_t* v1, int64_t s_b_and_tail, int32_t s_h, uint32_t rows_heads,
                   const int32_t* seq_lens, const int32_t* tail_start, const uint16_t* q, const TileParams& p, int c, int g, int b) {
     constexpr bool TRIG = TEST != kNoTest;
     constexpr int WG = 16 * NW * R;           // rows of a workgroup
     constexpr int DT = 8 / NW, KS = NW * R / 2;   // P V: tiles of 16 dims of a wavefront, steps of 32 rows
-    static_assert(R == 1 || (!GATHER && !TRIG), "not built");
+    static_assert(R == 1 || !GATHER, "not built");
     // P's lanes in LDS: those beyond the group hold nothing that is used, so where there is much of it they read the others'
     constexpr int GP = R == 1 ? 16 : G <= 4 ? 4 : 8;
     constexpr int VS = kD + 8;                // LDS row stride of the V tile (272 bytes: rows spread over banks)
@@ -137,7 +143,12 @@ bool partial_tile(const uint16_t* k1, const uint16_t* v1, int64_t s_b_and_tail, 
         }
     };
 
-    __shared__ __attribute__((aligned(16))) uint16_t sV[WG][VS];
+    __shared__ __attribute__((aligned(16))) uint16_t own[ROOM ? 1 : WG][VS];
+    uint16_t (*sV)[VS] = own;
+    if constexpr (ROOM != 0) {
+        static_assert(ROOM >= (int)(WG * VS * sizeof(uint16_t)), "room");
+        sV = reinterpret_cast<uint16_t (*)[VS]>(lds_room<ROOM>());
+    }
     __shared__ __attribute__((aligned(16))) uint2 sP[2][KS][4 * GP][2];  // hi and lo, step, lane, half of the step
     __shared__ __attribute__((aligned(16))) float sM[16][NW], sL[16][NW];
     __shared__ int sTicket, sNeed;

@@ -93,7 +93,7 @@ int main() {
         for (int hkv : {1, 3, 4, 8, 16, 32}) for (int G : {1, 4, 7, 8}) {
             rk_geom g{b, hkv * G, hkv, 128, 1.0f};
             const TileForm f = test_step_form(&g, k, recent, l);
-            printf("test_step %ld %ld %d %d %d %d %d %d %d %d\n", l, k, recent, b, hkv, G, f.waves, f.nch, f.tail, inside_split_workgroups(&g, l));
+            printf("test_step %ld %ld %d %d %d %d %d %d %d %d %d\n", l, k, recent, b, hkv, G, f.waves, f.nch, f.tail, inside_split_workgroups(&g, l), f.tiles);
         }
     for (long l : {1L, 63L, 512L, 513L, 1100L, 1400L, 2100L, 16000L, 32768L, 36000L, 40000L, 64000L, 76000L, 131072L}) for (long p : {1L, 4L, 8L, 128L, 260L, 520L, 4096L})
         for (int blocks : {1, 2, 3, 8, 16}) {
@@ -186,13 +186,14 @@ def test_test_step_in_one_launch_is_resident_as_a_whole(table):
     for kind, *v in table:
         if kind != "test_step":
             continue
-        n, k, recent, batch, hkv, G, waves, nch, tail, inside = map(int, v)
-        got[(n, k, recent, batch, hkv, G)] = waves
+        n, k, recent, batch, hkv, G, waves, nch, tail, inside, tiles = map(int, v)
+        got[(n, k, recent, batch, hkv, G)] = tiles
+        assert (waves != 0) == (tiles != 0)
         if waves:
-            assert waves == 4 and batch == 1 and inside >= 1
-            assert max(nch + tail, inside) * hkv <= 512 and nch * 64 >= k and tail * 64 >= recent and nch + tail <= 65
-    assert got[(66000, 4096, 1, 1, 4, 7)] == 4 and got[(33000, 2048, 64, 1, 8, 4)] == 4
-    assert got[(66000, 4096, 65, 1, 4, 7)] == 0          # a 66th partial result
+            assert waves == 4 and tiles in (1, 2) and batch == 1 and inside >= 1
+            assert max(nch + tail, inside) * hkv <= 512 and nch * 64 * tiles >= k and tail * 64 * tiles >= recent and nch <= 64 and nch + tail <= 65
+    assert got[(66000, 4096, 1, 1, 4, 7)] == 1 and got[(33000, 2048, 64, 1, 8, 4)] == 1
+    assert got[(66000, 4096, 65, 1, 4, 7)] == 2 and got[(33000, 4096, 1, 1, 8, 4)] == 2          # a 66th partial result; more than one workgroup per unit
     assert got[(33000, 8192, 1, 1, 8, 4)] == 0 and got[(33000, 2048, 1, 2, 8, 4)] == 0
 
 
