@@ -239,7 +239,7 @@ def _stream(stream) -> int:
     return int(stream)
 
 
-_native.setup(_stream, _raw_stream, _device)
+_native.setup(_stream, _raw_stream, _device, _Geom, _H2oState)
 
 
 def workspace_bytes(geom: Geom, max_len: int, max_k: int) -> int:

@@ -19,6 +19,8 @@ namespace {
 
 // binding.py's _stream, and the two functions of torch that give the current stream's handle (None where torch lacks them).
 PyObject *g_stream, *g_raw_stream, *g_device;
+// The ctypes classes of rk_geom and rk_h2o_state: what is of another class is binding.py's to refuse.
+PyObject *g_geom, *g_h2o_state;
 
 // One call's arguments: `ok` until one of them is not the common case's.
 struct Args {
@@ -53,10 +55,10 @@ struct Args {
         return (int32_t)v;
     }
     // A ctypes structure by value.
-    template <class T> T structure(PyObject* o) {
+    template <class T> T structure(PyObject* o, PyObject* type) {
         T s{};
         Py_buffer b;
-        if (!ok || PyObject_GetBuffer(o, &b, PyBUF_SIMPLE) != 0) { PyErr_Clear(); ok = false; return s; }
+        if (!ok || (PyObject*)Py_TYPE(o) != type || PyObject_GetBuffer(o, &b, PyBUF_SIMPLE) != 0) { PyErr_Clear(); ok = false; return s; }
         ok = b.len == (Py_ssize_t)sizeof(T);
         if (ok) s = *(const T*)b.buf;
         PyBuffer_Release(&b);
@@ -66,7 +68,7 @@ struct Args {
         static PyObject* const name = PyUnicode_InternFromString("_c");
         PyObject* c = PyObject_GetAttr(a[i], name);
         if (!c) { PyErr_Clear(); ok = false; return; }
-        geom = structure<rk_geom>(c);
+        geom = structure<rk_geom>(c, g_geom);
         Py_DECREF(c);
     }
     rk_kv kv(int k, int v, int64_t min_rows) {
@@ -181,7 +183,7 @@ PyObject* gather(PyObject*, PyObject* const* a, Py_ssize_t n) {
 PyObject* h2o_step(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return with_args(a, n, 13, [](Args& x) -> PyObject* {
         const rk_geom& g = x.geom;
-        const rk_h2o_state state = x.structure<rk_h2o_state>(x.a[1]);
+        const rk_h2o_state state = x.structure<rk_h2o_state>(x.a[1], g_h2o_state);
         void* q = x.dev(2, bf16, {g.batch, g.n_q_heads, g.head_dim});
         void* k_new = x.dev(3, bf16, {g.batch, g.n_kv_heads, g.head_dim});
         void* v_new = x.dev(4, bf16, {g.batch, g.n_kv_heads, g.head_dim});
@@ -215,9 +217,9 @@ PyObject* full_attn(PyObject*, PyObject* const* a, Py_ssize_t n) {
 }
 
 PyObject* setup(PyObject*, PyObject* const* a, Py_ssize_t n) {
-    if (n != 3) { PyErr_SetString(PyExc_TypeError, "setup(stream, raw_stream, device)"); return nullptr; }
-    for (int i = 0; i < 3; ++i) Py_INCREF(a[i]);
-    g_stream = a[0]; g_raw_stream = a[1]; g_device = a[2];
+    if (n != 5) { PyErr_SetString(PyExc_TypeError, "setup(stream, raw_stream, device, geom, h2o_state)"); return nullptr; }
+    for (int i = 0; i < 5; ++i) Py_INCREF(a[i]);
+    g_stream = a[0]; g_raw_stream = a[1]; g_device = a[2]; g_geom = a[3]; g_h2o_state = a[4];
     Py_RETURN_NONE;
 }
 

@@ -1,4 +1,5 @@
 """Sizes at which a kernel's tiles, rounds and dispatch rules change hands, against the CPU oracle."""
+import ctypes
 import sys
 
 import numpy as np
@@ -744,7 +745,7 @@ def test_gather_inside_the_step(rk, case):
             assert (d <= torch.maximum(out[b].double().abs(), want.abs()) * 2.0 ** -7 + 4e-6).all(), (b, float(d.max()))
 
 
-@pytest.mark.parametrize("form", ["plain", "strided", "subclass", "numpy_int", "stream", "wrong_shape", "wrong_type", "not_contiguous", "short_cache"])
+@pytest.mark.parametrize("form", ["plain", "strided", "subclass", "numpy_int", "stream", "wrong_shape", "wrong_type", "not_contiguous", "short_cache", "not_a_state"])
 def test_calls_marshalled_in_cpp_take_what_python_takes(rk, form, monkeypatch):
     """The same results, or the same exception, whether the arguments go through the C++ checks or through those of binding.py alone."""
     B, G, Hkv, n, k = 2, 4, 3, 300, 64
@@ -780,6 +781,8 @@ def test_calls_marshalled_in_cpp_take_what_python_takes(rk, form, monkeypatch):
         cache = [t.clone().contiguous() for t in (K, V)]
         n_rows, n_attend = torch.full((B,), n - 1, dtype=torch.int32, device="cuda"), torch.zeros(B, dtype=torch.int32, device="cuda")
         state = rk.h2o_state(geom, *cache, total, pos, n_rows, n_attend)
+        if form == "not_a_state":
+            state = bytes(state)           # as long as the structure, but not one
         outs = [torch.zeros(B, G * Hkv, 128, dtype=torch.bfloat16, device="cuda") for _ in range(4)]
         res = []
         for call in (lambda: rk.rk_gather_small_kv(geom, K, V, idx, n_sel, sK, sV, seq_lens=lens, tail_start=tail.clone(), stream=stream),
@@ -790,7 +793,7 @@ def test_calls_marshalled_in_cpp_take_what_python_takes(rk, form, monkeypatch):
             try:
                 call()
                 res.append(None)
-            except ValueError as e:
+            except (ValueError, ctypes.ArgumentError) as e:
                 res.append(str(e))
         torch.cuda.synchronize()
         return res, [sK, sV, *outs, total, pos, *cache, n_rows]
@@ -799,7 +802,7 @@ def test_calls_marshalled_in_cpp_take_what_python_takes(rk, form, monkeypatch):
     monkeypatch.setattr(rk.binding, "_native", type("none", (), {name: staticmethod(lambda *a: None) for name in dir(rk.binding._native)}))
     by_python = run()
     assert by_cpp[0] == by_python[0], (by_cpp[0], by_python[0])
-    assert any(by_cpp[0]) == (form in ("wrong_shape", "wrong_type", "not_contiguous", "short_cache"))
+    assert any(by_cpp[0]) == (form in ("wrong_shape", "wrong_type", "not_contiguous", "short_cache", "not_a_state"))
     for a, b in zip(by_cpp[1], by_python[1]):
         assert torch.equal(a, b)
 
