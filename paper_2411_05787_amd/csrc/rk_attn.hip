@@ -1562,29 +1562,28 @@ void merge_normalise_kernel(const AttnParams p, int G) {
     if (p.pred != nullptr && p.pred[b] != p.pred_val) return;
     const int tid = threadIdx.x;
     const int g = h / G, gi = h % G;
+    const int len = min(max(min(p.seq_lens[b], p.cap2), 0), p.max_rows2);
     const int j0 = (x - 1) * kNormTile;
+    if (x >= 1 && j0 >= len) return;
+    const int nchunks = p.ragged_batch != 0 ? stored_chunks(p.counters, (int64_t)b * p.Hkv + g) : active_workgroups(len, p.nch);
+
     __shared__ HeadMergeLds s;
     constexpr int PER = kNormTile / 256;         // scores per thread
     const int64_t bg = (int64_t)b * p.Hkv + g;
     float* row = p.weights + ((int64_t)b * p.Hq + h) * p.w_stride;
 
-    // ---- request everything this workgroup needs before the first wait; one sequence: the scores before its length is known too ----
-    const bool early = gridDim.z == 1;
+    // ---- request everything this workgroup needs before the first wait ----
     float sc[PER];
     float2 v[kOutBatch];
-    auto request = [&](int end) {
+    if (x >= 1) {
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
             const int j = j0 + i * 256 + tid;
-            sc[i] = (j < end) ? row[j] : 0.f;
+            sc[i] = (j < len) ? row[j] : 0.f;
         }
-    };
-    if (early && x >= 1) request(p.max_rows2);
-    const int len = min(max(min(p.seq_lens[b], p.cap2), 0), p.max_rows2);
-    if (x >= 1 && j0 >= len) return;
-    const int nchunks = p.ragged_batch != 0 ? stored_chunks(p.counters, (int64_t)b * p.Hkv + g) : active_workgroups(len, p.nch);
-    if (x == 0) head_out_request(p, G, bg, gi, nchunks, v);
-    else if (!early) request(len);
+    } else {
+        head_out_request(p, G, bg, gi, nchunks, v);
+    }
     block_head_lse(p, G, bg, gi, nchunks, s, p.weights == nullptr);       // (no weights: this is an output merge and nothing else)
     if (x == 0) {
         block_head_out(p, G, b, bg, gi, nchunks, s, v);
@@ -1615,12 +1614,12 @@ void finish_pool_body(const AttnParams& p, const float* __restrict__ scores, int
     const int64_t bg = (int64_t)b * p.Hkv + g;
     const int n_merge = p.out != nullptr ? G : 0;     // no output to merge after a scores-only pass
     const int j0 = (x - n_merge) * TILE;
-    auto row_len = [&]() { return min(max(min(p.seq_lens[b], p.cap2), 0), p.max_rows2); };
-    auto chunks_of = [&](int len) { return p.ragged_batch != 0 ? stored_chunks(p.counters, bg) : active_workgroups(len, p.nch); };
+    const int len = min(max(min(p.seq_lens[b], p.cap2), 0), p.max_rows2);
+    if (x >= n_merge && j0 >= len && !(j0 == 0 && n_merge == 0)) return;   // (an empty sequence still gets its lse = -inf)
+    const int nchunks = p.ragged_batch != 0 ? stored_chunks(p.counters, bg) : active_workgroups(len, p.nch);
 
     __shared__ HeadMergeLds s;
     if (x < n_merge) {
-        const int nchunks = chunks_of(row_len());
         float2 v[kOutBatch];
         head_out_request(p, G, bg, x, nchunks, v);
         block_head_lse(p, G, bg, x, nchunks, s);
@@ -1633,59 +1632,41 @@ void finish_pool_body(const AttnParams& p, const float* __restrict__ scores, int
     constexpr int R = (TILE + RK_MAX_POOL_W - 1 + 255) / 256;
     const int span = TILE + 2 * half;
     const float* sg = scores + ((int64_t)b * p.Hq + (int64_t)g * G) * s_stride;
+
+    // ---- request the raw scores of the tile and its halo, and the chunk statistics.  Not ahead of the length, which saves a round trip: max_len
+    //      is a bound that may lie far above it (a captured step's; the longest of a batch).  us, ahead of it / behind it, 32 heads over 8: selection from the
+    //      scores alone, 32768 rows of at most 32768 27.7 / 27.9, 8192 of 524288 36.8 / 26.1; a full step of 8 layers, 32768 of 131072: 282 / 272 ----
+    float sc[G][R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int i = r * 256 + tid, j = j0 - half + i;
+        const bool in = i < span && j >= 0 && j < len;
+        if (G == 4 && p.w_inter) {                  // the four heads of a position side by side: one 16-byte load
+            const float4 v4 = in ? *reinterpret_cast<const float4*>(sg + (int64_t)j * 4) : make_float4(0.f, 0.f, 0.f, 0.f);
+            sc[0][r] = v4.x; sc[1 % G][r] = v4.y; sc[2 % G][r] = v4.z; sc[3 % G][r] = v4.w;
+        } else {
+#pragma unroll
+            for (int gi = 0; gi < G; ++gi) sc[gi][r] = in ? sg[(int64_t)gi * s_stride + j] : 0.f;
+        }
+    }
     const int wv = tid >> 6, lane = tid & 63;
     constexpr int HPW = (G + 3) / 4;              // heads per wavefront
     constexpr int CPL = kMaxChunks / 64;          // chunk statistics per lane
-
-    // ---- request the raw scores of the tile and its halo, and the chunk statistics: before the length is known, unless the batch
-    //      is ragged (both have room for the longest row; what lies beyond this one's end is not looked at).  A round trip less in a chain of
-    //      five: 8 rows of 32768 6.8 -> 6.5 us, of 131072 12.0 -> 11.3, 4 of 65536 with 7 heads per group 9.1 -> 8.1 ----
-    float sc[G][R];
     float m[HPW][CPL], l[HPW][CPL];
-    auto request = [&](int end, int n_stats) {
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int i = r * 256 + tid, j = j0 - half + i;
-            const bool in = i < span && j >= 0 && j < end;
-            if (G == 4 && p.w_inter) {                  // the four heads of a position side by side: one 16-byte load
-                const float4 v4 = in ? *reinterpret_cast<const float4*>(sg + (int64_t)j * 4) : make_float4(0.f, 0.f, 0.f, 0.f);
-                sc[0][r] = v4.x; sc[1 % G][r] = v4.y; sc[2 % G][r] = v4.z; sc[3 % G][r] = v4.w;
-            } else {
+    for (int e = 0; e < HPW; ++e) {
+        const int gi = wv + 4 * e;
+        const float* ml = p.part_ml + (bg * kMaxChunks * G + min(gi, G - 1)) * 2;
 #pragma unroll
-                for (int gi = 0; gi < G; ++gi) sc[gi][r] = in ? sg[(int64_t)gi * s_stride + j] : 0.f;
+        for (int u = 0; u < CPL; ++u) {
+            const int c = lane + 64 * u;
+            m[e][u] = -INFINITY; l[e][u] = 0.f;
+            if (c < nchunks) {
+                const float2 t2 = *reinterpret_cast<const float2*>(ml + (int64_t)c * G * 2);
+                m[e][u] = t2.x; l[e][u] = t2.y;
             }
         }
-#pragma unroll
-        for (int e = 0; e < HPW; ++e) {
-            const int gi = wv + 4 * e;
-            const float* ml = p.part_ml + (bg * kMaxChunks * G + min(gi, G - 1)) * 2;
-#pragma unroll
-            for (int u = 0; u < CPL; ++u) {
-                const int c = lane + 64 * u;
-                m[e][u] = 0.f; l[e][u] = 0.f;
-                if (c < n_stats) {
-                    const float2 t2 = *reinterpret_cast<const float2*>(ml + (int64_t)c * G * 2);
-                    m[e][u] = t2.x; l[e][u] = t2.y;
-                }
-            }
-        }
-    };
-    const bool early = p.ragged_batch == 0;
-    int len = 0, nchunks = 0, end = p.max_rows2, n_stats = p.nch;
-    if (!early) {
-        len = row_len();
-        nchunks = n_stats = chunks_of(len);
-        end = len;
-        asm volatile("" : "+s"(end));        // (the length is waited for here, and nowhere where it is not yet needed)
     }
-    request(end, n_stats);
-    if (early) { len = row_len(); nchunks = chunks_of(len); }
-    if (j0 >= len && !(j0 == 0 && n_merge == 0)) return;      // (an empty sequence still gets its lse = -inf)
-#pragma unroll
-    for (int e = 0; e < HPW; ++e)
-#pragma unroll
-        for (int u = 0; u < CPL; ++u)
-            if (lane + 64 * u >= nchunks) { m[e][u] = -INFINITY; l[e][u] = 0.f; }
     for (int i = tid; i < kHistBins; i += 256) sH[i] = 0;
 
     // ---- lse of the G heads, fp64, one wavefront per head ----

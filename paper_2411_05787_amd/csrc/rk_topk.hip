@@ -78,28 +78,25 @@ void pool_hist_kernel(const float* __restrict__ weights, int64_t w_stride, const
                       const int32_t* pred, int32_t pred_val) {
     const int g = blockIdx.y, b = blockIdx.z;
     if (pred != nullptr && pred[b] != pred_val) return;
+    const int len = min(seq_lens[b], max_len);
     const int j0 = blockIdx.x * TILE;
+    if (j0 >= len) return;
     __shared__ __attribute__((aligned(16))) float sA[TILE + RK_MAX_POOL_W + 1];
     __shared__ __attribute__((aligned(8))) uint32_t sH[kHistBins];
     const float* wg = weights + ((int64_t)b * Hq + (int64_t)g * G) * w_stride;
     const int span = TILE + 2 * half;
     constexpr int R = (TILE + RK_MAX_POOL_W - 1 + 255) / 256;
-    // the heads' weights, all requested together; one sequence: before its length is known (rows have room for max_len)
+    // The heads' weights of every round, all requested together.  us per call of rk_topk_select, a round at a time (18 registers) / as it is (86), 32 heads over 8: 16
+    // rows of 32768 33.4 / 29.9, 4 of 131072 34.2 / 32.6, 16 of 131072 96.8 / 76.8.  Ahead of the length they gained nothing (24.2 at one row of 131072 either way),
+    // and all of it was lost where max_len is a bound far above it: 65536 of 1048576: 34.7 / 19.3.
     float w[R][RK_MAX_GROUP];
-    auto request = [&](int end) {
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int i = r * 256 + threadIdx.x, j = j0 - half + i;
-            const bool in = i < span && j >= 0 && j < end;
+    for (int r = 0; r < R; ++r) {
+        const int i = r * 256 + threadIdx.x, j = j0 - half + i;
+        const bool in = i < span && j >= 0 && j < len;
 #pragma unroll
-            for (int gi = 0; gi < RK_MAX_GROUP; ++gi) w[r][gi] = in && gi < G ? wg[(int64_t)gi * w_stride + j] : 0.f;
-        }
-    };
-    const bool early = gridDim.z == 1;
-    if (early) request(max_len);
-    const int len = min(seq_lens[b], max_len);
-    if (j0 >= len) return;
-    if (!early) request(len);
+        for (int gi = 0; gi < RK_MAX_GROUP; ++gi) w[r][gi] = in && gi < G ? wg[(int64_t)gi * w_stride + j] : 0.f;
+    }
     for (int i = threadIdx.x; i < kHistBins; i += 256) sH[i] = 0;
 #pragma unroll
     for (int r = 0; r < R; ++r) {

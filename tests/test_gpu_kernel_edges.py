@@ -945,3 +945,66 @@ def test_selection_of_few_among_tens_of_millions_in_one_bin(rk, n, k):
     rest = [j for j in range(k + 2) if j not in taken][:2]
     assert idx[0, 0].tolist() == at.flip(0).tolist() + rest
     assert torch.equal(sel[0, 0], w[0, 0, idx[0, 0].long()])
+
+
+def _us(call, per_graph=10, replays=9):
+    """Shortest time of a call inside a captured graph."""
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(stream):
+        call()
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            for _ in range(per_graph):
+                call()
+        best = float("inf")
+        for _ in range(replays):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            graph.replay()
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) * 1000 / per_graph)
+    return best
+
+
+# (call, rows, bound far above them, most that it may cost against a bound of the rows themselves: half way between the ratio of a launch whose workgroups
+# beyond the rows leave at once, 1.10 / 1.33 / 1.36 / 1.27, and with their scores requested first, 1.71 / 2.05 / 1.87 / 1.75)
+LOOSE_BOUNDS = [("topk", 65536, 1 << 20, 1.4), ("weights", 8192, 1 << 19, 1.7), ("scores", 8192, 1 << 19, 1.6), ("refresh", 8192, 1 << 19, 1.5)]
+
+
+@pytest.mark.parametrize("case", LOOSE_BOUNDS, ids=[c[0] for c in LOOSE_BOUNDS])
+def test_bound_far_above_the_length_costs_little(rk, case):
+    """max_len bounds seq_lens and no more: a captured step's holds for the whole run.  Nothing between the two is read."""
+    what, n, cap, most = case
+    say("loose bound", *case[:3])
+    Hq, Hkv, k = 32, 8, 1024
+    g = torch.Generator(device="cuda").manual_seed(n)
+    geom = rk.Geom(1, Hq, Hkv, 128, SCALE)
+    lens = torch.tensor([n], dtype=torch.int32, device="cuda")
+    idx = torch.zeros(1, Hkv, k, dtype=torch.int32, device="cuda")
+    q = torch.randn(1, Hq, 128, generator=g, device="cuda").to(torch.bfloat16)
+    out = torch.empty_like(q)
+    if what != "topk":
+        K = torch.zeros(1, Hkv, cap, 128, dtype=torch.bfloat16, device="cuda")
+        K[:, :, :n] = torch.randn(1, Hkv, n, 128, generator=g, device="cuda").to(torch.bfloat16)
+    us, found = {}, {}
+    for bound in (n, cap):
+        ws = rk.Workspace(geom, bound, k)
+        w = torch.zeros(1, Hq, bound, device="cuda")
+        if what == "topk":
+            w[:, :, :n] = torch.rand(1, Hq, n, generator=torch.Generator(device="cuda").manual_seed(1), device="cuda")
+            call = lambda: rk.rk_topk_select(geom, w, lens, bound, k, 7, idx, workspace=ws)
+        elif what == "weights":
+            call = lambda: rk.rk_full_attn(geom, q, K, K, lens, bound, out, weights=w, workspace=ws)
+        elif what == "scores":
+            call = lambda: rk.rk_score_select(geom, q, K, lens, bound, k, 7, idx, workspace=ws)
+        else:
+            call = lambda: rk.rk_full_attn_select(geom, q, K, K, lens, bound, out, k, 7, idx, workspace=ws)
+        us[bound] = _us(call)
+        found[bound] = idx.clone()
+    say("  %.2f us, bound of %d: %.2f us, %.2f" % (us[n], cap, us[cap], us[cap] / us[n]))
+    if what == "topk":
+        assert torch.equal(found[n], found[cap])
+    assert us[cap] <= most * us[n]
