@@ -210,30 +210,35 @@ static inline TileForm partial_tile_form(int64_t rows, int64_t tail_rows, int64_
     return {0, 0, 0, false, 0};
 }
 
-// ... with two tiles of 16 rows to each of 8 wavefronts, 256 rows to a workgroup, two workgroups per compute unit: half the partial results to write and
-// read, for a longer chain ahead of them.  The rows since have workgroups of their own, or, where those would be the only ones beyond one
-// per unit, the slots that the small cache's rows leave (0.5 - 0.9 us, as they are requested late, against 3 for a second workgroup on some
-// of the units).  `fixed`: every row since takes the place of a selected one.
-// One workgroup per unit: instead of more than 512 of 128 rows (that are not resident, or three to a unit), or of more than 256 where
-// their results are many.  Two: where they come close to filling the units; between, some units have twice the others' work.  us per
-// launch, before (attn_split_kernel or one tile) / this, 32 heads over 8: 5120 rows 8.4 / 8.1, 6000: 9.0 / 8.3, 8150: 10.9 / 10.1, 8192 with a
-// fixed size: 12.2 / 10.4; 2 sequences of 4000: 11.0 / 10.0, of 8000 (512): 15.9 / 15.5; 4 of 2000: 11.9 / 9.9, of 3500 (448): 15.6 / 14.7; 8 of
-// 1000: 11.8 / 10.1, of 1700 (448): 16.1 / 14.7; 16 of 1000 (512): 17.0 / 16.4; 28 over 4: 9000: 10.3 / 8.4, 16000: 12.1 / 9.8, 4 of 4000: 12.6 / 9.9, 8 of
-// 1500: 9.7 / 9.2, of 2000: 12.4 / 10.1, 16 of 1000: 12.5 / 10.2; 64 over 8: 5000: 9.5 / 8.5, 4 of 2000: 12.0 / 10.1.  Left as they are, 32 over 8: 3000 rows
-// 6.7 / 8.5, 2 of 3000 (one tile: 384): 8.6 / 9.2, 8 of 1250 (320): 12.2 / 13.4, 6 of 1500 (288): 11.7 / 13.4, 8192 with rows since (264): 11.5 / 12.4.
+// ... with two tiles of 16 rows to each of 8 wavefronts, 256 rows to a workgroup: half the partial results to write and read, for a longer chain ahead of
+// them.  The rows since have workgroups of their own, or, where those would be the only ones beyond one per unit, the slots that the small cache's
+// rows leave (0.5 - 0.9 us, as they are requested late, against 3 for a second workgroup on some of the units), up to half of all.  `fixed`: every row since
+// takes the place of a selected one.
+// All K rows are requested before the lengths are known, and a workgroup's rows are the same ones however many there are: a sequence that holds fewer than K
+// costs the same, where attn_split_kernel reads and shares out what is there.  (Waiting for the lengths cost full caches 10 % and did not make up
+// for it: the workgroups left over are those of half the dies.)  So, as a ratio of the time of what was there before (one tile, or attn_split_kernel), with
+// K rows / with half of them:
+//   one workgroup per unit, where one tile is not resident in two: from 5 to a pair on 0.73 - 1.0 / 0.83 - 1.05, 4 to a pair 0.87 - 0.95 / 0.99 - 1.14 (groups of
+//     8: 1.02 / 1.13), 2 to a pair 0.98 / 1.10, one 1.03 / 0.98.  us per launch in a captured graph: 32 heads over 8, 8192 rows with a fixed size 10.5 / 9.5, 4 sequences
+//     of 2000 8.9 / 8.3, 8 of 1000 9.2 / 8.5; 28 over 4, 9000 9.0 / 7.5, 16000 10.1 / 8.0, 4 of 4000 10.3 / 8.4, 8 of 2000 10.1 / 8.5, 16 of 1000 10.0 / 8.7; 64
+//     over 8, 4 of 2000 9.7 / 8.4;
+//   ... and where one tile is: 1.0 / 1.02; groups of 4, more than 45 x 128 rows, more than three quarters of the units 0.94 - 0.98 / 1.02 (6000: 7.4 / 7.3 us);
+//   two per unit: 0.96 / 1.42 (up to 1.6); (max, sum) pairs over up to 24 pairs, which attn_split_kernel is slow with, 0.71 - 0.79 / 1.07 - 1.25 (48 over
+//     8, 3 of 5000: 19.4 / 13.7 us).
 static inline TileForm two_tile_form(int64_t rows, int64_t tail_rows, int64_t problems, int G, bool fixed) {
     const TileForm none{0, 0, 0, false, 0};
     const bool exact = G > 4 && problems > 16;
     const int64_t all = fixed ? (rows > tail_rows ? rows : tail_rows) : rows + tail_rows;
-    const int64_t nch = (rows + 255) / 256, ones = (rows + 127) / 128, one_total = (ones + (tail_rows + 127) / 128) * problems;
+    const int64_t nch = (rows + 255) / 256;
     int64_t tail = (tail_rows + 255) / 256;
     if (nch == 0 || tail == 0) return none;
-    if ((nch + tail) * problems > kComputeUnits && all <= nch * 256) tail = 0;
+    if ((nch + tail) * problems > kComputeUnits && all <= nch * 256 && 2 * tail_rows <= nch * 256) tail = 0;
     const int64_t total = (nch + tail) * problems;
     if (nch > kMergeChunks || nch + tail > (exact ? kTileExactChunks : kTagSlots) || total > 2 * kComputeUnits) return none;
-    if (exact && nch + tail <= 3 && (G == 8 || problems >= (G > 5 ? 128 : 192))) return none;      // (see partial_tile_form)
-    const bool better = total <= kComputeUnits ? one_total > 2 * kComputeUnits || (one_total > kComputeUnits && ones >= (G > 4 ? 12 : 40))
-                                               : one_total > 2 * kComputeUnits && 8 * total >= 7 * 2 * kComputeUnits;
+    const TileForm one = partial_tile_form(rows, tail_rows, problems, G, false);
+    const bool resident = one.waves != 0 && (one.nch + one.tail) * problems <= 2 * kComputeUnits;
+    const bool better = total > kComputeUnits ? exact && problems <= 24 && !resident && 8 * total >= 7 * 2 * kComputeUnits
+                        : resident ? G == 4 && rows > 45 * 128 && 4 * total > 3 * kComputeUnits : nch >= (G == 8 ? 5 : 4);
     return better ? TileForm{8, (int)nch, (int)tail, exact, 2} : none;
 }
 

@@ -17,9 +17,9 @@
 // of 16 bytes per head and partial result instead of 44, and twice the partial results (K = 2048: 12.0 MB per launch against 9.8
 // with attn_split_kernel, 8.4 needed), which is one reason why more than two workgroups per unit are better off there.
 //
-// Longer small caches and batches: two tiles to a wavefront (two_tile_form has the figures).  16 sequences of 1024 or one of 8192 rows are 33 to 67 MB,
-// which take 5.5 and 11 us to arrive; half as many partial results is what is gained, with P's lanes beyond the group left out of LDS so that two
-// workgroups of 256 rows fit a compute unit.
+// Longer small caches and batches: two tiles to a wavefront (two_tile_form has the figures).  8 sequences of 1000 or one of 8192 rows are 33 MB, which take
+// 5.5 us to arrive; half as many partial results is what is gained, with P's lanes beyond the group left out of LDS so that two workgroups of 256 rows
+// fit a compute unit.
 #include "rk_tile.h"
 
 namespace rk {

@@ -495,7 +495,8 @@ TILE_EDGES = [("k1", 4, 8, 1, 4, 0, [(900, 3)]), ("k16_17_g1", 1, 3, 17, 4, 0, [
 # cache's, where that ends inside a tile, at its edge, at a wavefront's and a workgroup's; cached rows fewer than K; up to 64 results.
 TILE_EDGES += [("two_own_tail", 4, 8, 6000, 11, 0, [(6000, 11)]), ("two_inside_8150", 4, 8, 8150, 40, 0, [(8190, 40)]), ("two_inside_fixed", 4, 8, 8192, 300, 1, [(8200, 300)]),
                ("two_inside_fixed_17", 4, 8, 8192, 20, 1, [(8200, 17)]), ("two_batch", 4, 8, 2000, 48, 0, [(2100, 48), (1999, 16), (1008, 33), (0, 7)]), ("two_batch_fixed", 3, 8, 2048, 32, 1, [(2100, 32), (2048, 31), (1000, 0), (5, 16)]),
-               ("two_512", 4, 8, 1700, 9, 0, [(1690 + 10 * b, 9 - b) for b in range(8)]), ("two_g7_64_results", 7, 4, 16000, 250, 0, [(16010, 250)]), ("two_exact_g8", 8, 8, 1900, 60, 0, [(1900, 60), (1800, 59), (40, 1), (3000, 0)]),
+               ("two_exact_g5_24_results", 5, 4, 6100, 9, 0, [(6100, 9), (3000, 2), (6109, 0), (6090, 8), (100, 1)]), ("two_exact_g7_own_tail", 7, 4, 5880, 9, 0, [(5880 + b, 9 - b) for b in range(5)]),
+               ("batch_1700", 4, 8, 1700, 9, 0, [(1690 + 10 * b, 9 - b) for b in range(8)]), ("two_g7_64_results", 7, 4, 16000, 250, 0, [(16010, 250)]), ("two_exact_g8", 8, 8, 1900, 60, 0, [(1900, 60), (1800, 59), (40, 1), (3000, 0)]),
                ("two_exact_g5_fixed", 5, 8, 1536, 9, 1, [(1600, 9 - b) for b in range(5)]), ("two_g1", 1, 8, 4000, 30, 0, [(4000, 30), (100, 30)])]
 
 

@@ -261,7 +261,12 @@ def test_two_tile_form_bounds_and_measured_choices(table):
             assert ntail * 256 >= tail or (ntail == 0 and nch * 256 >= (max(rows, tail) if fixed else rows + tail))
     assert got[(8192, 8, 11, 4, 1)] == (32, 0) and got[(8192, 8, 11, 4, 0)] == (0, 0)
     assert got[(8150, 8, 11, 4, 0)] == (32, 0) and got[(6000, 8, 11, 4, 0)] == (24, 1)
-    assert got[(2000, 32, 11, 4, 0)] == (8, 0) and got[(1000, 128, 11, 4, 0)] == (4, 0) and got[(3000, 8, 11, 4, 0)] == (0, 0)
+    assert got[(2000, 32, 11, 4, 0)] == (8, 0) and got[(1000, 64, 11, 4, 0)] == (4, 0) and got[(3000, 8, 11, 4, 0)] == (0, 0)
+    # where sequences that hold fewer rows than K, or few of the rows since, cost more than full ones gain: two workgroups to a unit, few of them
+    # to a pair, one tile to a wavefront resident
+    assert got[(1000, 128, 11, 4, 0)] == (0, 0) and got[(1700, 64, 11, 4, 0)] == (0, 0) and got[(8150, 16, 11, 4, 0)] == (0, 0)
+    assert got[(256, 128, 1, 4, 1)] == (0, 0) and got[(256, 128, 257, 8, 0)] == (0, 0) and got[(500, 128, 11, 4, 0)] == (0, 0)
+    assert got[(4000, 8, 11, 5, 0)] == (0, 0) and got[(8150, 4, 11, 5, 0)] == (0, 0) and got[(1000, 64, 11, 8, 0)] == (0, 0)
 
 
 def test_selection_parts_are_resident_at_once(table):
