@@ -3,6 +3,8 @@ arguments on the host before anything is launched (no GPU needed)."""
 import ctypes as C
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -202,3 +204,42 @@ def test_chunk_policy_host_logic():
     # beyond 256 chunks of 128 rows the partial area stops growing; only the pooled scores (one
     # row per KV head) and the raw scores (one row per query head) grow
     assert big - small == (8 + 32) * (64 * 512 * 3) * 4
+
+
+def test_package_is_complete_without_the_marshalling_extension():
+    """_rkbind.so only saves the host time: without it the package imports, says so, and every call goes through binding.py."""
+    code = """
+import importlib.abc, sys, warnings
+class Missing(importlib.abc.MetaPathFinder):
+    def find_spec(self, name, path, target=None):
+        if name.endswith("._rkbind"):
+            raise ImportError("no module named " + name)
+sys.meta_path.insert(0, Missing())
+with warnings.catch_warnings(record=True) as said:
+    warnings.simplefilter("always")
+    import paper_2411_05787_amd as rk
+assert any("marshalled in Python" in str(w.message) for w in said)
+for name in ("rk_partial_attn", "rk_partial_attn_fixed", "rk_gather_small_kv", "rk_h2o_step", "rk_full_attn"):
+    assert getattr(rk.binding._native, name)(1, 2, 3) is None
+try:
+    rk.rk_gather_small_kv(rk.Geom(1, 4, 1, 128, 1.0), None, None, None, 1, None, None)
+except (ValueError, AttributeError):
+    print("refused", rk.version())
+"""
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and r.stdout.startswith("refused"), r.stderr[-2000:]
+
+
+@pytest.mark.parametrize("commands", [(["false"], ["true"]), (["true"], ["false"]), (["no-such-compiler"], ["true"]), None], ids=["compile", "link", "no_compiler", "no_torch"])
+def test_library_is_built_where_the_extension_cannot_be(commands, tmp_path, monkeypatch, capsys):
+    """A marshalling extension that does not build is said, does not stop the build, and leaves no older one behind."""
+    from paper_2411_05787_amd import build
+    old = tmp_path / "_rkbind.so"
+    old.write_bytes(b"of another library")
+    monkeypatch.setattr(build, "BIND", str(old))
+    if commands is None:
+        monkeypatch.setitem(sys.modules, "torch", None)       # not importable
+    else:
+        monkeypatch.setattr(build, "bind_commands", lambda obj: commands)
+    build.build_bind(str(tmp_path / "rk_bind.o"))
+    assert not old.exists() and "rk_bind.cpp was not built" in capsys.readouterr().err
