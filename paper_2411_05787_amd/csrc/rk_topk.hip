@@ -86,16 +86,20 @@ void pool_hist_kernel(const float* __restrict__ weights, int64_t w_stride, const
     const float* wg = weights + ((int64_t)b * Hq + (int64_t)g * G) * w_stride;
     const int span = TILE + 2 * half;
     constexpr int R = (TILE + RK_MAX_POOL_W - 1 + 255) / 256;
-    // The heads' weights of every round, all requested together.  us per call of rk_topk_select, a round at a time (18 registers) / as it is (86), 32 heads over 8: 16
-    // rows of 32768 33.4 / 29.9, 4 of 131072 34.2 / 32.6, 16 of 131072 96.8 / 76.8.  Ahead of the length they gained nothing (24.2 at one row of 131072 either way),
-    // and all of it was lost where max_len is a bound far above it: 65536 of 1048576: 34.7 / 19.3.
+    // The heads' weights of every round, all requested together: a head's row is a buffer, what lies outside [0, len) reads as zero (a branch per load made the
+    // compiler wait for one before the next).  us per call of rk_topk_select, a round at a time behind branches / as it is, 32 heads over 8: 16 rows of 32768
+    // 33.4 / 28.7, 4 of 131072 34.2 / 31.6, 16 of 131072 96.8 / 76.7, one 24.2 / 23.5.  Ahead of the length they gained nothing (24.3), and all of it was lost where
+    // max_len is a bound far above it: 65536 of 1048576: 34.6 / 18.2.
     float w[R][RK_MAX_GROUP];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int i = r * 256 + threadIdx.x, j = j0 - half + i;
-        const bool in = i < span && j >= 0 && j < len;
+    for (int gi = 0; gi < RK_MAX_GROUP; ++gi) {
+        if (gi >= G) break;
+        const __amdgpu_buffer_rsrc_t row = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(wg + (int64_t)gi * w_stride), 0, len * 4, 0x00020000);
 #pragma unroll
-        for (int gi = 0; gi < RK_MAX_GROUP; ++gi) w[r][gi] = in && gi < G ? wg[(int64_t)gi * w_stride + j] : 0.f;
+        for (int r = 0; r < R; ++r) {
+            const int i = r * 256 + threadIdx.x;
+            w[r][gi] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(row, i < span ? (j0 - half + i) * 4 : -4, 0, 0));
+        }
     }
     for (int i = threadIdx.x; i < kHistBins; i += 256) sH[i] = 0;
 #pragma unroll
