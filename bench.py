@@ -443,7 +443,7 @@ def run_workload(args, workload, light):
     partial_bytes = 2 * Hkv * D * 2 * (sel_rows + recent_rows)
     partial_us = graph_us(partial_call, reps=8)
     p_traffic, p_source = profile_traffic(w.name, "partial_attn")
-    roofline_partial = {"bound": "hbm", "kernel": "rk::partial_tile_kernel<%d, *, false, *, *>, or rk::attn_split_kernel<%d, 4, false, true, ...> over longer or more small caches (rk_partial_attn)" % (w.group, w.group),
+    roofline_partial = {"bound": "hbm", "kernel": "rk::partial_tile_kernel<%d, *, false, *, *, *>, or rk::attn_split_kernel<%d, 4, false, true, ...> over longer or more small caches (rk_partial_attn)" % (w.group, w.group),
                         "achieved": round(partial_bytes / (partial_us * 1e-6) / 1e9, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                         "frac": round(partial_bytes / (partial_us * 1e-6) / 1e9 / HBM_PEAK_GBPS, 4),
                         "traffic": p_traffic, "traffic_source": p_source, "avg_launch_us": round(partial_us, 2),

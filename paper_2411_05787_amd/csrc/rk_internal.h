@@ -184,7 +184,7 @@ constexpr int kTagRegionRows = kTagSlots * (kD / 2);   // rows per head of a pai
 // 7.4 / 5.1 / 5.9, 4096: 7.4 / 6.0 / 6.3, 8192: 9.9 / - / 8.5; 2 sequences of 2048: 8.7 / 7.9 / 7.9, of 4096: 11.2 / - / 11.4; 4 of 1024:
 // 9.3 / 7.8 / 8.2, of 2048: 12.3 / 16.8 / 11.1, of 2048 and 28 over 4: 10.1 / 9.3 / 8.8; 8 of 1024: 12.1 / 13.8 / 11.1; 16 of 512:
 // 12.2 / 14.1 / 10.8, of 1024: 17.7 / 22.9 / 19.0.
-struct TileForm { int waves, nch, tail; bool exact; int tiles; };
+struct TileForm { int waves, nch, tail; bool exact; int tiles; bool late; };
 // exact: partial results weighed by (max, sum) pairs (rk_attn_common.h): groups beyond 4 over more than 16 pairs, which have no tagged form in
 // attn_split_kernel and kept such pairs before they came here; a lane of a wavefront each, and the region has room for 65 rows of each.  us per launch, attn_split_kernel with
 // pairs / this kernel with a lambda / with pairs: 28 heads over 4, 6 sequences of K = 512: 8.5 / 5.2 / 5.4, of 2048: 11.2 / 7.7 / 7.7, 8 of 512:
@@ -205,41 +205,39 @@ static inline TileForm partial_tile_form(int64_t rows, int64_t tail_rows, int64_
         if (nch > kMergeChunks || nch + tail > (exact ? kTileExactChunks : kTagSlots)) continue;
         if (waves == 4 ? nch * problems <= kComputeUnits && total <= 2 * kComputeUnits
                        : total <= 2 * kComputeUnits || (G <= 4 && total <= 3 * kComputeUnits && nch <= 20))
-            return {waves, (int)nch, (int)tail, exact, 1};
+            return {waves, (int)nch, (int)tail, exact, 1, false};
     }
-    return {0, 0, 0, false, 0};
+    return {0, 0, 0, false, 0, false};
 }
 
 // ... with two tiles of 16 rows to each of 8 wavefronts, 256 rows to a workgroup: half the partial results to write and read, for a longer chain ahead of
 // them.  The rows since have workgroups of their own, or, where those would be the only ones beyond one per unit, the slots that the small cache's
-// rows leave (0.5 - 0.9 us, as they are requested late, against 3 for a second workgroup on some of the units), up to half of all.  `fixed`: every row since
-// takes the place of a selected one.
-// All K rows are requested before the lengths are known, and a workgroup's rows are the same ones however many there are: a sequence that holds fewer than K
-// costs the same, where attn_split_kernel reads and shares out what is there.  (Waiting for the lengths cost full caches 10 % and did not make up
-// for it: the workgroups left over are those of half the dies.)  So, as a ratio of the time of what was there before (one tile, or attn_split_kernel), with
-// K rows / with half of them:
-//   one workgroup per unit, where one tile is not resident in two: from 5 to a pair on 0.73 - 1.0 / 0.83 - 1.05, 4 to a pair 0.87 - 0.95 / 0.99 - 1.14 (groups of
-//     8: 1.02 / 1.13), 2 to a pair 0.98 / 1.10, one 1.03 / 0.98.  us per launch in a captured graph: 32 heads over 8, 8192 rows with a fixed size 10.5 / 9.5, 4 sequences
-//     of 2000 8.9 / 8.3, 8 of 1000 9.2 / 8.5; 28 over 4, 9000 9.0 / 7.5, 16000 10.1 / 8.0, 4 of 4000 10.3 / 8.4, 8 of 2000 10.1 / 8.5, 16 of 1000 10.0 / 8.7; 64
-//     over 8, 4 of 2000 9.7 / 8.4;
-//   ... and where one tile is: 1.0 / 1.02; groups of 4, more than 45 x 128 rows, more than three quarters of the units 0.94 - 0.98 / 1.02 (6000: 7.4 / 7.3 us);
-//   two per unit: 0.96 / 1.42 (up to 1.6); (max, sum) pairs over up to 24 pairs, which attn_split_kernel is slow with, 0.71 - 0.79 / 1.07 - 1.25 (48 over
-//     8, 3 of 5000: 19.4 / 13.7 us).
+// rows leave (0.5 - 0.9 us, as they are requested late, against 3 for a second workgroup on some of the units).  `fixed`: every row since takes the place of a
+// selected one.
+// One workgroup per unit: instead of more than 512 of 128 rows (that are not resident, or three to a unit), or of more than 256 where their results
+// are many.  All rows are requested before the lengths are known.  Two per unit, where they come close to filling the units (but for 16 pairs, which
+// attn_split_kernel does as well), are bound by memory: rows that a sequence turns out not to hold cost as much as those that it does, and whole
+// dies have none of its workgroups.  There, and where the workgroups of a pair are few or many of the rows since may be beside the small cache's, the
+// wavefronts' second tiles, the cache's second half, are requested once the lengths are known (`late`): hidden behind the first ones' traffic.
+// Time as a ratio of the form before (attn_split_kernel or one tile), rows from memory, K rows cached / half of them: one per unit 0.94 / 0.97 (one tile
+// resident), 0.87 / 0.95 (not); two per unit, all at once 0.90 - 0.95 / 1.24, late 0.92 - 0.96 / 1.0; lengths uniform up to K: 1.07 and 0.96.  us per launch, before /
+// this: 32 heads over 8, 8192 rows with a fixed size 12.1 / 10.1, 6000 9.2 / 8.5, 4 sequences of 2000 11.9 / 10.2, 8 of 1000 11.6 / 10.3; 28 over 4, 9000 10.5 / 8.7,
+// 16000 12.2 / 10.0, 4 of 4000 12.5 / 10.3, 8 of 2000 12.9 / 10.3, 16 of 1000 12.6 / 10.7; 64 over 8, 4 of 2000 12.2 / 10.3; late: 32 over 8, 12 of 1150 16.0 / 14.3; 40 over
+// 8, 5 of 3000 17.3 / 16.2; 48 over 8, 3 of 4900 21.6 / 15.9.
 static inline TileForm two_tile_form(int64_t rows, int64_t tail_rows, int64_t problems, int G, bool fixed) {
-    const TileForm none{0, 0, 0, false, 0};
+    const TileForm none{0, 0, 0, false, 0, false};
     const bool exact = G > 4 && problems > 16;
     const int64_t all = fixed ? (rows > tail_rows ? rows : tail_rows) : rows + tail_rows;
-    const int64_t nch = (rows + 255) / 256;
+    const int64_t nch = (rows + 255) / 256, ones = (rows + 127) / 128, one_total = (ones + (tail_rows + 127) / 128) * problems;
     int64_t tail = (tail_rows + 255) / 256;
-    if (nch == 0 || tail == 0) return none;
-    if ((nch + tail) * problems > kComputeUnits && all <= nch * 256 && 2 * tail_rows <= nch * 256) tail = 0;
+    if (nch < 2 || tail == 0) return none;
+    if ((nch + tail) * problems > kComputeUnits && all <= nch * 256) tail = 0;
     const int64_t total = (nch + tail) * problems;
     if (nch > kMergeChunks || nch + tail > (exact ? kTileExactChunks : kTagSlots) || total > 2 * kComputeUnits) return none;
-    const TileForm one = partial_tile_form(rows, tail_rows, problems, G, false);
-    const bool resident = one.waves != 0 && (one.nch + one.tail) * problems <= 2 * kComputeUnits;
-    const bool better = total > kComputeUnits ? exact && problems <= 24 && !resident && 8 * total >= 7 * 2 * kComputeUnits
-                        : resident ? G == 4 && rows > 45 * 128 && 4 * total > 3 * kComputeUnits : nch >= (G == 8 ? 5 : 4);
-    return better ? TileForm{8, (int)nch, (int)tail, exact, 2} : none;
+    if (exact && nch + tail <= 3 && (G == 8 || problems >= (G > 5 ? 128 : 192))) return none;      // (see partial_tile_form)
+    const bool better = total <= kComputeUnits ? one_total > 2 * kComputeUnits || (one_total > kComputeUnits && ones >= (G > 4 ? 12 : 40))
+                        : one_total > 2 * kComputeUnits && 8 * total >= 7 * 2 * kComputeUnits && nch >= (G == 8 ? 5 : 4) && 2 * tail_rows <= nch * 256 && problems != 16;
+    return better ? TileForm{8, (int)nch, (int)tail, exact, 2, total > kComputeUnits || nch <= 3 || (tail == 0 && tail_rows > 256)} : none;
 }
 
 static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -487,15 +485,15 @@ static inline int deferred_split_workgroups(const rk_geom* g, int64_t max_len) {
 // where the bound on the rows since, which the trigger's schedule lets grow, leaves no slot for a 66th result), 32 over 8: 40000, 3000: 10.4 / 8.9, 47.2 / 46.0;
 // 60000, 4096: 12.9 / 10.1, 65.9 / 65.1; 65536, 7000: 14.9 / 13.2, 78.7 / 73.6; 64 over 8, 40000, 3500: 12.0 / 10.9, 54.4 / 53.7.
 static inline TileForm test_step_form(const rk_geom* g, int64_t n_sel, int64_t max_recent, int64_t max_len) {
-    if (g->batch != 1) return {0, 0, 0, false, 0};
+    if (g->batch != 1) return {0, 0, 0, false, 0, false};
     const int64_t inside = inside_split_workgroups(g, max_len);
-    if (inside == 0 || inside * g->n_kv_heads > 2 * kComputeUnits || (g->n_kv_heads > 16 && g->n_q_heads > 4 * g->n_kv_heads)) return {0, 0, 0, false, 0};
+    if (inside == 0 || inside * g->n_kv_heads > 2 * kComputeUnits || (g->n_kv_heads > 16 && g->n_q_heads > 4 * g->n_kv_heads)) return {0, 0, 0, false, 0, false};
     for (int tiles = 1; tiles <= 2; ++tiles) {             // 64 or 128 rows to a workgroup
         const int64_t wg = 64 * tiles, nch = (n_sel + wg - 1) / wg, tail = (max_recent + wg - 1) / wg;
         if (nch <= kMergeChunks && nch + tail <= kTagSlots && (nch + tail) * g->n_kv_heads <= 2 * kComputeUnits &&
             (tiles == 2 || nch * g->n_kv_heads <= kComputeUnits)) return {4, (int)nch, (int)tail, false, tiles};
     }
-    return {0, 0, 0, false, 0};
+    return {0, 0, 0, false, 0, false};
 }
 
 // Form and split of the two passes of rk_window_select over K (see rk_window.hip): 16 T rows per wavefront and step,

@@ -17,20 +17,21 @@
 // of 16 bytes per head and partial result instead of 44, and twice the partial results (K = 2048: 12.0 MB per launch against 9.8
 // with attn_split_kernel, 8.4 needed), which is one reason why more than two workgroups per unit are better off there.
 //
-// Longer small caches and batches: two tiles to a wavefront (two_tile_form has the figures).  8 sequences of 1000 or one of 8192 rows are 33 MB, which take
-// 5.5 us to arrive; half as many partial results is what is gained, with P's lanes beyond the group left out of LDS so that two workgroups of 256 rows
-// fit a compute unit.
+// Longer small caches and batches: two tiles to a wavefront (two_tile_form has the figures).  16 sequences of 1000 or one of 8192 rows are 67 and 33 MB, which
+// take 11 and 5.5 us to arrive; half as many partial results is what is gained, with P's lanes beyond the group left out of LDS so that two workgroups of
+// 256 rows fit a compute unit.  LATE: with two per unit the second tiles' requests can wait for the lengths behind the first ones' traffic (2 % of the launch), so
+// that rows which a sequence does not hold are not read.
 #include "rk_tile.h"
 
 namespace rk {
 
 static_assert(sizeof(TileParams) == 136, "arguments");
 
-template <int G, int NW, bool TRIG, bool EXACT, int R>
+template <int G, int NW, bool TRIG, bool EXACT, int R, bool LATE>
 __global__ __launch_bounds__((NW + TRIG) * 64, 4)
 void partial_tile_kernel(const uint16_t* k1, const uint16_t* v1, int64_t s_b_and_tail, int32_t s_h, uint32_t rows_heads,
                          const int32_t* seq_lens, const int32_t* tail_start, const uint16_t* q, const TileParams p) {
-    partial_tile<G, NW, TRIG ? kTestBeside : kNoTest, EXACT, false, R>(k1, v1, s_b_and_tail, s_h, rows_heads, seq_lens, tail_start, q, p, blockIdx.x, blockIdx.y, blockIdx.z);
+    partial_tile<G, NW, TRIG ? kTestBeside : kNoTest, EXACT, false, R, 0, LATE>(k1, v1, s_b_and_tail, s_h, rows_heads, seq_lens, tail_start, q, p, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
 // The step right after a selection, with the gather in it: bound by memory, every row read and written once, where a gather writes what a second
@@ -44,12 +45,12 @@ void gather_tile_kernel(uint16_t* k1, uint16_t* v1, int64_t s_b_and_tail, int32_
     partial_tile<G, NW, kNoTest, EXACT, true>(k1, v1, s_b_and_tail, s_h, rows_heads, seq_lens, idx, q, p, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
-template <int G, int NW, bool EXACT, int R = 1>
+template <int G, int NW, bool EXACT, int R = 1, bool LATE = false>
 static int launch_g(const AttnParams& p, int batch, bool trig, const int32_t* idx, hipStream_t st) {
     const TileArgs a = tile_args(p);
     dim3 grid(p.nch + p.tail_wg, p.Hkv, batch);
     if constexpr (R > 1) {
-        hipLaunchKernelGGL((partial_tile_kernel<G, NW, false, EXACT, R>), grid, dim3(NW * 64), 0, st, p.k1, p.v1, a.s_b_and_tail, (int32_t)p.s1_h,
+        hipLaunchKernelGGL((partial_tile_kernel<G, NW, false, EXACT, R, LATE>), grid, dim3(NW * 64), 0, st, p.k1, p.v1, a.s_b_and_tail, (int32_t)p.s1_h,
                            a.rows_heads, p.seq_lens, p.tail_start, p.q, a.t);
         return launch_status();
     }
@@ -58,7 +59,7 @@ static int launch_g(const AttnParams& p, int batch, bool trig, const int32_t* id
                            a.s_b_and_tail, (int32_t)p.s1_h, a.rows_heads, p.seq_lens, idx, p.q, a.t);
         return launch_status();
     }
-    auto kernel = trig ? partial_tile_kernel<G, NW, true, EXACT, 1> : partial_tile_kernel<G, NW, false, EXACT, 1>;
+    auto kernel = trig ? partial_tile_kernel<G, NW, true, EXACT, 1, false> : partial_tile_kernel<G, NW, false, EXACT, 1, false>;
     hipLaunchKernelGGL(kernel, grid, dim3((NW + (trig ? 1 : 0)) * 64), 0, st, p.k1, p.v1, a.s_b_and_tail, (int32_t)p.s1_h, a.rows_heads,
                        p.seq_lens, p.tail_start, p.q, a.t);
     return launch_status();
@@ -69,8 +70,8 @@ static int launch_form(const AttnParams& p, int batch, const TileForm& form, boo
     if (form.tiles == 2) {
         if (trig || idx != nullptr || form.waves != 8) return RK_ERR_UNSUPPORTED;
         if constexpr (G > 4)
-            if (form.exact) return launch_g<G, 8, true, 2>(p, batch, false, nullptr, st);
-        return launch_g<G, 8, false, 2>(p, batch, false, nullptr, st);
+            if (form.exact) return form.late ? launch_g<G, 8, true, 2, true>(p, batch, false, nullptr, st) : launch_g<G, 8, true, 2>(p, batch, false, nullptr, st);
+        return form.late ? launch_g<G, 8, false, 2, true>(p, batch, false, nullptr, st) : launch_g<G, 8, false, 2>(p, batch, false, nullptr, st);
     }
     if constexpr (G > 4)
         if (form.exact) return form.waves == 4 ? launch_g<G, 4, true>(p, batch, trig, idx, st) : launch_g<G, 8, true>(p, batch, trig, idx, st);

@@ -36,16 +36,20 @@ template <int BYTES> __device__ __forceinline__ unsigned char* lds_room() {
 // selection, which takes tail_start's place among the arguments, and are written to the small cache (k1 / v1) on the way, those beyond the
 // sequence's end too; a row whose entry is no position of the full cache is the small cache's own.  No rows since.
 enum TestBy { kNoTest, kTestBeside, kTestInside };      // the test is the work of a wavefront more, or of the first one with rows
-// R: tiles of 16 rows to a wavefront, all requested at once.  Two: where the launch has no workgroups for the rows since, they
-// follow those of the small cache in the slots that are left (kTailInside); the host knows that they fit.
-template <int G, int NW, TestBy TEST, bool EXACT, bool GATHER = false, int R = 1, int ROOM = 0>
+// R: tiles of 16 rows to a wavefront.  Two: 32 rows next to each other, requested at once; or (LATE) the first tiles of all workgroups have the first half
+// of the small cache and the second ones, requested as soon as the lengths are known, the other half: a cache with few rows is read for what it holds, and by
+// every workgroup.  Where the launch has no workgroups for the rows since, they follow those of the small cache in the slots that are left
+// (kTailInside); the host knows that they fit.
+template <int G, int NW, TestBy TEST, bool EXACT, bool GATHER = false, int R = 1, int ROOM = 0, bool LATE = false>
 __device__ __forceinline__
 bool partial_tile(const uint16_t* k1, const uint16_t* v1, int64_t s_b_and_tail, int32_t s_h, uint32_t rows_heads,
                   const int32_t* seq_lens, const int32_t* tail_start, const uint16_t* q, const TileParams& p, int c, int g, int b) {
     constexpr bool TRIG = TEST != kNoTest;
     constexpr int WG = 16 * NW * R;           // rows of a workgroup
+    constexpr int STEP = LATE ? 16 * NW : WG; // rows from a workgroup's first to the next one's
     constexpr int DT = 8 / NW, KS = NW * R / 2;   // P V: tiles of 16 dims of a wavefront, steps of 32 rows
     static_assert(R == 1 || !GATHER, "not built");
+    static_assert(!LATE || (R == 2 && !TRIG), "two tiles, no test");
     // P's lanes in LDS: those beyond the group hold nothing that is used, so where there is much of it they read the others'
     constexpr int GP = R == 1 ? 16 : G <= 4 ? 4 : 8;
     constexpr int VS = kD + 8;                // LDS row stride of the V tile (272 bytes: rows spread over banks)
@@ -93,17 +97,25 @@ bool partial_tile(const uint16_t* k1, const uint16_t* v1, int64_t s_b_and_tail, 
         for (int x = 0; x < 4 * R; ++x)
             vA[x >> 2][x & 3] = __builtin_amdgcn_raw_buffer_load_b128(rv, row * (kD * 2) + v_lane + x * 4 * (kD * 2), 0, 0);
     };
-    int r_first = c * WG + w * 16 * R;
+    auto request_tile = [&](const uint16_t* k, const uint16_t* v, int rows, int row, int x) {
+        const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(k), 0, rows * (kD * 2), 0x00020000);
+        const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(v), 0, rows * (kD * 2), 0x00020000);
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) kA[x][kk] = __builtin_amdgcn_raw_buffer_load_b128(rk, row * (kD * 2) + k_lane + kk * 64, 0, 0);
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) vA[x][jj] = __builtin_amdgcn_raw_buffer_load_b128(rv, row * (kD * 2) + v_lane + jj * 4 * (kD * 2), 0, 0);
+    };
+    int r_first = c * STEP + w * (LATE ? 16 : 16 * R), step = LATE ? first_tail * STEP : 16;      // the wavefront's first row, rows to its next tile's
     // (inside: the last workgroup, which has the most of the rows since, requests nothing yet: it waits for the lengths and requests every row from
     // where it is; requested once more, those rows would come behind everybody's)
-    const bool waits = inside && c + 1 == first_tail;
+    const bool waits = !LATE && inside && c + 1 == first_tail;
     const int early = c < first_tail && !waits ? spec_rows : 0;
     // GATHER: where the rows of this lane are: row n16 of the wavefront's 16 for K, rows 4 jj + c4 for V
     int from_k = -1, from_v[4] = {-1, -1, -1, -1};
     if constexpr (GATHER) {
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(tail_start) + bg * spec_rows, 0, spec_rows * 4, 0x00020000);
         from_k = (int)__builtin_amdgcn_raw_buffer_load_b32(rs, (r_first + n16) * 4, 0, 0);
-    } else {
+    } else if constexpr (!LATE) {
         request_k(k1, early, r_first);
     }
     {                                         // (heads beyond the group read as zero)
@@ -111,7 +123,8 @@ bool partial_tile(const uint16_t* k1, const uint16_t* v1, int64_t s_b_and_tail, 
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) qa[kk] = __builtin_amdgcn_raw_buffer_load_b128(rq, k_lane + kk * 64, 0, 0);
     }
-    if constexpr (!GATHER) request_v(v1, early, r_first);
+    if constexpr (LATE) request_tile(k1, v1, early, r_first, 0);
+    else if constexpr (!GATHER) request_v(v1, early, r_first);
     asm volatile("" :: "s"(scale2), "s"(spin), "s"(out_all), "s"(counters), "s"(tag_rows), "s"(epochs),
                  "s"(k2), "s"(v2), "s"(s2_b), "s"(s2_h), "s"(p.pred_val));
     const uint32_t epoch = *(const __attribute__((address_space(4))) uint32_t*)(epochs + bg);      // (the kernel's own store comes after: a scalar load)
@@ -210,7 +223,8 @@ bool partial_tile(const uint16_t* k1, const uint16_t* v1, int64_t s_b_and_tail, 
     const int n1 = min(keep, t0), n2 = min(recent, max_rows2);
     // partial results in all (an empty sequence leaves one of no rows), this workgroup's place among them, the end of its rows
     const int n_in = inside ? n2 : 0;         // rows since in the slots behind the small cache's
-    const int n_main = inside ? max((int)((uint32_t)(n1 + n2 + WG - 1) / WG), 1) : first_tail != 0 ? max((int)((uint32_t)(n1 + WG - 1) / WG), n2 == 0 ? 1 : 0) : 0;
+    const int n_late = min((int)((uint32_t)(n1 + n_in + 16 * NW - 1) / (16 * NW)), first_tail);      // LATE: workgroups whose first tiles have rows
+    const int n_main = LATE ? max(n_late, inside || n2 == 0 ? 1 : 0) : inside ? max((int)((uint32_t)(n1 + n2 + WG - 1) / WG), 1) : first_tail != 0 ? max((int)((uint32_t)(n1 + WG - 1) / WG), n2 == 0 ? 1 : 0) : 0;
     const int n_tail = inside ? 0 : max((int)((uint32_t)(n2 + WG - 1) / WG), first_tail != 0 ? 0 : 1);
     const int nchunks = n_main + n_tail;
     const bool tail = c >= first_tail;
@@ -226,12 +240,37 @@ bool partial_tile(const uint16_t* k1, const uint16_t* v1, int64_t s_b_and_tail, 
     }
     if (tail) {
         // row r of the list lives at row t0 + r - n1 of the full cache
-        r_first += n1 - first_tail * WG;
+        if constexpr (LATE) {
+            r_first = n1 + (c - first_tail) * WG + w * 16 * R;
+            step = 16;
+        } else {
+            r_first += n1 - first_tail * WG;
+        }
         const uint64_t at = (uint64_t)s2_b * (uint32_t)b + (uint64_t)s2_h * (uint32_t)g + (uint64_t)(uint32_t)t0 * kD;
         request_k(k2 + at, n2, r_first - n1);
         request_v(v2 + at, n2, r_first - n1);
     }
-    if constexpr (R > 1) {
+    if constexpr (LATE) {
+        if (!tail) {
+            // a tile with rows since (the same for the whole wavefront): row r of the list is the small cache's, or row t0 + r - n1 of the full one; past
+            // the list's end its last row again (masked)
+            const uint64_t at = (uint64_t)s2_b * (uint32_t)b + (uint64_t)s2_h * (uint32_t)g;
+            auto request_list = [&](int x) {
+                auto row_at = [&](const uint16_t* small, const uint16_t* full, int r) {
+                    r = min(r_first + x * step + r, row1 - 1);
+                    return r < n1 ? small + (int64_t)r * kD : full + at + (int64_t)(t0 + r - n1) * kD;
+                };
+#pragma unroll
+                for (int kk = 0; kk < 4; ++kk) kA[x][kk] = *reinterpret_cast<const u32x4*>(row_at(k1, k2, n16) + c4 * 8 + kk * 32);
+#pragma unroll
+                for (int jj = 0; jj < 4; ++jj) vA[x][jj] = *reinterpret_cast<const u32x4*>(row_at(v1, v2, jj * 4 + c4) + n16 * 8);
+            };
+            auto has_since = [&](int x) { return inside && n2 > 0 && r_first + x * step < row1 && r_first + x * step + 16 > n1; };
+            if (has_since(0)) request_list(0);
+            if (has_since(1)) request_list(1);
+            else request_tile(k1, v1, n1, r_first + step, 1);
+        }
+    } else if constexpr (R > 1) {
         if (waits || (inside && n2 > 0 && r_first < row1 && r_first + 16 * R > n1)) {      // (the same for the whole wavefront)
             // row r of the list: the small cache's, or row t0 + r - n1 of the full one; past the list's end its last row again (masked)
             const uint64_t at = (uint64_t)s2_b * (uint32_t)b + (uint64_t)s2_h * (uint32_t)g;
@@ -267,7 +306,7 @@ bool partial_tile(const uint16_t* k1, const uint16_t* v1, int64_t s_b_and_tail, 
     }
     // ---- S^T = K Q^T: head n16, rows 4 c4 + i of each of the wavefront's tiles ----
     float s[R][4];
-    const bool whole = r_first + 16 * R <= row1;
+    const bool whole = r_first + (LATE ? step + 16 : 16 * R) <= row1;
 #pragma unroll
     for (int x = 0; x < R; ++x) {
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
@@ -278,7 +317,7 @@ bool partial_tile(const uint16_t* k1, const uint16_t* v1, int64_t s_b_and_tail, 
         for (int i = 0; i < 4; ++i) s[x][i] = acc[i] * scale2;
         if (!whole) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) s[x][i] = r_first + x * 16 + 4 * c4 + i < row1 ? s[x][i] : -INFINITY;
+            for (int i = 0; i < 4; ++i) s[x][i] = r_first + x * step + 4 * c4 + i < row1 ? s[x][i] : -INFINITY;
         }
     }
     float mx = fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3]));
@@ -318,7 +357,7 @@ bool partial_tile(const uint16_t* k1, const uint16_t* v1, int64_t s_b_and_tail, 
     if (!whole) {       // V rows past the end hold whatever the cache holds there, maybe NaN: P is 0 for them, but 0 * NaN is NaN
 #pragma unroll
         for (int x = 0; x < 4 * R; ++x)
-            if (r_first + x * 4 + c4 >= row1) vA[x >> 2][x & 3] = u32x4{0u, 0u, 0u, 0u};
+            if (r_first + (LATE ? (x >> 2) * step + (x & 3) * 4 : x * 4) + c4 >= row1) vA[x >> 2][x & 3] = u32x4{0u, 0u, 0u, 0u};
     }
 #pragma unroll
     for (int x = 0; x < 4 * R; ++x) *reinterpret_cast<u32x4*>(&sV[w * 16 * R + x * 4 + c4][n16 * 8]) = vA[x >> 2][x & 3];

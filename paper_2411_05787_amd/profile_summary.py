@@ -23,14 +23,14 @@ import sys
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
-# attn_split_kernel<G, NW, EMIT, TWO_SEG, LAZY, TAGGED, TRIG, EXACT>: the first kernel of a full step, and the partial step without the trigger inside (or partial_tile_kernel<G, NW, TRIG, EXACT, R>)
+# attn_split_kernel<G, NW, EMIT, TWO_SEG, LAZY, TAGGED, TRIG, EXACT>: the first kernel of a full step, and the partial step without the trigger inside (or partial_tile_kernel<G, NW, TRIG, EXACT, R, LATE>)
 FULL_KERNEL = r"attn_split_kernel<\d+, 4, true, false, false, false, false, false>"
-PARTIAL_KERNEL = r"partial_tile_kernel<\d+, \d+, false, (true|false), [12]>|attn_split_kernel<\d+, 4, false, true, false, (true|false), false, false>"
+PARTIAL_KERNEL = r"partial_tile_kernel<\d+, \d+, false, (true|false), [12], (true|false)>|attn_split_kernel<\d+, 4, false, true, false, (true|false), false, false>"
 LEGEND = [
     ("attn_split_kernel<G, 4, true, false, false, false, false, false>", "streams C_f once and emits raw scores: first kernel of rk_full_attn (weights returned) and rk_full_attn_select; rk_full_attn_scores launches it alone (the roofline measurement)"),
     ("attn_split_kernel<G, 4, true, false, false, true, false, *>", "the same with the output merged inside (tagged partial results, by slices or by the last workgroup): the one kernel of rk_full_attn_deferred and of rk_full_attn without weights over long rows; last parameter true: with the sums and the order of the merge launch"),
     ("attn_split_kernel<G, 4, true, true, false, false, false, false>", "rk_h2o_step: the policy's cache and the new token's row as two segments, scores emitted"),
-    ("partial_tile_kernel<G, NW, TRIG, EXACT, R>", "rk_partial_attn in one round of R tiles of 16 rows per wavefront; TRIG true: rk_partial_attn_triggered; EXACT true: partial results weighed by (max, sum) pairs (groups of more than 4 heads over more than 16 pairs)"),
+    ("partial_tile_kernel<G, NW, TRIG, EXACT, R, LATE>", "rk_partial_attn in one round of R tiles of 16 rows per wavefront (LATE true: the second ones requested once the lengths are known); TRIG true: rk_partial_attn_triggered; EXACT true: partial results weighed by (max, sum) pairs (groups of more than 4 heads over more than 16 pairs)"),
     ("test_step_kernel<G, EXACT, R>", "rk_decode_step_batched, a layer's step on which the trigger is tested: the partial step with the test, or the full pass, in one launch (one sequence)"),
     ("gather_tile_kernel<G, NW, EXACT>", "rk_gather_attn: the gather and the partial step over its rows in one launch"),
     ("attn_split_kernel<G, 4, false, true, false, true, false, false>", "rk_partial_attn over longer or more small caches: one launch, tagged partial results, merged by slices (every workgroup its share) or by the last workgroup"),

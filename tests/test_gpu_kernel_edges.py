@@ -495,9 +495,14 @@ TILE_EDGES = [("k1", 4, 8, 1, 4, 0, [(900, 3)]), ("k16_17_g1", 1, 3, 17, 4, 0, [
 # cache's, where that ends inside a tile, at its edge, at a wavefront's and a workgroup's; cached rows fewer than K; up to 64 results.
 TILE_EDGES += [("two_own_tail", 4, 8, 6000, 11, 0, [(6000, 11)]), ("two_inside_8150", 4, 8, 8150, 40, 0, [(8190, 40)]), ("two_inside_fixed", 4, 8, 8192, 300, 1, [(8200, 300)]),
                ("two_inside_fixed_17", 4, 8, 8192, 20, 1, [(8200, 17)]), ("two_batch", 4, 8, 2000, 48, 0, [(2100, 48), (1999, 16), (1008, 33), (0, 7)]), ("two_batch_fixed", 3, 8, 2048, 32, 1, [(2100, 32), (2048, 31), (1000, 0), (5, 16)]),
-               ("two_exact_g5_24_results", 5, 4, 6100, 9, 0, [(6100, 9), (3000, 2), (6109, 0), (6090, 8), (100, 1)]), ("two_exact_g7_own_tail", 7, 4, 5880, 9, 0, [(5880 + b, 9 - b) for b in range(5)]),
-               ("batch_1700", 4, 8, 1700, 9, 0, [(1690 + 10 * b, 9 - b) for b in range(8)]), ("two_g7_64_results", 7, 4, 16000, 250, 0, [(16010, 250)]), ("two_exact_g8", 8, 8, 1900, 60, 0, [(1900, 60), (1800, 59), (40, 1), (3000, 0)]),
+               ("two_512", 4, 8, 1700, 9, 0, [(1690 + 10 * b, 9 - b) for b in range(8)]), ("two_g7_64_results", 7, 4, 16000, 250, 0, [(16010, 250)]), ("two_exact_g8", 8, 8, 1900, 60, 0, [(1900, 60), (1800, 59), (40, 1), (3000, 0)]),
                ("two_exact_g5_fixed", 5, 8, 1536, 9, 1, [(1600, 9 - b) for b in range(5)]), ("two_g1", 1, 8, 4000, 30, 0, [(4000, 30), (100, 30)])]
+# ... their second tiles, the small cache's second half, requested once the lengths are known: rows that end in either half, at its edge and a tile's, rows
+# since in one tile, over the edge and in workgroups of their own, fewer selected rows than evicted ones.
+TILE_EDGES += [("late_halves", 4, 8, 1700, 9, 0, [(896, 0), (895, 9), (880, 9), (897, 0), (1700, 9), (0, 5), (0, 0), (17, 1)]), ("late_2_of_440", 4, 8, 440, 16, 0, [(440 - 23 * b, b) for b in range(16)]),
+               ("late_fixed_300", 4, 8, 1000, 300, 1, [(1000, 300), (900, 299), (700, 150), (512, 0), (1000, 1), (300, 300), (0, 300), (1100, 44)]),
+               ("late_exact_g5_24_results", 5, 4, 6100, 9, 0, [(6100, 9), (3000, 2), (6109, 0), (6090, 8), (100, 1)]), ("late_exact_g7_own_tail", 7, 4, 5880, 9, 0, [(5880 + b, 9 - b) for b in range(5)]),
+               ("late_g8_15", 8, 8, 3600, 20, 0, [(3600, 20), (1920, 20), (3700, 0), (1905, 17)])]
 
 
 @pytest.mark.parametrize("case", TILE_EDGES, ids=[c[0] for c in TILE_EDGES])

@@ -46,7 +46,7 @@ int main() {
     for (long r : {0L, 1L, 256L, 500L, 1000L, 1700L, 2000L, 2048L, 3000L, 4000L, 6000L, 8150L, 8181L, 8192L, 9000L, 16000L, 16384L, 20000L}) for (long p : {1L, 4L, 8L, 16L, 32L, 64L, 128L, 512L})
         for (int tail : {0, 1, 11, 256, 257, 9000}) for (int G : {1, 4, 5, 8}) for (int fixed : {0, 1}) {
             const TileForm f = two_tile_form(r, tail, p, G, fixed != 0);
-            printf("two %ld %ld %d %d %d %d %d %d %d %d\n", r, p, tail, G, fixed, f.waves, f.nch, f.tail, (int)f.exact, f.tiles);
+            printf("two %ld %ld %d %d %d %d %d %d %d %d %d\n", r, p, tail, G, fixed, f.waves, f.nch, f.tail, (int)f.exact, f.tiles, (int)f.late);
         }
     for (long p : {1L, 4L, 8L, 12L, 32L, 33L, 64L, 65L, 128L, 129L, 256L, 257L, 100000L}) printf("parts %ld %d\n", p, select_parts(p));
     for (long l : {1000L, 49151L, 49152L, 65536L, 131072L, 163840L, 196608L, 1000000L}) for (long k : {1L, 3072L, 3073L, 4097L, 8192L, 12288L, 16384L}) for (int b : {1, 2}) for (int hkv : {1, 2, 3, 4, 7}) {
@@ -253,20 +253,19 @@ def test_two_tile_form_bounds_and_measured_choices(table):
     for kind, *v in table:
         if kind != "two":
             continue
-        rows, pairs, tail, G, fixed, waves, nch, ntail, exact, tiles = map(int, v)
-        got[(rows, pairs, tail, G, fixed)] = (nch, ntail)
+        rows, pairs, tail, G, fixed, waves, nch, ntail, exact, tiles, late = map(int, v)
+        got[(rows, pairs, tail, G, fixed)] = (nch, ntail, late)
         if waves:
             assert (waves, tiles) == (8, 2) and exact == (G > 4 and pairs > 16)
             assert nch * 256 >= rows and 1 <= nch <= 64 and nch + ntail <= (64 if exact else 65) and (nch + ntail) * pairs <= 512
             assert ntail * 256 >= tail or (ntail == 0 and nch * 256 >= (max(rows, tail) if fixed else rows + tail))
-    assert got[(8192, 8, 11, 4, 1)] == (32, 0) and got[(8192, 8, 11, 4, 0)] == (0, 0)
-    assert got[(8150, 8, 11, 4, 0)] == (32, 0) and got[(6000, 8, 11, 4, 0)] == (24, 1)
-    assert got[(2000, 32, 11, 4, 0)] == (8, 0) and got[(1000, 64, 11, 4, 0)] == (4, 0) and got[(3000, 8, 11, 4, 0)] == (0, 0)
-    # where sequences that hold fewer rows than K, or few of the rows since, cost more than full ones gain: two workgroups to a unit, few of them
-    # to a pair, one tile to a wavefront resident
-    assert got[(1000, 128, 11, 4, 0)] == (0, 0) and got[(1700, 64, 11, 4, 0)] == (0, 0) and got[(8150, 16, 11, 4, 0)] == (0, 0)
-    assert got[(256, 128, 1, 4, 1)] == (0, 0) and got[(256, 128, 257, 8, 0)] == (0, 0) and got[(500, 128, 11, 4, 0)] == (0, 0)
-    assert got[(4000, 8, 11, 5, 0)] == (0, 0) and got[(8150, 4, 11, 5, 0)] == (0, 0) and got[(1000, 64, 11, 8, 0)] == (0, 0)
+            assert late == ((nch + ntail) * pairs > 256 or nch <= 3 or (ntail == 0 and tail > 256))      # (two per unit are bound by memory)
+    assert got[(8192, 8, 11, 4, 1)] == (32, 0, 0) and got[(8192, 8, 11, 4, 0)] == (0, 0, 0)
+    assert got[(8150, 8, 11, 4, 0)] == (32, 0, 0) and got[(6000, 8, 11, 4, 0)] == (24, 1, 0)
+    assert got[(2000, 32, 11, 4, 0)] == (8, 0, 0) and got[(1000, 128, 11, 4, 0)] == (4, 0, 1) and got[(3000, 8, 11, 4, 0)] == (0, 0, 0)
+    assert got[(1700, 64, 11, 4, 0)] == (7, 0, 1) and got[(500, 128, 11, 4, 0)] == (2, 0, 1) and got[(1000, 64, 257, 4, 1)] == (4, 0, 1)
+    # no gain, or less than short rows lose: one workgroup to a pair, 16 pairs at two per unit, few to a pair of groups of 8
+    assert got[(256, 128, 1, 4, 1)] == (0, 0, 0) and got[(8150, 16, 11, 4, 0)] == (0, 0, 0) and got[(1000, 128, 11, 8, 0)] == (0, 0, 0)
 
 
 def test_selection_parts_are_resident_at_once(table):
