@@ -485,16 +485,16 @@ TILE_EDGES = [("k1", 4, 8, 1, 4, 0, [(900, 3)]), ("k16_17_g1", 1, 3, 17, 4, 0, [
               ("k64_g5", 5, 2, 64, 8, 0, [(64, 8), (63, 7), (0, 2), (0, 0)]), ("k65_evict", 4, 4, 65, 40, 1, [(900, 40), (900, 1), (900, 0)]),
               ("k256_evicts_all", 2, 2, 256, 300, 1, [(900, 300), (900, 256), (900, 129)]), ("none_selected", 4, 2, 0, 200, 0, [(900, 200), (500, 0), (0, 129)]),
               ("k1280_20_chunks", 3, 2, 1280, 5, 0, [(1279, 5), (2000, 0)]), ("k2560_g7", 7, 2, 2560, 5, 0, [(2560, 5)]), ("k2561_u4", 4, 4, 2561, 1, 0, [(3000, 1)]),
-              ("k4096_65_chunks_g7", 7, 4, 4096, 64, 0, [(4096, 64)]), ("k4096_8w", 4, 8, 4096, 5, 0, [(4096, 5)]), ("k4100_8w_g6", 6, 8, 4100, 128, 0, [(4100, 128)]),
-              ("k8192_65_chunks_8w_g8", 8, 4, 8192, 100, 0, [(8192, 100)]), ("k8192_split", 4, 8, 8192, 5, 0, [(8192, 5)]),
+              ("k4096_65_chunks_g7", 7, 4, 4096, 64, 0, [(4096, 64)]), ("k4096_8w", 4, 8, 4096, 5, 0, [(4096, 5)]), ("two_17_g6", 6, 8, 4100, 128, 0, [(4100, 128)]),
+              ("two_32_g8", 8, 4, 8192, 100, 0, [(8192, 100)]), ("k7900_63_chunks_8w_g7", 7, 4, 7900, 9, 0, [(7900, 9)]), ("k3900_8w_g8", 8, 8, 3900, 5, 0, [(3900, 5)]), ("k8192_split", 4, 8, 8192, 5, 0, [(8192, 5)]),
               ("batch", 4, 8, 700, 9, 0, [(700 + 37 * b, b) for b in range(9)]), ("batch_3_per_cu", 4, 8, 512, 9, 0, [(600, 9 - b % 4) for b in range(16)]),
               # groups beyond 4 over more than 16 pairs: partial results with maximum and sum apart
               ("exact_g7", 7, 4, 300, 9, 0, [(700 + 37 * b, b) for b in range(6)]), ("exact_g8_8w", 8, 8, 500, 9, 0, [(505, 9 - b) for b in range(7)]),
-              ("exact_g5_23_chunks", 5, 1, 2800, 5, 1, [(2790 + b, 5) for b in range(17)]), ("exact_g6_empty", 6, 9, 70, 70, 0, [(0, 0), (0, 70), (200, 0)])]
-# Two tiles to a wavefront (test_launch_sizes asserts which take that form): rows since in workgroups of their own and in the slots behind the small
+              ("two_exact_g5_11", 5, 1, 2800, 5, 1, [(2790 + b, 5) for b in range(17)]), ("exact_g5_25_chunks", 5, 4, 3070, 5, 0, [(3065 + b, 5 - b) for b in range(5)]), ("exact_g6_empty", 6, 9, 70, 70, 0, [(0, 0), (0, 70), (200, 0)])]
+# Two tiles to a wavefront (test_launch_sizes has the form that each of the list takes): rows since in workgroups of their own and in the slots behind the small
 # cache's, where that ends inside a tile, at its edge, at a wavefront's and a workgroup's; cached rows fewer than K; up to 64 results.
 TILE_EDGES += [("two_own_tail", 4, 8, 6000, 11, 0, [(6000, 11)]), ("two_inside_8150", 4, 8, 8150, 40, 0, [(8190, 40)]), ("two_inside_fixed", 4, 8, 8192, 300, 1, [(8200, 300)]),
-               ("two_inside_fixed_17", 4, 8, 8192, 20, 1, [(8200, 17)]), ("two_batch", 4, 8, 2000, 48, 0, [(2100, 48), (1999, 16), (1008, 33), (0, 7)]), ("two_batch_fixed", 3, 8, 2048, 32, 1, [(2100, 32), (2048, 31), (1000, 0), (5, 16)]),
+               ("two_inside_fixed_17", 4, 8, 8192, 20, 1, [(8200, 17)]), ("two_inside_fixed_256", 4, 8, 8192, 256, 1, [(8200, 256)]), ("two_batch", 4, 8, 2000, 48, 0, [(2100, 48), (1999, 16), (1008, 33), (0, 7)]), ("two_batch_fixed", 3, 8, 2048, 32, 1, [(2100, 32), (2048, 31), (1000, 0), (5, 16)]),
                ("two_512", 4, 8, 1700, 9, 0, [(1690 + 10 * b, 9 - b) for b in range(8)]), ("two_g7_64_results", 7, 4, 16000, 250, 0, [(16010, 250)]), ("two_exact_g8", 8, 8, 1900, 60, 0, [(1900, 60), (1800, 59), (40, 1), (3000, 0)]),
                ("two_exact_g5_fixed", 5, 8, 1536, 9, 1, [(1600, 9 - b) for b in range(5)]), ("two_g1", 1, 8, 4000, 30, 0, [(4000, 30), (100, 30)])]
 # ... their second tiles, the small cache's second half, requested once the lengths are known: rows that end in either half, at its edge and a tile's, rows
@@ -703,19 +703,19 @@ def test_test_step_in_one_launch(rk, case):
 # (heads per group, KV heads, sequences, rows, K): tiles of 4 and 8 wavefronts, their last one partly filled, pairs and log-sum-exps as weights, more
 # ranks than rows, and more rows than are resident at once (two launches).
 GATHER_ATTN = [(4, 8, 1, 9000, 8192), (4, 8, 1, 3000, 2048), (4, 8, 1, 3000, 65), (7, 4, 1, 5000, 4097), (1, 8, 1, 500, 1), (3, 3, 2, 700, 127), (8, 4, 1, 90, 200),
-               (4, 8, 4, 2100, 1025), (7, 4, 6, 1300, 512), (5, 8, 3, 1000, 300), (2, 8, 5, 3000, 2500), (6, 8, 16, 700, 350)]
+               (4, 8, 4, 2100, 1025), (7, 4, 6, 1300, 512), (5, 8, 3, 1000, 300), (2, 8, 5, 3000, 2500), (6, 8, 16, 700, 350), (8, 8, 4, 1200, 900)]
 
 
 @pytest.mark.parametrize("case", GATHER_ATTN, ids=["g%d_%dx%d_n%d_k%d" % (c[0], c[2], c[1], c[3], c[4]) for c in GATHER_ATTN])
 def test_gather_inside_the_step(rk, case):
-    """Small caches and tail_start bit for bit as the gather leaves them, rows without an entry untouched; outputs against fp64 (one bf16 step
+    """Small caches (strided, of more than K rows) and tail_start bit for bit as the gather leaves them, rows without an entry untouched; outputs against fp64 (one bf16 step
     of the larger value and 4e-6); a sequence that the predicate leaves out stays as it is."""
     G, Hkv, B, n, k = case
     say("gather inside", case)
     Hq, cap = G * Hkv, n + 6
     g = torch.Generator(device="cuda").manual_seed(n + k)
     rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
-    K, V, q = rnd(B, Hkv, cap, 128), rnd(B, Hkv, cap, 128), rnd(B, Hq, 128)
+    K, V, q = rnd(B, Hkv + 1, cap + 3, 128)[:, 1:, :cap], rnd(B, Hkv + 1, cap + 3, 128)[:, 1:, :cap], rnd(B, Hq, 128)      # heads and rows that are others'
     lens = torch.tensor([n - 37 * (b % 2) for b in range(B)], dtype=torch.int32, device="cuda")
     idx = torch.full((B, Hkv, k), -1, dtype=torch.int32, device="cuda")
     for b in range(B):
@@ -728,15 +728,15 @@ def test_gather_inside_the_step(rk, case):
         p = pred if use_pred else None
         rk.rk_debug_set_slice_spin(spin)
         try:
-            state = [[torch.full((B, Hkv, k, 128), 3.0, dtype=torch.bfloat16, device="cuda") for _ in range(2)] +
-                     [torch.full((B,), 5, dtype=torch.int32, device="cuda")] for _ in range(2)]
+            small = [[torch.full((B, Hkv + 2, k + 5, 128), 3.0, dtype=torch.bfloat16, device="cuda") for _ in range(2)] for _ in range(2)]
+            state = [[t[:, 1:-1] for t in pair] + [torch.full((B,), 5, dtype=torch.int32, device="cuda")] for pair in small]
             rk.rk_gather_small_kv(geom, K, V, idx, k, state[0][0], state[0][1], seq_lens=lens, tail_start=state[0][2], pred=p, pred_val=1)
             out = torch.full((B, Hq, 128), 7.0, dtype=torch.bfloat16, device="cuda")
             rk.rk_gather_attn(geom, q, K, V, idx, k, state[1][0], state[1][1], lens, state[1][2], out, pred=p, pred_val=1, workspace=ws)
             torch.cuda.synchronize()
         finally:
             rk.rk_debug_set_slice_spin(256)
-        for a, b in zip(*state):
+        for a, b in zip(small[0] + state[0][2:], small[1] + state[1][2:]):
             assert torch.equal(a, b)
         for b in range(B):
             if use_pred and b == 1:
@@ -751,9 +751,20 @@ def test_gather_inside_the_step(rk, case):
             assert (d <= torch.maximum(out[b].double().abs(), want.abs()) * 2.0 ** -7 + 4e-6).all(), (b, float(d.max()))
 
 
-@pytest.mark.parametrize("form", ["plain", "strided", "subclass", "numpy_int", "stream", "wrong_shape", "wrong_type", "not_contiguous", "short_cache", "not_a_state"])
+# What the C++ checks leave to binding.py: the calls, in order gather, partial, fixed, partial with a predicate, full, full with lse and a predicate, H2O
+MARSHALLED = {"plain": "", "strided": "", "parameter": "", "stream": "", "subclass": "partial fixed pred full lse h2o", "numpy_int": "gather partial fixed pred",
+              "wrong_shape": "partial fixed pred full lse h2o", "wrong_type": "partial fixed pred full lse h2o", "not_contiguous": "partial fixed pred full lse h2o",
+              "short_cache": "gather partial fixed pred", "not_a_state": "h2o"}
+
+
+class _Sub(torch.Tensor):
+    pass
+
+
+@pytest.mark.parametrize("form", list(MARSHALLED))
 def test_calls_marshalled_in_cpp_take_what_python_takes(rk, form, monkeypatch):
-    """The same results, or the same exception, whether the arguments go through the C++ checks or through those of binding.py alone."""
+    """The same results, or the same exception, whether the arguments go through the C++ checks or through those of binding.py alone; the common case goes
+    through C++, and what is not does not."""
     B, G, Hkv, n, k = 2, 4, 3, 300, 64
     g = torch.Generator(device="cuda").manual_seed(5)
     rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
@@ -764,12 +775,14 @@ def test_calls_marshalled_in_cpp_take_what_python_takes(rk, form, monkeypatch):
     n_sel, stream = k, None
     if form == "strided":
         K, V = rnd(B, Hkv + 2, n + 5, 128)[:, 1:-1, :n], rnd(B, Hkv + 2, n + 5, 128)[:, 1:-1, :n]
-    elif form == "subclass":
+    elif form == "parameter":
         q = torch.nn.Parameter(q, requires_grad=False)
+    elif form == "subclass":
+        q = q.as_subclass(_Sub)
     elif form == "numpy_int":
         n_sel = np.int64(k)
     elif form == "stream":
-        stream = torch.cuda.current_stream()
+        stream = torch.cuda.Stream()
     elif form == "wrong_shape":
         q = q[:, :-1].contiguous()
     elif form == "wrong_type":
@@ -789,26 +802,42 @@ def test_calls_marshalled_in_cpp_take_what_python_takes(rk, form, monkeypatch):
         state = rk.h2o_state(geom, *cache, total, pos, n_rows, n_attend)
         if form == "not_a_state":
             state = bytes(state)           # as long as the structure, but not one
-        outs = [torch.zeros(B, G * Hkv, 128, dtype=torch.bfloat16, device="cuda") for _ in range(4)]
-        res = []
-        for call in (lambda: rk.rk_gather_small_kv(geom, K, V, idx, n_sel, sK, sV, seq_lens=lens, tail_start=tail.clone(), stream=stream),
-                     lambda: rk.rk_partial_attn(geom, q, sK, sV, n_sel, K, V, tail, lens, 16, outs[0], workspace=ws, stream=stream),
-                     lambda: rk.rk_partial_attn_fixed(geom, q, sK, sV, n_sel, K, V, tail, lens, 16, outs[1], workspace=ws, stream=stream),
-                     lambda: rk.rk_full_attn(geom, q, K, V, lens, n, outs[2], workspace=ws, stream=stream),
-                     lambda: rk.rk_h2o_step(geom, state, q, new[0], new[1], lens, n - 1, n // 2, outs[3], workspace=ws, stream=stream)):
+        outs = [torch.zeros(B, G * Hkv, 128, dtype=torch.bfloat16, device="cuda") for _ in range(6)]
+        pred, lse, dropped = torch.tensor([1, 0], dtype=torch.int32, device="cuda"), torch.zeros(B, G * Hkv, device="cuda"), torch.full((B, Hkv), -9, dtype=torch.int32, device="cuda")
+        if stream is not None:
+            stream.wait_stream(torch.cuda.current_stream())
+        res = {}
+        for name, call in (("gather", lambda: rk.rk_gather_small_kv(geom, K, V, idx, n_sel, sK, sV, seq_lens=lens, tail_start=tail.clone() if stream is None else None, stream=stream)),
+                           ("partial", lambda: rk.rk_partial_attn(geom, q, sK, sV, n_sel, K, V, tail, lens, 16, outs[0], workspace=ws, stream=stream)),
+                           ("fixed", lambda: rk.rk_partial_attn_fixed(geom, q, sK, sV, n_sel, K, V, tail, lens, 16, outs[1], workspace=ws, stream=stream)),
+                           ("pred", lambda: rk.rk_partial_attn(geom, q, sK, sV, n_sel, K, V, tail, lens, 16, outs[2], pred=pred, pred_val=1, workspace=ws, stream=stream)),
+                           ("full", lambda: rk.rk_full_attn(geom, q, K, V, lens, n, outs[3], workspace=ws, stream=stream)),
+                           ("lse", lambda: rk.rk_full_attn(geom, q, K, V, lens, n, outs[4], lse=lse, pred=pred, pred_val=0, workspace=ws, stream=stream)),
+                           ("h2o", lambda: rk.rk_h2o_step(geom, state, q, new[0], new[1], lens, n - 1, n // 2, outs[5], dropped=dropped, workspace=ws, stream=stream))):
             try:
                 call()
-                res.append(None)
+                res[name] = None
             except (ValueError, ctypes.ArgumentError) as e:
-                res.append(str(e))
+                res[name] = str(e)
         torch.cuda.synchronize()
-        return res, [sK, sV, *outs, total, pos, *cache, n_rows]
+        return res, [sK, sV, *outs, lse, dropped, total, pos, *cache, n_rows]
 
+    taken = []
+
+    def watched(call):
+        def f(*a):
+            taken.append(call(*a) is not None)
+            return 0 if taken[-1] else None                   # (every call that C++ takes here succeeds)
+        return f
+    names = ("rk_gather_small_kv", "rk_partial_attn", "rk_partial_attn_fixed", "rk_full_attn", "rk_h2o_step")
+    native = rk.binding._native
+    monkeypatch.setattr(rk.binding, "_native", type("watched", (), {name: staticmethod(watched(getattr(native, name))) for name in names}))
     by_cpp = run()
-    monkeypatch.setattr(rk.binding, "_native", type("none", (), {name: staticmethod(lambda *a: None) for name in dir(rk.binding._native)}))
+    monkeypatch.setattr(rk.binding, "_native", type("none", (), {name: staticmethod(lambda *a: None) for name in names}))
     by_python = run()
     assert by_cpp[0] == by_python[0], (by_cpp[0], by_python[0])
-    assert any(by_cpp[0]) == (form in ("wrong_shape", "wrong_type", "not_contiguous", "short_cache", "not_a_state"))
+    assert [name for name, t in zip(by_cpp[0], taken) if not t] == MARSHALLED[form].split() and len(taken) == len(by_cpp[0])
+    assert any(by_cpp[0].values()) == (form in ("wrong_shape", "wrong_type", "not_contiguous", "short_cache", "not_a_state"))
     for a, b in zip(by_cpp[1], by_python[1]):
         assert torch.equal(a, b)
 

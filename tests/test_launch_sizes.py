@@ -380,3 +380,64 @@ def test_h2o_split_bounds(table):
             assert n == emit, (rows, b, hkv)
         seen += 1
     assert seen == 9 * 4 * 3
+
+
+# What the lists of test_gpu_kernel_edges.py mean to reach: (wavefronts, tiles to each, workgroups of the small cache and of the rows since, (max, sum)
+# pairs, late), no wavefronts: attn_split_kernel; the trigger's without tiles and late; (tiles, workgroups) of the test steps in one launch; (wavefronts,
+# workgroups, pairs) of the gather inside the step, no wavefronts: two launches.
+FORMS = {
+    "tile": {
+        "k1": (4, 1, 1, 1, 0, 0), "k16_17_g1": (4, 1, 1, 1, 0, 0), "k63_g8": (4, 1, 1, 2, 0, 0), "k64_g5": (4, 1, 1, 1, 0, 0),
+        "k65_evict": (4, 1, 2, 1, 0, 0), "k256_evicts_all": (4, 1, 4, 5, 0, 0), "none_selected": (4, 1, 0, 4, 0, 0),
+        "k1280_20_chunks": (4, 1, 20, 1, 0, 0), "k2560_g7": (4, 1, 40, 1, 0, 0), "k2561_u4": (4, 1, 41, 1, 0, 0),
+        "k4096_65_chunks_g7": (4, 1, 64, 1, 0, 0), "k4096_8w": (8, 1, 32, 1, 0, 0), "two_17_g6": (8, 2, 17, 1, 0, 0),
+        "two_32_g8": (8, 2, 32, 1, 0, 0), "k7900_63_chunks_8w_g7": (8, 1, 62, 1, 0, 0), "k3900_8w_g8": (8, 1, 31, 1, 0, 0),
+        "k8192_split": (0, 0, 0, 0, 0, 0), "batch": (8, 1, 6, 1, 0, 0), "batch_3_per_cu": (8, 1, 4, 1, 0, 0), "exact_g7": (4, 1, 5, 1, 1, 0),
+        "exact_g8_8w": (8, 1, 4, 1, 1, 0), "two_exact_g5_11": (8, 2, 11, 1, 1, 0), "exact_g5_25_chunks": (8, 1, 24, 1, 1, 0),
+        "exact_g6_empty": (4, 1, 2, 2, 1, 0), "two_own_tail": (8, 2, 24, 1, 0, 0), "two_inside_8150": (8, 2, 32, 0, 0, 0),
+        "two_inside_fixed": (8, 2, 32, 0, 0, 1), "two_inside_fixed_17": (8, 2, 32, 0, 0, 0), "two_inside_fixed_256": (8, 2, 32, 0, 0, 0),
+        "two_batch": (8, 2, 8, 0, 0, 0), "two_batch_fixed": (8, 2, 8, 0, 0, 0), "two_512": (8, 2, 7, 0, 0, 1),
+        "two_g7_64_results": (8, 2, 63, 1, 0, 0), "two_exact_g8": (8, 2, 8, 0, 1, 0), "two_exact_g5_fixed": (8, 2, 6, 0, 1, 0),
+        "two_g1": (8, 2, 16, 0, 0, 0), "late_halves": (8, 2, 7, 0, 0, 1), "late_2_of_440": (8, 2, 2, 0, 0, 1), "late_fixed_300": (8, 2, 4, 0, 0, 1),
+        "late_exact_g5_24_results": (8, 2, 24, 0, 1, 1), "late_exact_g7_own_tail": (8, 2, 23, 1, 1, 1), "late_g8_15": (8, 2, 15, 0, 1, 1)},
+    "triggered": {
+        "tile_4w": (4, 32, 1, 0), "tile_4w_g8": (4, 11, 1, 0), "tile_8w": (8, 8, 1, 0), "tile_8w_g7": (8, 9, 1, 0), "tile_8w_exact_g8": (8, 6, 1, 1),
+        "split_tagged_long": (0, 0, 0, 0), "split_tagged_batch": (0, 0, 0, 0), "split_tagged_g8": (0, 0, 0, 0), "split_ticketed_g7": (0, 0, 0, 0)},
+    "test_step": [
+        (1, 32, 1), (1, 32, 1), (1, 64, 1), (1, 11, 1), (1, 2, 1), (1, 4, 1), (1, 1, 1), (1, 1, 1), (1, 8, 1), (1, 16, 1), (1, 1, 1), (1, 32, 3),
+        (2, 32, 1), (2, 32, 2), (2, 24, 1), (2, 32, 1), (2, 63, 1)],
+    "gather": [
+        (8, 64, 0), (4, 32, 0), (4, 2, 0), (8, 33, 0), (4, 1, 0), (4, 2, 0), (4, 4, 0), (8, 9, 0), (4, 8, 1), (4, 5, 1), (0, 0, 0), (0, 0, 0),
+        (8, 8, 1)]}
+
+
+def test_edge_cases_reach_the_forms_they_are_for(tmp_path):
+    import test_gpu_kernel_edges as edges
+    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    if not os.path.exists(hipcc):
+        pytest.skip("hipcc not found")
+    body = []
+    for name, G, Hkv, k, recent, evict, seqs in edges.TILE_EDGES:
+        pairs = len(seqs) * Hkv
+        body.append("f = two_tile_form(%d, %d, %d, %d, %d); if (f.waves == 0) f = partial_tile_form(%d, %d, %d, %d, false);" % (k, recent, pairs, G, evict, k, recent, pairs, G))
+        body.append('printf("%d %d %d %d %d %d\\n", f.waves, f.tiles, f.nch, f.tail, (int)f.exact, (int)f.late);')
+    for G, Hkv, B, k, recent, fixed in edges.TRIGGERED.values():
+        body.append("f = partial_tile_form(%d, %d, %d, %d, true);" % (k, recent, B * Hkv, G))
+        body.append('printf("%d %d %d %d\\n", f.waves, f.nch, f.tail, (int)f.exact);')
+    for G, Hkv, n, k, recent, fixed in edges.TEST_STEPS:
+        body.append("{ rk_geom g{1, %d, %d, 128, 1.f}; f = test_step_form(&g, %d, %d, %d); }" % (G * Hkv, Hkv, k, max(recent, 1), n))
+        body.append('printf("%d %d %d\\n", f.tiles, f.nch, f.tail);')
+    for G, Hkv, B, n, k in edges.GATHER_ATTN:
+        body.append("f = partial_tile_form(%d, 0, %d, %d, false);" % (k, B * Hkv, G))
+        body.append('printf("%d %d %d\\n", f.waves, f.nch, (int)f.exact);')
+    src, exe = tmp_path / "forms.cpp", tmp_path / "forms"
+    src.write_text('#include "rk_internal.h"\n#include <cstdio>\nusing namespace rk;\nint main() {\n    TileForm f;\n%s\n    return 0;\n}\n' % "\n".join(body))
+    r = subprocess.run([hipcc, "-O1", "-std=c++17", "-I", CSRC, "-x", "hip", "--offload-arch=gfx950", str(src), "-o", str(exe)],
+                       capture_output=True, text=True, timeout=600)
+    assert r.returncode == 0, r.stderr[-2000:]
+    got = [tuple(map(int, ln.split())) for ln in subprocess.run([str(exe)], capture_output=True, text=True, timeout=60).stdout.splitlines()]
+    assert list(FORMS["tile"]) == [c[0] for c in edges.TILE_EDGES] and list(FORMS["triggered"]) == list(edges.TRIGGERED)
+    names = [*FORMS["tile"], *FORMS["triggered"], *edges.TEST_STEPS, *edges.GATHER_ATTN]
+    want = [*FORMS["tile"].values(), *FORMS["triggered"].values(), *FORMS["test_step"], *FORMS["gather"]]
+    assert len(got) == len(want) == len(names)
+    assert [(n, g) for n, g, w in zip(names, got, want) if g != w] == []
