@@ -6,7 +6,8 @@
 // stride every S-th step is a full step for all layers.  With the query-similarity trigger every
 // S-th step tests, per layer and sequence, the head-averaged query against the one of the last
 // full step; both branches are enqueued and the device predicate written by the test switches
-// one of them off per sequence, so nothing is read back to the host.
+// one of them off per sequence, so nothing is read back to the host (rk_decode_step_batched over one
+// sequence: one launch that goes one way or the other, test_step_stage).
 #include "rk_internal.h"
 
 using namespace rk;
